@@ -81,7 +81,7 @@ WORKLOADS = {
                  desc="cfg3's model width with head dimension 256: B1 H16 d256 S262144 N8, bf16, q_dev 7 "
                       "(matrix-core kernels, two 128-column halves)"),
     "cfg1": dict(B=1, H=1, d=64, S=256, N=4, q_dev=-1, dtype="f32",
-                 desc="Tiny: B1 H1 d64 S256 N4 (64-token shards), fp32, all 16 steps (generic fp32 kernels; "
+                 desc="Tiny: B1 H1 d64 S256 N4 (64-token shards), fp32, all 16 steps (fp32 matrix-core kernels; "
                       "launch-bound)"),
     "tiny": dict(B=1, H=2, d=128, S=4096, N=4, q_dev=-1, desc="B1 H2 d128 S4096 N4, bf16 (quick check)"),
 }
@@ -354,13 +354,13 @@ def main():
     traffic = measured_traffic(args.workload) if plain else {}
     c_rows = w["S"] // N
 
-    f32 = w.get("dtype") == "f32"      # the generic kernels: fp32 FMA arithmetic, vector ALU peak
-    peak, bound = (157.3, "alu") if f32 else (PEAK_BF16_TFLOPS, "mfma")
+    f32 = w.get("dtype") == "f32"      # fp32 matrix-core kernels and peak
+    peak, bound = (157.3, "mfma") if f32 else (PEAK_BF16_TFLOPS, "mfma")
 
     def roof(rows, family, alg_bytes):
         name, kernels = FAMILIES[family]
         if f32:
-            name = name.replace("_mfma_kernel", "_generic_kernel").replace("bwd_dkdv", "bwd_dkv")
+            name = name.replace("_mfma_kernel", "_f32_kernel")
         live = [r for r in rows if r["ms"] > 0]
         tot_ms = sum(r["ms"] for r in live)
         ach = sum(r["tflops"] * r["ms"] for r in live) / max(1e-9, tot_ms)

@@ -15,7 +15,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libstriped_attn.so")
 OBJ_DIR = os.path.join(ROOT, "_build")
 
-SOURCES = ["api.hip", "permute.hip", "elementwise.hip", "generic_step.hip", "fwd_mfma.hip",
+SOURCES = ["api.hip", "permute.hip", "elementwise.hip", "f32_step.hip", "fwd_mfma.hip",
            "bwd_mfma.hip"]
 
 # packed fp32 VALU forms are switched off on purpose for the test machines

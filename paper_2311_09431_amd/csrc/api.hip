@@ -128,7 +128,7 @@ int step_fwd(const void* q, const void* k, const void* v, float* o, float* lse, 
     }
     if (a.kind == sa::MASK_EMPTY) return SA_OK;   // entirely masked block: nothing to launch
     hipError_t e = sa::fwd_mfma_supported(a, s->dtype) ? sa::launch_fwd_mfma(a, st)
-                                                       : sa::launch_fwd_generic(a, s->dtype, st);
+                                                       : sa::launch_fwd_f32(a, s->dtype, st);
     return e == hipSuccess ? SA_OK : SA_ERR_HIP;
 }
 
@@ -142,7 +142,7 @@ int step_bwd(const void* q, const void* k, const void* v, const void* dout, cons
     a.q = q; a.k = k; a.v = v; a.dout = dout; a.lse = const_cast<float*>(lse); a.delta = delta;
     a.dq = dq; a.dk = dk; a.dv = dv;
     hipError_t e = sa::bwd_mfma_supported(a, s->dtype) ? sa::launch_bwd_mfma(a, st)
-                                                       : sa::launch_bwd_generic(a, s->dtype, st);
+                                                       : sa::launch_bwd_f32(a, s->dtype, st);
     return e == hipSuccess ? SA_OK : SA_ERR_HIP;
 }
 

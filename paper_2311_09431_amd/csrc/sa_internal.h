@@ -61,8 +61,8 @@ hipError_t launch_zero_f32(float* p, const sa_shape& s, hipStream_t st);
 hipError_t launch_rope(const void* x, void* y, const int32_t* pos, int64_t pos_stride_b, const sa_shape& s,
                        float base, bool inverse, hipStream_t st);
 
-hipError_t launch_fwd_generic(const StepArgs& a, int dtype, hipStream_t st);
-hipError_t launch_bwd_generic(const StepArgs& a, int dtype, hipStream_t st);
+hipError_t launch_fwd_f32(const StepArgs& a, int dtype, hipStream_t st);
+hipError_t launch_bwd_f32(const StepArgs& a, int dtype, hipStream_t st);
 bool fwd_mfma_supported(const StepArgs& a, int dtype);
 bool fwd_mfma_rope_supported(const StepArgs& a, int dtype);
 hipError_t launch_fwd_mfma(const StepArgs& a, hipStream_t st);
