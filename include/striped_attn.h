@@ -193,6 +193,9 @@ int sa_attn_step_bwd(const void* q, const void* k, const void* v, const void* do
  * (stripe-permuted for SA_STRIPED), LSE is [B, H, N*c]; `shape` describes one
  * shard (c rows) and the strides of the full tensors.  O and LSE are initialised
  * here.  q_dev_only >= 0 plays only that device's N steps (one device's share).
+ * With step_ms NULL the steps are folded into one launch that keeps the running state
+ * in registers from the first shard to the last (same result up to the rounding of the
+ * state between steps, deterministic).
  * step_ms: NULL, or a HOST array of N*N floats receiving the duration of step
  * (round i, device j) at [i*N + j] in milliseconds (steps not played: 0); when
  * non-NULL the call synchronises the stream before returning.
@@ -203,8 +206,8 @@ int sa_ring_fwd(const void* Q, const void* K, const void* V, float* O, float* LS
 
 /*
  * Ring driver, backward: delta = rowsum(dO * O) for the played devices, then the
- * same schedule calling sa_attn_step_bwd.  dQ, dK, dV are full fp32 tensors,
- * zeroed here.  With q_dev_only >= 0 only that device's steps are played (dQ is
+ * same schedule calling sa_attn_step_bwd (folded like the forward when step_ms is NULL).
+ * dQ, dK, dV are full fp32 tensors, zeroed here.  With q_dev_only >= 0 only that device's steps are played (dQ is
  * then complete for that device; dK/dV hold only its contributions).
  */
 int sa_ring_bwd(const void* Q, const void* K, const void* V, const void* dO, const float* O,

@@ -65,21 +65,10 @@ int check_step(int q_dev, int kv_dev, int N, int layout) {
     return SA_OK;
 }
 
-// GetMask(j, k) in local indices (Sec. 2.2, 2.3): query a = original position
-// j*c + a (contiguous) or a*N + j (striped); key b likewise with k.  Allowed iff
-// key position <= query position, which reduces to b <= a - off.
-void classify(int q_dev, int kv_dev, int layout, int* kind, int* off) {
-    *off = 0;
-    if (layout == SA_CONTIGUOUS) {
-        *kind = q_dev < kv_dev ? sa::MASK_EMPTY : (q_dev == kv_dev ? sa::MASK_TRI : sa::MASK_FULL);
-    } else {
-        *kind = sa::MASK_TRI;
-        *off = kv_dev > q_dev ? 1 : 0;
-    }
-}
-
-StepArgs make_args(const sa_shape* s) {
+// the block of query device q_dev and key device kv_dev
+StepArgs make_args(const sa_shape* s, int q_dev = 0, int kv_dev = 0, int layout = SA_STRIPED) {
     StepArgs a{};
+    a.layout = layout; a.q_dev = q_dev; a.n_q = 1; a.kv_dev = kv_dev; a.n_kv = 1;
     a.B = s->B; a.H = s->H; a.c = s->c; a.d = s->d;
     a.stride_b = s->stride_b; a.stride_h = s->stride_h;
     a.stat_stride_b = s->stat_stride_b; a.stat_stride_h = s->stat_stride_h;
@@ -118,15 +107,14 @@ int check_skip(const sa_shape* s, int bq, int bk) {
 int step_fwd(const void* q, const void* k, const void* v, float* o, float* lse, int q_dev, int kv_dev,
              int layout, const sa_shape* s, int bq, int bk, hipStream_t st, const int32_t* q_pos = nullptr,
              int64_t pos_stride_b = 0, float rope_base = 0.f) {
-    StepArgs a = make_args(s);
-    classify(q_dev, kv_dev, layout, &a.kind, &a.off);
+    StepArgs a = make_args(s, q_dev, kv_dev, layout);
     a.q = q; a.k = k; a.v = v; a.o = o; a.lse = lse;
     a.skip_bq = bq; a.skip_bk = bk;
     if (q_pos) {
         if (!sa::fwd_mfma_rope_supported(a, s->dtype)) return SA_ERR_SHAPE;
         a.q_pos = q_pos; a.pos_stride_b = pos_stride_b; a.rope_log2_base = log2((double)rope_base);
     }
-    if (a.kind == sa::MASK_EMPTY) return SA_OK;   // entirely masked block: nothing to launch
+    if (sa::block_kind(q_dev, kv_dev, layout) == sa::MASK_EMPTY) return SA_OK;   // nothing to launch
     hipError_t e = sa::fwd_mfma_supported(a, s->dtype) ? sa::launch_fwd_mfma(a, st)
                                                        : sa::launch_fwd_f32(a, s->dtype, st);
     return e == hipSuccess ? SA_OK : SA_ERR_HIP;
@@ -135,15 +123,21 @@ int step_fwd(const void* q, const void* k, const void* v, float* o, float* lse, 
 int step_bwd(const void* q, const void* k, const void* v, const void* dout, const float* lse,
              const float* delta, float* dq, float* dk, float* dv, int q_dev, int kv_dev, int layout,
              const sa_shape* s, int bq, int bk, hipStream_t st) {
-    StepArgs a = make_args(s);
-    classify(q_dev, kv_dev, layout, &a.kind, &a.off);
-    if (a.kind == sa::MASK_EMPTY) return SA_OK;
+    StepArgs a = make_args(s, q_dev, kv_dev, layout);
+    if (sa::block_kind(q_dev, kv_dev, layout) == sa::MASK_EMPTY) return SA_OK;
     a.skip_bq = bq; a.skip_bk = bk;
     a.q = q; a.k = k; a.v = v; a.dout = dout; a.lse = const_cast<float*>(lse); a.delta = delta;
     a.dq = dq; a.dk = dk; a.dv = dv;
     hipError_t e = sa::bwd_mfma_supported(a, s->dtype) ? sa::launch_bwd_mfma(a, st)
                                                        : sa::launch_bwd_f32(a, s->dtype, st);
     return e == hipSuccess ? SA_OK : SA_ERR_HIP;
+}
+
+// The ring drivers without per-step timings: one launch per kernel for all blocks of the played
+// devices, where the kernels' grids and the row counts stay within 31 bits (else, and when the
+// caller wants each step's time, one launch per block and kernel).
+bool one_launch(const StepArgs& a, int dtype, int N) {
+    return (int64_t)N * a.c < (int64_t(1) << 31) && sa::fwd_mfma_supported(a, dtype) && sa::bwd_mfma_supported(a, dtype);
 }
 
 size_t elt_size(int dtype) { return dtype == SA_F32 ? 4 : 2; }
@@ -249,7 +243,7 @@ int sa_bwd_preprocess(const float* o, const void* dout, float* delta, const sa_s
     if (!o || !dout || !delta) return SA_ERR_NULL;
     if (int e = check_shape(shape)) return e;
     if (!aligned16(o) || !aligned16(dout)) return SA_ERR_ALIGN;
-    return sa::launch_bwd_preprocess(o, dout, delta, *shape, (hipStream_t)stream) == hipSuccess
+    return sa::launch_bwd_preprocess(o, dout, delta, *shape, shape->c, (hipStream_t)stream) == hipSuccess
                ? SA_OK : SA_ERR_HIP;
 }
 
@@ -293,6 +287,14 @@ int sa_ring_fwd_tiled(const void* Q, const void* K, const void* V, float* O, flo
     auto kv_at = [&](const void* p, int dev) { return (const char*)p + (size_t)dev * kv_shard * es; };
     if (step_ms) for (int i = 0; i < N * N; ++i) step_ms[i] = 0.f;
     const int j0 = q_dev_only >= 0 ? q_dev_only : 0, j1 = q_dev_only >= 0 ? q_dev_only + 1 : N;
+    StepArgs all = make_args(shape, j0, 0, layout);
+    all.n_q = j1 - j0; all.n_kv = N; all.q_shard = shard; all.kv_shard = kv_shard; all.fresh = true;
+    if (!step_ms && one_launch(all, shape->dtype, N)) {
+        all.q = in_at(Q, j0); all.k = K; all.v = V;
+        all.o = O + j0 * shard; all.lse = LSE + (int64_t)j0 * shape->c;
+        all.skip_bq = skip_bq; all.skip_bk = skip_bk;
+        return sa::launch_fwd_mfma(all, st) == hipSuccess ? SA_OK : SA_ERR_HIP;
+    }
     for (int j = j0; j < j1; ++j)
         if (sa::launch_state_init(O + j * shard, LSE + (int64_t)j * shape->c, *shape, st) != hipSuccess)
             return SA_ERR_HIP;
@@ -339,15 +341,35 @@ int sa_ring_bwd_tiled(const void* Q, const void* K, const void* V, const void* d
     const int j0 = q_dev_only >= 0 ? q_dev_only : 0, j1 = q_dev_only >= 0 ? q_dev_only + 1 : N;
     sa_shape kv_shape = *shape;          // dK and dV as a tensor family of their own
     kv_shape.H = kvg.heads; kv_shape.stride_b = kvg.sb; kv_shape.stride_h = kvg.sh; kv_shape.stride_s = kvg.ss;
-    for (int dev = 0; dev < N; ++dev) {
-        if (sa::launch_zero_f32(dQ + dev * shard, *shape, st) != hipSuccess ||
-            sa::launch_zero_f32(dK + dev * kv_shard, kv_shape, st) != hipSuccess ||
-            sa::launch_zero_f32(dV + dev * kv_shard, kv_shape, st) != hipSuccess)
+    // rows first .. first + n - 1 of the devices' shards, as one tensor
+    auto zero = [&](float* p, int64_t shard_elts, const sa_shape& s, int first, int n) {
+        return n <= 0 || sa::launch_zero_f32(p + first * shard_elts, s, (int64_t)n * shape->c, st) == hipSuccess;
+    };
+    StepArgs all = make_args(shape, j0, 0, layout);
+    all.n_q = j1 - j0; all.q_shard = shard; all.kv_shard = kv_shard; all.fresh = true;
+    // key shards that some played device sees; contiguous layout: none further on than the last
+    all.n_kv = layout == SA_STRIPED ? N : j1;
+    if (!step_ms && one_launch(all, shape->dtype, N)) {
+        all.q = in_at(Q, j0); all.k = K; all.v = V; all.dout = in_at(dO, j0);
+        all.lse = const_cast<float*>(LSE) + (int64_t)j0 * shape->c;
+        all.delta = delta + (int64_t)j0 * shape->c;
+        all.dq = dQ + j0 * shard; all.dk = dK; all.dv = dV;
+        all.skip_bq = skip_bq; all.skip_bk = skip_bk;
+        // what the kernels do not write: other devices' dQ, dK / dV of shards no played device sees
+        if (!zero(dQ, shard, *shape, 0, j0) || !zero(dQ, shard, *shape, j1, N - j1) ||
+            !zero(dK, kv_shard, kv_shape, all.n_kv, N - all.n_kv) ||
+            !zero(dV, kv_shard, kv_shape, all.n_kv, N - all.n_kv) ||
+            sa::launch_bwd_preprocess(O + j0 * shard, in_at(dO, j0), delta + (int64_t)j0 * shape->c, *shape,
+                                      (int64_t)(j1 - j0) * shape->c, st) != hipSuccess)
             return SA_ERR_HIP;
+        return sa::launch_bwd_mfma(all, st) == hipSuccess ? SA_OK : SA_ERR_HIP;
     }
+    if (!zero(dQ, shard, *shape, 0, N) || !zero(dK, kv_shard, kv_shape, 0, N) ||
+        !zero(dV, kv_shard, kv_shape, 0, N))
+        return SA_ERR_HIP;
     for (int j = j0; j < j1; ++j)
         if (sa::launch_bwd_preprocess(O + j * shard, in_at(dO, j), delta + (int64_t)j * shape->c, *shape,
-                                      st) != hipSuccess)
+                                      shape->c, st) != hipSuccess)
             return SA_ERR_HIP;
     StepTimer timer(step_ms != nullptr);
     for (int i = 0; i < N; ++i) {
@@ -375,17 +397,14 @@ int sa_ring_bwd(const void* Q, const void* K, const void* V, const void* dO, con
 int sa_step_mask(int32_t q_dev, int32_t kv_dev, int32_t N, int32_t layout, int32_t* kind, int32_t* off) {
     if (!kind || !off) return SA_ERR_NULL;
     if (int e = check_step(q_dev, kv_dev, N, layout)) return e;
-    int kd, of;
-    classify(q_dev, kv_dev, layout, &kd, &of);
-    *kind = kd;
-    *off = of;
+    *kind = sa::block_kind(q_dev, kv_dev, layout);
+    *off = sa::block_off(q_dev, kv_dev, layout);
     return SA_OK;
 }
 
 int64_t sa_step_pairs(int32_t q_dev, int32_t kv_dev, int32_t N, int32_t layout, int64_t c) {
     if (check_step(q_dev, kv_dev, N, layout) || c < 0) return -1;
-    int kind, off;
-    classify(q_dev, kv_dev, layout, &kind, &off);
+    const int kind = sa::block_kind(q_dev, kv_dev, layout), off = sa::block_off(q_dev, kv_dev, layout);
     if (kind == sa::MASK_EMPTY) return 0;
     if (kind == sa::MASK_FULL) return c * c;
     return off ? c * (c - 1) / 2 : c * (c + 1) / 2;
@@ -396,8 +415,7 @@ int sa_step_tiles(int32_t q_dev, int32_t kv_dev, int32_t N, int32_t layout, int6
     if (!computed || !total) return SA_ERR_NULL;
     if (int e = check_step(q_dev, kv_dev, N, layout)) return e;
     if (c < 1 || skip_bq < 1 || skip_bk < 1 || c % skip_bq || c % skip_bk) return SA_ERR_SHAPE;
-    int kind, off;
-    classify(q_dev, kv_dev, layout, &kind, &off);
+    const int kind = sa::block_kind(q_dev, kv_dev, layout), off = sa::block_off(q_dev, kv_dev, layout);
     const int64_t nq = c / skip_bq, nk = c / skip_bk;
     *total = nq * nk;
     if (kind == sa::MASK_EMPTY) { *computed = 0; return SA_OK; }

@@ -125,9 +125,9 @@ __device__ inline void dq_step(f32x16& s_cur, f32x16& dp_cur, f32x16& s_next, f3
 // last key (c - 1) for a full block.  RAGGED (c not a multiple of 128): loads of rows beyond
 // the shard are clamped, their results are not stored, keys beyond it come in as zero rows
 // and are removed by the mask.
-// (FULL is a template argument rather than a launch argument so that profiler traces name
-// triangular and full launches apart; the code is the same.)
-template <bool RAGGED, bool FULL, int DP, bool PART>
+// WALK: one block, or (WALK_RING) the blocks of several key shards one after the other, as in
+// the forward kernel: dQ stays in registers over all of them.
+template <bool RAGGED, int WALK, int DP, bool PART>
 __global__ void __launch_bounds__(256, DP > 128 ? 1 : 2)
 bwd_dq_mfma_kernel(StepArgs p, int n_tiles) {
     constexpr int NH = halves_of(DP), KS = ksteps_of(DP), MB = halves_of(DP) * blocks_of(DP);      // k-steps per half, column blocks
@@ -139,38 +139,52 @@ bwd_dq_mfma_kernel(StepArgs p, int n_tiles) {
 
     const int tid = threadIdx.x, lane = tid & 63, n = lane & 31, h = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);      // wave-uniform, kept scalar
-    int rank, bh;
-    decode_block<true>((int)blockIdx.x, n_tiles, p.B * p.H, rank, bh);
+    constexpr bool RING = WALK == WALK_RING;
+    int rank, bh, dev = p.q_dev;
+    decode_block<true>((int)blockIdx.x, RING ? n_tiles * p.n_q : n_tiles, p.B * p.H, rank, bh);
+    if (RING) {
+        int dev_rank;
+        decode_rank(rank, n_tiles, p.n_q, p.layout, rank, dev_rank);
+        dev += p.n_q - 1 - dev_rank;
+    }
     const int qt = n_tiles - 1 - rank;      // heaviest query tiles first
     const int b = bh / p.H, hd = bh - b * p.H;
-    const int64_t base = b * p.stride_b + hd * p.stride_h;
+    const int64_t base = b * p.stride_b + hd * p.stride_h + (RING ? (dev - p.q_dev) * p.q_shard : 0);
     // key/value head of this query head's group (the same head when H_kv == H)
     const int64_t kv_base = b * p.kv_stride_b + (hd / (p.H / p.H_kv)) * p.kv_stride_h;
-    const int64_t sbase = b * p.stat_stride_b + hd * p.stat_stride_h;
+    const int64_t sbase = b * p.stat_stride_b + hd * p.stat_stride_h + (RING ? (int64_t)(dev - p.q_dev) * p.c : 0);
     const __bf16* Q = (const __bf16*)p.q + base;
     const int d = p.d;                                 // d <= DP, zero-padded to DP columns
     const int64_t ss = p.stride_s;                     // elements between consecutive rows of Q, dO, dQ
     const int pitch = 2 * (int)p.kv_stride_s;          // bytes between consecutive rows of K and V
     const int tile_pitch = DT_ROWS * pitch;            // bytes between 64-row tiles in global memory
-    const dt_rsrc Kr = dt_make_rsrc((const __bf16*)p.k + kv_base, p.c, pitch, d);
-    const dt_rsrc Vr = dt_make_rsrc((const __bf16*)p.v + kv_base, p.c, pitch, d);
+    dt_rsrc Kr = dt_make_rsrc((const __bf16*)p.k + kv_base, p.c, pitch, d);
+    dt_rsrc Vr = dt_make_rsrc((const __bf16*)p.v + kv_base, p.c, pitch, d);
     const __bf16* G = (const __bf16*)p.dout + base;
     float* DQ = p.dq + base;
 
     const int q0 = qt * BM, a_own = q0 + 32 * wave + n;
     const bool row_ok = !RAGGED || a_own < p.c;
     const int a = RAGGED ? min(a_own, p.c - 1) : a_own;      // the row this lane loads
-    constexpr bool full_block = FULL;                // every key allowed: the mask limit is the last key
-    // all four wavefronts walk the 2 n_kt sub-tiles of the workgroup (at most three are
-    // entirely masked for a wavefront); the element mask runs on the last four only
-    const int n_kt_fine = full_block ? 2 * n_tiles : (q0 + BM) / DT_ROWS;
-    int n_kt = n_kt_fine;
-    if (!full_block && p.skip_bq > 0) {       // emulated coarse skipping, as in the forward kernel
-        const int q_hi = (q0 / p.skip_bq + 1) * p.skip_bq - 1;
-        n_kt = min(p.c, ((q_hi - p.off) / p.skip_bk + 1) * p.skip_bk) / DT_ROWS;
-    }
-    // sub-tile v: allowed iff 8 (r/4) + r%4 <= mask_base - 32 v
-    const int mask_base = (full_block ? p.c - 1 : a_own - p.off) - 4 * h;
+    // The block being walked, as in the forward kernel: key shard kv, its 64-key tiles, those of
+    // the walk without emulated coarse skipping (the last two carry the element mask) and the
+    // mask: sub-tile v is allowed iff 8 (r/4) + r%4 <= mask_base - 32 v.  All four wavefronts
+    // walk the 2 n_kt sub-tiles (at most three are entirely masked for a wavefront).
+    int kv = p.kv_dev, n_kt, n_kt_fine, mask_base;
+    auto enter_block = [&]() {
+        const bool full = RING ? block_kind(dev, kv, p.layout) == MASK_FULL : WALK == WALK_FULL;
+        const int off = block_off(dev, kv, p.layout);
+        n_kt = n_kt_fine = full ? 2 * n_tiles : (q0 + BM) / DT_ROWS;
+        if (!full && p.skip_bq > 0) {       // emulated coarse skipping, as in the forward kernel
+            const int q_hi = (q0 / p.skip_bq + 1) * p.skip_bq - 1;
+            n_kt = min(p.c, ((q_hi - off) / p.skip_bk + 1) * p.skip_bk) / DT_ROWS;
+        }
+        mask_base = (full ? p.c - 1 : a_own - off) - 4 * h;
+    };
+    enter_block();
+    // contiguous layout: the blocks of devices further on are entirely masked
+    const int kv_end = !RING ? kv + 1
+                             : (p.layout == SA_STRIPED ? p.kv_dev + p.n_kv : min(p.kv_dev + p.n_kv, dev + 1));
 
     uint32_t arow[8], tr0[4], tr1[4], gl[NH][4];
     dt_row_addrs(arow, n, h);
@@ -222,9 +236,11 @@ bwd_dq_mfma_kernel(StepArgs p, int n_tiles) {
     }
 
     // Trip t = iterations 2t (scores in *_a) and 2t+1 (scores in *_b); PAR = t & 1 selects
-    // the buffers of tile t at compile time.
-    auto trip = [&](auto last_c, auto mask_c, auto par_c, int t) {
+    // the buffers of tile t at compile time.  REQ: the tiles of kr, vr at `at` are requested into
+    // the buffers this trip frees.
+    auto trip = [&](auto last_c, auto mask_c, auto par_c, auto req_c, int t, dt_rsrc kr, dt_rsrc vr, int at) {
         constexpr bool LAST = decltype(last_c)::value, MASK = decltype(mask_c)::value;
+        constexpr bool REQ = decltype(req_c)::value;
         constexpr int PAR = decltype(par_c)::value;
         char* const k_cur = PAR ? k_lds1 : k_lds0;
         char* const v_cur = PAR ? v_lds1 : v_lds0;
@@ -239,31 +255,51 @@ bwd_dq_mfma_kernel(StepArgs p, int n_tiles) {
         }
         dq_step<!LAST, MASK, DP, PART>(s_b, dp_b, s_a, dp_a, acc, qf, gf, kappa, lse2, delta, arow, tr0, tr1,
                                        k_nxt, v_nxt, k_cur + DT_BYTES / 2, mask_base - 64 * t - 32, part_ks);
-        if (!LAST) {
+        if (REQ) {
             __syncthreads();                    // every wavefront is done with tile t
-            if (t + 2 < n_kt) {
-                load_tile(Kr, (t + 2) * tile_pitch, k_cur);
-                load_tile(Vr, (t + 2) * tile_pitch, v_cur);
-            }
+            load_tile(kr, at, k_cur);
+            load_tile(vr, at, v_cur);
         }
     };
     using T = std::true_type;
     using F = std::false_type;
     using P0 = std::integral_constant<int, 0>;
     using P1 = std::integral_constant<int, 1>;
-    // trips before the last tile pair of the fine walk without the element mask, then masked
-    // trips: two, more under emulated coarse skipping (n_kt_fine and n_kt are even)
+    // per block: trips before the last tile pair of the fine walk without the element mask, then
+    // masked trips: two, more under emulated coarse skipping (n_kt_fine and n_kt are even)
     int t = 0;
-    for (; t + 2 < n_kt_fine; t += 2) {
-        trip(F{}, F{}, P0{}, t);
-        trip(F{}, F{}, P1{}, t + 1);
+    for (;;) {
+        for (; t + 2 < n_kt_fine; t += 2) {
+            trip(F{}, F{}, P0{}, T{}, t, Kr, Vr, (t + 2) * tile_pitch);
+            trip(F{}, F{}, P1{}, T{}, t + 1, Kr, Vr, (t + 3) * tile_pitch);
+        }
+        if (!RING) {
+            for (; t + 2 < n_kt; t += 2) {
+                trip(F{}, T{}, P0{}, T{}, t, Kr, Vr, (t + 2) * tile_pitch);
+                trip(F{}, T{}, P1{}, T{}, t + 1, Kr, Vr, (t + 3) * tile_pitch);
+            }
+            break;
+        }
+        // a masked pair and what follows it: the next pair of the block, the next block, or the
+        // last pair of the walk
+        const bool leave = t + 2 >= n_kt;
+        if (leave && kv + 1 == kv_end) break;
+        const int64_t move = leave ? 2 * p.kv_shard : 0;
+        const dt_rsrc kr = dt_advance(Kr, move), vr = dt_advance(Vr, move);
+        const int at = leave ? 0 : (t + 2) * tile_pitch;
+        trip(F{}, T{}, P0{}, T{}, t, kr, vr, at);
+        trip(F{}, T{}, P1{}, T{}, t + 1, kr, vr, at + tile_pitch);
+        t += 2;
+        if (leave) {
+            Kr = kr;
+            Vr = vr;
+            t = 0;
+            ++kv;
+            enter_block();
+        }
     }
-    for (; t + 2 < n_kt; t += 2) {
-        trip(F{}, T{}, P0{}, t);
-        trip(F{}, T{}, P1{}, t + 1);
-    }
-    trip(F{}, T{}, P0{}, t);
-    trip(T{}, T{}, P1{}, t + 1);
+    trip(F{}, T{}, P0{}, F{}, t, Kr, Vr, 0);
+    trip(T{}, T{}, P1{}, F{}, t + 1, Kr, Vr, 0);
 
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb)
@@ -272,7 +308,7 @@ bwd_dq_mfma_kernel(StepArgs p, int n_tiles) {
             const int col = 32 * mb + 8 * g + 4 * h;
             if (col >= d || !row_ok) continue;            // padding columns, rows beyond the shard
             float4* dst = reinterpret_cast<float4*>(DQ + (int64_t)a * ss + col);
-            float4 x = *dst;
+            float4 x = RING ? make_float4(0.f, 0.f, 0.f, 0.f) : *dst;       // a ring walk is all of dQ
             x.x = fmaf(p.scale, acc[mb][4 * g + 0], x.x); x.y = fmaf(p.scale, acc[mb][4 * g + 1], x.y);
             x.z = fmaf(p.scale, acc[mb][4 * g + 2], x.z); x.w = fmaf(p.scale, acc[mb][4 * g + 3], x.w);
             *dst = x;
@@ -452,7 +488,10 @@ __device__ inline void dkdv_step(f32x16& s_cur, f32x16& dp_cur, f32x16& s_next, 
 // RAGGED (c not a multiple of 128): key rows beyond the shard are loaded from its last row and
 // not stored; query rows beyond it come in as zero rows of Q and dO with LSE = +inf, so their
 // P and dS are exactly zero.
-template <bool TRI, bool RAGGED, int DP, bool PART>
+// WALK: one block, or (WALK_RING) several one after the other with dK and dV in registers from the
+// first to the last: the query heads that share this key/value head, each with the query shards of
+// the devices that see these keys.
+template <int WALK, bool RAGGED, int DP, bool PART>
 __global__ void __launch_bounds__(256, 1)
 bwd_dkdv_mfma_kernel(StepArgs p, int n_tiles) {
     constexpr int NH = halves_of(DP), KS = ksteps_of(DP), MB = blocks_of(DP);      // per half
@@ -465,26 +504,24 @@ bwd_dkdv_mfma_kernel(StepArgs p, int n_tiles) {
 
     const int tid = threadIdx.x, lane = tid & 63, n = lane & 31, h = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);      // wave-uniform, kept scalar
-    int ktile, bhh;                               // triangular steps: low key tiles see most queries: first
-    // one workgroup per (key tile, batch, key/value head, 128-column half of dK / dV); the query
-    // head is this launch's member of the group that shares the key/value head
-    decode_block<false>((int)blockIdx.x, n_tiles, p.B * p.H_kv * NH, ktile, bhh);
+    constexpr bool RING = WALK == WALK_RING;
+    int ktile, bhh, dev = p.kv_dev;               // triangular blocks: low key tiles see most queries: first
+    // one workgroup per (key tile, device, batch, key/value head, 128-column half of dK / dV)
+    decode_block<false>((int)blockIdx.x, RING ? n_tiles * p.n_kv : n_tiles, p.B * p.H_kv * NH, ktile, bhh);
+    if (RING) {
+        int dev_rank;
+        decode_rank(ktile, n_tiles, p.n_kv, p.layout, ktile, dev_rank);
+        dev += dev_rank;
+    }
     const int bh = bhh / NH, ohalf = bhh - bh * NH;
     const int b = bh / p.H_kv, kvh = bh - b * p.H_kv;
-    const int hd = kvh * (p.H / p.H_kv) + p.member;
-    const int64_t base = b * p.stride_b + hd * p.stride_h;
-    const int64_t kv_base = b * p.kv_stride_b + kvh * p.kv_stride_h;
-    const int64_t sbase = b * p.stat_stride_b + hd * p.stat_stride_h;
+    const int64_t kv_base = b * p.kv_stride_b + kvh * p.kv_stride_h + (RING ? (dev - p.kv_dev) * p.kv_shard : 0);
     const int d = p.d;                                 // d <= DP, zero-padded to DP columns
     const int64_t ss = p.kv_stride_s;                  // elements between consecutive rows of K, V, dK, dV
     const int pitch = 2 * (int)p.stride_s;             // bytes between consecutive rows of Q and dO
     const int tile_pitch = DT_ROWS * pitch;            // bytes between 64-row tiles in global memory
-    const dt_rsrc Qr = dt_make_rsrc((const __bf16*)p.q + base, p.c, pitch, d);
-    const dt_rsrc Gr = dt_make_rsrc((const __bf16*)p.dout + base, p.c, pitch, d);
     const __bf16* K = (const __bf16*)p.k + kv_base;
     const __bf16* V = (const __bf16*)p.v + kv_base;
-    const float* LSE = p.lse + sbase;
-    const float* DEL = p.delta + sbase;
     float* DK = p.dk + kv_base;
     float* DV = p.dv + kv_base;
 
@@ -492,16 +529,37 @@ bwd_dkdv_mfma_kernel(StepArgs p, int n_tiles) {
     const bool key_ok = !RAGGED || key_own < p.c;
     const int key = RAGGED ? min(key_own, p.c - 1) : key_own;     // the row this lane loads
     const int n_qt = RAGGED ? 2 * n_tiles : p.c / DT_ROWS;
-    // query tiles holding at least one allowed pair (query a >= key + off): from tile k0 / 64
-    // on; only its first four 32-query sub-tiles can cross the diagonal for some wavefront
-    const int t_first_fine = TRI ? k0 / DT_ROWS : 0;
-    int t_first = t_first_fine;
-    if (TRI && p.skip_bq > 0)   // emulated coarse skipping: from the first skip_bq-tall query tile
-                                // that shares an allowed pair with these keys' skip_bk-wide tile
-        t_first = ((k0 / p.skip_bk * p.skip_bk + p.off) / p.skip_bq) * p.skip_bq / DT_ROWS;
-    // sub-tile u: register r (query 32 u + 8 (r/4) + 4h + r%4) is allowed iff
-    // 8 (r/4) + r%4 >= mask_base - 32 u
-    const int mask_base = key_own + p.off - 4 * h;
+    // The block being walked: query head q_head of the group and query shard q_dev.  Query tiles
+    // holding at least one allowed pair (query a >= key + off) are those from k0 / 64 on; only the
+    // first four 32-query sub-tiles of these can cross the diagonal for some wavefront, the trips
+    // before t_plain carry the mask.  Sub-tile u: register r (query 32 u + 8 (r/4) + 4h + r%4) is
+    // allowed iff 8 (r/4) + r%4 >= mask_base - 32 u.
+    const int group = RING ? p.H / p.H_kv : 1;
+    // contiguous layout: earlier devices' queries see nothing of these keys
+    const int dev0 = RING && p.layout != SA_STRIPED ? max(p.q_dev, dev) : p.q_dev;
+    int q_head = 0, q_dev = dev0, t_first, t_plain, mask_base;
+    dt_rsrc Qr, Gr;
+    const float* stat_src;      // this thread's next statistics row
+    int stat_row;               // its number (RAGGED only)
+    auto enter_block = [&]() {
+        const int hd = kvh * group + q_head;
+        const bool tri = RING ? block_kind(q_dev, dev, p.layout) == MASK_TRI : WALK == WALK_TRI;
+        const int off = block_off(q_dev, dev, p.layout);
+        t_first = tri ? k0 / DT_ROWS : 0;
+        t_plain = tri ? t_first + 2 : 0;
+        if (tri && p.skip_bq > 0)   // emulated coarse skipping: from the first skip_bq-tall query tile
+                                    // that shares an allowed pair with these keys' skip_bk-wide tile
+            t_first = ((k0 / p.skip_bk * p.skip_bk + off) / p.skip_bq) * p.skip_bq / DT_ROWS;
+        mask_base = tri ? key_own + off - 4 * h : 0;
+        const int64_t base = b * p.stride_b + hd * p.stride_h + (RING ? (q_dev - p.q_dev) * p.q_shard : 0);
+        const int64_t sbase = b * p.stat_stride_b + hd * p.stat_stride_h +
+                              (RING ? (int64_t)(q_dev - p.q_dev) * p.c : 0);
+        Qr = dt_make_rsrc((const __bf16*)p.q + base, p.c, pitch, d);
+        Gr = dt_make_rsrc((const __bf16*)p.dout + base, p.c, pitch, d);
+        stat_row = (tid & (DT_ROWS - 1)) + t_first * DT_ROWS;
+        stat_src = ((tid & DT_ROWS) ? p.delta : p.lse) + sbase + stat_row;
+    };
+    enter_block();
 
     uint32_t arow[8], tr0[4], tr1[4], gl[NH][4];
     dt_row_addrs(arow, n, h);
@@ -528,9 +586,7 @@ bwd_dkdv_mfma_kernel(StepArgs p, int n_tiles) {
     // statistics of query tile t -> stat[(t & 1)][0 | 1][64]: threads 0..63 LSE * log2(e), 64..127
     // -delta.  The fetch is branch-free (wavefronts 2 and 3 re-read what 0 and 1 read and drop
     // it), so nothing waits for it before the store one trip later.
-    const float* stat_src = ((tid & DT_ROWS) ? DEL : LSE) + (tid & (DT_ROWS - 1)) + t_first * DT_ROWS;
     const float stat_mul = (tid & DT_ROWS) ? -1.f : LOG2E;
-    int stat_row = (tid & (DT_ROWS - 1)) + t_first * DT_ROWS;      // RAGGED only
     auto stat_fetch = [&]() -> float {          // tiles in order: the pointer walks with them
         float x;
         if (RAGGED) {       // rows beyond the shard: LSE = +inf, delta = 0 (still branch-free)
@@ -547,7 +603,7 @@ bwd_dkdv_mfma_kernel(StepArgs p, int n_tiles) {
         if (tid < 2 * DT_ROWS) stat[(t & 1) * 2 * DT_ROWS + tid] = x * stat_mul;
     };
     stat_store(t_first, stat_fetch());
-    stat_store(t_first + 1, stat_fetch());
+    float rstat = stat_fetch();         // statistics of the tile after the present one
 
     bf16x8 kf[8 * NH], vf[8 * NH];
     load_b_frags<8 * NH>(kf, K + (int64_t)key * ss, h, d);
@@ -586,10 +642,12 @@ bwd_dkdv_mfma_kernel(StepArgs p, int n_tiles) {
         if (DP <= 128) mfma_results_to_valu(s_a, dp_a);
     }
 
-    float rstat = 0.f;          // statistics of the tile after next, in flight
-    // Trip t = iterations 2t (scores in *_a) and 2t+1 (scores in *_b) on query tile t.
-    auto trip = [&](auto mask_c, auto par_c, auto last_c, int t) {
+    // Trip t = iterations 2t (scores in *_a) and 2t+1 (scores in *_b) on query tile t.  REQ: the
+    // tile at `at` of the present Qr, Gr (which the caller may have moved on to the next block's)
+    // is requested into the buffers this trip frees.  mask_at = mask_base - 64 t.
+    auto trip = [&](auto mask_c, auto par_c, auto last_c, auto req_c, int mask_at, int at) {
         constexpr bool MASK = decltype(mask_c)::value, last = decltype(last_c)::value;
+        constexpr bool REQ = decltype(req_c)::value;
         constexpr int PAR = decltype(par_c)::value;
         char* const q_cur = PAR ? q_lds1 : q_lds0;
         char* const g_cur = PAR ? g_lds1 : g_lds0;
@@ -599,63 +657,61 @@ bwd_dkdv_mfma_kernel(StepArgs p, int n_tiles) {
         const float* st_nxt = stat + (1 - PAR) * 2 * DT_ROWS;       // statistics of tile t + 1
         dkdv_step<true, MASK, DP, PART>(s_a, dp_a, s_b, dp_b, acck, accv, kf, vf, kappa, arow, tr0, tr1,
                               q_cur + DT_BYTES / 2, g_cur + DT_BYTES / 2, q_cur, g_cur, st, st + 32, h,
-                              mask_base - 64 * t, part_ks);
+                              mask_at, part_ks);
         if (!last) {
-            if (t > t_first) stat_store(t + 1, rstat);     // fetched at the end of trip t-1
+            stat_store(1 - PAR, rstat);          // fetched at the end of the previous trip
             __builtin_amdgcn_s_waitcnt(0);       // tile t+1, requested one iteration ago, has landed
             __syncthreads();
-            dkdv_step<true, MASK, DP, PART>(s_b, dp_b, s_a, dp_a, acck, accv, kf, vf, kappa, arow, tr0, tr1, q_nxt,
-                                  g_nxt, q_cur + DT_BYTES / 2, g_cur + DT_BYTES / 2, st + 32, st_nxt, h,
-                                  mask_base - 64 * t - 32, part_ks);
+        }
+        dkdv_step<!last, MASK, DP, PART>(s_b, dp_b, s_a, dp_a, acck, accv, kf, vf, kappa, arow, tr0, tr1, q_nxt,
+                              g_nxt, q_cur + DT_BYTES / 2, g_cur + DT_BYTES / 2, st + 32, st_nxt, h,
+                              mask_at - 32, part_ks);
+        if (REQ) {
             __syncthreads();                     // every wavefront is done with tile t
-            if (t + 2 < n_qt) {
-                load_tile(Qr, (t + 2) * tile_pitch, q_cur);
-                load_tile(Gr, (t + 2) * tile_pitch, g_cur);
-                rstat = stat_fetch();
-            }
-        } else {
-            dkdv_step<false, MASK, DP, PART>(s_b, dp_b, s_a, dp_a, acck, accv, kf, vf, kappa, arow, tr0, tr1, q_nxt,
-                                   g_nxt, q_cur + DT_BYTES / 2, g_cur + DT_BYTES / 2, st + 32, st_nxt, h,
-                                   mask_base - 64 * t - 32, part_ks);
+            load_tile(Qr, at, q_cur);
+            load_tile(Gr, at, g_cur);
+            rstat = stat_fetch();
         }
     };
     using T = std::true_type;
     using F = std::false_type;
     using P0 = std::integral_constant<int, 0>;
     using P1 = std::integral_constant<int, 1>;
-    // t_first and n_qt are even (c and k0 are multiples of 128): trips come in pairs and the
-    // last one has odd parity
+    using M = std::integral_constant<bool, WALK != WALK_FULL>;
+    // t_first and n_qt are even (c and k0 are multiples of 128, or tiles are counted in pairs): trips
+    // come in pairs.  Masked pairs up to the diagonal (one, more under emulated coarse skipping),
+    // plain pairs, and the last pair of the block, in masked form (beyond the diagonal the limit is
+    // negative and removes nothing).
+    // DP = 256: one form (masked unless the block is full) for every pair but the last.  With a second, unmasked copy of the
+    // loop this instantiation, which is over the register budget, kept spilled registers live
+    // across its hot loop, and every reload there waits for the tile loads in flight as well.
+    constexpr bool ONE_FORM = DP > 128;
     int t = t_first;
-    if (TRI && DP > 128) {
-        // One masked form for every trip (beyond the diagonal the mask limit is negative and
-        // removes nothing).  With a second, unmasked copy of the loop this instantiation,
-        // which is over the register budget, kept spilled registers live across its hot loop,
-        // and every reload there waits for the tile loads in flight as well.
-        for (; t + 2 < n_qt; t += 2) {
-            trip(T{}, P0{}, F{}, t);
-            trip(T{}, P1{}, F{}, t + 1);
+    for (;;) {
+        int mask_at = mask_base - 64 * t, at = (t + 2) * tile_pitch;
+        if (t + 2 < n_qt && !ONE_FORM && t >= t_plain) {
+            for (; t + 2 < n_qt; t += 2) {              // the hot loop
+                trip(F{}, P0{}, F{}, T{}, 0, (t + 2) * tile_pitch);
+                trip(F{}, P1{}, F{}, T{}, 0, (t + 3) * tile_pitch);
+            }
+            continue;
         }
-        trip(T{}, P0{}, F{}, t);
-        trip(T{}, P1{}, T{}, t + 1);
-    } else if (TRI) {
-        // the trips up to the diagonal carry the element mask: the first two, more under
-        // emulated coarse skipping
-        for (; t < t_first_fine + 2; t += 2) {
-            trip(T{}, P0{}, F{}, t);
-            if (t + 2 < n_qt) trip(T{}, P1{}, F{}, t + 1);
-            else trip(T{}, P1{}, T{}, t + 1);
+        if (t + 2 >= n_qt) {                            // last pair of the block
+            if (!RING) break;
+            if (++q_dev == p.q_dev + p.n_q) {
+                q_dev = dev0;
+                if (++q_head == group) break;
+            }
+            enter_block();
+            t = t_first - 2;
+            at = t_first * tile_pitch;
         }
+        trip(M{}, P0{}, F{}, T{}, mask_at, at);
+        trip(M{}, P1{}, F{}, T{}, mask_at - 64, at + tile_pitch);
+        t += 2;
     }
-    if (!(TRI && DP > 128)) {
-        for (; t + 2 < n_qt; t += 2) {
-            trip(F{}, P0{}, F{}, t);
-            trip(F{}, P1{}, F{}, t + 1);
-        }
-        if (t < n_qt) {
-            trip(F{}, P0{}, F{}, t);
-            trip(F{}, P1{}, T{}, t + 1);
-        }
-    }
+    trip(M{}, P0{}, F{}, F{}, mask_base - 64 * t, 0);
+    trip(M{}, P1{}, T{}, F{}, mask_base - 64 * t - 64, 0);
 
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb)
@@ -664,11 +720,14 @@ bwd_dkdv_mfma_kernel(StepArgs p, int n_tiles) {
             const int col = 128 * ohalf + 32 * mb + 8 * g + 4 * h;
             if (col >= d || !key_ok) continue;            // padding columns, keys beyond the shard
             const int64_t o = (int64_t)key * ss + col;
-            float4 x = *reinterpret_cast<float4*>(DV + o);
+            float4 x = make_float4(0.f, 0.f, 0.f, 0.f), y = x;
+            if (!RING || !p.fresh) {
+                x = *reinterpret_cast<float4*>(DV + o);
+                y = *reinterpret_cast<float4*>(DK + o);
+            }
             x.x += accv[mb][4 * g + 0]; x.y += accv[mb][4 * g + 1];
             x.z += accv[mb][4 * g + 2]; x.w += accv[mb][4 * g + 3];
             *reinterpret_cast<float4*>(DV + o) = x;
-            float4 y = *reinterpret_cast<float4*>(DK + o);
             y.x = fmaf(p.scale, acck[mb][4 * g + 0], y.x); y.y = fmaf(p.scale, acck[mb][4 * g + 1], y.y);
             y.z = fmaf(p.scale, acck[mb][4 * g + 2], y.z); y.w = fmaf(p.scale, acck[mb][4 * g + 3], y.w);
             *reinterpret_cast<float4*>(DK + o) = y;
@@ -683,8 +742,8 @@ bool bwd_mfma_supported(const StepArgs& a, int dtype) {
     // its first
     const int64_t widest = a.stride_s > a.kv_stride_s ? a.stride_s : a.kv_stride_s;
     const int64_t rows = (int64_t)(a.c + BM - 1) / BM * BM;
-    // one workgroup per (128-row tile, batch, head) in a 1-D grid
-    if (rows / BM * a.B * a.H >= (int64_t(1) << 31)) return false;
+    // one workgroup per (128-row tile, device, batch, head) in a 1-D grid
+    if (rows / BM * a.B * a.H * (a.n_q > a.n_kv ? a.n_q : a.n_kv) >= (int64_t(1) << 31)) return false;
     // head dimensions above 128 (two 128-column halves) in whole 16-byte chunks only
     if (a.d > 2 * D || (a.d > D && a.d % 8)) return false;
     return dtype == SA_BF16 && a.d % 4 == 0 && a.c >= BM &&
@@ -692,35 +751,32 @@ bool bwd_mfma_supported(const StepArgs& a, int dtype) {
 }
 
 namespace {
+template <int WALK, int DP, bool PART>
+void launch_dq(const StepArgs& a, hipStream_t st, int n_tiles) {
+    const dim3 grid((unsigned)n_tiles * a.n_q * a.B * a.H), block(256);
+    if (a.c % BM) hipLaunchKernelGGL((bwd_dq_mfma_kernel<true, WALK, DP, PART>), grid, block, 0, st, a, n_tiles);
+    else hipLaunchKernelGGL((bwd_dq_mfma_kernel<false, WALK, DP, PART>), grid, block, 0, st, a, n_tiles);
+}
+template <int WALK, int DP, bool PART>
+void launch_dkdv(const StepArgs& a, hipStream_t st, int n_tiles) {
+    const dim3 grid((unsigned)n_tiles * a.n_kv * a.B * a.H_kv * halves_of(DP)), block(256);
+    if (a.c % BM) hipLaunchKernelGGL((bwd_dkdv_mfma_kernel<WALK, true, DP, PART>), grid, block, 0, st, a, n_tiles);
+    else hipLaunchKernelGGL((bwd_dkdv_mfma_kernel<WALK, false, DP, PART>), grid, block, 0, st, a, n_tiles);
+}
 template <int DP, bool PART>
 hipError_t launch_bwd_variant(const StepArgs& a, hipStream_t st) {
     const int n_tiles = (a.c + BM - 1) / BM;
-    const bool ragged = a.c % BM != 0;
-    const dim3 grid_q((unsigned)n_tiles * a.B * a.H), block(256);
-    const dim3 grid_kv((unsigned)n_tiles * a.B * a.H_kv * (DP > 128 ? 2 : 1));
-    const bool full = a.kind == MASK_FULL;
-    if (ragged) {
-        if (full) hipLaunchKernelGGL((bwd_dq_mfma_kernel<true, true, DP, PART>), grid_q, block, 0, st, a, n_tiles);
-        else hipLaunchKernelGGL((bwd_dq_mfma_kernel<true, false, DP, PART>), grid_q, block, 0, st, a, n_tiles);
-    } else {
-        if (full) hipLaunchKernelGGL((bwd_dq_mfma_kernel<false, true, DP, PART>), grid_q, block, 0, st, a, n_tiles);
-        else hipLaunchKernelGGL((bwd_dq_mfma_kernel<false, false, DP, PART>), grid_q, block, 0, st, a, n_tiles);
-    }
-    hipError_t e = hipGetLastError();
-    // dK, dV: the members of a group of query heads one after the other, each adding to the
-    // shared head's accumulators in stream order (deterministic)
-    StepArgs m = a;
-    for (m.member = 0; m.member < a.H / a.H_kv && e == hipSuccess; ++m.member) {
-        if (a.kind == MASK_TRI) {
-            if (ragged) hipLaunchKernelGGL((bwd_dkdv_mfma_kernel<true, true, DP, PART>), grid_kv, block, 0, st, m, n_tiles);
-            else hipLaunchKernelGGL((bwd_dkdv_mfma_kernel<true, false, DP, PART>), grid_kv, block, 0, st, m, n_tiles);
-        } else {
-            if (ragged) hipLaunchKernelGGL((bwd_dkdv_mfma_kernel<false, true, DP, PART>), grid_kv, block, 0, st, m, n_tiles);
-            else hipLaunchKernelGGL((bwd_dkdv_mfma_kernel<false, false, DP, PART>), grid_kv, block, 0, st, m, n_tiles);
-        }
-        e = hipGetLastError();
-    }
-    return e;
+    const bool one_block = a.n_q == 1 && a.n_kv == 1 && !a.fresh;
+    const bool full = block_kind(a.q_dev, a.kv_dev, a.layout) == MASK_FULL;
+    if (!one_block) launch_dq<WALK_RING, DP, PART>(a, st, n_tiles);
+    else if (full) launch_dq<WALK_FULL, DP, PART>(a, st, n_tiles);
+    else launch_dq<WALK_TRI, DP, PART>(a, st, n_tiles);
+    if (hipError_t e = hipGetLastError()) return e;
+    // query heads that share a key/value head are blocks of one walk
+    if (!one_block || a.H != a.H_kv) launch_dkdv<WALK_RING, DP, PART>(a, st, n_tiles);
+    else if (full) launch_dkdv<WALK_FULL, DP, PART>(a, st, n_tiles);
+    else launch_dkdv<WALK_TRI, DP, PART>(a, st, n_tiles);
+    return hipGetLastError();
 }
 }  // namespace
 

@@ -10,7 +10,7 @@ namespace sa {
 
 // grid: (row blocks, B*H); each thread handles 4 floats of a row; rows are ss elements apart.
 __global__ void __launch_bounds__(256)
-state_init_kernel(float* __restrict__ o, float* __restrict__ lse, int H, int c, int d,
+state_init_kernel(float* __restrict__ o, float* __restrict__ lse, int H, int64_t c, int d,
                   int64_t sb, int64_t sh, int64_t ss, int64_t ssb, int64_t ssh, float lse_value,
                   bool touch_lse) {
     const int bh = blockIdx.y, b = bh / H, h = bh - b * H;
@@ -44,9 +44,9 @@ hipError_t launch_state_init(float* o, float* lse, const sa_shape& s, hipStream_
     return hipGetLastError();
 }
 
-hipError_t launch_zero_f32(float* p, const sa_shape& s, hipStream_t st) {
-    dim3 grid(row_blocks((int64_t)s.c * s.d / 4), s.B * s.H);
-    hipLaunchKernelGGL(state_init_kernel, grid, dim3(256), 0, st, p, (float*)nullptr, s.H, s.c, s.d,
+hipError_t launch_zero_f32(float* p, const sa_shape& s, int64_t rows, hipStream_t st) {
+    dim3 grid(row_blocks(rows * s.d / 4), s.B * s.H);
+    hipLaunchKernelGGL(state_init_kernel, grid, dim3(256), 0, st, p, (float*)nullptr, s.H, rows, s.d,
                        s.stride_b, s.stride_h, row_stride(s), (int64_t)0, (int64_t)0, 0.f, false);
     return hipGetLastError();
 }
@@ -108,7 +108,7 @@ __device__ inline float4 load4<__hip_bfloat16>(const __hip_bfloat16* p) {
 template <typename T>
 __global__ void __launch_bounds__(256)
 bwd_preprocess_kernel(const float* __restrict__ o, const T* __restrict__ dout, float* __restrict__ delta,
-                      int H, int c, int d, int64_t sb, int64_t sh, int64_t ss, int64_t ssb, int64_t ssh) {
+                      int H, int64_t c, int d, int64_t sb, int64_t sh, int64_t ss, int64_t ssb, int64_t ssh) {
     const int bh = blockIdx.y, b = bh / H, h = bh - b * H;
     const int g = threadIdx.x >> 4, l = threadIdx.x & 15;
     for (int64_t row = (int64_t)blockIdx.x * 16 + g; row < c; row += (int64_t)gridDim.x * 16) {
@@ -129,17 +129,17 @@ bwd_preprocess_kernel(const float* __restrict__ o, const T* __restrict__ dout, f
 }
 
 hipError_t launch_bwd_preprocess(const float* o, const void* dout, float* delta, const sa_shape& s,
-                                 hipStream_t st) {
-    int64_t g = ((int64_t)s.c + 15) / 16;
+                                 int64_t rows, hipStream_t st) {
+    int64_t g = (rows + 15) / 16;
     if (g > 8192) g = 8192;
     dim3 grid((unsigned)g, s.B * s.H);
     if (s.dtype == SA_F32)
         hipLaunchKernelGGL(bwd_preprocess_kernel<float>, grid, dim3(256), 0, st, o, (const float*)dout,
-                           delta, s.H, s.c, s.d, s.stride_b, s.stride_h, row_stride(s), s.stat_stride_b,
+                           delta, s.H, rows, s.d, s.stride_b, s.stride_h, row_stride(s), s.stat_stride_b,
                            s.stat_stride_h);
     else
         hipLaunchKernelGGL(bwd_preprocess_kernel<__hip_bfloat16>, grid, dim3(256), 0, st, o,
-                           (const __hip_bfloat16*)dout, delta, s.H, s.c, s.d, s.stride_b, s.stride_h,
+                           (const __hip_bfloat16*)dout, delta, s.H, rows, s.d, s.stride_b, s.stride_h,
                            row_stride(s), s.stat_stride_b, s.stat_stride_h);
     return hipGetLastError();
 }

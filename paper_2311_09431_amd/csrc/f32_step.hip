@@ -188,10 +188,11 @@ fwd_f32_kernel(StepArgs p, int n_tiles) {
     for (int mb = 0; mb < NB; ++mb) acc[mb] = zero16();
     float m = -INFINITY, l = 0.f;           // l: this half-wave's share of the row sum
 
-    const bool full = p.kind == MASK_FULL;
-    const int last_key = full ? p.c - 1 : min(q0 + 32 * OWN, p.c) - 1 - p.off;          // for the workgroup
-    const int wave_last = full ? p.c - 1 : min(q0 + 32 * qw + 31, p.c - 1) - p.off;     // for the wavefront
-    const int lane_last = full ? p.c - 1 : a - p.off;
+    const bool full = block_kind(p.q_dev, p.kv_dev, p.layout) == MASK_FULL;
+    const int off = block_off(p.q_dev, p.kv_dev, p.layout);
+    const int last_key = full ? p.c - 1 : min(q0 + 32 * OWN, p.c) - 1 - off;          // for the workgroup
+    const int wave_last = full ? p.c - 1 : min(q0 + 32 * qw + 31, p.c - 1) - off;     // for the wavefront
+    const int lane_last = full ? p.c - 1 : a - off;
     for (int t0 = 0; t0 <= last_key; t0 += TK) {
         __syncthreads();
         stage<T, DP, TK>(k_lds, K, p.kv_stride_s, t0, p.c, d);
@@ -339,10 +340,11 @@ bwd_dq_f32_kernel(StepArgs p, int n_tiles) {
 #pragma unroll
     for (int mb = 0; mb < NB; ++mb) acc[mb] = zero16();
 
-    const bool full = p.kind == MASK_FULL;
-    const int last_key = full ? p.c - 1 : min(q0 + 32 * OWN, p.c) - 1 - p.off;
-    const int wave_last = full ? p.c - 1 : min(q0 + 32 * qw + 31, p.c - 1) - p.off;
-    const int lane_last = full ? p.c - 1 : a - p.off;
+    const bool full = block_kind(p.q_dev, p.kv_dev, p.layout) == MASK_FULL;
+    const int off = block_off(p.q_dev, p.kv_dev, p.layout);
+    const int last_key = full ? p.c - 1 : min(q0 + 32 * OWN, p.c) - 1 - off;
+    const int wave_last = full ? p.c - 1 : min(q0 + 32 * qw + 31, p.c - 1) - off;
+    const int lane_last = full ? p.c - 1 : a - off;
     for (int t0 = 0; t0 <= last_key; t0 += TK) {
         __syncthreads();
         stage<T, DP, TK>(k_lds, K, p.kv_stride_s, t0, p.c, d);
@@ -403,11 +405,12 @@ bwd_dkdv_f32_kernel(StepArgs p, int n_tiles) {
 #pragma unroll
     for (int mb = 0; mb < NB; ++mb) acck[mb] = accv[mb] = zero16();
 
-    const bool full = p.kind == MASK_FULL;
+    const bool full = block_kind(p.q_dev, p.kv_dev, p.layout) == MASK_FULL;
+    const int off = block_off(p.q_dev, p.kv_dev, p.layout);
     // queries a >= key + off see the key: from this sub-tile on for the workgroup, the wavefront
-    const int first_query = full ? 0 : k0 + p.off;
-    const int wave_first = full ? 0 : k0 + 32 * own + p.off;
-    const int lane_first = full ? 0 : key_own + p.off;
+    const int first_query = full ? 0 : k0 + off;
+    const int wave_first = full ? 0 : k0 + 32 * own + off;
+    const int lane_first = full ? 0 : key_own + off;
     for (int member = 0; member < group; ++member) {
         const int hd = kvh * group + member;
         const T* Q = (const T*)p.q + b * p.stride_b + hd * p.stride_h;

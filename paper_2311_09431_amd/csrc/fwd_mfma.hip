@@ -232,7 +232,7 @@ __device__ inline void rope_rotate(bf16x8 (&f)[8 * halves_of(DP)], const double*
         }
 }
 
-// One code path serves every step: a block is walked up to the last key tile that holds an
+// One code path serves every block: it is walked up to the last key tile that holds an
 // allowed pair, and the last BM / 64 tiles of the walk carry the element mask.  For a
 // triangular block the mask limit is the query's own position; for a full block (contiguous
 // layout, q_dev > kv_dev) it is the last key, c - 1, which for a multiple of 128 masks
@@ -240,13 +240,18 @@ __device__ inline void rope_rotate(bf16x8 (&f)[8 * halves_of(DP)], const double*
 // the shard (their loads are clamped to the last row, their results are not stored) and the
 // last key tiles hold keys beyond it (the tile loads return zeros there and the mask removes
 // them).
-// (FULL is a template argument rather than a launch argument so that profiler traces name
-// triangular and full launches apart; the code is the same.)
+// WALK: one block of a kind known here, or (WALK_RING) the blocks of several shards one after the
+// other.  A ring of launches, one per block, pays for each block the filling and draining of the
+// pipeline, the read and write of the fp32 running state and, where a block does not fill the
+// chip, its idle compute units; here the state stays in registers from the first shard to the
+// last and the rows of all devices are in one grid.  Whole ring, 8 x 4096 tokens, 16 heads,
+// d 128, forward: 5.93 -> 4.03 ms; 4 x 1024 tokens, 2 heads, forward + backward: 1.42 -> 0.27 ms.
 // ROPE: the query rows are rotated by their position ids as they are loaded (d == DP).
-template <bool RAGGED, bool FULL, int DP, bool PART, bool ROPE = false>
+template <bool RAGGED, int WALK, int DP, bool PART, bool ROPE = false>
 __global__ void __launch_bounds__(64 * NW, DP > 128 ? 1 : 2)
 fwd_mfma_kernel(StepArgs p, int n_qtiles) {
     constexpr int NH = halves_of(DP), KS = ksteps_of(DP), MB = halves_of(DP) * blocks_of(DP);      // k-steps per half, column blocks
+    constexpr bool RING = WALK == WALK_RING;
     __shared__ double rope_turns[ROPE ? DP / 2 : 1];
     // one LDS object per tile buffer (two 128-column halves each when DP = 256)
     __shared__ __attribute__((aligned(1024))) char k_lds0[TILE_BYTES * NH];
@@ -256,11 +261,16 @@ fwd_mfma_kernel(StepArgs p, int n_qtiles) {
 
     const int tid = threadIdx.x, lane = tid & 63, n = lane & 31, h = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);      // wave-uniform, kept scalar
-    int rank, bh;
-    decode_block<true>((int)blockIdx.x, n_qtiles, p.B * p.H, rank, bh);
-    const int qt = n_qtiles - 1 - rank;      // triangular steps: heaviest query tiles first
+    int rank, bh, dev = p.q_dev;
+    decode_block<true>((int)blockIdx.x, RING ? n_qtiles * p.n_q : n_qtiles, p.B * p.H, rank, bh);
+    if (RING) {
+        int dev_rank;
+        decode_rank(rank, n_qtiles, p.n_q, p.layout, rank, dev_rank);
+        dev += p.n_q - 1 - dev_rank;
+    }
+    const int qt = n_qtiles - 1 - rank;      // triangular blocks: heaviest query tiles first
     const int b = bh / p.H, hd = bh - b * p.H;
-    const int64_t base = b * p.stride_b + hd * p.stride_h;
+    const int64_t base = b * p.stride_b + hd * p.stride_h + (RING ? (dev - p.q_dev) * p.q_shard : 0);
     // key/value head of this query head's group (the same head when H_kv == H)
     const int64_t kv_base = b * p.kv_stride_b + (hd / (p.H / p.H_kv)) * p.kv_stride_h;
     const __bf16* Q = (const __bf16*)p.q + base;
@@ -268,31 +278,40 @@ fwd_mfma_kernel(StepArgs p, int n_qtiles) {
     const int64_t ss = p.stride_s;                     // elements between consecutive rows of Q and O
     const int pitch = 2 * (int)p.kv_stride_s;          // bytes between consecutive rows of K and V
     const int tile_pitch = TILE_ROWS * pitch;          // bytes between 64-row tiles in global memory
-    const dt_rsrc K = dt_make_rsrc((const __bf16*)p.k + kv_base, p.c, pitch, d);
-    const dt_rsrc V = dt_make_rsrc((const __bf16*)p.v + kv_base, p.c, pitch, d);
+    dt_rsrc K = dt_make_rsrc((const __bf16*)p.k + kv_base, p.c, pitch, d);
+    dt_rsrc V = dt_make_rsrc((const __bf16*)p.v + kv_base, p.c, pitch, d);
     float* O = p.o + base;
-    float* L = p.lse + b * p.stat_stride_b + hd * p.stat_stride_h;
+    float* L = p.lse + b * p.stat_stride_b + hd * p.stat_stride_h + (RING ? (int64_t)(dev - p.q_dev) * p.c : 0);
 
     const int q0 = qt * BM;
     const int a_own = q0 + 32 * wave + n;     // this lane's query row
     const bool row_ok = !RAGGED || a_own < p.c;
     const int a = RAGGED ? min(a_own, p.c - 1) : a_own;      // the row it loads
-    constexpr bool full_block = FULL;                // every key allowed: the mask limit is the last key
-    // 64-key tiles holding at least one allowed pair for the workgroup.  Triangular: keys
-    // b <= a - off, i.e. tiles 0 .. (q0 + 127) / 64.  All four wavefronts walk all 2 n_kt
-    // sub-tiles (at most NW - 1 of them are entirely masked for a wavefront); the element
-    // mask is applied on the last NW sub-tiles only.
-    const int n_kt_fine = full_block ? 2 * n_qtiles : (q0 + BM) / TILE_ROWS;
-    int n_kt = n_kt_fine;
-    if (!full_block && p.skip_bq > 0) {
-        // emulated coarse skipping: up to the last skip_bk-wide key tile that shares an allowed
-        // pair with the skip_bq-tall tile these queries belong to
-        const int q_hi = (q0 / p.skip_bq + 1) * p.skip_bq - 1;
-        n_kt = min(p.c, ((q_hi - p.off) / p.skip_bk + 1) * p.skip_bk) / TILE_ROWS;
-    }
-    // sub-tile v: register r (key 32 v + 8 (r/4) + 4h + r%4) is allowed iff
-    // 8 (r/4) + r%4 <= mask_base - 32 v
-    const int mask_base = (full_block ? p.c - 1 : a_own - p.off) - 4 * h;
+    // The block being walked: key shard kv, its number of 64-key tiles holding at least one
+    // allowed pair for the workgroup (triangular: keys b <= a - off, i.e. tiles
+    // 0 .. (q0 + 127) / 64), the first tile with the element mask, and the mask itself: of
+    // sub-tile v, register r (key 32 v + 8 (r/4) + 4h + r%4) is allowed iff
+    // 8 (r/4) + r%4 <= mask_base - 32 v.  All four wavefronts walk all 2 n_kt sub-tiles (at most
+    // NW - 1 of them are entirely masked for a wavefront).
+    int kv = p.kv_dev, n_kt, t_mask, mask_base;
+    auto enter_block = [&]() {
+        const bool full = RING ? block_kind(dev, kv, p.layout) == MASK_FULL : WALK == WALK_FULL;
+        const int off = block_off(dev, kv, p.layout);
+        const int n_kt_fine = full ? 2 * n_qtiles : (q0 + BM) / TILE_ROWS;
+        n_kt = n_kt_fine;
+        if (!full && p.skip_bq > 0) {
+            // emulated coarse skipping: up to the last skip_bk-wide key tile that shares an allowed
+            // pair with the skip_bq-tall tile these queries belong to
+            const int q_hi = (q0 / p.skip_bq + 1) * p.skip_bq - 1;
+            n_kt = min(p.c, ((q_hi - off) / p.skip_bk + 1) * p.skip_bk) / TILE_ROWS;
+        }
+        t_mask = n_kt_fine - BM / TILE_ROWS;
+        mask_base = (full ? p.c - 1 : a_own - off) - 4 * h;
+    };
+    enter_block();
+    // contiguous layout: the blocks of devices further on are entirely masked
+    const int kv_end = !RING ? kv + 1
+                             : (p.layout == SA_STRIPED ? p.kv_dev + p.n_kv : min(p.kv_dev + p.n_kv, dev + 1));
 
     // per-lane addresses: K A-operand reads per k-step, V transposing reads per 32-column
     // block (bytes within a 32-row half tile), and the global byte offsets of this lane's
@@ -320,20 +339,20 @@ fwd_mfma_kernel(StepArgs p, int n_qtiles) {
         }
     }
 
-    auto load_k = [&](int tile_byte_offset, char* buf) {
+    auto load_k = [&](dt_rsrc K, int tile_byte_offset, char* buf) {
 #pragma unroll
         for (int hh = 0; hh < NH; ++hh)
             load_tile_direct(K, tile_byte_offset, buf + hh * TILE_BYTES, kg0[hh], wave, pitch);
     };
-    auto load_v = [&](int tile_byte_offset, char* buf) {
+    auto load_v = [&](dt_rsrc V, int tile_byte_offset, char* buf) {
 #pragma unroll
         for (int hh = 0; hh < NH; ++hh)
             load_v_tile_direct(V, tile_byte_offset, buf + hh * TILE_BYTES, vg0[hh], wave, pitch);
     };
     // first tiles on their way while the running state is loaded
-    load_k(0, k_lds0);
-    load_v(0, v_lds0);
-    load_k(tile_pitch, k_lds1);     // n_kt >= 2 always
+    load_k(K, 0, k_lds0);
+    load_v(V, 0, v_lds0);
+    load_k(K, tile_pitch, k_lds1);     // n_kt >= 2 always
 
     bf16x8 qf[8 * NH];
     load_b_frags<8 * NH>(qf, Q + (int64_t)a * ss, h, d);
@@ -388,8 +407,10 @@ fwd_mfma_kernel(StepArgs p, int n_qtiles) {
     //   u = 2t+1: QK(2t+2): K tile t+1, first half     PV(2t): V tile t, first half
     // PAR = t & 1 fixes every LDS offset at compile time.
     // LD: which of the two tile requests of the trip exist: 2 = K(t+2) and V(t+1), 1 = V(t+1)
-    // only (the last trip but one), 0 = none (the last trip)
-    auto trip = [&](auto first_c, auto last_c, auto mask_c, auto par_c, int t, auto ld_c) __attribute__((always_inline)) {
+    // only (the last trip but one), 0 = none (the last trip); kr, k_at and vr, v_at: where these
+    // two tiles lie, which for the last tiles of a block is the next shard
+    auto trip = [&](auto first_c, auto last_c, auto mask_c, auto par_c, int t, auto ld_c, dt_rsrc kr, int k_at,
+                    dt_rsrc vr, int v_at) __attribute__((always_inline)) {
         constexpr bool FIRST = decltype(first_c)::value, LAST = decltype(last_c)::value;
         constexpr bool MASK = decltype(mask_c)::value;
         constexpr int PAR = decltype(par_c)::value, LD = decltype(ld_c)::value;
@@ -402,8 +423,8 @@ fwd_mfma_kernel(StepArgs p, int n_qtiles) {
                                                  mask_base - 64 * t, part_ks);
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
-        if (LD >= 2) load_k((t + 2) * tile_pitch, k_cur);
-        if (LD >= 1) load_v((t + 1) * tile_pitch, v_prv);
+        if (LD >= 2) load_k(kr, k_at, k_cur);
+        if (LD >= 1) load_v(vr, v_at, v_prv);
         step<!LAST, true, true, MASK, DP, PART>(s_b, s_a, p_b, p_a, oacc, qf, m, l, kappa, kaddr, vaddr, k_nxt,
                                                 v_cur, mask_base - 64 * t - 32, part_ks);
     };
@@ -414,34 +435,63 @@ fwd_mfma_kernel(StepArgs p, int n_qtiles) {
     using L0 = std::integral_constant<int, 0>;
     using L1 = std::integral_constant<int, 1>;
     using L2 = std::integral_constant<int, 2>;
-    // The number of trips is even (tiles come in pairs of 64 keys per 128-row block), so the
-    // walk is a sequence of (even, odd) pairs of fixed form: the first pair, plain pairs (the
-    // hot loop), masked pairs, the last pair.  Triangular steps: the trips from t_mask on carry
-    // the element mask (the last BM / 64 ones, more under emulated coarse skipping).
-    const int t_mask = n_kt_fine - BM / TILE_ROWS;
-    if (n_kt == 2) {                   // a single pair (triangular: the first query tile)
-        trip(T{}, F{}, T{}, P0{}, 0, L1{});
-        trip(F{}, T{}, T{}, P1{}, 1, L0{});
-    } else {
-        if (t_mask == 0) {      // masked from the start (emulated coarse skipping only)
-            trip(T{}, F{}, T{}, P0{}, 0, L2{});
-            trip(F{}, F{}, T{}, P1{}, 1, L2{});
+    // The number of trips of a block is even (tiles come in pairs of 64 keys per 128-row block), so
+    // the walk is a sequence of (even, odd) pairs of fixed form: the first pair of the walk, then
+    // per block plain pairs (the hot loop) and masked pairs, and the last pair of the walk.  The
+    // trips of a block from t_mask on carry the element mask (its last BM / 64 ones, more under
+    // emulated coarse skipping).
+    int t = 0;
+    // a pair that requests the two tiles at `at` of kr / vr as the next ones
+    auto pair = [&](auto first_c, auto mask_c, dt_rsrc kr, dt_rsrc vr, int at) __attribute__((always_inline)) {
+        trip(first_c, F{}, mask_c, P0{}, t, L2{}, kr, at, V, (t + 1) * tile_pitch);
+        trip(F{}, F{}, mask_c, P1{}, t + 1, L2{}, kr, at + tile_pitch, vr, at);
+    };
+    // a masked pair and what follows it: the next pair of the block or the next block
+    auto masked_pair = [&](auto first_c) __attribute__((always_inline)) {
+        if (RING) {
+            const bool leave = t + 2 >= n_kt;
+            const int64_t move = leave ? 2 * p.kv_shard : 0;
+            const dt_rsrc kr = dt_advance(K, move), vr = dt_advance(V, move);
+            pair(first_c, T{}, kr, vr, leave ? 0 : (t + 2) * tile_pitch);
+            t += 2;
+            if (leave) {
+                K = kr;
+                V = vr;
+                t = 0;
+                ++kv;
+                enter_block();
+            }
         } else {
-            trip(T{}, F{}, F{}, P0{}, 0, L2{});
-            trip(F{}, F{}, F{}, P1{}, 1, L2{});
+            pair(first_c, T{}, K, V, (t + 2) * tile_pitch);
+            t += 2;
         }
-        int t = 2;
-        const int t_plain = min(t_mask, n_kt - 2);
-        for (; t < t_plain; t += 2) {                  // the hot loop: two plain trips per turn
-            trip(F{}, F{}, F{}, P0{}, t, L2{});
-            trip(F{}, F{}, F{}, P1{}, t + 1, L2{});
+    };
+    auto last_pair = [&](auto first_c) __attribute__((always_inline)) {        // always carries the mask
+        trip(first_c, F{}, T{}, P0{}, t, L1{}, K, 0, V, (t + 1) * tile_pitch);
+        trip(F{}, T{}, T{}, P1{}, t + 1, L0{}, K, 0, V, 0);
+    };
+    if (n_kt == 2 && kv + 1 == kv_end) {                   // a single pair (triangular: the first query tile)
+        last_pair(T{});
+    } else {
+        if (t_mask == 0) {          // masked from the start: a one-pair block or emulated coarse skipping
+            masked_pair(T{});
+        } else {
+            pair(T{}, F{}, K, V, 2 * tile_pitch);
+            t = 2;
         }
-        for (; t < n_kt - 2; t += 2) {                 // masked pairs before the last one
-            trip(F{}, F{}, T{}, P0{}, t, L2{});
-            trip(F{}, F{}, T{}, P1{}, t + 1, L2{});
-        }
-        trip(F{}, F{}, T{}, P0{}, n_kt - 2, L1{});    // the last pair always carries the mask
-        trip(F{}, T{}, T{}, P1{}, n_kt - 1, L0{});
+        do {
+            const int t_plain = min(t_mask, n_kt - 2);
+            for (; t < t_plain; t += 2)                     // the hot loop: two plain trips per turn
+                pair(F{}, F{}, K, V, (t + 2) * tile_pitch);
+            if (!RING) {
+                while (t < n_kt - 2) masked_pair(F{});
+            } else if (t < n_kt - 2 || kv + 1 < kv_end) {
+                masked_pair(F{});
+                continue;
+            }
+            break;
+        } while (true);
+        last_pair(F{});
     }
     // final iteration u = 2 n_kt: PV(2 n_kt - 1): V tile n_kt - 1, second half; P in p_b
     {
@@ -454,10 +504,11 @@ fwd_mfma_kernel(StepArgs p, int n_qtiles) {
     // into the running state by log-sum-exp (Alg. 1: accumulate into the output and update the
     // running softmax statistics), everything in base-2 units:
     //   LSE' = log2(2^LSE + 2^(m + log2 l)),  O' = O 2^(LSE - LSE') + oacc 2^(m - LSE')
+    // A ring walk starts from the empty state, which is not read.
     // A row that saw no key here (l = 0) keeps its state bit for bit; a row whose state is still
     // empty (LSE = -inf) takes the partial and never looks at the stored O.
     const float l_tot = half_wave_sum(l);
-    const float lse_old = L[a] * LOG2E;                                       // -inf stays -inf
+    const float lse_old = RING ? -INFINITY : L[a] * LOG2E;                    // -inf stays -inf
     const float lse_part = l_tot > 0.f ? m + __builtin_amdgcn_logf(l_tot) : -INFINITY;
     const float top = fmaxf(lse_old, lse_part);
     const float ref = top == -INFINITY ? 0.f : top;                           // no (-inf) - (-inf)
@@ -492,8 +543,8 @@ bool fwd_mfma_supported(const StepArgs& a, int dtype) {
     // the last row of its last (possibly partial) tile pair must end below 2^31 bytes from
     // its first
     const int64_t rows = (int64_t)(a.c + BM - 1) / BM * BM;
-    // one workgroup per (128-row tile, batch, head) in a 1-D grid
-    if (rows / BM * a.B * a.H >= (int64_t(1) << 31)) return false;
+    // one workgroup per (128-row tile, device, batch, head) in a 1-D grid
+    if (rows / BM * a.B * a.H * a.n_q >= (int64_t(1) << 31)) return false;
     // head dimensions above 128 (two 128-column halves) in whole 16-byte chunks only
     if (a.d > 2 * D || (a.d > D && a.d % 8)) return false;
     return dtype == SA_BF16 && a.d % 4 == 0 && a.c >= BM &&
@@ -501,21 +552,25 @@ bool fwd_mfma_supported(const StepArgs& a, int dtype) {
 }
 
 namespace {
+bool one_block(const StepArgs& a) { return a.n_q == 1 && a.n_kv == 1 && !a.fresh; }
+template <int WALK, int DP, bool PART>
+void launch_fwd_walk(const StepArgs& a, hipStream_t st, dim3 grid, dim3 block, int n_qtiles) {
+    if (a.c % BM) hipLaunchKernelGGL((fwd_mfma_kernel<true, WALK, DP, PART>), grid, block, 0, st, a, n_qtiles);
+    else hipLaunchKernelGGL((fwd_mfma_kernel<false, WALK, DP, PART>), grid, block, 0, st, a, n_qtiles);
+}
 template <int DP, bool PART>
 void launch_fwd_variant(const StepArgs& a, hipStream_t st, dim3 grid, dim3 block, int n_qtiles) {
-    const bool full = a.kind == MASK_FULL;
-    if (a.c % BM) {
-        if (full) hipLaunchKernelGGL((fwd_mfma_kernel<true, true, DP, PART>), grid, block, 0, st, a, n_qtiles);
-        else hipLaunchKernelGGL((fwd_mfma_kernel<true, false, DP, PART>), grid, block, 0, st, a, n_qtiles);
-    } else {
-        if (full) hipLaunchKernelGGL((fwd_mfma_kernel<false, true, DP, PART>), grid, block, 0, st, a, n_qtiles);
-        else hipLaunchKernelGGL((fwd_mfma_kernel<false, false, DP, PART>), grid, block, 0, st, a, n_qtiles);
-    }
+    if (!one_block(a)) launch_fwd_walk<WALK_RING, DP, PART>(a, st, grid, block, n_qtiles);
+    else if (block_kind(a.q_dev, a.kv_dev, a.layout) == MASK_FULL)
+        launch_fwd_walk<WALK_FULL, DP, PART>(a, st, grid, block, n_qtiles);
+    else launch_fwd_walk<WALK_TRI, DP, PART>(a, st, grid, block, n_qtiles);
 }
 template <int DP>
 void launch_fwd_rope(const StepArgs& a, hipStream_t st, dim3 grid, dim3 block, int n_qtiles) {
-    if (a.kind == MASK_FULL) hipLaunchKernelGGL((fwd_mfma_kernel<false, true, DP, false, true>), grid, block, 0, st, a, n_qtiles);
-    else hipLaunchKernelGGL((fwd_mfma_kernel<false, false, DP, false, true>), grid, block, 0, st, a, n_qtiles);
+    if (block_kind(a.q_dev, a.kv_dev, a.layout) == MASK_FULL)
+        hipLaunchKernelGGL((fwd_mfma_kernel<false, WALK_FULL, DP, false, true>), grid, block, 0, st, a, n_qtiles);
+    else
+        hipLaunchKernelGGL((fwd_mfma_kernel<false, WALK_TRI, DP, false, true>), grid, block, 0, st, a, n_qtiles);
 }
 }  // namespace
 
@@ -527,7 +582,7 @@ bool fwd_mfma_rope_supported(const StepArgs& a, int dtype) {
 
 hipError_t launch_fwd_mfma(const StepArgs& a, hipStream_t st) {
     const int n_qtiles = (a.c + BM - 1) / BM;
-    const dim3 grid((unsigned)n_qtiles * a.B * a.H), block(64 * NW);
+    const dim3 grid((unsigned)n_qtiles * a.n_q * a.B * a.H), block(64 * NW);
     const bool part = a.d % 8 != 0;
     if (a.q_pos) {
         if (a.d == 64) launch_fwd_rope<64>(a, st, grid, block, n_qtiles);

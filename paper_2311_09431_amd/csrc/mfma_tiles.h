@@ -14,6 +14,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "striped_attn.h"
+
 namespace sa {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -118,6 +120,13 @@ __device__ inline dt_rsrc dt_make_rsrc(const void* matrix, int rows, int pitch, 
     r[3] = 0x00020000;
     return r;
 }
+// the same rows `bytes` further on (another device's shard)
+__device__ inline dt_rsrc dt_advance(dt_rsrc r, int64_t bytes) {
+    const uint64_t a = (((uint64_t)(uint32_t)r[1] << 32) | (uint32_t)r[0]) + (uint64_t)bytes;
+    r[0] = (int)(uint32_t)a;
+    r[1] = (int)((uint32_t)(a >> 32) & 0xffffu);
+    return r;
+}
 // one 1 KiB piece: 64 lanes x 16 bytes from matrix + tile_byte_offset + lane_offset to
 // lds_dst + 16 * lane (lds_dst wave-uniform)
 // (m0 is named as clobbered although the compiler calls it reserved: nothing else in these
@@ -204,6 +213,20 @@ __device__ inline void decode_block(int linear, int n_tiles, int n_bh, int& rank
     const int heads = min(HEAD_GROUP, n_bh - grp * HEAD_GROUP);
     rank = within / heads;
     bh = grp * HEAD_GROUP + (within - rank * heads);
+}
+
+// Rank of a (tile, device) pair -> both, heaviest first.  Striped blocks all have the same
+// shape, so the tile decides; contiguous ones are walked whole for every device further on, so
+// the device does.  tile_rank: 0 = the heaviest tile of a triangular block, dev_rank: 0 = the
+// device with the most blocks.
+__device__ inline void decode_rank(int rank, int n_tiles, int n_dev, int layout, int& tile_rank, int& dev_rank) {
+    if (layout == SA_STRIPED) {
+        tile_rank = rank / n_dev;
+        dev_rank = rank - tile_rank * n_dev;
+    } else {
+        dev_rank = rank / n_tiles;
+        tile_rank = rank - dev_rank * n_tiles;
+    }
 }
 
 // Row of d <= 16 NF elements (d a multiple of 4) as B-operand fragments, NF k-steps of 16,

@@ -12,6 +12,22 @@ namespace sa {
 // original token positions: striped a*N + dev, contiguous dev*c + a.
 enum MaskKind : int { MASK_EMPTY = 0, MASK_TRI = 1, MASK_FULL = 2 };
 
+// GetMask(j, k) in local indices (Sec. 2.2, 2.3): query a = original position j*c + a
+// (contiguous) or a*N + j (striped); key b likewise with k.  Allowed iff key position <= query
+// position, which reduces to b <= a - off.
+__host__ __device__ inline int block_kind(int q_dev, int kv_dev, int layout) {
+    if (layout == SA_STRIPED || q_dev == kv_dev) return MASK_TRI;
+    return q_dev < kv_dev ? MASK_EMPTY : MASK_FULL;
+}
+__host__ __device__ inline int block_off(int q_dev, int kv_dev, int layout) {
+    return layout == SA_STRIPED && kv_dev > q_dev ? 1 : 0;
+}
+
+// What a workgroup of the matrix-core kernels walks: one triangular or one full block (a ring
+// step; the mask form is then known when the kernel is compiled), or the blocks of several shards
+// one after the other without draining the pipeline between them.
+enum Walk : int { WALK_TRI = 0, WALK_FULL = 1, WALK_RING = 2 };
+
 struct StepArgs {
     const void* q;
     const void* k;
@@ -30,12 +46,17 @@ struct StepArgs {
     // strides of their own; equal to H and the strides above for plain multi-head attention
     int H_kv;
     int64_t kv_stride_b, kv_stride_h, kv_stride_s;
-    // dK/dV kernels run once per member of a group of H / H_kv query heads: this launch takes
-    // query head kv_head * (H / H_kv) + member
-    int member;
     float scale;
-    int kind;             // MaskKind (never MASK_EMPTY at launch)
-    int off;              // 0 or 1 when kind == MASK_TRI
+    // Blocks of this launch: query shards of devices q_dev .. q_dev + n_q - 1 against key shards
+    // of devices kv_dev .. kv_dev + n_kv - 1 (the pointers are those of the first of each; further
+    // ones follow q_shard / kv_shard elements on, statistics c rows on).  One ring step is 1 x 1
+    // (never an empty block); the ring drivers hand over all blocks of a device or of the ring at
+    // once, and each workgroup walks the other side's shards in the order of their device index.
+    int layout, q_dev, n_q, kv_dev, n_kv;
+    int64_t q_shard, kv_shard;
+    // results start from an empty state (forward) or zero accumulators (backward): nothing of
+    // o, lse, dq, dk, dv is read.  Otherwise they are folded into what is there.
+    bool fresh;
     // Emulated tile-skipping granularity (Sec. 3.1), MFMA kernels only: 0 = the kernel's own
     // (32 x 32); otherwise every sub-tile of a skip_bq x skip_bk tile of the block that holds
     // at least one allowed pair is computed (masked elements contribute exact zeros).
@@ -55,9 +76,10 @@ hipError_t launch_permute(const void* src, void* dst, int64_t outer, int64_t n_s
                           int64_t inner_bytes, int N, bool inverse, hipStream_t st);
 hipError_t launch_state_init(float* o, float* lse, const sa_shape& s, hipStream_t st);
 hipError_t launch_finalize(const float* o, void* out, const sa_shape& s, hipStream_t st);
+// rows: of each (batch, head), with the shape's strides; its c is not used
 hipError_t launch_bwd_preprocess(const float* o, const void* dout, float* delta,
-                                 const sa_shape& s, hipStream_t st);
-hipError_t launch_zero_f32(float* p, const sa_shape& s, hipStream_t st);
+                                 const sa_shape& s, int64_t rows, hipStream_t st);
+hipError_t launch_zero_f32(float* p, const sa_shape& s, int64_t rows, hipStream_t st);
 hipError_t launch_rope(const void* x, void* y, const int32_t* pos, int64_t pos_stride_b, const sa_shape& s,
                        float base, bool inverse, hipStream_t st);
 

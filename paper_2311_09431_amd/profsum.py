@@ -69,8 +69,8 @@ def counter_table(tag, agg):
     return out
 
 
-# triangular-step instantiations: fwd / dq <RAGGED=false, FULL=false, ...>, dkdv <TRI=true, RAGGED=false, ...>
-_TRI = {"fwd_mfma_kernel": "<false, false", "bwd_dq_mfma_kernel": "<false, false", "bwd_dkdv_mfma_kernel": "<true, false"}
+# triangular-step instantiations: fwd / dq <RAGGED=false, WALK=0, ...>, dkdv <WALK=0, RAGGED=false, ...>
+_TRI = {"fwd_mfma_kernel": "<false, 0", "bwd_dq_mfma_kernel": "<false, 0", "bwd_dkdv_mfma_kernel": "<0, false"}
 
 
 def traffic_lines(fetch, write):
