@@ -104,6 +104,13 @@ int check_skip(const sa_shape* s, int bq, int bk) {
                                                                                       : SA_ERR_SHAPE;
 }
 
+hipError_t launch_fwd(const StepArgs& a, int dtype, hipStream_t st) {
+    return sa::fwd_mfma_supported(a, dtype) ? sa::launch_fwd_mfma(a, st) : sa::launch_fwd_f32(a, dtype, st);
+}
+hipError_t launch_bwd(const StepArgs& a, int dtype, hipStream_t st) {
+    return sa::bwd_mfma_supported(a, dtype) ? sa::launch_bwd_mfma(a, st) : sa::launch_bwd_f32(a, dtype, st);
+}
+
 int step_fwd(const void* q, const void* k, const void* v, float* o, float* lse, int q_dev, int kv_dev,
              int layout, const sa_shape* s, int bq, int bk, hipStream_t st, const int32_t* q_pos = nullptr,
              int64_t pos_stride_b = 0, float rope_base = 0.f) {
@@ -115,9 +122,7 @@ int step_fwd(const void* q, const void* k, const void* v, float* o, float* lse, 
         a.q_pos = q_pos; a.pos_stride_b = pos_stride_b; a.rope_log2_base = log2((double)rope_base);
     }
     if (sa::block_kind(q_dev, kv_dev, layout) == sa::MASK_EMPTY) return SA_OK;   // nothing to launch
-    hipError_t e = sa::fwd_mfma_supported(a, s->dtype) ? sa::launch_fwd_mfma(a, st)
-                                                       : sa::launch_fwd_f32(a, s->dtype, st);
-    return e == hipSuccess ? SA_OK : SA_ERR_HIP;
+    return launch_fwd(a, s->dtype, st) == hipSuccess ? SA_OK : SA_ERR_HIP;
 }
 
 int step_bwd(const void* q, const void* k, const void* v, const void* dout, const float* lse,
@@ -128,16 +133,16 @@ int step_bwd(const void* q, const void* k, const void* v, const void* dout, cons
     a.skip_bq = bq; a.skip_bk = bk;
     a.q = q; a.k = k; a.v = v; a.dout = dout; a.lse = const_cast<float*>(lse); a.delta = delta;
     a.dq = dq; a.dk = dk; a.dv = dv;
-    hipError_t e = sa::bwd_mfma_supported(a, s->dtype) ? sa::launch_bwd_mfma(a, st)
-                                                       : sa::launch_bwd_f32(a, s->dtype, st);
-    return e == hipSuccess ? SA_OK : SA_ERR_HIP;
+    return launch_bwd(a, s->dtype, st) == hipSuccess ? SA_OK : SA_ERR_HIP;
 }
 
 // The ring drivers without per-step timings: one launch per kernel for all blocks of the played
-// devices, where the kernels' grids and the row counts stay within 31 bits (else, and when the
-// caller wants each step's time, one launch per block and kernel).
-bool one_launch(const StepArgs& a, int dtype, int N) {
-    return (int64_t)N * a.c < (int64_t(1) << 31) && sa::fwd_mfma_supported(a, dtype) && sa::bwd_mfma_supported(a, dtype);
+// devices, where row counts and grids (at worst one workgroup per 32 rows, two kinds of them in
+// the backward) stay within 31 bits.  Else, and when the caller wants each step's time, one launch
+// per block and kernel.
+bool one_launch(const sa_shape* s, int N) {
+    const int64_t most = int64_t(1) << 31;
+    return (int64_t)N * s->c < most && ((int64_t)s->c / 32 + 1) * N * s->B * s->H * 4 < most;
 }
 
 size_t elt_size(int dtype) { return dtype == SA_F32 ? 4 : 2; }
@@ -289,11 +294,11 @@ int sa_ring_fwd_tiled(const void* Q, const void* K, const void* V, float* O, flo
     const int j0 = q_dev_only >= 0 ? q_dev_only : 0, j1 = q_dev_only >= 0 ? q_dev_only + 1 : N;
     StepArgs all = make_args(shape, j0, 0, layout);
     all.n_q = j1 - j0; all.n_kv = N; all.q_shard = shard; all.kv_shard = kv_shard; all.fresh = true;
-    if (!step_ms && one_launch(all, shape->dtype, N)) {
+    if (!step_ms && one_launch(shape, N)) {
         all.q = in_at(Q, j0); all.k = K; all.v = V;
         all.o = O + j0 * shard; all.lse = LSE + (int64_t)j0 * shape->c;
         all.skip_bq = skip_bq; all.skip_bk = skip_bk;
-        return sa::launch_fwd_mfma(all, st) == hipSuccess ? SA_OK : SA_ERR_HIP;
+        return launch_fwd(all, shape->dtype, st) == hipSuccess ? SA_OK : SA_ERR_HIP;
     }
     for (int j = j0; j < j1; ++j)
         if (sa::launch_state_init(O + j * shard, LSE + (int64_t)j * shape->c, *shape, st) != hipSuccess)
@@ -349,7 +354,7 @@ int sa_ring_bwd_tiled(const void* Q, const void* K, const void* V, const void* d
     all.n_q = j1 - j0; all.q_shard = shard; all.kv_shard = kv_shard; all.fresh = true;
     // key shards that some played device sees; contiguous layout: none further on than the last
     all.n_kv = layout == SA_STRIPED ? N : j1;
-    if (!step_ms && one_launch(all, shape->dtype, N)) {
+    if (!step_ms && one_launch(shape, N)) {
         all.q = in_at(Q, j0); all.k = K; all.v = V; all.dout = in_at(dO, j0);
         all.lse = const_cast<float*>(LSE) + (int64_t)j0 * shape->c;
         all.delta = delta + (int64_t)j0 * shape->c;
@@ -362,7 +367,7 @@ int sa_ring_bwd_tiled(const void* Q, const void* K, const void* V, const void* d
             sa::launch_bwd_preprocess(O + j0 * shard, in_at(dO, j0), delta + (int64_t)j0 * shape->c, *shape,
                                       (int64_t)(j1 - j0) * shape->c, st) != hipSuccess)
             return SA_ERR_HIP;
-        return sa::launch_bwd_mfma(all, st) == hipSuccess ? SA_OK : SA_ERR_HIP;
+        return launch_bwd(all, shape->dtype, st) == hipSuccess ? SA_OK : SA_ERR_HIP;
     }
     if (!zero(dQ, shard, *shape, 0, N) || !zero(dK, kv_shard, kv_shape, 0, N) ||
         !zero(dV, kv_shard, kv_shape, 0, N))

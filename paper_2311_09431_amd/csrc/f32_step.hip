@@ -7,6 +7,10 @@
 // Measured against kernels with one wavefront per row and serial dot products on the vector ALU
 // (which they replace): whole ring forward + backward of 16 heads, d = 128, 4 x 2048 tokens, fp32
 // 575 -> 24.1 ms (1.7 -> 40 useful TFLOP/s); 4 x 64 tokens, one head 2.68 -> 0.53 ms.
+// A launch holds all blocks of the devices it plays and a workgroup walks the other side's shards
+// in turn, and the backward's two kinds of workgroups share a launch: 24.1 -> 12.1 ms (a block of
+// 2048 tokens and 16 heads is one 128-row workgroup per compute unit, and lasts as long as the
+// heaviest) and 0.53 -> 0.098 ms; step by step, 8 x 96 tokens, 32 heads, bf16 0.34 -> 0.26 ms.
 //
 // What bounds them: the fp32 matrix cores run at 1/16 of the bf16 rate (64 cycles per
 // instruction, 157 TFLOP/s on the chip), so one instruction leaves room for everything that
@@ -127,6 +131,11 @@ __device__ inline void accumulate(f32x16 (&acc)[NB], const float* rows, const f3
 __device__ inline float half_max(float x) { return fmaxf(x, __shfl_xor(x, 32)); }
 __device__ inline float half_sum(float x) { return x + __shfl_xor(x, 32); }
 
+// one past the last key shard that device dev's queries see
+__device__ inline int last_shard(const StepArgs& p, int dev) {
+    return p.layout == SA_STRIPED ? p.kv_dev + p.n_kv : min(p.kv_dev + p.n_kv, dev + 1);
+}
+
 // Workgroup -> (tile rank, head): ranks heaviest first over all heads.
 __device__ inline void decode(int linear, int n_heads, int& rank, int& head) {
     rank = linear / n_heads;
@@ -171,14 +180,13 @@ fwd_f32_kernel(StepArgs p, int n_tiles) {
     const int lane = threadIdx.x & 63, n = lane & 31, h = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int qw = wave / SPLIT, kw = wave % SPLIT;
-    int rank, bh;
+    int rank, bh, dev_rank;
     decode((int)blockIdx.x, p.B * p.H, rank, bh);
-    const int q0 = (n_tiles - 1 - rank) * 32 * OWN;
+    decode_rank(rank, n_tiles, p.n_q, p.layout, rank, dev_rank);
+    const int q0 = (n_tiles - 1 - rank) * 32 * OWN, dev_i = p.n_q - 1 - dev_rank, dev = p.q_dev + dev_i;
     const int b = bh / p.H, hd = bh - b * p.H, d = p.d;
-    const int64_t base = b * p.stride_b + hd * p.stride_h;
+    const int64_t base = b * p.stride_b + hd * p.stride_h + dev_i * p.q_shard;
     const int64_t kv_base = b * p.kv_stride_b + (hd / (p.H / p.H_kv)) * p.kv_stride_h;
-    const T* K = (const T*)p.k + kv_base;
-    const T* V = (const T*)p.v + kv_base;
 
     const int a_own = q0 + 32 * qw + n, a = min(a_own, p.c - 1);
     float4 qf[DP / 8];
@@ -188,49 +196,55 @@ fwd_f32_kernel(StepArgs p, int n_tiles) {
     for (int mb = 0; mb < NB; ++mb) acc[mb] = zero16();
     float m = -INFINITY, l = 0.f;           // l: this half-wave's share of the row sum
 
-    const bool full = block_kind(p.q_dev, p.kv_dev, p.layout) == MASK_FULL;
-    const int off = block_off(p.q_dev, p.kv_dev, p.layout);
-    const int last_key = full ? p.c - 1 : min(q0 + 32 * OWN, p.c) - 1 - off;          // for the workgroup
-    const int wave_last = full ? p.c - 1 : min(q0 + 32 * qw + 31, p.c - 1) - off;     // for the wavefront
-    const int lane_last = full ? p.c - 1 : a - off;
-    for (int t0 = 0; t0 <= last_key; t0 += TK) {
-        __syncthreads();
-        stage<T, DP, TK>(k_lds, K, p.kv_stride_s, t0, p.c, d);
-        stage<T, DP, TK>(v_lds, V, p.kv_stride_s, t0, p.c, d);
-        __syncthreads();
+    // the key shards one after the other; contiguous layout: none further on than the queries' own
+    const int kv_end = last_shard(p, dev);
+    for (int kv = p.kv_dev; kv < kv_end; ++kv) {
+        const T* K = (const T*)p.k + kv_base + (kv - p.kv_dev) * p.kv_shard;
+        const T* V = (const T*)p.v + kv_base + (kv - p.kv_dev) * p.kv_shard;
+        const bool full = block_kind(dev, kv, p.layout) == MASK_FULL;
+        const int off = block_off(dev, kv, p.layout);
+        const int last_key = full ? p.c - 1 : min(q0 + 32 * OWN, p.c) - 1 - off;          // for the workgroup
+        const int wave_last = full ? p.c - 1 : min(q0 + 32 * qw + 31, p.c - 1) - off;     // for the wavefront
+        const int lane_last = full ? p.c - 1 : a - off;
+        for (int t0 = 0; t0 <= last_key; t0 += TK) {
+            __syncthreads();
+            stage<T, DP, TK>(k_lds, K, p.kv_stride_s, t0, p.c, d);
+            stage<T, DP, TK>(v_lds, V, p.kv_stride_s, t0, p.c, d);
+            __syncthreads();
 #pragma unroll 1
-        for (int s = 0; s < SUB; ++s) {
-            const int at = 32 * (SUB * kw + s), key0 = t0 + at;
-            if (key0 > wave_last) break;
-            f32x16 x = scores<DP>(k_lds + at * lds_pitch(DP), qf, n, h);
-            float mx = -INFINITY;
+            for (int s = 0; s < SUB; ++s) {
+                const int at = 32 * (SUB * kw + s), key0 = t0 + at;
+                if (key0 > wave_last) break;
+                f32x16 x = scores<DP>(k_lds + at * lds_pitch(DP), qf, n, h);
+                float mx = -INFINITY;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                x[r] = key0 + reg_row(r, h) <= lane_last ? x[r] * p.scale : -INFINITY;
-                mx = fmaxf(mx, x[r]);
+                for (int r = 0; r < 16; ++r) {
+                    x[r] = key0 + reg_row(r, h) <= lane_last ? x[r] * p.scale : -INFINITY;
+                    mx = fmaxf(mx, x[r]);
+                }
+                const float m_new = fmaxf(m, half_max(mx));
+                const float ref = m_new == -INFINITY ? 0.f : m_new;         // a row without a key so far
+                const float alpha = expf(m - ref);
+                float sum = 0.f;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    x[r] = expf(x[r] - ref);
+                    sum += x[r];
+                }
+                l = l * alpha + sum;
+                if (__builtin_amdgcn_ballot_w64(m_new != m) != 0) {
+#pragma unroll
+                    for (int mb = 0; mb < NB; ++mb)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) acc[mb][r] *= alpha;
+                }
+                m = m_new;
+                accumulate<DP, NB>(acc, v_lds + at * lds_pitch(DP), x, n, h);
             }
-            const float m_new = fmaxf(m, half_max(mx));
-            const float ref = m_new == -INFINITY ? 0.f : m_new;         // a row without a key so far
-            const float alpha = expf(m - ref);
-            float sum = 0.f;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                x[r] = expf(x[r] - ref);
-                sum += x[r];
-            }
-            l = l * alpha + sum;
-            if (__builtin_amdgcn_ballot_w64(m_new != m) != 0) {
-#pragma unroll
-                for (int mb = 0; mb < NB; ++mb)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) acc[mb][r] *= alpha;
-            }
-            m = m_new;
-            accumulate<DP, NB>(acc, v_lds + at * lds_pitch(DP), x, n, h);
         }
     }
 
-    // fold the block's partial result into the running (O, LSE)
+    // fold the partial result into the running (O, LSE)
     float l_tot = half_sum(l);
     if (SPLIT > 1) {
         // common reference of the wavefronts that own these rows
@@ -260,14 +274,17 @@ fwd_f32_kernel(StepArgs p, int n_tiles) {
         __syncthreads();
         combine<SPLIT, NB>(acc, lds + qw * SPLIT * NB * 16 * 64, kw, lane);
     }
-    float* L = p.lse + b * p.stat_stride_b + hd * p.stat_stride_h + a;
-    const float old = *L;
+    float* L = p.lse + b * p.stat_stride_b + hd * p.stat_stride_h + (int64_t)dev_i * p.c + a;
+    const float old = p.fresh ? -INFINITY : *L;
     const float part = l_tot > 0.f ? m + logf(l_tot) : -INFINITY;
     const float top = fmaxf(old, part);
     if (SPLIT > 1) __syncthreads();         // every wavefront has read the old LSE
-    if (a_own >= p.c || part == -INFINITY) return;          // no row here, or no key seen: state unchanged
-    const float w_old = expf(old - top), w_part = expf(part - top), inv = 1.f / (w_old + w_part);
-    const float f_old = w_old * inv, f_part = w_part * inv / l_tot;
+    // no row here, or no key seen: state unchanged
+    if (a_own >= p.c || (part == -INFINITY && !p.fresh)) return;
+    const float ref = top == -INFINITY ? 0.f : top;
+    const float w_old = expf(old - ref), w_part = expf(part - ref), w_sum = w_old + w_part;
+    const float inv = w_sum > 0.f ? 1.f / w_sum : 0.f;
+    const float f_old = w_old * inv, f_part = l_tot > 0.f ? w_part * inv / l_tot : 0.f;
     float* O = p.o + base + (int64_t)a * p.stride_s;
 #pragma unroll
     for (int mb = 0; mb < NB; ++mb) {
@@ -287,12 +304,13 @@ fwd_f32_kernel(StepArgs p, int n_tiles) {
             *dst = x;
         }
     }
-    if (kw == 0 && h == 0) *L = top + logf(w_old + w_part);
+    if (kw == 0 && h == 0) *L = top + logf(w_sum);
 }
 
-// adds scale * acc to 32 owned rows (this lane's row at dst), column blocks mb0 ..
+// scale * acc to 32 owned rows (this lane's row at dst_row), added to what is there unless fresh
 template <int SPLIT, int NB>
-__device__ inline void add_rows(float* dst_row, const f32x16 (&acc)[NB], float scale, int col0, int d, int kw, int h) {
+__device__ inline void add_rows(float* dst_row, const f32x16 (&acc)[NB], float scale, int col0, int d, int kw, int h,
+                                bool fresh) {
 #pragma unroll
     for (int mb = 0; mb < NB; ++mb) {
         if (SPLIT > 1 && mb % SPLIT != kw) continue;
@@ -301,7 +319,7 @@ __device__ inline void add_rows(float* dst_row, const f32x16 (&acc)[NB], float s
             const int col = col0 + 32 * mb + 8 * g + 4 * h;
             if (col >= d) continue;
             float4* dst = reinterpret_cast<float4*>(dst_row + col);
-            float4 x = *dst;
+            float4 x = fresh ? make_float4(0.f, 0.f, 0.f, 0.f) : *dst;
             x.x = fmaf(scale, acc[mb][4 * g + 0], x.x); x.y = fmaf(scale, acc[mb][4 * g + 1], x.y);
             x.z = fmaf(scale, acc[mb][4 * g + 2], x.z); x.w = fmaf(scale, acc[mb][4 * g + 3], x.w);
             *dst = x;
@@ -311,25 +329,22 @@ __device__ inline void add_rows(float* dst_row, const f32x16 (&acc)[NB], float s
 
 // ----------------------------------------------------------------------- dQ
 template <typename T, int DP, int SPLIT>
-__global__ void __launch_bounds__(64 * WAVES, DP > 64 ? 1 : 2)
-bwd_dq_f32_kernel(StepArgs p, int n_tiles) {
+__device__ inline void bwd_dq(const StepArgs& p, int n_tiles, int linear, float* lds) {
     constexpr int OWN = WAVES / SPLIT, TK = tile_rows(SPLIT), SUB = subtiles(SPLIT), NB = DP / 32;
-    __shared__ __attribute__((aligned(16))) float lds[tile_floats<SPLIT, DP>()];
     float* const k_lds = lds;
     float* const v_lds = lds + TK * lds_pitch(DP);
 
     const int lane = threadIdx.x & 63, n = lane & 31, h = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int qw = wave / SPLIT, kw = wave % SPLIT;
-    int rank, bh;
-    decode((int)blockIdx.x, p.B * p.H, rank, bh);
-    const int q0 = (n_tiles - 1 - rank) * 32 * OWN;
+    int rank, bh, dev_rank;
+    decode(linear, p.B * p.H, rank, bh);
+    decode_rank(rank, n_tiles, p.n_q, p.layout, rank, dev_rank);
+    const int q0 = (n_tiles - 1 - rank) * 32 * OWN, dev_i = p.n_q - 1 - dev_rank, dev = p.q_dev + dev_i;
     const int b = bh / p.H, hd = bh - b * p.H, d = p.d;
-    const int64_t base = b * p.stride_b + hd * p.stride_h;
+    const int64_t base = b * p.stride_b + hd * p.stride_h + dev_i * p.q_shard;
     const int64_t kv_base = b * p.kv_stride_b + (hd / (p.H / p.H_kv)) * p.kv_stride_h;
-    const int64_t sbase = b * p.stat_stride_b + hd * p.stat_stride_h;
-    const T* K = (const T*)p.k + kv_base;
-    const T* V = (const T*)p.v + kv_base;
+    const int64_t sbase = b * p.stat_stride_b + hd * p.stat_stride_h + (int64_t)dev_i * p.c;
 
     const int a_own = q0 + 32 * qw + n, a = min(a_own, p.c - 1);
     float4 qf[DP / 8], gf[DP / 8];
@@ -340,28 +355,33 @@ bwd_dq_f32_kernel(StepArgs p, int n_tiles) {
 #pragma unroll
     for (int mb = 0; mb < NB; ++mb) acc[mb] = zero16();
 
-    const bool full = block_kind(p.q_dev, p.kv_dev, p.layout) == MASK_FULL;
-    const int off = block_off(p.q_dev, p.kv_dev, p.layout);
-    const int last_key = full ? p.c - 1 : min(q0 + 32 * OWN, p.c) - 1 - off;
-    const int wave_last = full ? p.c - 1 : min(q0 + 32 * qw + 31, p.c - 1) - off;
-    const int lane_last = full ? p.c - 1 : a - off;
-    for (int t0 = 0; t0 <= last_key; t0 += TK) {
-        __syncthreads();
-        stage<T, DP, TK>(k_lds, K, p.kv_stride_s, t0, p.c, d);
-        stage<T, DP, TK>(v_lds, V, p.kv_stride_s, t0, p.c, d);
-        __syncthreads();
+    const int kv_end = last_shard(p, dev);
+    for (int kv = p.kv_dev; kv < kv_end; ++kv) {
+        const T* K = (const T*)p.k + kv_base + (kv - p.kv_dev) * p.kv_shard;
+        const T* V = (const T*)p.v + kv_base + (kv - p.kv_dev) * p.kv_shard;
+        const bool full = block_kind(dev, kv, p.layout) == MASK_FULL;
+        const int off = block_off(dev, kv, p.layout);
+        const int last_key = full ? p.c - 1 : min(q0 + 32 * OWN, p.c) - 1 - off;
+        const int wave_last = full ? p.c - 1 : min(q0 + 32 * qw + 31, p.c - 1) - off;
+        const int lane_last = full ? p.c - 1 : a - off;
+        for (int t0 = 0; t0 <= last_key; t0 += TK) {
+            __syncthreads();
+            stage<T, DP, TK>(k_lds, K, p.kv_stride_s, t0, p.c, d);
+            stage<T, DP, TK>(v_lds, V, p.kv_stride_s, t0, p.c, d);
+            __syncthreads();
 #pragma unroll 1
-        for (int s = 0; s < SUB; ++s) {
-            const int at = 32 * (SUB * kw + s), key0 = t0 + at;
-            if (key0 > wave_last) break;
-            f32x16 x = scores<DP>(k_lds + at * lds_pitch(DP), qf, n, h);
-            const f32x16 dp = scores<DP>(v_lds + at * lds_pitch(DP), gf, n, h);
+            for (int s = 0; s < SUB; ++s) {
+                const int at = 32 * (SUB * kw + s), key0 = t0 + at;
+                if (key0 > wave_last) break;
+                f32x16 x = scores<DP>(k_lds + at * lds_pitch(DP), qf, n, h);
+                const f32x16 dp = scores<DP>(v_lds + at * lds_pitch(DP), gf, n, h);
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const float pr = key0 + reg_row(r, h) <= lane_last ? expf(x[r] * p.scale - lse) : 0.f;
-                x[r] = pr * (dp[r] - delta);
+                for (int r = 0; r < 16; ++r) {
+                    const float pr = key0 + reg_row(r, h) <= lane_last ? expf(x[r] * p.scale - lse) : 0.f;
+                    x[r] = pr * (dp[r] - delta);
+                }
+                accumulate<DP, NB>(acc, k_lds + at * lds_pitch(DP), x, n, h);
             }
-            accumulate<DP, NB>(acc, k_lds + at * lds_pitch(DP), x, n, h);
         }
     }
     if (SPLIT > 1) {
@@ -369,7 +389,7 @@ bwd_dq_f32_kernel(StepArgs p, int n_tiles) {
         combine<SPLIT, NB>(acc, lds + qw * SPLIT * NB * 16 * 64, kw, lane);
     }
     if (a_own >= p.c) return;
-    add_rows<SPLIT, NB>(p.dq + base + (int64_t)a * p.stride_s, acc, p.scale, 0, d, kw, h);
+    add_rows<SPLIT, NB>(p.dq + base + (int64_t)a * p.stride_s, acc, p.scale, 0, d, kw, h, p.fresh);
 }
 
 // -------------------------------------------------------------------- dK/dV
@@ -378,24 +398,23 @@ bwd_dq_f32_kernel(StepArgs p, int n_tiles) {
 // half of dK and dV (both halves beside K and V do not fit the registers) and scores are formed
 // once per half.
 template <typename T, int DP, int SPLIT>
-__global__ void __launch_bounds__(64 * WAVES, DP > 64 ? 1 : 2)
-bwd_dkdv_f32_kernel(StepArgs p, int n_tiles) {
+__device__ inline void bwd_dkdv(const StepArgs& p, int n_tiles, int linear, float* lds, float* stats) {
     constexpr int OWN = WAVES / SPLIT, TK = tile_rows(SPLIT), SUB = subtiles(SPLIT);
     constexpr int HALVES = DP > 128 ? 2 : 1, NB = DP / HALVES / 32;
-    __shared__ __attribute__((aligned(16))) float lds[tile_floats<SPLIT, DP>()];
-    __shared__ float stats[2 * TK];                     // LSE | delta of the tile's queries
     float* const q_lds = lds;
     float* const g_lds = lds + TK * lds_pitch(DP);
 
     const int lane = threadIdx.x & 63, n = lane & 31, h = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int own = wave / SPLIT, qsub = wave % SPLIT;
-    int tile, rest;                                     // low key tiles see most queries: first
-    decode((int)blockIdx.x, p.B * p.H_kv * HALVES, tile, rest);
+    int tile, rest, dev_i;                              // low key tiles see most queries: first
+    decode(linear, p.B * p.H_kv * HALVES, tile, rest);
+    decode_rank(tile, n_tiles, p.n_kv, p.layout, tile, dev_i);
+    const int dev = p.kv_dev + dev_i;
     const int bh = rest / HALVES, col0 = (rest - bh * HALVES) * 128;
     const int k0 = tile * 32 * OWN;
     const int b = bh / p.H_kv, kvh = bh - b * p.H_kv, group = p.H / p.H_kv, d = p.d;
-    const int64_t kv_base = b * p.kv_stride_b + kvh * p.kv_stride_h;
+    const int64_t kv_base = b * p.kv_stride_b + kvh * p.kv_stride_h + dev_i * p.kv_shard;
 
     const int key_own = k0 + 32 * own + n, key = min(key_own, p.c - 1);
     float4 kf[DP / 8], vf[DP / 8];
@@ -405,41 +424,46 @@ bwd_dkdv_f32_kernel(StepArgs p, int n_tiles) {
 #pragma unroll
     for (int mb = 0; mb < NB; ++mb) acck[mb] = accv[mb] = zero16();
 
-    const bool full = block_kind(p.q_dev, p.kv_dev, p.layout) == MASK_FULL;
-    const int off = block_off(p.q_dev, p.kv_dev, p.layout);
-    // queries a >= key + off see the key: from this sub-tile on for the workgroup, the wavefront
-    const int first_query = full ? 0 : k0 + off;
-    const int wave_first = full ? 0 : k0 + 32 * own + off;
-    const int lane_first = full ? 0 : key_own + off;
+    // contiguous layout: earlier devices' queries see nothing of these keys
+    const int q_dev0 = p.layout == SA_STRIPED ? p.q_dev : max(p.q_dev, dev);
     for (int member = 0; member < group; ++member) {
         const int hd = kvh * group + member;
-        const T* Q = (const T*)p.q + b * p.stride_b + hd * p.stride_h;
-        const T* G = (const T*)p.dout + b * p.stride_b + hd * p.stride_h;
-        const int64_t sbase = b * p.stat_stride_b + hd * p.stat_stride_h;
-        for (int t0 = first_query / 32 * 32; t0 < p.c; t0 += TK) {
-            __syncthreads();
-            stage<T, DP, TK>(q_lds, Q, p.stride_s, t0, p.c, d);
-            stage<T, DP, TK>(g_lds, G, p.stride_s, t0, p.c, d);
-            if (threadIdx.x < 2 * TK) {
-                const int row = min(t0 + (int)threadIdx.x % TK, p.c - 1);
-                stats[threadIdx.x] = threadIdx.x < TK ? p.lse[sbase + row] : p.delta[sbase + row];
-            }
-            __syncthreads();
-#pragma unroll 1
-            for (int s = 0; s < SUB; ++s) {
-                const int at = 32 * (SUB * qsub + s), a0 = t0 + at;
-                if (a0 >= p.c) break;
-                if (a0 + 31 < wave_first) continue;
-                const f32x16 x = scores<DP>(q_lds + at * lds_pitch(DP), kf, n, h);
-                f32x16 dp = scores<DP>(g_lds + at * lds_pitch(DP), vf, n, h), pr;
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int row = reg_row(r, h), a = a0 + row;
-                    pr[r] = a >= lane_first && a < p.c ? expf(x[r] * p.scale - stats[at + row]) : 0.f;
-                    dp[r] = pr[r] * (dp[r] - stats[TK + at + row]);
+        for (int q_dev = q_dev0; q_dev < p.q_dev + p.n_q; ++q_dev) {
+            const int64_t base = b * p.stride_b + hd * p.stride_h + (q_dev - p.q_dev) * p.q_shard;
+            const int64_t sbase = b * p.stat_stride_b + hd * p.stat_stride_h + (int64_t)(q_dev - p.q_dev) * p.c;
+            const T* Q = (const T*)p.q + base;
+            const T* G = (const T*)p.dout + base;
+            const bool full = block_kind(q_dev, dev, p.layout) == MASK_FULL;
+            const int off = block_off(q_dev, dev, p.layout);
+            // queries a >= key + off see the key: from this sub-tile on for the workgroup, the wavefront
+            const int first_query = full ? 0 : k0 + off;
+            const int wave_first = full ? 0 : k0 + 32 * own + off;
+            const int lane_first = full ? 0 : key_own + off;
+            for (int t0 = first_query / 32 * 32; t0 < p.c; t0 += TK) {
+                __syncthreads();
+                stage<T, DP, TK>(q_lds, Q, p.stride_s, t0, p.c, d);
+                stage<T, DP, TK>(g_lds, G, p.stride_s, t0, p.c, d);
+                if (threadIdx.x < 2 * TK) {
+                    const int row = min(t0 + (int)threadIdx.x % TK, p.c - 1);
+                    stats[threadIdx.x] = threadIdx.x < TK ? p.lse[sbase + row] : p.delta[sbase + row];
                 }
-                accumulate<DP, NB>(accv, g_lds + at * lds_pitch(DP) + col0, pr, n, h);
-                accumulate<DP, NB>(acck, q_lds + at * lds_pitch(DP) + col0, dp, n, h);
+                __syncthreads();
+#pragma unroll 1
+                for (int s = 0; s < SUB; ++s) {
+                    const int at = 32 * (SUB * qsub + s), a0 = t0 + at;
+                    if (a0 >= p.c) break;
+                    if (a0 + 31 < wave_first) continue;
+                    const f32x16 x = scores<DP>(q_lds + at * lds_pitch(DP), kf, n, h);
+                    f32x16 dp = scores<DP>(g_lds + at * lds_pitch(DP), vf, n, h), pr;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        const int row = reg_row(r, h), a = a0 + row;
+                        pr[r] = a >= lane_first && a < p.c ? expf(x[r] * p.scale - stats[at + row]) : 0.f;
+                        dp[r] = pr[r] * (dp[r] - stats[TK + at + row]);
+                    }
+                    accumulate<DP, NB>(accv, g_lds + at * lds_pitch(DP) + col0, pr, n, h);
+                    accumulate<DP, NB>(acck, q_lds + at * lds_pitch(DP) + col0, dp, n, h);
+                }
             }
         }
     }
@@ -452,8 +476,20 @@ bwd_dkdv_f32_kernel(StepArgs p, int n_tiles) {
     }
     if (key_own >= p.c) return;
     const int64_t row = kv_base + (int64_t)key * p.kv_stride_s;
-    add_rows<SPLIT, NB>(p.dv + row, accv, 1.f, col0, d, qsub, h);
-    add_rows<SPLIT, NB>(p.dk + row, acck, p.scale, col0, d, qsub, h);
+    add_rows<SPLIT, NB>(p.dv + row, accv, 1.f, col0, d, qsub, h, p.fresh);
+    add_rows<SPLIT, NB>(p.dk + row, acck, p.scale, col0, d, qsub, h, p.fresh);
+}
+
+// Both in one launch (KEYS and QUERIES): workgroups 0 .. n_dkdv - 1 own keys, the others queries.
+// They share nothing but the inputs; where neither fills the chip they run beside each other, and
+// a step is one launch less.  At 256 columns each by itself: together they spill registers.
+template <typename T, int DP, int SPLIT, bool KEYS, bool QUERIES>
+__global__ void __launch_bounds__(64 * WAVES, DP > 64 ? 1 : 2)
+bwd_f32_kernel(StepArgs p, int n_tiles, int n_dkdv) {
+    __shared__ __attribute__((aligned(16))) float lds[tile_floats<SPLIT, DP>()];
+    __shared__ float stats[KEYS ? 2 * tile_rows(SPLIT) : 1];        // LSE | delta of a tile's queries
+    if (KEYS && (!QUERIES || (int)blockIdx.x < n_dkdv)) bwd_dkdv<T, DP, SPLIT>(p, n_tiles, (int)blockIdx.x, lds, stats);
+    else if (QUERIES) bwd_dq<T, DP, SPLIT>(p, n_tiles, (int)blockIdx.x - (KEYS ? n_dkdv : 0), lds);
 }
 
 // ----------------------------------------------------------------- dispatch
@@ -464,26 +500,32 @@ constexpr int64_t kFullGrid = 256;
 template <typename T, int DP, int SPLIT>
 hipError_t run_fwd(const StepArgs& a, hipStream_t st) {
     const int rows = 32 * (WAVES / SPLIT), n_tiles = (a.c + rows - 1) / rows;
-    hipLaunchKernelGGL((fwd_f32_kernel<T, DP, SPLIT>), dim3((unsigned)n_tiles * a.B * a.H), dim3(64 * WAVES), 0, st,
-                       a, n_tiles);
+    hipLaunchKernelGGL((fwd_f32_kernel<T, DP, SPLIT>), dim3((unsigned)n_tiles * a.n_q * a.B * a.H), dim3(64 * WAVES),
+                       0, st, a, n_tiles);
     return hipGetLastError();
 }
 template <typename T, int DP, int SPLIT>
 hipError_t run_bwd(const StepArgs& a, hipStream_t st) {
     const int rows = 32 * (WAVES / SPLIT), n_tiles = (a.c + rows - 1) / rows;
-    hipLaunchKernelGGL((bwd_dq_f32_kernel<T, DP, SPLIT>), dim3((unsigned)n_tiles * a.B * a.H), dim3(64 * WAVES), 0,
-                       st, a, n_tiles);
-    if (hipError_t e = hipGetLastError()) return e;
-    hipLaunchKernelGGL((bwd_dkdv_f32_kernel<T, DP, SPLIT>),
-                       dim3((unsigned)n_tiles * a.B * a.H_kv * (DP > 128 ? 2 : 1)), dim3(64 * WAVES), 0, st, a,
-                       n_tiles);
+    const int n_dkdv = n_tiles * a.n_kv * a.B * a.H_kv * (DP > 128 ? 2 : 1), n_dq = n_tiles * a.n_q * a.B * a.H;
+    const dim3 block(64 * WAVES);
+    if constexpr (DP <= 128) {
+        hipLaunchKernelGGL((bwd_f32_kernel<T, DP, SPLIT, true, true>), dim3((unsigned)(n_dkdv + n_dq)), block, 0, st, a,
+                           n_tiles, n_dkdv);
+    } else {
+        hipLaunchKernelGGL((bwd_f32_kernel<T, DP, SPLIT, false, true>), dim3((unsigned)n_dq), block, 0, st, a, n_tiles,
+                           0);
+        if (hipError_t e = hipGetLastError()) return e;
+        hipLaunchKernelGGL((bwd_f32_kernel<T, DP, SPLIT, true, false>), dim3((unsigned)n_dkdv), block, 0, st, a,
+                           n_tiles, n_dkdv);
+    }
     return hipGetLastError();
 }
 
 template <typename T, int DP>
 hipError_t run(const StepArgs& a, bool backward, hipStream_t st) {
     constexpr int MOST = DP > 128 ? 2 : 4;          // what 160 KiB of LDS hold
-    const bool split = (int64_t)((a.c + 127) / 128) * a.B * a.H < kFullGrid;
+    const bool split = (int64_t)((a.c + 127) / 128) * a.n_q * a.B * a.H < kFullGrid;
     if (backward) return split ? run_bwd<T, DP, MOST>(a, st) : run_bwd<T, DP, 1>(a, st);
     return split ? run_fwd<T, DP, MOST>(a, st) : run_fwd<T, DP, 1>(a, st);
 }

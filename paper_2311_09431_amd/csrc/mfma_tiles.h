@@ -14,8 +14,6 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#include "striped_attn.h"
-
 namespace sa {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -213,20 +211,6 @@ __device__ inline void decode_block(int linear, int n_tiles, int n_bh, int& rank
     const int heads = min(HEAD_GROUP, n_bh - grp * HEAD_GROUP);
     rank = within / heads;
     bh = grp * HEAD_GROUP + (within - rank * heads);
-}
-
-// Rank of a (tile, device) pair -> both, heaviest first.  Striped blocks all have the same
-// shape, so the tile decides; contiguous ones are walked whole for every device further on, so
-// the device does.  tile_rank: 0 = the heaviest tile of a triangular block, dev_rank: 0 = the
-// device with the most blocks.
-__device__ inline void decode_rank(int rank, int n_tiles, int n_dev, int layout, int& tile_rank, int& dev_rank) {
-    if (layout == SA_STRIPED) {
-        tile_rank = rank / n_dev;
-        dev_rank = rank - tile_rank * n_dev;
-    } else {
-        dev_rank = rank / n_tiles;
-        tile_rank = rank - dev_rank * n_tiles;
-    }
 }
 
 // Row of d <= 16 NF elements (d a multiple of 4) as B-operand fragments, NF k-steps of 16,

@@ -28,6 +28,20 @@ __host__ __device__ inline int block_off(int q_dev, int kv_dev, int layout) {
 // one after the other without draining the pipeline between them.
 enum Walk : int { WALK_TRI = 0, WALK_FULL = 1, WALK_RING = 2 };
 
+// Rank of a (tile, device) pair -> both, heaviest first.  Striped blocks all have the same
+// shape, so the tile decides; contiguous ones are walked whole for every device further on, so
+// the device does.  tile_rank: 0 = the heaviest tile of a triangular block, dev_rank: 0 = the
+// device with the most blocks.
+__device__ inline void decode_rank(int rank, int n_tiles, int n_dev, int layout, int& tile_rank, int& dev_rank) {
+    if (layout == SA_STRIPED) {
+        tile_rank = rank / n_dev;
+        dev_rank = rank - tile_rank * n_dev;
+    } else {
+        dev_rank = rank / n_tiles;
+        tile_rank = rank - dev_rank * n_tiles;
+    }
+}
+
 struct StepArgs {
     const void* q;
     const void* k;
