@@ -16,7 +16,7 @@ LIB = os.path.join(HERE, "libstriped_attn.so")
 OBJ_DIR = os.path.join(ROOT, "_build")
 
 SOURCES = ["api.hip", "permute.hip", "elementwise.hip", "f32_step.hip", "fwd_mfma.hip",
-           "bwd_mfma.hip"]
+           "bwd_mfma.hip", "split_mfma.hip"]
 
 # packed fp32 VALU forms are switched off on purpose for the test machines
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-fno-gpu-rdc",

@@ -105,10 +105,12 @@ int check_skip(const sa_shape* s, int bq, int bk) {
 }
 
 hipError_t launch_fwd(const StepArgs& a, int dtype, hipStream_t st) {
-    return sa::fwd_mfma_supported(a, dtype) ? sa::launch_fwd_mfma(a, st) : sa::launch_fwd_f32(a, dtype, st);
+    if (!sa::fwd_mfma_supported(a, dtype)) return sa::launch_fwd_f32(a, dtype, st);
+    return sa::launch_fwd_mfma(a, st);
 }
 hipError_t launch_bwd(const StepArgs& a, int dtype, hipStream_t st) {
-    return sa::bwd_mfma_supported(a, dtype) ? sa::launch_bwd_mfma(a, st) : sa::launch_bwd_f32(a, dtype, st);
+    if (!sa::bwd_mfma_supported(a, dtype)) return sa::launch_bwd_f32(a, dtype, st);
+    return sa::bwd_split_wanted(a) ? sa::launch_bwd_split(a, st) : sa::launch_bwd_mfma(a, st);
 }
 
 int step_fwd(const void* q, const void* k, const void* v, float* o, float* lse, int q_dev, int kv_dev,

@@ -127,21 +127,20 @@ __device__ inline void dq_step(f32x16& s_cur, f32x16& dp_cur, f32x16& s_next, f3
 // and are removed by the mask.
 // WALK: one block, or (WALK_RING) the blocks of several key shards one after the other, as in
 // the forward kernel: dQ stays in registers over all of them.
+// lds: four tile buffers (two 128-column halves each when DP = 256)
 template <bool RAGGED, int WALK, int DP, bool PART>
-__global__ void __launch_bounds__(256, DP > 128 ? 1 : 2)
-bwd_dq_mfma_kernel(StepArgs p, int n_tiles) {
+__device__ __forceinline__ void bwd_dq(const StepArgs& p, int n_tiles, int linear, char* lds) {
     constexpr int NH = halves_of(DP), KS = ksteps_of(DP), MB = halves_of(DP) * blocks_of(DP);      // k-steps per half, column blocks
-    // one LDS object per tile buffer (two 128-column halves each when DP = 256)
-    __shared__ __attribute__((aligned(1024))) char k_lds0[DT_BYTES * NH];
-    __shared__ __attribute__((aligned(1024))) char k_lds1[DT_BYTES * NH];
-    __shared__ __attribute__((aligned(1024))) char v_lds0[DT_BYTES * NH];
-    __shared__ __attribute__((aligned(1024))) char v_lds1[DT_BYTES * NH];
+    char* const k_lds0 = lds;
+    char* const k_lds1 = lds + DT_BYTES * NH;
+    char* const v_lds0 = lds + 2 * DT_BYTES * NH;
+    char* const v_lds1 = lds + 3 * DT_BYTES * NH;
 
     const int tid = threadIdx.x, lane = tid & 63, n = lane & 31, h = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);      // wave-uniform, kept scalar
     constexpr bool RING = WALK == WALK_RING;
     int rank, bh, dev = p.q_dev;
-    decode_block<true>((int)blockIdx.x, RING ? n_tiles * p.n_q : n_tiles, p.B * p.H, rank, bh);
+    decode_block<true>(linear, RING ? n_tiles * p.n_q : n_tiles, p.B * p.H, rank, bh);
     if (RING) {
         int dev_rank;
         decode_rank(rank, n_tiles, p.n_q, p.layout, rank, dev_rank);
@@ -308,7 +307,7 @@ bwd_dq_mfma_kernel(StepArgs p, int n_tiles) {
             const int col = 32 * mb + 8 * g + 4 * h;
             if (col >= d || !row_ok) continue;            // padding columns, rows beyond the shard
             float4* dst = reinterpret_cast<float4*>(DQ + (int64_t)a * ss + col);
-            float4 x = RING ? make_float4(0.f, 0.f, 0.f, 0.f) : *dst;       // a ring walk is all of dQ
+            float4 x = RING && p.fresh ? make_float4(0.f, 0.f, 0.f, 0.f) : *dst;
             x.x = fmaf(p.scale, acc[mb][4 * g + 0], x.x); x.y = fmaf(p.scale, acc[mb][4 * g + 1], x.y);
             x.z = fmaf(p.scale, acc[mb][4 * g + 2], x.z); x.w = fmaf(p.scale, acc[mb][4 * g + 3], x.w);
             *dst = x;
@@ -491,23 +490,21 @@ __device__ inline void dkdv_step(f32x16& s_cur, f32x16& dp_cur, f32x16& s_next, 
 // WALK: one block, or (WALK_RING) several one after the other with dK and dV in registers from the
 // first to the last: the query heads that share this key/value head, each with the query shards of
 // the devices that see these keys.
+// lds: four tile buffers (two 128-column halves each when DP = 256), stat: KV_STAT_FLOATS floats
 template <int WALK, bool RAGGED, int DP, bool PART>
-__global__ void __launch_bounds__(256, 1)
-bwd_dkdv_mfma_kernel(StepArgs p, int n_tiles) {
+__device__ __forceinline__ void bwd_dkdv(const StepArgs& p, int n_tiles, int linear, char* lds, float* stat) {
     constexpr int NH = halves_of(DP), KS = ksteps_of(DP), MB = blocks_of(DP);      // per half
-    // one LDS object per tile buffer (two 128-column halves each when DP = 256)
-    __shared__ __attribute__((aligned(1024))) char q_lds0[DT_BYTES * NH];
-    __shared__ __attribute__((aligned(1024))) char q_lds1[DT_BYTES * NH];
-    __shared__ __attribute__((aligned(1024))) char g_lds0[DT_BYTES * NH];
-    __shared__ __attribute__((aligned(1024))) char g_lds1[DT_BYTES * NH];
-    __shared__ __attribute__((aligned(16))) float stat[KV_STAT_FLOATS];
+    char* const q_lds0 = lds;
+    char* const q_lds1 = lds + DT_BYTES * NH;
+    char* const g_lds0 = lds + 2 * DT_BYTES * NH;
+    char* const g_lds1 = lds + 3 * DT_BYTES * NH;
 
     const int tid = threadIdx.x, lane = tid & 63, n = lane & 31, h = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);      // wave-uniform, kept scalar
     constexpr bool RING = WALK == WALK_RING;
     int ktile, bhh, dev = p.kv_dev;               // triangular blocks: low key tiles see most queries: first
     // one workgroup per (key tile, device, batch, key/value head, 128-column half of dK / dV)
-    decode_block<false>((int)blockIdx.x, RING ? n_tiles * p.n_kv : n_tiles, p.B * p.H_kv * NH, ktile, bhh);
+    decode_block<false>(linear, RING ? n_tiles * p.n_kv : n_tiles, p.B * p.H_kv * NH, ktile, bhh);
     if (RING) {
         int dev_rank;
         decode_rank(ktile, n_tiles, p.n_kv, p.layout, ktile, dev_rank);
@@ -734,6 +731,34 @@ bwd_dkdv_mfma_kernel(StepArgs p, int n_tiles) {
         }
 }
 
+template <bool RAGGED, int WALK, int DP, bool PART>
+__global__ void __launch_bounds__(256, DP > 128 ? 1 : 2)
+bwd_dq_mfma_kernel(StepArgs p, int n_tiles) {
+    __shared__ __attribute__((aligned(1024))) char lds[4 * DT_BYTES * halves_of(DP)];
+    bwd_dq<RAGGED, WALK, DP, PART>(p, n_tiles, (int)blockIdx.x, lds);
+}
+template <int WALK, bool RAGGED, int DP, bool PART>
+__global__ void __launch_bounds__(256, 1)
+bwd_dkdv_mfma_kernel(StepArgs p, int n_tiles) {
+    __shared__ __attribute__((aligned(1024))) char lds[4 * DT_BYTES * halves_of(DP)];
+    __shared__ __attribute__((aligned(16))) float stat[KV_STAT_FLOATS];
+    bwd_dkdv<WALK, RAGGED, DP, PART>(p, n_tiles, (int)blockIdx.x, lds, stat);
+}
+// Both kinds of workgroups in one launch, the two sequences of n_dkdv and n_dq evenly interleaved
+// (each heaviest first): where the key-owning ones do not fill the chip, or fill it once and last
+// as long as the heaviest, the query-owning ones run beside and behind them instead of after.
+// One workgroup per compute unit (the key-owning side's registers).
+template <bool RAGGED, int DP, bool PART>
+__global__ void __launch_bounds__(256, 1)
+bwd_both_mfma_kernel(StepArgs p, int n_tiles, int n_dkdv, int n_dq) {
+    __shared__ __attribute__((aligned(1024))) char lds[4 * DT_BYTES * halves_of(DP)];
+    __shared__ __attribute__((aligned(16))) float stat[KV_STAT_FLOATS];
+    const int total = n_dkdv + n_dq, before = (int)((int64_t)blockIdx.x * n_dkdv / total);
+    const bool keys = (int)(((int64_t)blockIdx.x + 1) * n_dkdv / total) > before;
+    if (keys) bwd_dkdv<WALK_RING, RAGGED, DP, PART>(p, n_tiles, before, lds, stat);
+    else bwd_dq<RAGGED, WALK_RING, DP, PART>(p, n_tiles, (int)blockIdx.x - before, lds);
+}
+
 }  // namespace
 
 bool bwd_mfma_supported(const StepArgs& a, int dtype) {
@@ -764,8 +789,30 @@ void launch_dkdv(const StepArgs& a, hipStream_t st, int n_tiles) {
     else hipLaunchKernelGGL((bwd_dkdv_mfma_kernel<WALK, false, DP, PART>), grid, block, 0, st, a, n_tiles);
 }
 template <int DP, bool PART>
+void launch_both(const StepArgs& a, hipStream_t st, int n_tiles) {
+    const int n_dkdv = n_tiles * a.n_kv * a.B * a.H_kv * halves_of(DP), n_dq = n_tiles * a.n_q * a.B * a.H;
+    const dim3 grid((unsigned)(n_dkdv + n_dq)), block(256);
+    if (a.c % BM) hipLaunchKernelGGL((bwd_both_mfma_kernel<true, DP, PART>), grid, block, 0, st, a, n_tiles, n_dkdv, n_dq);
+    else hipLaunchKernelGGL((bwd_both_mfma_kernel<false, DP, PART>), grid, block, 0, st, a, n_tiles, n_dkdv, n_dq);
+}
+// Both kinds of workgroups in one launch.  Measured per backward step (d 128, one launch against
+// two, us): uneven work up to one key-owning workgroup per compute unit: 2048 x 2048 triangular,
+// 2 heads 60 / 102, 8 heads 66 / 106, 16 heads (256 workgroups) 92 / 115, 24 heads 137 / 131; 32
+// query heads on 8 key/value heads, 4096 x 4096, 515 / 642.  Even work (a full block) has no
+// tail to fill, only idle compute units: 128 + 128 workgroups 75 / 108, 256 + 256 144 / 133.
+// d 256 (two key-owning workgroups per tile): 256 of them 109 / 189, 512 207 / 225.
+template <int DP>
+bool want_both(const StepArgs& a, int n_tiles) {
+    const int64_t keys = (int64_t)n_tiles * a.n_kv * a.B * a.H_kv * halves_of(DP), queries = (int64_t)n_tiles * a.n_q * a.B * a.H;
+    return uneven(a) ? keys <= N_CU * halves_of(DP) : keys + queries <= N_CU;
+}
+template <int DP, bool PART>
 hipError_t launch_bwd_variant(const StepArgs& a, hipStream_t st) {
     const int n_tiles = (a.c + BM - 1) / BM;
+    if (want_both<DP>(a, n_tiles)) {
+        launch_both<DP, PART>(a, st, n_tiles);
+        return hipGetLastError();
+    }
     const bool one_block = a.n_q == 1 && a.n_kv == 1 && !a.fresh;
     const bool full = block_kind(a.q_dev, a.kv_dev, a.layout) == MASK_FULL;
     if (!one_block) launch_dq<WALK_RING, DP, PART>(a, st, n_tiles);

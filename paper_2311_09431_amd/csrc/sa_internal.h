@@ -85,6 +85,10 @@ struct StepArgs {
     double rope_log2_base;
 };
 
+// The workgroups of a launch carry uneven work: triangular blocks, or contiguous blocks of
+// several query devices (a key shard is seen by the devices from its own on).
+inline bool uneven(const StepArgs& a) { return a.layout == SA_STRIPED || a.n_q > 1 || a.q_dev == a.kv_dev; }
+
 // launchers: return hipSuccess or the launch error
 hipError_t launch_permute(const void* src, void* dst, int64_t outer, int64_t n_seq,
                           int64_t inner_bytes, int N, bool inverse, hipStream_t st);
@@ -104,5 +108,7 @@ bool fwd_mfma_rope_supported(const StepArgs& a, int dtype);
 hipError_t launch_fwd_mfma(const StepArgs& a, hipStream_t st);
 bool bwd_mfma_supported(const StepArgs& a, int dtype);
 hipError_t launch_bwd_mfma(const StepArgs& a, hipStream_t st);
+bool bwd_split_wanted(const StepArgs& a);
+hipError_t launch_bwd_split(const StepArgs& a, hipStream_t st);
 
 }  // namespace sa

@@ -1,0 +1,396 @@
+// Backward ring step for launches that leave most of the chip idle with 128-row workgroups (bf16
+// matrix cores, head dimension up to 128, blocks of at least 128 rows): same operands, same
+// products and same precision as bwd_mfma.hip, other split of the work.
+//
+// What bounds such a launch is the walk of one workgroup: about 1.4 us (dQ) or 1.7 us (dK/dV) per
+// 64 streamed rows, however few workgroups there are.  Here a workgroup owns 32 rows and its four
+// wavefronts take the 32-row sub-tiles of each 128-row group of the streamed side, one each; the
+// partial results meet in LDS at the end.  Four times the workgroups and a walk of about 2 us per
+// 128 rows; groups are double buffered, one barrier per group.  Nothing is interleaved by hand and
+// a tile load feeds a quarter of the products, so a fuller chip is better served by the other
+// kernels (figures at bwd_split_wanted).  Whole ring, 4 x 1024 tokens, 2 heads, forward +
+// backward: 272 -> 162 us.  A forward kernel of this form was no faster than the 128-row one
+// (37 us both for 2048 x 2048, 2 heads).
+//
+// The wavefront that takes a sub-tile is given by the sub-tile's place in its shard, so summation
+// orders are fixed and the same under emulated coarse skipping.
+#include <hip/hip_bf16.h>
+
+#include "mfma_tiles.h"
+#include "sa_internal.h"
+
+namespace sa {
+
+namespace {
+
+constexpr int WAVES = 4, OWN = 32, GROUP = 32 * WAVES;
+constexpr int SUB_BYTES = DT_BYTES / 2;                      // 32 rows
+constexpr int GROUP_BYTES = 2 * DT_BYTES;                    // one operand's 128 rows
+
+// what every kernel of this file keeps per lane
+struct Lane {
+    int lane, n, h, wave;
+    uint32_t arow[8], tr0[4], tr1[4];
+    __device__ Lane() {
+        lane = threadIdx.x & 63;
+        n = lane & 31;
+        h = lane >> 5;
+        wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+        dt_row_addrs(arow, n, h);
+        dt_tr_addrs(tr0, tr1, lane);
+    }
+};
+
+// 128 rows starting at row first, as two 64-row tiles (rows beyond the matrix arrive as zeros)
+__device__ inline void load_group(dt_rsrc m, int first, int pitch, char* lds, const uint32_t (&gl)[4], int wave) {
+    dt_load(m, first * pitch, lds, gl, wave);
+    dt_load(m, (first + DT_ROWS) * pitch, lds + DT_BYTES, gl, wave);
+}
+
+__device__ inline f32x16 zero16() {
+    f32x16 z;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) z[r] = 0.f;
+    return z;
+}
+// streamed row (within a 32-row sub-tile) of score register r
+__device__ inline int reg_row(int r, int h) { return 8 * (r / 4) + 4 * h + r % 4; }
+
+// 32 x 32 scores: rows = the sub-tile at `rows`, columns = the owned rows
+template <int DP, bool PART>
+__device__ inline f32x16 scores(const char* rows, const bf16x8 (&f)[8], const Lane& ln, int part_ks) {
+    f32x16 s = zero16();
+#pragma unroll
+    for (int ks = 0; ks < ksteps_of(DP); ++ks) {
+        const bf16x8 x = dt_read_row(rows, ln.arow[ks]);
+        s = mfma(PART ? zero_beyond_d(x, ks == part_ks) : x, f[ks], s);
+    }
+    return s;
+}
+// acc (32-column blocks x owned rows) += streamed^T w
+template <int DP>
+__device__ inline void accumulate(f32x16 (&acc)[4], const char* rows, const bf16x8 (&w)[2], const Lane& ln) {
+#pragma unroll
+    for (int g = 0; g < 2; ++g)
+#pragma unroll
+        for (int mb = 0; mb < blocks_of(DP); ++mb)
+            acc[mb] = mfma(dt_read_tr(rows + g * 16 * 256, ln.tr0[mb], ln.tr1[mb]), w[g], acc[mb]);
+}
+
+// Sum of the four wavefronts' accumulators through LDS: each writes its own (16 KiB at DP = 128)
+// and takes registers 4 wave .. + 3 of every block of the sum, i.e. columns
+// 32 mb + 8 wave + 4 h .. + 3 of its lane's row.
+template <int DP>
+__device__ inline void put_partial(char* buf, const f32x16 (&acc)[4], const Lane& ln) {
+    float4* mine = reinterpret_cast<float4*>(buf) + ln.wave * blocks_of(DP) * 4 * 64;
+#pragma unroll
+    for (int mb = 0; mb < blocks_of(DP); ++mb)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+            mine[(mb * 4 + g) * 64 + ln.lane] =
+                make_float4(acc[mb][4 * g], acc[mb][4 * g + 1], acc[mb][4 * g + 2], acc[mb][4 * g + 3]);
+}
+template <int DP>
+__device__ inline float4 take_sum(const char* buf, int mb, const Lane& ln) {
+    const float4* at = reinterpret_cast<const float4*>(buf) + (mb * 4 + ln.wave) * 64 + ln.lane;
+    float4 x = at[0];
+#pragma unroll
+    for (int w = 1; w < WAVES; ++w) {
+        const float4 y = at[w * blocks_of(DP) * 4 * 64];
+        x.x += y.x; x.y += y.y; x.z += y.z; x.w += y.w;
+    }
+    return x;
+}
+
+// one past the last key shard that device dev's queries see
+__device__ inline int last_shard(const StepArgs& p, int dev) {
+    return p.layout == SA_STRIPED ? p.kv_dev + p.n_kv : min(p.kv_dev + p.n_kv, dev + 1);
+}
+// last key of a block that the workgroup of queries q0 .. q0 + 31 looks at: the last allowed one,
+// or under emulated coarse skipping the last one of the skip_bk-wide tile that shares an allowed
+// pair with its skip_bq-tall tile
+__device__ inline int last_key_of(const StepArgs& p, int q0, bool full, int off) {
+    if (full) return p.c - 1;
+    if (p.skip_bq > 0) {
+        const int q_hi = (q0 / p.skip_bq + 1) * p.skip_bq - 1;
+        return min(p.c, ((q_hi - off) / p.skip_bk + 1) * p.skip_bk) - 1;
+    }
+    return min(q0 + OWN, p.c) - 1 - off;
+}
+
+// The walk of a query-owning workgroup over the 128-key groups of its shards.  body(k, v, g0):
+// one group, its keys at LDS addresses k, v, the first one key g0 of the present block.
+struct Block { int kv; bool full; int off, last_key; };
+template <typename Body>
+__device__ inline void walk_keys(const StepArgs& p, int dev, int q0, dt_rsrc K, dt_rsrc V, char* lds, const Lane& ln,
+                                 Body body) {
+    const int pitch = 2 * (int)p.kv_stride_s, kv_end = last_shard(p, dev);
+    uint32_t gl[4];
+    dt_load_offsets(gl, ln.lane, ln.wave, pitch, p.d);
+    auto block = [&](int kv) {
+        Block b;
+        b.kv = kv;
+        b.full = block_kind(dev, kv, p.layout) == MASK_FULL;
+        b.off = block_off(dev, kv, p.layout);
+        b.last_key = last_key_of(p, q0, b.full, b.off);
+        return b;
+    };
+    Block now = block(p.kv_dev);
+    int g0 = 0, parity = 0;
+    load_group(K, 0, pitch, lds, gl, ln.wave);
+    load_group(V, 0, pitch, lds + GROUP_BYTES, gl, ln.wave);
+    for (;;) {
+        Block next = now;
+        int next_g0 = g0 + GROUP;
+        if (next_g0 > now.last_key) {
+            next_g0 = 0;
+            next.kv = now.kv + 1;
+        }
+        const bool more = next.kv < kv_end;
+        __builtin_amdgcn_s_waitcnt(0);         // this group has landed (vmcnt) ...
+        __syncthreads();                       // ... for every wavefront, and all are done with the last one
+        if (more) {
+            if (next.kv != now.kv) {
+                next = block(next.kv);
+                K = dt_advance(K, 2 * p.kv_shard);
+                V = dt_advance(V, 2 * p.kv_shard);
+            }
+            char* to = lds + (1 - parity) * 2 * GROUP_BYTES;
+            load_group(K, next_g0, pitch, to, gl, ln.wave);
+            load_group(V, next_g0, pitch, to + GROUP_BYTES, gl, ln.wave);
+        }
+        const char* k = lds + parity * 2 * GROUP_BYTES + ln.wave * SUB_BYTES;
+        if (g0 + OWN * ln.wave <= now.last_key) body(k, k + GROUP_BYTES, g0 + OWN * ln.wave, now);
+        if (!more) break;
+        now = next;
+        g0 = next_g0;
+        parity ^= 1;
+    }
+}
+
+// Workgroup -> (32-row tile rank, head), ranks heaviest first over all heads
+__device__ inline void decode(int linear, int n_heads, int& rank, int& head) {
+    rank = linear / n_heads;
+    head = linear - rank * n_heads;
+}
+
+// adds scale * (sum of the partial results at buf) to the lane's row, or stores it (fresh)
+template <int DP>
+__device__ inline void add_rows(float* row, const char* buf, float scale, int d, bool fresh, const Lane& ln) {
+#pragma unroll
+    for (int mb = 0; mb < blocks_of(DP); ++mb) {
+        const int col = 32 * mb + 8 * ln.wave + 4 * ln.h;
+        if (col >= d) continue;
+        float4* dst = reinterpret_cast<float4*>(row + col);
+        const float4 s = take_sum<DP>(buf, mb, ln);
+        float4 x = fresh ? make_float4(0.f, 0.f, 0.f, 0.f) : *dst;
+        x.x = fmaf(scale, s.x, x.x); x.y = fmaf(scale, s.y, x.y);
+        x.z = fmaf(scale, s.z, x.z); x.w = fmaf(scale, s.w, x.w);
+        *dst = x;
+    }
+}
+
+// ----------------------------------------------------------------------- dQ
+template <int DP, bool PART>
+__device__ inline void bwd_dq(const StepArgs& p, int n_tiles, int linear, char* lds) {
+    const Lane ln;
+    const int n = ln.n, h = ln.h;
+    int rank, bh, dev_rank;
+    decode(linear, p.B * p.H, rank, bh);
+    decode_rank(rank, n_tiles, p.n_q, p.layout, rank, dev_rank);
+    const int q0 = (n_tiles - 1 - rank) * OWN, dev_i = p.n_q - 1 - dev_rank, dev = p.q_dev + dev_i;
+    const int b = bh / p.H, hd = bh - b * p.H, d = p.d;
+    const int64_t base = b * p.stride_b + hd * p.stride_h + dev_i * p.q_shard;
+    const int64_t kv_base = b * p.kv_stride_b + (hd / (p.H / p.H_kv)) * p.kv_stride_h;
+    const int64_t sbase = b * p.stat_stride_b + hd * p.stat_stride_h + (int64_t)dev_i * p.c;
+    const int pitch = 2 * (int)p.kv_stride_s;
+
+    const int a_own = q0 + n, a = min(a_own, p.c - 1);
+    bf16x8 qf[8], gf[8];
+    load_b_frags<8>(qf, (const __bf16*)p.q + base + (int64_t)a * p.stride_s, h, d);
+    load_b_frags<8>(gf, (const __bf16*)p.dout + base + (int64_t)a * p.stride_s, h, d);
+    const float lse2 = p.lse[sbase + a] * LOG2E, delta = p.delta[sbase + a], kappa = p.scale * LOG2E;
+    const int part_ks = (PART && ((d >> 3) & 1) == h) ? (d >> 4) : -1;
+    f32x16 acc[4];
+#pragma unroll
+    for (int mb = 0; mb < 4; ++mb) acc[mb] = zero16();
+
+    walk_keys(p, dev, q0, dt_make_rsrc((const __bf16*)p.k + kv_base, p.c, pitch, d),
+              dt_make_rsrc((const __bf16*)p.v + kv_base, p.c, pitch, d), lds, ln,
+              [&](const char* k, const char* v, int key0, const Block& blk) {
+        const f32x16 s = scores<DP, PART>(k, qf, ln, part_ks), dp = scores<DP, PART>(v, gf, ln, part_ks);
+        const int lane_last = (blk.full ? p.c - 1 : a_own - blk.off) - key0;
+        bf16x8 ds[2];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            float pr = __builtin_amdgcn_exp2f(fmaf(s[r], kappa, -lse2));
+            if (reg_row(r, h) > lane_last) pr = 0.f;
+            ds[r / 8][r % 8] = (__bf16)(pr * (dp[r] - delta));
+        }
+        accumulate<DP>(acc, k, ds, ln);
+    });
+
+    __syncthreads();
+    put_partial<DP>(lds, acc, ln);
+    __syncthreads();
+    if (a_own < p.c) add_rows<DP>(p.dq + base + (int64_t)a * p.stride_s, lds, p.scale, d, p.fresh, ln);
+}
+
+// -------------------------------------------------------------------- dK/dV
+// Owned rows are keys, the streamed groups 128 queries with their LSE and delta beside them; the
+// query heads that share the key/value head and the query shards that see it come one after the
+// other.
+template <int DP, bool PART>
+__device__ inline void bwd_dkdv(const StepArgs& p, int n_tiles, int linear, char* lds, float* stats) {
+    const Lane ln;
+    const int n = ln.n, h = ln.h, tid = threadIdx.x;
+    int tile, bh, dev_i;                                // low key tiles see most queries: first
+    decode(linear, p.B * p.H_kv, tile, bh);
+    decode_rank(tile, n_tiles, p.n_kv, p.layout, tile, dev_i);
+    const int k0 = tile * OWN, dev = p.kv_dev + dev_i;
+    const int b = bh / p.H_kv, kvh = bh - b * p.H_kv, group = p.H / p.H_kv, d = p.d;
+    const int64_t kv_base = b * p.kv_stride_b + kvh * p.kv_stride_h + dev_i * p.kv_shard;
+    const int pitch = 2 * (int)p.stride_s;
+
+    const int key_own = k0 + n, key = min(key_own, p.c - 1);
+    const int64_t row = kv_base + (int64_t)key * p.kv_stride_s;
+    bf16x8 kf[8], vf[8];
+    load_b_frags<8>(kf, (const __bf16*)p.k + row, h, d);
+    load_b_frags<8>(vf, (const __bf16*)p.v + row, h, d);
+    const float kappa = p.scale * LOG2E;
+    const int part_ks = (PART && ((d >> 3) & 1) == h) ? (d >> 4) : -1;
+    f32x16 acck[4], accv[4];
+#pragma unroll
+    for (int mb = 0; mb < 4; ++mb) acck[mb] = accv[mb] = zero16();
+    uint32_t gl[4];
+    dt_load_offsets(gl, ln.lane, ln.wave, pitch, d);
+
+    // the block being walked: query head and shard, its queries' first group, sub-tile and mask
+    const int q_dev0 = p.layout == SA_STRIPED ? p.q_dev : max(p.q_dev, dev);
+    int member = 0, q_dev = q_dev0, first, off;
+    bool full;
+    dt_rsrc Q, G;
+    const float* stat_src;          // this thread's statistic: LSE (threads 0..127) or delta of a group's row
+    auto enter_block = [&]() {
+        const int hd = kvh * group + member;
+        full = block_kind(q_dev, dev, p.layout) == MASK_FULL;
+        off = block_off(q_dev, dev, p.layout);
+        // first query a workgroup of these keys looks at (emulated coarse skipping: from the first
+        // skip_bq-tall tile that shares an allowed pair with the keys' skip_bk-wide one)
+        first = full ? 0 : k0;
+        if (!full && p.skip_bq > 0) first = (k0 / p.skip_bk * p.skip_bk + off) / p.skip_bq * p.skip_bq;
+        const int64_t base = b * p.stride_b + hd * p.stride_h + (q_dev - p.q_dev) * p.q_shard;
+        Q = dt_make_rsrc((const __bf16*)p.q + base, p.c, pitch, d);
+        G = dt_make_rsrc((const __bf16*)p.dout + base, p.c, pitch, d);
+        stat_src = (tid < GROUP ? p.lse : p.delta) + b * p.stat_stride_b + hd * p.stat_stride_h +
+                   (int64_t)(q_dev - p.q_dev) * p.c;
+    };
+    float stat;
+    auto request = [&](int g0, char* to) {
+        load_group(Q, g0, pitch, to, gl, ln.wave);
+        load_group(G, g0, pitch, to + GROUP_BYTES, gl, ln.wave);
+        // rows beyond the shard arrive as zeros; LSE = +inf makes their P and dS zero
+        const int r = g0 + (tid & (GROUP - 1));
+        stat = stat_src[min(r, p.c - 1)];
+        if (tid < GROUP) stat = r < p.c ? stat * LOG2E : INFINITY;
+    };
+    enter_block();
+    int g0 = first / GROUP * GROUP, parity = 0;
+    request(g0, lds);
+    for (;;) {
+        const int now_first = first, lane_first = full ? 0 : key_own + off;
+        int next_g0 = g0 + GROUP;
+        bool more = next_g0 < p.c;
+        __builtin_amdgcn_s_waitcnt(0);
+        stats[parity * 2 * GROUP + tid] = stat;
+        __syncthreads();
+        if (!more) {
+            if (++q_dev == p.q_dev + p.n_q) {
+                q_dev = q_dev0;
+                ++member;
+            }
+            more = member < group;
+            if (more) {
+                enter_block();
+                next_g0 = first / GROUP * GROUP;
+            }
+        }
+        if (more) request(next_g0, lds + (1 - parity) * 2 * GROUP_BYTES);
+        const int a0 = g0 + OWN * ln.wave;
+        if (a0 + 31 >= now_first && a0 < p.c) {
+            const char* q = lds + parity * 2 * GROUP_BYTES + ln.wave * SUB_BYTES;
+            const char* g = q + GROUP_BYTES;
+            const float* st = stats + parity * 2 * GROUP + OWN * ln.wave;
+            const f32x16 s = scores<DP, PART>(q, kf, ln, part_ks), dp = scores<DP, PART>(g, vf, ln, part_ks);
+            bf16x8 pb[2], ds[2];
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int i = reg_row(r, h);
+                float pr = __builtin_amdgcn_exp2f(fmaf(s[r], kappa, -st[i]));
+                if (a0 + i < lane_first) pr = 0.f;
+                pb[r / 8][r % 8] = (__bf16)pr;
+                ds[r / 8][r % 8] = (__bf16)(pr * (dp[r] - st[GROUP + i]));
+            }
+            accumulate<DP>(accv, g, pb, ln);
+            accumulate<DP>(acck, q, ds, ln);
+        }
+        if (!more) break;
+        g0 = next_g0;
+        parity ^= 1;
+    }
+
+    constexpr int HALF = 2 * GROUP_BYTES;               // 4 wavefronts x 16 KiB
+    __syncthreads();
+    put_partial<DP>(lds, accv, ln);
+    put_partial<DP>(lds + HALF, acck, ln);
+    __syncthreads();
+    if (key_own >= p.c) return;
+    add_rows<DP>(p.dv + row, lds, 1.f, d, p.fresh, ln);
+    add_rows<DP>(p.dk + row, lds + HALF, p.scale, d, p.fresh, ln);
+}
+
+// Both in one launch, the two sequences of n_dkdv key-owning and n_dq query-owning workgroups
+// evenly interleaved (each heaviest first): they share nothing but the inputs.
+template <int DP, bool PART>
+__global__ void __launch_bounds__(64 * WAVES, 1)
+bwd_split_kernel(StepArgs p, int n_tiles, int n_dkdv, int n_dq) {
+    __shared__ __attribute__((aligned(1024))) char lds[4 * GROUP_BYTES];
+    __shared__ float stats[2 * 2 * GROUP];                              // [buffer][LSE | delta][row]
+    const int total = n_dkdv + n_dq, before = (int)((int64_t)blockIdx.x * n_dkdv / total);
+    const bool keys = (int)(((int64_t)blockIdx.x + 1) * n_dkdv / total) > before;
+    if (keys) bwd_dkdv<DP, PART>(p, n_tiles, before, lds, stats);
+    else bwd_dq<DP, PART>(p, n_tiles, (int)blockIdx.x - before, lds);
+}
+
+template <int DP, bool PART>
+hipError_t run(const StepArgs& a, hipStream_t st) {
+    const int n_tiles = (a.c + OWN - 1) / OWN;
+    const int n_dkdv = n_tiles * a.n_kv * a.B * a.H_kv, n_dq = n_tiles * a.n_q * a.B * a.H;
+    hipLaunchKernelGGL((bwd_split_kernel<DP, PART>), dim3((unsigned)(n_dkdv + n_dq)), dim3(64 * WAVES), 0, st, a, n_tiles,
+                       n_dkdv, n_dq);
+    return hipGetLastError();
+}
+template <int DP>
+hipError_t run(const StepArgs& a, hipStream_t st) {
+    return a.d % 8 ? run<DP, true>(a, st) : run<DP, false>(a, st);
+}
+
+}  // namespace
+
+// (of shapes that the 128-row matrix-core kernels take.)  Measured against both kinds of 128-row
+// workgroups in one launch, us per backward step, d 128: triangular 2048 x 2048, 2 heads (32
+// 128-row tiles) 38 / 60, 4 heads 46 / 62, 6 heads 71 / 65; 8192 x 8192, one head 131 / 193, two
+// 254 / 207.  Full blocks have twice the work: 2 heads 40 / 61, 4 heads 71 / 65.  Few key/value
+// heads, 32 query heads on one, 8192 x 8192 triangular: 4464 / 6131.
+bool bwd_split_wanted(const StepArgs& a) {
+    const int64_t tiles = (int64_t)((a.c + 127) / 128) * a.B;
+    const int64_t keys = tiles * a.n_kv * a.H_kv, queries = tiles * a.n_q * a.H;
+    return a.d <= TD && (uneven(a) ? keys <= 64 : keys + queries <= 64);
+}
+hipError_t launch_bwd_split(const StepArgs& a, hipStream_t st) {
+    if (a.d <= 64) return run<64>(a, st);
+    if (a.d <= 112) return run<112>(a, st);
+    return run<128>(a, st);
+}
+
+}  // namespace sa

@@ -1,0 +1,66 @@
+"""Backward steps on both sides of the rules that choose the split of the work: 32-row workgroups
+(few rows), both kinds of 128-row workgroups in one launch, one launch each.  Against the oracle at
+the edges of the tiles: blocks of exactly one tile, one row more, a last tile of one row, partial
+16-byte chunks, grouped heads, triangular (both offsets) and full blocks."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2311_09431_amd import binding as sa
+from paper_2311_09431_amd import inputs
+from tests import helpers as hp
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # B, H, H_kv, c, d: 128-row tiles of the key-owning side
+    (1, 1, 1, 128, 128),        # 1
+    (1, 2, 2, 129, 64),         # 4
+    (1, 3, 3, 257, 100),        # 9, last tile of one row
+    (2, 2, 1, 384, 112),        # 6, grouped heads
+    (1, 16, 16, 512, 36),       # 64: last split for uneven work, not for full blocks
+    (1, 13, 13, 640, 128),      # 65
+    (1, 32, 4, 256, 128),       # 8 keys, 64 queries: full blocks beyond the split
+    (1, 64, 64, 512, 64),       # 256: last one launch for uneven work, not for full blocks
+    (1, 43, 43, 768, 128),      # 258: one launch each
+    (1, 24, 24, 520, 256),      # two key-owning workgroups per tile: 240 of 512
+    (1, 3, 3, 130, 200),
+]
+
+
+@pytest.mark.parametrize("q_dev,kv_dev,layout", [(1, 0, sa.STRIPED), (0, 1, sa.STRIPED), (1, 0, sa.CONTIGUOUS)])
+@pytest.mark.parametrize("B,H,Hkv,c,d", CASES)
+def test_step_against_the_oracle(B, H, Hkv, c, d, q_dev, kv_dev, layout):
+    # one block, softmax over the block alone (LSE and delta of it), two heads checked
+    scale, dt = 1.0 / np.sqrt(d), torch.bfloat16
+    q, g = (inputs.gaussian((B, H, c, d), 60 + c + i, dt) for i in (0, 1))
+    k, v = (inputs.gaussian((B, Hkv, c, d), 70 + c + i, dt) for i in (0, 1))
+    a, b = np.arange(c)[:, None], np.arange(c)[None, :]
+    allowed = (b <= a - (kv_dev > q_dev)) if layout == sa.STRIPED else np.ones((c, c), bool)
+    gq, gg, gk, gv = (x.cuda() for x in (q, g, k, v))
+    f32 = dict(dtype=torch.float32, device="cuda")
+    o, lse, delta = torch.empty(B, H, c, d, **f32), torch.empty(B, H, c, **f32), torch.empty(B, H, c, **f32)
+    dq, dk, dv = torch.zeros(B, H, c, d, **f32), torch.zeros(B, Hkv, c, d, **f32), torch.zeros(B, Hkv, c, d, **f32)
+    shape = sa.shard_shape(gq, c, lse, kv=gk if Hkv != H else None)
+    sa.sa_state_init(o, lse, shape)
+    sa.sa_attn_step_fwd(gq, gk, gv, o, lse, q_dev, kv_dev, 2, layout, shape)
+    # a row without a key has LSE = -inf and no P; any finite LSE stands for it
+    lse = torch.where(torch.isinf(lse), torch.zeros_like(lse), lse)
+    sa.sa_bwd_preprocess(o, gg, delta, shape)
+    sa.sa_attn_step_bwd(gq, gk, gv, gg, lse, delta, dq, dk, dv, q_dev, kv_dev, 2, layout, shape)
+    torch.cuda.synchronize()
+    group = H // Hkv
+    for kvh in {0, Hkv - 1}:
+        wk, wv = np.zeros((c, d)), np.zeros((c, d))
+        for h in range(kvh * group, (kvh + 1) * group):
+            x = {n: inputs.to_f64(t[B - 1, i]) for n, t, i in (("q", q, h), ("g", g, h), ("k", k, kvh), ("v", v, kvh))}
+            s = np.where(allowed, x["q"] @ x["k"].T * scale, -np.inf)
+            p = np.exp(s - np.where(allowed.any(1), s.max(1, initial=-np.inf, where=allowed), 0.0)[:, None])
+            p /= np.maximum(p.sum(1, keepdims=True), 1e-300)
+            dp = x["g"] @ x["v"].T
+            ds = p * (dp - (p * dp).sum(1, keepdims=True))
+            wk += scale * ds.T @ x["q"]
+            wv += p.T @ x["g"]
+            hp.check_grad("dQ", dq[B - 1, h].cpu().numpy(), scale * ds @ x["k"], True)
+        hp.check_grad("dK", dk[B - 1, kvh].cpu().numpy(), wk, True)
+        hp.check_grad("dV", dv[B - 1, kvh].cpu().numpy(), wv, True)
