@@ -16,7 +16,12 @@ LIB = os.path.join(HERE, "libstriped_attn.so")
 OBJ_DIR = os.path.join(ROOT, "_build")
 
 SOURCES = ["api.hip", "permute.hip", "elementwise.hip", "f32_step.hip", "fwd_mfma.hip",
-           "bwd_mfma.hip", "split_mfma.hip"]
+           "bwd_mfma.hip", "split_mfma.hip", "f32x3_step.hip"]
+
+# Flags of single sources.  f32x3_step: score tiles are read by vector instructions right after
+# their products, so MFMA results stay out of the accumulation registers (forward 2.20 -> 2.10 ms,
+# backward 6.7 -> 6.1 ms for 16 heads, d 128, 4 x 2048 tokens).
+SOURCE_FLAGS = {"f32x3_step.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
 
 # packed fp32 VALU forms are switched off on purpose for the test machines
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-fno-gpu-rdc",
@@ -34,7 +39,7 @@ def _hipcc():
 
 def _compile(src, extra):
     obj = os.path.join(OBJ_DIR, os.path.splitext(src)[0] + ".o")
-    cmd = [_hipcc(), *FLAGS, *extra, "-c", os.path.join(CSRC, src), "-o", obj]
+    cmd = [_hipcc(), *FLAGS, *SOURCE_FLAGS.get(src, []), *extra, "-c", os.path.join(CSRC, src), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode:
         raise RuntimeError("hipcc failed on %s:\n%s\n%s" % (src, r.stdout, r.stderr))

@@ -526,6 +526,8 @@ template <typename T, int DP>
 hipError_t run(const StepArgs& a, bool backward, hipStream_t st) {
     constexpr int MOST = DP > 128 ? 2 : 4;          // what 160 KiB of LDS hold
     const bool split = (int64_t)((a.c + 127) / 128) * a.n_q * a.B * a.H < kFullGrid;
+    if constexpr (DP <= 128 && sizeof(T) == 4)      // fuller fp32 launches: f32x3_wanted
+        return backward ? run_bwd<T, DP, MOST>(a, st) : run_fwd<T, DP, MOST>(a, st);
     if (backward) return split ? run_bwd<T, DP, MOST>(a, st) : run_bwd<T, DP, 1>(a, st);
     return split ? run_fwd<T, DP, MOST>(a, st) : run_fwd<T, DP, 1>(a, st);
 }
@@ -540,9 +542,11 @@ hipError_t run(const StepArgs& a, bool backward, hipStream_t st) {
 }  // namespace
 
 hipError_t launch_fwd_f32(const StepArgs& a, int dtype, hipStream_t st) {
+    if (dtype == SA_F32 && f32x3_wanted(a)) return launch_f32x3(a, false, st);
     return dtype == SA_F32 ? run<float>(a, false, st) : run<__hip_bfloat16>(a, false, st);
 }
 hipError_t launch_bwd_f32(const StepArgs& a, int dtype, hipStream_t st) {
+    if (dtype == SA_F32 && f32x3_wanted(a)) return launch_f32x3(a, true, st);
     return dtype == SA_F32 ? run<float>(a, true, st) : run<__hip_bfloat16>(a, true, st);
 }
 

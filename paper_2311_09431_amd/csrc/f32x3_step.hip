@@ -1,0 +1,551 @@
+// Ring-step kernels for fp32 operands on the bf16 matrix cores, head dimension up to 128, launches
+// with enough 128-row workgroups to fill the chip.
+//
+// The fp32 matrix cores run at a sixteenth of the bf16 rate.  A fp32 number is the sum of three
+// bf16 ones (each the rounding of what the ones before leave: 3 x 8 bits and two signs cover its 24
+// bits), and a product of two such sums needs six of the nine bf16 products: the three dropped
+// ones, mid x lo twice and lo x lo, are below 2^-26 of the whole, a quarter of fp32's own rounding.  So
+// every product of the step is six v_mfma_f32_32x32x16_bf16 with fp32 accumulation, six
+// sixteenths of the time of the fp32 instruction.  Error against 64 bits (2-norm of the error over
+// that of the result; one head, 2048 tokens, d 128), fp32 instruction -> here: O 3.7e-7 -> 1.8e-7,
+// dQ 5.4e-7 -> 3.3e-7, dK 7.1e-7 -> 3.7e-7, dV 6.4e-7 -> 3.4e-7.  Whole ring, 16 heads, d 128,
+// 4 x 2048 tokens, forward + backward: 12.1 -> 7.9 ms.
+//
+// Everything else is as in f32_step.hip: transposed scores, a score register is the B operand of
+// the product over the streamed rows, one wavefront owns 32 rows, four make a workgroup.  The
+// owned rows sit in registers as three bf16 operands; the streamed ones go global -> registers (a
+// tile ahead) -> split -> three swizzled bf16 planes in LDS, two buffers, one barrier per 32-row
+// tile.
+#include "mfma_tiles.h"
+#include "sa_internal.h"
+
+namespace sa {
+
+namespace {
+
+constexpr int TILE = 32;
+constexpr int PLANE = TILE * 256, OPERAND = 3 * PLANE, BUFFER = 2 * OPERAND;
+
+typedef bf16x8 bf16x8x3[3];
+
+// Wavefronts of a workgroup.  Eight share the splitting of a tile and hide each other's latency,
+// which the forward kernel's registers allow (256 a wavefront): whole ring above, forward, 2.09 ms
+// with four, 1.57 with eight; but 0.23 against 0.29 where eight leave half of the chip idle
+// (256 row tiles of 128).  The backward's three terms of two owned operands take 512 registers.
+constexpr int BWD_WAVES = 4;
+
+__device__ inline f32x16 zero16() {
+    f32x16 z;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) z[r] = 0.f;
+    return z;
+}
+// streamed row (within a tile) of score register r
+__device__ inline int reg_row(int r, int h) { return 8 * (r / 4) + 4 * h + r % 4; }
+
+// x = hi + mid + lo (+ less than 2^-26 x).  An infinite x, or one that rounds to an infinite hi, is
+// its hi.
+__device__ inline void split(float x, __bf16& hi, __bf16& mid, __bf16& lo) {
+    hi = (__bf16)x;
+    float r = x - (float)hi;
+    mid = (__bf16)r;
+    lo = (__bf16)(r - (float)mid);
+}
+__device__ inline void split_any(float x, __bf16& hi, __bf16& mid, __bf16& lo) {
+    hi = (__bf16)x;
+    float r = x - (float)hi;
+    r = fabsf(r) < INFINITY ? r : 0.f;
+    mid = (__bf16)r;
+    lo = (__bf16)(r - (float)mid);
+}
+
+// 8 consecutive floats of a row from column col on, zeros from column d on (d a multiple of 4)
+struct Chunk { float4 a, b; };
+__device__ inline Chunk load_chunk(const float* row, int col, int d, bool ok) {
+    const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
+    Chunk x = {z, z};
+    if (ok && col < d) x.a = *reinterpret_cast<const float4*>(row + col);
+    if (ok && col + 4 < d) x.b = *reinterpret_cast<const float4*>(row + col + 4);
+    return x;
+}
+__device__ inline void split_chunk(const Chunk& x, bf16x8 (&o)[3]) {
+    const float v[8] = {x.a.x, x.a.y, x.a.z, x.a.w, x.b.x, x.b.y, x.b.z, x.b.w};
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        __bf16 hi, mid, lo;
+        split_any(v[e], hi, mid, lo);
+        o[0][e] = hi; o[1][e] = mid; o[2][e] = lo;
+    }
+}
+// registers first .. first + 7 of a score tile as B operands
+__device__ inline void split_regs(const f32x16& x, int first, bf16x8 (&o)[3]) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        __bf16 hi, mid, lo;
+        split(x[first + e], hi, mid, lo);
+        o[0][e] = hi; o[1][e] = mid; o[2][e] = lo;
+    }
+}
+// a b = hi + lo: the leading product, and the five others smallest first
+__device__ inline void mfma6(const bf16x8 (&a)[3], const bf16x8 (&b)[3], f32x16& hi, f32x16& lo) {
+    lo = mfma(a[1], b[1], lo);
+    lo = mfma(a[2], b[0], lo);
+    hi = mfma(a[0], b[0], hi);
+    lo = mfma(a[0], b[2], lo);
+    lo = mfma(a[1], b[0], lo);
+    lo = mfma(a[0], b[1], lo);
+}
+
+// an owned row as B operands
+template <int KS>
+__device__ inline void load_row(bf16x8x3 (&f)[KS], const float* row, int h, int d) {
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) split_chunk(load_chunk(row, 16 * ks + 8 * h, d, true), f[ks]);
+}
+
+// What a thread stages of a tile: chunks tid, tid + THREADS, ... of 8 columns, row-major
+template <int DP, int WAVES>
+struct Staged {
+    static constexpr int PER_ROW = DP / 8, CHUNKS = TILE * PER_ROW, THREADS = 64 * WAVES;
+    static constexpr int N = (CHUNKS + THREADS - 1) / THREADS;
+    static constexpr bool SOME_IDLE = CHUNKS % THREADS != 0;
+    Chunk x[N];
+    __device__ inline void fetch(const float* m, int64_t ss, int first, int c, int d) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const int at = (int)threadIdx.x + i * THREADS, row = first + at / PER_ROW;
+            if (SOME_IDLE && at >= CHUNKS) continue;
+            x[i] = load_chunk(m + (int64_t)min(row, c - 1) * ss, 8 * (at % PER_ROW), d, row < c);
+        }
+    }
+    __device__ inline void put(char* lds) const {
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const int at = (int)threadIdx.x + i * THREADS, row = at / PER_ROW, chunk = at % PER_ROW;
+            if (SOME_IDLE && at >= CHUNKS) continue;
+            bf16x8 o[3];
+            split_chunk(x[i], o);
+            char* to = lds + row * 256 + ((chunk ^ dt_swz(row)) << 4);
+#pragma unroll
+            for (int p = 0; p < 3; ++p) *reinterpret_cast<bf16x8*>(to + p * PLANE) = o[p];
+        }
+    }
+};
+
+struct Lane {
+    int lane, n, h, wave;
+    uint32_t arow[8], tr0[4], tr1[4];
+    __device__ Lane() {
+        lane = threadIdx.x & 63;
+        n = lane & 31;
+        h = lane >> 5;
+        wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+        dt_row_addrs(arow, n, h);
+        dt_tr_addrs(tr0, tr1, lane);
+    }
+};
+
+// 32 x 32 scores: rows = the tile at `planes`, columns = the wavefront's owned rows.  An infinite
+// operand makes the leading products infinite with the right sign and the others anything.
+template <int KS>
+__device__ inline f32x16 scores(const char* planes, const bf16x8x3 (&f)[KS], const Lane& ln) {
+    f32x16 hi = zero16(), lo = zero16();
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+        bf16x8 a[3];
+#pragma unroll
+        for (int p = 0; p < 3; ++p) a[p] = dt_read_row(planes + p * PLANE, ln.arow[ks]);
+        mfma6(a, f[ks], hi, lo);
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) hi[r] = fabsf(hi[r]) < INFINITY ? hi[r] + lo[r] : hi[r];
+    return hi;
+}
+// acc (32-column blocks x owned rows) += tile^T w.  The tile's sum is formed by itself and added
+// once: the instruction does not round its sums to nearest, and against the accumulator's
+// magnitude that error is larger than the fp32 instruction's (dV of 2048 rows: 8.5e-7 against
+// 6.4e-7; this way 3.4e-7).
+template <int NB>
+__device__ inline void accumulate(f32x16 (&acc)[NB], const char* planes, const f32x16& w, const Lane& ln) {
+    bf16x8 b[2][3];
+#pragma unroll
+    for (int g = 0; g < 2; ++g) split_regs(w, 8 * g, b[g]);
+#pragma unroll
+    for (int mb = 0; mb < NB; ++mb) {
+        f32x16 t = zero16();
+#pragma unroll
+        for (int g = 0; g < 2; ++g) {
+            bf16x8 a[3];
+#pragma unroll
+            for (int p = 0; p < 3; ++p) a[p] = dt_read_tr(planes + p * PLANE + g * 16 * 256, ln.tr0[mb], ln.tr1[mb]);
+            mfma6(a, b[g], t, t);
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[mb][r] += t[r];
+    }
+}
+
+// Exponentials in base 2: log2(e) (and scale log2(e)) as hi + lo, so that the argument is formed
+// with no more rounding than x * scale - m would have.
+constexpr float L2E_HI = 1.44269502162933349609f, L2E_LO = 1.925963033500011079e-08f;
+constexpr float LN2_HI = 0.693147182464599609375f, LN2_LO = -1.904654299957767878e-09f;
+struct Scale2 {
+    float hi, lo;
+    __device__ explicit Scale2(float scale) {
+        hi = scale * L2E_HI;
+        lo = fmaf(scale, L2E_HI, -hi) + scale * L2E_LO;
+    }
+    // 2^(x (hi + lo) - m - m_lo); 0 for x = -inf (lo may be negative)
+    __device__ float exp2(float x, float m, float m_lo) const {
+        return __builtin_amdgcn_exp2f(fmaf(x, hi, -m) + fmaf(fmaxf(x, -1e30f), lo, -m_lo));
+    }
+};
+// natural to base-2 units, as hi + lo (an infinite x is its hi)
+__device__ inline void to_base2(float x, float& hi, float& lo) {
+    hi = x * L2E_HI;
+    lo = fabsf(x) < INFINITY ? fmaf(x, L2E_HI, -hi) + x * L2E_LO : 0.f;
+}
+
+// Workgroup -> (tile rank, head): ranks heaviest first over all heads.
+__device__ inline void decode(int linear, int n_heads, int& rank, int& head) {
+    rank = linear / n_heads;
+    head = linear - rank * n_heads;
+}
+// one past the last key shard that device dev's queries see
+__device__ inline int last_shard(const StepArgs& p, int dev) {
+    return p.layout == SA_STRIPED ? p.kv_dev + p.n_kv : min(p.kv_dev + p.n_kv, dev + 1);
+}
+// The walk of a query-owning workgroup over the 32-key tiles of its shards, q0 its first query:
+// body(k, v, key0, full, off) on one tile.
+template <int DP, int WAVES, typename Body>
+__device__ inline void walk_keys(const StepArgs& p, int dev, int q0, int64_t kv_base, char* lds, Body body) {
+    const int kv_end = last_shard(p, dev), q_last = min(q0 + 32 * WAVES, p.c) - 1;
+    const float* K = (const float*)p.k + kv_base;
+    const float* V = (const float*)p.v + kv_base;
+    Staged<DP, WAVES> sk, sv;
+    // tile after tile of the walk: `ahead` is the next one to fetch
+    int kv_a = p.kv_dev, t_a = 0;
+    auto last_key = [&](int kv) {
+        return block_kind(dev, kv, p.layout) == MASK_FULL ? p.c - 1 : q_last - block_off(dev, kv, p.layout);
+    };
+    auto fetch = [&]() {
+        sk.fetch(K + (kv_a - p.kv_dev) * p.kv_shard, p.kv_stride_s, t_a, p.c, p.d);
+        sv.fetch(V + (kv_a - p.kv_dev) * p.kv_shard, p.kv_stride_s, t_a, p.c, p.d);
+        t_a += TILE;
+        if (t_a > last_key(kv_a)) {
+            t_a = 0;
+            ++kv_a;
+        }
+    };
+    int kv = kv_a, t0 = t_a, parity = 0;
+    fetch();
+    sk.put(lds);
+    sv.put(lds + OPERAND);
+    for (;;) {
+        const int kv_n = kv_a, t_n = t_a;
+        const bool more = kv_n < kv_end;
+        if (more) fetch();
+        __syncthreads();                // this tile is written, the other buffer read
+        const char* k = lds + parity * BUFFER;
+        body(k, k + OPERAND, t0, block_kind(dev, kv, p.layout) == MASK_FULL, block_off(dev, kv, p.layout));
+        if (!more) break;
+        char* to = lds + (1 - parity) * BUFFER;
+        sk.put(to);
+        sv.put(to + OPERAND);
+        kv = kv_n;
+        t0 = t_n;
+        parity ^= 1;
+    }
+}
+
+// ------------------------------------------------------------------ forward
+template <int DP, int WAVES>
+__global__ void __launch_bounds__(64 * WAVES, WAVES / 4)
+fwd_f32x3_kernel(StepArgs p, int n_tiles) {
+    constexpr int KS = ksteps_of(DP), NB = blocks_of(DP);
+    __shared__ __attribute__((aligned(1024))) char lds[2 * BUFFER];
+
+    const Lane ln;
+    const int n = ln.n, h = ln.h;
+    int rank, bh, dev_rank;
+    decode((int)blockIdx.x, p.B * p.H, rank, bh);
+    decode_rank(rank, n_tiles, p.n_q, p.layout, rank, dev_rank);
+    const int q0 = (n_tiles - 1 - rank) * 32 * WAVES, dev_i = p.n_q - 1 - dev_rank, dev = p.q_dev + dev_i;
+    const int b = bh / p.H, hd = bh - b * p.H, d = p.d;
+    const int64_t base = b * p.stride_b + hd * p.stride_h + dev_i * p.q_shard;
+    const int64_t kv_base = b * p.kv_stride_b + (hd / (p.H / p.H_kv)) * p.kv_stride_h;
+
+    const int a_own = q0 + 32 * ln.wave + n, a = min(a_own, p.c - 1);
+    bf16x8x3 qf[KS];
+    load_row<KS>(qf, (const float*)p.q + base + (int64_t)a * p.stride_s, h, d);
+    float* L = p.lse + b * p.stat_stride_b + hd * p.stat_stride_h + (int64_t)dev_i * p.c + a;
+    const float old = p.fresh ? -INFINITY : *L;
+    f32x16 acc[NB];
+#pragma unroll
+    for (int mb = 0; mb < NB; ++mb) acc[mb] = zero16();
+    const Scale2 kappa(p.scale);
+    float m = -INFINITY, l = 0.f;           // m in base-2 units; l: this half-wave's share of the row sum
+
+    walk_keys<DP, WAVES>(p, dev, q0, kv_base, lds, [&](const char* k, const char* v, int key0, bool full, int off) {
+        const int wave_last = full ? p.c - 1 : min(q0 + 32 * ln.wave + 31, p.c - 1) - off;
+        if (key0 > wave_last) return;
+        const int lane_last = (full ? p.c - 1 : a - off) - key0;
+        f32x16 x = scores<KS>(k, qf, ln);
+        float mx = -INFINITY;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            x[r] = reg_row(r, h) <= lane_last ? x[r] : -INFINITY;
+            mx = fmaxf(mx, x[r]);
+        }
+        const float m_new = fmaxf(m, half_wave_max(mx) * kappa.hi);         // base 2
+        const float ref = m_new == -INFINITY ? 0.f : m_new;                 // a row without a key so far
+        const float alpha = __builtin_amdgcn_exp2f(m - ref);
+        float sum = 0.f;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            x[r] = kappa.exp2(x[r], ref, 0.f);
+            sum += x[r];
+        }
+        l = l * alpha + sum;
+        if (__builtin_amdgcn_ballot_w64(m_new != m) != 0) {
+#pragma unroll
+            for (int mb = 0; mb < NB; ++mb)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[mb][r] *= alpha;
+        }
+        m = m_new;
+        accumulate<NB>(acc, v, x, ln);
+    });
+
+    // fold the partial result into the running (O, LSE)
+    const float l_tot = half_wave_sum(l);
+    const float part = l_tot > 0.f ? fmaf(m, LN2_HI, fmaf(m, LN2_LO, logf(l_tot))) : -INFINITY;
+    const float top = fmaxf(old, part);
+    // no row here, or no key seen: state unchanged
+    if (a_own >= p.c || (part == -INFINITY && !p.fresh)) return;
+    const float ref = top == -INFINITY ? 0.f : top;
+    const float w_old = expf(old - ref), w_part = expf(part - ref), w_sum = w_old + w_part;
+    const float inv = w_sum > 0.f ? 1.f / w_sum : 0.f;
+    const float f_old = w_old * inv, f_part = l_tot > 0.f ? w_part * inv / l_tot : 0.f;
+    float* O = p.o + base + (int64_t)a * p.stride_s;
+#pragma unroll
+    for (int mb = 0; mb < NB; ++mb)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const int col = 32 * mb + 8 * g + 4 * h;
+            if (col >= d) continue;
+            float4* dst = reinterpret_cast<float4*>(O + col);
+            float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (f_old != 0.f) {
+                x = *dst;
+                x.x *= f_old; x.y *= f_old; x.z *= f_old; x.w *= f_old;
+            }
+            x.x = fmaf(acc[mb][4 * g + 0], f_part, x.x); x.y = fmaf(acc[mb][4 * g + 1], f_part, x.y);
+            x.z = fmaf(acc[mb][4 * g + 2], f_part, x.z); x.w = fmaf(acc[mb][4 * g + 3], f_part, x.w);
+            *dst = x;
+        }
+    if (h == 0) *L = top + logf(w_sum);
+}
+
+// scale * acc to this lane's row, added to what is there unless fresh
+template <int NB>
+__device__ inline void add_rows(float* row, const f32x16 (&acc)[NB], float scale, int d, int h, bool fresh) {
+#pragma unroll
+    for (int mb = 0; mb < NB; ++mb)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const int col = 32 * mb + 8 * g + 4 * h;
+            if (col >= d) continue;
+            float4* dst = reinterpret_cast<float4*>(row + col);
+            float4 x = fresh ? make_float4(0.f, 0.f, 0.f, 0.f) : *dst;
+            x.x = fmaf(scale, acc[mb][4 * g + 0], x.x); x.y = fmaf(scale, acc[mb][4 * g + 1], x.y);
+            x.z = fmaf(scale, acc[mb][4 * g + 2], x.z); x.w = fmaf(scale, acc[mb][4 * g + 3], x.w);
+            *dst = x;
+        }
+}
+
+// ----------------------------------------------------------------------- dQ
+template <int DP>
+__device__ inline void bwd_dq(const StepArgs& p, int n_tiles, int linear, char* lds) {
+    constexpr int KS = ksteps_of(DP), NB = blocks_of(DP);
+    const Lane ln;
+    const int n = ln.n, h = ln.h;
+    int rank, bh, dev_rank;
+    decode(linear, p.B * p.H, rank, bh);
+    decode_rank(rank, n_tiles, p.n_q, p.layout, rank, dev_rank);
+    const int q0 = (n_tiles - 1 - rank) * 32 * BWD_WAVES, dev_i = p.n_q - 1 - dev_rank, dev = p.q_dev + dev_i;
+    const int b = bh / p.H, hd = bh - b * p.H, d = p.d;
+    const int64_t base = b * p.stride_b + hd * p.stride_h + dev_i * p.q_shard;
+    const int64_t kv_base = b * p.kv_stride_b + (hd / (p.H / p.H_kv)) * p.kv_stride_h;
+    const int64_t sbase = b * p.stat_stride_b + hd * p.stat_stride_h + (int64_t)dev_i * p.c;
+
+    const int a_own = q0 + 32 * ln.wave + n, a = min(a_own, p.c - 1);
+    bf16x8x3 qf[KS], gf[KS];
+    load_row<KS>(qf, (const float*)p.q + base + (int64_t)a * p.stride_s, h, d);
+    load_row<KS>(gf, (const float*)p.dout + base + (int64_t)a * p.stride_s, h, d);
+    const float delta = p.delta[sbase + a];
+    const Scale2 kappa(p.scale);
+    float lse, lse_lo;
+    to_base2(p.lse[sbase + a], lse, lse_lo);
+    f32x16 acc[NB];
+#pragma unroll
+    for (int mb = 0; mb < NB; ++mb) acc[mb] = zero16();
+
+    walk_keys<DP, BWD_WAVES>(p, dev, q0, kv_base, lds, [&](const char* k, const char* v, int key0, bool full, int off) {
+        const int wave_last = full ? p.c - 1 : min(q0 + 32 * ln.wave + 31, p.c - 1) - off;
+        if (key0 > wave_last) return;
+        const int lane_last = (full ? p.c - 1 : a - off) - key0;
+        f32x16 x = scores<KS>(k, qf, ln);
+        const f32x16 dp = scores<KS>(v, gf, ln);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const float pr = reg_row(r, h) <= lane_last ? kappa.exp2(x[r], lse, lse_lo) : 0.f;
+            x[r] = pr * (dp[r] - delta);
+        }
+        accumulate<NB>(acc, k, x, ln);
+    });
+    if (a_own < p.c) add_rows<NB>(p.dq + base + (int64_t)a * p.stride_s, acc, p.scale, d, h, p.fresh);
+}
+
+// -------------------------------------------------------------------- dK/dV
+// Owned rows are keys, streamed rows queries; the query heads of the group that shares the
+// key/value head and the query shards that see it come one after the other.
+template <int DP>
+__device__ inline void bwd_dkdv(const StepArgs& p, int n_tiles, int linear, char* lds, float* stats) {
+    constexpr int KS = ksteps_of(DP), NB = blocks_of(DP);
+    const Lane ln;
+    const int n = ln.n, h = ln.h, tid = threadIdx.x;
+    int tile, bh, dev_i;                                // low key tiles see most queries: first
+    decode(linear, p.B * p.H_kv, tile, bh);
+    decode_rank(tile, n_tiles, p.n_kv, p.layout, tile, dev_i);
+    const int k0 = tile * 32 * BWD_WAVES, dev = p.kv_dev + dev_i;
+    const int b = bh / p.H_kv, kvh = bh - b * p.H_kv, group = p.H / p.H_kv, d = p.d;
+    const int64_t kv_base = b * p.kv_stride_b + kvh * p.kv_stride_h + dev_i * p.kv_shard;
+
+    const int key_own = k0 + 32 * ln.wave + n, key = min(key_own, p.c - 1);
+    const int64_t row = kv_base + (int64_t)key * p.kv_stride_s;
+    const Scale2 kappa(p.scale);
+    bf16x8x3 kf[KS], vf[KS];
+    load_row<KS>(kf, (const float*)p.k + row, h, d);
+    load_row<KS>(vf, (const float*)p.v + row, h, d);
+    f32x16 acck[NB], accv[NB];
+#pragma unroll
+    for (int mb = 0; mb < NB; ++mb) acck[mb] = accv[mb] = zero16();
+
+    // contiguous layout: earlier devices' queries see nothing of these keys
+    const int q_dev0 = p.layout == SA_STRIPED ? p.q_dev : max(p.q_dev, dev);
+    auto first_tile = [&](int q_dev) {
+        return block_kind(q_dev, dev, p.layout) == MASK_FULL ? 0 : (k0 + block_off(q_dev, dev, p.layout)) / TILE * TILE;
+    };
+    Staged<DP, BWD_WAVES> sq, sg;
+    float stat = 0.f;           // LSE (threads 0 .. 31) or delta (32 .. 63) of a row of the tile
+    int member_a = 0, dev_a = q_dev0, t_a = first_tile(q_dev0);
+    auto fetch = [&]() {
+        const int hd = kvh * group + member_a;
+        const int64_t base = b * p.stride_b + hd * p.stride_h + (dev_a - p.q_dev) * p.q_shard;
+        sq.fetch((const float*)p.q + base, p.stride_s, t_a, p.c, d);
+        sg.fetch((const float*)p.dout + base, p.stride_s, t_a, p.c, d);
+        if (tid < 2 * TILE) {
+            const int64_t at = b * p.stat_stride_b + hd * p.stat_stride_h + (int64_t)(dev_a - p.q_dev) * p.c +
+                               min(t_a + tid % TILE, p.c - 1);
+            stat = tid < TILE ? p.lse[at] : p.delta[at];
+        }
+        t_a += TILE;
+        // a tile row may lie beyond the shard (last tile of a block) but a tile may not
+        if (t_a >= p.c) {
+            if (++dev_a == p.q_dev + p.n_q) {
+                dev_a = q_dev0;
+                ++member_a;
+            }
+            t_a = first_tile(dev_a);
+        }
+    };
+    auto put = [&](int parity) {
+        sq.put(lds + parity * BUFFER);
+        sg.put(lds + parity * BUFFER + OPERAND);
+        float* st = stats + parity * 3 * TILE;
+        if (tid < TILE) to_base2(stat, st[tid], st[TILE + tid]);
+        else if (tid < 2 * TILE) st[TILE + tid] = stat;
+    };
+    // keys whose first query lies beyond the shard (last key, off = 1) start at row c: nothing there
+    // is in the mask, and rows beyond the shard read as zeros
+    int q_dev = dev_a, t0 = t_a, parity = 0;
+    fetch();
+    put(0);
+    for (;;) {
+        const int dev_n = dev_a, t_n = t_a;
+        const bool more = member_a < group;
+        if (more) fetch();
+        __syncthreads();                // this tile is written, the other buffer read
+        const bool full = block_kind(q_dev, dev, p.layout) == MASK_FULL;
+        const int off = block_off(q_dev, dev, p.layout);
+        if (full || t0 + 31 >= k0 + 32 * ln.wave + off) {
+            const char* q = lds + parity * BUFFER;
+            const char* g = q + OPERAND;
+            const float* st = stats + parity * 3 * TILE;
+            const int lane_first = (full ? 0 : key_own + off) - t0, rows = p.c - t0;
+            const f32x16 x = scores<KS>(q, kf, ln);
+            f32x16 dp = scores<KS>(g, vf, ln), pr;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int i = reg_row(r, h);
+                pr[r] = i >= lane_first && i < rows ? kappa.exp2(x[r], st[i], st[TILE + i]) : 0.f;
+                dp[r] = pr[r] * (dp[r] - st[2 * TILE + i]);
+            }
+            accumulate<NB>(accv, g, pr, ln);
+            accumulate<NB>(acck, q, dp, ln);
+        }
+        if (!more) break;
+        parity ^= 1;
+        put(parity);
+        q_dev = dev_n;
+        t0 = t_n;
+    }
+    if (key_own >= p.c) return;
+    add_rows<NB>(p.dv + row, accv, 1.f, d, h, p.fresh);
+    add_rows<NB>(p.dk + row, acck, p.scale, d, h, p.fresh);
+}
+
+// Both in one launch: workgroups 0 .. n_dkdv - 1 own keys, the others queries (they share nothing
+// but the inputs; one compute unit each, so the second kind fills the tail of the first).
+template <int DP>
+__global__ void __launch_bounds__(64 * BWD_WAVES, 1)
+bwd_f32x3_kernel(StepArgs p, int n_tiles, int n_dkdv) {
+    __shared__ __attribute__((aligned(1024))) char lds[2 * BUFFER];
+    __shared__ float stats[2 * 3 * TILE];          // [buffer][LSE hi | LSE lo | delta][row]
+    if ((int)blockIdx.x < n_dkdv) bwd_dkdv<DP>(p, n_tiles, (int)blockIdx.x, lds, stats);
+    else bwd_dq<DP>(p, n_tiles, (int)blockIdx.x - n_dkdv, lds);
+}
+
+template <int DP, int WAVES>
+hipError_t run_fwd(const StepArgs& a, hipStream_t st) {
+    const int rows = 32 * WAVES, n_tiles = (a.c + rows - 1) / rows;
+    hipLaunchKernelGGL((fwd_f32x3_kernel<DP, WAVES>), dim3((unsigned)n_tiles * a.n_q * a.B * a.H), dim3(64 * WAVES), 0, st,
+                       a, n_tiles);
+    return hipGetLastError();
+}
+template <int DP>
+hipError_t run(const StepArgs& a, bool backward, hipStream_t st) {
+    const int rows = 32 * BWD_WAVES, n_tiles = (a.c + rows - 1) / rows;
+    if (!backward) return (int64_t)n_tiles * a.n_q * a.B * a.H >= 512 ? run_fwd<DP, 8>(a, st) : run_fwd<DP, 4>(a, st);
+    const int n_dkdv = n_tiles * a.n_kv * a.B * a.H_kv, n_dq = n_tiles * a.n_q * a.B * a.H;
+    hipLaunchKernelGGL((bwd_f32x3_kernel<DP>), dim3((unsigned)(n_dkdv + n_dq)), dim3(64 * BWD_WAVES), 0, st, a, n_tiles,
+                       n_dkdv);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+// Measured against the fp32 instruction's kernels with 128 rows a workgroup (256 row tiles, one
+// step, 2048 tokens, 16 heads, d 128): forward 0.23 / 0.36 ms, backward 0.46 / 0.68; with the
+// streamed rows split over the wavefronts, which those do below that (128 row tiles, 4096 tokens
+// on 2 devices, 4 heads): 0.48 / 0.26 and 0.81 / 0.71.
+bool f32x3_wanted(const StepArgs& a) {
+    return a.d <= 128 && (int64_t)((a.c + 127) / 128) * a.n_q * a.B * a.H >= 256;
+}
+
+hipError_t launch_f32x3(const StepArgs& a, bool backward, hipStream_t st) {
+    return a.d <= 64 ? run<64>(a, backward, st) : run<128>(a, backward, st);
+}
+
+}  // namespace sa

@@ -103,6 +103,8 @@ hipError_t launch_rope(const void* x, void* y, const int32_t* pos, int64_t pos_s
 
 hipError_t launch_fwd_f32(const StepArgs& a, int dtype, hipStream_t st);
 hipError_t launch_bwd_f32(const StepArgs& a, int dtype, hipStream_t st);
+bool f32x3_wanted(const StepArgs& a);
+hipError_t launch_f32x3(const StepArgs& a, bool backward, hipStream_t st);
 bool fwd_mfma_supported(const StepArgs& a, int dtype);
 bool fwd_mfma_rope_supported(const StepArgs& a, int dtype);
 hipError_t launch_fwd_mfma(const StepArgs& a, hipStream_t st);
