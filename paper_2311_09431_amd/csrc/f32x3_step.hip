@@ -140,8 +140,8 @@ struct Lane {
         n = lane & 31;
         h = lane >> 5;
         wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-        dt_row_addrs(arow, n, h);
-        dt_tr_addrs(tr0, tr1, lane);
+        dt_row_addrs<TD>(arow, n, h);
+        dt_tr_addrs<TD>(tr0, tr1, lane);
     }
 };
 

@@ -92,9 +92,10 @@ __device__ inline uint32_t k_step_addr(const uint32_t (&kaddr)[8], int ks) { ret
 __device__ inline bf16x8 lds_read_b128(const char* lds, uint32_t addr) {
     return *reinterpret_cast<const bf16x8*>(lds + addr);
 }
-__device__ inline bf16x8 lds_read_tr(const char* lds, uint32_t addr) {
+// (rows +8: eight 256-byte rows further; with two rows to a line an address of its own)
+__device__ inline bf16x8 lds_read_tr(const char* lds, uint32_t addr, uint32_t addr8) {
     const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(lds + addr));
-    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(lds + addr + 8 * 256));
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(lds + addr8));
     return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
@@ -125,7 +126,8 @@ __device__ inline void step(f32x16& s_cur, f32x16& s_next, bf16x8 (&p_cur)[2], b
         for (int hh = 0; hh < NH; ++hh) {
             if (QK && i < KS) ka[hh][i] = lds_read_b128(k_next + hh * TILE_BYTES, k_step_addr(kaddr, i));
             if (PV && i % 4 < MB)
-                va[hh][i] = lds_read_tr(v_prev + hh * TILE_BYTES + (i / 4) * 16 * 256, vaddr[i % 4]);
+                va[hh][i] = lds_read_tr(v_prev + hh * TILE_BYTES + (i / 4) * 16 * row_bytes(DP), vaddr[i % 4],
+                                        DP <= 64 ? vaddr[i % 4 + 2] : vaddr[i % 4] + 8 * 256);
         }
     };
     // operands are requested this many slices ahead of their use (3 and 4 measured the same or
@@ -254,10 +256,10 @@ fwd_mfma_kernel(StepArgs p, int n_qtiles) {
     constexpr bool RING = WALK == WALK_RING;
     __shared__ double rope_turns[ROPE ? DP / 2 : 1];
     // one LDS object per tile buffer (two 128-column halves each when DP = 256)
-    __shared__ __attribute__((aligned(1024))) char k_lds0[TILE_BYTES * NH];
-    __shared__ __attribute__((aligned(1024))) char k_lds1[TILE_BYTES * NH];
-    __shared__ __attribute__((aligned(1024))) char v_lds0[TILE_BYTES * NH];
-    __shared__ __attribute__((aligned(1024))) char v_lds1[TILE_BYTES * NH];
+    __shared__ __attribute__((aligned(1024))) char k_lds0[tile_bytes(DP) * NH];
+    __shared__ __attribute__((aligned(1024))) char k_lds1[tile_bytes(DP) * NH];
+    __shared__ __attribute__((aligned(1024))) char v_lds0[tile_bytes(DP) * NH];
+    __shared__ __attribute__((aligned(1024))) char v_lds1[tile_bytes(DP) * NH];
 
     const int tid = threadIdx.x, lane = tid & 63, n = lane & 31, h = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);      // wave-uniform, kept scalar
@@ -325,6 +327,12 @@ fwd_mfma_kernel(StepArgs p, int n_qtiles) {
 #pragma unroll
         for (int mb = 0; mb < 4; ++mb)
             vaddr[mb] = (4 * h + j4) * 256 + ((4 * (mb ^ j4) + 2 * nh + ((i & 3) >> 1)) << 4) + (i & 1) * 8;
+        if (DP <= 64) {         // two rows to a line: blocks 0, 1 at rows +0 and +8
+            uint32_t tr0[4], tr1[4];
+            dt_row_addrs<DP>(kaddr, n, h);
+            dt_tr_addrs<DP>(tr0, tr1, lane);
+            vaddr[0] = tr0[0]; vaddr[1] = tr0[1]; vaddr[2] = tr1[0]; vaddr[3] = tr1[1];
+        }
         const int lr = lane >> 4, pc = lane & 15;      // row within the 4-row group, physical chunk
 #pragma unroll
         for (int hh = 0; hh < NH; ++hh) {
@@ -339,12 +347,16 @@ fwd_mfma_kernel(StepArgs p, int n_qtiles) {
         }
     }
 
+    uint32_t g2[4];             // up to 64 columns: the two pieces of either tile
+    if (DP <= 64) dt_load_offsets<DP>(g2, lane, wave, pitch, d);
     auto load_k = [&](dt_rsrc K, int tile_byte_offset, char* buf) {
+        if (DP <= 64) return dt_load<DP>(K, tile_byte_offset, buf, g2, wave);
 #pragma unroll
         for (int hh = 0; hh < NH; ++hh)
             load_tile_direct(K, tile_byte_offset, buf + hh * TILE_BYTES, kg0[hh], wave, pitch);
     };
     auto load_v = [&](dt_rsrc V, int tile_byte_offset, char* buf) {
+        if (DP <= 64) return dt_load<DP>(V, tile_byte_offset, buf, g2, wave);
 #pragma unroll
         for (int hh = 0; hh < NH; ++hh)
             load_v_tile_direct(V, tile_byte_offset, buf + hh * TILE_BYTES, vg0[hh], wave, pitch);
@@ -419,7 +431,7 @@ fwd_mfma_kernel(StepArgs p, int n_qtiles) {
         char* const v_cur = PAR ? v_lds1 : v_lds0;
         char* const v_prv = PAR ? v_lds0 : v_lds1;
         step<true, true, !FIRST, MASK, DP, PART>(s_a, s_b, p_a, p_b, oacc, qf, m, l, kappa, kaddr, vaddr,
-                                                 k_cur + TILE_BYTES / 2, v_prv + TILE_BYTES / 2,
+                                                 k_cur + tile_bytes(DP) / 2, v_prv + tile_bytes(DP) / 2,
                                                  mask_base - 64 * t, part_ks);
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
@@ -495,7 +507,7 @@ fwd_mfma_kernel(StepArgs p, int n_qtiles) {
     }
     // final iteration u = 2 n_kt: PV(2 n_kt - 1): V tile n_kt - 1, second half; P in p_b
     {
-        const char* v_last = v_lds1 + TILE_BYTES / 2;          // n_kt - 1 is odd
+        const char* v_last = v_lds1 + tile_bytes(DP) / 2;          // n_kt - 1 is odd
         step<false, false, true, false, DP, PART>(s_a, s_b, p_a, p_b, oacc, qf, m, l, kappa, kaddr, vaddr, v_last,
                                                   v_last, 0, part_ks);
     }

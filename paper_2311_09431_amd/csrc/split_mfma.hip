@@ -36,15 +36,15 @@ struct Lane {
         n = lane & 31;
         h = lane >> 5;
         wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-        dt_row_addrs(arow, n, h);
-        dt_tr_addrs(tr0, tr1, lane);
+        dt_row_addrs<TD>(arow, n, h);
+        dt_tr_addrs<TD>(tr0, tr1, lane);
     }
 };
 
 // 128 rows starting at row first, as two 64-row tiles (rows beyond the matrix arrive as zeros)
 __device__ inline void load_group(dt_rsrc m, int first, int pitch, char* lds, const uint32_t (&gl)[4], int wave) {
-    dt_load(m, first * pitch, lds, gl, wave);
-    dt_load(m, (first + DT_ROWS) * pitch, lds + DT_BYTES, gl, wave);
+    dt_load<TD>(m, first * pitch, lds, gl, wave);
+    dt_load<TD>(m, (first + DT_ROWS) * pitch, lds + DT_BYTES, gl, wave);
 }
 
 __device__ inline f32x16 zero16() {
@@ -126,7 +126,7 @@ __device__ inline void walk_keys(const StepArgs& p, int dev, int q0, dt_rsrc K, 
                                  Body body) {
     const int pitch = 2 * (int)p.kv_stride_s, kv_end = last_shard(p, dev);
     uint32_t gl[4];
-    dt_load_offsets(gl, ln.lane, ln.wave, pitch, p.d);
+    dt_load_offsets<TD>(gl, ln.lane, ln.wave, pitch, p.d);
     auto block = [&](int kv) {
         Block b;
         b.kv = kv;
@@ -263,7 +263,7 @@ __device__ inline void bwd_dkdv(const StepArgs& p, int n_tiles, int linear, char
 #pragma unroll
     for (int mb = 0; mb < 4; ++mb) acck[mb] = accv[mb] = zero16();
     uint32_t gl[4];
-    dt_load_offsets(gl, ln.lane, ln.wave, pitch, d);
+    dt_load_offsets<TD>(gl, ln.lane, ln.wave, pitch, d);
 
     // the block being walked: query head and shard, its queries' first group, sub-tile and mask
     const int q_dev0 = p.layout == SA_STRIPED ? p.q_dev : max(p.q_dev, dev);
