@@ -97,8 +97,9 @@ __device__ inline void dq_step(f32x16& s_cur, f32x16& dp_cur, f32x16& s_next, f3
 #pragma unroll
             for (int hh = 0; hh < NH; ++hh) {
                 const bool last_chunk = 8 * hh + i == part_ks;
-                s_next = mfma(PART ? zero_beyond_d(ka[hh][i], last_chunk) : ka[hh][i], qf[8 * hh + i], s_next);
-                dp_next = mfma(PART ? zero_beyond_d(va[hh][i], last_chunk) : va[hh][i], gf[8 * hh + i], dp_next);
+                const bool select = PART && i >= part_from(DP);
+                s_next = mfma(select ? zero_beyond_d(ka[hh][i], last_chunk) : ka[hh][i], qf[8 * hh + i], s_next);
+                dp_next = mfma(select ? zero_beyond_d(va[hh][i], last_chunk) : va[hh][i], gf[8 * hh + i], dp_next);
             }
         }
 #pragma unroll
@@ -334,17 +335,15 @@ __device__ inline void mfma_results_to_valu(f32x16& a, f32x16& b) {
 }
 // The other software-managed hazard is on the input side: a VALU write of a VGPR followed by
 // an MFMA read of it needs 2 wait states (same table).  The operands normally come straight
-// from LDS reads (ordered by s_waitcnt, no hazard); only the PART instantiations pass them
-// through VALU selects first (zero_beyond_d), and then AFTER_VALU puts the wait in front of
-// the instruction.
-template <bool AFTER_VALU>
-__device__ inline void mfma_vgpr_first(f32x16& acc, bf16x8 a, bf16x8 b) {
-    if (AFTER_VALU) asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(acc) : "v"(a), "v"(b));
+// from LDS reads (ordered by s_waitcnt, no hazard); only the PART instantiations pass some of them
+// through VALU selects first (zero_beyond_d), and then after_valu (known when compiled) puts the
+// wait in front of the instruction.
+__device__ __forceinline__ void mfma_vgpr_first(f32x16& acc, bf16x8 a, bf16x8 b, bool after_valu) {
+    if (after_valu) asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(acc) : "v"(a), "v"(b));
     else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(acc) : "v"(a), "v"(b));
 }
-template <bool AFTER_VALU>
-__device__ inline void mfma_vgpr_acc(f32x16& acc, bf16x8 a, bf16x8 b) {
-    if (AFTER_VALU) asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));
+__device__ __forceinline__ void mfma_vgpr_acc(f32x16& acc, bf16x8 a, bf16x8 b, bool after_valu) {
+    if (after_valu) asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));
     else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));
 }
 
@@ -353,8 +352,8 @@ __device__ inline void mfma_vgpr_acc(f32x16& acc, bf16x8 a, bf16x8 b) {
 // pin them and the score tiles to VGPRs and spill a hundred registers, while the compiler keeps
 // part of them in AGPRs and copies a score tile back when the VALU code wants it (32 copies
 // against 48 MFMAs per step, affordable at this head dimension).
-template <int DP, bool PART>
-__device__ inline void score_mfma(f32x16& acc, bf16x8 a, bf16x8 b, bool first) {
+template <int DP>
+__device__ __forceinline__ void score_mfma(f32x16& acc, bf16x8 a, bf16x8 b, bool first, bool after_valu) {
     if (DP > 128) {
         if (first) {
 #pragma unroll
@@ -362,9 +361,9 @@ __device__ inline void score_mfma(f32x16& acc, bf16x8 a, bf16x8 b, bool first) {
         }
         acc = mfma(a, b, acc);
     } else if (first) {
-        mfma_vgpr_first<PART>(acc, a, b);
+        mfma_vgpr_first(acc, a, b, after_valu);
     } else {
-        mfma_vgpr_acc<PART>(acc, a, b);
+        mfma_vgpr_acc(acc, a, b, after_valu);
     }
 }
 
@@ -456,15 +455,16 @@ __device__ inline void dkdv_step(f32x16& s_cur, f32x16& dp_cur, f32x16& s_next, 
         if (NEXT && i < KS) {
 #pragma unroll
             for (int hh = 0; hh < NH; ++hh) {
-                const bf16x8 qx = PART ? zero_beyond_d(qa[hh][i], 8 * hh + i == part_ks) : qa[hh][i];
-                const bf16x8 gx = PART ? zero_beyond_d(ga[hh][i], 8 * hh + i == part_ks) : ga[hh][i];
-                score_mfma<DP, PART>(s_next, qx, kf[8 * hh + i], i == 0 && hh == 0);
+                const bool select = PART && i >= part_from(DP);
+                const bf16x8 qx = select ? zero_beyond_d(qa[hh][i], 8 * hh + i == part_ks) : qa[hh][i];
+                const bf16x8 gx = select ? zero_beyond_d(ga[hh][i], 8 * hh + i == part_ks) : ga[hh][i];
+                score_mfma<DP>(s_next, qx, kf[8 * hh + i], i == 0 && hh == 0, select);
                 if (hh == 0) {
                     __builtin_amdgcn_sched_barrier(0);
                     score(2 * i);
                     __builtin_amdgcn_sched_barrier(0);
                 }
-                score_mfma<DP, PART>(dp_next, gx, vf[8 * hh + i], false);
+                score_mfma<DP>(dp_next, gx, vf[8 * hh + i], false, select);
             }
             score(2 * i + 1);
         } else {
@@ -633,8 +633,8 @@ __device__ __forceinline__ void bwd_dkdv(const StepArgs& p, int n_tiles, int lin
                     qx = zero_beyond_d(qx, 8 * hh + ks == part_ks);
                     gx = zero_beyond_d(gx, 8 * hh + ks == part_ks);
                 }
-                score_mfma<DP, PART>(s_a, qx, kf[8 * hh + ks], ks == 0 && hh == 0);
-                score_mfma<DP, PART>(dp_a, gx, vf[8 * hh + ks], false);
+                score_mfma<DP>(s_a, qx, kf[8 * hh + ks], ks == 0 && hh == 0, PART);
+                score_mfma<DP>(dp_a, gx, vf[8 * hh + ks], false, PART);
             }
         if (DP <= 128) mfma_results_to_valu(s_a, dp_a);
     }

@@ -156,7 +156,7 @@ __device__ inline void step(f32x16& s_cur, f32x16& s_next, bf16x8 (&p_cur)[2], b
 #pragma unroll
         for (int hh = 0; hh < NH; ++hh)
             if (QK && i < KS)
-                s_next = mfma(PART ? zero_beyond_d(ka[hh][i], 8 * hh + i == part_ks) : ka[hh][i], qf[8 * hh + i],
+                s_next = mfma(PART && i >= part_from(DP) ? zero_beyond_d(ka[hh][i], 8 * hh + i == part_ks) : ka[hh][i], qf[8 * hh + i],
                               s_next);
         __builtin_amdgcn_sched_barrier(0);
         float p0 = 0.f;
