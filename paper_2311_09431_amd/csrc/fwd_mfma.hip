@@ -112,7 +112,7 @@ __device__ inline bf16x8 lds_read_tr(const char* lds, uint32_t addr, uint32_t ad
 // column d is cleared beyond it (part_ks = its k-step, or -1 for the lanes of the other
 // half-wave).
 template <bool QK, bool SM, bool PV, bool MASK, int DP, bool PART>
-__device__ inline void step(f32x16& s_cur, f32x16& s_next, bf16x8 (&p_cur)[2], bf16x8 (&p_prev)[2],
+__device__ __forceinline__ void step(f32x16& s_cur, f32x16& s_next, bf16x8 (&p_cur)[2], bf16x8 (&p_prev)[2],
                             f32x16 (&oacc)[4 * halves_of(DP)], const bf16x8 (&qf)[8 * halves_of(DP)], float& m,
                             float& l, float kappa, const uint32_t (&kaddr)[8], const uint32_t (&vaddr)[4],
                             const char* k_next, const char* v_prev, int mask_lim, int part_ks) {
@@ -127,7 +127,7 @@ __device__ inline void step(f32x16& s_cur, f32x16& s_next, bf16x8 (&p_cur)[2], b
             if (QK && i < KS) ka[hh][i] = lds_read_b128(k_next + hh * TILE_BYTES, k_step_addr(kaddr, i));
             if (PV && i % 4 < MB)
                 va[hh][i] = lds_read_tr(v_prev + hh * TILE_BYTES + (i / 4) * 16 * row_bytes(DP), vaddr[i % 4],
-                                        DP <= 64 ? vaddr[i % 4 + 2] : vaddr[i % 4] + 8 * 256);
+                                        DP <= 64 ? vaddr[2 + i % 2] : vaddr[i % 4] + 8 * 256);
         }
     };
     // operands are requested this many slices ahead of their use (3 and 4 measured the same or
@@ -327,7 +327,7 @@ fwd_mfma_kernel(StepArgs p, int n_qtiles) {
 #pragma unroll
         for (int mb = 0; mb < 4; ++mb)
             vaddr[mb] = (4 * h + j4) * 256 + ((4 * (mb ^ j4) + 2 * nh + ((i & 3) >> 1)) << 4) + (i & 1) * 8;
-        if (DP <= 64) {         // two rows to a line: blocks 0, 1 at rows +0 and +8
+        if constexpr (DP <= 64) {         // two rows to a line: blocks 0, 1 at rows +0 and +8
             uint32_t tr0[4], tr1[4];
             dt_row_addrs<DP>(kaddr, n, h);
             dt_tr_addrs<DP>(tr0, tr1, lane);
@@ -348,7 +348,7 @@ fwd_mfma_kernel(StepArgs p, int n_qtiles) {
     }
 
     uint32_t g2[4];             // up to 64 columns: the two pieces of either tile
-    if (DP <= 64) dt_load_offsets<DP>(g2, lane, wave, pitch, d);
+    if constexpr (DP <= 64) dt_load_offsets<DP>(g2, lane, wave, pitch, d);
     auto load_k = [&](dt_rsrc K, int tile_byte_offset, char* buf) {
         if (DP <= 64) return dt_load<DP>(K, tile_byte_offset, buf, g2, wave);
 #pragma unroll
