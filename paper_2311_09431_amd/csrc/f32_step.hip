@@ -1,8 +1,9 @@
 // Ring-step kernels on the CDNA4 fp32 matrix cores (v_mfma_f32_32x32x2_f32: fp32 operands, fp32
 // accumulation): any head dimension up to 256, any block size, fp32 or bf16 inputs.  They serve
 // the fp32 configuration (error budget 1e-5, so no reduced-precision products and the accurate
-// expf / logf) and every bf16 shape the bf16 matrix-core kernels do not take (widened to fp32
-// on the way into LDS, so its probabilities are not rounded either).
+// expf / logf) and the bf16 shapes the bf16 matrix-core kernels do not take (widened to fp32
+// on the way into LDS, so their probabilities are not rounded either).  Fuller fp32 launches go to
+// f32x3_step.hip, most short bf16 blocks to split_mfma.hip.
 //
 // Measured against kernels with one wavefront per row and serial dot products on the vector ALU
 // (which they replace): whole ring forward + backward of 16 heads, d = 128, 4 x 2048 tokens, fp32
@@ -543,10 +544,12 @@ hipError_t run(const StepArgs& a, bool backward, hipStream_t st) {
 
 hipError_t launch_fwd_f32(const StepArgs& a, int dtype, hipStream_t st) {
     if (dtype == SA_F32 && f32x3_wanted(a)) return launch_f32x3(a, false, st);
+    if (short_exact_wanted(a, dtype, false)) return launch_short_exact(a, false, st);
     return dtype == SA_F32 ? run<float>(a, false, st) : run<__hip_bfloat16>(a, false, st);
 }
 hipError_t launch_bwd_f32(const StepArgs& a, int dtype, hipStream_t st) {
     if (dtype == SA_F32 && f32x3_wanted(a)) return launch_f32x3(a, true, st);
+    if (short_exact_wanted(a, dtype, true)) return launch_short_exact(a, true, st);
     return dtype == SA_F32 ? run<float>(a, true, st) : run<__hip_bfloat16>(a, true, st);
 }
 

@@ -16,6 +16,7 @@
 // owned rows sit in registers as three bf16 operands; the streamed ones go global -> registers (a
 // tile ahead) -> split -> three swizzled bf16 planes in LDS, two buffers, one barrier per 32-row
 // tile.
+#include "f32_terms.h"
 #include "mfma_tiles.h"
 #include "sa_internal.h"
 
@@ -43,14 +44,7 @@ __device__ inline f32x16 zero16() {
 // streamed row (within a tile) of score register r
 __device__ inline int reg_row(int r, int h) { return 8 * (r / 4) + 4 * h + r % 4; }
 
-// x = hi + mid + lo (+ less than 2^-26 x).  An infinite x, or one that rounds to an infinite hi, is
-// its hi.
-__device__ inline void split(float x, __bf16& hi, __bf16& mid, __bf16& lo) {
-    hi = (__bf16)x;
-    float r = x - (float)hi;
-    mid = (__bf16)r;
-    lo = (__bf16)(r - (float)mid);
-}
+// as split; an infinite x, or one that rounds to an infinite hi, is its hi
 __device__ inline void split_any(float x, __bf16& hi, __bf16& mid, __bf16& lo) {
     hi = (__bf16)x;
     float r = x - (float)hi;
@@ -74,15 +68,6 @@ __device__ inline void split_chunk(const Chunk& x, bf16x8 (&o)[3]) {
     for (int e = 0; e < 8; ++e) {
         __bf16 hi, mid, lo;
         split_any(v[e], hi, mid, lo);
-        o[0][e] = hi; o[1][e] = mid; o[2][e] = lo;
-    }
-}
-// registers first .. first + 7 of a score tile as B operands
-__device__ inline void split_regs(const f32x16& x, int first, bf16x8 (&o)[3]) {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        __bf16 hi, mid, lo;
-        split(x[first + e], hi, mid, lo);
         o[0][e] = hi; o[1][e] = mid; o[2][e] = lo;
     }
 }
@@ -183,27 +168,6 @@ __device__ inline void accumulate(f32x16 (&acc)[NB], const char* planes, const f
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[mb][r] += t[r];
     }
-}
-
-// Exponentials in base 2: log2(e) (and scale log2(e)) as hi + lo, so that the argument is formed
-// with no more rounding than x * scale - m would have.
-constexpr float L2E_HI = 1.44269502162933349609f, L2E_LO = 1.925963033500011079e-08f;
-constexpr float LN2_HI = 0.693147182464599609375f, LN2_LO = -1.904654299957767878e-09f;
-struct Scale2 {
-    float hi, lo;
-    __device__ explicit Scale2(float scale) {
-        hi = scale * L2E_HI;
-        lo = fmaf(scale, L2E_HI, -hi) + scale * L2E_LO;
-    }
-    // 2^(x (hi + lo) - m - m_lo); 0 for x = -inf (lo may be negative)
-    __device__ float exp2(float x, float m, float m_lo) const {
-        return __builtin_amdgcn_exp2f(fmaf(x, hi, -m) + fmaf(fmaxf(x, -1e30f), lo, -m_lo));
-    }
-};
-// natural to base-2 units, as hi + lo (an infinite x is its hi)
-__device__ inline void to_base2(float x, float& hi, float& lo) {
-    hi = x * L2E_HI;
-    lo = fabsf(x) < INFINITY ? fmaf(x, L2E_HI, -hi) + x * L2E_LO : 0.f;
 }
 
 // Workgroup -> (tile rank, head): ranks heaviest first over all heads.
