@@ -58,7 +58,7 @@ __device__ inline bf16x8 pack8(const f32x16& x, int first) {
 // fragments that hold column d are cleared beyond it (part_ks = the k-step, or -1 for the lanes
 // of the other half-wave).
 template <bool NEXT, bool MASK, int DP, bool PART>
-__device__ inline void dq_step(f32x16& s_cur, f32x16& dp_cur, f32x16& s_next, f32x16& dp_next,
+__device__ __forceinline__ void dq_step(f32x16& s_cur, f32x16& dp_cur, f32x16& s_next, f32x16& dp_next,
                                f32x16 (&acc)[4 * halves_of(DP)], const bf16x8 (&qf)[8 * halves_of(DP)],
                                const bf16x8 (&gf)[8 * halves_of(DP)], float kappa, float lse2, float delta,
                                const uint32_t (&arow)[8], const uint32_t (&tr0)[4], const uint32_t (&tr1)[4],
@@ -395,7 +395,7 @@ __device__ inline void load_neg_delta(f32x16& dp, const float* neg_delta, int h)
 // the score tiles), so tr0 / tr1 arrive with that half's LDS offset added and the other half is
 // another workgroup's, which computes S and dP again.
 template <bool NEXT, bool MASK, int DP, bool PART>
-__device__ inline void dkdv_step(f32x16& s_cur, f32x16& dp_cur, f32x16& s_next, f32x16& dp_next,
+__device__ __forceinline__ void dkdv_step(f32x16& s_cur, f32x16& dp_cur, f32x16& s_next, f32x16& dp_next,
                                  f32x16 (&acck)[4], f32x16 (&accv)[4], const bf16x8 (&kf)[8 * halves_of(DP)],
                                  const bf16x8 (&vf)[8 * halves_of(DP)], float kappa, const uint32_t (&arow)[8],
                                  const uint32_t (&tr0)[4], const uint32_t (&tr1)[4], const char* q_next,

@@ -567,8 +567,12 @@ namespace {
 bool one_block(const StepArgs& a) { return a.n_q == 1 && a.n_kv == 1 && !a.fresh; }
 template <int WALK, int DP, bool PART>
 void launch_fwd_walk(const StepArgs& a, hipStream_t st, dim3 grid, dim3 block, int n_qtiles) {
-    if (a.c % BM) hipLaunchKernelGGL((fwd_mfma_kernel<true, WALK, DP, PART>), grid, block, 0, st, a, n_qtiles);
-    else hipLaunchKernelGGL((fwd_mfma_kernel<false, WALK, DP, PART>), grid, block, 0, st, a, n_qtiles);
+    // Up to 64 columns three workgroups fit a compute unit; uneven work that they would hold all (or
+    // nearly all) at once is balanced better by two, so LDS is asked for that keeps the third out: 640
+    // workgroups 96 -> 77 us, 768 96 -> 84, 1024 183 -> 173, but 1536 242 -> 260.
+    const unsigned wgs = grid.x, keep_out = DP <= 64 && uneven(a) && wgs > 2 * N_CU && wgs <= 4 * N_CU ? 24576 : 0;
+    if (a.c % BM) hipLaunchKernelGGL((fwd_mfma_kernel<true, WALK, DP, PART>), grid, block, keep_out, st, a, n_qtiles);
+    else hipLaunchKernelGGL((fwd_mfma_kernel<false, WALK, DP, PART>), grid, block, keep_out, st, a, n_qtiles);
 }
 template <int DP, bool PART>
 void launch_fwd_variant(const StepArgs& a, hipStream_t st, dim3 grid, dim3 block, int n_qtiles) {
