@@ -33,8 +33,7 @@
 // owns 32 (64) rows and its wavefronts take the streamed sub-tiles in turn (SPLIT = 4 or 2),
 // the partial results meeting in LDS at the end.  Summation orders are fixed: results do not
 // depend on timing.
-#include <hip/hip_bf16.h>
-
+#include "f32_rows.h"
 #include "sa_internal.h"
 
 namespace sa {
@@ -61,17 +60,6 @@ __device__ inline f32x16 zero16() {
 }
 // streamed row (within a 32-row sub-tile) of score register r
 __device__ inline int reg_row(int r, int h) { return 8 * (r / 4) + 4 * h + r % 4; }
-
-template <typename T>
-__device__ inline float4 ld4(const T* p);
-template <>
-__device__ inline float4 ld4<float>(const float* p) { return *reinterpret_cast<const float4*>(p); }
-template <>
-__device__ inline float4 ld4<__hip_bfloat16>(const __hip_bfloat16* p) {
-    const uint2 raw = *reinterpret_cast<const uint2*>(p);
-    return make_float4(__uint_as_float(raw.x << 16), __uint_as_float(raw.x & 0xffff0000u),
-                       __uint_as_float(raw.y << 16), __uint_as_float(raw.y & 0xffff0000u));
-}
 
 // rows first .. first + ROWS - 1 of a [rows, d] matrix into an LDS tile, zeros beyond row c and
 // column d
@@ -132,11 +120,6 @@ __device__ inline void accumulate(f32x16 (&acc)[NB], const float* rows, const f3
 __device__ inline float half_max(float x) { return fmaxf(x, __shfl_xor(x, 32)); }
 __device__ inline float half_sum(float x) { return x + __shfl_xor(x, 32); }
 
-// one past the last key shard that device dev's queries see
-__device__ inline int last_shard(const StepArgs& p, int dev) {
-    return p.layout == SA_STRIPED ? p.kv_dev + p.n_kv : min(p.kv_dev + p.n_kv, dev + 1);
-}
-
 // Workgroup -> (tile rank, head): ranks heaviest first over all heads.
 __device__ inline void decode(int linear, int n_heads, int& rank, int& head) {
     rank = linear / n_heads;
@@ -145,9 +128,12 @@ __device__ inline void decode(int linear, int n_heads, int& rank, int& head) {
 
 // Partial accumulators of the SPLIT wavefronts that own the same rows, summed through LDS
 // (wavefront kw keeps column blocks kw, kw + SPLIT, ... of the sum in acc).  buf holds
-// SPLIT x 32-row x NB*32-column floats per group of wavefronts.
+// SPLIT x 32-row x NB*32-column floats per group of wavefronts.  masks: one word per wavefront of the
+// group; returns the rows for which one of them says odd.
 template <int SPLIT, int NB>
-__device__ inline void combine(f32x16 (&acc)[NB], float* buf, int kw, int lane) {
+__device__ inline uint32_t combine(f32x16 (&acc)[NB], float* buf, uint32_t* masks, bool odd, int kw, int lane) {
+    const uint32_t own = row_mask(odd);
+    if (lane == 0) masks[kw] = own;
     float* mine = buf + kw * NB * 16 * 64;
 #pragma unroll
     for (int mb = 0; mb < NB; ++mb)
@@ -165,6 +151,10 @@ __device__ inline void combine(f32x16 (&acc)[NB], float* buf, int kw, int lane) 
             acc[mb][r] = x;
         }
     }
+    uint32_t rows = 0;
+#pragma unroll
+    for (int w = 0; w < SPLIT; ++w) rows |= masks[w];
+    return __builtin_amdgcn_readfirstlane(rows);
 }
 template <int SPLIT, int DP>
 constexpr int tile_floats() { return 2 * tile_rows(SPLIT) * lds_pitch(DP); }
@@ -175,6 +165,7 @@ __global__ void __launch_bounds__(64 * WAVES, DP > 128 ? 1 : 2)
 fwd_f32_kernel(StepArgs p, int n_tiles) {
     constexpr int OWN = WAVES / SPLIT, TK = tile_rows(SPLIT), SUB = subtiles(SPLIT), NB = DP / 32;
     __shared__ __attribute__((aligned(16))) float lds[tile_floats<SPLIT, DP>()];
+    __shared__ uint32_t masks[WAVES];
     float* const k_lds = lds;
     float* const v_lds = lds + TK * lds_pitch(DP);
 
@@ -273,39 +264,44 @@ fwd_f32_kernel(StepArgs p, int n_tiles) {
             for (int r = 0; r < 16; ++r) acc[mb][r] *= f;
         m = m_all;
         __syncthreads();
-        combine<SPLIT, NB>(acc, lds + qw * SPLIT * NB * 16 * 64, kw, lane);
     }
+    // a row sum that is no positive number although the row sees a key: see f32_rows.h
+    const bool odd = a_own < p.c && !(l_tot > 0.f && l_tot < INFINITY) && sees_a_key(p, dev, a);
+    const uint32_t odd_rows =
+        SPLIT > 1 ? combine<SPLIT, NB>(acc, lds + qw * SPLIT * NB * 16 * 64, masks + qw * SPLIT, odd, kw, lane) : row_mask(odd);
     float* L = p.lse + b * p.stat_stride_b + hd * p.stat_stride_h + (int64_t)dev_i * p.c + a;
     const float old = p.fresh ? -INFINITY : *L;
     const float part = l_tot > 0.f ? m + logf(l_tot) : -INFINITY;
     const float top = fmaxf(old, part);
     if (SPLIT > 1) __syncthreads();         // every wavefront has read the old LSE
     // no row here, or no key seen: state unchanged
-    if (a_own >= p.c || (part == -INFINITY && !p.fresh)) return;
-    const float ref = top == -INFINITY ? 0.f : top;
-    const float w_old = expf(old - ref), w_part = expf(part - ref), w_sum = w_old + w_part;
-    const float inv = w_sum > 0.f ? 1.f / w_sum : 0.f;
-    const float f_old = w_old * inv, f_part = l_tot > 0.f ? w_part * inv / l_tot : 0.f;
-    float* O = p.o + base + (int64_t)a * p.stride_s;
+    if (a_own < p.c && !((odd_rows >> n) & 1) && (part != -INFINITY || p.fresh)) {
+        const float ref = top == -INFINITY ? 0.f : top;
+        const float w_old = expf(old - ref), w_part = expf(part - ref), w_sum = w_old + w_part;
+        const float inv = w_sum > 0.f ? 1.f / w_sum : 0.f;
+        const float f_old = w_old * inv, f_part = l_tot > 0.f ? w_part * inv / l_tot : 0.f;
+        float* O = p.o + base + (int64_t)a * p.stride_s;
 #pragma unroll
-    for (int mb = 0; mb < NB; ++mb) {
-        if (SPLIT > 1 && mb % SPLIT != kw) continue;
+        for (int mb = 0; mb < NB; ++mb) {
+            if (SPLIT > 1 && mb % SPLIT != kw) continue;
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            const int col = 32 * mb + 8 * g + 4 * h;
-            if (col >= d) continue;
-            float4* dst = reinterpret_cast<float4*>(O + col);
-            float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (f_old != 0.f) {
-                x = *dst;
-                x.x *= f_old; x.y *= f_old; x.z *= f_old; x.w *= f_old;
+            for (int g = 0; g < 4; ++g) {
+                const int col = 32 * mb + 8 * g + 4 * h;
+                if (col >= d) continue;
+                float4* dst = reinterpret_cast<float4*>(O + col);
+                float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (f_old != 0.f) {
+                    x = *dst;
+                    x.x *= f_old; x.y *= f_old; x.z *= f_old; x.w *= f_old;
+                }
+                x.x = fmaf(acc[mb][4 * g + 0], f_part, x.x); x.y = fmaf(acc[mb][4 * g + 1], f_part, x.y);
+                x.z = fmaf(acc[mb][4 * g + 2], f_part, x.z); x.w = fmaf(acc[mb][4 * g + 3], f_part, x.w);
+                *dst = x;
             }
-            x.x = fmaf(acc[mb][4 * g + 0], f_part, x.x); x.y = fmaf(acc[mb][4 * g + 1], f_part, x.y);
-            x.z = fmaf(acc[mb][4 * g + 2], f_part, x.z); x.w = fmaf(acc[mb][4 * g + 3], f_part, x.w);
-            *dst = x;
         }
+        if (kw == 0 && h == 0) *L = top + logf(w_sum);
     }
-    if (kw == 0 && h == 0) *L = top + logf(w_sum);
+    each_row<SPLIT>(odd_rows, kw, [&](int i) { fwd_row<T>(p, b, hd, dev_i, q0 + 32 * qw + i, lane); });
 }
 
 // scale * acc to 32 owned rows (this lane's row at dst_row), added to what is there unless fresh
@@ -330,7 +326,7 @@ __device__ inline void add_rows(float* dst_row, const f32x16 (&acc)[NB], float s
 
 // ----------------------------------------------------------------------- dQ
 template <typename T, int DP, int SPLIT>
-__device__ inline void bwd_dq(const StepArgs& p, int n_tiles, int linear, float* lds) {
+__device__ inline void bwd_dq(const StepArgs& p, int n_tiles, int linear, float* lds, uint32_t* masks) {
     constexpr int OWN = WAVES / SPLIT, TK = tile_rows(SPLIT), SUB = subtiles(SPLIT), NB = DP / 32;
     float* const k_lds = lds;
     float* const v_lds = lds + TK * lds_pitch(DP);
@@ -387,7 +383,7 @@ __device__ inline void bwd_dq(const StepArgs& p, int n_tiles, int linear, float*
     }
     if (SPLIT > 1) {
         __syncthreads();
-        combine<SPLIT, NB>(acc, lds + qw * SPLIT * NB * 16 * 64, kw, lane);
+        combine<SPLIT, NB>(acc, lds + qw * SPLIT * NB * 16 * 64, masks + qw * SPLIT, false, kw, lane);
     }
     if (a_own >= p.c) return;
     add_rows<SPLIT, NB>(p.dq + base + (int64_t)a * p.stride_s, acc, p.scale, 0, d, kw, h, p.fresh);
@@ -399,7 +395,7 @@ __device__ inline void bwd_dq(const StepArgs& p, int n_tiles, int linear, float*
 // half of dK and dV (both halves beside K and V do not fit the registers) and scores are formed
 // once per half.
 template <typename T, int DP, int SPLIT>
-__device__ inline void bwd_dkdv(const StepArgs& p, int n_tiles, int linear, float* lds, float* stats) {
+__device__ inline void bwd_dkdv(const StepArgs& p, int n_tiles, int linear, float* lds, float* stats, uint32_t* masks) {
     constexpr int OWN = WAVES / SPLIT, TK = tile_rows(SPLIT), SUB = subtiles(SPLIT);
     constexpr int HALVES = DP > 128 ? 2 : 1, NB = DP / HALVES / 32;
     float* const q_lds = lds;
@@ -471,9 +467,9 @@ __device__ inline void bwd_dkdv(const StepArgs& p, int n_tiles, int linear, floa
     if (SPLIT > 1) {
         float* const buf = lds + own * SPLIT * NB * 16 * 64;
         __syncthreads();
-        combine<SPLIT, NB>(accv, buf, qsub, lane);
+        combine<SPLIT, NB>(accv, buf, masks + own * SPLIT, false, qsub, lane);
         __syncthreads();
-        combine<SPLIT, NB>(acck, buf, qsub, lane);
+        combine<SPLIT, NB>(acck, buf, masks + own * SPLIT, false, qsub, lane);
     }
     if (key_own >= p.c) return;
     const int64_t row = kv_base + (int64_t)key * p.kv_stride_s;
@@ -488,9 +484,10 @@ template <typename T, int DP, int SPLIT, bool KEYS, bool QUERIES>
 __global__ void __launch_bounds__(64 * WAVES, DP > 64 ? 1 : 2)
 bwd_f32_kernel(StepArgs p, int n_tiles, int n_dkdv) {
     __shared__ __attribute__((aligned(16))) float lds[tile_floats<SPLIT, DP>()];
+    __shared__ uint32_t masks[WAVES];
     __shared__ float stats[KEYS ? 2 * tile_rows(SPLIT) : 1];        // LSE | delta of a tile's queries
-    if (KEYS && (!QUERIES || (int)blockIdx.x < n_dkdv)) bwd_dkdv<T, DP, SPLIT>(p, n_tiles, (int)blockIdx.x, lds, stats);
-    else if (QUERIES) bwd_dq<T, DP, SPLIT>(p, n_tiles, (int)blockIdx.x - (KEYS ? n_dkdv : 0), lds);
+    if (KEYS && (!QUERIES || (int)blockIdx.x < n_dkdv)) bwd_dkdv<T, DP, SPLIT>(p, n_tiles, (int)blockIdx.x, lds, stats, masks);
+    else if (QUERIES) bwd_dq<T, DP, SPLIT>(p, n_tiles, (int)blockIdx.x - (KEYS ? n_dkdv : 0), lds, masks);
 }
 
 // ----------------------------------------------------------------- dispatch

@@ -16,6 +16,7 @@
 // owned rows sit in registers as three bf16 operands; the streamed ones go global -> registers (a
 // tile ahead) -> split -> three swizzled bf16 planes in LDS, two buffers, one barrier per 32-row
 // tile.
+#include "f32_rows.h"
 #include "f32_terms.h"
 #include "mfma_tiles.h"
 #include "sa_internal.h"
@@ -175,10 +176,6 @@ __device__ inline void decode(int linear, int n_heads, int& rank, int& head) {
     rank = linear / n_heads;
     head = linear - rank * n_heads;
 }
-// one past the last key shard that device dev's queries see
-__device__ inline int last_shard(const StepArgs& p, int dev) {
-    return p.layout == SA_STRIPED ? p.kv_dev + p.n_kv : min(p.kv_dev + p.n_kv, dev + 1);
-}
 // The walk of a query-owning workgroup over the 32-key tiles of its shards, q0 its first query:
 // body(k, v, key0, full, off) on one tile.
 template <int DP, int WAVES, typename Body>
@@ -285,30 +282,35 @@ fwd_f32x3_kernel(StepArgs p, int n_tiles) {
     const float l_tot = half_wave_sum(l);
     const float part = l_tot > 0.f ? fmaf(m, LN2_HI, fmaf(m, LN2_LO, logf(l_tot))) : -INFINITY;
     const float top = fmaxf(old, part);
+    // a row sum that is no positive number although the row sees a key: see f32_rows.h
+    const uint32_t odd_rows =
+        row_mask(a_own < p.c && !(l_tot > 0.f && l_tot < INFINITY) && sees_a_key(p, dev, a));
     // no row here, or no key seen: state unchanged
-    if (a_own >= p.c || (part == -INFINITY && !p.fresh)) return;
-    const float ref = top == -INFINITY ? 0.f : top;
-    const float w_old = expf(old - ref), w_part = expf(part - ref), w_sum = w_old + w_part;
-    const float inv = w_sum > 0.f ? 1.f / w_sum : 0.f;
-    const float f_old = w_old * inv, f_part = l_tot > 0.f ? w_part * inv / l_tot : 0.f;
-    float* O = p.o + base + (int64_t)a * p.stride_s;
+    if (a_own < p.c && !((odd_rows >> n) & 1) && (part != -INFINITY || p.fresh)) {
+        const float ref = top == -INFINITY ? 0.f : top;
+        const float w_old = expf(old - ref), w_part = expf(part - ref), w_sum = w_old + w_part;
+        const float inv = w_sum > 0.f ? 1.f / w_sum : 0.f;
+        const float f_old = w_old * inv, f_part = l_tot > 0.f ? w_part * inv / l_tot : 0.f;
+        float* O = p.o + base + (int64_t)a * p.stride_s;
 #pragma unroll
-    for (int mb = 0; mb < NB; ++mb)
+        for (int mb = 0; mb < NB; ++mb)
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            const int col = 32 * mb + 8 * g + 4 * h;
-            if (col >= d) continue;
-            float4* dst = reinterpret_cast<float4*>(O + col);
-            float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (f_old != 0.f) {
-                x = *dst;
-                x.x *= f_old; x.y *= f_old; x.z *= f_old; x.w *= f_old;
+            for (int g = 0; g < 4; ++g) {
+                const int col = 32 * mb + 8 * g + 4 * h;
+                if (col >= d) continue;
+                float4* dst = reinterpret_cast<float4*>(O + col);
+                float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (f_old != 0.f) {
+                    x = *dst;
+                    x.x *= f_old; x.y *= f_old; x.z *= f_old; x.w *= f_old;
+                }
+                x.x = fmaf(acc[mb][4 * g + 0], f_part, x.x); x.y = fmaf(acc[mb][4 * g + 1], f_part, x.y);
+                x.z = fmaf(acc[mb][4 * g + 2], f_part, x.z); x.w = fmaf(acc[mb][4 * g + 3], f_part, x.w);
+                *dst = x;
             }
-            x.x = fmaf(acc[mb][4 * g + 0], f_part, x.x); x.y = fmaf(acc[mb][4 * g + 1], f_part, x.y);
-            x.z = fmaf(acc[mb][4 * g + 2], f_part, x.z); x.w = fmaf(acc[mb][4 * g + 3], f_part, x.w);
-            *dst = x;
-        }
-    if (h == 0) *L = top + logf(w_sum);
+        if (h == 0) *L = top + logf(w_sum);
+    }
+    each_row<1>(odd_rows, 0, [&](int i) { fwd_row<float>(p, b, hd, dev_i, q0 + 32 * ln.wave + i, ln.lane); });
 }
 
 // scale * acc to this lane's row, added to what is there unless fresh

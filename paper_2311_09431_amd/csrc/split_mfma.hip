@@ -18,8 +18,7 @@
 //
 // The wavefront that takes a sub-tile is given by the sub-tile's place in its shard, so summation
 // orders are fixed and the same under emulated coarse skipping.
-#include <hip/hip_bf16.h>
-
+#include "f32_rows.h"
 #include "f32_terms.h"
 #include "mfma_tiles.h"
 #include "sa_internal.h"
@@ -126,16 +125,24 @@ __device__ inline float4 take_sum(const char* buf, int piece, const Lane<DP>& ln
     }
     return x;
 }
+// EXACT: rows that are done over one by one (f32_rows.h): each wavefront puts its mask beside its
+// partial accumulators, and after the barrier takes every fourth of the rows that one of them names
+__device__ inline void put_odd(uint32_t* masks, bool odd, int wave, int lane) {
+    const uint32_t rows = row_mask(odd);
+    if (lane == 0) masks[wave] = rows;
+}
+__device__ inline uint32_t take_odd(const uint32_t* masks) {
+    uint32_t rows = 0;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) rows |= masks[w];
+    return __builtin_amdgcn_readfirstlane(rows);
+}
 // piece i of this wavefront's share and its first column
 template <int DP>
 __device__ inline int piece_of(int i, const Lane<DP>& ln) { return ln.wave * blocks_of(DP) + i; }
 template <int DP>
 __device__ inline int column_of(int i, const Lane<DP>& ln) { return 8 * piece_of<DP>(i, ln) + 4 * ln.h; }
 
-// one past the last key shard that device dev's queries see
-__device__ inline int last_shard(const StepArgs& p, int dev) {
-    return p.layout == SA_STRIPED ? p.kv_dev + p.n_kv : min(p.kv_dev + p.n_kv, dev + 1);
-}
 // last key of a block that the workgroup of queries q0 .. q0 + 31 looks at: the last allowed one,
 // or under emulated coarse skipping the last one of the skip_bk-wide tile that shares an allowed
 // pair with its skip_bq-tall tile
@@ -212,6 +219,7 @@ fwd_split_kernel(StepArgs p, int n_tiles) {
     // two buffers of K and V; at the end the statistics and four wavefronts' partial results
     __shared__ __attribute__((aligned(1024))) char lds[4 * GROUP_BYTES<DP>];
     static_assert(1024 + PARTIAL_BYTES<DP> <= 4 * GROUP_BYTES<DP>, "partial results");
+    __shared__ uint32_t masks[WAVES];
 
     const Lane<DP> ln;
     const int n = ln.n, h = ln.h;
@@ -291,6 +299,8 @@ fwd_split_kernel(StepArgs p, int n_tiles) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[mb][r] *= f;
     put_partial<DP>(buf, acc, ln);
+    // a row sum that is no positive number although the row sees a key: see f32_rows.h
+    put_odd(masks, a_own < p.c && !(l_tot > 0.f && l_tot < INFINITY) && sees_a_key(p, dev, a), ln.wave, ln.lane);
 
     const float part = l_tot > 0.f ? fmaf(m_all, LN2_HI, fmaf(m_all, LN2_LO, logf(l_tot))) : -INFINITY;
     const float top = fmaxf(old, part);
@@ -306,21 +316,24 @@ fwd_split_kernel(StepArgs p, int n_tiles) {
         if (f_old != 0.f && column_of<DP>(i, ln) < d) o_old[i] = *reinterpret_cast<const float4*>(O + column_of<DP>(i, ln));
     }
     __syncthreads();
+    const uint32_t odd_rows = take_odd(masks);
     // no row here, or no key seen: state unchanged
-    if (a_own >= p.c || (part == -INFINITY && !p.fresh)) return;
+    if (a_own < p.c && !((odd_rows >> n) & 1) && (part != -INFINITY || p.fresh)) {
 #pragma unroll
-    for (int i = 0; i < MB; ++i) {
-        const int col = column_of<DP>(i, ln);
-        if (col >= d) continue;
-        float4* dst = reinterpret_cast<float4*>(O + col);
-        const float4 s = take_sum<DP>(buf, piece_of<DP>(i, ln), ln);
-        float4 x = o_old[i];
-        x.x *= f_old; x.y *= f_old; x.z *= f_old; x.w *= f_old;
-        x.x = fmaf(s.x, f_part, x.x); x.y = fmaf(s.y, f_part, x.y);
-        x.z = fmaf(s.z, f_part, x.z); x.w = fmaf(s.w, f_part, x.w);
-        *dst = x;
+        for (int i = 0; i < MB; ++i) {
+            const int col = column_of<DP>(i, ln);
+            if (col >= d) continue;
+            float4* dst = reinterpret_cast<float4*>(O + col);
+            const float4 s = take_sum<DP>(buf, piece_of<DP>(i, ln), ln);
+            float4 x = o_old[i];
+            x.x *= f_old; x.y *= f_old; x.z *= f_old; x.w *= f_old;
+            x.x = fmaf(s.x, f_part, x.x); x.y = fmaf(s.y, f_part, x.y);
+            x.z = fmaf(s.z, f_part, x.z); x.w = fmaf(s.w, f_part, x.w);
+            *dst = x;
+        }
+        if (ln.wave == 0 && h == 0) *L = top + logf(w_sum);
     }
-    if (ln.wave == 0 && h == 0) *L = top + logf(w_sum);
+    each_row<WAVES>(odd_rows, ln.wave, [&](int i) { fwd_row<__hip_bfloat16>(p, b, hd, dev_i, q0 + i, ln.lane); });
 }
 
 // adds scale * (sum of the partial results at buf) to the lane's row, or stores it (fresh)
