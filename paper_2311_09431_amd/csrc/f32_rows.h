@@ -1,11 +1,14 @@
 // Single rows of a ring step in plain fp32 arithmetic, one wavefront a row, looking at nothing but
 // the pairs that the mask allows.
 //
-// A row whose sum of weights in the fp32-precision matrix-core kernels (f32_step.hip, f32x3_step.hip,
-// the exact ones of split_mfma.hip) is no positive number although it sees a key, has a NaN or +inf
-// score, nothing but scores of -inf, or scores that overflow a reference: a kernel looks there once,
-// at its end, and does such a row over here.  One wavefront and serial dot products: about the speed
-// of a vector kernel, and only for such rows.
+// The fp32-precision matrix-core kernels (f32_step.hip, f32x3_step.hip, the exact ones of
+// split_mfma.hip) multiply whole 32 x 32 sub-tiles, masked pairs with a weight of zero, and two of
+// them an operand as three terms.  For finite numbers that is the same sum; an infinite or NaN element
+// makes 0 * inf, inf - inf, or a sum of row weights that is no number.  All of these leave something
+// that is not finite in the row's accumulators or row sum, so a kernel looks there once, at its end,
+// and a row where it finds it is done over here: NaN and infinities then reach the rows that see them
+// and no others.  One wavefront and serial dot products: about the speed of a vector kernel, and only
+// for such rows.  The look costs 16 fmas per 32 x 32 accumulator and workgroup.
 #pragma once
 #include <hip/hip_bf16.h>
 
@@ -37,6 +40,16 @@ __device__ inline bool sees_a_key(const StepArgs& p, int dev, int a) {
     return p.layout != SA_STRIPED || a > 0 || p.kv_dev <= dev;
 }
 
+// some register of the first NB accumulators is infinite or NaN
+template <int NB, typename Acc>
+__device__ inline bool not_finite(const Acc& acc) {
+    float z = 0.f;
+#pragma unroll
+    for (int mb = 0; mb < NB; ++mb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) z = fmaf(acc[mb][r], 0.f, z);
+    return z != 0.f;
+}
 // rows (bit n: lanes n and n + 32) for which a lane says so
 __device__ inline uint32_t row_mask(bool lane_says) {
     const uint64_t m = __builtin_amdgcn_ballot_w64(lane_says);
@@ -135,6 +148,83 @@ __device__ inline void fwd_row(const StepArgs& p, int b, int hd, int dev_i, int 
     for (int k = 0; k < ROW_COLS; ++k)
         if (lane + 64 * k < p.d) O[lane + 64 * k] = acc[k] * inv;
     if (lane == 0) *L = !sees ? -INFINITY : l == 0.f ? NAN : m + logf(l);
+}
+
+// backward, query row a of the launch's device dev_i: adds to (fresh: stores) its dQ
+template <typename T>
+__device__ inline void dq_row(const StepArgs& p, int b, int hd, int dev_i, int a, int lane) {
+    const int dev = p.q_dev + dev_i;
+    const int64_t row = b * p.stride_b + hd * p.stride_h + dev_i * p.q_shard + (int64_t)a * p.stride_s;
+    const int64_t kv_base = b * p.kv_stride_b + (hd / (p.H / p.H_kv)) * p.kv_stride_h;
+    const int64_t stat = b * p.stat_stride_b + hd * p.stat_stride_h + (int64_t)dev_i * p.c + a;
+    const T* q = (const T*)p.q + row;
+    const T* g = (const T*)p.dout + row;
+    const float lse = p.lse[stat], delta = p.delta[stat];
+    float acc[ROW_COLS] = {};
+    const int kv_end = last_shard(p, dev);
+#pragma unroll 1
+    for (int kv = p.kv_dev; kv < kv_end; ++kv) {
+        const T* K = (const T*)p.k + kv_base + (kv - p.kv_dev) * p.kv_shard;
+        const T* V = (const T*)p.v + kv_base + (kv - p.kv_dev) * p.kv_shard;
+        const int keys = block_kind(dev, kv, p.layout) == MASK_FULL ? p.c : a - block_off(dev, kv, p.layout) + 1;
+#pragma unroll 1
+        for (int k0 = 0; k0 < keys; k0 += 64) {
+            float ds = 0.f;
+            if (k0 + lane < keys) {
+                const int64_t at = (int64_t)(k0 + lane) * p.kv_stride_s;
+                const float pr = expf(p.scale * dot_rows<T>(q, K + at, p.d) - lse);
+                ds = pr * (dot_rows<T>(g, V + at, p.d) - delta);
+            }
+            add_weighted<T>(acc, ds, K + (int64_t)k0 * p.kv_stride_s, p.kv_stride_s, min(64, keys - k0), 0, p.d, lane);
+        }
+    }
+    float* DQ = p.dq + row;
+#pragma unroll
+    for (int k = 0; k < ROW_COLS; ++k)
+        if (lane + 64 * k < p.d) DQ[lane + 64 * k] = (p.fresh ? 0.f : DQ[lane + 64 * k]) + p.scale * acc[k];
+}
+
+// backward, key row `key` of the launch's device dev_i: adds to (fresh: stores) columns col0 .. end - 1 of
+// its dK and dV
+template <typename T>
+__device__ inline void dkdv_row(const StepArgs& p, int b, int kvh, int dev_i, int key, int col0, int end, int lane) {
+    const int dev = p.kv_dev + dev_i, group = p.H / p.H_kv;
+    const int64_t row = b * p.kv_stride_b + kvh * p.kv_stride_h + dev_i * p.kv_shard + (int64_t)key * p.kv_stride_s;
+    const T* kr = (const T*)p.k + row;
+    const T* vr = (const T*)p.v + row;
+    float acck[ROW_COLS] = {}, accv[ROW_COLS] = {};
+    const int q_dev0 = p.layout == SA_STRIPED ? p.q_dev : max(p.q_dev, dev);
+#pragma unroll 1
+    for (int member = 0; member < group; ++member) {
+        const int hd = kvh * group + member;
+#pragma unroll 1
+        for (int q_dev = q_dev0; q_dev < p.q_dev + p.n_q; ++q_dev) {
+            const int64_t base = b * p.stride_b + hd * p.stride_h + (q_dev - p.q_dev) * p.q_shard;
+            const int64_t sbase = b * p.stat_stride_b + hd * p.stat_stride_h + (int64_t)(q_dev - p.q_dev) * p.c;
+            const T* Q = (const T*)p.q + base;
+            const T* G = (const T*)p.dout + base;
+            const int first = block_kind(q_dev, dev, p.layout) == MASK_FULL ? 0 : key + block_off(q_dev, dev, p.layout);
+#pragma unroll 1
+            for (int a0 = first; a0 < p.c; a0 += 64) {
+                float pr = 0.f, ds = 0.f;
+                if (a0 + lane < p.c) {
+                    const int64_t at = (int64_t)(a0 + lane) * p.stride_s;
+                    pr = expf(p.scale * dot_rows<T>(kr, Q + at, p.d) - p.lse[sbase + a0 + lane]);
+                    ds = pr * (dot_rows<T>(vr, G + at, p.d) - p.delta[sbase + a0 + lane]);
+                }
+                const int rows = min(64, p.c - a0);
+                add_weighted<T>(accv, pr, G + (int64_t)a0 * p.stride_s, p.stride_s, rows, col0, end, lane);
+                add_weighted<T>(acck, ds, Q + (int64_t)a0 * p.stride_s, p.stride_s, rows, col0, end, lane);
+            }
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < ROW_COLS; ++k) {
+        const int col = col0 + lane + 64 * k;
+        if (col >= end) continue;
+        p.dv[row + col] = (p.fresh ? 0.f : p.dv[row + col]) + accv[k];
+        p.dk[row + col] = (p.fresh ? 0.f : p.dk[row + col]) + p.scale * acck[k];
+    }
 }
 
 }  // namespace sa

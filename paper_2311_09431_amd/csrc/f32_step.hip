@@ -266,7 +266,8 @@ fwd_f32_kernel(StepArgs p, int n_tiles) {
         __syncthreads();
     }
     // a row sum that is no positive number although the row sees a key: see f32_rows.h
-    const bool odd = a_own < p.c && !(l_tot > 0.f && l_tot < INFINITY) && sees_a_key(p, dev, a);
+    const bool odd = a_own < p.c &&
+                     (not_finite<NB>(acc) || (!(l_tot > 0.f && l_tot < INFINITY) && sees_a_key(p, dev, a)));
     const uint32_t odd_rows =
         SPLIT > 1 ? combine<SPLIT, NB>(acc, lds + qw * SPLIT * NB * 16 * 64, masks + qw * SPLIT, odd, kw, lane) : row_mask(odd);
     float* L = p.lse + b * p.stat_stride_b + hd * p.stat_stride_h + (int64_t)dev_i * p.c + a;
@@ -381,12 +382,13 @@ __device__ inline void bwd_dq(const StepArgs& p, int n_tiles, int linear, float*
             }
         }
     }
-    if (SPLIT > 1) {
-        __syncthreads();
-        combine<SPLIT, NB>(acc, lds + qw * SPLIT * NB * 16 * 64, masks + qw * SPLIT, false, kw, lane);
-    }
-    if (a_own >= p.c) return;
-    add_rows<SPLIT, NB>(p.dq + base + (int64_t)a * p.stride_s, acc, p.scale, 0, d, kw, h, p.fresh);
+    const bool odd = a_own < p.c && not_finite<NB>(acc);
+    if (SPLIT > 1) __syncthreads();
+    const uint32_t odd_rows =
+        SPLIT > 1 ? combine<SPLIT, NB>(acc, lds + qw * SPLIT * NB * 16 * 64, masks + qw * SPLIT, odd, kw, lane) : row_mask(odd);
+    if (a_own < p.c && !((odd_rows >> n) & 1))
+        add_rows<SPLIT, NB>(p.dq + base + (int64_t)a * p.stride_s, acc, p.scale, 0, d, kw, h, p.fresh);
+    each_row<SPLIT>(odd_rows, kw, [&](int i) { dq_row<T>(p, b, hd, dev_i, q0 + 32 * qw + i, lane); });
 }
 
 // -------------------------------------------------------------------- dK/dV
@@ -464,17 +466,23 @@ __device__ inline void bwd_dkdv(const StepArgs& p, int n_tiles, int linear, floa
             }
         }
     }
+    const bool odd = key_own < p.c && (not_finite<NB>(accv) || not_finite<NB>(acck));
+    uint32_t odd_rows = row_mask(odd);
     if (SPLIT > 1) {
         float* const buf = lds + own * SPLIT * NB * 16 * 64;
         __syncthreads();
-        combine<SPLIT, NB>(accv, buf, masks + own * SPLIT, false, qsub, lane);
+        odd_rows = combine<SPLIT, NB>(accv, buf, masks + own * SPLIT, odd, qsub, lane);
         __syncthreads();
-        combine<SPLIT, NB>(acck, buf, masks + own * SPLIT, false, qsub, lane);
+        combine<SPLIT, NB>(acck, buf, masks + own * SPLIT, odd, qsub, lane);
     }
-    if (key_own >= p.c) return;
-    const int64_t row = kv_base + (int64_t)key * p.kv_stride_s;
-    add_rows<SPLIT, NB>(p.dv + row, accv, 1.f, col0, d, qsub, h, p.fresh);
-    add_rows<SPLIT, NB>(p.dk + row, acck, p.scale, col0, d, qsub, h, p.fresh);
+    if (key_own < p.c && !((odd_rows >> n) & 1)) {
+        const int64_t row = kv_base + (int64_t)key * p.kv_stride_s;
+        add_rows<SPLIT, NB>(p.dv + row, accv, 1.f, col0, d, qsub, h, p.fresh);
+        add_rows<SPLIT, NB>(p.dk + row, acck, p.scale, col0, d, qsub, h, p.fresh);
+    }
+    each_row<SPLIT>(odd_rows, qsub, [&](int i) {
+        dkdv_row<T>(p, b, kvh, dev_i, k0 + 32 * own + i, col0, HALVES > 1 ? min(d, col0 + 128) : d, lane);
+    });
 }
 
 // Both in one launch (KEYS and QUERIES): workgroups 0 .. n_dkdv - 1 own keys, the others queries.
@@ -484,9 +492,10 @@ template <typename T, int DP, int SPLIT, bool KEYS, bool QUERIES>
 __global__ void __launch_bounds__(64 * WAVES, DP > 64 ? 1 : 2)
 bwd_f32_kernel(StepArgs p, int n_tiles, int n_dkdv) {
     __shared__ __attribute__((aligned(16))) float lds[tile_floats<SPLIT, DP>()];
-    __shared__ uint32_t masks[WAVES];
     __shared__ float stats[KEYS ? 2 * tile_rows(SPLIT) : 1];        // LSE | delta of a tile's queries
-    if (KEYS && (!QUERIES || (int)blockIdx.x < n_dkdv)) bwd_dkdv<T, DP, SPLIT>(p, n_tiles, (int)blockIdx.x, lds, stats, masks);
+    __shared__ uint32_t masks[WAVES];
+    if (KEYS && (!QUERIES || (int)blockIdx.x < n_dkdv))
+        bwd_dkdv<T, DP, SPLIT>(p, n_tiles, (int)blockIdx.x, lds, stats, masks);
     else if (QUERIES) bwd_dq<T, DP, SPLIT>(p, n_tiles, (int)blockIdx.x - (KEYS ? n_dkdv : 0), lds, masks);
 }
 

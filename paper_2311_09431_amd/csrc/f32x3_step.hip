@@ -284,7 +284,7 @@ fwd_f32x3_kernel(StepArgs p, int n_tiles) {
     const float top = fmaxf(old, part);
     // a row sum that is no positive number although the row sees a key: see f32_rows.h
     const uint32_t odd_rows =
-        row_mask(a_own < p.c && !(l_tot > 0.f && l_tot < INFINITY) && sees_a_key(p, dev, a));
+        row_mask(a_own < p.c && (not_finite<NB>(acc) || (!(l_tot > 0.f && l_tot < INFINITY) && sees_a_key(p, dev, a))));
     // no row here, or no key seen: state unchanged
     if (a_own < p.c && !((odd_rows >> n) & 1) && (part != -INFINITY || p.fresh)) {
         const float ref = top == -INFINITY ? 0.f : top;
@@ -370,7 +370,10 @@ __device__ inline void bwd_dq(const StepArgs& p, int n_tiles, int linear, char* 
         }
         accumulate<NB>(acc, k, x, ln);
     });
-    if (a_own < p.c) add_rows<NB>(p.dq + base + (int64_t)a * p.stride_s, acc, p.scale, d, h, p.fresh);
+    const uint32_t odd_rows = row_mask(a_own < p.c && not_finite<NB>(acc));
+    if (a_own < p.c && !((odd_rows >> n) & 1))
+        add_rows<NB>(p.dq + base + (int64_t)a * p.stride_s, acc, p.scale, d, h, p.fresh);
+    each_row<1>(odd_rows, 0, [&](int i) { dq_row<float>(p, b, hd, dev_i, q0 + 32 * ln.wave + i, ln.lane); });
 }
 
 // -------------------------------------------------------------------- dK/dV
@@ -467,9 +470,12 @@ __device__ inline void bwd_dkdv(const StepArgs& p, int n_tiles, int linear, char
         q_dev = dev_n;
         t0 = t_n;
     }
-    if (key_own >= p.c) return;
-    add_rows<NB>(p.dv + row, accv, 1.f, d, h, p.fresh);
-    add_rows<NB>(p.dk + row, acck, p.scale, d, h, p.fresh);
+    const uint32_t odd_rows = row_mask(key_own < p.c && (not_finite<NB>(accv) || not_finite<NB>(acck)));
+    if (key_own < p.c && !((odd_rows >> n) & 1)) {
+        add_rows<NB>(p.dv + row, accv, 1.f, d, h, p.fresh);
+        add_rows<NB>(p.dk + row, acck, p.scale, d, h, p.fresh);
+    }
+    each_row<1>(odd_rows, 0, [&](int i) { dkdv_row<float>(p, b, kvh, dev_i, k0 + 32 * ln.wave + i, 0, d, ln.lane); });
 }
 
 // Both in one launch: workgroups 0 .. n_dkdv - 1 own keys, the others queries (they share nothing

@@ -300,7 +300,8 @@ fwd_split_kernel(StepArgs p, int n_tiles) {
         for (int r = 0; r < 16; ++r) acc[mb][r] *= f;
     put_partial<DP>(buf, acc, ln);
     // a row sum that is no positive number although the row sees a key: see f32_rows.h
-    put_odd(masks, a_own < p.c && !(l_tot > 0.f && l_tot < INFINITY) && sees_a_key(p, dev, a), ln.wave, ln.lane);
+    put_odd(masks, a_own < p.c && (not_finite<MB>(acc) ||
+                                   (!(l_tot > 0.f && l_tot < INFINITY) && sees_a_key(p, dev, a))), ln.wave, ln.lane);
 
     const float part = l_tot > 0.f ? fmaf(m_all, LN2_HI, fmaf(m_all, LN2_LO, logf(l_tot))) : -INFINITY;
     const float top = fmaxf(old, part);
@@ -354,7 +355,7 @@ __device__ inline void add_rows(float* row, const char* buf, float scale, int d,
 
 // ----------------------------------------------------------------------- dQ
 template <int DP, bool PART, bool EXACT>
-__device__ inline void bwd_dq(const StepArgs& p, int n_tiles, int linear, char* lds) {
+__device__ inline void bwd_dq(const StepArgs& p, int n_tiles, int linear, char* lds, uint32_t* masks) {
     const Lane<DP> ln;
     const int n = ln.n, h = ln.h;
     int rank, bh, dev_rank;
@@ -397,8 +398,12 @@ __device__ inline void bwd_dq(const StepArgs& p, int n_tiles, int linear, char* 
 
     __syncthreads();
     put_partial<DP>(lds, acc, ln);
+    if (EXACT) put_odd(masks, a_own < p.c && not_finite<blocks_of(DP)>(acc), ln.wave, ln.lane);
     __syncthreads();
-    if (a_own < p.c) add_rows<DP>(p.dq + base + (int64_t)a * p.stride_s, lds, p.scale, d, p.fresh, ln);
+    const uint32_t odd_rows = EXACT ? take_odd(masks) : 0;
+    if (a_own < p.c && !((odd_rows >> n) & 1))
+        add_rows<DP>(p.dq + base + (int64_t)a * p.stride_s, lds, p.scale, d, p.fresh, ln);
+    if (EXACT) each_row<WAVES>(odd_rows, ln.wave, [&](int i) { dq_row<__hip_bfloat16>(p, b, hd, dev_i, q0 + i, ln.lane); });
 }
 
 // -------------------------------------------------------------------- dK/dV
@@ -406,7 +411,7 @@ __device__ inline void bwd_dq(const StepArgs& p, int n_tiles, int linear, char* 
 // query heads that share the key/value head and the query shards that see it come one after the
 // other.
 template <int DP, bool PART, bool EXACT>
-__device__ inline void bwd_dkdv(const StepArgs& p, int n_tiles, int linear, char* lds, float* stats) {
+__device__ inline void bwd_dkdv(const StepArgs& p, int n_tiles, int linear, char* lds, float* stats, uint32_t* masks) {
     const Lane<DP> ln;
     const int n = ln.n, h = ln.h, tid = threadIdx.x;
     int tile, bh, dev_i;                                // low key tiles see most queries: first
@@ -511,10 +516,18 @@ __device__ inline void bwd_dkdv(const StepArgs& p, int n_tiles, int linear, char
     __syncthreads();
     put_partial<DP>(lds, accv, ln);
     put_partial<DP>(lds + HALF, acck, ln);
+    if (EXACT) {
+        const bool odd = not_finite<blocks_of(DP)>(accv) || not_finite<blocks_of(DP)>(acck);
+        put_odd(masks, key_own < p.c && odd, ln.wave, ln.lane);
+    }
     __syncthreads();
-    if (key_own >= p.c) return;
-    add_rows<DP>(p.dv + row, lds, 1.f, d, p.fresh, ln);
-    add_rows<DP>(p.dk + row, lds + HALF, p.scale, d, p.fresh, ln);
+    const uint32_t odd_rows = EXACT ? take_odd(masks) : 0;
+    if (key_own < p.c && !((odd_rows >> n) & 1)) {
+        add_rows<DP>(p.dv + row, lds, 1.f, d, p.fresh, ln);
+        add_rows<DP>(p.dk + row, lds + HALF, p.scale, d, p.fresh, ln);
+    }
+    if (EXACT)
+        each_row<WAVES>(odd_rows, ln.wave, [&](int i) { dkdv_row<__hip_bfloat16>(p, b, kvh, dev_i, k0 + i, 0, d, ln.lane); });
 }
 
 // Both in one launch, the two sequences of n_dkdv key-owning and n_dq query-owning workgroups
@@ -524,10 +537,11 @@ __global__ void __launch_bounds__(64 * WAVES, DP <= 64 ? 2 : 1)
 bwd_split_kernel(StepArgs p, int n_tiles, int n_dkdv, int n_dq) {
     __shared__ __attribute__((aligned(1024))) char lds[4 * GROUP_BYTES<DP>];
     __shared__ float stats[2 * 3 * GROUP];
+    __shared__ uint32_t masks[WAVES];
     const int total = n_dkdv + n_dq, before = (int)((int64_t)blockIdx.x * n_dkdv / total);
     const bool keys = (int)(((int64_t)blockIdx.x + 1) * n_dkdv / total) > before;
-    if (keys) bwd_dkdv<DP, PART, EXACT>(p, n_tiles, before, lds, stats);
-    else bwd_dq<DP, PART, EXACT>(p, n_tiles, (int)blockIdx.x - before, lds);
+    if (keys) bwd_dkdv<DP, PART, EXACT>(p, n_tiles, before, lds, stats, masks);
+    else bwd_dq<DP, PART, EXACT>(p, n_tiles, (int)blockIdx.x - before, lds, masks);
 }
 
 enum Pass { FWD_EXACT, BWD_EXACT, BWD };

@@ -54,6 +54,18 @@ def row_forward(q, K, V, scale, o0, lse0):
     return (old + (w[:, None] * V).sum(0)) / total, m + np.log(total)
 
 
+def rows_backward(q, K, V, g, scale, lse, delta, n_keys):
+    """Gradients of the pairs (a, b < n_keys[a])."""
+    dq, dk, dv = np.zeros_like(q), np.zeros_like(K), np.zeros_like(V)
+    for a, n in enumerate(n_keys):
+        p = np.exp(scale * (K[:n] * q[a]).sum(1) - lse[a])
+        ds = p * ((V[:n] * g[a]).sum(1) - delta[a])
+        dq[a] = scale * (ds[:, None] * K[:n]).sum(0)
+        dk[:n] += scale * ds[:, None] * q[a]
+        dv[:n] += p[:, None] * g[a]
+    return dq, dk, dv
+
+
 def swallowed(t, at):
     """Scores that are no number, or minus infinity."""
     first = t["q"][..., 0].abs() + 0.25
@@ -65,6 +77,31 @@ def swallowed(t, at):
         "all keys -inf": lambda x: (x["q"][..., 0].copy_(first), x["k"][..., 0].fill_(-INF)),
     }
     return cases
+
+
+def masked(t, at):
+    """Elements of a later token that earlier rows of the same sub-tile must not see."""
+    return {
+        "v nan": lambda x: x["v"][:, :, at, 3].fill_(NAN),
+        "v inf": lambda x: x["v"][:, :, at, 3].fill_(INF),
+        "last v nan": lambda x: x["v"][:, :, -1, 0].fill_(NAN),
+    }
+
+
+def backward_kinds(t, at):
+    first = t["q"][..., 0].abs() + 0.25
+    return {
+        "q nan": lambda x: x["q"][:, :, at, 2].fill_(NAN),
+        "k nan": lambda x: x["k"][:, :, at, 1].fill_(NAN),
+        "v inf": lambda x: x["v"][:, :, at, 3].fill_(INF),
+        "k -inf": lambda x: (x["q"][..., 0].copy_(first), x["k"][:, :, at, 0].fill_(-INF)),
+        "dO nan": lambda x: x["g"][:, :, at, 3].fill_(NAN),
+        "dO -inf": lambda x: x["g"][:, :, at, 3].fill_(-INF),
+        "delta nan": lambda x: x["delta"][:, :, at].fill_(NAN),
+        "lse -inf": lambda x: x["lse"][:, :, at].fill_(-INF),
+        "lse +inf": lambda x: x["lse"][:, :, at].fill_(INF),
+        "first dO, last v": lambda x: (x["g"][:, :, 0, 0].fill_(INF), x["v"][:, :, -1, 1].fill_(NAN)),
+    }
 
 
 def draw(H, Hkv, rows, d, dtype):
@@ -104,25 +141,65 @@ def check_forward_step(route, block, kinds):
                 close((name, fresh, "LSE"), lse[0, h].cpu().numpy(), np.array([w[1] for w in want]))
 
 
-def check_ring(route, layout, N, kinds):
-    """The driver on the whole ring: every row over all shards."""
+def check_backward_step(route, block, kinds):
+    (H, Hkv, c, d, dtype), (q_dev, kv_dev, layout) = route, block
+    t, at, scale, group = draw(H, Hkv, c, d, dtype), min(20, c - 2), 1.0 / np.sqrt(d), H // Hkv
+    n_keys = [c if layout == sa.CONTIGUOUS else a + 1 - (kv_dev > q_dev) for a in range(c)]
+    for name, poison in kinds(t, at).items():
+        x = poisoned(t, poison)
+        gq, gk, gv, gg, lse, delta = (x[n].cuda() for n in ("q", "k", "v", "g", "lse", "delta"))
+        grads = [torch.zeros(y.shape, dtype=F32, device="cuda") for y in (gq, gk, gv)]
+        shape = sa.shard_shape(gq, c, lse, kv=gk if Hkv != H else None)
+        sa.sa_attn_step_bwd(gq, gk, gv, gg, lse, delta, *grads, q_dev, kv_dev, 2, layout, shape)
+        torch.cuda.synchronize()
+        for kvh in {0, Hkv - 1}:
+            k, v = (inputs.to_f64(x[n][0, kvh]) for n in ("k", "v"))
+            dk, dv = np.zeros((c, d)), np.zeros((c, d))
+            for h in range(kvh * group, (kvh + 1) * group):
+                q, g, l, de = (inputs.to_f64(x[n][0, h]) for n in ("q", "g", "lse", "delta"))
+                dq, a, b = rows_backward(q, k, v, g, scale, l, de, n_keys)
+                dk, dv = dk + a, dv + b
+                close((name, "dQ"), grads[0][0, h].cpu().numpy(), dq)
+            close((name, "dK"), grads[1][0, kvh].cpu().numpy(), dk)
+            close((name, "dV"), grads[2][0, kvh].cpu().numpy(), dv)
+
+
+def check_ring(route, layout, N, kinds, backward):
+    """The drivers on the whole ring: every row over all shards."""
     H, Hkv, c, d, dtype = route
-    S, scale = N * c, 1.0 / np.sqrt(d)
+    S, scale, group = N * c, 1.0 / np.sqrt(d), H // Hkv
     t, at = draw(H, Hkv, S, d, dtype), c + 5
     for name, poison in kinds(t, at).items():
         x = poisoned(t, poison)
-        p = {n: hp.to_device_order(x[n].cuda(), N, layout) for n in ("q", "k", "v")}
+        p = {n: hp.to_device_order(x[n].cuda(), N, layout) for n in ("q", "k", "v", "g")}
         f32 = dict(dtype=F32, device="cuda")
-        O, LSE = torch.empty(1, H, S, d, **f32), torch.empty(1, H, S, **f32)
+        O, LSE, delta = torch.empty(1, H, S, d, **f32), torch.empty(1, H, S, **f32), torch.empty(1, H, S, **f32)
         shape = sa.shard_shape(p["q"], c, LSE, kv=p["k"] if Hkv != H else None)
         host = lambda y, h: hp.from_device_order_host(y[:, h:h + 1].cpu().numpy(), N, layout)[0, 0]
         sa.sa_ring_fwd(p["q"], p["k"], p["v"], O, LSE, N, layout, shape)
+        if backward:        # with the statistics of the clean tensors
+            y = {n: hp.to_device_order(t[n].cuda(), N, layout) for n in ("q", "k", "v")}
+            sa.sa_ring_fwd(y["q"], y["k"], y["v"], O, LSE, N, layout, shape)
+            grads = [torch.empty(z.shape, **f32) for z in (p["q"], p["k"], p["v"])]
+            sa.sa_ring_bwd(p["q"], p["k"], p["v"], p["g"], O, LSE, delta, *grads, N, layout, shape)
         torch.cuda.synchronize()
-        for h in {0, H - 1}:
-            q, k, v = (inputs.to_f64(x[n][0, i]) for n, i in (("q", h), ("k", h * Hkv // H), ("v", h * Hkv // H)))
-            want = [row_forward(q[a], k[:a + 1], v[:a + 1], scale, np.zeros(d), -INF) for a in range(S)]
-            close((name, "O"), host(O, h), np.stack([w[0] for w in want]))
-            close((name, "LSE"), host(LSE, h), np.array([w[1] for w in want]))
+        for kvh in {0, Hkv - 1}:
+            k, v = (inputs.to_f64(x[n][0, kvh]) for n in ("k", "v"))
+            dk, dv = np.zeros((S, d)), np.zeros((S, d))
+            for h in range(kvh * group, (kvh + 1) * group):
+                q, g = (inputs.to_f64(x[n][0, h]) for n in ("q", "g"))
+                if not backward:
+                    want = [row_forward(q[a], k[:a + 1], v[:a + 1], scale, np.zeros(d), -INF) for a in range(S)]
+                    close((name, "O"), host(O, h), np.stack([w[0] for w in want]))
+                    close((name, "LSE"), host(LSE, h), np.array([w[1] for w in want]))
+                    continue
+                dq, a, b = rows_backward(q, k, v, g, scale, host(LSE, h).astype(float), host(delta, h).astype(float),
+                                         range(1, S + 1))
+                dk, dv = dk + a, dv + b
+                close((name, "dQ"), host(grads[0], h), dq)
+            if backward:
+                close((name, "dK"), host(grads[1], kvh), dk)
+                close((name, "dV"), host(grads[2], kvh), dv)
 
 
 np_quiet = pytest.mark.filterwarnings("ignore::RuntimeWarning")
@@ -139,4 +216,26 @@ def test_a_score_that_is_no_number_makes_its_rows_nan(route, block):
 @pytest.mark.parametrize("layout", [sa.STRIPED, sa.CONTIGUOUS])
 @pytest.mark.parametrize("route", ROUTES)
 def test_scores_that_are_no_numbers_in_a_ring(route, layout):
-    check_ring(route, layout, 2, swallowed)
+    check_ring(route, layout, 2, swallowed, False)
+
+
+@np_quiet
+@pytest.mark.parametrize("block", BLOCKS)
+@pytest.mark.parametrize("route", ROUTES)
+def test_masked_values_stay_out_of_the_forward(route, block):
+    check_forward_step(route, block, masked)
+
+
+@np_quiet
+@pytest.mark.parametrize("block", BLOCKS)
+@pytest.mark.parametrize("route", ROUTES)
+def test_masked_values_stay_out_of_the_gradients(route, block):
+    check_backward_step(route, block, backward_kinds)
+
+
+@np_quiet
+@pytest.mark.parametrize("layout", [sa.STRIPED, sa.CONTIGUOUS])
+@pytest.mark.parametrize("route", ROUTES[:2] + ROUTES[4:5] + ROUTES[6:8])
+def test_masked_values_in_a_ring(route, layout):
+    check_ring(route, layout, 2, masked, False)
+    check_ring(route, layout, 2, lambda t, at: {n: f for n, f in backward_kinds(t, at).items() if "l" != n[0] and "delta" not in n}, True)
