@@ -5,7 +5,9 @@
 
 namespace sa {
 
-// x = hi + mid + lo (+ less than 2^-26 x)
+// x = hi + mid + lo (+ less than 2^-26 x; below 2^-109 in magnitude lo is a subnormal number, and x has
+// fewer than 24 bits left).  An infinite x, or one that rounds to an infinite hi, has NaN among its
+// terms, and every sum of products with it is NaN: the kernels do such rows over (f32_rows.h).
 __device__ inline void split(float x, __bf16& hi, __bf16& mid, __bf16& lo) {
     hi = (__bf16)x;
     float r = x - (float)hi;
@@ -36,10 +38,11 @@ struct Scale2 {
         return __builtin_amdgcn_exp2f(fmaf(x, hi, -m) + fmaf(fmaxf(x, -1e30f), lo, -m_lo));
     }
 };
-// natural to base-2 units, as hi + lo (an infinite x is its hi)
+// natural to base-2 units, as hi + lo.  x = +inf (no weight) is its hi; x = -inf and an x that
+// overflows have a lo that makes the exponential NaN: see split.
 __device__ inline void to_base2(float x, float& hi, float& lo) {
     hi = x * L2E_HI;
-    lo = fabsf(x) < INFINITY ? fmaf(x, L2E_HI, -hi) + x * L2E_LO : 0.f;
+    lo = x == INFINITY ? 0.f : fmaf(x, L2E_HI, -hi) + x * L2E_LO;
 }
 
 }  // namespace sa

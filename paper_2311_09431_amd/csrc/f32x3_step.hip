@@ -45,15 +45,6 @@ __device__ inline f32x16 zero16() {
 // streamed row (within a tile) of score register r
 __device__ inline int reg_row(int r, int h) { return 8 * (r / 4) + 4 * h + r % 4; }
 
-// as split; an infinite x, or one that rounds to an infinite hi, is its hi
-__device__ inline void split_any(float x, __bf16& hi, __bf16& mid, __bf16& lo) {
-    hi = (__bf16)x;
-    float r = x - (float)hi;
-    r = fabsf(r) < INFINITY ? r : 0.f;
-    mid = (__bf16)r;
-    lo = (__bf16)(r - (float)mid);
-}
-
 // 8 consecutive floats of a row from column col on, zeros from column d on (d a multiple of 4)
 struct Chunk { float4 a, b; };
 __device__ inline Chunk load_chunk(const float* row, int col, int d, bool ok) {
@@ -68,7 +59,7 @@ __device__ inline void split_chunk(const Chunk& x, bf16x8 (&o)[3]) {
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
         __bf16 hi, mid, lo;
-        split_any(v[e], hi, mid, lo);
+        split(v[e], hi, mid, lo);
         o[0][e] = hi; o[1][e] = mid; o[2][e] = lo;
     }
 }
@@ -131,8 +122,8 @@ struct Lane {
     }
 };
 
-// 32 x 32 scores: rows = the tile at `planes`, columns = the wavefront's owned rows.  An infinite
-// operand makes the leading products infinite with the right sign and the others anything.
+// 32 x 32 scores: rows = the tile at `planes`, columns = the wavefront's owned rows.  NaN where an
+// operand is infinite or rounds to an infinite hi (its other terms are NaN).
 template <int KS>
 __device__ inline f32x16 scores(const char* planes, const bf16x8x3 (&f)[KS], const Lane& ln) {
     f32x16 hi = zero16(), lo = zero16();
@@ -144,7 +135,7 @@ __device__ inline f32x16 scores(const char* planes, const bf16x8x3 (&f)[KS], con
         mfma6(a, f[ks], hi, lo);
     }
 #pragma unroll
-    for (int r = 0; r < 16; ++r) hi[r] = fabsf(hi[r]) < INFINITY ? hi[r] + lo[r] : hi[r];
+    for (int r = 0; r < 16; ++r) hi[r] += lo[r];
     return hi;
 }
 // acc (32-column blocks x owned rows) += tile^T w.  The tile's sum is formed by itself and added

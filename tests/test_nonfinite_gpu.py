@@ -104,6 +104,16 @@ def backward_kinds(t, at):
     }
 
 
+def large(t, at):
+    """Finite, but beyond the largest bf16 number (fp32 storage)."""
+    half = torch.full_like(t["q"][..., 0], 0.5)
+    return {
+        "k large": lambda x: (x["q"][..., 0].copy_(half), x["k"][:, :, at, 0].fill_(3.4e38)),
+        "k large, negative": lambda x: (x["q"][..., 0].copy_(half), x["k"][:, :, at, 0].fill_(-3.4e38)),
+        "v large": lambda x: x["v"][:, :, at, 3].fill_(3.4e38),
+    }
+
+
 def draw(H, Hkv, rows, d, dtype):
     t = {n: inputs.gaussian((1, h, rows, d), 40 + i + rows + d, dtype)
          for i, (n, h) in enumerate((("q", H), ("k", Hkv), ("v", Hkv), ("g", H)))}
@@ -239,3 +249,10 @@ def test_masked_values_stay_out_of_the_gradients(route, block):
 def test_masked_values_in_a_ring(route, layout):
     check_ring(route, layout, 2, masked, False)
     check_ring(route, layout, 2, lambda t, at: {n: f for n, f in backward_kinds(t, at).items() if "l" != n[0] and "delta" not in n}, True)
+
+
+@np_quiet
+@pytest.mark.parametrize("block", BLOCKS)
+@pytest.mark.parametrize("route", [r for r in ROUTES if r[4] is F32])
+def test_numbers_beyond_the_largest_bf16(route, block):
+    check_forward_step(route, block, large)
