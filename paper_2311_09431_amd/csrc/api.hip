@@ -2,6 +2,7 @@
 // the kernels, and the single-GPU ring drivers (Algorithm 1 played in sequence).
 #include <math.h>
 
+#include <algorithm>
 #include <vector>
 
 #include "sa_internal.h"
@@ -104,13 +105,55 @@ int check_skip(const sa_shape* s, int bq, int bk) {
                                                                                       : SA_ERR_SHAPE;
 }
 
-hipError_t launch_fwd(const StepArgs& a, int dtype, hipStream_t st) {
-    if (!sa::fwd_mfma_supported(a, dtype)) return sa::launch_fwd_f32(a, dtype, st);
-    return sa::launch_fwd_mfma(a, st);
+size_t elt_size(int dtype) { return dtype == SA_F32 ? 4 : 2; }
+
+// HIP takes fewer than 2^32 threads a launch.  The kernels' grids are one-dimensional; at worst they
+// hold one workgroup of 256 threads per 32 rows of each side (as many at d > 128, where a key-owning
+// workgroup has 64 rows and half of the columns).
+constexpr int64_t kMostWorkgroups = (int64_t(1) << 24) - 1;
+int64_t workgroups_per_kv_head(const StepArgs& a) {
+    return ((int64_t)a.c / 32 + 2) * ((int64_t)a.n_q * (a.H / a.H_kv) + a.n_kv);
 }
-hipError_t launch_bwd(const StepArgs& a, int dtype, hipStream_t st) {
-    if (!sa::bwd_mfma_supported(a, dtype)) return sa::launch_bwd_f32(a, dtype, st);
-    return sa::bwd_split_wanted(a) ? sa::launch_bwd_split(a, st) : sa::launch_bwd_mfma(a, st);
+// Blocks of a launch that may hold more are played in parts of whole key/value heads and their groups.
+template <typename Launch>
+hipError_t in_parts(const StepArgs& a, int dtype, Launch launch) {
+    const int64_t fit = std::max<int64_t>(1, kMostWorkgroups / workgroups_per_kv_head(a));
+    if ((int64_t)a.B * a.H_kv <= fit) return launch(a);
+    const int heads = (int)std::min<int64_t>(fit, a.H_kv), batches = (int)std::max<int64_t>(1, fit / a.H_kv);
+    const int group = a.H / a.H_kv;
+    const int64_t es = (int64_t)elt_size(dtype);
+    for (int b = 0; b < a.B; b += batches)
+        for (int h = 0; h < a.H_kv; h += heads) {
+            StepArgs part = a;
+            part.B = std::min(batches, a.B - b);
+            part.H_kv = std::min(heads, a.H_kv - h);
+            part.H = part.H_kv * group;
+            const int64_t q = b * a.stride_b + (int64_t)h * group * a.stride_h, kv = b * a.kv_stride_b + h * a.kv_stride_h;
+            const int64_t stat = b * a.stat_stride_b + (int64_t)h * group * a.stat_stride_h;
+            auto in = [&](const void* p, int64_t at) -> const void* { return p ? (const char*)p + at * es : nullptr; };
+            part.q = in(a.q, q); part.dout = in(a.dout, q); part.k = in(a.k, kv); part.v = in(a.v, kv);
+            if (a.o) part.o = a.o + q;
+            if (a.dq) part.dq = a.dq + q;
+            if (a.dk) part.dk = a.dk + kv;
+            if (a.dv) part.dv = a.dv + kv;
+            part.lse = a.lse + stat;
+            if (a.delta) part.delta = a.delta + stat;
+            if (a.q_pos) part.q_pos = a.q_pos + b * a.pos_stride_b;
+            if (hipError_t e = launch(part)) return e;
+        }
+    return hipSuccess;
+}
+
+hipError_t launch_fwd(const StepArgs& all, int dtype, hipStream_t st) {
+    return in_parts(all, dtype, [&](const StepArgs& a) {
+        return sa::fwd_mfma_supported(a, dtype) ? sa::launch_fwd_mfma(a, st) : sa::launch_fwd_f32(a, dtype, st);
+    });
+}
+hipError_t launch_bwd(const StepArgs& all, int dtype, hipStream_t st) {
+    return in_parts(all, dtype, [&](const StepArgs& a) {
+        if (!sa::bwd_mfma_supported(a, dtype)) return sa::launch_bwd_f32(a, dtype, st);
+        return sa::bwd_split_wanted(a) ? sa::launch_bwd_split(a, st) : sa::launch_bwd_mfma(a, st);
+    });
 }
 
 int step_fwd(const void* q, const void* k, const void* v, float* o, float* lse, int q_dev, int kv_dev,
@@ -139,15 +182,11 @@ int step_bwd(const void* q, const void* k, const void* v, const void* dout, cons
 }
 
 // The ring drivers without per-step timings: one launch per kernel for all blocks of the played
-// devices, where row counts and grids (at worst one workgroup per 32 rows, two kinds of them in
-// the backward) stay within 31 bits.  Else, and when the caller wants each step's time, one launch
-// per block and kernel.
-bool one_launch(const sa_shape* s, int N) {
-    const int64_t most = int64_t(1) << 31;
-    return (int64_t)N * s->c < most && ((int64_t)s->c / 32 + 1) * N * s->B * s->H * 4 < most;
+// devices, where rows are numbered in 31 bits and a key/value head's blocks fit a launch.  Else,
+// and when the caller wants each step's time, one launch per block and kernel.
+bool one_launch(const StepArgs& a, int N) {
+    return (int64_t)N * a.c < (int64_t(1) << 31) && workgroups_per_kv_head(a) <= kMostWorkgroups;
 }
-
-size_t elt_size(int dtype) { return dtype == SA_F32 ? 4 : 2; }
 
 // Event bookkeeping for the drivers' optional per-step timings.
 struct StepTimer {
@@ -296,7 +335,7 @@ int sa_ring_fwd_tiled(const void* Q, const void* K, const void* V, float* O, flo
     const int j0 = q_dev_only >= 0 ? q_dev_only : 0, j1 = q_dev_only >= 0 ? q_dev_only + 1 : N;
     StepArgs all = make_args(shape, j0, 0, layout);
     all.n_q = j1 - j0; all.n_kv = N; all.q_shard = shard; all.kv_shard = kv_shard; all.fresh = true;
-    if (!step_ms && one_launch(shape, N)) {
+    if (!step_ms && one_launch(all, N)) {
         all.q = in_at(Q, j0); all.k = K; all.v = V;
         all.o = O + j0 * shard; all.lse = LSE + (int64_t)j0 * shape->c;
         all.skip_bq = skip_bq; all.skip_bk = skip_bk;
@@ -356,7 +395,7 @@ int sa_ring_bwd_tiled(const void* Q, const void* K, const void* V, const void* d
     all.n_q = j1 - j0; all.q_shard = shard; all.kv_shard = kv_shard; all.fresh = true;
     // key shards that some played device sees; contiguous layout: none further on than the last
     all.n_kv = layout == SA_STRIPED ? N : j1;
-    if (!step_ms && one_launch(shape, N)) {
+    if (!step_ms && one_launch(all, N)) {
         all.q = in_at(Q, j0); all.k = K; all.v = V; all.dout = in_at(dO, j0);
         all.lse = const_cast<float*>(LSE) + (int64_t)j0 * shape->c;
         all.delta = delta + (int64_t)j0 * shape->c;
