@@ -521,7 +521,7 @@ fwd_mfma_kernel(StepArgs p, int n_qtiles) {
     // empty (LSE = -inf) takes the partial and never looks at the stored O.
     const float l_tot = half_wave_sum(l);
     const float lse_old = RING ? -INFINITY : L[a] * LOG2E;                    // -inf stays -inf
-    const float lse_part = l_tot > 0.f ? m + __builtin_amdgcn_logf(l_tot) : -INFINITY;
+    const float lse_part = l_tot == 0.f ? -INFINITY : m + __builtin_amdgcn_logf(l_tot);      // a NaN score: NaN
     const float top = fmaxf(lse_old, lse_part);
     const float ref = top == -INFINITY ? 0.f : top;                           // no (-inf) - (-inf)
     const float w_old = __builtin_amdgcn_exp2f(lse_old - ref), w_part = __builtin_amdgcn_exp2f(lse_part - ref);

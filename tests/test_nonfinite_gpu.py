@@ -32,12 +32,12 @@ BLOCKS = [(1, 0, sa.STRIPED), (0, 1, sa.STRIPED), (1, 0, sa.CONTIGUOUS)]
 INF, NAN = float("inf"), float("nan")
 
 
-def close(name, got, want):
+def close(name, got, want, tol=2e-5):
     for what in (np.isnan, np.isposinf, np.isneginf):
         assert np.array_equal(what(got), what(want)), (name, what.__name__, np.argwhere(what(got) != what(want))[:4])
     ok = np.isfinite(want)
     err = np.abs(got[ok] - want[ok]) / np.maximum(1.0, np.abs(want[ok]))
-    assert err.size == 0 or err.max() <= 2e-5, (name, float(err.max()))
+    assert err.size == 0 or err.max() <= tol, (name, float(err.max()))
 
 
 def row_forward(q, K, V, scale, o0, lse0):
@@ -129,7 +129,7 @@ def poisoned(t, poison):
     return x
 
 
-def check_forward_step(route, block, kinds):
+def check_forward_step(route, block, kinds, tol=2e-5):
     (H, Hkv, c, d, dtype), (q_dev, kv_dev, layout) = route, block
     t, at, scale = draw(H, Hkv, c, d, dtype), min(20, c - 2), 1.0 / np.sqrt(d)
     n_keys = [c if layout == sa.CONTIGUOUS else a + 1 - (kv_dev > q_dev) for a in range(c)]
@@ -147,8 +147,8 @@ def check_forward_step(route, block, kinds):
                 o0 = np.zeros((c, d)) if fresh else inputs.to_f64(x["o"][0, h])
                 l0 = np.full(c, -INF) if fresh else inputs.to_f64(x["lse"][0, h])
                 want = [row_forward(q[a], k[:n], v[:n], scale, o0[a], l0[a]) for a, n in enumerate(n_keys)]
-                close((name, fresh, "O"), o[0, h].cpu().numpy(), np.stack([w[0] for w in want]))
-                close((name, fresh, "LSE"), lse[0, h].cpu().numpy(), np.array([w[1] for w in want]))
+                close((name, fresh, "O"), o[0, h].cpu().numpy(), np.stack([w[0] for w in want]), tol)
+                close((name, fresh, "LSE"), lse[0, h].cpu().numpy(), np.array([w[1] for w in want]), tol)
 
 
 def check_backward_step(route, block, kinds):
@@ -174,11 +174,11 @@ def check_backward_step(route, block, kinds):
             close((name, "dV"), grads[2][0, kvh].cpu().numpy(), dv)
 
 
-def check_ring(route, layout, N, kinds, backward):
+def check_ring(route, layout, N, kinds, backward, tol=2e-5):
     """The drivers on the whole ring: every row over all shards."""
     H, Hkv, c, d, dtype = route
     S, scale, group = N * c, 1.0 / np.sqrt(d), H // Hkv
-    t, at = draw(H, Hkv, S, d, dtype), c + 5
+    t, at = draw(H, Hkv, S, d, dtype), S // 2 + 5
     for name, poison in kinds(t, at).items():
         x = poisoned(t, poison)
         p = {n: hp.to_device_order(x[n].cuda(), N, layout) for n in ("q", "k", "v", "g")}
@@ -200,8 +200,8 @@ def check_ring(route, layout, N, kinds, backward):
                 q, g = (inputs.to_f64(x[n][0, h]) for n in ("q", "g"))
                 if not backward:
                     want = [row_forward(q[a], k[:a + 1], v[:a + 1], scale, np.zeros(d), -INF) for a in range(S)]
-                    close((name, "O"), host(O, h), np.stack([w[0] for w in want]))
-                    close((name, "LSE"), host(LSE, h), np.array([w[1] for w in want]))
+                    close((name, "O"), host(O, h), np.stack([w[0] for w in want]), tol)
+                    close((name, "LSE"), host(LSE, h), np.array([w[1] for w in want]), tol)
                     continue
                 dq, a, b = rows_backward(q, k, v, g, scale, host(LSE, h).astype(float), host(delta, h).astype(float),
                                          range(1, S + 1))
@@ -256,3 +256,15 @@ def test_masked_values_in_a_ring(route, layout):
 @pytest.mark.parametrize("route", [r for r in ROUTES if r[4] is F32])
 def test_numbers_beyond_the_largest_bf16(route, block):
     check_forward_step(route, block, large)
+
+
+@np_quiet
+@pytest.mark.parametrize("layout", [sa.STRIPED, sa.CONTIGUOUS])
+@pytest.mark.parametrize("route", [(2, 1, 160, 64, BF16), (1, 1, 128, 128, BF16), (1, 1, 130, 136, BF16)])
+def test_the_128_row_kernels_leave_no_number_in_the_lse_of_such_a_row(route, layout):
+    # O of a row with a NaN or +inf score is NaN there too; its LSE would pass for that of a row without keys
+    kinds = lambda t, at: {n: f for n, f in swallowed(t, at).items() if "-inf" not in n}
+    for N in (1, 2):
+        check_ring(route, layout, N, kinds, False, 2e-2)
+    for block in BLOCKS:
+        check_forward_step(route, block, kinds, 2e-2)
