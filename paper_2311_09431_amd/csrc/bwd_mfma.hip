@@ -687,8 +687,10 @@ __device__ __forceinline__ void bwd_dkdv(const StepArgs& p, int n_tiles, int lin
                 trip(F{}, P0{}, F{}, T{}, 0, (t + 2) * tile_pitch);
                 trip(F{}, P1{}, F{}, T{}, 0, (t + 3) * tile_pitch);
             }
+            if (WALK == WALK_FULL) break;               // nothing else comes before the last pair
             continue;
         }
+        if (WALK == WALK_FULL && !ONE_FORM) break;
         if (t + 2 >= n_qt) {                            // last pair of the block
             if (!RING) break;
             if (++q_dev == p.q_dev + p.n_q) {
@@ -800,10 +802,12 @@ void launch_dkdv_waves(const StepArgs& a, hipStream_t st, int n_tiles) {
 template <int WALK, int DP, bool PART>
 void launch_dkdv(const StepArgs& a, hipStream_t st, int n_tiles) {
     if constexpr (DP <= 64) {
-        // Uneven work that two workgroups per compute unit would hold all at once is better taken up
-        // one after the other, heaviest first (16 heads of 4096 tokens, triangular: 0.168 against
-        // 0.177 ms).
-        if (!uneven(a) || (int64_t)n_tiles * a.n_kv * a.B * a.H_kv > 2 * N_CU)
+        // Uneven work that two workgroups per compute unit would hold all at once, or whose longest walk is
+        // short, is better taken up one after the other, heaviest first (triangular, whole step: 512
+        // workgroups of 4096 rows 0.168 against 0.177 ms; 768 of 1024, 2048 and 4096 rows 116 / 124, 157 /
+        // 173, 266 / 257 us; 1536 of 2048 and 4096 291 / 304, 460 / 458).
+        const int64_t wgs = (int64_t)n_tiles * a.n_kv * a.B * a.H_kv;
+        if (!uneven(a) || (wgs > 2 * N_CU && n_tiles >= 32))
             return launch_dkdv_waves<WALK, DP, PART, 2>(a, st, n_tiles);
     }
     launch_dkdv_waves<WALK, DP, PART, 1>(a, st, n_tiles);
