@@ -302,7 +302,7 @@ fwd_f32_kernel(StepArgs p, int n_tiles) {
         }
         if (kw == 0 && h == 0) *L = top + logf(w_sum);
     }
-    each_row<SPLIT>(odd_rows, kw, [&](int i) { fwd_row<T>(p, b, hd, dev_i, q0 + 32 * qw + i, lane); });
+    each_row<SPLIT>(odd_rows, kw, [&](const StepArgs& again, int i) { fwd_row<T>(again, b, hd, dev_i, q0 + 32 * qw + i, lane); });
 }
 
 // scale * acc to 32 owned rows (this lane's row at dst_row), added to what is there unless fresh
@@ -388,7 +388,7 @@ __device__ inline void bwd_dq(const StepArgs& p, int n_tiles, int linear, float*
         SPLIT > 1 ? combine<SPLIT, NB>(acc, lds + qw * SPLIT * NB * 16 * 64, masks + qw * SPLIT, odd, kw, lane) : row_mask(odd);
     if (a_own < p.c && !((odd_rows >> n) & 1))
         add_rows<SPLIT, NB>(p.dq + base + (int64_t)a * p.stride_s, acc, p.scale, 0, d, kw, h, p.fresh);
-    each_row<SPLIT>(odd_rows, kw, [&](int i) { dq_row<T>(p, b, hd, dev_i, q0 + 32 * qw + i, lane); });
+    each_row<SPLIT>(odd_rows, kw, [&](const StepArgs& again, int i) { dq_row<T>(again, b, hd, dev_i, q0 + 32 * qw + i, lane); });
 }
 
 // -------------------------------------------------------------------- dK/dV
@@ -480,8 +480,8 @@ __device__ inline void bwd_dkdv(const StepArgs& p, int n_tiles, int linear, floa
         add_rows<SPLIT, NB>(p.dv + row, accv, 1.f, col0, d, qsub, h, p.fresh);
         add_rows<SPLIT, NB>(p.dk + row, acck, p.scale, col0, d, qsub, h, p.fresh);
     }
-    each_row<SPLIT>(odd_rows, qsub, [&](int i) {
-        dkdv_row<T>(p, b, kvh, dev_i, k0 + 32 * own + i, col0, HALVES > 1 ? min(d, col0 + 128) : d, lane);
+    each_row<SPLIT>(odd_rows, qsub, [&](const StepArgs& again, int i) {
+        dkdv_row<T>(again, b, kvh, dev_i, k0 + 32 * own + i, col0, HALVES > 1 ? min(d, col0 + 128) : d, lane);
     });
 }
 

@@ -301,7 +301,7 @@ fwd_f32x3_kernel(StepArgs p, int n_tiles) {
             }
         if (h == 0) *L = top + logf(w_sum);
     }
-    each_row<1>(odd_rows, 0, [&](int i) { fwd_row<float>(p, b, hd, dev_i, q0 + 32 * ln.wave + i, ln.lane); });
+    each_row<1>(odd_rows, 0, [&](const StepArgs& again, int i) { fwd_row<float>(again, b, hd, dev_i, q0 + 32 * ln.wave + i, ln.lane); });
 }
 
 // scale * acc to this lane's row, added to what is there unless fresh
@@ -364,7 +364,7 @@ __device__ inline void bwd_dq(const StepArgs& p, int n_tiles, int linear, char* 
     const uint32_t odd_rows = row_mask(a_own < p.c && not_finite<NB>(acc));
     if (a_own < p.c && !((odd_rows >> n) & 1))
         add_rows<NB>(p.dq + base + (int64_t)a * p.stride_s, acc, p.scale, d, h, p.fresh);
-    each_row<1>(odd_rows, 0, [&](int i) { dq_row<float>(p, b, hd, dev_i, q0 + 32 * ln.wave + i, ln.lane); });
+    each_row<1>(odd_rows, 0, [&](const StepArgs& again, int i) { dq_row<float>(again, b, hd, dev_i, q0 + 32 * ln.wave + i, ln.lane); });
 }
 
 // -------------------------------------------------------------------- dK/dV
@@ -466,7 +466,7 @@ __device__ inline void bwd_dkdv(const StepArgs& p, int n_tiles, int linear, char
         add_rows<NB>(p.dv + row, accv, 1.f, d, h, p.fresh);
         add_rows<NB>(p.dk + row, acck, p.scale, d, h, p.fresh);
     }
-    each_row<1>(odd_rows, 0, [&](int i) { dkdv_row<float>(p, b, kvh, dev_i, k0 + 32 * ln.wave + i, 0, d, ln.lane); });
+    each_row<1>(odd_rows, 0, [&](const StepArgs& again, int i) { dkdv_row<float>(again, b, kvh, dev_i, k0 + 32 * ln.wave + i, 0, d, ln.lane); });
 }
 
 // Both in one launch: workgroups 0 .. n_dkdv - 1 own keys, the others queries (they share nothing

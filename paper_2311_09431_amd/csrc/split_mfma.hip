@@ -137,6 +137,16 @@ __device__ inline uint32_t take_odd(const uint32_t* masks) {
     for (int w = 0; w < WAVES; ++w) rows |= masks[w];
     return __builtin_amdgcn_readfirstlane(rows);
 }
+// Backward, what makes a row odd: a score that is not finite (z: NaN then), or a dS that is not, which
+// leaves no column of its sum finite.  (Elements of the operands reach one of the two; masked pairs
+// have a dS of 0 * (dP - delta).)
+__device__ inline void look_at(float (&z)[2], const f32x16& s) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) z[r % 2] = fmaf(s[r], 0.f, z[r % 2]);
+}
+__device__ inline bool odd_sum(const float (&z)[2], const f32x16 (&ds_sum)[4]) {
+    return z[0] + z[1] != 0.f || not_finite<1>(ds_sum);
+}
 // piece i of this wavefront's share and its first column
 template <int DP>
 __device__ inline int piece_of(int i, const Lane<DP>& ln) { return ln.wave * blocks_of(DP) + i; }
@@ -334,22 +344,31 @@ fwd_split_kernel(StepArgs p, int n_tiles) {
         }
         if (ln.wave == 0 && h == 0) *L = top + logf(w_sum);
     }
-    each_row<WAVES>(odd_rows, ln.wave, [&](int i) { fwd_row<__hip_bfloat16>(p, b, hd, dev_i, q0 + i, ln.lane); });
+    each_row<WAVES>(odd_rows, ln.wave, [&](const StepArgs& again, int i) { fwd_row<__hip_bfloat16>(again, b, hd, dev_i, q0 + i, ln.lane); });
 }
 
-// adds scale * (sum of the partial results at buf) to the lane's row, or stores it (fresh)
+// this wavefront's share of the lane's row as it stands (zeros if not wanted): on its way while the
+// partial results meet
 template <int DP>
-__device__ inline void add_rows(float* row, const char* buf, float scale, int d, bool fresh, const Lane<DP>& ln) {
+__device__ inline void load_old(float4 (&x)[blocks_of(DP)], const float* row, int d, bool wanted, const Lane<DP>& ln) {
+#pragma unroll
+    for (int i = 0; i < blocks_of(DP); ++i) {
+        x[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (wanted && column_of<DP>(i, ln) < d) x[i] = *reinterpret_cast<const float4*>(row + column_of<DP>(i, ln));
+    }
+}
+// x + scale * (sum of the partial results at buf) to the lane's row
+template <int DP>
+__device__ inline void add_rows(float* row, float4 (&x)[blocks_of(DP)], const char* buf, float scale, int d,
+                                const Lane<DP>& ln) {
 #pragma unroll
     for (int i = 0; i < blocks_of(DP); ++i) {
         const int col = column_of<DP>(i, ln);
         if (col >= d) continue;
-        float4* dst = reinterpret_cast<float4*>(row + col);
         const float4 s = take_sum<DP>(buf, piece_of<DP>(i, ln), ln);
-        float4 x = fresh ? make_float4(0.f, 0.f, 0.f, 0.f) : *dst;
-        x.x = fmaf(scale, s.x, x.x); x.y = fmaf(scale, s.y, x.y);
-        x.z = fmaf(scale, s.z, x.z); x.w = fmaf(scale, s.w, x.w);
-        *dst = x;
+        x[i].x = fmaf(scale, s.x, x[i].x); x[i].y = fmaf(scale, s.y, x[i].y);
+        x[i].z = fmaf(scale, s.z, x[i].z); x[i].w = fmaf(scale, s.w, x[i].w);
+        *reinterpret_cast<float4*>(row + col) = x[i];
     }
 }
 
@@ -381,6 +400,7 @@ __device__ inline void bwd_dq(const StepArgs& p, int n_tiles, int linear, char* 
 #pragma unroll
     for (int mb = 0; mb < 4; ++mb) acc[mb] = zero16();
 
+    float z[2] = {0.f, 0.f};
     walk_keys<DP>(p, dev, q0, dt_make_rsrc((const __bf16*)p.k + kv_base, p.c, pitch, d),
               dt_make_rsrc((const __bf16*)p.v + kv_base, p.c, pitch, d), lds, ln,
               [&](const char* k, const char* v, int key0, const Block& blk) {
@@ -393,17 +413,21 @@ __device__ inline void bwd_dq(const StepArgs& p, int n_tiles, int linear, char* 
             if (reg_row(r, h) > lane_last) pr = 0.f;
             ds[r] = pr * (dp[r] - delta);
         }
+        if (EXACT) look_at(z, s);
         accumulate<DP, EXACT>(acc, k, ds, ln);
     });
 
+    float* const DQ = p.dq + base + (int64_t)a * p.stride_s;
+    float4 old[blocks_of(DP)];
+    load_old<DP>(old, DQ, d, !p.fresh && a_own < p.c, ln);
     __syncthreads();
     put_partial<DP>(lds, acc, ln);
-    if (EXACT) put_odd(masks, a_own < p.c && not_finite<blocks_of(DP)>(acc), ln.wave, ln.lane);
+    if (EXACT) put_odd(masks, a_own < p.c && odd_sum(z, acc), ln.wave, ln.lane);
     __syncthreads();
     const uint32_t odd_rows = EXACT ? take_odd(masks) : 0;
     if (a_own < p.c && !((odd_rows >> n) & 1))
-        add_rows<DP>(p.dq + base + (int64_t)a * p.stride_s, lds, p.scale, d, p.fresh, ln);
-    if (EXACT) each_row<WAVES>(odd_rows, ln.wave, [&](int i) { dq_row<__hip_bfloat16>(p, b, hd, dev_i, q0 + i, ln.lane); });
+        add_rows<DP>(DQ, old, lds, p.scale, d, ln);
+    if (EXACT) each_row<WAVES>(odd_rows, ln.wave, [&](const StepArgs& again, int i) { dq_row<__hip_bfloat16>(again, b, hd, dev_i, q0 + i, ln.lane); });
 }
 
 // -------------------------------------------------------------------- dK/dV
@@ -465,6 +489,7 @@ __device__ inline void bwd_dkdv(const StepArgs& p, int n_tiles, int linear, char
         if (tid < GROUP && r >= p.c) stat = INFINITY;
     };
     enter_block();
+    float z[2] = {0.f, 0.f};
     int g0 = first / GROUP * GROUP, parity = 0;
     request(g0, lds);
     for (;;) {
@@ -503,6 +528,7 @@ __device__ inline void bwd_dkdv(const StepArgs& p, int n_tiles, int linear, char
                 if (a0 + i < lane_first) pr[r] = 0.f;
                 ds[r] = pr[r] * (dp[r] - st[2 * GROUP + i]);
             }
+            if (EXACT) look_at(z, s);
             accumulate<DP, EXACT>(accv, g, pr, ln);
             accumulate<DP, EXACT>(acck, q, ds, ln);
         }
@@ -513,21 +539,21 @@ __device__ inline void bwd_dkdv(const StepArgs& p, int n_tiles, int linear, char
 
     constexpr int HALF = PARTIAL_BYTES<DP>;
     static_assert(2 * HALF <= 4 * GROUP_BYTES<DP>, "partial results");
+    float4 old_v[blocks_of(DP)], old_k[blocks_of(DP)];
+    load_old<DP>(old_v, p.dv + row, d, !p.fresh && key_own < p.c, ln);
+    load_old<DP>(old_k, p.dk + row, d, !p.fresh && key_own < p.c, ln);
     __syncthreads();
     put_partial<DP>(lds, accv, ln);
     put_partial<DP>(lds + HALF, acck, ln);
-    if (EXACT) {
-        const bool odd = not_finite<blocks_of(DP)>(accv) || not_finite<blocks_of(DP)>(acck);
-        put_odd(masks, key_own < p.c && odd, ln.wave, ln.lane);
-    }
+    if (EXACT) put_odd(masks, key_own < p.c && odd_sum(z, acck), ln.wave, ln.lane);
     __syncthreads();
     const uint32_t odd_rows = EXACT ? take_odd(masks) : 0;
     if (key_own < p.c && !((odd_rows >> n) & 1)) {
-        add_rows<DP>(p.dv + row, lds, 1.f, d, p.fresh, ln);
-        add_rows<DP>(p.dk + row, lds + HALF, p.scale, d, p.fresh, ln);
+        add_rows<DP>(p.dv + row, old_v, lds, 1.f, d, ln);
+        add_rows<DP>(p.dk + row, old_k, lds + HALF, p.scale, d, ln);
     }
     if (EXACT)
-        each_row<WAVES>(odd_rows, ln.wave, [&](int i) { dkdv_row<__hip_bfloat16>(p, b, kvh, dev_i, k0 + i, 0, d, ln.lane); });
+        each_row<WAVES>(odd_rows, ln.wave, [&](const StepArgs& again, int i) { dkdv_row<__hip_bfloat16>(again, b, kvh, dev_i, k0 + i, 0, d, ln.lane); });
 }
 
 // Both in one launch, the two sequences of n_dkdv key-owning and n_dq query-owning workgroups
