@@ -500,10 +500,6 @@ bwd_f32_kernel(StepArgs p, int n_tiles, int n_dkdv) {
 }
 
 // ----------------------------------------------------------------- dispatch
-// Streamed rows split over the wavefronts (SPLIT) while 128-row workgroups would leave compute
-// units idle.
-constexpr int64_t kFullGrid = 256;
-
 template <typename T, int DP, int SPLIT>
 hipError_t run_fwd(const StepArgs& a, hipStream_t st) {
     const int rows = 32 * (WAVES / SPLIT), n_tiles = (a.c + rows - 1) / rows;
@@ -532,11 +528,13 @@ hipError_t run_bwd(const StepArgs& a, hipStream_t st) {
 template <typename T, int DP>
 hipError_t run(const StepArgs& a, bool backward, hipStream_t st) {
     constexpr int MOST = DP > 128 ? 2 : 4;          // what 160 KiB of LDS hold
-    const bool split = (int64_t)((a.c + 127) / 128) * a.n_q * a.B * a.H < kFullGrid;
-    if constexpr (DP <= 128 && sizeof(T) == 4)      // fuller fp32 launches: f32x3_wanted
+    if constexpr (DP <= 128 && sizeof(T) == 4) {      // fuller fp32 launches: f32x3_wanted
         return backward ? run_bwd<T, DP, MOST>(a, st) : run_fwd<T, DP, MOST>(a, st);
-    if (backward) return split ? run_bwd<T, DP, MOST>(a, st) : run_bwd<T, DP, 1>(a, st);
-    return split ? run_fwd<T, DP, MOST>(a, st) : run_fwd<T, DP, 1>(a, st);
+    } else {
+        const bool split = few_row_tiles(a, backward);
+        if (backward) return split ? run_bwd<T, DP, MOST>(a, st) : run_bwd<T, DP, 1>(a, st);
+        return split ? run_fwd<T, DP, MOST>(a, st) : run_fwd<T, DP, 1>(a, st);
+    }
 }
 template <typename T>
 hipError_t run(const StepArgs& a, bool backward, hipStream_t st) {
@@ -549,12 +547,12 @@ hipError_t run(const StepArgs& a, bool backward, hipStream_t st) {
 }  // namespace
 
 hipError_t launch_fwd_f32(const StepArgs& a, int dtype, hipStream_t st) {
-    if (dtype == SA_F32 && f32x3_wanted(a)) return launch_f32x3(a, false, st);
+    if (dtype == SA_F32 && f32x3_wanted(a, false)) return launch_f32x3(a, false, st);
     if (short_exact_wanted(a, dtype, false)) return launch_short_exact(a, false, st);
     return dtype == SA_F32 ? run<float>(a, false, st) : run<__hip_bfloat16>(a, false, st);
 }
 hipError_t launch_bwd_f32(const StepArgs& a, int dtype, hipStream_t st) {
-    if (dtype == SA_F32 && f32x3_wanted(a)) return launch_f32x3(a, true, st);
+    if (dtype == SA_F32 && f32x3_wanted(a, true)) return launch_f32x3(a, true, st);
     if (short_exact_wanted(a, dtype, true)) return launch_short_exact(a, true, st);
     return dtype == SA_F32 ? run<float>(a, true, st) : run<__hip_bfloat16>(a, true, st);
 }

@@ -503,9 +503,7 @@ hipError_t run(const StepArgs& a, bool backward, hipStream_t st) {
 // step, 2048 tokens, 16 heads, d 128): forward 0.23 / 0.36 ms, backward 0.46 / 0.68; with the
 // streamed rows split over the wavefronts, which those do below that (128 row tiles, 4096 tokens
 // on 2 devices, 4 heads): 0.48 / 0.26 and 0.81 / 0.71.
-bool f32x3_wanted(const StepArgs& a) {
-    return a.d <= 128 && (int64_t)((a.c + 127) / 128) * a.n_q * a.B * a.H >= 256;
-}
+bool f32x3_wanted(const StepArgs& a, bool backward) { return a.d <= 128 && !few_row_tiles(a, backward); }
 
 hipError_t launch_f32x3(const StepArgs& a, bool backward, hipStream_t st) {
     return a.d <= 64 ? run<64>(a, backward, st) : run<128>(a, backward, st);

@@ -21,6 +21,8 @@ CASES = [
     (2, 32, 32, 260, 100, 2, 1.0),
     (1, 43, 43, 256, 128, 3, 1.0),      # 258 row tiles: four-wave workgroups
     (1, 64, 64, 300, 128, 3, 2.0),      # 576: eight
+    (1, 32, 2, 260, 36, 3, 1.0),        # backward of 18 key tiles: streamed rows split (f32_step.hip)
+    (4, 16, 4, 300, 36, 3, 1.0),        # 144: this one's
 ]
 
 
