@@ -38,6 +38,7 @@ FAMILIES = {
     "bwd": ("bwd ring step (bwd_dq_mfma_kernel + bwd_dkdv_mfma_kernel)",
             ("bwd_dq_mfma_kernel", "bwd_dkdv_mfma_kernel")),
 }
+F32_FAMILIES = {"fwd": "fwd ring step (fwd_f32_kernel)", "bwd": "bwd ring step (bwd_f32_kernel)"}
 
 
 def measured_traffic(workload):
@@ -360,7 +361,7 @@ def main():
     def roof(rows, family, alg_bytes):
         name, kernels = FAMILIES[family]
         if f32:
-            name = name.replace("_mfma_kernel", "_f32_kernel")
+            name = F32_FAMILIES[family]
         live = [r for r in rows if r["ms"] > 0]
         tot_ms = sum(r["ms"] for r in live)
         ach = sum(r["tflops"] * r["ms"] for r in live) / max(1e-9, tot_ms)

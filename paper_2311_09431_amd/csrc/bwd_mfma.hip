@@ -753,7 +753,7 @@ bwd_dkdv_mfma_kernel(StepArgs p, int n_tiles) {
     bwd_dkdv<WALK, RAGGED, DP, PART>(p, n_tiles, (int)blockIdx.x, lds0, lds1, lds2, lds3, stat);
 }
 // Both kinds of workgroups in one launch, the two sequences of n_dkdv and n_dq evenly interleaved
-// (each heaviest first): where the key-owning ones do not fill the chip, or fill it once and last
+// (each heaviest first; above 512 of a kind by groups of heads, see decode_block): where the key-owning ones do not fill the chip, or fill it once and last
 // as long as the heaviest, the query-owning ones run beside and behind them instead of after.
 // One workgroup per compute unit (the key-owning side's registers).
 template <bool RAGGED, int DP, bool PART>

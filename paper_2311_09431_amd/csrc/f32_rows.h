@@ -31,6 +31,15 @@ __device__ inline float ld1(const __hip_bfloat16* p) {
     return __uint_as_float((uint32_t)(*reinterpret_cast<const uint16_t*>(p)) << 16);
 }
 
+// What f32_step.hip, f32x3_step.hip and split_mfma.hip share beside that.
+
+// streamed row (within a 32-row sub-tile) of register r of a 32 x 32 score tile, h = lane / 32
+__device__ inline int reg_row(int r, int h) { return 8 * (r / 4) + 4 * h + r % 4; }
+// Workgroup -> (tile rank, head): ranks heaviest first over all heads.
+__device__ inline void decode(int linear, int n_heads, int& rank, int& head) {
+    rank = linear / n_heads;
+    head = linear - rank * n_heads;
+}
 // one past the last key shard that device dev's queries see
 __device__ inline int last_shard(const StepArgs& p, int dev) {
     return p.layout == SA_STRIPED ? p.kv_dev + p.n_kv : min(p.kv_dev + p.n_kv, dev + 1);

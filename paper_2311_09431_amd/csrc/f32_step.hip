@@ -5,13 +5,12 @@
 // on the way into LDS, so their probabilities are not rounded either).  Fuller fp32 launches go to
 // f32x3_step.hip, most short bf16 blocks to split_mfma.hip.
 //
-// Measured against kernels with one wavefront per row and serial dot products on the vector ALU
-// (which they replace): whole ring forward + backward of 16 heads, d = 128, 4 x 2048 tokens, fp32
-// 575 -> 24.1 ms (1.7 -> 40 useful TFLOP/s); 4 x 64 tokens, one head 2.68 -> 0.53 ms.
-// A launch holds all blocks of the devices it plays and a workgroup walks the other side's shards
-// in turn, and the backward's two kinds of workgroups share a launch: 24.1 -> 12.1 ms (a block of
-// 2048 tokens and 16 heads is one 128-row workgroup per compute unit, and lasts as long as the
-// heaviest) and 0.53 -> 0.098 ms; step by step, 8 x 96 tokens, 32 heads, bf16 0.34 -> 0.26 ms.
+// Measured against kernels with one wavefront per row and serial dot products on the vector ALU:
+// whole ring forward + backward, 4 x 64 tokens, one head, fp32, 2.68 -> 0.097 ms (0.53 with one launch
+// per block and kernel; a launch now holds all blocks of the devices it plays, a workgroup walks the
+// other side's shards in turn, and the backward's two kinds of workgroups share a launch); a
+// full forward block of 2048 rows, 8 key/value heads for 32, d 128, 14.6 ms, backward 63, where the
+// split form here takes 2.7 backward.
 //
 // What bounds them: the fp32 matrix cores run at 1/16 of the bf16 rate (64 cycles per
 // instruction, 157 TFLOP/s on the chip), so one instruction leaves room for everything that
@@ -58,8 +57,6 @@ __device__ inline f32x16 zero16() {
     for (int r = 0; r < 16; ++r) z[r] = 0.f;
     return z;
 }
-// streamed row (within a 32-row sub-tile) of score register r
-__device__ inline int reg_row(int r, int h) { return 8 * (r / 4) + 4 * h + r % 4; }
 
 // rows first .. first + ROWS - 1 of a [rows, d] matrix into an LDS tile, zeros beyond row c and
 // column d
@@ -120,11 +117,6 @@ __device__ inline void accumulate(f32x16 (&acc)[NB], const float* rows, const f3
 __device__ inline float half_max(float x) { return fmaxf(x, __shfl_xor(x, 32)); }
 __device__ inline float half_sum(float x) { return x + __shfl_xor(x, 32); }
 
-// Workgroup -> (tile rank, head): ranks heaviest first over all heads.
-__device__ inline void decode(int linear, int n_heads, int& rank, int& head) {
-    rank = linear / n_heads;
-    head = linear - rank * n_heads;
-}
 
 // Partial accumulators of the SPLIT wavefronts that own the same rows, summed through LDS
 // (wavefront kw keeps column blocks kw, kw + SPLIT, ... of the sum in acc).  buf holds

@@ -42,8 +42,6 @@ __device__ inline f32x16 zero16() {
     for (int r = 0; r < 16; ++r) z[r] = 0.f;
     return z;
 }
-// streamed row (within a tile) of score register r
-__device__ inline int reg_row(int r, int h) { return 8 * (r / 4) + 4 * h + r % 4; }
 
 // 8 consecutive floats of a row from column col on, zeros from column d on (d a multiple of 4)
 struct Chunk { float4 a, b; };
@@ -162,11 +160,6 @@ __device__ inline void accumulate(f32x16 (&acc)[NB], const char* planes, const f
     }
 }
 
-// Workgroup -> (tile rank, head): ranks heaviest first over all heads.
-__device__ inline void decode(int linear, int n_heads, int& rank, int& head) {
-    rank = linear / n_heads;
-    head = linear - rank * n_heads;
-}
 // The walk of a query-owning workgroup over the 32-key tiles of its shards, q0 its first query:
 // body(k, v, key0, full, off) on one tile.
 template <int DP, int WAVES, typename Body>

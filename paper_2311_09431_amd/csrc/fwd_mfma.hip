@@ -39,7 +39,8 @@
 // taken over the fp32 probabilities before they are rounded to bf16 (summing the
 // rounded values costs 1e-3 of LSE accuracy on rows with few keys).
 //
-// LDS layout.  Both tiles are 64 rows x 256 bytes without padding (the direct
+// LDS layout (above 64 columns; up to 64 two rows share a line, as mfma_tiles.h describes).  Both tiles
+// are 64 rows x 256 bytes without padding (the direct
 // loads write 1 KiB per wavefront contiguously); bank conflicts are avoided by
 // XOR-swizzling the 16-byte chunk index with the row: K chunk c of row r sits at
 // chunk c ^ (r & 15) (16-byte A-operand reads of 16 consecutive rows hit 16

@@ -25,8 +25,8 @@ constexpr int TD = 128;          // tile columns: head dimensions up to 128 are 
 constexpr int TR = 64;           // tile rows streamed per iteration
 
 // DP, the number of columns a kernel instantiation computes: 64, 112, 128 or 256.  Tiles are
-// always 128 columns wide (two of them, "halves", for 256); a smaller DP only leaves out work:
-// a contraction over the head dimension takes ksteps_of(DP) steps of 16 columns per half, a
+// 128 columns wide (two of them, "halves", for 256), 64 for DP = 64; otherwise a smaller DP only leaves
+// out work: a contraction over the head dimension takes ksteps_of(DP) steps of 16 columns per half, a
 // product whose output has head-dimension columns blocks_of(DP) blocks of 32 per half.
 // 112 (head dimensions 65..112, e.g. the 100 of the paper's 3B model, Table 1) drops the last
 // k-step and keeps all four output blocks.
@@ -39,7 +39,7 @@ constexpr float LN2 = 0.6931471805599453f;
 // ---------------------------------------------------------------------------
 // Swizzled tiles filled by direct global -> LDS loads.
 //
-// A tile is 64 rows x 256 bytes (128 bf16) with NO padding: a direct load
+// A tile is 64 rows x 256 bytes (128 bf16; up to 64 columns see below) with NO padding: a direct load
 // writes the 64 lanes' 16-byte pieces contiguously (1 KiB per wavefront
 // instruction, 4 rows), so a 16 KiB tile takes 16 instructions, 4 per
 // wavefront.  Bank conflicts are avoided by storing the 16-byte chunk c of row

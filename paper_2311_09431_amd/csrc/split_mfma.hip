@@ -60,8 +60,6 @@ __device__ inline f32x16 zero16() {
     for (int r = 0; r < 16; ++r) z[r] = 0.f;
     return z;
 }
-// streamed row (within a 32-row sub-tile) of score register r
-__device__ inline int reg_row(int r, int h) { return 8 * (r / 4) + 4 * h + r % 4; }
 
 // 32 x 32 scores: rows = the sub-tile at `rows`, columns = the owned rows
 template <int DP, bool PART>
@@ -215,11 +213,6 @@ __device__ inline void walk_keys(const StepArgs& p, int dev, int q0, dt_rsrc K, 
     }
 }
 
-// Workgroup -> (32-row tile rank, head), ranks heaviest first over all heads
-__device__ inline void decode(int linear, int n_heads, int& rank, int& head) {
-    rank = linear / n_heads;
-    head = linear - rank * n_heads;
-}
 
 // ------------------------------------------------------------------ forward
 template <int DP, bool PART>
