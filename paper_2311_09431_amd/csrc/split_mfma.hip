@@ -586,15 +586,15 @@ hipError_t run(const StepArgs& a, Pass pass, hipStream_t st) {
 
 }  // namespace
 
-// (of shapes that the 128-row matrix-core kernels take.)  Measured against both kinds of 128-row
-// workgroups in one launch, us per backward step, d 128: triangular 2048 x 2048, 2 heads (32
-// 128-row tiles) 38 / 60, 4 heads 46 / 62, 6 heads 71 / 65; 8192 x 8192, one head 131 / 193, two
-// 254 / 207.  Full blocks have twice the work: 2 heads 40 / 61, 4 heads 71 / 65.  Few key/value
-// heads, 32 query heads on one, 8192 x 8192 triangular: 4464 / 6131.
+// (of shapes that the 128-row matrix-core kernels take.)  Measured against those, us per backward step,
+// here / there.  Triangular, d 128, 64 key tiles: 16 heads of 512 rows 25.5 / 27.7, 64 heads on 8 of 1024
+// 188 / 212, 32 on 4 of 2048 308 / 396, on 2 of 4096 1138 / 1514, on one of 8192 4555 / 6093; 128 key tiles:
+// 54.3 / 41.6, 32 on 8 of 2048 293 / 214, on 4 of 4096 1048 / 796, on 2 of 8192 4065 / 3174.  Full blocks have
+// twice the work, 32 key tiles: 2 heads of 2048 rows 40 / 61, 32 on 8 of 512 66.0 / 64.7, on 4 of 1024 210 /
+// 238, on 2 of 2048 823 / 865, on one of 4096 3292 / 3376; 64: 16 heads of 512 30.3 / 27.5, 32 on 8 of 1024
+// 178 / 142, on one of 8192 10543 / 7427.  d 64 alike (32 on 4, full, 32 key tiles 129 / 216, 64 335 / 378).
 bool bwd_split_wanted(const StepArgs& a) {
-    const int64_t tiles = (int64_t)((a.c + 127) / 128) * a.B;
-    const int64_t keys = tiles * a.n_kv * a.H_kv, queries = tiles * a.n_q * a.H;
-    return a.d <= TD && (uneven(a) ? keys <= 64 : keys + queries <= 64);
+    return a.d <= TD && (int64_t)((a.c + 127) / 128) * a.B * a.n_kv * a.H_kv <= (uneven(a) ? 64 : 32);
 }
 hipError_t launch_bwd_split(const StepArgs& a, hipStream_t st) { return run(a, BWD, st); }
 

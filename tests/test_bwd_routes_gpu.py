@@ -20,7 +20,9 @@ CASES = [
     (2, 2, 1, 384, 112),        # 6, grouped heads
     (1, 16, 16, 512, 36),       # 64: last split for uneven work, not for full blocks
     (1, 13, 13, 640, 128),      # 65
-    (1, 32, 4, 256, 128),       # 8 keys, 64 queries: full blocks beyond the split
+    (1, 32, 4, 256, 128),       # 8, 32 query heads
+    (1, 8, 8, 512, 100),        # 32: last split for full blocks
+    (1, 9, 9, 500, 100),        # 36
     (1, 64, 64, 512, 64),       # 256: last one launch for uneven work, not for full blocks
     (1, 43, 43, 768, 128),      # 258: one launch each
     (1, 24, 24, 520, 256),      # two key-owning workgroups per tile: 240 of 512
