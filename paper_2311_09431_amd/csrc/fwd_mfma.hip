@@ -66,7 +66,6 @@ constexpr int TILE_BYTES = TILE_ROWS * D * 2;   // 16 KiB
 constexpr float RESCALE_SUM = 16777216.f;      // 2^24: a row's partial sum of probabilities beyond which its
                                                 // reference is moved up to the row maximum
 
-constexpr int REBASE_ROWS = 1024;               // see rebase
 typedef __attribute__((address_space(3))) char lds_char;
 typedef lds_s16x4_t lds_s16x4;
 
@@ -355,13 +354,14 @@ fwd_mfma_kernel(StepArgs p, int n_qtiles) {
         }
     }
 
-    // A striped ring's rows meet few keys in each shard.  Where the walk keeps one reference over all of
-    // them, one probability per row is 1 and rounds to bf16 without an error; a step by itself has one such
-    // per shard, and the first rows, which carry most of O's norm, feel it.  So their references are set
-    // anew at each shard: 8 x 256 tokens, d 64, error of O against 64 bits 1.53e-3 -> 1.01e-3, 8 x 4096,
-    // d 128, 1.51e-3 -> 1.24e-3, step by step 1.01e-3 and 1.24e-3.  Beyond 1024 keys in a shard it gains
-    // less than 0.5 %.
-    const bool rebase = RING && p.layout == SA_STRIPED && q0 < REBASE_ROWS;
+    // Where the walk of a striped ring keeps one reference over all shards, one probability per row is 1
+    // and rounds to bf16 without an error; a step by itself has one such per shard, and the first rows,
+    // which meet few keys in each and carry most of O's norm, feel it.  So the references are set anew at
+    // each shard: error of O against 64 bits, 8 x 256 tokens, d 64, 1.53e-3 -> 1.01e-3, 8 x 4096, d 128,
+    // 1.51e-3 -> 1.24e-3, as step by step.  A shard of the walk costs about 0.3 us more (ring of 4 x 128, 2
+    // heads 16.2 -> 17.1 us, of 8 x 4096, 16 heads 3.93 -> 3.96 ms); limited to tiles below 1024 rows it would
+    // cost 0.2 to 2 % less there and leave 0.1 % of the error.
+    const bool rebase = RING && p.layout == SA_STRIPED;
     uint32_t g2[4];             // up to 64 columns: the two pieces of either tile
     if constexpr (DP <= 64) dt_load_offsets<DP>(g2, lane, wave, pitch, d);
     auto load_k = [&](dt_rsrc K, int tile_byte_offset, char* buf) {
