@@ -109,10 +109,11 @@ size_t elt_size(int dtype) { return dtype == SA_F32 ? 4 : 2; }
 
 // HIP takes fewer than 2^32 threads a launch.  The kernels' grids are one-dimensional; at worst they
 // hold one workgroup of 256 threads per 32 rows of each side (as many at d > 128, where a key-owning
-// workgroup has 64 rows and half of the columns).
+// workgroup has 64 rows and half of the columns; the forward workgroups of 512 threads, on blocks of fewer
+// than 128 rows or launches of a few workgroups, count as two).
 constexpr int64_t kMostWorkgroups = (int64_t(1) << 24) - 1;
 int64_t workgroups_per_kv_head(const StepArgs& a) {
-    return ((int64_t)a.c / 32 + 2) * ((int64_t)a.n_q * (a.H / a.H_kv) + a.n_kv);
+    return ((int64_t)a.c / 32 + 2) * ((int64_t)a.n_q * (a.H / a.H_kv) * (a.c < 128 ? 2 : 1) + a.n_kv);
 }
 // Blocks of a launch that may hold more are played in parts of whole key/value heads and their groups.
 template <typename Launch>
@@ -146,7 +147,8 @@ hipError_t in_parts(const StepArgs& a, int dtype, Launch launch) {
 
 hipError_t launch_fwd(const StepArgs& all, int dtype, hipStream_t st) {
     return in_parts(all, dtype, [&](const StepArgs& a) {
-        return sa::fwd_mfma_supported(a, dtype) ? sa::launch_fwd_mfma(a, st) : sa::launch_fwd_f32(a, dtype, st);
+        if (!sa::fwd_mfma_supported(a, dtype)) return sa::launch_fwd_f32(a, dtype, st);
+        return sa::fwd_split_wanted(a) ? sa::launch_fwd_split(a, st) : sa::launch_fwd_mfma(a, st);
     });
 }
 hipError_t launch_bwd(const StepArgs& all, int dtype, hipStream_t st) {

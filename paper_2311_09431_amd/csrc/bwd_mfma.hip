@@ -315,37 +315,6 @@ __device__ __forceinline__ void bwd_dq(const StepArgs& p, int n_tiles, int linea
 }
 
 // ------------------------------------------------------------- dK/dV kernel
-// MFMA whose accumulator is pinned to ordinary VGPRs.  The dK/dV kernel needs more than 256
-// registers, and once a kernel uses AGPRs the compiler places EVERY MFMA result there; the
-// S / dP tiles are consumed by VALU instructions, so they would be copied back register by
-// register.
-//
-// Issued from inline assembly, these MFMAs are invisible to the compiler's hazard recogniser,
-// so the one software-managed hazard they have is kept by hand.  ISA guide, "Manually inserted
-// wait states (NOPs)": XDL (matrix core) write of a VGPR followed by a VALU read or write of
-// it needs passes + 3 wait states: 11 for this 8-pass instruction (19 for a 16-pass one).
-//  * In the loops the distance is structural: the last S / dP MFMA of a pipeline step is
-//    followed by that step's dV / dK products, 4 * MB >= 8 further MFMAs of 8 passes each
-//    (>= 256 cycles of the same in-order pipeline), before the next step's first VALU read.
-//  * In the prologue nothing lies between: mfma_results_to_valu() inserts 32 wait states and
-//    ties the two tiles to the asm statement, so no read of them can be scheduled before it.
-__device__ inline void mfma_results_to_valu(f32x16& a, f32x16& b) {
-    asm volatile("s_nop 15\n\ts_nop 15" : "+v"(a), "+v"(b));
-}
-// The other software-managed hazard is on the input side: a VALU write of a VGPR followed by
-// an MFMA read of it needs 2 wait states (same table).  The operands normally come straight
-// from LDS reads (ordered by s_waitcnt, no hazard); only the PART instantiations pass some of them
-// through VALU selects first (zero_beyond_d), and then after_valu (known when compiled) puts the
-// wait in front of the instruction.
-__device__ __forceinline__ void mfma_vgpr_first(f32x16& acc, bf16x8 a, bf16x8 b, bool after_valu) {
-    if (after_valu) asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(acc) : "v"(a), "v"(b));
-    else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(acc) : "v"(a), "v"(b));
-}
-__device__ __forceinline__ void mfma_vgpr_acc(f32x16& acc, bf16x8 a, bf16x8 b, bool after_valu) {
-    if (after_valu) asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));
-    else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));
-}
-
 // S / dP product of the dK/dV kernel.  DP <= 128: the asm forms above (results stay in VGPRs).
 // DP = 256: the compiler's own MFMA; K and V alone are 128 registers there, the asm forms would
 // pin them and the score tiles to VGPRs and spill a hundred registers, while the compiler keeps

@@ -218,29 +218,6 @@ __device__ __forceinline__ void step(f32x16& s_cur, f32x16& s_next, bf16x8 (&p_c
     }
 }
 
-// Rotary embedding of a query row held as B-operand fragments (Sec. 2.3: a token keeps the
-// position id of its original place, whatever device it sits on).  Rotate-half pairing: column
-// i < d/2 with column i + d/2; with d == DP both sit in the same lane, KS/2 fragments apart.
-// turns[i] = base^(-2i/d) / (2 pi) in double precision (LDS, filled once per workgroup); the
-// angle in revolutions is reduced to [-1/2, 1/2] in double (position ids reach 10^6, where an
-// fp32 angle is off by 0.05 rad) and only then handed to the fp32 sine / cosine instructions,
-// which take revolutions.
-template <int DP>
-__device__ inline void rope_rotate(bf16x8 (&f)[8 * halves_of(DP)], const double* turns, int pos, int h) {
-    constexpr int KS = DP / 16;
-#pragma unroll
-    for (int ks = 0; ks < KS / 2; ++ks)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const double t = (double)pos * turns[16 * ks + 8 * h + e];
-            const float r = (float)(t - rint(t));
-            const float sn = __builtin_amdgcn_sinf(r), cs = __builtin_amdgcn_cosf(r);
-            const float lo = (float)f[ks][e], hi = (float)f[ks + KS / 2][e];
-            f[ks][e] = (__bf16)fmaf(lo, cs, -hi * sn);
-            f[ks + KS / 2][e] = (__bf16)fmaf(hi, cs, lo * sn);
-        }
-}
-
 // One code path serves every block: it is walked up to the last key tile that holds an
 // allowed pair, and the last BM / 64 tiles of the walk carry the element mask.  For a
 // triangular block the mask limit is the query's own position; for a full block (contiguous
@@ -386,7 +363,7 @@ fwd_mfma_kernel(StepArgs p, int n_qtiles) {
     int q_position = 0;
     if (ROPE) {
         q_position = p.q_pos[b * p.pos_stride_b + a];
-        if (tid < DP / 2) rope_turns[tid] = exp2(-2.0 * tid / DP * p.rope_log2_base) * 0.15915494309189535;
+        fill_rope_turns<DP>(rope_turns, tid, p.rope_log2_base);
     }
     const float kappa = p.scale * LOG2E;
     // This block's own partial result is accumulated from an empty state and folded into the

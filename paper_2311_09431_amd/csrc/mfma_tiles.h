@@ -167,6 +167,14 @@ __device__ inline void dt_load_piece(dt_rsrc matrix, int tile_byte_offset, uint3
                  : "s"(dst), "v"(lane_offset), "s"(matrix), "s"(tile_byte_offset)
                  : "memory", "m0");
 }
+// 64 lanes x 4 bytes, to lds_dst + 4 * lane
+__device__ inline void dt_load_dword(dt_rsrc matrix, int byte_offset, uint32_t lane_offset, const char* lds_dst) {
+    const uint32_t dst = (uint32_t)reinterpret_cast<uintptr_t>((const lds_char_t*)lds_dst);
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, %3 offen lds"
+                 :
+                 : "s"(dst), "v"(lane_offset), "s"(matrix), "s"(byte_offset)
+                 : "memory", "m0");
+}
 #pragma clang diagnostic pop
 // wave must be wave-uniform (scalar): it selects the LDS destination of each load
 template <int DP>
@@ -216,6 +224,39 @@ __device__ inline f32x16 mfma(bf16x8 a, bf16x8 b, f32x16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
+// MFMA whose accumulator is pinned to ordinary VGPRs.  The dK/dV kernel needs more than 256
+// registers, and once a kernel uses AGPRs the compiler places EVERY MFMA result there; the
+// S / dP tiles are consumed by VALU instructions, so they would be copied back register by
+// register.
+//
+// Issued from inline assembly, these MFMAs are invisible to the compiler's hazard recogniser,
+// so the one software-managed hazard they have is kept by hand.  ISA guide, "Manually inserted
+// wait states (NOPs)": XDL (matrix core) write of a VGPR followed by a VALU read or write of
+// it needs passes + 3 wait states: 11 for this 8-pass instruction (19 for a 16-pass one).
+//  * In the loops the distance is structural: the last S / dP MFMA of a pipeline step is
+//    followed by that step's dV / dK products, 4 * MB >= 8 further MFMAs of 8 passes each
+//    (>= 256 cycles of the same in-order pipeline), before the next step's first VALU read.
+//  * In the prologue nothing lies between: mfma_results_to_valu() inserts 32 wait states and
+//    ties the two tiles to the asm statement, so no read of them can be scheduled before it.
+__device__ inline void mfma_results_to_valu(f32x16& a) { asm volatile("s_nop 15" : "+v"(a)); }
+__device__ inline void mfma_results_to_valu(f32x16& a, f32x16& b) {
+    asm volatile("s_nop 15\n\ts_nop 15" : "+v"(a), "+v"(b));
+}
+// The other software-managed hazard is on the input side: a VALU write of a VGPR followed by
+// an MFMA read of it needs 2 wait states (same table).  The operands normally come straight
+// from LDS reads (ordered by s_waitcnt, no hazard); only the PART instantiations pass some of them
+// through VALU selects first (zero_beyond_d), and then after_valu (known when compiled) puts the
+// wait in front of the instruction.
+__device__ __forceinline__ void mfma_vgpr_first(f32x16& acc, bf16x8 a, bf16x8 b, bool after_valu) {
+    if (after_valu) asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(acc) : "v"(a), "v"(b));
+    else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(acc) : "v"(a), "v"(b));
+}
+__device__ __forceinline__ void mfma_vgpr_acc(f32x16& acc, bf16x8 a, bf16x8 b, bool after_valu) {
+    if (after_valu) asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));
+    else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));
+}
+
+
 // Workgroup order of a 1-D grid over (tile rank, batch*head), rank 0 = heaviest tile.
 // Large grids: heads are taken in groups of 8; inside a group the index runs over
 // heads fastest and tile ranks slowest, so (i) every group runs heaviest-first and
@@ -263,6 +304,33 @@ __device__ inline void load_b_frags(bf16x8 (&f)[NF], const __bf16* __restrict__ 
             f[ks] = __builtin_shufflevector(lo, z, 0, 1, 2, 3, 4, 5, 6, 7);
         }
     }
+}
+
+// Rotary embedding of a query row held as B-operand fragments (Sec. 2.3: a token keeps the
+// position id of its original place, whatever device it sits on).  Rotate-half pairing: column
+// i < d/2 with column i + d/2; with d == DP both sit in the same lane, KS/2 fragments apart.
+// turns[i] = base^(-2i/d) / (2 pi) in double precision (LDS, filled once per workgroup); the
+// angle in revolutions is reduced to [-1/2, 1/2] in double (position ids reach 10^6, where an
+// fp32 angle is off by 0.05 rad) and only then handed to the fp32 sine / cosine instructions,
+// which take revolutions.
+template <int DP>
+__device__ inline void rope_rotate(bf16x8 (&f)[8 * halves_of(DP)], const double* turns, int pos, int h) {
+    constexpr int KS = DP / 16;
+#pragma unroll
+    for (int ks = 0; ks < KS / 2; ++ks)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const double t = (double)pos * turns[16 * ks + 8 * h + e];
+            const float r = (float)(t - rint(t));
+            const float sn = __builtin_amdgcn_sinf(r), cs = __builtin_amdgcn_cosf(r);
+            const float lo = (float)f[ks][e], hi = (float)f[ks + KS / 2][e];
+            f[ks][e] = (__bf16)fmaf(lo, cs, -hi * sn);
+            f[ks + KS / 2][e] = (__bf16)fmaf(hi, cs, lo * sn);
+        }
+}
+template <int DP>
+__device__ inline void fill_rope_turns(double* turns, int tid, double log2_base) {
+    if (tid < DP / 2) turns[tid] = exp2(-2.0 * tid / DP * log2_base) * 0.15915494309189535;
 }
 
 }  // namespace sa

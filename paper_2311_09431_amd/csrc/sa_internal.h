@@ -125,9 +125,11 @@ bool bwd_mfma_supported(const StepArgs& a, int dtype);
 hipError_t launch_bwd_mfma(const StepArgs& a, hipStream_t st);
 bool bwd_split_wanted(const StepArgs& a);
 hipError_t launch_bwd_split(const StepArgs& a, hipStream_t st);
+bool fwd_split_wanted(const StepArgs& a);
+hipError_t launch_fwd_split(const StepArgs& a, hipStream_t st);
 bool few_rows_wanted(const StepArgs& a, int dtype, bool backward);
 hipError_t launch_few_rows(const StepArgs& a, int dtype, bool backward, hipStream_t st);
-bool short_exact_wanted(const StepArgs& a, int dtype, bool backward);
+bool short_exact_wanted(const StepArgs& a, int dtype);
 hipError_t launch_short_exact(const StepArgs& a, bool backward, hipStream_t st);
 
 }  // namespace sa

@@ -1,23 +1,25 @@
-// Backward ring step for launches that leave most of the chip idle with 128-row workgroups (bf16
-// matrix cores, head dimension up to 128, blocks of at least 128 rows): same operands, same
-// products and same precision as bwd_mfma.hip, other split of the work.
+// Ring step for launches that leave most of the chip idle with 128-row workgroups (bf16 matrix cores,
+// head dimension up to 128): same operands and products as fwd_mfma.hip and bwd_mfma.hip, other split
+// of the work.
 //
-// What bounds such a launch is the walk of one workgroup: about 1.4 us (dQ) or 1.7 us (dK/dV) per
-// 64 streamed rows, however few workgroups there are.  Here a workgroup owns 32 rows and its four
-// wavefronts take the 32-row sub-tiles of each 128-row group of the streamed side, one each; the
-// partial results meet in LDS at the end.  Four times the workgroups and a walk of about 2 us per
-// 128 rows; groups are double buffered, one barrier per group.  Nothing is interleaved by hand and
-// a tile load feeds a quarter of the products, so a fuller chip is better served by the other
-// kernels (figures at bwd_split_wanted).  Whole ring, 4 x 1024 tokens, 2 heads, forward +
-// backward: 272 -> 162 us.  A forward kernel of this form was no faster than the 128-row one
-// (37 us both for 2048 x 2048, 2 heads).
+// What bounds such a launch is the walk of one workgroup.  Here a workgroup owns 32 rows and its
+// wavefronts (8 forward, 4 backward) take every eighth (fourth) 32-row sub-tile of the streamed side; the
+// partial results meet in LDS at the end.  That is four times the workgroups, and a fraction of the walk.
+//
+// A wavefront streams its sub-tiles by itself: stages of LDS that nobody else touches, filled by
+// direct global -> LDS loads and ordered by its own vmcnt, no barrier before the end.  A sub-tile is read
+// into registers as soon as it has landed and its stage requested anew, so that about 100 KiB are in
+// flight on a compute unit all the time (64 KiB per 0.43 us with nothing but the loads, what its path to
+// the L2 carries).  What is left is the number of instructions: with one wavefront per SIMD each takes
+// its four cycles.
 //
 // Blocks shorter than one tile keep the precision of the fp32 kernels, which take them otherwise:
 // EXACT.  Products of bf16 operands are exact in fp32 anyway; probabilities and dS go into theirs as
 // three bf16 terms, and the exponents are formed with fp32's own rounding.
 //
-// The wavefront that takes a sub-tile is given by the sub-tile's place in its shard, so summation
-// orders are fixed and the same under emulated coarse skipping.
+// The wavefront that takes a sub-tile is given by the sub-tile's place in the walk without emulated
+// coarse skipping, so summation orders are fixed and the same under it.
+
 #include "f32_rows.h"
 #include "f32_terms.h"
 #include "mfma_tiles.h"
@@ -27,9 +29,24 @@ namespace sa {
 
 namespace {
 
-constexpr int WAVES = 4, OWN = 32, GROUP = 32 * WAVES;
+constexpr int FWD_WAVES = 8, BWD_WAVES = 4, OWN = 32;
 template <int DP> constexpr int SUB_BYTES = tile_bytes(DP) / 2;              // 32 rows
-template <int DP> constexpr int GROUP_BYTES = 2 * tile_bytes(DP);            // one operand's 128 rows
+template <int DP> constexpr int PIECES = SUB_BYTES<DP> / 1024;               // loads of 1 KiB they take
+template <int DP> constexpr int STAGE_BYTES = 2 * SUB_BYTES<DP>;             // of both streamed operands
+constexpr int STAT_BYTES = 512;                                              // 32 LSE, 32 delta, a load of 256 bytes each
+
+// byte offset (global side) that this lane fetches of piece j of 32 rows
+template <int DP>
+__device__ inline uint32_t piece_offset(int j, int lane, int pitch, int d) {
+    const int lr = lane >> 4, pc = lane & 15;
+    int r = 4 * j + lr, chunk = pc ^ dt_swz(r);
+    if (DP <= 64) {
+        const int s = 4 * j + lr, x = pc ^ (((s & 1) << 2) | ((s >> 1) & 3));
+        r = 2 * s + (x >> 3);
+        chunk = x & 7;
+    }
+    return 8 * chunk < d ? r * pitch + (chunk << 4) : DT_OUT_OF_RANGE;
+}
 
 // what every kernel of this file keeps per lane
 template <int DP>
@@ -46,13 +63,91 @@ struct Lane {
     }
 };
 
-// 128 rows starting at row first of c, as two 64-row tiles (rows beyond the matrix arrive as zeros; a
-// second tile beyond it is not read by anyone)
-template <int DP>
-__device__ inline void load_group(dt_rsrc m, int first, int c, int pitch, char* lds, const uint32_t (&gl)[4], int wave) {
-    dt_load<DP>(m, first * pitch, lds, gl, wave);
-    if (first + DT_ROWS < c) dt_load<DP>(m, (first + DT_ROWS) * pitch, lds + tile_bytes(DP), gl, wave);
+// 32 rows of a matrix from row `first` on, this wavefront's share of the pieces (rows beyond the
+// matrix arrive as zeros)
+template <int DP, int WAVES>
+__device__ inline void load_own(dt_rsrc m, int first, int pitch, int d, char* lds, const Lane<DP>& ln) {
+#pragma unroll
+    for (int j = 0; j < PIECES<DP>; j += WAVES)
+        if (PIECES<DP> % WAVES == 0 || j + ln.wave < PIECES<DP>)
+            dt_load_piece(m, first * pitch, piece_offset<DP>(j + ln.wave, ln.lane, pitch, d), lds + (j + ln.wave) * 1024);
 }
+// their B operands
+template <int DP, bool PART>
+__device__ inline void read_own(bf16x8 (&f)[8], const char* rows, const Lane<DP>& ln, int part_ks) {
+#pragma unroll
+    for (int ks = 0; ks < ksteps_of(DP); ++ks) {
+        const bf16x8 x = dt_read_row(rows, ln.arow[ks]);
+        f[ks] = PART ? zero_beyond_d(x, ks == part_ks) : x;
+    }
+}
+// 32 statistics from row `first` on
+__device__ inline void load_stat(dt_rsrc m, int first, char* lds, int lane) {
+    dt_load_dword(m, 4 * first, lane < 32 ? 4 * lane : DT_OUT_OF_RANGE, lds);
+}
+
+// The loads of a streamed sub-tile.  An instruction's immediate offset counts on both sides, so that the pieces
+// of 16 rows share one setting of m0: the lane's offset of piece j is 1024 j less, and to keep it from
+// getting negative the descriptor starts 4096 bytes ahead of the matrix.  (Each with an m0 of its own,
+// the 16 loads of a sub-tile were 64 instructions.)
+constexpr int AHEAD_BYTES = 4096;
+__device__ inline dt_rsrc stream_rsrc(const void* matrix, int rows, int pitch, int d) {
+    dt_rsrc r = dt_make_rsrc((const char*)matrix - AHEAD_BYTES, rows, pitch, d);
+    r[2] += AHEAD_BYTES;
+    return r;
+}
+template <int DP>
+struct Loader {
+    static constexpr int HALF = PIECES<DP> / 2;         // pieces of 16 rows
+    uint32_t at[HALF];
+    int pitch;
+    __device__ Loader(int pitch_, int d, int lane) : pitch(pitch_) {
+#pragma unroll
+        for (int j = 0; j < HALF; ++j) {
+            const uint32_t x = piece_offset<DP>(j, lane, pitch, d);
+            at[j] = x == DT_OUT_OF_RANGE ? x : x + AHEAD_BYTES - 1024 * j;
+        }
+    }
+    // 16 rows from row `row` on (the swizzle is the same for all such groups)
+    __device__ inline void rows16(dt_rsrc m, int row, const char* to) const {
+        const uint32_t dst = (uint32_t)reinterpret_cast<uintptr_t>((const lds_char_t*)to);
+        const int byte = row * pitch;
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+        if constexpr (HALF == 4)
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
+                         "buffer_load_dwordx4 %1, %5, %6 offen lds\n\t"
+                         "buffer_load_dwordx4 %2, %5, %6 offen offset:1024 lds\n\t"
+                         "buffer_load_dwordx4 %3, %5, %6 offen offset:2048 lds\n\t"
+                         "buffer_load_dwordx4 %4, %5, %6 offen offset:3072 lds"
+                         :
+                         : "s"(dst), "v"(at[0]), "v"(at[1]), "v"(at[2]), "v"(at[3]), "s"(m), "s"(byte)
+                         : "memory", "m0");
+        else
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
+                         "buffer_load_dwordx4 %1, %3, %4 offen lds\n\t"
+                         "buffer_load_dwordx4 %2, %3, %4 offen offset:1024 lds"
+                         :
+                         : "s"(dst), "v"(at[0]), "v"(at[1]), "s"(m), "s"(byte)
+                         : "memory", "m0");
+#pragma clang diagnostic pop
+    }
+    // both operands' 32 rows, in four parts
+    __device__ inline void part(int i, dt_rsrc a, dt_rsrc b, int row, const char* stage) const {
+        rows16(i / 2 ? b : a, row + 16 * (i % 2), stage + i * (SUB_BYTES<DP> / 2));
+    }
+    __device__ inline void all(dt_rsrc a, dt_rsrc b, int row, const char* stage) const {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) part(i, a, b, row, stage);
+    }
+};
+// at most the last n vector memory operations of this wavefront are still on their way
+template <int N>
+__device__ inline void wait_all_but() {
+    asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
+}
+// all LDS reads so far are in registers: what they read may be overwritten
+__device__ inline void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory"); }
 
 __device__ inline f32x16 zero16() {
     f32x16 z;
@@ -61,47 +156,46 @@ __device__ inline f32x16 zero16() {
     return z;
 }
 
-// 32 x 32 scores: rows = the sub-tile at `rows`, columns = the owned rows
-template <int DP, bool PART>
-__device__ inline f32x16 scores(const char* rows, const bf16x8 (&f)[8], const Lane<DP>& ln, int part_ks) {
-    f32x16 s = zero16();
+template <int DP>
+__device__ inline void read_rows(bf16x8 (&x)[8], const char* rows, const Lane<DP>& ln) {
 #pragma unroll
-    for (int ks = 0; ks < ksteps_of(DP); ++ks) {
-        const bf16x8 x = dt_read_row(rows, ln.arow[ks]);
-        s = mfma(PART ? zero_beyond_d(x, ks == part_ks) : x, f[ks], s);
-    }
-    return s;
+    for (int ks = 0; ks < ksteps_of(DP); ++ks) x[ks] = dt_read_row(rows, ln.arow[ks]);
 }
-// acc (32-column blocks x owned rows) += streamed^T w, w rounded to bf16 or (EXACT) as three terms,
-// smallest first
-template <int DP, bool EXACT>
-__device__ inline void accumulate(f32x16 (&acc)[4], const char* rows, const f32x16& w, const Lane<DP>& ln) {
-    constexpr int TERMS = EXACT ? 3 : 1;
-    bf16x8 b[2][3];
+// operand i of 2 blocks_of(DP): 32-column block i % blocks_of(DP) of 16 of the rows
+template <int DP>
+__device__ inline void read_transposed(bf16x8 (&x)[8], int i, const char* rows, const Lane<DP>& ln) {
+    const int g = i / blocks_of(DP), mb = i % blocks_of(DP);
+    x[4 * g + mb] = dt_read_tr(rows + g * 16 * row_bytes(DP), ln.tr0[mb], ln.tr1[mb]);
+}
+// One step of a score product whose result vector instructions read.  Its operands may have been fetched
+// from accumulation registers, which counts as a vector instruction; the wait states for that are
+// always there (the product before takes longer).
+template <bool PART, int DP>
+__device__ __forceinline__ bf16x8 row_operand(bf16x8 a, int ks, int part_ks) {
+    return PART && ks >= part_from(DP) ? zero_beyond_d(a, ks == part_ks) : a;
+}
+template <bool PART, int DP>
+__device__ __forceinline__ void score_product(f32x16& acc, bf16x8 a, bf16x8 b, int ks, int part_ks) {
+    const bf16x8 x = row_operand<PART, DP>(a, ks, part_ks);
+    if (ks == 0) mfma_vgpr_first(acc, x, b, true);
+    else mfma_vgpr_acc(acc, x, b, true);
+}
+// a weight tile as B operands, rounded to bf16 or (EXACT) as three terms
+template <bool EXACT>
+__device__ inline void as_operand(const f32x16& w, int g, bf16x8 (&b)[3]) {
+    if (EXACT) {
+        split_regs(w, 8 * g, b);
+    } else {
 #pragma unroll
-    for (int g = 0; g < 2; ++g) {
-        if (EXACT) {
-            split_regs(w, 8 * g, b[g]);
-        } else {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) b[g][0][e] = (__bf16)w[8 * g + e];
-        }
+        for (int e = 0; e < 8; ++e) b[0][e] = (__bf16)w[8 * g + e];
     }
-#pragma unroll
-    for (int g = 0; g < 2; ++g)
-#pragma unroll
-        for (int mb = 0; mb < blocks_of(DP); ++mb) {
-            const bf16x8 a = dt_read_tr(rows + g * 16 * row_bytes(DP), ln.tr0[mb], ln.tr1[mb]);
-#pragma unroll
-            for (int t = TERMS - 1; t >= 0; --t) acc[mb] = mfma(a, b[g][t], acc[mb]);
-        }
 }
 
-// bytes of the four wavefronts' accumulators
-template <int DP> constexpr int PARTIAL_BYTES = WAVES * blocks_of(DP) * 16 * 64 * 4;
+// bytes of the wavefronts' accumulators
+template <int DP, int WAVES> constexpr int PARTIAL_BYTES = WAVES * blocks_of(DP) * 16 * 64 * 4;
 
-// Sum of the four wavefronts' accumulators through LDS: each writes its own and takes a share of the
-// sum, pieces blocks wave .. of 8 columns (4 a lane), so that a row's columns stay together.
+// Sum of the wavefronts' accumulators through LDS: each writes its own and takes a share of the
+// sum, pieces of 8 columns (4 a lane), so that a row's columns stay together.
 template <int DP>
 __device__ inline void put_partial(char* buf, const f32x16 (&acc)[4], const Lane<DP>& ln) {
     float4* mine = reinterpret_cast<float4*>(buf) + ln.wave * blocks_of(DP) * 4 * 64;
@@ -112,9 +206,14 @@ __device__ inline void put_partial(char* buf, const f32x16 (&acc)[4], const Lane
             mine[(mb * 4 + g) * 64 + ln.lane] =
                 make_float4(acc[mb][4 * g], acc[mb][4 * g + 1], acc[mb][4 * g + 2], acc[mb][4 * g + 3]);
 }
-template <int DP>
-__device__ inline float4 take_sum(const char* buf, int piece, const Lane<DP>& ln) {
-    const float4* at = reinterpret_cast<const float4*>(buf) + piece * 64 + ln.lane;
+constexpr int share_of(int DP, int waves) { return blocks_of(DP) * 4 / waves; }        // pieces a wavefront takes
+template <int DP, int WAVES>
+__device__ inline int piece_of(int i, const Lane<DP>& ln) { return ln.wave * share_of(DP, WAVES) + i; }
+template <int DP, int WAVES>
+__device__ inline int column_of(int i, const Lane<DP>& ln) { return 8 * piece_of<DP, WAVES>(i, ln) + 4 * ln.h; }
+template <int DP, int WAVES>
+__device__ inline float4 take_sum(const char* buf, int i, const Lane<DP>& ln) {
+    const float4* at = reinterpret_cast<const float4*>(buf) + piece_of<DP, WAVES>(i, ln) * 64 + ln.lane;
     float4 x = at[0];
 #pragma unroll
     for (int w = 1; w < WAVES; ++w) {
@@ -123,12 +222,24 @@ __device__ inline float4 take_sum(const char* buf, int piece, const Lane<DP>& ln
     }
     return x;
 }
+// this wavefront's share of the lane's row as it stands (zeros if not wanted): on its way while the
+// partial results meet
+template <int DP, int WAVES>
+__device__ inline void load_old(float4 (&x)[share_of(DP, WAVES)], const float* row, int d, bool wanted, const Lane<DP>& ln) {
+#pragma unroll
+    for (int i = 0; i < share_of(DP, WAVES); ++i) {
+        const int col = column_of<DP, WAVES>(i, ln);
+        x[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (wanted && col < d) x[i] = *reinterpret_cast<const float4*>(row + col);
+    }
+}
 // EXACT: rows that are done over one by one (f32_rows.h): each wavefront puts its mask beside its
 // partial accumulators, and after the barrier takes every fourth of the rows that one of them names
 __device__ inline void put_odd(uint32_t* masks, bool odd, int wave, int lane) {
     const uint32_t rows = row_mask(odd);
     if (lane == 0) masks[wave] = rows;
 }
+template <int WAVES>
 __device__ inline uint32_t take_odd(const uint32_t* masks) {
     uint32_t rows = 0;
 #pragma unroll
@@ -145,84 +256,66 @@ __device__ inline void look_at(float (&z)[2], const f32x16& s) {
 __device__ inline bool odd_sum(const float (&z)[2], const f32x16 (&ds_sum)[4]) {
     return z[0] + z[1] != 0.f || not_finite<1>(ds_sum);
 }
-// piece i of this wavefront's share and its first column
-template <int DP>
-__device__ inline int piece_of(int i, const Lane<DP>& ln) { return ln.wave * blocks_of(DP) + i; }
-template <int DP>
-__device__ inline int column_of(int i, const Lane<DP>& ln) { return 8 * piece_of<DP>(i, ln) + 4 * ln.h; }
-
-// last key of a block that the workgroup of queries q0 .. q0 + 31 looks at: the last allowed one,
-// or under emulated coarse skipping the last one of the skip_bk-wide tile that shares an allowed
-// pair with its skip_bq-tall tile
-__device__ inline int last_key_of(const StepArgs& p, int q0, bool full, int off) {
-    if (full) return p.c - 1;
-    if (p.skip_bq > 0) {
-        const int q_hi = (q0 / p.skip_bq + 1) * p.skip_bq - 1;
-        return min(p.c, ((q_hi - off) / p.skip_bk + 1) * p.skip_bk) - 1;
-    }
-    return min(q0 + OWN, p.c) - 1 - off;
-}
-
-// The walk of a query-owning workgroup over the 128-key groups of its shards.  body(k, v, g0):
-// one group, its keys at LDS addresses k, v, the first one key g0 of the present block.
-struct Block { int kv; bool full; int off, last_key; };
-template <int DP, typename Body>
-__device__ inline void walk_keys(const StepArgs& p, int dev, int q0, dt_rsrc K, dt_rsrc V, char* lds, const Lane<DP>& ln,
-                                 Body body) {
-    const int pitch = 2 * (int)p.kv_stride_s, kv_end = last_shard(p, dev);
-    uint32_t gl[4];
-    dt_load_offsets<DP>(gl, ln.lane, ln.wave, pitch, p.d);
-    auto block = [&](int kv) {
-        Block b;
-        b.kv = kv;
-        b.full = block_kind(dev, kv, p.layout) == MASK_FULL;
-        b.off = block_off(dev, kv, p.layout);
-        b.last_key = last_key_of(p, q0, b.full, b.off);
-        return b;
-    };
-    Block now = block(p.kv_dev);
-    int g0 = 0, parity = 0;
-    load_group<DP>(K, 0, p.c, pitch, lds, gl, ln.wave);
-    load_group<DP>(V, 0, p.c, pitch, lds + GROUP_BYTES<DP>, gl, ln.wave);
-    for (;;) {
-        Block next = now;
-        int next_g0 = g0 + GROUP;
-        if (next_g0 > now.last_key) {
-            next_g0 = 0;
-            next.kv = now.kv + 1;
+// The sub-tiles of 32 keys that one wavefront of a query-owning workgroup takes: those of block kv whose
+// number v is `turn` modulo the number of wavefronts, turn being the wavefront's number less the sub-tiles of
+// the blocks before.
+// Sub-tiles of a block that hold work for queries q0 .. q0 + 31: all of a full block; of a triangular
+// one those up to the last allowed key, or under emulated coarse skipping up to the end of the
+// skip_bk-wide tile that shares an allowed pair with the queries' skip_bq-tall tile.
+struct KeyCursor {
+    int kv, kv_end;             // present block; at kv_end the walk is over
+    int v, n;                   // sub-tile, how many the block has
+    int shift;                  // query a sees the block's keys up to min(a + shift, c - 1)
+    int dev, layout, c, turn, n_full, n_off0, n_off1, n_fine;
+    __device__ KeyCursor(const StepArgs& p, int dev_, int q0, int wave)
+        : kv(p.kv_dev), kv_end(last_shard(p, dev_)), dev(dev_), layout(p.layout), c(p.c), turn(wave) {
+        n_full = (p.c + 31) / 32;
+        int end0 = min(q0 + OWN, p.c), end1 = end0 - 1;
+        if (p.skip_bq > 0) {
+            const int q_hi = (q0 / p.skip_bq + 1) * p.skip_bq - 1;
+            end0 = min(p.c, (q_hi / p.skip_bk + 1) * p.skip_bk);
+            end1 = min(p.c, ((q_hi - 1) / p.skip_bk + 1) * p.skip_bk);
         }
-        const bool more = next.kv < kv_end;
-        __builtin_amdgcn_s_waitcnt(0);         // this group has landed (vmcnt) ...
-        __syncthreads();                       // ... for every wavefront, and all are done with the last one
-        if (more) {
-            if (next.kv != now.kv) {
-                next = block(next.kv);
-                K = dt_advance(K, 2 * p.kv_shard);
-                V = dt_advance(V, 2 * p.kv_shard);
-            }
-            char* to = lds + (1 - parity) * 2 * GROUP_BYTES<DP>;
-            load_group<DP>(K, next_g0, p.c, pitch, to, gl, ln.wave);
-            load_group<DP>(V, next_g0, p.c, pitch, to + GROUP_BYTES<DP>, gl, ln.wave);
-        }
-        const char* k = lds + parity * 2 * GROUP_BYTES<DP> + ln.wave * SUB_BYTES<DP>;
-        if (g0 + OWN * ln.wave <= now.last_key) body(k, k + GROUP_BYTES<DP>, g0 + OWN * ln.wave, now);
-        if (!more) break;
-        now = next;
-        g0 = next_g0;
-        parity ^= 1;
+        n_off0 = (end0 + 31) / 32;
+        n_off1 = (end1 + 31) / 32;
+        n_fine = q0 / 32 + 1;
     }
-}
-
+    // to the wavefront's first sub-tile of block kv
+    template <int WAVES>
+    __device__ void enter() {
+        const bool full = block_kind(dev, kv, layout) == MASK_FULL;
+        const int off = block_off(dev, kv, layout);
+        // (values, not members, to choose from: a choice between addresses keeps the object in memory)
+        const int all = n_full, tri0 = n_off0, tri1 = n_off1, tri = n_fine;
+        n = full ? all : off ? tri1 : tri0;
+        shift = full ? c : -off;
+        v = turn & (WAVES - 1);
+        turn -= full ? all : tri;
+    }
+    template <int WAVES>
+    __device__ void settle() {
+        while (v >= n && kv < kv_end) {
+            ++kv;
+            enter<WAVES>();
+        }
+    }
+};
 
 // ------------------------------------------------------------------ forward
-template <int DP, bool PART>
-__global__ void __launch_bounds__(64 * WAVES, DP <= 64 ? 2 : 1)
+// Eight wavefronts, two to a SIMD: one's products run beside the other's vector instructions.  One stage each,
+// which is requested anew when the sub-tile has been read into registers.
+constexpr float RESCALE_SUM = 16777216.f;       // 2^24, see fwd_mfma.hip
+// ROPE: the query rows are rotated by their position ids (d == DP).
+template <int DP, bool PART, bool EXACT, bool ROPE = false>
+__global__ void __launch_bounds__(64 * FWD_WAVES, 2)
 fwd_split_kernel(StepArgs p, int n_tiles) {
-    constexpr int MB = blocks_of(DP);
-    // two buffers of K and V; at the end the statistics and four wavefronts' partial results
-    __shared__ __attribute__((aligned(1024))) char lds[4 * GROUP_BYTES<DP>];
-    static_assert(1024 + PARTIAL_BYTES<DP> <= 4 * GROUP_BYTES<DP>, "partial results");
+    constexpr int MB = blocks_of(DP), KS = ksteps_of(DP), WAVES = FWD_WAVES, N = share_of(DP, WAVES);
+    // the wavefronts' stages and the owned rows; at the end the statistics and partial results
+    constexpr int TILES = WAVES * STAGE_BYTES<DP> > PARTIAL_BYTES<DP, WAVES> ? WAVES * STAGE_BYTES<DP> : PARTIAL_BYTES<DP, WAVES>;
+    __shared__ __attribute__((aligned(1024))) char lds[TILES + SUB_BYTES<DP>];
+    __shared__ float stats[WAVES * 64];                // [wave][m | l][32]
     __shared__ uint32_t masks[WAVES];
+    __shared__ double rope_turns[ROPE ? DP / 2 : 1];
 
     const Lane<DP> ln;
     const int n = ln.n, h = ln.h;
@@ -233,56 +326,153 @@ fwd_split_kernel(StepArgs p, int n_tiles) {
     const int b = bh / p.H, hd = bh - b * p.H, d = p.d;
     const int64_t base = b * p.stride_b + hd * p.stride_h + dev_i * p.q_shard;
     const int64_t kv_base = b * p.kv_stride_b + (hd / (p.H / p.H_kv)) * p.kv_stride_h;
-    const int pitch = 2 * (int)p.kv_stride_s;
+    const int pitch = 2 * (int)p.kv_stride_s, own_pitch = 2 * (int)p.stride_s;
 
     const int a_own = q0 + n, a = min(a_own, p.c - 1);
-    bf16x8 qf[8];
-    load_b_frags<8>(qf, (const __bf16*)p.q + base + (int64_t)a * p.stride_s, h, d);
+    char* const own_rows = lds + TILES;
+    char* const k = lds + ln.wave * STAGE_BYTES<DP>;
+    char* const v = k + SUB_BYTES<DP>;
+    load_own<DP, WAVES>(dt_make_rsrc((const __bf16*)p.q + base, p.c, own_pitch, d), q0, own_pitch, d, own_rows, ln);
+
+    KeyCursor at(p, dev, q0, ln.wave);
+    const Loader<DP> loader(pitch, d, ln.lane);
+    dt_rsrc K = stream_rsrc((const __bf16*)p.k + kv_base, p.c, pitch, d);
+    dt_rsrc V = stream_rsrc((const __bf16*)p.v + kv_base, p.c, pitch, d);
+    int kv_loaded = at.kv, kv = 0, key0 = 0, shift = 0;
+    // requests the next sub-tile
+    auto request = [&]() {
+        at.settle<WAVES>();
+        kv = at.kv;
+        key0 = 32 * at.v;
+        shift = at.shift;
+        if (kv == at.kv_end) return;
+        if (kv != kv_loaded) {
+            K = dt_advance(K, (kv - kv_loaded) * 2 * p.kv_shard);
+            V = dt_advance(V, (kv - kv_loaded) * 2 * p.kv_shard);
+            kv_loaded = kv;
+        }
+        loader.all(K, V, key0, k);
+        at.v += WAVES;
+    };
+    at.enter<WAVES>();
+    request();
+
     float* L = p.lse + b * p.stat_stride_b + hd * p.stat_stride_h + (int64_t)dev_i * p.c + a;
-    const float old = p.fresh ? -INFINITY : *L;
     const Scale2 kappa(p.scale);
     const int part_ks = (PART && ((d >> 3) & 1) == h) ? (d >> 4) : -1;
     float m = -INFINITY, l = 0.f;           // m in base-2 units; l: this half-wave's share of the row sum
     f32x16 acc[4];
 #pragma unroll
     for (int mb = 0; mb < 4; ++mb) acc[mb] = zero16();
+    // as in fwd_mfma.hip: a walk over striped shards sets its references anew at each
+    const bool rebase_shards = !EXACT && p.n_kv > 1 && p.layout == SA_STRIPED;
+    int kv_before = -1;
 
-    walk_keys<DP>(p, dev, q0, dt_make_rsrc((const __bf16*)p.k + kv_base, p.c, pitch, d),
-              dt_make_rsrc((const __bf16*)p.v + kv_base, p.c, pitch, d), lds, ln,
-              [&](const char* k, const char* v, int key0, const Block& blk) {
-        f32x16 x = scores<DP, PART>(k, qf, ln, part_ks);
-        const int lane_last = (blk.full ? p.c - 1 : a_own - blk.off) - key0;
-        float mx = -INFINITY;
+    int position = 0;
+    if (ROPE) {
+        position = p.q_pos[b * p.pos_stride_b + a];
+        fill_rope_turns<DP>(rope_turns, threadIdx.x, p.rope_log2_base);
+        wait_lds();
+    }
+    wait_all_but<0>();
+    __builtin_amdgcn_s_barrier();
+    bf16x8 qf[8];
+    read_own<DP, PART>(qf, own_rows, ln, part_ks);
+    if (ROPE) rope_rotate<DP>(qf, rope_turns, position, h);
+    while (kv < at.kv_end) {
+        wait_all_but<0>();
+        bf16x8 kr[8], vt[8];
+        read_rows<DP>(kr, k, ln);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            x[r] = reg_row(r, h) <= lane_last ? x[r] : -INFINITY;
-            mx = fmaxf(mx, x[r]);
-        }
-        const float m_new = fmaxf(m, half_wave_max(mx) * kappa.hi);
-        const float ref = m_new == -INFINITY ? 0.f : m_new;                 // a row without a key so far
-        const float alpha = __builtin_amdgcn_exp2f(m - ref);
-        float sum = 0.f;
+        for (int i = 0; i < 2 * MB; ++i) read_transposed<DP>(vt, i, v, ln);
+        __builtin_amdgcn_sched_barrier(0);
+        f32x16 x;
+        // the first two products only need half of the rows: the other reads meanwhile
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            x[r] = kappa.exp2(x[r], ref, 0.f);
-            sum += x[r];
+        for (int ks = 0; ks < 2; ++ks) score_product<PART, DP>(x, kr[ks], qf[ks], ks, part_ks);
+        __builtin_amdgcn_sched_barrier(0);
+        wait_lds();
+        const bool masked = key0 + 31 > min(p.c - 1, q0 + shift);          // some pair of the sub-tile is
+        const int lane_last = min(p.c - 1, a_own + shift) - key0;
+        const bool rebase = rebase_shards && kv != kv_before;
+        kv_before = kv;
+        request();
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int ks = 2; ks < KS; ++ks) score_product<PART, DP>(x, kr[ks], qf[ks], ks, part_ks);
+        mfma_results_to_valu(x);
+        if (masked) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) x[r] = reg_row(r, h) <= lane_last ? x[r] : -INFINITY;
         }
-        l = l * alpha + sum;
-        if (__builtin_amdgcn_ballot_w64(m_new != m) != 0) {
+        auto highest = [&]() {
+            float mx[2] = {x[0], x[1]};
+#pragma unroll
+            for (int r = 2; r < 16; ++r) mx[r % 2] = fmaxf(mx[r % 2], x[r]);
+            return half_wave_max(fmaxf(mx[0], mx[1])) * kappa.hi;
+        };
+        auto rescale = [&](float alpha) {
+            l *= alpha;
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) acc[mb][r] *= alpha;
+        };
+        float sum[2] = {0.f, 0.f};
+        if (EXACT) {
+            const float m_new = fmaxf(m, highest());
+            const float ref = m_new == -INFINITY ? 0.f : m_new;                 // a row without a key so far
+            if (__builtin_amdgcn_ballot_w64(m_new != m) != 0) rescale(__builtin_amdgcn_exp2f(m - ref));
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                x[r] = kappa.exp2(x[r], ref, 0.f);
+                sum[r % 2] += x[r];
+            }
+            m = m_new;
+        } else {
+            // the reference moves when it has to, as in fwd_mfma.hip
+            f32x16 pr;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                pr[r] = __builtin_amdgcn_exp2f(fmaf(x[r], kappa.hi, -m));
+                sum[r % 2] += pr[r];
+            }
+            if (rebase || __builtin_amdgcn_ballot_w64(!(sum[0] + sum[1] < RESCALE_SUM)) != 0) {
+                const float mx = highest();
+                float m_new = fmaxf(m, mx);
+                if (rebase && mx != -INFINITY)
+                    m_new = fmaxf(mx, m + __builtin_amdgcn_logf(half_wave_sum(l) * (1.f / RESCALE_SUM)));
+                const float ref = m_new == -INFINITY ? 0.f : m_new;
+                rescale(__builtin_amdgcn_exp2f(m - ref));
+                m = m_new;
+                sum[0] = sum[1] = 0.f;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    pr[r] = __builtin_amdgcn_exp2f(fmaf(x[r], kappa.hi, -ref));
+                    sum[r % 2] += pr[r];
+                }
+            }
+            x = pr;
         }
-        m = m_new;
-        accumulate<DP, true>(acc, v, x, ln);
-    });
+        l += sum[0] + sum[1];
+#pragma unroll
+        for (int g = 0; g < 2; ++g) {
+            bf16x8 w[3];
+            as_operand<EXACT>(x, g, w);
+#pragma unroll
+            for (int t = EXACT ? 2 : 0; t >= 0; --t)          // smallest terms first
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb) acc[mb] = mfma(vt[4 * g + mb], w[t], acc[mb]);
+        }
+    }
 
-    // the four wavefronts' partial results against a common reference
-    float* const stats = reinterpret_cast<float*>(lds);                // [wave][m | l][32]
-    char* const buf = lds + 1024;
+    const float old = p.fresh ? -INFINITY : *L;
+    float* O = p.o + base + (int64_t)a * p.stride_s;
+    float4 o_old[N];
+    load_old<DP, WAVES>(o_old, O, d, !p.fresh && a_own < p.c, ln);
+    // the wavefronts' partial results against a common reference
     const float l_own = half_wave_sum(l);
-    __syncthreads();
     if (h == 0) {
         stats[ln.wave * 64 + n] = m;
         stats[ln.wave * 64 + 32 + n] = l_own;
@@ -301,73 +491,95 @@ fwd_split_kernel(StepArgs p, int n_tiles) {
     for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[mb][r] *= f;
-    put_partial<DP>(buf, acc, ln);
+    put_partial<DP>(lds, acc, ln);
     // a row sum that is no positive number although the row sees a key: see f32_rows.h
-    put_odd(masks, a_own < p.c && (not_finite<MB>(acc) ||
-                                   (!(l_tot > 0.f && l_tot < INFINITY) && sees_a_key(p, dev, a))), ln.wave, ln.lane);
+    if (EXACT)
+        put_odd(masks, a_own < p.c && (not_finite<MB>(acc) ||
+                                       (!(l_tot > 0.f && l_tot < INFINITY) && sees_a_key(p, dev, a))), ln.wave, ln.lane);
 
-    const float part = l_tot > 0.f ? fmaf(m_all, LN2_HI, fmaf(m_all, LN2_LO, logf(l_tot))) : -INFINITY;
+    const float part = l_tot == 0.f ? -INFINITY : fmaf(m_all, LN2_HI, fmaf(m_all, LN2_LO, logf(l_tot)));
     const float top = fmaxf(old, part);
     const float ref = top == -INFINITY ? 0.f : top;
     const float w_old = expf(old - ref), w_part = expf(part - ref), w_sum = w_old + w_part;
     const float inv = w_sum > 0.f ? 1.f / w_sum : 0.f;
     const float f_old = w_old * inv, f_part = l_tot > 0.f ? w_part * inv / l_tot : 0.f;
-    float* O = p.o + base + (int64_t)a * p.stride_s;
-    float4 o_old[MB];           // on its way while the partial results meet
-#pragma unroll
-    for (int i = 0; i < MB; ++i) {
-        o_old[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (f_old != 0.f && column_of<DP>(i, ln) < d) o_old[i] = *reinterpret_cast<const float4*>(O + column_of<DP>(i, ln));
-    }
     __syncthreads();
-    const uint32_t odd_rows = take_odd(masks);
+    const uint32_t odd_rows = EXACT ? take_odd<WAVES>(masks) : 0;
     // no row here, or no key seen: state unchanged
     if (a_own < p.c && !((odd_rows >> n) & 1) && (part != -INFINITY || p.fresh)) {
 #pragma unroll
-        for (int i = 0; i < MB; ++i) {
-            const int col = column_of<DP>(i, ln);
+        for (int i = 0; i < N; ++i) {
+            const int col = column_of<DP, WAVES>(i, ln);
             if (col >= d) continue;
             float4* dst = reinterpret_cast<float4*>(O + col);
-            const float4 s = take_sum<DP>(buf, piece_of<DP>(i, ln), ln);
+            const float4 s = take_sum<DP, WAVES>(lds, i, ln);
             float4 x = o_old[i];
-            x.x *= f_old; x.y *= f_old; x.z *= f_old; x.w *= f_old;
+            if (f_old != 0.f) {
+                x.x *= f_old; x.y *= f_old; x.z *= f_old; x.w *= f_old;
+            } else {                    // an empty state: nothing of O is looked at
+                x = make_float4(0.f, 0.f, 0.f, 0.f);
+            }
             x.x = fmaf(s.x, f_part, x.x); x.y = fmaf(s.y, f_part, x.y);
             x.z = fmaf(s.z, f_part, x.z); x.w = fmaf(s.w, f_part, x.w);
             *dst = x;
         }
         if (ln.wave == 0 && h == 0) *L = top + logf(w_sum);
     }
-    each_row<WAVES>(odd_rows, ln.wave, [&](const StepArgs& again, int i) { fwd_row<__hip_bfloat16>(again, b, hd, dev_i, q0 + i, ln.lane); });
+    if (EXACT) each_row<WAVES>(odd_rows, ln.wave, [&](const StepArgs& again, int i) { fwd_row<__hip_bfloat16>(again, b, hd, dev_i, q0 + i, ln.lane); });
 }
 
-// this wavefront's share of the lane's row as it stands (zeros if not wanted): on its way while the
-// partial results meet
-template <int DP>
-__device__ inline void load_old(float4 (&x)[blocks_of(DP)], const float* row, int d, bool wanted, const Lane<DP>& ln) {
-#pragma unroll
-    for (int i = 0; i < blocks_of(DP); ++i) {
-        x[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (wanted && column_of<DP>(i, ln) < d) x[i] = *reinterpret_cast<const float4*>(row + column_of<DP>(i, ln));
-    }
-}
 // x + scale * (sum of the partial results at buf) to the lane's row
 template <int DP>
 __device__ inline void add_rows(float* row, float4 (&x)[blocks_of(DP)], const char* buf, float scale, int d,
                                 const Lane<DP>& ln) {
 #pragma unroll
     for (int i = 0; i < blocks_of(DP); ++i) {
-        const int col = column_of<DP>(i, ln);
+        const int col = column_of<DP, BWD_WAVES>(i, ln);
         if (col >= d) continue;
-        const float4 s = take_sum<DP>(buf, piece_of<DP>(i, ln), ln);
+        const float4 s = take_sum<DP, BWD_WAVES>(buf, i, ln);
         x[i].x = fmaf(scale, s.x, x[i].x); x[i].y = fmaf(scale, s.y, x[i].y);
         x[i].z = fmaf(scale, s.z, x[i].z); x[i].w = fmaf(scale, s.w, x[i].w);
         *reinterpret_cast<float4*>(row + col) = x[i];
     }
 }
 
-// ----------------------------------------------------------------------- dQ
+// ----------------------------------------------------------------- backward
+// One wavefront per SIMD (the key-owning side's registers), so what overlaps is arranged by hand: a
+// product leaves room for five or six other instructions.  In sub-tile u:
+//     S(u)      beside the transposing reads of u
+//     dP(u)     beside the exponentials of S(u), and the first requests of u + 2
+//     dQ (or dV and dK) += ...(u)   beside dS(u), the other requests and the row reads of u + 1
+// Products whose result vector instructions read go through asm forms, which keep it out of the
+// accumulation registers (the owned operands are pinned to those, which the streamed ones leave
+// free).  What the compiler's hazard recogniser cannot see (mfma_tiles.h) is kept by the order: vector
+// instructions on S start behind the second product of dP, those on dP behind the second product
+// that follows its last.
+template <bool PART, int DP>
+__device__ __forceinline__ void score_product_own(f32x16& acc, bf16x8 a, bf16x8 own, int ks, int part_ks) {
+    const bf16x8 x = row_operand<PART, DP>(a, ks, part_ks);
+    if (PART && ks >= part_from(DP)) {          // a vector select before it
+        if (ks == 0) asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(acc) : "v"(x), "a"(own));
+        else asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(x), "a"(own));
+        return;
+    }
+    if (ks == 0) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(acc) : "v"(x), "a"(own));
+    else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(x), "a"(own));
+}
+// the same with other start values than zero
+template <bool PART, int DP>
+__device__ __forceinline__ void score_product_from(f32x16& acc, const f32x16& start, bf16x8 a, bf16x8 own, int part_ks) {
+    const bf16x8 x = row_operand<PART, DP>(a, 0, part_ks);
+    asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %3" : "=&v"(acc) : "v"(x), "a"(own), "v"(start));
+}
+__device__ inline bf16x8 negated(bf16x8 x) {
+    typedef int i32x4 __attribute__((ext_vector_type(4)));
+    return __builtin_bit_cast(bf16x8, __builtin_bit_cast(i32x4, x) ^ (int)0x80008000);
+}
+
+// dQ: a workgroup owns queries
 template <int DP, bool PART, bool EXACT>
-__device__ inline void bwd_dq(const StepArgs& p, int n_tiles, int linear, char* lds, uint32_t* masks) {
+__device__ inline void bwd_dq(const StepArgs& p, int n_tiles, int linear, char* lds, char* stats, uint32_t* masks) {
+    constexpr int KS = ksteps_of(DP), MB = blocks_of(DP), WAVES = BWD_WAVES, LOADS = 2 * PIECES<DP>, TERMS = EXACT ? 3 : 1;
     const Lane<DP> ln;
     const int n = ln.n, h = ln.h;
     int rank, bh, dev_rank;
@@ -378,172 +590,369 @@ __device__ inline void bwd_dq(const StepArgs& p, int n_tiles, int linear, char* 
     const int64_t base = b * p.stride_b + hd * p.stride_h + dev_i * p.q_shard;
     const int64_t kv_base = b * p.kv_stride_b + (hd / (p.H / p.H_kv)) * p.kv_stride_h;
     const int64_t sbase = b * p.stat_stride_b + hd * p.stat_stride_h + (int64_t)dev_i * p.c;
-    const int pitch = 2 * (int)p.kv_stride_s;
+    const int pitch = 2 * (int)p.kv_stride_s, own_pitch = 2 * (int)p.stride_s;
 
     const int a_own = q0 + n, a = min(a_own, p.c - 1);
-    bf16x8 qf[8], gf[8];
-    load_b_frags<8>(qf, (const __bf16*)p.q + base + (int64_t)a * p.stride_s, h, d);
-    load_b_frags<8>(gf, (const __bf16*)p.dout + base + (int64_t)a * p.stride_s, h, d);
-    const float delta = p.delta[sbase + a];
+    char* const own_rows = lds + WAVES * 2 * STAGE_BYTES<DP>;
+    load_own<DP, WAVES>(dt_make_rsrc((const __bf16*)p.q + base, p.c, own_pitch, d), q0, own_pitch, d, own_rows, ln);
+    load_own<DP, WAVES>(dt_make_rsrc((const __bf16*)p.dout + base, p.c, own_pitch, d), q0, own_pitch, d, own_rows + SUB_BYTES<DP>, ln);
+    char* const own_stats = stats + ln.wave * 2 * STAT_BYTES;       // every wavefront has its own
+    load_stat(dt_make_rsrc(p.lse + sbase, p.c, 4, 2), q0, own_stats, ln.lane);
+    load_stat(dt_make_rsrc(p.delta + sbase, p.c, 4, 2), q0, own_stats + 256, ln.lane);
+
+    KeyCursor at(p, dev, q0, ln.wave);
+    const Loader<DP> loader(pitch, d, ln.lane);
+    char* const tiles = lds + ln.wave * 2 * STAGE_BYTES<DP>;
+    dt_rsrc K = stream_rsrc((const __bf16*)p.k + kv_base, p.c, pitch, d);
+    dt_rsrc V = stream_rsrc((const __bf16*)p.v + kv_base, p.c, pitch, d);
+    int kv_at = at.kv;
+    // (behind the walk's end: rows beyond the matrix, whose loads deliver zeros without a look at memory)
+    const int beyond = 32 * at.n_full;
+    struct Tile { int key0, shift; };               // key0 == beyond: none
+    // the walk's next sub-tile; K, V: of its block
+    auto take = [&](Tile& t) {
+        at.settle<WAVES>();
+        t.key0 = at.kv < at.kv_end ? 32 * at.v : beyond;
+        t.shift = at.shift;
+        at.v += WAVES;
+        if (at.kv != kv_at) {
+            K = dt_advance(K, (at.kv - kv_at) * 2 * p.kv_shard);
+            V = dt_advance(V, (at.kv - kv_at) * 2 * p.kv_shard);
+            kv_at = at.kv;
+        }
+    };
+    Tile t0, t1 = {beyond, 0}, t2;
+    at.enter<WAVES>();
+#pragma unroll 1
+    for (int i = 0; i < 2; ++i) {
+        t0 = t1;
+        take(t1);
+        loader.all(K, V, t1.key0, tiles + i * STAGE_BYTES<DP>);
+    }
     const Scale2 kappa(p.scale);
-    float lse2, lse2_lo;
-    to_base2(p.lse[sbase + a], lse2, lse2_lo);
     const int part_ks = (PART && ((d >> 3) & 1) == h) ? (d >> 4) : -1;
     f32x16 acc[4];
 #pragma unroll
     for (int mb = 0; mb < 4; ++mb) acc[mb] = zero16();
-
-    float z[2] = {0.f, 0.f};
-    walk_keys<DP>(p, dev, q0, dt_make_rsrc((const __bf16*)p.k + kv_base, p.c, pitch, d),
-              dt_make_rsrc((const __bf16*)p.v + kv_base, p.c, pitch, d), lds, ln,
-              [&](const char* k, const char* v, int key0, const Block& blk) {
-        const f32x16 s = scores<DP, PART>(k, qf, ln, part_ks), dp = scores<DP, PART>(v, gf, ln, part_ks);
-        const int lane_last = (blk.full ? p.c - 1 : a_own - blk.off) - key0;
-        f32x16 ds;
+    wait_all_but<2 * LOADS>();
+    __builtin_amdgcn_s_barrier();
+    bf16x8 qf[8], gf[8], kr[8], vr[8];
+    read_own<DP, PART>(qf, own_rows, ln, part_ks);
+    read_own<DP, PART>(gf, own_rows + SUB_BYTES<DP>, ln, part_ks);
+    float lse2, lse2_lo;
+    to_base2(reinterpret_cast<const float*>(own_stats)[n], lse2, lse2_lo);
+    f32x16 neg_delta;           // dP starts from it
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            float pr = EXACT ? kappa.exp2(s[r], lse2, lse2_lo) : __builtin_amdgcn_exp2f(fmaf(s[r], kappa.hi, -lse2));
-            if (reg_row(r, h) > lane_last) pr = 0.f;
-            ds[r] = pr * (dp[r] - delta);
+    for (int r = 0; r < 16; ++r) neg_delta[r] = -reinterpret_cast<const float*>(own_stats)[64 + n];
+    float z[2] = {0.f, 0.f};
+    wait_all_but<LOADS>();
+    read_rows<DP>(kr, tiles, ln);
+    read_rows<DP>(vr, tiles + SUB_BYTES<DP>, ln);
+    for (int stage = 0; t0.key0 != beyond; stage ^= 1) {
+        char* const k = tiles + stage * STAGE_BYTES<DP>;
+        const char* const k_next = tiles + (stage ^ 1) * STAGE_BYTES<DP>;
+        bf16x8 kt[8];
+        f32x16 s, dp, pr;
+        take(t2);
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            __builtin_amdgcn_sched_barrier(0);
+            score_product_own<PART, DP>(s, kr[ks], qf[ks], ks, part_ks);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 2 * MB * ks / KS; i < 2 * MB * (ks + 1) / KS; ++i) read_transposed<DP>(kt, i, k, ln);
+        }
+        constexpr int EACH = (16 + KS - 2) / (KS - 1);
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            __builtin_amdgcn_sched_barrier(0);
+            if (ks == 0) score_product_from<PART, DP>(dp, neg_delta, vr[0], gf[0], part_ks);
+            else score_product_own<PART, DP>(dp, vr[ks], gf[ks], ks, part_ks);
+            __builtin_amdgcn_sched_barrier(0);
+            if (ks >= 1) {
+#pragma unroll
+                for (int r = (ks - 1) * EACH; r < min(16, ks * EACH); ++r)
+                    pr[r] = EXACT ? kappa.exp2(s[r], lse2, lse2_lo) : __builtin_amdgcn_exp2f(fmaf(s[r], kappa.hi, -lse2));
+            }
+            if (ks == KS / 2) wait_lds();           // the stage's last reads
+            if (ks == KS / 2) loader.part(0, K, V, t2.key0, k);
+            if (ks == KS - 2) loader.part(1, K, V, t2.key0, k);
+        }
+        asm volatile("" : "+v"(pr));            // there, beside the products
+        __builtin_amdgcn_sched_barrier(0);
+        if (t0.key0 + 31 > min(p.c - 1, q0 + t0.shift)) {          // some pair of the sub-tile is masked
+            const int lane_last = min(p.c - 1, a_own + t0.shift) - t0.key0;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) pr[r] = reg_row(r, h) <= lane_last ? pr[r] : 0.f;
         }
         if (EXACT) look_at(z, s);
-        accumulate<DP, EXACT>(acc, k, ds, ln);
-    });
+        mfma_results_to_valu(dp);
+        bf16x8 w[2][3];
+#pragma unroll
+        for (int r = 0; r < 8; ++r) pr[r] *= dp[r];
+        as_operand<EXACT>(pr, 0, w[0]);
+#pragma unroll
+        for (int g = 0; g < 2; ++g)
+#pragma unroll
+            for (int t = TERMS - 1; t >= 0; --t)          // smallest terms first
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    acc[mb] = mfma(kt[4 * g + mb], w[g][t], acc[mb]);
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (t != TERMS - 1) continue;
+                    if (g == 0 && mb == 0) {
+#pragma unroll
+                        for (int r = 8; r < 16; ++r) pr[r] *= dp[r];
+                        as_operand<EXACT>(pr, 1, w[1]);
+                    }
+                    if (g == 0 && mb == MB - 1) loader.part(2, K, V, t2.key0, k);
+                    if (g == 1 && mb == 0) {
+                        loader.part(3, K, V, t2.key0, k);
+                        wait_all_but<LOADS>();
+                        read_rows<DP>(kr, k_next, ln);
+                    }
+                    if (g == 1 && mb == 1) read_rows<DP>(vr, k_next + SUB_BYTES<DP>, ln);
+                }
+        __builtin_amdgcn_sched_barrier(0);
+        t0 = t1;
+        t1 = t2;
+    }
+    wait_all_but<0>();
 
     float* const DQ = p.dq + base + (int64_t)a * p.stride_s;
-    float4 old[blocks_of(DP)];
-    load_old<DP>(old, DQ, d, !p.fresh && a_own < p.c, ln);
+    float4 old[MB];
+    load_old<DP, WAVES>(old, DQ, d, !p.fresh && a_own < p.c, ln);
     __syncthreads();
     put_partial<DP>(lds, acc, ln);
     if (EXACT) put_odd(masks, a_own < p.c && odd_sum(z, acc), ln.wave, ln.lane);
     __syncthreads();
-    const uint32_t odd_rows = EXACT ? take_odd(masks) : 0;
+    const uint32_t odd_rows = EXACT ? take_odd<WAVES>(masks) : 0;
     if (a_own < p.c && !((odd_rows >> n) & 1))
         add_rows<DP>(DQ, old, lds, p.scale, d, ln);
     if (EXACT) each_row<WAVES>(odd_rows, ln.wave, [&](const StepArgs& again, int i) { dq_row<__hip_bfloat16>(again, b, hd, dev_i, q0 + i, ln.lane); });
 }
 
-// -------------------------------------------------------------------- dK/dV
-// Owned rows are keys, the streamed groups 128 queries with their LSE and delta beside them; the
-// query heads that share the key/value head and the query shards that see it come one after the
-// other.
+// dK, dV: owned rows are keys, the streamed ones queries with their LSE and delta beside them; the query heads
+// that share the key/value head and the query shards that see it come one after the other.  The owned V is
+// negated, so that delta - dP comes out of the product that starts from delta; dK changes its sign
+// at the end.
 template <int DP, bool PART, bool EXACT>
-__device__ inline void bwd_dkdv(const StepArgs& p, int n_tiles, int linear, char* lds, float* stats, uint32_t* masks) {
+__device__ inline void bwd_dkdv(const StepArgs& p, int n_tiles, int linear, char* lds, char* stats, uint32_t* masks) {
+    constexpr int KS = ksteps_of(DP), MB = blocks_of(DP), WAVES = BWD_WAVES, LOADS = 2 * PIECES<DP> + 2, TERMS = EXACT ? 3 : 1;
     const Lane<DP> ln;
-    const int n = ln.n, h = ln.h, tid = threadIdx.x;
+    const int n = ln.n, h = ln.h, wave = ln.wave;
     int tile, bh, dev_i;                                // low key tiles see most queries: first
     decode(linear, p.B * p.H_kv, tile, bh);
     decode_rank(tile, n_tiles, p.n_kv, p.layout, tile, dev_i);
     const int k0 = tile * OWN, dev = p.kv_dev + dev_i;
     const int b = bh / p.H_kv, kvh = bh - b * p.H_kv, group = p.H / p.H_kv, d = p.d;
     const int64_t kv_base = b * p.kv_stride_b + kvh * p.kv_stride_h + dev_i * p.kv_shard;
-    const int pitch = 2 * (int)p.stride_s;
+    const int pitch = 2 * (int)p.stride_s, own_pitch = 2 * (int)p.kv_stride_s;
 
     const int key_own = k0 + n, key = min(key_own, p.c - 1);
     const int64_t row = kv_base + (int64_t)key * p.kv_stride_s;
-    bf16x8 kf[8], vf[8];
-    load_b_frags<8>(kf, (const __bf16*)p.k + row, h, d);
-    load_b_frags<8>(vf, (const __bf16*)p.v + row, h, d);
+    char* const own_rows = lds + WAVES * 2 * STAGE_BYTES<DP>;
+    load_own<DP, WAVES>(dt_make_rsrc((const __bf16*)p.k + kv_base, p.c, own_pitch, d), k0, own_pitch, d, own_rows, ln);
+    load_own<DP, WAVES>(dt_make_rsrc((const __bf16*)p.v + kv_base, p.c, own_pitch, d), k0, own_pitch, d, own_rows + SUB_BYTES<DP>, ln);
+
+    // Blocks: the members of the group, each with the query shards that see the keys.  Of a block this
+    // wavefront takes the sub-tiles of 32 queries whose number less k0 / 32 (full blocks: whose number) is
+    // wave - turn modulo 4, turn counting the sub-tiles of the blocks before.
+    const Loader<DP> loader(pitch, d, ln.lane);
+    char* const tiles = lds + wave * 2 * STAGE_BYTES<DP>;
+    char* const tile_stats = stats + wave * 2 * STAT_BYTES;
+    const int q_dev0 = p.layout == SA_STRIPED ? p.q_dev : max(p.q_dev, dev), q_end = p.q_dev + p.n_q;
+    const int n_sub = (p.c + 31) / 32;
+    int member = q_dev0 < q_end ? 0 : group, q_dev = q_dev0, v = 0, turn = 0;
+    int shift = 0;              // key b is seen by the block's queries from b + shift on
+    dt_rsrc Q, G, S, E;
+    auto enter = [&]() {
+        const bool full = block_kind(q_dev, dev, p.layout) == MASK_FULL;
+        const int off = block_off(q_dev, dev, p.layout), fine = full ? 0 : k0 / 32;
+        // first query a workgroup of these keys looks at (emulated coarse skipping: from the first
+        // skip_bq-tall tile that shares an allowed pair with the keys' skip_bk-wide one)
+        int first = fine;
+        if (!full && p.skip_bq > 0) first = (k0 / p.skip_bk * p.skip_bk + off) / p.skip_bq * p.skip_bq / 32;
+        v = first + ((fine + wave - turn - first) & (WAVES - 1));
+        turn += n_sub - fine;
+        shift = full ? -(p.c + OWN) : off;
+        const int hd = kvh * group + member;
+        const int64_t base = b * p.stride_b + hd * p.stride_h + (q_dev - p.q_dev) * p.q_shard;
+        const int64_t sbase = b * p.stat_stride_b + hd * p.stat_stride_h + (int64_t)(q_dev - p.q_dev) * p.c;
+        Q = stream_rsrc((const __bf16*)p.q + base, p.c, pitch, d);
+        G = stream_rsrc((const __bf16*)p.dout + base, p.c, pitch, d);
+        S = dt_make_rsrc(p.lse + sbase, p.c, 4, 2);
+        E = dt_make_rsrc(p.delta + sbase, p.c, 4, 2);
+    };
+    const int beyond = 32 * n_sub;             // behind the walk's end, as above
+    struct Tile { int a0, shift; };            // a0 == beyond: none
+    // the walk's next sub-tile; Q, G, S, E: of its block
+    auto take = [&](Tile& t) {
+        while (v >= n_sub && member < group) {
+            if (++q_dev >= q_end) {
+                q_dev = q_dev0;
+                ++member;
+            }
+            if (member < group) enter();
+        }
+        t.a0 = member < group ? 32 * v : beyond;
+        t.shift = shift;
+        v += WAVES;
+    };
+    auto load_stats = [&](const Tile& t, int stage) {
+        load_stat(S, t.a0, tile_stats + stage * STAT_BYTES, ln.lane);
+        load_stat(E, t.a0, tile_stats + stage * STAT_BYTES + 256, ln.lane);
+    };
+    enter();
+    Tile t0, t1 = {beyond, 0}, t2;
+#pragma unroll 1
+    for (int i = 0; i < 2; ++i) {
+        t0 = t1;
+        take(t1);
+        loader.all(Q, G, t1.a0, tiles + i * STAGE_BYTES<DP>);
+        load_stats(t1, i);
+    }
     const Scale2 kappa(p.scale);
     const int part_ks = (PART && ((d >> 3) & 1) == h) ? (d >> 4) : -1;
     f32x16 acck[4], accv[4];
 #pragma unroll
     for (int mb = 0; mb < 4; ++mb) acck[mb] = accv[mb] = zero16();
-    uint32_t gl[4];
-    dt_load_offsets<DP>(gl, ln.lane, ln.wave, pitch, d);
-
-    // the block being walked: query head and shard, its queries' first group, sub-tile and mask
-    const int q_dev0 = p.layout == SA_STRIPED ? p.q_dev : max(p.q_dev, dev);
-    int member = 0, q_dev = q_dev0, first, off;
-    bool full;
-    dt_rsrc Q, G;
-    const float* stat_src;          // this thread's statistic: LSE (threads 0..127) or delta of a group's row
-    auto enter_block = [&]() {
-        const int hd = kvh * group + member;
-        full = block_kind(q_dev, dev, p.layout) == MASK_FULL;
-        off = block_off(q_dev, dev, p.layout);
-        // first query a workgroup of these keys looks at (emulated coarse skipping: from the first
-        // skip_bq-tall tile that shares an allowed pair with the keys' skip_bk-wide one)
-        first = full ? 0 : k0;
-        if (!full && p.skip_bq > 0) first = (k0 / p.skip_bk * p.skip_bk + off) / p.skip_bq * p.skip_bq;
-        const int64_t base = b * p.stride_b + hd * p.stride_h + (q_dev - p.q_dev) * p.q_shard;
-        Q = dt_make_rsrc((const __bf16*)p.q + base, p.c, pitch, d);
-        G = dt_make_rsrc((const __bf16*)p.dout + base, p.c, pitch, d);
-        stat_src = (tid < GROUP ? p.lse : p.delta) + b * p.stat_stride_b + hd * p.stat_stride_h +
-                   (int64_t)(q_dev - p.q_dev) * p.c;
-    };
-    float stat;
-    auto request = [&](int g0, char* to) {
-        load_group<DP>(Q, g0, p.c, pitch, to, gl, ln.wave);
-        load_group<DP>(G, g0, p.c, pitch, to + GROUP_BYTES<DP>, gl, ln.wave);
-        // rows beyond the shard arrive as zeros; LSE = +inf makes their P and dS zero
-        const int r = g0 + (tid & (GROUP - 1));
-        stat = stat_src[min(r, p.c - 1)];
-        if (tid < GROUP && r >= p.c) stat = INFINITY;
-    };
-    enter_block();
-    float z[2] = {0.f, 0.f};
-    int g0 = first / GROUP * GROUP, parity = 0;
-    request(g0, lds);
-    for (;;) {
-        const int now_first = first, lane_first = full ? 0 : key_own + off;
-        int next_g0 = g0 + GROUP;
-        bool more = next_g0 < p.c;
-        __builtin_amdgcn_s_waitcnt(0);
-        float* const st_now = stats + parity * 3 * GROUP;       // LSE in base-2 units, its rest, delta
-        if (tid < GROUP) to_base2(stat, st_now[tid], st_now[GROUP + tid]);
-        else st_now[GROUP + tid] = stat;
-        __syncthreads();
-        if (!more) {
-            if (++q_dev == p.q_dev + p.n_q) {
-                q_dev = q_dev0;
-                ++member;
-            }
-            more = member < group;
-            if (more) {
-                enter_block();
-                next_g0 = first / GROUP * GROUP;
-            }
-        }
-        if (more) request(next_g0, lds + (1 - parity) * 2 * GROUP_BYTES<DP>);
-        const int a0 = g0 + OWN * ln.wave;
-        if (a0 + 31 >= now_first && a0 < p.c) {
-            const char* q = lds + parity * 2 * GROUP_BYTES<DP> + ln.wave * SUB_BYTES<DP>;
-            const char* g = q + GROUP_BYTES<DP>;
-            const float* st = st_now + OWN * ln.wave;
-            const f32x16 s = scores<DP, PART>(q, kf, ln, part_ks), dp = scores<DP, PART>(g, vf, ln, part_ks);
-            f32x16 pr, ds;
+    wait_all_but<2 * LOADS>();
+    __builtin_amdgcn_s_barrier();
+    bf16x8 kf[8], vf[8], qr[8], gr[8];
+    read_own<DP, PART>(kf, own_rows, ln, part_ks);
+    read_own<DP, PART>(vf, own_rows + SUB_BYTES<DP>, ln, part_ks);
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int i = reg_row(r, h);
-                pr[r] = EXACT ? kappa.exp2(s[r], st[i], st[GROUP + i])
-                              : __builtin_amdgcn_exp2f(fmaf(s[r], kappa.hi, -st[i]));
-                if (a0 + i < lane_first) pr[r] = 0.f;
-                ds[r] = pr[r] * (dp[r] - st[2 * GROUP + i]);
+    for (int ks = 0; ks < KS; ++ks) vf[ks] = negated(vf[ks]);
+    // LSE (in base-2 units unless EXACT) and delta of this lane's registers' rows.  The 32 LSE of a sub-tile are
+    // scaled where they lie, by one instruction on one of each lane instead of one on each of 16.
+    f32x16 lse, delta;
+    float raw;
+    auto read_next = [&](int stage) {
+        if (!EXACT) raw = reinterpret_cast<const float*>(tile_stats + stage * STAT_BYTES)[ln.lane];
+        read_rows<DP>(qr, tiles + stage * STAGE_BYTES<DP>, ln);
+        read_rows<DP>(gr, tiles + stage * STAGE_BYTES<DP> + SUB_BYTES<DP>, ln);
+    };
+    float z[2] = {0.f, 0.f};
+    wait_all_but<LOADS>();
+    read_next(0);
+    for (int stage = 0; t0.a0 != beyond; stage ^= 1) {
+        char* const q = tiles + stage * STAGE_BYTES<DP>;
+        char* const g = q + SUB_BYTES<DP>;
+        char* const stat = tile_stats + stage * STAT_BYTES;
+        bf16x8 gt[8], qt[8];
+        f32x16 s, dp, pr, ds;
+        if (!EXACT) reinterpret_cast<float*>(stat)[ln.lane] = raw * LOG2E;         // (lanes 32 .. 63: nobody's)
+        take(t2);
+        // LDS reads: delta, LSE, transposed operands of dO and of Q
+        constexpr int READS = 8 + 4 * MB;
+        auto read = [&](int i) {
+            if (i < 8) {
+                const float4 y = *reinterpret_cast<const float4*>(stat + (i < 4 ? 256 : 0) + 4 * (8 * (i % 4) + 4 * h));
+                f32x16& x = i < 4 ? delta : lse;
+                const int r = 4 * (i % 4);
+                x[r] = y.x; x[r + 1] = y.y; x[r + 2] = y.z; x[r + 3] = y.w;
+            } else if (i < 8 + 2 * MB) {
+                read_transposed<DP>(gt, i - 8, g, ln);
+            } else {
+                read_transposed<DP>(qt, i - 8 - 2 * MB, q, ln);
             }
-            if (EXACT) look_at(z, s);
-            accumulate<DP, EXACT>(accv, g, pr, ln);
-            accumulate<DP, EXACT>(acck, q, ds, ln);
+        };
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            __builtin_amdgcn_sched_barrier(0);
+            score_product_own<PART, DP>(s, qr[ks], kf[ks], ks, part_ks);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = READS * ks / KS; i < READS * (ks + 1) / KS; ++i) read(i);
         }
-        if (!more) break;
-        g0 = next_g0;
-        parity ^= 1;
+        constexpr int EACH = (16 + KS - 2) / (KS - 1);
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            __builtin_amdgcn_sched_barrier(0);
+            if (ks == 0) score_product_from<PART, DP>(dp, delta, gr[0], vf[0], part_ks);
+            else score_product_own<PART, DP>(dp, gr[ks], vf[ks], ks, part_ks);
+            __builtin_amdgcn_sched_barrier(0);
+            if (ks >= 1) {
+#pragma unroll
+                for (int r = (ks - 1) * EACH; r < min(16, ks * EACH); ++r) {
+                    if (EXACT) {
+                        float hi, lo;
+                        to_base2(lse[r], hi, lo);
+                        pr[r] = kappa.exp2(s[r], hi, lo);
+                    } else {
+                        pr[r] = __builtin_amdgcn_exp2f(fmaf(s[r], kappa.hi, -lse[r]));
+                    }
+                }
+            }
+            if (ks == KS / 2) wait_lds();           // the stage's last reads
+            if (ks == KS / 2) loader.part(0, Q, G, t2.a0, q);
+            if (ks == KS - 2) loader.part(1, Q, G, t2.a0, q);
+        }
+        asm volatile("" : "+v"(pr));            // there, beside the products
+        __builtin_amdgcn_sched_barrier(0);
+        if (t0.a0 < k0 + OWN - 1 + t0.shift || t0.a0 + 32 > p.c) {       // some pair of the sub-tile is masked
+            const int lane_first = key_own + t0.shift - t0.a0, rows = p.c - t0.a0;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) pr[r] = reg_row(r, h) >= lane_first && reg_row(r, h) < rows ? pr[r] : 0.f;
+        }
+        if (EXACT) look_at(z, s);
+        bf16x8 wp[2][3], wd[2][3];
+        as_operand<EXACT>(pr, 0, wp[0]);
+        // dV over the first 16 rows, dK over them, dV and dK over the other 16
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int t = TERMS - 1; t >= 0; --t)          // smallest terms first
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (i % 2 == 0) accv[mb] = mfma(gt[4 * (i / 2) + mb], wp[i / 2][t], accv[mb]);
+                    else acck[mb] = mfma(qt[4 * (i / 2) + mb], wd[i / 2][t], acck[mb]);
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (t != TERMS - 1) continue;
+                    // beside each of the first rounds something else
+                    if (i == 0 && mb == 1) {
+                        asm volatile("" : "+v"(dp));
+#pragma unroll
+                        for (int r = 0; r < 8; ++r) ds[r] = pr[r] * dp[r];
+                        as_operand<EXACT>(ds, 0, wd[0]);
+                    }
+                    if (i == 0 && mb == MB - 1) as_operand<EXACT>(pr, 1, wp[1]);
+                    if (i == 1 && mb == 0) loader.part(2, Q, G, t2.a0, q);
+                    if (i == 1 && mb == 1) loader.part(3, Q, G, t2.a0, q);
+                    if (i == 1 && mb == MB - 1) {
+#pragma unroll
+                        for (int r = 8; r < 16; ++r) ds[r] = pr[r] * dp[r];
+                        as_operand<EXACT>(ds, 1, wd[1]);
+                    }
+                    if (i == 2 && mb == 0) load_stats(t2, stage);
+                    if (i == 3 && mb == 0) {
+                        wait_all_but<LOADS>();
+                        read_next(stage ^ 1);
+                    }
+                }
+        __builtin_amdgcn_sched_barrier(0);
+        t0 = t1;
+        t1 = t2;
     }
+    wait_all_but<0>();
 
-    constexpr int HALF = PARTIAL_BYTES<DP>;
-    static_assert(2 * HALF <= 4 * GROUP_BYTES<DP>, "partial results");
-    float4 old_v[blocks_of(DP)], old_k[blocks_of(DP)];
-    load_old<DP>(old_v, p.dv + row, d, !p.fresh && key_own < p.c, ln);
-    load_old<DP>(old_k, p.dk + row, d, !p.fresh && key_own < p.c, ln);
+    constexpr int HALF = PARTIAL_BYTES<DP, WAVES>;
+    static_assert(2 * HALF <= WAVES * 2 * STAGE_BYTES<DP>, "partial results");
+    float4 old_v[MB], old_k[MB];
+    load_old<DP, WAVES>(old_v, p.dv + row, d, !p.fresh && key_own < p.c, ln);
+    load_old<DP, WAVES>(old_k, p.dk + row, d, !p.fresh && key_own < p.c, ln);
     __syncthreads();
     put_partial<DP>(lds, accv, ln);
     put_partial<DP>(lds + HALF, acck, ln);
     if (EXACT) put_odd(masks, key_own < p.c && odd_sum(z, acck), ln.wave, ln.lane);
     __syncthreads();
-    const uint32_t odd_rows = EXACT ? take_odd(masks) : 0;
+    const uint32_t odd_rows = EXACT ? take_odd<WAVES>(masks) : 0;
     if (key_own < p.c && !((odd_rows >> n) & 1)) {
         add_rows<DP>(p.dv + row, old_v, lds, 1.f, d, ln);
-        add_rows<DP>(p.dk + row, old_k, lds + HALF, p.scale, d, ln);
+        add_rows<DP>(p.dk + row, old_k, lds + HALF, -p.scale, d, ln);
     }
     if (EXACT)
         each_row<WAVES>(odd_rows, ln.wave, [&](const StepArgs& again, int i) { dkdv_row<__hip_bfloat16>(again, b, kvh, dev_i, k0 + i, 0, d, ln.lane); });
@@ -552,24 +961,29 @@ __device__ inline void bwd_dkdv(const StepArgs& p, int n_tiles, int linear, char
 // Both in one launch, the two sequences of n_dkdv key-owning and n_dq query-owning workgroups
 // evenly interleaved (each heaviest first): they share nothing but the inputs.
 template <int DP, bool PART, bool EXACT>
-__global__ void __launch_bounds__(64 * WAVES, DP <= 64 ? 2 : 1)
+__global__ void __launch_bounds__(64 * BWD_WAVES, DP <= 64 ? 2 : 1)
 bwd_split_kernel(StepArgs p, int n_tiles, int n_dkdv, int n_dq) {
-    __shared__ __attribute__((aligned(1024))) char lds[4 * GROUP_BYTES<DP>];
-    __shared__ float stats[2 * 3 * GROUP];
-    __shared__ uint32_t masks[WAVES];
+    __shared__ __attribute__((aligned(1024))) char lds[BWD_WAVES * 2 * STAGE_BYTES<DP> + 2 * SUB_BYTES<DP>];
+    __shared__ __attribute__((aligned(1024))) char stats[BWD_WAVES * 2 * STAT_BYTES];
+    __shared__ uint32_t masks[BWD_WAVES];
     const int total = n_dkdv + n_dq, before = (int)((int64_t)blockIdx.x * n_dkdv / total);
     const bool keys = (int)(((int64_t)blockIdx.x + 1) * n_dkdv / total) > before;
     if (keys) bwd_dkdv<DP, PART, EXACT>(p, n_tiles, before, lds, stats, masks);
-    else bwd_dq<DP, PART, EXACT>(p, n_tiles, (int)blockIdx.x - before, lds, masks);
+    else bwd_dq<DP, PART, EXACT>(p, n_tiles, (int)blockIdx.x - before, lds, stats, masks);
 }
 
-enum Pass { FWD_EXACT, BWD_EXACT, BWD };
+enum Pass { FWD, FWD_EXACT, BWD_EXACT, BWD };
 template <int DP, bool PART>
 hipError_t run(const StepArgs& a, Pass pass, hipStream_t st) {
     const int n_tiles = (a.c + OWN - 1) / OWN;
     const int n_dkdv = n_tiles * a.n_kv * a.B * a.H_kv, n_dq = n_tiles * a.n_q * a.B * a.H;
-    const dim3 grid((unsigned)(pass == FWD_EXACT ? n_dq : n_dkdv + n_dq)), block(64 * WAVES);
-    if (pass == FWD_EXACT) hipLaunchKernelGGL((fwd_split_kernel<DP, PART>), grid, block, 0, st, a, n_tiles);
+    const bool forward = pass == FWD || pass == FWD_EXACT;
+    const dim3 grid((unsigned)(forward ? n_dq : n_dkdv + n_dq)), block(64 * (forward ? FWD_WAVES : BWD_WAVES));
+    if (pass == FWD && a.q_pos) {           // (d is 64 or 128: the other forms only exist for these)
+        if constexpr ((DP == 64 || DP == 128) && !PART)
+            hipLaunchKernelGGL((fwd_split_kernel<DP, PART, false, true>), grid, block, 0, st, a, n_tiles);
+    } else if (pass == FWD) hipLaunchKernelGGL((fwd_split_kernel<DP, PART, false>), grid, block, 0, st, a, n_tiles);
+    else if (pass == FWD_EXACT) hipLaunchKernelGGL((fwd_split_kernel<DP, PART, true>), grid, block, 0, st, a, n_tiles);
     else if (pass == BWD_EXACT) hipLaunchKernelGGL((bwd_split_kernel<DP, PART, true>), grid, block, 0, st, a, n_tiles, n_dkdv, n_dq);
     else hipLaunchKernelGGL((bwd_split_kernel<DP, PART, false>), grid, block, 0, st, a, n_tiles, n_dkdv, n_dq);
     return hipGetLastError();
@@ -586,30 +1000,46 @@ hipError_t run(const StepArgs& a, Pass pass, hipStream_t st) {
 
 }  // namespace
 
-// (of shapes that the 128-row matrix-core kernels take.)  Measured against those, us per backward step,
-// here / there.  Triangular, d 128, 64 key tiles: 16 heads of 512 rows 25.5 / 27.7, 64 heads on 8 of 1024
-// 188 / 212, 32 on 4 of 2048 308 / 396, on 2 of 4096 1138 / 1514, on one of 8192 4555 / 6093; 128 key tiles:
-// 54.3 / 41.6, 32 on 8 of 2048 293 / 214, on 4 of 4096 1048 / 796, on 2 of 8192 4065 / 3174.  Full blocks have
-// twice the work, 32 key tiles: 2 heads of 2048 rows 40 / 61, 32 on 8 of 512 66.0 / 64.7, on 4 of 1024 210 /
-// 238, on 2 of 2048 823 / 865, on one of 4096 3292 / 3376; 64: 16 heads of 512 30.3 / 27.5, 32 on 8 of 1024
-// 178 / 142, on one of 8192 10543 / 7427.  d 64 alike (32 on 4, full, 32 key tiles 129 / 216, 64 335 / 378).
+// (of shapes that the 128-row matrix-core kernels take.)  128-row kernels / these, us, d 128.
+// Forward, by 128-row tiles of all queries: up to 64 always: 2 heads of 256 rows 11 / 8.4, one of 4096 61 / 22
+// (full 61 / 24), ring of 4 x 1024, 2 heads 65 / 26.  128: triangular 32 heads of 512 16 / 15, 8 of 2048 36 / 23;
+// full 32 of 512 15.5 / 17.2, 8 of 2048 35.1 / 32.5, ring of 4 x 128, 32 heads, contiguous 15.1 / 15.4.  256:
+// triangular 16 heads of 2048 39 / 42, 4 of 8192 122 / 108, ring of 4 x 1024, 8 heads 66.7 / 68.3, of
+// 4 x 2048, 4 heads 121 / 112, full 8 of 4096 78 / 107; d 64: ring of 4 x 1024, 8 heads 49.7 / 45.9.  A single
+// block of 128 rows is as well off in one 128-row tile up to 112 columns (d 64 7.9 / 8.3, d 128 10 / 8.5).
+bool fwd_split_wanted(const StepArgs& a) {
+    const int64_t tiles = (int64_t)((a.c + 127) / 128) * a.B * a.n_q * a.H, walk = (int64_t)a.c * a.n_kv;
+    if (a.d > TD || (walk <= 128 && a.d <= 112)) return false;
+    if (tiles <= 64) return true;
+    if (tiles <= 128) return walk >= 1024 || a.layout == SA_STRIPED;
+    return tiles <= 256 && uneven(a) && walk >= (a.d <= 112 ? 4096 : 8192);
+}
+hipError_t launch_fwd_split(const StepArgs& a, hipStream_t st) { return run(a, FWD, st); }
+// Backward step, by 128-row tiles of all keys: up to 64 always: 16 heads of 512 rows 27 / 19.5 (full 27 / 22), one of
+// 8192 201 / 88 (207 / 154), 32 heads on 8 of 1024 115 / 62 (144 / 106), on one of 8192 in rings alike.  128,
+// triangular: 16 heads of 1024 41.5 / 44.0, 8 of 2048 65 / 59, 2 of 8192 211 / 166, 32 on 8 of 2048 234 / 194,
+// ring of 4 x 256, 16 heads 44 / 49, of 4 x 512, 8 heads 69 / 66; full 2 of 8192 250 / 299.  Up to 64 columns two
+// workgroups fit a compute unit: 128 tiles, 32 heads of 512 19.0 / 17.3, 2 of 8192 140 / 89; 256: 32 of 1024
+// 39.4 / 39.5, 8 of 4096 93 / 90, ring of 4 x 1024, 32 on 8 398 / 333, but 32 on 4 of 8192 (2048 query tiles) 1255 / 1523.
 bool bwd_split_wanted(const StepArgs& a) {
-    return a.d <= TD && (int64_t)((a.c + 127) / 128) * a.B * a.n_kv * a.H_kv <= (uneven(a) ? 64 : 32);
+    const int64_t rows = (int64_t)((a.c + 127) / 128) * a.B, keys = rows * a.n_kv * a.H_kv, queries = rows * a.n_q * a.H;
+    if (a.d > TD) return false;
+    if (keys <= 64) return true;
+    if (!uneven(a)) return false;
+    if (a.d <= 64) return keys <= 256 && queries <= 1024;
+    return keys <= 128 && (int64_t)a.c * a.n_q * (a.H / a.H_kv) >= 2048;
 }
 hipError_t launch_bwd_split(const StepArgs& a, hipStream_t st) { return run(a, BWD, st); }
 
 // bf16 blocks shorter than a 128-row tile, probabilities and dS in fp32 precision.  (Tile loads
 // address a group of 128 rows with 32-bit byte offsets.)  Against the fp32 instruction on widened
-// operands (f32_step.hip), us: whole ring, 8 x 96 tokens, 32 heads, d 64, forward 51 / 99, backward
-// 78 / 215; 4 x 120 tokens, 64 heads, d 128: 69 / 112 and 141 / 342; one backward step 12 / 15 and
-// 22 / 46.  A single forward block gains while few workgroups share the memory system: 2 heads of
-// 64 tokens, d 128, 8.4 / 15.4, 16 heads of 120 tokens (64 workgroups) 12.6 / 17.3, but 96
-// workgroups at d 64 12.6 / 10.9, 256 at d 128 21 / 18.  Error against 64 bits (2-norm, 16 x 127
-// tokens, d 128): O 2.2e-7 -> 1.6e-7, dQ 3.7e-7 -> 3.2e-7, dK 6.1e-7 -> 4.3e-7, dV 6.0e-7 -> 4.1e-7.
-bool short_exact_wanted(const StepArgs& a, int dtype, bool backward) {
+// operands (f32_step.hip), us: forward step, d 128, 4 heads of 64 tokens 15.7 / 7.7, 64 of 96 17.1 / 8.3, 256 of
+// 120 38.9 / 25.5, d 64 10.3 / 7.8, 11.1 / 8.0, 20.7 / 14.0, d 32 7.9 / 7.8, 8.0 / 7.8, 13.0 / 13.2 (7.7 is
+// what a launch takes).  Error against 64 bits (2-norm, 16 x 127 tokens, d 128): O 2.2e-7 -> 1.6e-7, dQ
+// 3.7e-7 -> 3.2e-7, dK 6.1e-7 -> 4.3e-7, dV 6.0e-7 -> 4.1e-7.
+bool short_exact_wanted(const StepArgs& a, int dtype) {
     const int64_t widest = a.stride_s > a.kv_stride_s ? a.stride_s : a.kv_stride_s;
-    if (dtype != SA_BF16 || a.d % 4 || a.d > TD || a.c >= GROUP || GROUP * 2 * widest + 2 * a.d >= (int64_t(1) << 31)) return false;
-    return backward || a.n_kv > 1 || (int64_t)((a.c + OWN - 1) / OWN) * a.n_q * a.B * a.H <= 64;
+    return dtype == SA_BF16 && a.d % 4 == 0 && a.d <= TD && a.c < 128 && 128 * 2 * widest + 2 * a.d < (int64_t(1) << 31);
 }
 hipError_t launch_short_exact(const StepArgs& a, bool backward, hipStream_t st) {
     return run(a, backward ? BWD_EXACT : FWD_EXACT, st);
