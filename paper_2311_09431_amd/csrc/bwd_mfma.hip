@@ -721,22 +721,21 @@ bwd_dkdv_mfma_kernel(StepArgs p, int n_tiles) {
     __shared__ __attribute__((aligned(16))) float stat[KV_STAT_FLOATS];
     bwd_dkdv<WALK, RAGGED, DP, PART>(p, n_tiles, (int)blockIdx.x, lds0, lds1, lds2, lds3, stat);
 }
-// Both kinds of workgroups in one launch, the two sequences of n_dkdv and n_dq evenly interleaved
-// (each heaviest first; above 512 of a kind by groups of heads, see decode_block): where the key-owning ones do not fill the chip, or fill it once and last
+// Both kinds of workgroups in one launch (each sequence heaviest first; above 512 of a kind by groups of
+// heads, see decode_block): where the key-owning ones do not fill the chip, or fill it once and last
 // as long as the heaviest, the query-owning ones run beside and behind them instead of after.
 // One workgroup per compute unit (the key-owning side's registers).
 template <bool RAGGED, int DP, bool PART>
 __global__ void __launch_bounds__(256, 1)
-bwd_both_mfma_kernel(StepArgs p, int n_tiles, int n_dkdv, int n_dq) {
+bwd_both_mfma_kernel(StepArgs p, int n_tiles, BothKinds kinds) {
     __shared__ __attribute__((aligned(1024))) char lds0[tile_bytes(DP) * halves_of(DP)];
     __shared__ __attribute__((aligned(1024))) char lds1[tile_bytes(DP) * halves_of(DP)];
     __shared__ __attribute__((aligned(1024))) char lds2[tile_bytes(DP) * halves_of(DP)];
     __shared__ __attribute__((aligned(1024))) char lds3[tile_bytes(DP) * halves_of(DP)];
     __shared__ __attribute__((aligned(16))) float stat[KV_STAT_FLOATS];
-    const int total = n_dkdv + n_dq, before = (int)((int64_t)blockIdx.x * n_dkdv / total);
-    const bool keys = (int)(((int64_t)blockIdx.x + 1) * n_dkdv / total) > before;
-    if (keys) bwd_dkdv<WALK_RING, RAGGED, DP, PART>(p, n_tiles, before, lds0, lds1, lds2, lds3, stat);
-    else bwd_dq<RAGGED, WALK_RING, DP, PART>(p, n_tiles, (int)blockIdx.x - before, lds0, lds1, lds2, lds3);
+    int linear = (int)blockIdx.x;
+    if (owns_keys(kinds, linear)) bwd_dkdv<WALK_RING, RAGGED, DP, PART>(p, n_tiles, linear, lds0, lds1, lds2, lds3, stat);
+    else bwd_dq<RAGGED, WALK_RING, DP, PART>(p, n_tiles, linear, lds0, lds1, lds2, lds3);
 }
 
 }  // namespace
@@ -784,9 +783,11 @@ void launch_dkdv(const StepArgs& a, hipStream_t st, int n_tiles) {
 template <int DP, bool PART>
 void launch_both(const StepArgs& a, hipStream_t st, int n_tiles) {
     const int n_dkdv = n_tiles * a.n_kv * a.B * a.H_kv * halves_of(DP), n_dq = n_tiles * a.n_q * a.B * a.H;
+    // (a group's long key walks all at once are no gain: 32 heads on 8 of 4096 rows 486 us, first 501)
+    const BothKinds kinds = both_kinds(a, n_dkdv, n_dq, a.H == a.H_kv ? 1.45 : 0.);
     const dim3 grid((unsigned)(n_dkdv + n_dq)), block(256);
-    if (a.c % BM) hipLaunchKernelGGL((bwd_both_mfma_kernel<true, DP, PART>), grid, block, 0, st, a, n_tiles, n_dkdv, n_dq);
-    else hipLaunchKernelGGL((bwd_both_mfma_kernel<false, DP, PART>), grid, block, 0, st, a, n_tiles, n_dkdv, n_dq);
+    if (a.c % BM) hipLaunchKernelGGL((bwd_both_mfma_kernel<true, DP, PART>), grid, block, 0, st, a, n_tiles, kinds);
+    else hipLaunchKernelGGL((bwd_both_mfma_kernel<false, DP, PART>), grid, block, 0, st, a, n_tiles, kinds);
 }
 // Both kinds of workgroups in one launch.  Measured per backward step (d 128, one launch against
 // two, us): uneven work up to one key-owning workgroup per compute unit: 2048 x 2048 triangular,

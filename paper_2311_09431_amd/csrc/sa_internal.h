@@ -89,6 +89,35 @@ struct StepArgs {
 // several query devices (a key shard is seen by the devices from its own on).
 inline bool uneven(const StepArgs& a) { return a.layout == SA_STRIPED || a.n_q > 1 || a.q_dev == a.kv_dev; }
 
+// Order of a backward launch of n_keys key-owning and n_queries query-owning workgroups, each sequence
+// heaviest first: `first` key-owning ones, whose walks are longer than the longest query-owning one, then the
+// rest of both evenly interleaved, in units of 8 workgroups where both numbers allow: consecutive
+// workgroups go round-robin to the 8 XCDs, and one by one equal numbers of both kinds left each kind
+// four of them (2 heads of 4096 rows, full block, split kernels 81 -> 66 us; 16 of 2048, triangular, 128-row
+// kernels 87 -> 83).  All of an even launch's key-owning walks are longer (`ratio` times, times the group);
+// of an uneven one, whose walks shrink evenly to almost nothing, those before that point are.  ratio 0: both
+// kinds from the start.
+struct BothKinds { int n_keys, first, unit, rest, total; };
+inline BothKinds both_kinds(const StepArgs& a, int64_t n_keys, int64_t n_queries, double ratio) {
+    BothKinds b;
+    const double longer = ratio * (a.H / a.H_kv);
+    b.n_keys = (int)n_keys;
+    b.first = !uneven(a) ? (int)n_keys : longer > 1. ? (int)(n_keys * (1. - 1. / longer)) / 8 * 8 : 0;
+    b.unit = n_keys % 8 || n_queries % 8 ? 1 : 8;
+    b.rest = (int)(n_keys - b.first) / b.unit;
+    b.total = b.rest + (int)n_queries / b.unit;
+    return b;
+}
+// the kind of workgroup `linear` and its place among those of its kind
+__device__ inline bool owns_keys(const BothKinds& b, int& linear) {
+    if (linear < b.first) return true;
+    const int u = (linear - b.first) / b.unit, at = linear - b.first - u * b.unit;
+    const int before = (int)((int64_t)u * b.rest / b.total);
+    const bool keys = (int)(((int64_t)u + 1) * b.rest / b.total) > before;
+    linear = keys ? b.first + before * b.unit + at : (u - before) * b.unit + at;
+    return keys;
+}
+
 // fp32 precision: 128-row workgroups would leave compute units idle, and the streamed rows are split
 // over the wavefronts instead.  In the backward a key-owning workgroup walks the queries of its whole
 // group of heads, so with few key/value heads it is their number that counts.  One step, 32 query

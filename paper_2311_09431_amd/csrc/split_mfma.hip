@@ -958,18 +958,16 @@ __device__ inline void bwd_dkdv(const StepArgs& p, int n_tiles, int linear, char
         each_row<WAVES>(odd_rows, ln.wave, [&](const StepArgs& again, int i) { dkdv_row<__hip_bfloat16>(again, b, kvh, dev_i, k0 + i, 0, d, ln.lane); });
 }
 
-// Both in one launch, the two sequences of n_dkdv key-owning and n_dq query-owning workgroups
-// evenly interleaved (each heaviest first): they share nothing but the inputs.
+// Both in one launch (they share nothing but the inputs).
 template <int DP, bool PART, bool EXACT>
 __global__ void __launch_bounds__(64 * BWD_WAVES, DP <= 64 ? 2 : 1)
-bwd_split_kernel(StepArgs p, int n_tiles, int n_dkdv, int n_dq) {
+bwd_split_kernel(StepArgs p, int n_tiles, BothKinds kinds) {
     __shared__ __attribute__((aligned(1024))) char lds[BWD_WAVES * 2 * STAGE_BYTES<DP> + 2 * SUB_BYTES<DP>];
     __shared__ __attribute__((aligned(1024))) char stats[BWD_WAVES * 2 * STAT_BYTES];
     __shared__ uint32_t masks[BWD_WAVES];
-    const int total = n_dkdv + n_dq, before = (int)((int64_t)blockIdx.x * n_dkdv / total);
-    const bool keys = (int)(((int64_t)blockIdx.x + 1) * n_dkdv / total) > before;
-    if (keys) bwd_dkdv<DP, PART, EXACT>(p, n_tiles, before, lds, stats, masks);
-    else bwd_dq<DP, PART, EXACT>(p, n_tiles, (int)blockIdx.x - before, lds, stats, masks);
+    int linear = (int)blockIdx.x;
+    if (owns_keys(kinds, linear)) bwd_dkdv<DP, PART, EXACT>(p, n_tiles, linear, lds, stats, masks);
+    else bwd_dq<DP, PART, EXACT>(p, n_tiles, linear, lds, stats, masks);
 }
 
 enum Pass { FWD, FWD_EXACT, BWD_EXACT, BWD };
@@ -978,14 +976,15 @@ hipError_t run(const StepArgs& a, Pass pass, hipStream_t st) {
     const int n_tiles = (a.c + OWN - 1) / OWN;
     const int n_dkdv = n_tiles * a.n_kv * a.B * a.H_kv, n_dq = n_tiles * a.n_q * a.B * a.H;
     const bool forward = pass == FWD || pass == FWD_EXACT;
+    const BothKinds kinds = both_kinds(a, n_dkdv, n_dq, 1.25);
     const dim3 grid((unsigned)(forward ? n_dq : n_dkdv + n_dq)), block(64 * (forward ? FWD_WAVES : BWD_WAVES));
     if (pass == FWD && a.q_pos) {           // (d is 64 or 128: the other forms only exist for these)
         if constexpr ((DP == 64 || DP == 128) && !PART)
             hipLaunchKernelGGL((fwd_split_kernel<DP, PART, false, true>), grid, block, 0, st, a, n_tiles);
     } else if (pass == FWD) hipLaunchKernelGGL((fwd_split_kernel<DP, PART, false>), grid, block, 0, st, a, n_tiles);
     else if (pass == FWD_EXACT) hipLaunchKernelGGL((fwd_split_kernel<DP, PART, true>), grid, block, 0, st, a, n_tiles);
-    else if (pass == BWD_EXACT) hipLaunchKernelGGL((bwd_split_kernel<DP, PART, true>), grid, block, 0, st, a, n_tiles, n_dkdv, n_dq);
-    else hipLaunchKernelGGL((bwd_split_kernel<DP, PART, false>), grid, block, 0, st, a, n_tiles, n_dkdv, n_dq);
+    else if (pass == BWD_EXACT) hipLaunchKernelGGL((bwd_split_kernel<DP, PART, true>), grid, block, 0, st, a, n_tiles, kinds);
+    else hipLaunchKernelGGL((bwd_split_kernel<DP, PART, false>), grid, block, 0, st, a, n_tiles, kinds);
     return hipGetLastError();
 }
 template <int DP>
@@ -1002,7 +1001,7 @@ hipError_t run(const StepArgs& a, Pass pass, hipStream_t st) {
 
 // (of shapes that the 128-row matrix-core kernels take.)  128-row kernels / these, us, d 128.
 // Forward, by 128-row tiles of all queries: up to 64 always: 2 heads of 256 rows 11 / 8.4, one of 4096 61 / 22
-// (full 61 / 24), ring of 4 x 1024, 2 heads 65 / 26.  128: triangular 32 heads of 512 16 / 15, 8 of 2048 36 / 23;
+// (full 61 / 24), ring of 4 x 1024, 2 heads 65 / 26.  128: triangular 64 heads of 200 12.1 / 13.0, 32 of 512 16 / 15, 8 of 2048 36 / 23;
 // full 32 of 512 15.5 / 17.2, 8 of 2048 35.1 / 32.5, ring of 4 x 128, 32 heads, contiguous 15.1 / 15.4.  256:
 // triangular 16 heads of 2048 39 / 42, 4 of 8192 122 / 108, ring of 4 x 1024, 8 heads 66.7 / 68.3, of
 // 4 x 2048, 4 heads 121 / 112, full 8 of 4096 78 / 107; d 64: ring of 4 x 1024, 8 heads 49.7 / 45.9.  A single
@@ -1011,23 +1010,25 @@ bool fwd_split_wanted(const StepArgs& a) {
     const int64_t tiles = (int64_t)((a.c + 127) / 128) * a.B * a.n_q * a.H, walk = (int64_t)a.c * a.n_kv;
     if (a.d > TD || (walk <= 128 && a.d <= 112)) return false;
     if (tiles <= 64) return true;
-    if (tiles <= 128) return walk >= 1024 || a.layout == SA_STRIPED;
+    if (tiles <= 128) return walk >= (a.layout == SA_STRIPED ? 512 : 1024);
     return tiles <= 256 && uneven(a) && walk >= (a.d <= 112 ? 4096 : 8192);
 }
 hipError_t launch_fwd_split(const StepArgs& a, hipStream_t st) { return run(a, FWD, st); }
-// Backward step, by 128-row tiles of all keys: up to 64 always: 16 heads of 512 rows 27 / 19.5 (full 27 / 22), one of
-// 8192 201 / 88 (207 / 154), 32 heads on 8 of 1024 115 / 62 (144 / 106), on one of 8192 in rings alike.  128,
-// triangular: 16 heads of 1024 41.5 / 44.0, 8 of 2048 65 / 59, 2 of 8192 211 / 166, 32 on 8 of 2048 234 / 194,
-// ring of 4 x 256, 16 heads 44 / 49, of 4 x 512, 8 heads 69 / 66; full 2 of 8192 250 / 299.  Up to 64 columns two
-// workgroups fit a compute unit: 128 tiles, 32 heads of 512 19.0 / 17.3, 2 of 8192 140 / 89; 256: 32 of 1024
-// 39.4 / 39.5, 8 of 4096 93 / 90, ring of 4 x 1024, 32 on 8 398 / 333, but 32 on 4 of 8192 (2048 query tiles) 1255 / 1523.
+// Backward step, by 128-row tiles of all keys: up to 64 always: 16 heads of 512 rows 27 / 19 (full 27 / 20), one of
+// 8192 201 / 88 (207 / 154), 32 heads on 8 of 1024 115 / 60 (141 / 87), ring of 4 x 1024, 2 heads 112 / 54.  128,
+// triangular: 16 heads of 1024 39.6 / 41.7, 8 of 2048 62 / 54, 2 of 8192 200 / 143, 32 on 8 of 2048 211 / 170,
+// ring of 4 x 256, 16 heads 42 / 48, of 4 x 512, 8 heads 67 / 60; full 2 of 8192 233 / 257, 32 on 8 of 2048 313 /
+// 281; 256: 8 of 4096 137 / 160, 32 on 8 of 4096 500 / 574.  Up to 64 columns two workgroups fit a compute unit: full,
+// 128 tiles, 32 heads of 512 18.5 / 18.1, 2 of 8192 147 / 135, 256: 46.4 / 45.8, 254 / 263; triangular, 256: 32 of
+// 1024 36.1 / 35.9, 8 of 4096 87 / 78, ring of 4 x 1024, 32 on 8 369 / 300, 512: 32 of 2048 94.0 / 93.3, 8 of 8192
+// 288 / 275, but 64 heads of 200 (128 tiles) 11.0 / 13.1.
 bool bwd_split_wanted(const StepArgs& a) {
-    const int64_t rows = (int64_t)((a.c + 127) / 128) * a.B, keys = rows * a.n_kv * a.H_kv, queries = rows * a.n_q * a.H;
+    const int64_t keys = (int64_t)((a.c + 127) / 128) * a.B * a.n_kv * a.H_kv, group = a.H / a.H_kv;
     if (a.d > TD) return false;
+    const int64_t walk = (int64_t)a.c * a.n_q * group;
     if (keys <= 64) return true;
-    if (!uneven(a)) return false;
-    if (a.d <= 64) return keys <= 256 && queries <= 1024;
-    return keys <= 128 && (int64_t)a.c * a.n_q * (a.H / a.H_kv) >= 2048;
+    if (a.d <= 64) return keys <= (uneven(a) ? 512 : 128) && walk >= 4 * keys;
+    return keys <= 128 && (uneven(a) ? walk >= 2048 : group >= 4);
 }
 hipError_t launch_bwd_split(const StepArgs& a, hipStream_t st) { return run(a, BWD, st); }
 
