@@ -698,6 +698,293 @@ __device__ __forceinline__ void bwd_dkdv(const StepArgs& p, int n_tiles, int lin
         }
 }
 
+// Head dimensions above 128, both column halves of dK and dV in one workgroup.  The kernel above forms
+// S and dP once per half: 12 products of d columns a pair where 8 do.  Here dK^T and dV^T of 32
+// keys and 256 columns are the 256 accumulation registers of a wavefront (one per SIMD), the K rows
+// 64 of its vector registers and the V rows WIDE_V_REGS k-steps there, the others in LDS, written and
+// read by their own wavefront alone.  Q and dO come in stages of 32 rows, three in LDS: stage u + 2 is
+// requested when everyone is done with u - 1 and has the whole step u to land, one barrier a step.
+// The walk over blocks is the requests' own, two stages ahead; a step knows only its stage's limit
+// of the element mask, which is far below zero where nothing is masked (64 matrix products a step
+// hide the 16 selects).
+// Bound by the matrix cores at the clock the power limit leaves: 8 instead of 12 products of d a pair,
+// one wavefront per SIMD.  Backward step (with its dQ kernel), 8 heads of 8192 rows, d 256, full block
+// 2210 -> 1761 us, triangular 1282 -> 1014; 12500 rows 6276 -> 5363, 2905 -> 2212; 16 heads of 4096 1166 ->
+// 944, 708 -> 562.  One or two k-steps of V in registers measured the same.
+constexpr int WIDE_ROWS = 32, WIDE_PART = WIDE_ROWS * 256;         // one 128-column half of a stage's Q or dO
+constexpr int WIDE_STAGE = 4 * WIDE_PART;                          // Q, Q, dO, dO
+constexpr int WIDE_V_REGS = 1;                                     // of 16 k-steps: what LDS has no room for
+constexpr int WIDE_V_LDS = (16 - WIDE_V_REGS) * 1024;              // per wavefront
+constexpr int WIDE_NO_MASK = -(1 << 20);
+
+// The accumulators are the accumulation registers themselves, by number: dV^T block b is a[16 b : 16 b + 15],
+// dK^T block b 128 further on.  As variables of the compiler, tied to that file or not, they were carried
+// to vector registers and scratch memory and back around every loop (444 spilled registers).  Each
+// statement declares the whole file as overwritten, so that nothing of the compiler's lives there
+// across one; it has no reason to use the file at all while its own values fit the 256 vector
+// registers, which the kernel's assembly shows: outside of these statements no instruction names one.
+#ifdef __HIP_DEVICE_COMPILE__
+#define ACC_TEN(b) "a" #b "0", "a" #b "1", "a" #b "2", "a" #b "3", "a" #b "4", "a" #b "5", "a" #b "6", "a" #b "7", "a" #b "8", "a" #b "9"
+#define ACC_FILE                                                                                                   \
+    "a0", "a1", "a2", "a3", "a4", "a5", "a6", "a7", "a8", "a9", ACC_TEN(1), ACC_TEN(2), ACC_TEN(3), ACC_TEN(4), ACC_TEN(5),    \
+        ACC_TEN(6), ACC_TEN(7), ACC_TEN(8), ACC_TEN(9), ACC_TEN(10), ACC_TEN(11), ACC_TEN(12), ACC_TEN(13), ACC_TEN(14), ACC_TEN(15), \
+        ACC_TEN(16), ACC_TEN(17), ACC_TEN(18), ACC_TEN(19), ACC_TEN(20), ACC_TEN(21), ACC_TEN(22), ACC_TEN(23), ACC_TEN(24),        \
+        "a250", "a251", "a252", "a253", "a254", "a255"
+#else
+#define ACC_FILE        // the host pass knows none of these names
+#endif
+__device__ __forceinline__ void acc_zero(int i) { asm volatile("v_accvgpr_write_b32 a[%0], 0" : : "n"(i) : ACC_FILE); }
+__device__ __forceinline__ float acc_read(int i) {
+    float x;
+    asm volatile("v_accvgpr_read_b32 %0, a[%1]" : "=v"(x) : "n"(i) : ACC_FILE);
+    return x;
+}
+// block += a b.  The two wait states stand in every one: b is packed by vector instructions, which the
+// compiler moves up to the very product that reads it, and its hazard recogniser does not see this one
+// (without them single columns of dK were wrong now and then).  They pass while the product before runs.
+__device__ __forceinline__ void acc_mfma(int block, bf16x8 a, bf16x8 b) {
+    asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 a[%2:%3], %0, %1, a[%2:%3]"
+                 : : "v"(a), "v"(b), "n"(16 * block), "n"(16 * block + 15) : ACC_FILE);
+}
+
+// products of one step, as dkdv_step.  arow: row reads in the next stage, tr0 / tr1: transposing reads
+// in the present one.
+template <bool NEXT>
+__device__ __forceinline__ void wide_step(f32x16& s_cur, f32x16& dp_cur, f32x16& s_next, f32x16& dp_next,
+                                 const bf16x8 (&kf)[16],
+                                 const bf16x8 (&vf)[WIDE_V_REGS], const char* v_own, float kappa, const char* lds,
+                                 const uint32_t (&arow)[8], const uint32_t (&tr0)[4], const uint32_t (&tr1)[4],
+                                 const float* stat_cur, const float* stat_next, int h, int mask_lim) {
+    bf16x8 qa[16], ga[16], va[16], qt[16], gt[16], pb[2], dsb[2];
+    if (NEXT) load_neg_delta(dp_next, stat_next + WIDE_ROWS, h);
+    auto fetch = [&](int ks) {
+        if (!NEXT) return;
+        const char* rows = lds + (ks / 8) * WIDE_PART;
+        qa[ks] = dt_read_row(rows, arow[ks % 8]);
+        ga[ks] = dt_read_row(rows + 2 * WIDE_PART, arow[ks % 8]);
+        va[ks] = ks < WIDE_V_REGS ? vf[ks % WIDE_V_REGS] : dt_read_row(v_own, (ks - WIDE_V_REGS) * 1024);
+    };
+    // i = 8 (group of 16 rows) + column block
+    auto fetch_t = [&](int i) {
+        const char* rows = lds + (i % 8 / 4) * WIDE_PART + (i / 8) * 16 * 256;
+        gt[i] = dt_read_tr(rows + 2 * WIDE_PART, tr0[i % 4], tr1[i % 4]);
+        qt[i] = dt_read_tr(rows, tr0[i % 4], tr1[i % 4]);
+    };
+    float2 lv[8];
+    auto fetch_stat = [&](int i) {
+        lv[i] = *reinterpret_cast<const float2*>(stat_cur + 8 * (i / 2) + 4 * h + 2 * (i % 2));
+    };
+    constexpr int AHEAD = 2, TAHEAD = 3;
+    fetch_stat(0);
+#pragma unroll
+    for (int i = 0; i < AHEAD; ++i) fetch(i);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        __builtin_amdgcn_sched_barrier(0);          // slices stay in program order
+        if (i + AHEAD < 16) fetch(i + AHEAD);
+        if (i % 2 == 0 && i < 14) fetch_stat(i / 2 + 1);
+        if (i >= 16 - TAHEAD) fetch_t(i - (16 - TAHEAD));
+        if (NEXT) {
+            if (i == 0) mfma_vgpr_first(s_next, qa[i], kf[i], false);
+            else mfma_vgpr_acc(s_next, qa[i], kf[i], false);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        const float lr = i % 2 ? lv[i / 2].y : lv[i / 2].x;
+        float pr = __builtin_amdgcn_exp2f(fmaf(s_cur[i], kappa, -lr));
+        if (8 * (i / 4) + (i % 4) < mask_lim) pr = 0.f;
+        pb[i / 8][i % 8] = (__bf16)pr;
+        dsb[i / 8][i % 8] = (__bf16)(pr * dp_cur[i]);
+        if (NEXT) {
+            __builtin_amdgcn_sched_barrier(0);
+            mfma_vgpr_acc(dp_next, ga[i], va[i], false);
+        }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        if (i + TAHEAD < 16) fetch_t(i + TAHEAD);
+        acc_mfma(i % 8, gt[i], pb[i / 8]);
+        acc_mfma(8 + i % 8, qt[i], dsb[i / 8]);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
+__global__ void __launch_bounds__(256, 1)
+bwd_dkdv_wide_kernel(StepArgs p, int n_tiles) {
+    __shared__ __attribute__((aligned(1024))) char lds[3 * WIDE_STAGE];
+    __shared__ __attribute__((aligned(1024))) char v_lds[4 * WIDE_V_LDS];
+    __shared__ __attribute__((aligned(16))) float stat[3 * 2 * WIDE_ROWS];         // [stage][lse2 | -delta][32]
+    const int tid = threadIdx.x, lane = tid & 63, n = lane & 31, h = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int ktile, bh, dev_rank;
+    decode_block<false>((int)blockIdx.x, n_tiles * p.n_kv, p.B * p.H_kv, ktile, bh);
+    decode_rank(ktile, n_tiles, p.n_kv, p.layout, ktile, dev_rank);
+    const int dev = p.kv_dev + dev_rank;
+    const int b = bh / p.H_kv, kvh = bh - b * p.H_kv;
+    const int64_t kv_base = b * p.kv_stride_b + kvh * p.kv_stride_h + (dev - p.kv_dev) * p.kv_shard;
+    const int d = p.d;
+    const int64_t ss = p.kv_stride_s;
+    const int pitch = 2 * (int)p.stride_s, stage_pitch = WIDE_ROWS * pitch;
+    const int k0 = ktile * BM, key_own = k0 + 32 * wave + n, key = min(key_own, p.c - 1);
+
+    // The requests: query head, query shard and 32-row stage of the next one, as in the kernel above.
+    const int group = p.H / p.H_kv;
+    const int dev0 = p.layout != SA_STRIPED ? max(p.q_dev, dev) : p.q_dev, n_st = (p.c + DT_ROWS - 1) / DT_ROWS * 2;
+    int q_head = 0, q_dev = dev0, t, lim;           // lim: mask limit of stage 0 but for the lane's part
+    dt_rsrc Qr, Gr;
+    const float* stat_src;
+    auto enter_block = [&]() {
+        const int hd = kvh * group + q_head;
+        const bool tri = block_kind(q_dev, dev, p.layout) == MASK_TRI;
+        const int off = block_off(q_dev, dev, p.layout);
+        t = tri ? k0 / WIDE_ROWS : 0;
+        if (tri && p.skip_bq > 0)
+            t = ((k0 / p.skip_bk * p.skip_bk + off) / p.skip_bq) * p.skip_bq / WIDE_ROWS;
+        lim = tri ? k0 + 32 * wave + off : WIDE_NO_MASK;
+        const int64_t base = b * p.stride_b + hd * p.stride_h + (q_dev - p.q_dev) * p.q_shard;
+        const int64_t sbase = b * p.stat_stride_b + hd * p.stat_stride_h + (int64_t)(q_dev - p.q_dev) * p.c;
+        Qr = dt_make_rsrc((const __bf16*)p.q + base, p.c, pitch, d);
+        Gr = dt_make_rsrc((const __bf16*)p.dout + base, p.c, pitch, d);
+        stat_src = ((tid & WIDE_ROWS) ? p.delta : p.lse) + sbase;
+    };
+    enter_block();
+    uint32_t gl[2][2];
+#pragma unroll
+    for (int hh = 0; hh < 2; ++hh)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int r = 8 * wave + 4 * j + (lane >> 4), chunk = (lane & 15) ^ dt_swz(r);
+            gl[hh][j] = 128 * hh + 8 * chunk < d ? r * pitch + 256 * hh + (chunk << 4) : DT_OUT_OF_RANGE;
+        }
+    float rstat;                                    // statistics of the stage requested last
+    int lim_req;                                    // and its limit
+    bool more = true;                               // stages are left to request
+    auto request = [&](int stage) {
+        const int at = t * stage_pitch;
+        char* dst = lds + stage * WIDE_STAGE + 2 * wave * 1024;
+#pragma unroll
+        for (int hh = 0; hh < 2; ++hh)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                dt_load_piece(Qr, at, gl[hh][j], dst + hh * WIDE_PART + j * 1024);
+                dt_load_piece(Gr, at, gl[hh][j], dst + (2 + hh) * WIDE_PART + j * 1024);
+            }
+        const int row = t * WIDE_ROWS + (tid & (WIDE_ROWS - 1));
+        rstat = stat_src[min(row, p.c - 1)];
+        if (row >= p.c) rstat = (tid & WIDE_ROWS) ? 0.f : INFINITY;       // no query: P and dS are exact zeros
+        lim_req = lim == WIDE_NO_MASK ? lim : lim - t * WIDE_ROWS;
+        if (++t == n_st) {
+            if (++q_dev == p.q_dev + p.n_q) {
+                q_dev = dev0;
+                more = ++q_head < group;
+            }
+            if (more) enter_block();
+        }
+    };
+    auto stat_store = [&](int stage) {
+        if (tid < 2 * WIDE_ROWS) stat[stage * 2 * WIDE_ROWS + tid] = rstat * ((tid & WIDE_ROWS) ? -1.f : LOG2E);
+    };
+
+    bf16x8 kf[16], vf[WIDE_V_REGS];
+    char* const v_own = v_lds + wave * WIDE_V_LDS + lane * 16;
+    {
+        bf16x8 v_all[16];
+        load_b_frags<16>(v_all, (const __bf16*)p.v + kv_base + (int64_t)key * ss, h, d);
+#pragma unroll
+        for (int ks = 0; ks < 16; ++ks) {
+            if (ks < WIDE_V_REGS) vf[ks % WIDE_V_REGS] = v_all[ks];
+            else *reinterpret_cast<bf16x8*>(v_own + (ks - WIDE_V_REGS) * 1024) = v_all[ks];
+        }
+    }
+    load_b_frags<16>(kf, (const __bf16*)p.k + kv_base + (int64_t)key * ss, h, d);
+    request(0);
+    const int lim_first = lim_req;
+    stat_store(0);
+    request(1);
+    uint32_t arow[8], tr0[4], tr1[4];
+    dt_row_addrs<256>(arow, n, h);
+    dt_tr_addrs<256>(tr0, tr1, lane);
+    const float kappa = p.scale * LOG2E;
+#pragma unroll
+    for (int r = 0; r < 256; ++r) acc_zero(r);
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+
+    f32x16 s_a, s_b, dp_a, dp_b;
+    load_neg_delta(dp_a, stat + WIDE_ROWS, h);
+#pragma unroll
+    for (int ks = 0; ks < 16; ++ks) {
+        const char* rows = lds + (ks / 8) * WIDE_PART;
+        const bf16x8 qx = dt_read_row(rows, arow[ks % 8]), gx = dt_read_row(rows + 2 * WIDE_PART, arow[ks % 8]);
+        const bf16x8 vx = ks < WIDE_V_REGS ? vf[ks % WIDE_V_REGS] : dt_read_row(v_own, (ks - WIDE_V_REGS) * 1024);
+        if (ks == 0) mfma_vgpr_first(s_a, qx, kf[ks], false);
+        else mfma_vgpr_acc(s_a, qx, kf[ks], false);
+        mfma_vgpr_acc(dp_a, gx, vx, false);
+    }
+    mfma_results_to_valu(s_a, dp_a);
+
+    // stage: of the present step.  The row reads are one stage further on.
+    int stage = 0, ahead = 2, lim_cur = lim_first, lim_next = lim_req;         // ahead: stages requested and not done
+    auto after = [](int x) { return x == 2 ? 0 : x + 1; };
+    auto move = [&](uint32_t (&a)[8], int from) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) a[i] += from == 2 ? -2 * WIDE_STAGE : WIDE_STAGE;
+    };
+    move(arow, 0);
+    auto step = [&](f32x16& s_cur, f32x16& dp_cur, f32x16& s_next, f32x16& dp_next) {
+        const int next = after(stage), free = after(next);
+        stat_store(next);
+        __builtin_amdgcn_s_waitcnt(0);              // the next stage has landed
+        __syncthreads();                            // for everyone; everyone is done with the one before this
+        if (more) {
+            request(free);
+            ++ahead;
+        }
+        wide_step<true>(s_cur, dp_cur, s_next, dp_next, kf, vf, v_own, kappa, lds, arow, tr0, tr1,
+                        stat + stage * 2 * WIDE_ROWS, stat + next * 2 * WIDE_ROWS, h, lim_cur + n - 4 * h);
+        lim_cur = lim_next;
+        lim_next = lim_req;
+        move(arow, next);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            tr0[i] += stage == 2 ? -2 * WIDE_STAGE : WIDE_STAGE;
+            tr1[i] += stage == 2 ? -2 * WIDE_STAGE : WIDE_STAGE;
+        }
+        stage = next;
+        --ahead;
+    };
+    for (;;) {          // every block has an even number of stages
+        step(s_a, dp_a, s_b, dp_b);
+        if (ahead == 1) break;
+        step(s_b, dp_b, s_a, dp_a);
+    }
+    wide_step<false>(s_b, dp_b, s_a, dp_a, kf, vf, v_own, kappa, lds, arow, tr0, tr1,
+                     stat + stage * 2 * WIDE_ROWS, stat, h, lim_cur + n - 4 * h);
+
+    asm volatile("s_nop 15\n\ts_nop 15" : : : ACC_FILE);      // the last products before they are read
+    if (key_own >= p.c) return;
+    float* DK = p.dk + kv_base + (int64_t)key * ss;
+    float* DV = p.dv + kv_base + (int64_t)key * ss;
+#pragma unroll
+    for (int mb = 0; mb < 8; ++mb)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const int col = 32 * mb + 8 * g + 4 * h;
+            if (col >= d) continue;
+            float4 x = make_float4(0.f, 0.f, 0.f, 0.f), y = x;
+            if (!p.fresh) {
+                x = *reinterpret_cast<float4*>(DV + col);
+                y = *reinterpret_cast<float4*>(DK + col);
+            }
+            x.x += acc_read(16 * mb + 4 * g + 0); x.y += acc_read(16 * mb + 4 * g + 1);
+            x.z += acc_read(16 * mb + 4 * g + 2); x.w += acc_read(16 * mb + 4 * g + 3);
+            *reinterpret_cast<float4*>(DV + col) = x;
+            y.x = fmaf(p.scale, acc_read(128 + 16 * mb + 4 * g + 0), y.x); y.y = fmaf(p.scale, acc_read(128 + 16 * mb + 4 * g + 1), y.y);
+            y.z = fmaf(p.scale, acc_read(128 + 16 * mb + 4 * g + 2), y.z); y.w = fmaf(p.scale, acc_read(128 + 16 * mb + 4 * g + 3), y.w);
+            *reinterpret_cast<float4*>(DK + col) = y;
+        }
+}
+
 template <bool RAGGED, int WALK, int DP, bool PART>
 __global__ void __launch_bounds__(256, DP > 128 ? 1 : 2)
 bwd_dq_mfma_kernel(StepArgs p, int n_tiles) {
@@ -813,10 +1100,22 @@ hipError_t launch_bwd_variant(const StepArgs& a, hipStream_t st) {
     else if (full) launch_dq<WALK_FULL, DP, PART>(a, st, n_tiles);
     else launch_dq<WALK_TRI, DP, PART>(a, st, n_tiles);
     if (hipError_t e = hipGetLastError()) return e;
+    if constexpr (DP > 128) {
+        // Up to half a key tile per compute unit the two column halves side by side are faster: a wide workgroup
+        // lasts 4 / 3 as long.  Full block, d 256, us, halves : wide: 128 tiles (8 heads of 2048) 197 : 224, (32
+        // heads on 4 of 4096) 2251 : 2718, 144 278 : 228, 192 280 : 227, 256 315 : 256, 320 475 : 463.  Triangular
+        // blocks of up to 256 tiles went to launch_both (16 heads of 2048 204 : 218, 8 of 4096 342 : 385; above it
+        // 320 tiles 285 : 239).
+        const int64_t tiles = (int64_t)n_tiles * a.n_kv * a.B * a.H_kv;
+        if (tiles > N_CU / 2) {
+            hipLaunchKernelGGL(bwd_dkdv_wide_kernel, dim3((unsigned)tiles), dim3(256), 0, st, a, n_tiles);
+            return hipGetLastError();
+        }
+    }
     // query heads that share a key/value head are blocks of one walk
     if (!one_block || a.H != a.H_kv) launch_dkdv<WALK_RING, DP, PART>(a, st, n_tiles);
     else if (full) launch_dkdv<WALK_FULL, DP, PART>(a, st, n_tiles);
-    else launch_dkdv<WALK_TRI, DP, PART>(a, st, n_tiles);
+    else if constexpr (DP <= 128) launch_dkdv<WALK_TRI, DP, PART>(a, st, n_tiles);      // above: launch_both or wide
     return hipGetLastError();
 }
 }  // namespace
