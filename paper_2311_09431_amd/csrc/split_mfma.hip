@@ -1009,6 +1009,9 @@ hipError_t run(const StepArgs& a, Pass pass, hipStream_t st) {
 bool fwd_split_wanted(const StepArgs& a) {
     const int64_t tiles = (int64_t)((a.c + 127) / 128) * a.B * a.n_q * a.H, walk = (int64_t)a.c * a.n_kv;
     if (a.d > TD || (walk <= 128 && a.d <= 112)) return false;
+    // the query rows come through a descriptor too, which fwd_mfma.hip reads by 64-bit pointers (fwd_mfma_supported
+    // looks at the rows of K and V only)
+    if ((int64_t)(a.c + 127) / 128 * 128 * 2 * a.stride_s + 2 * a.d >= (int64_t(1) << 31)) return false;
     if (tiles <= 64) return true;
     if (tiles <= 128) return walk >= (a.layout == SA_STRIPED ? 512 : 1024);
     return tiles <= 256 && uneven(a) && walk >= (a.d <= 112 ? 4096 : 8192);

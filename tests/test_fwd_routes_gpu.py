@@ -10,6 +10,7 @@ from oracle import striped_attention as orc
 from paper_2311_09431_amd import binding as sa
 from paper_2311_09431_amd import inputs
 from tests import helpers as hp
+from tests import routes
 
 pytestmark = pytest.mark.gpu
 
@@ -77,3 +78,38 @@ def test_fused_rotation_like_rotated_queries(c, H, d, shape_n):
     sa.sa_attn_step_fwd(qr, k, v, o[1], lse[1], 1, 0, 8, sa.STRIPED, shape)
     assert float((o[0] - o[1]).norm() / o[1].norm()) <= 1e-3
     assert hp.max_abs_err(lse[0].cpu().numpy(), lse[1].cpu().numpy()) <= 5e-3
+
+
+@pytest.mark.parametrize("fused", [False, True])
+@pytest.mark.parametrize("c,d,pitch", [(128, 128, 1 << 24), (160, 100, 1 << 23), (8192, 64, (1 << 18) + 8)])
+def test_query_rows_far_apart(c, d, pitch, fused):
+    # Q (and O) narrow views of a wide buffer, K and V packed: 4 GiB and more, or between 2 and 4, from the first to
+    # the last row of a launch small enough for the split kernel, whose offsets have 32 bits.  NaN behind every row.
+    if fused and c % 128 or fused and d not in (64, 128):
+        pytest.skip("no fused rotation at this shape")
+    assert routes.forward(routes.args(c, d, 1, q_dev=0, layout=sa.CONTIGUOUS, stride_s=pitch)) == "128 rows"
+    f32, bf = dict(dtype=torch.float32, device="cuda"), dict(dtype=torch.bfloat16, device="cuda")
+    wide = lambda **kw: torch.empty((c - 1) * pitch + d + 64, **kw).as_strided((1, 1, c, d + 64), (c * pitch, c * pitch, pitch, 1))  # noqa: E731
+    q, k, v = (inputs.gaussian((1, 1, c, d), 20 + i, torch.bfloat16).cuda() for i in range(3))
+    qw, ow = wide(**bf).fill_(float("nan"))[..., :d], wide(**f32)[..., :d]
+    qw.copy_(q)
+    pos = torch.arange(c, dtype=torch.int32, device="cuda") * 3
+    outs = []
+    for x, o in ((qw, ow), (q, torch.empty(1, 1, c, d, **f32))):
+        lse = torch.empty(1, 1, c, **f32)
+        shape = sa.shard_shape(x, c, lse, kv=k)
+        sa.sa_state_init(o, lse, shape)
+        if fused:
+            sa.sa_attn_step_fwd_rope(x, k, v, o, lse, pos, 0, 0, 1, sa.CONTIGUOUS, shape)
+        else:
+            sa.sa_attn_step_fwd(x, k, v, o, lse, 0, 0, 1, sa.CONTIGUOUS, shape)
+        outs.append((o.contiguous(), lse))
+    torch.cuda.synchronize()
+    (o, lse), (o1, lse1) = outs
+    # the packed call's kernel rounds P to bf16 against other references
+    assert float((o - o1).norm()) <= 4e-3 * float(o1.norm())
+    assert hp.max_abs_err(lse.cpu().numpy(), lse1.cpu().numpy()) <= 1e-3
+    if not fused:
+        want_o, want_l = hp.oracle_forward(q, k, v, 1.0 / np.sqrt(d))
+        assert hp.max_abs_err(o.cpu().numpy(), want_o) <= 2e-2
+        assert hp.max_abs_err(lse.cpu().numpy(), want_l) <= 1e-3

@@ -1,0 +1,32 @@
+"""Host-side rules of the dispatch: which calls the kernels that address rows through 32-bit byte offsets
+take (no GPU needed)."""
+import pytest
+
+from paper_2311_09431_amd import binding as sa
+from tests import routes
+
+MOST = 1 << 31          # byte offsets below it
+
+
+def test_ordinary_calls():
+    # (what the strides below are measured against; also that the mirrored struct is the library's)
+    assert routes.forward(routes.args(128, 128, 1)) == "split"
+    assert routes.forward(routes.args(4096, 128, 32)) == "128 rows"
+    assert routes.forward(routes.args(127, 128, 1)) == "short"
+    assert routes.forward(routes.args(128, 132, 1)) == "fp32"
+    assert routes.forward(routes.args(128, 128, 1), sa.F32) == "fp32"
+    assert routes.backward(routes.args(128, 128, 1)) == "split"
+    assert routes.backward(routes.args(4096, 128, 32)) == "128 rows"
+    assert routes.backward(routes.args(127, 128, 1)) == "short"
+    assert routes.forward(routes.args(1024, 128, 2, N=4, layout=sa.CONTIGUOUS)) == "split"
+
+
+@pytest.mark.parametrize("d", [64, 100, 128])
+@pytest.mark.parametrize("c", [128, 160, 8192])
+def test_wide_query_rows_stay_with_the_kernel_that_reads_them_by_pointer(c, d):
+    # 128-row workgroups read Q by 64-bit pointers and take any row stride; the split ones go through a descriptor
+    for pitch in (MOST // 2 // c + 8, MOST // c + 8, MOST // 2 + 8):
+        assert routes.forward(routes.args(c, d, 1, stride_s=pitch)) == "128 rows"
+        assert routes.backward(routes.args(c, d, 1, stride_s=pitch)) == "fp32"
+    # and keys as far apart: neither
+    assert routes.forward(routes.args(c, d, 1, kv_stride_s=MOST // 2 // c + 8)) == "fp32"
