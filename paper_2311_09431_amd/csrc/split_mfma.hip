@@ -997,6 +997,14 @@ hipError_t run(const StepArgs& a, Pass pass, hipStream_t st) {
     return run<128>(a, pass, st);
 }
 
+// Both sides' rows come through descriptors with 32-bit byte offsets (fwd_mfma.hip reads Q by 64-bit pointers, and
+// fwd_mfma_supported looks at the rows of K and V only).  Requests behind a walk's end name up to 32 rows behind the
+// block's last sub-tile: their offsets must not wrap into the matrix.
+bool rows_in_reach(const StepArgs& a) {
+    const int64_t widest = a.stride_s > a.kv_stride_s ? a.stride_s : a.kv_stride_s;
+    return ((int64_t)(a.c + 127) / 128 * 128 + OWN) * 2 * widest + 2 * a.d < (int64_t(1) << 31);
+}
+
 }  // namespace
 
 // (of shapes that the 128-row matrix-core kernels take.)  128-row kernels / these, us, d 128.
@@ -1009,9 +1017,7 @@ hipError_t run(const StepArgs& a, Pass pass, hipStream_t st) {
 bool fwd_split_wanted(const StepArgs& a) {
     const int64_t tiles = (int64_t)((a.c + 127) / 128) * a.B * a.n_q * a.H, walk = (int64_t)a.c * a.n_kv;
     if (a.d > TD || (walk <= 128 && a.d <= 112)) return false;
-    // the query rows come through a descriptor too, which fwd_mfma.hip reads by 64-bit pointers (fwd_mfma_supported
-    // looks at the rows of K and V only)
-    if ((int64_t)(a.c + 127) / 128 * 128 * 2 * a.stride_s + 2 * a.d >= (int64_t(1) << 31)) return false;
+    if (!rows_in_reach(a)) return false;
     if (tiles <= 64) return true;
     if (tiles <= 128) return walk >= (a.layout == SA_STRIPED ? 512 : 1024);
     return tiles <= 256 && uneven(a) && walk >= (a.d <= 112 ? 4096 : 8192);
@@ -1027,7 +1033,7 @@ hipError_t launch_fwd_split(const StepArgs& a, hipStream_t st) { return run(a, F
 // 288 / 275, but 64 heads of 200 (128 tiles) 11.0 / 13.1.
 bool bwd_split_wanted(const StepArgs& a) {
     const int64_t keys = (int64_t)((a.c + 127) / 128) * a.B * a.n_kv * a.H_kv, group = a.H / a.H_kv;
-    if (a.d > TD) return false;
+    if (a.d > TD || !rows_in_reach(a)) return false;
     const int64_t walk = (int64_t)a.c * a.n_q * group;
     if (keys <= 64) return true;
     if (a.d <= 64) return keys <= (uneven(a) ? 512 : 128) && walk >= 4 * keys;
@@ -1035,15 +1041,13 @@ bool bwd_split_wanted(const StepArgs& a) {
 }
 hipError_t launch_bwd_split(const StepArgs& a, hipStream_t st) { return run(a, BWD, st); }
 
-// bf16 blocks shorter than a 128-row tile, probabilities and dS in fp32 precision.  (Tile loads
-// address a group of 128 rows with 32-bit byte offsets.)  Against the fp32 instruction on widened
+// bf16 blocks shorter than a 128-row tile, probabilities and dS in fp32 precision.  Against the fp32 instruction on widened
 // operands (f32_step.hip), us: forward step, d 128, 4 heads of 64 tokens 15.7 / 7.7, 64 of 96 17.1 / 8.3, 256 of
 // 120 38.9 / 25.5, d 64 10.3 / 7.8, 11.1 / 8.0, 20.7 / 14.0, d 32 7.9 / 7.8, 8.0 / 7.8, 13.0 / 13.2 (7.7 is
 // what a launch takes).  Error against 64 bits (2-norm, 16 x 127 tokens, d 128): O 2.2e-7 -> 1.6e-7, dQ
 // 3.7e-7 -> 3.2e-7, dK 6.1e-7 -> 4.3e-7, dV 6.0e-7 -> 4.1e-7.
 bool short_exact_wanted(const StepArgs& a, int dtype) {
-    const int64_t widest = a.stride_s > a.kv_stride_s ? a.stride_s : a.kv_stride_s;
-    return dtype == SA_BF16 && a.d % 4 == 0 && a.d <= TD && a.c < 128 && 128 * 2 * widest + 2 * a.d < (int64_t(1) << 31);
+    return dtype == SA_BF16 && a.d % 4 == 0 && a.d <= TD && a.c < 128 && rows_in_reach(a);
 }
 hipError_t launch_short_exact(const StepArgs& a, bool backward, hipStream_t st) {
     return run(a, backward ? BWD_EXACT : FWD_EXACT, st);

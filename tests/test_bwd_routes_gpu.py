@@ -9,6 +9,7 @@ import torch
 from paper_2311_09431_amd import binding as sa
 from paper_2311_09431_amd import inputs
 from tests import helpers as hp
+from tests import routes
 
 pytestmark = pytest.mark.gpu
 
@@ -66,3 +67,28 @@ def test_step_against_the_oracle(B, H, Hkv, c, d, q_dev, kv_dev, layout):
             hp.check_grad("dQ", dq[B - 1, h].cpu().numpy(), scale * ds @ x["k"], True)
         hp.check_grad("dK", dk[B - 1, kvh].cpu().numpy(), wk, True)
         hp.check_grad("dV", dv[B - 1, kvh].cpu().numpy(), wv, True)
+
+
+@pytest.mark.parametrize("c,d,route", [(128, 128, "128 rows"), (250, 60, "128 rows"), (120, 100, "fp32")])
+def test_rows_at_the_end_of_reach(c, d, route):
+    # K, V, dK, dV rows so far apart that the block's rows (rounded up to a tile) just end below 2^31 bytes, but not the
+    # rows behind them that the split kernels' last requests name
+    pitch = (1 << 31) // (2 * ((c + 127) // 128 * 128)) - 64
+    a = routes.args(c, d, 1, q_dev=0, layout=sa.CONTIGUOUS, kv_stride_s=pitch)
+    assert routes.forward(a) == routes.backward(a) == route
+    wide = lambda dtype: torch.empty(c * pitch, dtype=dtype, device="cuda").as_strided((1, 1, c, d), (c * pitch, c * pitch, pitch, 1))  # noqa: E731
+    q, g, k0, v0 = (inputs.gaussian((1, 1, c, d), 30 + d + i, torch.bfloat16) for i in range(4))
+    gq, gg, k, v, dk, dv = q.cuda(), g.cuda(), wide(q.dtype), wide(q.dtype), wide(torch.float32), wide(torch.float32)
+    k.copy_(k0), v.copy_(v0), dk.zero_(), dv.zero_()
+    f32 = dict(dtype=torch.float32, device="cuda")
+    o, lse, delta, dq = (torch.zeros(*s, **f32) for s in ((1, 1, c, d), (1, 1, c), (1, 1, c), (1, 1, c, d)))
+    shape = sa.shard_shape(gq, c, lse, kv=k)
+    sa.sa_state_init(o, lse, shape)
+    sa.sa_attn_step_fwd(gq, k, v, o, lse, 0, 0, 1, sa.CONTIGUOUS, shape)
+    sa.sa_bwd_preprocess(o, gg, delta, shape)
+    sa.sa_attn_step_bwd(gq, k, v, gg, lse, delta, dq, dk, dv, 0, 0, 1, sa.CONTIGUOUS, shape)
+    torch.cuda.synchronize()
+    want_o, want_l = hp.oracle_forward(q, k0, v0, 1.0 / np.sqrt(d))
+    assert hp.max_abs_err(o.cpu().numpy(), want_o) <= 2e-2 and hp.max_abs_err(lse.cpu().numpy(), want_l) <= 1e-3
+    for name, got, want in zip(("dQ", "dK", "dV"), (dq, dk, dv), hp.oracle_backward(q, k0, v0, g, 1.0 / np.sqrt(d))):
+        hp.check_grad(name, got.contiguous().cpu().numpy(), want, True)

@@ -30,3 +30,17 @@ def test_wide_query_rows_stay_with_the_kernel_that_reads_them_by_pointer(c, d):
         assert routes.backward(routes.args(c, d, 1, stride_s=pitch)) == "fp32"
     # and keys as far apart: neither
     assert routes.forward(routes.args(c, d, 1, kv_stride_s=MOST // 2 // c + 8)) == "fp32"
+
+
+@pytest.mark.parametrize("c", [1, 33, 97, 127, 128, 129, 160, 8192])
+@pytest.mark.parametrize("side", ["stride_s", "kv_stride_s"])
+def test_every_offset_of_a_split_launch_is_below_the_limit(c, side):
+    # the split kernels' last requests name the 32 rows behind the block's last sub-tile, 16 and 16
+    d, behind = 64, (c + 31) // 32 * 32 + 31
+    taken = []
+    for pitch in range(8 * (MOST // 2 // (c + 160) // 8) - 64, 8 * (MOST // 2 // c // 8) + 65, max(8, 8 * (MOST // 2 // c // 8 // 4096))):
+        for ask in (routes.forward, routes.backward):
+            if ask(routes.args(c, d, 1, **{side: pitch})) in ("split", "short"):
+                taken.append(pitch)
+                assert behind * 2 * pitch + 2 * d < MOST, (ask.__name__, pitch)
+    assert taken or c == 1          # the rule is not empty there
