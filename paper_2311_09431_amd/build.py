@@ -4,10 +4,13 @@
 
 Objects go to _build/ at the repository root, the library next to this file.
 """
+import glob
 import os
 import subprocess
 import sys
 from concurrent.futures import ThreadPoolExecutor
+
+from . import asm_check
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -22,6 +25,10 @@ SOURCES = ["api.hip", "permute.hip", "elementwise.hip", "f32_step.hip", "fwd_mfm
 # their products, so MFMA results stay out of the accumulation registers (forward 2.20 -> 2.10 ms,
 # backward 6.7 -> 6.1 ms for 16 heads, d 128, 4 x 2048 tokens).
 SOURCE_FLAGS = {"f32x3_step.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
+
+# Sources with matrix instructions in asm statements, and their kernels whose accumulators are registers by
+# number: the assembly of these is looked over (asm_check.py).
+ASM_CHECKED = {"bwd_mfma.hip": ["bwd_dkdv_wide_kernel"], "split_mfma.hip": []}
 
 # packed fp32 VALU forms are switched off on purpose for the test machines
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-fno-gpu-rdc",
@@ -40,6 +47,8 @@ def _hipcc():
 def _compile(src, extra):
     obj = os.path.join(OBJ_DIR, os.path.splitext(src)[0] + ".o")
     cmd = [_hipcc(), *FLAGS, *SOURCE_FLAGS.get(src, []), *extra, "-c", os.path.join(CSRC, src), "-o", obj]
+    if src in ASM_CHECKED:
+        cmd.append("-save-temps=obj")       # the assembly that is assembled; the code is the same
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode:
         raise RuntimeError("hipcc failed on %s:\n%s\n%s" % (src, r.stdout, r.stderr))
@@ -47,7 +56,20 @@ def _compile(src, extra):
     warn = "\n".join(l for l in r.stderr.splitlines() if not any(n in l for n in noise)).strip()
     if warn:
         sys.stderr.write(warn + "\n")
+    if src in ASM_CHECKED:
+        _check_asm(src, obj)
     return obj
+
+
+def _check_asm(src, obj):
+    stem = obj[:-2]
+    with open(stem + "-hip-amdgcn-amd-amdhsa-gfx950.s") as f:
+        findings = asm_check.check(f.read(), ASM_CHECKED[src])
+    for left in glob.glob(stem + "-h*") + glob.glob(stem + ".hip-*"):
+        os.remove(left)
+    if findings:
+        os.remove(obj)
+        raise RuntimeError("%s: the compiled code breaks what its asm statements rest on:\n%s" % (src, "\n".join(findings)))
 
 
 def build_library(extra_flags=(), jobs=8):

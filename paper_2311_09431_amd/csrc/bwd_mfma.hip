@@ -722,7 +722,8 @@ constexpr int WIDE_NO_MASK = -(1 << 20);
 // to vector registers and scratch memory and back around every loop (444 spilled registers).  Each
 // statement declares the whole file as overwritten, so that nothing of the compiler's lives there
 // across one; it has no reason to use the file at all while its own values fit the 256 vector
-// registers, which the kernel's assembly shows: outside of these statements no instruction names one.
+// registers.  The build looks that outside of these statements no instruction names one, and for the wait states
+// of all products in asm statements (asm_check.py).
 #ifdef __HIP_DEVICE_COMPILE__
 #define ACC_TEN(b) "a" #b "0", "a" #b "1", "a" #b "2", "a" #b "3", "a" #b "4", "a" #b "5", "a" #b "6", "a" #b "7", "a" #b "8", "a" #b "9"
 #define ACC_FILE                                                                                                   \
