@@ -91,30 +91,35 @@ inline bool uneven(const StepArgs& a) { return a.layout == SA_STRIPED || a.n_q >
 
 // Order of a backward launch of n_keys key-owning and n_queries query-owning workgroups, each sequence
 // heaviest first: `first` key-owning ones, whose walks are longer than the longest query-owning one, then the
-// rest of both evenly interleaved, in units of 8 workgroups where both numbers allow: consecutive
-// workgroups go round-robin to the 8 XCDs, and one by one equal numbers of both kinds left each kind
-// four of them (2 heads of 4096 rows, full block, split kernels 81 -> 66 us; 16 of 2048, triangular, 128-row
-// kernels 87 -> 83).  All of an even launch's key-owning walks are longer (`ratio` times, times the group);
-// of an uneven one, whose walks shrink evenly to almost nothing, those before that point are.  ratio 0: both
-// kinds from the start.
-struct BothKinds { int n_keys, first, unit, rest, total; };
+// rest of both evenly interleaved, in units of 8 workgroups: consecutive workgroups go round-robin to the 8 XCDs,
+// and one by one equal numbers of both kinds left each kind four of them (2 heads of 4096 rows, full block,
+// split kernels 81 -> 66 us; 16 of 2048, triangular, 128-row kernels 87 -> 81).  What fills no unit, less than 8
+// of each kind, the lightest, comes last.  All of an even launch's key-owning walks are longer (`ratio` times,
+// times the group); of an uneven one, whose walks shrink evenly to almost nothing, those before that point
+// are.  ratio 0: both kinds from the start.
+struct BothKinds { int first, keys, total, last; };            // keys, total: units; last: key-owning ones of the end
 inline BothKinds both_kinds(const StepArgs& a, int64_t n_keys, int64_t n_queries, double ratio) {
     BothKinds b;
     const double longer = ratio * (a.H / a.H_kv);
-    b.n_keys = (int)n_keys;
     b.first = !uneven(a) ? (int)n_keys : longer > 1. ? (int)(n_keys * (1. - 1. / longer)) / 8 * 8 : 0;
-    b.unit = n_keys % 8 || n_queries % 8 ? 1 : 8;
-    b.rest = (int)(n_keys - b.first) / b.unit;
-    b.total = b.rest + (int)n_queries / b.unit;
+    b.keys = (int)(n_keys - b.first) / 8;
+    b.total = b.keys + (int)n_queries / 8;
+    b.last = (int)(n_keys - b.first) % 8;
     return b;
 }
 // the kind of workgroup `linear` and its place among those of its kind
 __device__ inline bool owns_keys(const BothKinds& b, int& linear) {
     if (linear < b.first) return true;
-    const int u = (linear - b.first) / b.unit, at = linear - b.first - u * b.unit;
-    const int before = (int)((int64_t)u * b.rest / b.total);
-    const bool keys = (int)(((int64_t)u + 1) * b.rest / b.total) > before;
-    linear = keys ? b.first + before * b.unit + at : (u - before) * b.unit + at;
+    const int u = (linear - b.first) / 8, at = (linear - b.first) % 8;
+    if (u >= b.total) {
+        const int end = linear - b.first - 8 * b.total;
+        const bool keys = end < b.last;
+        linear = keys ? b.first + 8 * b.keys + end : 8 * (b.total - b.keys) + end - b.last;
+        return keys;
+    }
+    const int before = (int)((int64_t)u * b.keys / b.total);
+    const bool keys = (int)(((int64_t)u + 1) * b.keys / b.total) > before;
+    linear = keys ? b.first + 8 * before + at : 8 * (u - before) + at;
     return keys;
 }
 

@@ -544,6 +544,26 @@ __device__ inline void add_rows(float* row, float4 (&x)[blocks_of(DP)], const ch
 }
 
 // ----------------------------------------------------------------- backward
+// Workgroup -> (tile rank, head), ranks heaviest first.  Consecutive workgroups go round-robin to the 8 XCDs; taken
+// in chunks of as many ranks as make a multiple of 8 workgroups, an XCD gets the same heads (and at most two others'
+// shares) of every chunk, and its L2 holds what they stream.  Head by head, an odd number of heads has every XCD
+// stream all of them: d 64, triangular, 25 heads of 2048 rows 125 -> 75 us, 15 of 4096 260 -> 145, 7 of 8192 360 ->
+// 242, 128 on 32 of 2048 343 -> 315.  Few ranks, where a chunk is a large part of the order, and those behind
+// the last whole chunk stay head by head (9 heads of 500 rows, d 100, in chunks 15.3 -> 16.1).  (Backward only: the
+// forward gained as often as it lost, full blocks, d 128, 15 heads of 1024 28.0 -> 21.7, 3 of 5000 60.8 -> 63.7.)
+__device__ inline void decode_near(int linear, int n_ranks, int n_heads, int& rank, int& head) {
+    const int chunk = n_heads % 8 == 0 ? 1 : n_heads % 4 == 0 ? 2 : n_heads % 2 == 0 ? 4 : 8;
+    const int size = chunk * n_heads, i = linear / size, j = linear - i * size;
+    if ((i + 1) * chunk > n_ranks || n_ranks < 4 * chunk) {
+        rank = linear / n_heads;
+        head = linear - rank * n_heads;
+        return;
+    }
+    const int at = j % 8 * (size / 8) + j / 8;
+    head = at / chunk;
+    rank = i * chunk + at - head * chunk;
+}
+
 // One wavefront per SIMD (the key-owning side's registers), so what overlaps is arranged by hand: a
 // product leaves room for five or six other instructions.  In sub-tile u:
 //     S(u)      beside the transposing reads of u
@@ -583,7 +603,7 @@ __device__ inline void bwd_dq(const StepArgs& p, int n_tiles, int linear, char* 
     const Lane<DP> ln;
     const int n = ln.n, h = ln.h;
     int rank, bh, dev_rank;
-    decode(linear, p.B * p.H, rank, bh);
+    decode_near(linear, n_tiles * p.n_q, p.B * p.H, rank, bh);
     decode_rank(rank, n_tiles, p.n_q, p.layout, rank, dev_rank);
     const int q0 = (n_tiles - 1 - rank) * OWN, dev_i = p.n_q - 1 - dev_rank, dev = p.q_dev + dev_i;
     const int b = bh / p.H, hd = bh - b * p.H, d = p.d;
@@ -743,7 +763,7 @@ __device__ inline void bwd_dkdv(const StepArgs& p, int n_tiles, int linear, char
     const Lane<DP> ln;
     const int n = ln.n, h = ln.h, wave = ln.wave;
     int tile, bh, dev_i;                                // low key tiles see most queries: first
-    decode(linear, p.B * p.H_kv, tile, bh);
+    decode_near(linear, n_tiles * p.n_kv, p.B * p.H_kv, tile, bh);
     decode_rank(tile, n_tiles, p.n_kv, p.layout, tile, dev_i);
     const int k0 = tile * OWN, dev = p.kv_dev + dev_i;
     const int b = bh / p.H_kv, kvh = bh - b * p.H_kv, group = p.H / p.H_kv, d = p.d;

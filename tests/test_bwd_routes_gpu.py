@@ -19,12 +19,12 @@ CASES = [
     (1, 2, 2, 129, 64),         # 4
     (1, 3, 3, 257, 100),        # 9, last tile of one row
     (2, 2, 1, 384, 112),        # 6, grouped heads
-    (1, 16, 16, 512, 36),       # 64: last split for uneven work, not for full blocks
-    (1, 13, 13, 640, 128),      # 65
+    (1, 16, 16, 512, 36),       # 64: split
+    (1, 13, 13, 640, 128),      # 65: short walks, 128 rows
     (1, 32, 4, 256, 128),       # 8, 32 query heads
-    (1, 8, 8, 512, 100),        # 32: last split for full blocks
+    (1, 8, 8, 512, 100),        # 32
     (1, 9, 9, 500, 100),        # 36
-    (1, 64, 64, 512, 64),       # 256: last one launch for uneven work, not for full blocks
+    (1, 64, 64, 512, 64),       # 256: one launch of 128-row workgroups for uneven work, not for full blocks
     (1, 43, 43, 768, 128),      # 258: one launch each
     (1, 24, 24, 520, 256),      # two key-owning workgroups per tile: 240 of 512
     (1, 3, 3, 130, 200),
@@ -92,3 +92,43 @@ def test_rows_at_the_end_of_reach(c, d, route):
     assert hp.max_abs_err(o.cpu().numpy(), want_o) <= 2e-2 and hp.max_abs_err(lse.cpu().numpy(), want_l) <= 1e-3
     for name, got, want in zip(("dQ", "dK", "dV"), (dq, dk, dv), hp.oracle_backward(q, k0, v0, g, 1.0 / np.sqrt(d))):
         hp.check_grad(name, got.contiguous().cpu().numpy(), want, True)
+
+
+SPLIT = [
+    # B, H, H_kv, c, d: more than 64 key tiles, long walks
+    (1, 20, 20, 513, 64),       # 100; 340 workgroups of a kind, an uneven number of units of 8
+    (2, 7, 7, 1500, 36),        # 168 (triangular only), ranks in chunks of four and three left over
+    (1, 29, 29, 1100, 64),      # 261 (triangular only), an odd number of heads: chunks of eight ranks
+    (1, 24, 12, 1300, 60),      # 132 (triangular only), grouped heads
+    (1, 7, 7, 2100, 100),       # 119 (triangular only)
+    (1, 32, 8, 1030, 128),      # 72, four heads per key/value head
+]
+
+
+@pytest.mark.parametrize("q_dev,kv_dev,layout", [(1, 0, sa.STRIPED), (0, 1, sa.STRIPED), (1, 0, sa.CONTIGUOUS)])
+@pytest.mark.parametrize("B,H,Hkv,c,d", SPLIT)
+def test_larger_split_launches(B, H, Hkv, c, d, q_dev, kv_dev, layout):
+    a = routes.args(c, d, H, Hkv, B, q_dev=q_dev, kv_dev=kv_dev, layout=layout)
+    full = layout == sa.CONTIGUOUS
+    assert routes.backward(a) == ("128 rows" if full and (c, H) not in ((513, 20), (1030, 32)) else "split")
+    if not full:
+        test_step_against_the_oracle(B, H, Hkv, c, d, q_dev, kv_dev, layout)
+    if routes.backward(a) != "split":
+        return
+    # every head as a launch of its own gives it: the order of a launch's workgroups touches no sum
+    q, g = (inputs.gaussian((B, H, c, d), 60 + c + i, torch.bfloat16).cuda() for i in (0, 1))
+    k, v = (inputs.gaussian((B, Hkv, c, d), 70 + c + i, torch.bfloat16).cuda() for i in (0, 1))
+    f32 = dict(dtype=torch.float32, device="cuda")
+    lse, delta = torch.full((B, H, c), 7.0, **f32), inputs.gaussian((B, H, c), 5).cuda()
+    whole, single = ([torch.zeros(x.shape, **f32) for x in (q, k, v)] for _ in range(2))
+    group = H // Hkv
+    sa.sa_attn_step_bwd(q, k, v, g, lse, delta, *whole, q_dev, kv_dev, 2, layout, sa.shard_shape(q, c, lse, kv=k))
+    for b in range(B):
+        for h in range(Hkv):
+            own = slice(h * group, (h + 1) * group)
+            sq, sg, sl, sd, sdq = (x[b:b + 1, own] for x in (q, g, lse, delta, single[0]))
+            sk, sv, sdk, sdv = (x[b:b + 1, h:h + 1] for x in (k, v, *single[1:]))
+            sa.sa_attn_step_bwd(sq, sk, sv, sg, sl, sd, sdq, sdk, sdv, q_dev, kv_dev, 2, layout, sa.shard_shape(sq, c, sl, kv=sk))
+    torch.cuda.synchronize()
+    for x, y in zip(whole, single):
+        assert torch.equal(x, y)
