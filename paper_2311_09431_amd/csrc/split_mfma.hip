@@ -1033,13 +1033,16 @@ bool rows_in_reach(const StepArgs& a) {
 // full 32 of 512 15.5 / 17.2, 8 of 2048 35.1 / 32.5, ring of 4 x 128, 32 heads, contiguous 15.1 / 15.4.  256:
 // triangular 16 heads of 2048 39 / 42, 4 of 8192 122 / 108, ring of 4 x 1024, 8 heads 66.7 / 68.3, of
 // 4 x 2048, 4 heads 121 / 112, full 8 of 4096 78 / 107; d 64: ring of 4 x 1024, 8 heads 49.7 / 45.9.  A single
-// block of 128 rows is as well off in one 128-row tile up to 112 columns (d 64 7.9 / 8.3, d 128 10 / 8.5).
+// block of 128 rows is as well off in one 128-row tile up to 112 columns (d 64 7.9 / 8.3, d 128 10 / 8.5).  An odd number
+// of heads has every XCD stream all of them, full blocks of 65 to 128 tiles above 64 columns: d 128, 11 heads of
+// 1024 23.0 / 24.3, 13 of 1100 26.0 / 27.4, 15 of 1024 24.2 / 28.0, 9 of 1700 34.3 / 32.0, but 14 of 1152 25.2 / 23.6,
+// 15 on 3 of 1024 22.5 / 21.0.
 bool fwd_split_wanted(const StepArgs& a) {
     const int64_t tiles = (int64_t)((a.c + 127) / 128) * a.B * a.n_q * a.H, walk = (int64_t)a.c * a.n_kv;
     if (a.d > TD || (walk <= 128 && a.d <= 112)) return false;
     if (!rows_in_reach(a)) return false;
     if (tiles <= 64) return true;
-    if (tiles <= 128) return walk >= (a.layout == SA_STRIPED ? 512 : 1024);
+    if (tiles <= 128) return walk >= (a.layout == SA_STRIPED ? 512 : a.d > 64 && a.H == a.H_kv && a.B * a.H % 2 ? 1536 : 1024);
     return tiles <= 256 && uneven(a) && walk >= (a.d <= 112 ? 4096 : 8192);
 }
 hipError_t launch_fwd_split(const StepArgs& a, hipStream_t st) { return run(a, FWD, st); }
@@ -1047,16 +1050,21 @@ hipError_t launch_fwd_split(const StepArgs& a, hipStream_t st) { return run(a, F
 // 8192 201 / 88 (207 / 154), 32 heads on 8 of 1024 115 / 60 (141 / 87), ring of 4 x 1024, 2 heads 112 / 54.  128,
 // triangular: 16 heads of 1024 39.6 / 41.7, 8 of 2048 62 / 54, 2 of 8192 200 / 143, 32 on 8 of 2048 211 / 170,
 // ring of 4 x 256, 16 heads 42 / 48, of 4 x 512, 8 heads 67 / 60; full 2 of 8192 233 / 257, 32 on 8 of 2048 313 /
-// 281; 256: 8 of 4096 137 / 160, 32 on 8 of 4096 500 / 574.  Up to 64 columns two workgroups fit a compute unit: full,
-// 128 tiles, 32 heads of 512 18.5 / 18.1, 2 of 8192 147 / 135, 256: 46.4 / 45.8, 254 / 263; triangular, 256: 32 of
-// 1024 36.1 / 35.9, 8 of 4096 87 / 78, ring of 4 x 1024, 32 on 8 369 / 300, 512: 32 of 2048 94.0 / 93.3, 8 of 8192
-// 288 / 275, but 64 heads of 200 (128 tiles) 11.0 / 13.1.
+// 281; 256: 8 of 4096 137 / 160, 32 on 8 of 4096 500 / 574.  Up to 64 columns two workgroups fit a compute unit.  Full
+// blocks, 128 tiles: 32 heads of 512 19.6 / 18.3, but at d 32 16.1 / 17.0 (20 of 512 15.2 / 13.4), 16 of 1024 29.2 /
+// 25.0, 2 of 8192 147 / 135; 256: 46.4 / 45.8, 254 / 263.  Triangular, 256: 32 of 1024 40.6 / 36.4, 8 of 4096 87 / 78,
+// ring of 4 x 1024, 32 on 8 369 / 300; up to 512: 24 of 1300 51 / 35, 31 of 2048 99 / 96, 8 of 8192 308 / 287, 5 of 12500
+// 435 / 391, 64 on 16 of 4096 606 / 611; but 32 of 2048, d 32, 80 / 82, contiguous ring of 2 x 1024, 32 heads, 92 / 96.
+// 64 heads of 200 (128 tiles) 11.0 / 13.1.
 bool bwd_split_wanted(const StepArgs& a) {
     const int64_t keys = (int64_t)((a.c + 127) / 128) * a.B * a.n_kv * a.H_kv, group = a.H / a.H_kv;
     if (a.d > TD || !rows_in_reach(a)) return false;
     const int64_t walk = (int64_t)a.c * a.n_q * group;
     if (keys <= 64) return true;
-    if (a.d <= 64) return keys <= (uneven(a) ? 512 : 128) && walk >= 4 * keys;
+    if (a.d <= 64) {
+        if (!uneven(a)) return keys <= 128 && walk >= (a.d <= 32 ? 6 : 4) * keys;
+        return keys <= 256 ? walk >= 4 * keys : keys <= 512 && walk > 4 * keys;
+    }
     return keys <= 128 && (uneven(a) ? walk >= 2048 : group >= 4);
 }
 hipError_t launch_bwd_split(const StepArgs& a, hipStream_t st) { return run(a, BWD, st); }

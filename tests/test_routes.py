@@ -44,3 +44,15 @@ def test_every_offset_of_a_split_launch_is_below_the_limit(c, side):
                 taken.append(pitch)
                 assert behind * 2 * pitch + 2 * d < MOST, (ask.__name__, pitch)
     assert taken or c == 1          # the rule is not empty there
+
+
+def test_split_rules_at_their_edges():
+    # where the measured lines lie (the figures stand at the rules)
+    bwd = lambda H, c, d, layout=sa.STRIPED, **kw: routes.backward(routes.args(c, d, H, layout=layout, **kw))     # noqa: E731
+    assert bwd(32, 512, 64, sa.CONTIGUOUS) == "split" and bwd(32, 512, 32, sa.CONTIGUOUS) == "128 rows"
+    assert bwd(20, 512, 32, sa.CONTIGUOUS) == "split"
+    assert bwd(32, 2048, 64) == "128 rows" and bwd(31, 2048, 64) == "split" and bwd(32, 1024, 64) == "split"
+    assert bwd(32, 1024, 64, sa.CONTIGUOUS, N=2) == "128 rows"
+    fwd = lambda H, c, d, Hkv=None: routes.forward(routes.args(c, d, H, Hkv, layout=sa.CONTIGUOUS))               # noqa: E731
+    assert fwd(15, 1024, 128) == "128 rows" and fwd(15, 1024, 64) == "split" and fwd(14, 1152, 128) == "split"
+    assert fwd(9, 1700, 128) == "split" and fwd(15, 1024, 128, 3) == "split"
