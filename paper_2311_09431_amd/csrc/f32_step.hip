@@ -541,13 +541,13 @@ hipError_t run(const StepArgs& a, bool backward, hipStream_t st) {
 hipError_t launch_fwd_f32(const StepArgs& a, int dtype, hipStream_t st) {
     if (few_rows_wanted(a, dtype, false)) return launch_few_rows(a, dtype, false, st);
     if (dtype == SA_F32 && f32x3_wanted(a, false)) return launch_f32x3(a, false, st);
-    if (short_exact_wanted(a, dtype)) return launch_short_exact(a, false, st);
+    if (short_exact_wanted(a, dtype, false)) return launch_short_exact(a, false, st);
     return dtype == SA_F32 ? run<float>(a, false, st) : run<__hip_bfloat16>(a, false, st);
 }
 hipError_t launch_bwd_f32(const StepArgs& a, int dtype, hipStream_t st) {
     if (few_rows_wanted(a, dtype, true)) return launch_few_rows(a, dtype, true, st);
     if (dtype == SA_F32 && f32x3_wanted(a, true)) return launch_f32x3(a, true, st);
-    if (short_exact_wanted(a, dtype)) return launch_short_exact(a, true, st);
+    if (short_exact_wanted(a, dtype, true)) return launch_short_exact(a, true, st);
     return dtype == SA_F32 ? run<float>(a, true, st) : run<__hip_bfloat16>(a, true, st);
 }
 

@@ -97,29 +97,30 @@ inline bool uneven(const StepArgs& a) { return a.layout == SA_STRIPED || a.n_q >
 // of each kind, the lightest, comes last.  All of an even launch's key-owning walks are longer (`ratio` times,
 // times the group); of an uneven one, whose walks shrink evenly to almost nothing, those before that point
 // are.  ratio 0: both kinds from the start.
-struct BothKinds { int first, keys, total, last; };            // keys, total: units; last: key-owning ones of the end
-inline BothKinds both_kinds(const StepArgs& a, int64_t n_keys, int64_t n_queries, double ratio) {
+struct BothKinds { int first, unit, keys, total, last; };      // keys, total: units; last: key-owning ones of the end
+inline BothKinds both_kinds(const StepArgs& a, int64_t n_keys, int64_t n_queries, double ratio, int unit = 8) {
     BothKinds b;
     const double longer = ratio * (a.H / a.H_kv);
     b.first = !uneven(a) ? (int)n_keys : longer > 1. ? (int)(n_keys * (1. - 1. / longer)) / 8 * 8 : 0;
-    b.keys = (int)(n_keys - b.first) / 8;
-    b.total = b.keys + (int)n_queries / 8;
-    b.last = (int)(n_keys - b.first) % 8;
+    b.unit = unit;
+    b.keys = (int)(n_keys - b.first) / unit;
+    b.total = b.keys + (int)n_queries / unit;
+    b.last = (int)(n_keys - b.first) % unit;
     return b;
 }
 // the kind of workgroup `linear` and its place among those of its kind
 __device__ inline bool owns_keys(const BothKinds& b, int& linear) {
     if (linear < b.first) return true;
-    const int u = (linear - b.first) / 8, at = (linear - b.first) % 8;
+    const int u = (linear - b.first) / b.unit, at = linear - b.first - u * b.unit;
     if (u >= b.total) {
-        const int end = linear - b.first - 8 * b.total;
+        const int end = linear - b.first - b.total * b.unit;
         const bool keys = end < b.last;
-        linear = keys ? b.first + 8 * b.keys + end : 8 * (b.total - b.keys) + end - b.last;
+        linear = keys ? b.first + b.keys * b.unit + end : (b.total - b.keys) * b.unit + end - b.last;
         return keys;
     }
     const int before = (int)((int64_t)u * b.keys / b.total);
     const bool keys = (int)(((int64_t)u + 1) * b.keys / b.total) > before;
-    linear = keys ? b.first + 8 * before + at : 8 * (u - before) + at;
+    linear = keys ? b.first + before * b.unit + at : (u - before) * b.unit + at;
     return keys;
 }
 
@@ -163,7 +164,7 @@ bool fwd_split_wanted(const StepArgs& a);
 hipError_t launch_fwd_split(const StepArgs& a, hipStream_t st);
 bool few_rows_wanted(const StepArgs& a, int dtype, bool backward);
 hipError_t launch_few_rows(const StepArgs& a, int dtype, bool backward, hipStream_t st);
-bool short_exact_wanted(const StepArgs& a, int dtype);
+bool short_exact_wanted(const StepArgs& a, int dtype, bool backward);
 hipError_t launch_short_exact(const StepArgs& a, bool backward, hipStream_t st);
 
 }  // namespace sa

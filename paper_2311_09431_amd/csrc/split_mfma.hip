@@ -996,7 +996,9 @@ hipError_t run(const StepArgs& a, Pass pass, hipStream_t st) {
     const int n_tiles = (a.c + OWN - 1) / OWN;
     const int n_dkdv = n_tiles * a.n_kv * a.B * a.H_kv, n_dq = n_tiles * a.n_q * a.B * a.H;
     const bool forward = pass == FWD || pass == FWD_EXACT;
-    const BothKinds kinds = both_kinds(a, n_dkdv, n_dq, 1.25);
+    // (short blocks, all key-owning ones first: 2048 heads of 16 rows, d 128, 124 -> 116 us, 512 of 96 98 -> 94, ring of 8 x
+    // 96, 32 heads, 97 -> 92)
+    const BothKinds kinds = both_kinds(a, n_dkdv, n_dq, pass == BWD_EXACT ? INFINITY : 1.25);
     const dim3 grid((unsigned)(forward ? n_dq : n_dkdv + n_dq)), block(64 * (forward ? FWD_WAVES : BWD_WAVES));
     if (pass == FWD && a.q_pos) {           // (d is 64 or 128: the other forms only exist for these)
         if constexpr ((DP == 64 || DP == 128) && !PART)
@@ -1073,9 +1075,13 @@ hipError_t launch_bwd_split(const StepArgs& a, hipStream_t st) { return run(a, B
 // operands (f32_step.hip), us: forward step, d 128, 4 heads of 64 tokens 15.7 / 7.7, 64 of 96 17.1 / 8.3, 256 of
 // 120 38.9 / 25.5, d 64 10.3 / 7.8, 11.1 / 8.0, 20.7 / 14.0, d 32 7.9 / 7.8, 8.0 / 7.8, 13.0 / 13.2 (7.7 is
 // what a launch takes).  Error against 64 bits (2-norm, 16 x 127 tokens, d 128): O 2.2e-7 -> 1.6e-7, dQ
-// 3.7e-7 -> 3.2e-7, dK 6.1e-7 -> 4.3e-7, dV 6.0e-7 -> 4.1e-7.
-bool short_exact_wanted(const StepArgs& a, int dtype) {
-    return dtype == SA_BF16 && a.d % 4 == 0 && a.d <= TD && a.c < 128 && rows_in_reach(a);
+// 3.7e-7 -> 3.2e-7, dK 6.1e-7 -> 4.3e-7, dV 6.0e-7 -> 4.1e-7.  A single forward block of many heads stays with the fp32
+// instruction up to 32 columns (half of the columns computed here are padding): d 16, 600 heads of 30 rows 10.0 / 11.0,
+// 512 8.7 / 8.4, 400 heads of 60 11.4 / 13.1, of 96 15.1 / 16.1, of 127 18.5 / 21.2, 360 11.4 / 11.1, 15.1 / 16.1, 18.6 /
+// 18.5; 1024 of 96 23.9 / 33.8, d 32 26.2 / 34.1, d 36 54 / 41.
+bool short_exact_wanted(const StepArgs& a, int dtype, bool backward) {
+    if (dtype != SA_BF16 || a.d % 4 || a.d > TD || a.c >= 128 || !rows_in_reach(a)) return false;
+    return backward || a.n_kv > 1 || a.d > 32 || (int64_t)a.B * a.n_q * a.H <= (a.c <= 32 ? 512 : 384);
 }
 hipError_t launch_short_exact(const StepArgs& a, bool backward, hipStream_t st) {
     return run(a, backward ? BWD_EXACT : FWD_EXACT, st);

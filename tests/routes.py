@@ -36,11 +36,11 @@ def _ask(name, a, *more):
 
 def forward(a, dtype=sa.BF16):
     if not _ask("fwd_mfma_supported", a, dtype):
-        return "short" if _ask("short_exact_wanted", a, dtype) else "fp32"
+        return "short" if _ask("short_exact_wanted", a, dtype, False) else "fp32"
     return "split" if _ask("fwd_split_wanted", a) else "128 rows"
 
 
 def backward(a, dtype=sa.BF16):
     if not _ask("bwd_mfma_supported", a, dtype):
-        return "short" if _ask("short_exact_wanted", a, dtype) else "fp32"
+        return "short" if _ask("short_exact_wanted", a, dtype, True) else "fp32"
     return "split" if _ask("bwd_split_wanted", a) else "128 rows"

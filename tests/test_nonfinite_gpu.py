@@ -24,8 +24,9 @@ ROUTES = [
     (520, 520, 40, 68, F32),        # ... eight
     (2, 1, 48, 64, BF16),           # short bf16 blocks
     (1, 1, 100, 100, BF16),
-    (96, 96, 40, 64, BF16),         # a single forward block of them by the fp32 instruction
+    (96, 96, 40, 64, BF16),         # ... more workgroups than compute units
     (256, 256, 33, 32, BF16),
+    (400, 400, 40, 32, BF16),       # many heads up to 32 columns: a single forward block by the fp32 instruction
     (1, 1, 132, 132, BF16),         # above 128 columns, not whole 16-byte chunks
 ]
 BLOCKS = [(1, 0, sa.STRIPED), (0, 1, sa.STRIPED), (1, 0, sa.CONTIGUOUS)]

@@ -56,3 +56,7 @@ def test_split_rules_at_their_edges():
     fwd = lambda H, c, d, Hkv=None: routes.forward(routes.args(c, d, H, Hkv, layout=sa.CONTIGUOUS))               # noqa: E731
     assert fwd(15, 1024, 128) == "128 rows" and fwd(15, 1024, 64) == "split" and fwd(14, 1152, 128) == "split"
     assert fwd(9, 1700, 128) == "split" and fwd(15, 1024, 128, 3) == "split"
+    # short blocks of many heads, few columns: one forward block, not the backward or a walk over several
+    for H, c, d, route in ((512, 32, 32, "short"), (513, 32, 32, "fp32"), (384, 33, 32, "short"), (385, 33, 32, "fp32"), (1000, 33, 36, "short")):
+        assert fwd(H, c, d) == route and bwd(H, c, d) == "short"
+        assert routes.forward(routes.args(c, d, H, N=2)) == "short"
