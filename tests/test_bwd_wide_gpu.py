@@ -1,6 +1,8 @@
-"""Backward above 128 columns with both column halves of dK and dV in one workgroup (more than 128 key
-tiles): single steps against the oracle on both sides of that rule and at the edges of its 32-row stages,
-with last tiles of a few rows, columns short of both halves, grouped heads; and the ring drivers."""
+"""Backward above 128 columns with both column halves of dK and dV in one workgroup (full blocks of more than
+128 key tiles, triangular ones and rings of more than 256): single steps against the oracle on both sides of
+these rules and at the edges of its 32-row stages, with last tiles of a few rows, columns short of both
+halves, grouped heads; and the ring drivers.  Coarse tile skipping, rows with gaps, interleaved heads and NaN on
+this route are in test_tiled_gpu, test_strides_gpu and test_nonfinite_gpu."""
 import pytest
 import torch
 
@@ -13,7 +15,7 @@ pytestmark = pytest.mark.gpu
 STEPS = [
     # B, H, H_kv, c, d                key tiles
     (1, 64, 64, 256, 256),          # 128: column halves side by side (full block)
-    (1, 65, 65, 130, 136),          # 130, last tile of two rows
+    (1, 65, 65, 130, 136),          # 130, last tile of two rows (triangular: up to 256 halves side by side)
     (2, 35, 35, 161, 200),          # 140, one row into a stage
     (1, 32, 16, 1121, 144),         # 144, two heads per key/value head
     (1, 257, 257, 128, 256),        # 257: triangular blocks too

@@ -8,6 +8,7 @@ from oracle import striped_attention as orc
 from paper_2311_09431_amd import binding as sa
 from paper_2311_09431_amd import inputs
 from tests import helpers as hp
+from tests import routes
 
 pytestmark = pytest.mark.gpu
 
@@ -21,6 +22,7 @@ def _check_ring(B, H, S, d, N, layout, dtype, seed, scale=None, use_driver=False
     sc = scale if scale else 1.0 / np.sqrt(d)
     O, LSE = hp.ring_forward_gpu(Q.cuda(), K.cuda(), V.cuda(), N, layout, scale, use_driver, order)
     torch.cuda.synchronize()
+    O, LSE, Q, K, V = hp.some_heads(O, LSE, Q, K, V)
     Oh = hp.from_device_order_host(O.cpu().numpy(), N, layout)
     Lh = hp.from_device_order_host(LSE.cpu().numpy(), N, layout)
     Ow, Lw = hp.oracle_forward(Q, K, V, sc)
@@ -130,6 +132,14 @@ def test_mfma_bf16_padded_head_dimension(layout, d):
 
 
 @pytest.mark.parametrize("layout", [sa.CONTIGUOUS, sa.STRIPED])
+@pytest.mark.parametrize("d", [100, 64, 72, 4, 124, 112, 116, 128])
+def test_mfma_bf16_head_dimensions_in_128_row_workgroups(layout, d):
+    # the same on launches of more than 256 row tiles (two heads take the split kernel)
+    assert routes.forward(routes.args(256, d, 33, N=4, layout=layout)) == "128 rows"
+    _check_ring(1, 33, 1024, d, 4, layout, torch.bfloat16, seed=1000 + d, use_driver=True)
+
+
+@pytest.mark.parametrize("layout", [sa.CONTIGUOUS, sa.STRIPED])
 @pytest.mark.parametrize("B,H,S,d,N", [
     (1, 2, 1024, 256, 4),     # two 128-column halves of K and V per tile
     (2, 1, 2048, 256, 2),     # c = 1024: unmasked tiles before the diagonal
@@ -154,27 +164,32 @@ def test_mfma_matches_generic_kernel_on_large_scores():
     _check_ring(1, 1, 512, 128, 2, sa.STRIPED, torch.bfloat16, seed=5, scale=1.0)
 
 
+@pytest.mark.parametrize("H", [2, 33])         # split, 128-row workgroups
 @pytest.mark.parametrize("layout", [sa.CONTIGUOUS, sa.STRIPED])
-def test_mfma_scores_far_above_the_running_reference(layout):
+def test_mfma_scores_far_above_the_running_reference(layout, H):
     # q.k of magnitude ~ 50-250 nats with scale 1: exp2 of a score against a reference that
     # lags behind overflows fp32, and every later block may bring a much larger maximum; the
     # kernel must notice from the row sums, redo the sub-tile against its row maximum and
     # stay within tolerance (LSE ~ 200: the 1e-3 bound is 40 ulp of fp32 there)
-    B, H, S, d, N = 1, 2, 1024, 128, 4
+    B, S, d, N = 1, 1024, 128, 4
+    assert routes.forward(routes.args(S // N, d, H, N=N, layout=layout)) == ("split" if H == 2 else "128 rows")
     Q, K, V = inputs.qkv(B, H, S, d, 4242, torch.bfloat16)
     Q, K = (Q * 2).to(torch.bfloat16), (K * 2).to(torch.bfloat16)
     O, LSE = hp.ring_forward_gpu(Q.cuda(), K.cuda(), V.cuda(), N, layout, 1.0, True)
     torch.cuda.synchronize()
+    O, LSE = hp.some_heads(O, LSE)
     Oh = hp.from_device_order_host(O.cpu().numpy(), N, layout)
     Lh = hp.from_device_order_host(LSE.cpu().numpy(), N, layout)
-    Ow, Lw = hp.oracle_forward(Q, K, V, 1.0)
+    Qs, Ks, Vs = hp.some_heads(Q, K, V)
+    Ow, Lw = hp.oracle_forward(Qs, Ks, Vs, 1.0)
     assert np.isfinite(Oh).all() and np.isfinite(Lh).all()
     assert float(np.max(Lw)) > 150.0                      # the case is what it claims to be
     assert hp.max_abs_err(Oh, Ow) <= 2e-2 and hp.max_abs_err(Lh, Lw) <= 1e-3
     # all-zero queries: every score equals the reference-free value 0, uniform attention
     O2, LSE2 = hp.ring_forward_gpu((Q * 0).cuda(), K.cuda(), V.cuda(), N, layout, 1.0, True)
     torch.cuda.synchronize()
-    Ow2, Lw2 = hp.oracle_forward(Q * 0, K, V, 1.0)
+    O2, LSE2 = hp.some_heads(O2, LSE2)
+    Ow2, Lw2 = hp.oracle_forward(Qs * 0, Ks, Vs, 1.0)
     assert hp.max_abs_err(hp.from_device_order_host(O2.cpu().numpy(), N, layout), Ow2) <= 2e-2
     assert hp.max_abs_err(hp.from_device_order_host(LSE2.cpu().numpy(), N, layout), Lw2) <= 1e-3
 

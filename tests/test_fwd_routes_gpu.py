@@ -15,7 +15,7 @@ from tests import routes
 pytestmark = pytest.mark.gpu
 
 CASES = [
-    # B, H, H_kv, c, d, N: 128-row tiles of all devices' queries
+    # B, H, H_kv, c, d, N: 128-row tiles of all devices' queries (single steps: of one device's)
     (1, 1, 1, 128, 128, 1),         # one block of one tile
     (1, 1, 1, 128, 64, 1),          # (stays with a 128-row tile)
     (1, 2, 2, 129, 64, 2),          # 8, last sub-tile of one row
@@ -62,9 +62,13 @@ def test_rings_against_the_oracle(B, H, Hkv, c, d, N, layout):
             assert hp.max_abs_err(got_l, want_l) <= 1e-3
 
 
-@pytest.mark.parametrize("c,H,d,shape_n", [(256, 2, 64, 2), (640, 13, 128, 1), (512, 32, 64, 1)])
-def test_fused_rotation_like_rotated_queries(c, H, d, shape_n):
+@pytest.mark.parametrize("c,H,d,shape_n,route", [
+    (256, 2, 64, 2, "split"), (640, 13, 128, 1, "split"), (512, 32, 64, 1, "split"), (512, 33, 64, 2, "128 rows"),
+    (640, 27, 128, 2, "128 rows"),
+])
+def test_fused_rotation_like_rotated_queries(c, H, d, shape_n, route):
     # on both sides of the rule; the two sine evaluations round a few queries to neighbouring bf16 values
+    assert routes.forward(routes.args(c, d, H, B=shape_n)) == route
     dt, f32 = torch.bfloat16, dict(dtype=torch.float32, device="cuda")
     q, k, v = (inputs.gaussian((shape_n, H, c, d), 100 + i, dt).cuda() for i in range(3))
     pos = (torch.arange(c, dtype=torch.int32) * 8 + 1).cuda()

@@ -10,6 +10,7 @@ import torch
 from paper_2311_09431_amd import binding as sa
 from paper_2311_09431_amd import inputs
 from tests import helpers as hp
+from tests import routes
 
 pytestmark = pytest.mark.gpu
 
@@ -261,11 +262,46 @@ def test_numbers_beyond_the_largest_bf16(route, block):
 
 @np_quiet
 @pytest.mark.parametrize("layout", [sa.STRIPED, sa.CONTIGUOUS])
-@pytest.mark.parametrize("route", [(2, 1, 160, 64, BF16), (1, 1, 128, 128, BF16), (1, 1, 130, 136, BF16)])
+@pytest.mark.parametrize("route", [(2, 1, 160, 64, BF16), (1, 1, 128, 128, BF16), (1, 1, 130, 136, BF16),
+                                   (260, 130, 160, 64, BF16), (260, 260, 128, 128, BF16), (260, 260, 130, 100, BF16)])
 def test_the_128_row_kernels_leave_no_number_in_the_lse_of_such_a_row(route, layout):
-    # O of a row with a NaN or +inf score is NaN there too; its LSE would pass for that of a row without keys
+    # O of a row with a NaN or +inf score is NaN there too; its LSE would pass for that of a row without keys.
+    # (Few heads up to 128 columns: the split kernel, but for a block of one tile and d 64.)
+    H, Hkv, c, d, _ = route
+    if H == 260:
+        for N in (1, 2):
+            assert routes.forward(routes.args(c, d, H, Hkv, N=N, layout=layout)) == "128 rows"
     kinds = lambda t, at: {n: f for n, f in swallowed(t, at).items() if "-inf" not in n}
     for N in (1, 2):
         check_ring(route, layout, N, kinds, False, 2e-2)
     for block in BLOCKS:
         check_forward_step(route, block, kinds, 2e-2)
+
+
+@np_quiet
+@pytest.mark.parametrize("layout", [sa.STRIPED, sa.CONTIGUOUS])
+@pytest.mark.parametrize("name", ["q", "k", "v", "g"])
+def test_both_column_halves_in_a_workgroup_as_side_by_side(layout, name):
+    # above 128 columns, bf16: what a NaN reaches in dQ, dK and dV is the same whether a launch is large enough for the
+    # workgroups that hold both column halves of dK and dV or each head is a launch of its own
+    H, c, d = 260, 160, 144
+    t, f32 = draw(H, H, c, d, BF16), dict(dtype=F32, device="cuda")
+    t[name][0, :, 70, 130] = NAN
+    x = {n: t[n].cuda() for n in ("q", "k", "v", "g", "lse", "delta")}
+    x["lse"] += 4.0
+    play = lambda y, out: sa.sa_attn_step_bwd(y["q"], y["k"], y["v"], y["g"], y["lse"], y["delta"], *out, 1, 0, 2, layout,     # noqa: E731
+                                              sa.shard_shape(y["q"], c, y["lse"]))
+    whole = [torch.zeros(1, H, c, d, **f32) for _ in range(3)]
+    play(x, whole)
+    for h in (0, 7, H - 1):
+        single = [torch.zeros(1, 1, c, d, **f32) for _ in range(3)]
+        play({n: y[:, h:h + 1] for n, y in x.items()}, single)
+        torch.cuda.synchronize()
+        for got, want in zip(whole, single):
+            got = got[:, h:h + 1]
+            nan = torch.isnan(want)
+            assert bool(nan.any()) or name != "q" and name != "k"
+            assert torch.equal(torch.isnan(got), nan)
+            # (products of one head summed in another order, in fp32)
+            ok = ~nan
+            assert float((got[ok] - want[ok]).norm()) <= 1e-5 * float(want[ok].norm())

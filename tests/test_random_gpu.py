@@ -9,6 +9,7 @@ import torch
 from paper_2311_09431_amd import binding as sa
 from paper_2311_09431_amd import inputs
 from tests import helpers as hp
+from tests import routes
 
 pytestmark = pytest.mark.gpu
 
@@ -50,6 +51,7 @@ def test_random_shapes_forward_and_backward(case):
     sa.sa_ring_fwd(Qp, Kp, Vp, O, LSE, N, layout, shape)
     sa.sa_ring_bwd(Qp, Kp, Vp, Gp, O, LSE, delta, *grads, N, layout, shape)
     torch.cuda.synchronize()
+    Q, K, V, dO, O, LSE, *grads = hp.some_heads(Q, K, V, dO, O, LSE, *grads)
     back = lambda t: hp.from_device_order_host(t.cpu().numpy(), N, layout)
     bf16 = dtype == torch.bfloat16
     Ow, Lw = hp.oracle_forward(Q, K, V, sc)
@@ -57,6 +59,33 @@ def test_random_shapes_forward_and_backward(case):
     assert hp.max_abs_err(back(LSE), Lw) <= (1e-3 if bf16 else 1e-5)
     for g, w in zip(grads, hp.oracle_backward(Q, K, V, dO, sc)):
         hp.check_grad("gradient", back(g), w, bf16)
+
+
+def _many_head_cases(n, seed):
+    """Launches of more than 256 row tiles on both sides: none takes the split kernels."""
+    rng = np.random.default_rng(seed)
+    out = []
+    while len(out) < n:
+        N, c = int(rng.integers(1, 4)), int(rng.integers(128, 400))
+        d = int(rng.choice([128, 100, 64, 96, 32, 120, 36, 256, 136]))
+        if rng.random() < 0.4:
+            c = c // 128 * 128
+        while (c * d * 2) % 16:
+            c += 1
+        tiles = (c + 127) // 128 * N
+        H = 256 // tiles + int(rng.integers(1, 8))
+        layout = sa.STRIPED if rng.random() < 0.6 else sa.CONTIGUOUS
+        out.append((1, H, c, N, d, torch.bfloat16, layout, None if rng.random() < 0.5 else float(rng.uniform(0.02, 0.3)),
+                    int(rng.integers(1, 10 ** 6))))
+    return out
+
+
+@pytest.mark.parametrize("case", _many_head_cases(12, 94312), ids=lambda c: "B%dH%dc%dN%dd%d" % c[:5])
+def test_random_shapes_of_many_heads(case):
+    B, H, c, N, d, dtype, layout = case[:7]
+    a = routes.args(c, d, H, N=N, layout=layout)
+    assert routes.forward(a) == routes.backward(a) == "128 rows"
+    test_random_shapes_forward_and_backward(case)
 
 
 def _grouped_cases(n, seed):

@@ -8,6 +8,7 @@ from oracle import striped_attention as orc
 from paper_2311_09431_amd import binding as sa
 from paper_2311_09431_amd import inputs
 from tests import helpers as hp
+from tests import routes
 
 pytestmark = pytest.mark.gpu
 
@@ -99,13 +100,15 @@ def test_striped_ring_attention_on_rotated_inputs():
 
 
 @pytest.mark.parametrize("layout", [sa.CONTIGUOUS, sa.STRIPED])
-@pytest.mark.parametrize("d", [128, 64, 256])
-def test_query_rotation_fused_into_the_forward_step(layout, d):
+@pytest.mark.parametrize("d,H,route", [(128, 2, "split"), (64, 2, "split"), (256, 2, "128 rows"), (128, 65, "128 rows"),
+                                       (64, 65, "128 rows")])
+def test_query_rotation_fused_into_the_forward_step(layout, d, H, route):
     # sa_attn_step_fwd_rope rotates the query rows as it loads them; keys are rotated once per
     # shard by sa_rope.  Against the oracle: rotate in fp64, round the rotated queries to bf16
     # (the precision in which the kernel hands them to the matrix cores), attention on that.
-    B, H, S, N = 2, 2, 1024, 4
+    B, S, N = 2, 1024, 4
     c = S // N
+    assert routes.forward(routes.args(c, d, H, B=B, layout=layout)) == route
     Q, K, V = inputs.qkv(B, H, S, d, 70 + d, torch.bfloat16)
     ids = np.arange(S, dtype=np.int32) * 700 + 3            # positions up to 7 * 10^5
     pos = torch.from_numpy(ids).cuda()
@@ -135,6 +138,8 @@ def test_query_rotation_fused_into_the_forward_step(layout, d):
                     sa.sa_attn_step_fwd(r(Qr, j), r(Kr, k), r(Vp, k), r(O, j), r(LSE, j), j, k, N, layout, shape)
         outs.append((O, LSE))
     torch.cuda.synchronize()
+    outs = [hp.some_heads(*x) for x in outs]
+    Q, Kr, V = hp.some_heads(Q, Kr, V)
     scale = 1.0 / np.sqrt(d)
     q_rot = torch.from_numpy(orc.rope(inputs.to_f64(Q), ids)).to(torch.bfloat16)
     k_rot = hp.from_device_order_host(inputs.to_f64(Kr), N, layout)       # the bits the kernel read

@@ -8,6 +8,7 @@ import torch
 from paper_2311_09431_amd import binding as sa
 from paper_2311_09431_amd import inputs
 from tests import helpers as hp
+from tests import routes
 
 pytestmark = pytest.mark.gpu
 
@@ -28,6 +29,9 @@ def _empty_like_view(B, H, S, d, dtype):
     (2, 3, 1024, 128, 4, torch.bfloat16, True),    # matrix-core kernels, row pitch 3 * 256 bytes
     (1, 2, 768, 100, 3, torch.bfloat16, False),    # padded head dimension and a row pitch
     (2, 2, 120, 32, 4, torch.float32, True),       # generic kernels
+    (1, 44, 768, 128, 3, torch.bfloat16, True),    # many heads: 128-row workgroups
+    (1, 44, 768, 100, 3, torch.bfloat16, True),
+    (1, 44, 600, 192, 3, torch.bfloat16, True),    # both column halves in a workgroup, ragged (c = 200)
 ])
 def test_seq_major_forward_and_backward(layout, B, H, S, d, N, dtype, use_driver):
     c = S // N
@@ -71,6 +75,7 @@ def test_seq_major_forward_and_backward(layout, B, H, S, d, N, dtype, use_driver
         sa.sa_finalize(O[:, :, j * c:], out[:, :, j * c:], shape)
     torch.cuda.synchronize()
 
+    Q, K, V, dO, O, LSE, out, *grads = hp.some_heads(Q, K, V, dO, O, LSE, out, *grads)
     scale = 1.0 / np.sqrt(d)
     Oref, Lref = hp.oracle_forward(Q, K, V, scale)
     gref = hp.oracle_backward(Q, K, V, dO, scale)
@@ -96,14 +101,17 @@ def test_rows_that_overlap_are_rejected():
         assert e.value.status in (-2, -6)
 
 
+@pytest.mark.parametrize("H", [2, 44])         # split kernels (column halves side by side), 128-row workgroups (both halves)
 @pytest.mark.parametrize("layout", [sa.CONTIGUOUS, sa.STRIPED])
 @pytest.mark.parametrize("d,pitch", [(100, 128), (64, 128), (36, 40), (124, 136), (192, 256), (136, 144)])
-def test_gap_between_rows_may_hold_anything(layout, d, pitch):
+def test_gap_between_rows_may_hold_anything(layout, d, pitch, H):
     # Rows of d elements at a pitch of more than d, the gap filled with NaN (what an
     # uninitialised buffer may hold): the matrix-core kernels compute 64, 112, 128 or 256 columns
     # and must neither read the gap into a product nor write into it.
-    B, H, S, N = 1, 2, 768, 3
+    B, S, N = 1, 768, 3
     c = S // N
+    a = routes.args(c, d, H, N=N, layout=layout)
+    assert routes.forward(a) == routes.backward(a) == ("split" if H == 2 and d <= 128 else "128 rows")
     Q, K, V, dO = (x.cuda() for x in inputs.qkv(B, H, S, d, 900 + d, torch.bfloat16, with_dout=True))
 
     def padded(x, dtype, fill):
@@ -132,6 +140,7 @@ def test_gap_between_rows_may_hold_anything(layout, d, pitch):
     torch.cuda.synchronize()
     for st in (O_store,) + tuple(g_stores):
         assert bool(torch.isnan(st[..., d:]).all())          # the gap is left alone
+    Q, K, V, dO, O, LSE, *grads = hp.some_heads(Q, K, V, dO, O, LSE, *grads)
     scale = 1.0 / np.sqrt(d)
     Oref, Lref = hp.oracle_forward(Q, K, V, scale)
     back = lambda t: hp.from_device_order_host(t.contiguous().cpu().float().numpy(), N, layout)

@@ -15,6 +15,7 @@ import torch
 from paper_2311_09431_amd import binding as sa
 from paper_2311_09431_amd import inputs
 from tests import helpers as hp
+from tests import routes
 
 pytestmark = pytest.mark.gpu
 
@@ -47,8 +48,22 @@ def _ring_fwd(Qp, Kp, Vp, N, layout, c, bq, bk):
 @pytest.mark.parametrize("S,N,bq,bk", CASES)
 def test_tiled_ring_gives_the_same_bits(layout, S, N, bq, bk):
     # the padded, the 64-column, the two-half and the full head dimension
-    B, H, d = 1, 2, {256: 100, 1024: 64, 512: 256}.get(bq, 128)
-    c = S // N
+    _same_bits(layout, S, N, bq, bk, 2, {256: 100, 1024: 64, 512: 256}.get(bq, 128))
+
+
+@pytest.mark.parametrize("layout", [sa.CONTIGUOUS, sa.STRIPED])
+@pytest.mark.parametrize("d,H", [(64, 33), (100, 17), (128, 17), (256, 17)])
+@pytest.mark.parametrize("S,N,bq,bk", [CASES[0], CASES[1], CASES[4]])
+def test_tiled_ring_of_128_row_workgroups_gives_the_same_bits(layout, S, N, bq, bk, d, H):
+    # more than 256 tiles of rows and of keys: 128-row workgroups both ways, above 128 columns those that hold both
+    # halves of dK and dV (two heads take the split kernels, or the column halves side by side)
+    a = routes.args(S // N, d, H, N=N, layout=layout)
+    assert routes.forward(a) == routes.backward(a) == "128 rows"
+    _same_bits(layout, S, N, bq, bk, H, d)
+
+
+def _same_bits(layout, S, N, bq, bk, H, d):
+    B, c = 1, S // N
     Q, K, V, dO = (x.cuda() for x in inputs.qkv(B, H, S, d, S + bq + bk, torch.bfloat16, with_dout=True))
     Qp, Kp, Vp, dOp = (hp.to_device_order(x, N, layout) for x in (Q, K, V, dO))
     O0, L0, shape = _ring_fwd(Qp, Kp, Vp, N, layout, c, 0, 0)
