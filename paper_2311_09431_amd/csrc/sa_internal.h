@@ -87,7 +87,7 @@ struct StepArgs {
 
 // The workgroups of a launch carry uneven work: triangular blocks, or contiguous blocks of
 // several query devices (a key shard is seen by the devices from its own on).
-inline bool uneven(const StepArgs& a) { return a.layout == SA_STRIPED || a.n_q > 1 || a.q_dev == a.kv_dev; }
+__host__ __device__ inline bool uneven(const StepArgs& a) { return a.layout == SA_STRIPED || a.n_q > 1 || a.q_dev == a.kv_dev; }
 
 // Order of a backward launch of n_keys key-owning and n_queries query-owning workgroups, each sequence
 // heaviest first: `first` key-owning ones, whose walks are longer than the longest query-owning one, then the

@@ -548,18 +548,20 @@ __device__ inline void add_rows(float* row, float4 (&x)[blocks_of(DP)], const ch
 // in chunks of as many ranks as make a multiple of 8 workgroups, an XCD gets the same heads (and at most two others'
 // shares) of every chunk, and its L2 holds what they stream.  Head by head, an odd number of heads has every XCD
 // stream all of them: d 64, triangular, 25 heads of 2048 rows 125 -> 75 us, 15 of 4096 260 -> 145, 7 of 8192 360 ->
-// 242, 128 on 32 of 2048 343 -> 315.  Few ranks, where a chunk is a large part of the order, and those behind
-// the last whole chunk stay head by head (9 heads of 500 rows, d 100, in chunks 15.3 -> 16.1).  (Backward only: the
-// forward gained as often as it lost, full blocks, d 128, 15 heads of 1024 28.0 -> 21.7, 3 of 5000 60.8 -> 63.7.)
-__device__ inline void decode_near(int linear, int n_ranks, int n_heads, int& rank, int& head) {
-    const int chunk = n_heads % 8 == 0 ? 1 : n_heads % 4 == 0 ? 2 : n_heads % 2 == 0 ? 4 : 8;
-    const int size = chunk * n_heads, i = linear / size, j = linear - i * size;
-    if ((i + 1) * chunk > n_ranks || n_ranks < 4 * chunk) {
+// 242, 128 on 32 of 2048 343 -> 315.  Small launches of uneven work with few ranks, where a chunk is a large part of
+// the order, and ranks behind the last whole chunk stay head by head (9 heads of 500 rows, d 100, in chunks 15.3 ->
+// 16.1).  (Backward only: the forward gained as often as it lost, full blocks, d 128, 15 heads of 1024 28.0 -> 21.7, 3
+// of 5000 60.8 -> 63.7.)
+__device__ inline void decode_near(int linear, int n_ranks, int n_heads, bool uneven, int& rank, int& head) {
+    const int chunk = n_heads % 8 == 0 ? 1 : n_heads % 4 == 0 ? 2 : n_heads % 2 == 0 ? 4 : 8, size = chunk * n_heads;
+    const bool by_head = uneven && n_ranks < 4 * chunk && n_ranks * n_heads < 1024;
+    const int i = by_head ? n_ranks : linear / size;
+    if ((i + 1) * chunk > n_ranks) {
         rank = linear / n_heads;
         head = linear - rank * n_heads;
         return;
     }
-    const int at = j % 8 * (size / 8) + j / 8;
+    const int j = linear - i * size, at = j % 8 * (size / 8) + j / 8;
     head = at / chunk;
     rank = i * chunk + at - head * chunk;
 }
@@ -603,7 +605,7 @@ __device__ inline void bwd_dq(const StepArgs& p, int n_tiles, int linear, char* 
     const Lane<DP> ln;
     const int n = ln.n, h = ln.h;
     int rank, bh, dev_rank;
-    decode_near(linear, n_tiles * p.n_q, p.B * p.H, rank, bh);
+    decode_near(linear, n_tiles * p.n_q, p.B * p.H, uneven(p), rank, bh);
     decode_rank(rank, n_tiles, p.n_q, p.layout, rank, dev_rank);
     const int q0 = (n_tiles - 1 - rank) * OWN, dev_i = p.n_q - 1 - dev_rank, dev = p.q_dev + dev_i;
     const int b = bh / p.H, hd = bh - b * p.H, d = p.d;
@@ -763,7 +765,7 @@ __device__ inline void bwd_dkdv(const StepArgs& p, int n_tiles, int linear, char
     const Lane<DP> ln;
     const int n = ln.n, h = ln.h, wave = ln.wave;
     int tile, bh, dev_i;                                // low key tiles see most queries: first
-    decode_near(linear, n_tiles * p.n_kv, p.B * p.H_kv, tile, bh);
+    decode_near(linear, n_tiles * p.n_kv, p.B * p.H_kv, uneven(p), tile, bh);
     decode_rank(tile, n_tiles, p.n_kv, p.layout, tile, dev_i);
     const int k0 = tile * OWN, dev = p.kv_dev + dev_i;
     const int b = bh / p.H_kv, kvh = bh - b * p.H_kv, group = p.H / p.H_kv, d = p.d;
@@ -1048,26 +1050,28 @@ bool fwd_split_wanted(const StepArgs& a) {
     return tiles <= 256 && uneven(a) && walk >= (a.d <= 112 ? 4096 : 8192);
 }
 hipError_t launch_fwd_split(const StepArgs& a, hipStream_t st) { return run(a, FWD, st); }
-// Backward step, by 128-row tiles of all keys: up to 64 always: 16 heads of 512 rows 27 / 19 (full 27 / 20), one of
-// 8192 201 / 88 (207 / 154), 32 heads on 8 of 1024 115 / 60 (141 / 87), ring of 4 x 1024, 2 heads 112 / 54.  128,
-// triangular: 16 heads of 1024 39.6 / 41.7, 8 of 2048 62 / 54, 2 of 8192 200 / 143, 32 on 8 of 2048 211 / 170,
-// ring of 4 x 256, 16 heads 42 / 48, of 4 x 512, 8 heads 67 / 60; full 2 of 8192 233 / 257, 32 on 8 of 2048 313 /
-// 281; 256: 8 of 4096 137 / 160, 32 on 8 of 4096 500 / 574.  Up to 64 columns two workgroups fit a compute unit.  Full
-// blocks, 128 tiles: 32 heads of 512 19.6 / 18.3, but at d 32 16.1 / 17.0 (20 of 512 15.2 / 13.4), 16 of 1024 29.2 /
-// 25.0, 2 of 8192 147 / 135; 256: 46.4 / 45.8, 254 / 263.  Triangular, 256: 32 of 1024 40.6 / 36.4, 8 of 4096 87 / 78,
-// ring of 4 x 1024, 32 on 8 369 / 300; up to 512: 24 of 1300 51 / 35, 31 of 2048 99 / 96, 8 of 8192 308 / 287, 5 of 12500
-// 435 / 391, 64 on 16 of 4096 606 / 611; but 32 of 2048, d 32, 80 / 82, contiguous ring of 2 x 1024, 32 heads, 92 / 96.
-// 64 heads of 200 (128 tiles) 11.0 / 13.1.
+// Backward step, by 128-row tiles of all keys ("tiles") and key/value heads: four times the workgroups walk a quarter
+// of the rows each, which pays while a head has many of them; a last 128-row tile that is nearly empty counts for it,
+// so the heads are weighed by the square of what 32-row tiles save there.  Several hundred drawn shapes a line, geometric mean
+// (worst) of 128-row time / this one:
+//  * up to 64 tiles 1.2 to 2.3; full blocks above 64 columns 1.2 to 1.4 (1.0) up to 40 heads, beyond 1.0 (0.8)
+//  * 65 to 128 tiles above 64 columns: triangular, walks of 2048 rows of the group and more, up to 8 heads 1.4 to 2.1
+//    (1.2), 16 1.2 (1.05), 20 1.1 (0.9), 30 0.9 (0.8); full with groups of four and more, up to 16 heads 1.5 (1.0), 24 1.3
+//    (1.0), 40 1.15 (0.9), beyond 0.9 (0.7); without groups 2 heads of 8192 rows 233 / 257 us
+//  * 65 to 128 tiles up to 64 columns, where two workgroups fit a compute unit: 1.2 to 2.5 (1.0), full blocks of short
+//    walks excepted (32 heads of 512 rows 19.6 / 18.3 us, but at d 32 16.1 / 17.0, 20 of 512 15.2 / 13.4)
+//  * 129 to 512 tiles up to 64 columns, triangular: up to 24 heads 1.15 to 1.5 (1.05), 56 1.1 (0.94), 100 1.0 (0.85),
+//    beyond 0.9 (0.7); 32 heads of 2048 rows (512 tiles) 99 / 99, d 32 80 / 82; full, 256: 46.4 / 45.8, 254 / 263
+//  * 256 tiles above 64 columns: 8 heads of 4096 137 / 160, 32 on 8 of 4096 500 / 574
 bool bwd_split_wanted(const StepArgs& a) {
-    const int64_t keys = (int64_t)((a.c + 127) / 128) * a.B * a.n_kv * a.H_kv, group = a.H / a.H_kv;
+    const int64_t t128 = (a.c + 127) / 128, t32 = (a.c + 31) / 32, heads = (int64_t)a.B * a.H_kv, group = a.H / a.H_kv;
+    const int64_t keys = t128 * a.n_kv * heads, walk = (int64_t)a.c * a.n_q * group;
+    auto up_to = [&](int64_t most) { return heads * t32 * t32 <= most * 16 * t128 * t128; };
     if (a.d > TD || !rows_in_reach(a)) return false;
-    const int64_t walk = (int64_t)a.c * a.n_q * group;
-    if (keys <= 64) return true;
-    if (a.d <= 64) {
-        if (!uneven(a)) return keys <= 128 && walk >= (a.d <= 32 ? 6 : 4) * keys;
-        return keys <= 256 ? walk >= 4 * keys : keys <= 512 && walk > 4 * keys;
-    }
-    return keys <= 128 && (uneven(a) ? walk >= 2048 : group >= 4);
+    if (keys <= 64) return a.d <= 64 || uneven(a) || up_to(40);
+    if (a.d > 64) return keys <= 128 && (uneven(a) ? walk >= 2048 && up_to(16) : group >= 4 && up_to(24));
+    if (!uneven(a)) return keys <= 128 && walk >= (a.d <= 32 ? 6 : 4) * keys;
+    return up_to(56) && (keys <= 256 ? walk >= 4 * keys : keys <= 512 && walk > 4 * keys);
 }
 hipError_t launch_bwd_split(const StepArgs& a, hipStream_t st) { return run(a, BWD, st); }
 

@@ -102,6 +102,8 @@ SPLIT = [
     (1, 24, 12, 1300, 60),      # 132 (triangular only), grouped heads
     (1, 7, 7, 2100, 100),       # 119 (triangular only)
     (1, 32, 8, 1030, 128),      # 72, four heads per key/value head
+    (1, 104, 13, 640, 72),      # 65, eight heads per key/value head, ranks in chunks of eight and four left over
+    (1, 110, 55, 384, 64),      # 165 (triangular only), few ranks: in chunks all the same
 ]
 
 
@@ -110,7 +112,7 @@ SPLIT = [
 def test_larger_split_launches(B, H, Hkv, c, d, q_dev, kv_dev, layout):
     a = routes.args(c, d, H, Hkv, B, q_dev=q_dev, kv_dev=kv_dev, layout=layout)
     full = layout == sa.CONTIGUOUS
-    assert routes.backward(a) == ("128 rows" if full and (c, H) not in ((513, 20), (1030, 32)) else "split")
+    assert routes.backward(a) == ("128 rows" if full and c not in (513, 1030, 640) else "split")
     if not full:
         test_step_against_the_oracle(B, H, Hkv, c, d, q_dev, kv_dev, layout)
     if routes.backward(a) != "split":

@@ -53,6 +53,11 @@ def test_split_rules_at_their_edges():
     assert bwd(20, 512, 32, sa.CONTIGUOUS) == "split"
     assert bwd(32, 2048, 64) == "128 rows" and bwd(31, 2048, 64) == "split" and bwd(32, 1024, 64) == "split"
     assert bwd(32, 1024, 64, sa.CONTIGUOUS, N=2) == "128 rows"
+    # key/value heads, a nearly empty last tile counting for them
+    assert bwd(40, 128, 96, sa.CONTIGUOUS) == "split" and bwd(41, 128, 96, sa.CONTIGUOUS) == "128 rows" and bwd(64, 128, 96) == "split"
+    assert bwd(64, 768, 128, Hkv=16) == "split" and bwd(68, 768, 128, Hkv=17) == "128 rows" and bwd(68, 672, 128, Hkv=17) == "split"
+    assert bwd(96, 512, 128, sa.CONTIGUOUS, Hkv=24) == "split" and bwd(100, 512, 128, sa.CONTIGUOUS, Hkv=25) == "128 rows"
+    assert bwd(224, 512, 64, Hkv=56) == "split" and bwd(228, 512, 64, Hkv=57) == "128 rows" and bwd(228, 416, 64, Hkv=57) == "split"
     fwd = lambda H, c, d, Hkv=None: routes.forward(routes.args(c, d, H, Hkv, layout=sa.CONTIGUOUS))               # noqa: E731
     assert fwd(15, 1024, 128) == "128 rows" and fwd(15, 1024, 64) == "split" and fwd(14, 1152, 128) == "split"
     assert fwd(9, 1700, 128) == "split" and fwd(15, 1024, 128, 3) == "split"
