@@ -206,3 +206,18 @@ def test_rope_argument_errors():
 def test_device_props_are_those_of_an_mi355x():
     cus, khz, mem = sa.sa_device_props()
     assert cus == 256 and 1_000_000 <= khz <= 3_000_000 and mem > 200 * 2 ** 30
+
+
+def test_the_stream_handle_without_torchs_own_functions(monkeypatch):
+    # a torch without them falls back to the stream object
+    class Stream:
+        cuda_stream = 0x5150
+
+    monkeypatch.setattr(sa.torch.cuda, "current_stream", lambda: Stream)
+    for missing in ("_raw_stream", "_device"):
+        with monkeypatch.context() as m:
+            m.setattr(sa, "_raw_stream", lambda device: 0xd0 + device)
+            m.setattr(sa, "_device", lambda: 3)
+            assert sa._stream() == 0xd3
+            m.setattr(sa, missing, None)
+            assert sa._stream() == 0x5150
