@@ -256,7 +256,6 @@ __device__ __forceinline__ void mfma_vgpr_acc(f32x16& acc, bf16x8 a, bf16x8 b, b
     else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));
 }
 
-
 // Workgroup order of a 1-D grid over (tile rank, batch*head), rank 0 = heaviest tile.
 // Large grids: heads are taken in groups of 8; inside a group the index runs over
 // heads fastest and tile ranks slowest, so (i) every group runs heaviest-first and

@@ -234,7 +234,7 @@ __device__ inline void load_old(float4 (&x)[share_of(DP, WAVES)], const float* r
     }
 }
 // EXACT: rows that are done over one by one (f32_rows.h): each wavefront puts its mask beside its
-// partial accumulators, and after the barrier takes every fourth of the rows that one of them names
+// partial accumulators, and after the barrier takes every WAVES-th of the rows that one of them names
 __device__ inline void put_odd(uint32_t* masks, bool odd, int wave, int lane) {
     const uint32_t rows = row_mask(odd);
     if (lane == 0) masks[wave] = rows;

@@ -29,7 +29,8 @@ CASES = [
     (1, 1, 161, 256, 2, torch.float32),
     (1, 1, 260, 100, 2, torch.float32),
     (4, 64, 33, 32, 2, torch.float32),          # 256 heads: three terms
-    (4, 64, 65, 64, 2, torch.bfloat16),         # ... 128 rows per workgroup (forward steps)
+    (4, 64, 65, 64, 2, torch.bfloat16),         # (short blocks on the bf16 matrix cores)
+    (4, 128, 65, 32, 2, torch.bfloat16),        # ... 128 rows per workgroup (forward steps)
     (2, 128, 40, 128, 2, torch.float32),
     (2, 128, 36, 200, 2, torch.float32),        # ... 128 rows per workgroup
     (1, 128, 130, 64, 2, torch.float32),        # two row tiles per head
