@@ -19,12 +19,13 @@ LIB = os.path.join(HERE, "libstriped_attn.so")
 OBJ_DIR = os.path.join(ROOT, "_build")
 
 SOURCES = ["api.hip", "permute.hip", "elementwise.hip", "f32_step.hip", "fwd_mfma.hip",
-           "bwd_mfma.hip", "split_mfma.hip", "f32x3_step.hip", "rows_step.hip"]
+           "bwd_mfma.hip", "split_mfma.hip", "f32x3_step.hip", "f32x3_split.hip", "rows_step.hip"]
 
 # Flags of single sources.  f32x3_step: score tiles are read by vector instructions right after
 # their products, so MFMA results stay out of the accumulation registers (forward 2.20 -> 2.10 ms,
 # backward 6.7 -> 6.1 ms for 16 heads, d 128, 4 x 2048 tokens).
-SOURCE_FLAGS = {"f32x3_step.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
+SOURCE_FLAGS = {"f32x3_step.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
+                "f32x3_split.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
 
 # Sources with matrix instructions in asm statements, and their kernels whose accumulators are registers by
 # number: the assembly of these is looked over (asm_check.py).

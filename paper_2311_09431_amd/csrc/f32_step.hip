@@ -1,16 +1,13 @@
 // Ring-step kernels on the CDNA4 fp32 matrix cores (v_mfma_f32_32x32x2_f32: fp32 operands, fp32
 // accumulation): any head dimension up to 256, any block size, fp32 or bf16 inputs.  They serve
-// the fp32 configuration (error budget 1e-5, so no reduced-precision products and the accurate
+// fp32 storage above 128 columns (error budget 1e-5, so no reduced-precision products and the accurate
 // expf / logf) and the bf16 shapes the bf16 matrix-core kernels do not take (widened to fp32
-// on the way into LDS, so their probabilities are not rounded either).  Fuller fp32 launches go to
-// f32x3_step.hip, most short bf16 blocks to split_mfma.hip.
+// on the way into LDS, so their probabilities are not rounded either).  fp32 up to 128 columns goes to
+// f32x3_step.hip and f32x3_split.hip, most short bf16 blocks to split_mfma.hip.
 //
-// Measured against kernels with one wavefront per row and serial dot products on the vector ALU:
-// whole ring forward + backward, 4 x 64 tokens, one head, fp32, 2.68 -> 0.097 ms (0.53 with one launch
-// per block and kernel; a launch now holds all blocks of the devices it plays, a workgroup walks the
-// other side's shards in turn, and the backward's two kinds of workgroups share a launch); a
-// full forward block of 2048 rows, 8 key/value heads for 32, d 128, 14.6 ms, backward 63, where the
-// split form here takes 2.7 backward.
+// Measured against kernels with one wavefront per row and serial dot products on the vector ALU: a full
+// forward block of 2048 rows, 8 key/value heads for 32, d 128, fp32, 14.6 ms, backward 63, where the split form
+// here takes 2.7 backward.
 //
 // What bounds them: the fp32 matrix cores run at 1/16 of the bf16 rate (64 cycles per
 // instruction, 157 TFLOP/s on the chip), so one instruction leaves room for everything that
@@ -520,20 +517,17 @@ hipError_t run_bwd(const StepArgs& a, hipStream_t st) {
 template <typename T, int DP>
 hipError_t run(const StepArgs& a, bool backward, hipStream_t st) {
     constexpr int MOST = DP > 128 ? 2 : 4;          // what 160 KiB of LDS hold
-    if constexpr (DP <= 128 && sizeof(T) == 4) {      // fuller fp32 launches: f32x3_wanted
-        return backward ? run_bwd<T, DP, MOST>(a, st) : run_fwd<T, DP, MOST>(a, st);
-    } else {
-        const bool split = few_row_tiles(a, backward);
-        if (backward) return split ? run_bwd<T, DP, MOST>(a, st) : run_bwd<T, DP, 1>(a, st);
-        return split ? run_fwd<T, DP, MOST>(a, st) : run_fwd<T, DP, 1>(a, st);
-    }
+    const bool split = few_row_tiles(a, backward);
+    if (backward) return split ? run_bwd<T, DP, MOST>(a, st) : run_bwd<T, DP, 1>(a, st);
+    return split ? run_fwd<T, DP, MOST>(a, st) : run_fwd<T, DP, 1>(a, st);
 }
-template <typename T>
-hipError_t run(const StepArgs& a, bool backward, hipStream_t st) {
-    if (a.d <= 32) return run<T, 32>(a, backward, st);
-    if (a.d <= 64) return run<T, 64>(a, backward, st);
-    if (a.d <= 128) return run<T, 128>(a, backward, st);
-    return run<T, 256>(a, backward, st);
+hipError_t run(const StepArgs& a, int dtype, bool backward, hipStream_t st) {
+    // (fp32 storage up to 128 columns: only rows too far apart for f32x3_split.hip's 32-bit offsets)
+    if (dtype == SA_F32) return run<float, 256>(a, backward, st);
+    if (a.d <= 32) return run<__hip_bfloat16, 32>(a, backward, st);
+    if (a.d <= 64) return run<__hip_bfloat16, 64>(a, backward, st);
+    if (a.d <= 128) return run<__hip_bfloat16, 128>(a, backward, st);
+    return run<__hip_bfloat16, 256>(a, backward, st);
 }
 
 }  // namespace
@@ -541,14 +535,16 @@ hipError_t run(const StepArgs& a, bool backward, hipStream_t st) {
 hipError_t launch_fwd_f32(const StepArgs& a, int dtype, hipStream_t st) {
     if (few_rows_wanted(a, dtype, false)) return launch_few_rows(a, dtype, false, st);
     if (dtype == SA_F32 && f32x3_wanted(a, false)) return launch_f32x3(a, false, st);
+    if (dtype == SA_F32 && f32x3_split_wanted(a, false)) return launch_f32x3_split(a, false, st);
     if (short_exact_wanted(a, dtype, false)) return launch_short_exact(a, false, st);
-    return dtype == SA_F32 ? run<float>(a, false, st) : run<__hip_bfloat16>(a, false, st);
+    return run(a, dtype, false, st);
 }
 hipError_t launch_bwd_f32(const StepArgs& a, int dtype, hipStream_t st) {
     if (few_rows_wanted(a, dtype, true)) return launch_few_rows(a, dtype, true, st);
     if (dtype == SA_F32 && f32x3_wanted(a, true)) return launch_f32x3(a, true, st);
+    if (dtype == SA_F32 && f32x3_split_wanted(a, true)) return launch_f32x3_split(a, true, st);
     if (short_exact_wanted(a, dtype, true)) return launch_short_exact(a, true, st);
-    return dtype == SA_F32 ? run<float>(a, true, st) : run<__hip_bfloat16>(a, true, st);
+    return run(a, dtype, true, st);
 }
 
 }  // namespace sa

@@ -153,6 +153,8 @@ hipError_t launch_fwd_f32(const StepArgs& a, int dtype, hipStream_t st);
 hipError_t launch_bwd_f32(const StepArgs& a, int dtype, hipStream_t st);
 bool f32x3_wanted(const StepArgs& a, bool backward);
 hipError_t launch_f32x3(const StepArgs& a, bool backward, hipStream_t st);
+bool f32x3_split_wanted(const StepArgs& a, bool backward);
+hipError_t launch_f32x3_split(const StepArgs& a, bool backward, hipStream_t st);
 bool fwd_mfma_supported(const StepArgs& a, int dtype);
 bool fwd_mfma_rope_supported(const StepArgs& a, int dtype);
 hipError_t launch_fwd_mfma(const StepArgs& a, hipStream_t st);

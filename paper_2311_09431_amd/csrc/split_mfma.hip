@@ -20,20 +20,16 @@
 // The wavefront that takes a sub-tile is given by the sub-tile's place in the walk without emulated
 // coarse skipping, so summation orders are fixed and the same under it.
 
-#include "f32_rows.h"
-#include "f32_terms.h"
-#include "mfma_tiles.h"
-#include "sa_internal.h"
+#include "split_parts.h"
 
 namespace sa {
 
 namespace {
 
-constexpr int FWD_WAVES = 8, BWD_WAVES = 4, OWN = 32;
+constexpr int FWD_WAVES = 8, BWD_WAVES = 4;
 template <int DP> constexpr int SUB_BYTES = tile_bytes(DP) / 2;              // 32 rows
 template <int DP> constexpr int PIECES = SUB_BYTES<DP> / 1024;               // loads of 1 KiB they take
 template <int DP> constexpr int STAGE_BYTES = 2 * SUB_BYTES<DP>;             // of both streamed operands
-constexpr int STAT_BYTES = 512;                                              // 32 LSE, 32 delta, a load of 256 bytes each
 
 // byte offset (global side) that this lane fetches of piece j of 32 rows
 template <int DP>
@@ -80,10 +76,6 @@ __device__ inline void read_own(bf16x8 (&f)[8], const char* rows, const Lane<DP>
         const bf16x8 x = dt_read_row(rows, ln.arow[ks]);
         f[ks] = PART ? zero_beyond_d(x, ks == part_ks) : x;
     }
-}
-// 32 statistics from row `first` on
-__device__ inline void load_stat(dt_rsrc m, int first, char* lds, int lane) {
-    dt_load_dword(m, 4 * first, lane < 32 ? 4 * lane : DT_OUT_OF_RANGE, lds);
 }
 
 // The loads of a streamed sub-tile.  An instruction's immediate offset counts on both sides, so that the pieces
@@ -141,21 +133,6 @@ struct Loader {
         for (int i = 0; i < 4; ++i) part(i, a, b, row, stage);
     }
 };
-// at most the last n vector memory operations of this wavefront are still on their way
-template <int N>
-__device__ inline void wait_all_but() {
-    asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
-}
-// all LDS reads so far are in registers: what they read may be overwritten
-__device__ inline void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory"); }
-
-__device__ inline f32x16 zero16() {
-    f32x16 z;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) z[r] = 0.f;
-    return z;
-}
-
 template <int DP>
 __device__ inline void read_rows(bf16x8 (&x)[8], const char* rows, const Lane<DP>& ln) {
 #pragma unroll
@@ -191,61 +168,6 @@ __device__ inline void as_operand(const f32x16& w, int g, bf16x8 (&b)[3]) {
     }
 }
 
-// bytes of the wavefronts' accumulators
-template <int DP, int WAVES> constexpr int PARTIAL_BYTES = WAVES * blocks_of(DP) * 16 * 64 * 4;
-
-// Sum of the wavefronts' accumulators through LDS: each writes its own and takes a share of the
-// sum, pieces of 8 columns (4 a lane), so that a row's columns stay together.
-template <int DP>
-__device__ inline void put_partial(char* buf, const f32x16 (&acc)[4], const Lane<DP>& ln) {
-    float4* mine = reinterpret_cast<float4*>(buf) + ln.wave * blocks_of(DP) * 4 * 64;
-#pragma unroll
-    for (int mb = 0; mb < blocks_of(DP); ++mb)
-#pragma unroll
-        for (int g = 0; g < 4; ++g)
-            mine[(mb * 4 + g) * 64 + ln.lane] =
-                make_float4(acc[mb][4 * g], acc[mb][4 * g + 1], acc[mb][4 * g + 2], acc[mb][4 * g + 3]);
-}
-constexpr int share_of(int DP, int waves) { return blocks_of(DP) * 4 / waves; }        // pieces a wavefront takes
-template <int DP, int WAVES>
-__device__ inline int piece_of(int i, const Lane<DP>& ln) { return ln.wave * share_of(DP, WAVES) + i; }
-template <int DP, int WAVES>
-__device__ inline int column_of(int i, const Lane<DP>& ln) { return 8 * piece_of<DP, WAVES>(i, ln) + 4 * ln.h; }
-template <int DP, int WAVES>
-__device__ inline float4 take_sum(const char* buf, int i, const Lane<DP>& ln) {
-    const float4* at = reinterpret_cast<const float4*>(buf) + piece_of<DP, WAVES>(i, ln) * 64 + ln.lane;
-    float4 x = at[0];
-#pragma unroll
-    for (int w = 1; w < WAVES; ++w) {
-        const float4 y = at[w * blocks_of(DP) * 4 * 64];
-        x.x += y.x; x.y += y.y; x.z += y.z; x.w += y.w;
-    }
-    return x;
-}
-// this wavefront's share of the lane's row as it stands (zeros if not wanted): on its way while the
-// partial results meet
-template <int DP, int WAVES>
-__device__ inline void load_old(float4 (&x)[share_of(DP, WAVES)], const float* row, int d, bool wanted, const Lane<DP>& ln) {
-#pragma unroll
-    for (int i = 0; i < share_of(DP, WAVES); ++i) {
-        const int col = column_of<DP, WAVES>(i, ln);
-        x[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (wanted && col < d) x[i] = *reinterpret_cast<const float4*>(row + col);
-    }
-}
-// EXACT: rows that are done over one by one (f32_rows.h): each wavefront puts its mask beside its
-// partial accumulators, and after the barrier takes every WAVES-th of the rows that one of them names
-__device__ inline void put_odd(uint32_t* masks, bool odd, int wave, int lane) {
-    const uint32_t rows = row_mask(odd);
-    if (lane == 0) masks[wave] = rows;
-}
-template <int WAVES>
-__device__ inline uint32_t take_odd(const uint32_t* masks) {
-    uint32_t rows = 0;
-#pragma unroll
-    for (int w = 0; w < WAVES; ++w) rows |= masks[w];
-    return __builtin_amdgcn_readfirstlane(rows);
-}
 // Backward, what makes a row odd: a score that is not finite (z: NaN then), or a dS that is not, which
 // leaves no column of its sum finite.  (Elements of the operands reach one of the two; masked pairs
 // have a dS of 0 * (dP - delta).)
@@ -256,51 +178,6 @@ __device__ inline void look_at(float (&z)[2], const f32x16& s) {
 __device__ inline bool odd_sum(const float (&z)[2], const f32x16 (&ds_sum)[4]) {
     return z[0] + z[1] != 0.f || not_finite<1>(ds_sum);
 }
-// The sub-tiles of 32 keys that one wavefront of a query-owning workgroup takes: those of block kv whose
-// number v is `turn` modulo the number of wavefronts, turn being the wavefront's number less the sub-tiles of
-// the blocks before.
-// Sub-tiles of a block that hold work for queries q0 .. q0 + 31: all of a full block; of a triangular
-// one those up to the last allowed key, or under emulated coarse skipping up to the end of the
-// skip_bk-wide tile that shares an allowed pair with the queries' skip_bq-tall tile.
-struct KeyCursor {
-    int kv, kv_end;             // present block; at kv_end the walk is over
-    int v, n;                   // sub-tile, how many the block has
-    int shift;                  // query a sees the block's keys up to min(a + shift, c - 1)
-    int dev, layout, c, turn, n_full, n_off0, n_off1, n_fine;
-    __device__ KeyCursor(const StepArgs& p, int dev_, int q0, int wave)
-        : kv(p.kv_dev), kv_end(last_shard(p, dev_)), dev(dev_), layout(p.layout), c(p.c), turn(wave) {
-        n_full = (p.c + 31) / 32;
-        int end0 = min(q0 + OWN, p.c), end1 = end0 - 1;
-        if (p.skip_bq > 0) {
-            const int q_hi = (q0 / p.skip_bq + 1) * p.skip_bq - 1;
-            end0 = min(p.c, (q_hi / p.skip_bk + 1) * p.skip_bk);
-            end1 = min(p.c, ((q_hi - 1) / p.skip_bk + 1) * p.skip_bk);
-        }
-        n_off0 = (end0 + 31) / 32;
-        n_off1 = (end1 + 31) / 32;
-        n_fine = q0 / 32 + 1;
-    }
-    // to the wavefront's first sub-tile of block kv
-    template <int WAVES>
-    __device__ void enter() {
-        const bool full = block_kind(dev, kv, layout) == MASK_FULL;
-        const int off = block_off(dev, kv, layout);
-        // (values, not members, to choose from: a choice between addresses keeps the object in memory)
-        const int all = n_full, tri0 = n_off0, tri1 = n_off1, tri = n_fine;
-        n = full ? all : off ? tri1 : tri0;
-        shift = full ? c : -off;
-        v = turn & (WAVES - 1);
-        turn -= full ? all : tri;
-    }
-    template <int WAVES>
-    __device__ void settle() {
-        while (v >= n && kv < kv_end) {
-            ++kv;
-            enter<WAVES>();
-        }
-    }
-};
-
 // ------------------------------------------------------------------ forward
 // Eight wavefronts, two to a SIMD: one's products run beside the other's vector instructions.  One stage each,
 // which is requested anew when the sub-tile has been read into registers.
@@ -309,7 +186,7 @@ constexpr float RESCALE_SUM = 16777216.f;       // 2^24, see fwd_mfma.hip
 template <int DP, bool PART, bool EXACT, bool ROPE = false>
 __global__ void __launch_bounds__(64 * FWD_WAVES, 2)
 fwd_split_kernel(StepArgs p, int n_tiles) {
-    constexpr int MB = blocks_of(DP), KS = ksteps_of(DP), WAVES = FWD_WAVES, N = share_of(DP, WAVES);
+    constexpr int MB = blocks_of(DP), KS = ksteps_of(DP), WAVES = FWD_WAVES;
     // the wavefronts' stages and the owned rows; at the end the statistics and partial results
     constexpr int TILES = WAVES * STAGE_BYTES<DP> > PARTIAL_BYTES<DP, WAVES> ? WAVES * STAGE_BYTES<DP> : PARTIAL_BYTES<DP, WAVES>;
     __shared__ __attribute__((aligned(1024))) char lds[TILES + SUB_BYTES<DP>];
@@ -467,105 +344,12 @@ fwd_split_kernel(StepArgs p, int n_tiles) {
         }
     }
 
-    const float old = p.fresh ? -INFINITY : *L;
-    float* O = p.o + base + (int64_t)a * p.stride_s;
-    float4 o_old[N];
-    load_old<DP, WAVES>(o_old, O, d, !p.fresh && a_own < p.c, ln);
-    // the wavefronts' partial results against a common reference
-    const float l_own = half_wave_sum(l);
-    if (h == 0) {
-        stats[ln.wave * 64 + n] = m;
-        stats[ln.wave * 64 + 32 + n] = l_own;
-    }
-    __syncthreads();
-    float m_all = -INFINITY;
-#pragma unroll
-    for (int w = 0; w < WAVES; ++w) m_all = fmaxf(m_all, stats[w * 64 + n]);
-    const float m_ref = m_all == -INFINITY ? 0.f : m_all;
-    float l_tot = 0.f;
-#pragma unroll
-    for (int w = 0; w < WAVES; ++w)
-        l_tot += stats[w * 64 + 32 + n] * __builtin_amdgcn_exp2f(stats[w * 64 + n] - m_ref);
-    const float f = __builtin_amdgcn_exp2f(m - m_ref);
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[mb][r] *= f;
-    put_partial<DP>(lds, acc, ln);
-    // a row sum that is no positive number although the row sees a key: see f32_rows.h
-    if (EXACT)
-        put_odd(masks, a_own < p.c && (not_finite<MB>(acc) ||
-                                       (!(l_tot > 0.f && l_tot < INFINITY) && sees_a_key(p, dev, a))), ln.wave, ln.lane);
-
-    const float part = l_tot == 0.f ? -INFINITY : fmaf(m_all, LN2_HI, fmaf(m_all, LN2_LO, logf(l_tot)));
-    const float top = fmaxf(old, part);
-    const float ref = top == -INFINITY ? 0.f : top;
-    const float w_old = expf(old - ref), w_part = expf(part - ref), w_sum = w_old + w_part;
-    const float inv = w_sum > 0.f ? 1.f / w_sum : 0.f;
-    const float f_old = w_old * inv, f_part = l_tot > 0.f ? w_part * inv / l_tot : 0.f;
-    __syncthreads();
-    const uint32_t odd_rows = EXACT ? take_odd<WAVES>(masks) : 0;
-    // no row here, or no key seen: state unchanged
-    if (a_own < p.c && !((odd_rows >> n) & 1) && (part != -INFINITY || p.fresh)) {
-#pragma unroll
-        for (int i = 0; i < N; ++i) {
-            const int col = column_of<DP, WAVES>(i, ln);
-            if (col >= d) continue;
-            float4* dst = reinterpret_cast<float4*>(O + col);
-            const float4 s = take_sum<DP, WAVES>(lds, i, ln);
-            float4 x = o_old[i];
-            if (f_old != 0.f) {
-                x.x *= f_old; x.y *= f_old; x.z *= f_old; x.w *= f_old;
-            } else {                    // an empty state: nothing of O is looked at
-                x = make_float4(0.f, 0.f, 0.f, 0.f);
-            }
-            x.x = fmaf(s.x, f_part, x.x); x.y = fmaf(s.y, f_part, x.y);
-            x.z = fmaf(s.z, f_part, x.z); x.w = fmaf(s.w, f_part, x.w);
-            *dst = x;
-        }
-        if (ln.wave == 0 && h == 0) *L = top + logf(w_sum);
-    }
+    const uint32_t odd_rows = fold_forward<DP, WAVES, EXACT>(p, acc, m, l, lds, stats, masks, ln, dev, a_own, a, L,
+                                                             p.o + base + (int64_t)a * p.stride_s);
     if (EXACT) each_row<WAVES>(odd_rows, ln.wave, [&](const StepArgs& again, int i) { fwd_row<__hip_bfloat16>(again, b, hd, dev_i, q0 + i, ln.lane); });
 }
 
-// x + scale * (sum of the partial results at buf) to the lane's row
-template <int DP>
-__device__ inline void add_rows(float* row, float4 (&x)[blocks_of(DP)], const char* buf, float scale, int d,
-                                const Lane<DP>& ln) {
-#pragma unroll
-    for (int i = 0; i < blocks_of(DP); ++i) {
-        const int col = column_of<DP, BWD_WAVES>(i, ln);
-        if (col >= d) continue;
-        const float4 s = take_sum<DP, BWD_WAVES>(buf, i, ln);
-        x[i].x = fmaf(scale, s.x, x[i].x); x[i].y = fmaf(scale, s.y, x[i].y);
-        x[i].z = fmaf(scale, s.z, x[i].z); x[i].w = fmaf(scale, s.w, x[i].w);
-        *reinterpret_cast<float4*>(row + col) = x[i];
-    }
-}
-
 // ----------------------------------------------------------------- backward
-// Workgroup -> (tile rank, head), ranks heaviest first.  Consecutive workgroups go round-robin to the 8 XCDs; taken
-// in chunks of as many ranks as make a multiple of 8 workgroups, an XCD gets the same heads (and at most two others'
-// shares) of every chunk, and its L2 holds what they stream.  Head by head, an odd number of heads has every XCD
-// stream all of them: d 64, triangular, 25 heads of 2048 rows 125 -> 75 us, 15 of 4096 260 -> 145, 7 of 8192 360 ->
-// 242, 128 on 32 of 2048 343 -> 315.  Small launches of uneven work with few ranks, where a chunk is a large part of
-// the order, and ranks behind the last whole chunk stay head by head (9 heads of 500 rows, d 100, in chunks 15.3 ->
-// 16.1).  (Backward only: the forward gained as often as it lost, full blocks, d 128, 15 heads of 1024 28.0 -> 21.7, 3
-// of 5000 60.8 -> 63.7.)
-__device__ inline void decode_near(int linear, int n_ranks, int n_heads, bool uneven, int& rank, int& head) {
-    const int chunk = n_heads % 8 == 0 ? 1 : n_heads % 4 == 0 ? 2 : n_heads % 2 == 0 ? 4 : 8, size = chunk * n_heads;
-    const bool by_head = uneven && n_ranks < 4 * chunk && n_ranks * n_heads < 1024;
-    const int i = by_head ? n_ranks : linear / size;
-    if ((i + 1) * chunk > n_ranks) {
-        rank = linear / n_heads;
-        head = linear - rank * n_heads;
-        return;
-    }
-    const int j = linear - i * size, at = j % 8 * (size / 8) + j / 8;
-    head = at / chunk;
-    rank = i * chunk + at - head * chunk;
-}
-
 // One wavefront per SIMD (the key-owning side's registers), so what overlaps is arranged by hand: a
 // product leaves room for five or six other instructions.  In sub-tile u:
 //     S(u)      beside the transposing reads of u
@@ -751,7 +535,7 @@ __device__ inline void bwd_dq(const StepArgs& p, int n_tiles, int linear, char* 
     __syncthreads();
     const uint32_t odd_rows = EXACT ? take_odd<WAVES>(masks) : 0;
     if (a_own < p.c && !((odd_rows >> n) & 1))
-        add_rows<DP>(DQ, old, lds, p.scale, d, ln);
+        add_rows<DP, WAVES>(DQ, old, lds, p.scale, d, ln);
     if (EXACT) each_row<WAVES>(odd_rows, ln.wave, [&](const StepArgs& again, int i) { dq_row<__hip_bfloat16>(again, b, hd, dev_i, q0 + i, ln.lane); });
 }
 
@@ -973,8 +757,8 @@ __device__ inline void bwd_dkdv(const StepArgs& p, int n_tiles, int linear, char
     __syncthreads();
     const uint32_t odd_rows = EXACT ? take_odd<WAVES>(masks) : 0;
     if (key_own < p.c && !((odd_rows >> n) & 1)) {
-        add_rows<DP>(p.dv + row, old_v, lds, 1.f, d, ln);
-        add_rows<DP>(p.dk + row, old_k, lds + HALF, -p.scale, d, ln);
+        add_rows<DP, WAVES>(p.dv + row, old_v, lds, 1.f, d, ln);
+        add_rows<DP, WAVES>(p.dk + row, old_k, lds + HALF, -p.scale, d, ln);
     }
     if (EXACT)
         each_row<WAVES>(odd_rows, ln.wave, [&](const StepArgs& again, int i) { dkdv_row<__hip_bfloat16>(again, b, kvh, dev_i, k0 + i, 0, d, ln.lane); });
