@@ -1,4 +1,4 @@
-// Ring step for fp32 launches that leave most of the chip idle with 128-row workgroups, head dimension up to 128:
+// Ring step for fp32 launches that leave much of the chip idle with 128-row workgroups, head dimension up to 128:
 // products of three bf16 terms a number, as in f32x3_step.hip, in the work split of split_mfma.hip.
 //
 // What bounds such a launch is the walk of one workgroup, and in it the matrix cores and the vector instructions
@@ -9,6 +9,7 @@
 // direct loads fill with the fp32 rows as they are, and the terms of one k-step are made beside the products of
 // the one before.  A stage is requested anew as soon as its last read is in registers, and the order of the
 // contractions is such that another one lies between that and the next use.
+#include "f32x3_parts.h"
 #include "split_parts.h"
 
 namespace sa {
@@ -20,8 +21,6 @@ template <int DP> constexpr int ROW_BYTES = 4 * DP;
 template <int DP> constexpr int RAW_BYTES = 32 * ROW_BYTES<DP>;          // 32 rows of one streamed operand
 template <int DP> constexpr int LOADS = RAW_BYTES<DP> / 1024;            // direct loads they take
 template <int DP> constexpr int STAGES_BYTES = WAVES_OF<DP> * 2 * RAW_BYTES<DP>;
-
-typedef bf16x8 bf16x8x3[3];
 
 // Rows of 16-byte chunks; chunk c of row r lies at chunk position c ^ swizzle(r), so that the row reads of 16
 // consecutive rows (one logical chunk) hit different positions of a 256-byte line: at 32 columns, two rows to
@@ -119,66 +118,6 @@ __device__ inline void read_column(float (&x)[8], const char* raw, int mb, int g
         x[e] = *reinterpret_cast<const float*>(raw + at + ln.tr[e]);
     }
 }
-// Eight numbers as three terms each: 11 vector instructions a pair, in six steps that go beside one product each.
-// (What a term leaves as a dot product with (-1, 0), one instruction instead of two, is no gain: the matrix core
-// does not work beside those.)
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-struct Split8 {
-    float x[8], y[8];           // what is left, the last term
-    bf16x2 t[3][4];
-    template <int P>
-    __device__ __forceinline__ void round() {
-        typedef float f32x2 __attribute__((ext_vector_type(2)));
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const f32x2 v = {x[2 * i], x[2 * i + 1]};
-            t[P][i] = __builtin_convertvector(v, bf16x2);
-        }
-    }
-    template <int P>
-    __device__ __forceinline__ void widen(int first, int end) {
-#pragma unroll
-        for (int i = first; i < end; ++i) {
-            const uint32_t w = __builtin_bit_cast(uint32_t, t[P][i]);
-            y[2 * i] = __uint_as_float(w << 16);
-            y[2 * i + 1] = __uint_as_float(w & 0xffff0000u);
-        }
-    }
-    __device__ __forceinline__ void rest(int first, int end) {
-#pragma unroll
-        for (int i = 2 * first; i < 2 * end; ++i) x[i] -= y[i];
-    }
-    __device__ __forceinline__ void step(int i) {
-        if (i == 0) { round<0>(); widen<0>(0, 2); }
-        if (i == 1) { widen<0>(2, 4); rest(0, 2); }
-        if (i == 2) { rest(2, 4); round<1>(); }
-        if (i == 3) widen<1>(0, 4);
-        if (i == 4) rest(0, 4);
-        if (i == 5) round<2>();
-    }
-    __device__ __forceinline__ void operands(bf16x8 (&o)[3]) const {
-#pragma unroll
-        for (int p = 0; p < 3; ++p) {
-            struct Quad { bf16x2 t[4]; } q = {t[p][0], t[p][1], t[p][2], t[p][3]};
-            o[p] = __builtin_bit_cast(bf16x8, q);
-        }
-    }
-};
-__device__ __forceinline__ void split8(const float (&x)[8], bf16x8 (&o)[3]) {
-    Split8 c;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) c.x[e] = x[e];
-#pragma unroll
-    for (int i = 0; i < 6; ++i) c.step(i);
-    c.operands(o);
-}
-// registers first .. first + 7 of a score tile
-__device__ inline void split_tile(const f32x16& w, int first, bf16x8 (&o)[3]) {
-    float x[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) x[e] = w[first + e];
-    split8(x, o);
-}
 // k-step ks of an owned row (its d columns, zeros beyond)
 __device__ __forceinline__ void load_own(bf16x8 (&o)[3], const float* row, int ks, int h, int d) {
     const int col = 16 * ks + 8 * h;
@@ -234,20 +173,6 @@ struct Own<DP, false> {
         for (int t = 0; t < 3; ++t) o[t] = f[ks][t];
     }
 };
-// a b: the leading product, and the five others smallest first; beside(i) goes with the i-th of the six
-template <typename Beside>
-__device__ __forceinline__ void products(const bf16x8 (&a)[3], const bf16x8 (&b)[3], f32x16& hi, f32x16& lo, Beside beside) {
-    constexpr int A[6] = {1, 2, 0, 0, 1, 0}, B[6] = {1, 0, 0, 2, 0, 1};
-#pragma unroll
-    for (int i = 0; i < 6; ++i) {
-        __builtin_amdgcn_sched_barrier(0);
-        f32x16& c = i == 2 ? hi : lo;
-        c = mfma(a[A[i]], b[B[i]], c);
-        __builtin_amdgcn_sched_barrier(0);
-        beside(i);
-    }
-}
-
 // 32 x 32 scores: rows = the 32 streamed rows, columns = the owned ones.  NaN where an operand is infinite or
 // rounds to an infinite hi.  beside(i), i = 0 .. KS - 1: vector work to go with the products.
 template <int DP, typename Beside>

@@ -176,6 +176,21 @@ __device__ inline void dt_load_dword(dt_rsrc matrix, int byte_offset, uint32_t l
                  : "memory", "m0");
 }
 #pragma clang diagnostic pop
+// at most the last n vector memory operations of this wavefront are still on their way
+template <int N>
+__device__ inline void wait_all_but() {
+    asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
+}
+// all LDS reads so far are in registers: what they read may be overwritten
+__device__ inline void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory"); }
+
+// what the wavefronts have written to LDS is there for all (direct loads on their way stay so)
+__device__ inline void meet() {
+    wait_lds();
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" : : : "memory");
+}
+
 // wave must be wave-uniform (scalar): it selects the LDS destination of each load
 template <int DP>
 __device__ inline void dt_load(dt_rsrc matrix, int tile_byte_offset, char* lds_tile, const uint32_t (&g)[4], int wave) {

@@ -12,21 +12,6 @@ namespace sa {
 constexpr int OWN = 32;
 constexpr int STAT_BYTES = 512;         // 32 LSE, 32 delta, a load of 256 bytes each
 
-// at most the last n vector memory operations of this wavefront are still on their way
-template <int N>
-__device__ inline void wait_all_but() {
-    asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
-}
-// all LDS reads so far are in registers: what they read may be overwritten
-__device__ inline void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory"); }
-
-// what the wavefronts have written to LDS is there for all (direct loads on their way stay so)
-__device__ inline void meet() {
-    wait_lds();
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" : : : "memory");
-}
-
 __device__ inline f32x16 zero16() {
     f32x16 z;
 #pragma unroll
