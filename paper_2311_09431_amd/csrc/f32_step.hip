@@ -2,8 +2,8 @@
 // accumulation): any head dimension up to 256, any block size, fp32 or bf16 inputs.  They serve
 // fp32 storage above 128 columns (error budget 1e-5, so no reduced-precision products and the accurate
 // expf / logf) and the bf16 shapes the bf16 matrix-core kernels do not take (widened to fp32
-// on the way into LDS, so their probabilities are not rounded either).  fp32 up to 128 columns goes to
-// f32x3_step.hip and f32x3_split.hip, most short bf16 blocks to split_mfma.hip.
+// on the way into LDS, so their probabilities are not rounded either).  fp32 up to 128 columns is
+// f32x3_step.hip's and f32x3_split.hip's, most short bf16 blocks to split_mfma.hip.
 //
 // Measured against kernels with one wavefront per row and serial dot products on the vector ALU: a full
 // forward block of 2048 rows, 8 key/value heads for 32, d 128, fp32, 14.6 ms, backward 63, where the split form
@@ -522,7 +522,6 @@ hipError_t run(const StepArgs& a, bool backward, hipStream_t st) {
     return split ? run_fwd<T, DP, MOST>(a, st) : run_fwd<T, DP, 1>(a, st);
 }
 hipError_t run(const StepArgs& a, int dtype, bool backward, hipStream_t st) {
-    // (fp32 storage up to 128 columns: only rows too far apart for f32x3_split.hip's 32-bit offsets)
     if (dtype == SA_F32) return run<float, 256>(a, backward, st);
     if (a.d <= 32) return run<__hip_bfloat16, 32>(a, backward, st);
     if (a.d <= 64) return run<__hip_bfloat16, 64>(a, backward, st);
@@ -534,15 +533,15 @@ hipError_t run(const StepArgs& a, int dtype, bool backward, hipStream_t st) {
 
 hipError_t launch_fwd_f32(const StepArgs& a, int dtype, hipStream_t st) {
     if (few_rows_wanted(a, dtype, false)) return launch_few_rows(a, dtype, false, st);
-    if (dtype == SA_F32 && f32x3_wanted(a, false)) return launch_f32x3(a, false, st);
-    if (dtype == SA_F32 && f32x3_split_wanted(a, false)) return launch_f32x3_split(a, false, st);
+    if (dtype == SA_F32 && a.d <= 128)
+        return f32x3_split_wanted(a, false) ? launch_f32x3_split(a, false, st) : launch_f32x3(a, false, st);
     if (short_exact_wanted(a, dtype, false)) return launch_short_exact(a, false, st);
     return run(a, dtype, false, st);
 }
 hipError_t launch_bwd_f32(const StepArgs& a, int dtype, hipStream_t st) {
     if (few_rows_wanted(a, dtype, true)) return launch_few_rows(a, dtype, true, st);
-    if (dtype == SA_F32 && f32x3_wanted(a, true)) return launch_f32x3(a, true, st);
-    if (dtype == SA_F32 && f32x3_split_wanted(a, true)) return launch_f32x3_split(a, true, st);
+    if (dtype == SA_F32 && a.d <= 128)
+        return f32x3_split_wanted(a, true) ? launch_f32x3_split(a, true, st) : launch_f32x3(a, true, st);
     if (short_exact_wanted(a, dtype, true)) return launch_short_exact(a, true, st);
     return run(a, dtype, true, st);
 }

@@ -1,5 +1,5 @@
 // Ring-step kernels for fp32 operands on the bf16 matrix cores, head dimension up to 128, launches
-// with enough 128-row workgroups to fill the chip (fewer: f32x3_split.hip).
+// with enough 128-row workgroups to fill the chip (fewer: f32x3_split.hip, which has the rule).
 //
 // The fp32 matrix cores run at a sixteenth of the bf16 rate.  A fp32 number is the sum of three
 // bf16 ones (each the rounding of what the ones before leave: 3 x 8 bits and two signs cover its 24
@@ -628,12 +628,6 @@ hipError_t run(const StepArgs& a, bool backward, hipStream_t st) {
 }
 
 }  // namespace
-
-// Measured against the fp32 instruction's kernels with 128 rows a workgroup (256 row tiles, one
-// step, 2048 tokens, 16 heads, d 128): forward 0.23 / 0.36 ms, backward 0.46 / 0.68; with the
-// streamed rows split over the wavefronts, which those do below that (128 row tiles, 4096 tokens
-// on 2 devices, 4 heads): 0.48 / 0.26 and 0.81 / 0.71.
-bool f32x3_wanted(const StepArgs& a, bool backward) { return a.d <= 128 && !few_row_tiles(a, backward); }
 
 hipError_t launch_f32x3(const StepArgs& a, bool backward, hipStream_t st) {
     return a.d <= 64 ? run<64>(a, backward, st) : run<128>(a, backward, st);

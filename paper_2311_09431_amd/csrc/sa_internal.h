@@ -124,14 +124,12 @@ __device__ inline bool owns_keys(const BothKinds& b, int& linear) {
     return keys;
 }
 
-// fp32 precision: 128-row workgroups would leave compute units idle, and the streamed rows are split
+// The fp32 instruction's kernels: 128-row workgroups would leave compute units idle, and the streamed rows are split
 // over the wavefronts instead.  In the backward a key-owning workgroup walks the queries of its whole
 // group of heads, so with few key/value heads it is their number that counts.  One step, 32 query
-// heads, three-term kernel at d 128 / 128-row fp32 kernel at d 256 each against the split one, ms,
-// triangular and full block: 64 key tiles (8 key/value heads of 1024 tokens) 0.83 : 0.41, 0.83 : 0.70 /
-// 2.37 : 1.42, 2.38 : 1.64; 128 (8 of 2048) 1.64 : 1.42, 1.71 : 2.67 / 4.90 : 3.66, 5.58 : 6.46; 256
-// (16 of 2048) 0.86 : 1.45, 1.42 : 2.69 / 3.12 : 3.58, 5.62 : 6.38; one head of 4096 (32 tiles)
-// 26.5 : 12.3, 26.7 : 11.9 / 64 : 38, 70 : 43.
+// heads, d 256, 128-row kernel against the split one, ms, triangular and full block: 64 key tiles (8 key/value heads
+// of 1024 tokens) 2.37 : 1.42, 2.38 : 1.64; 128 (8 of 2048) 4.90 : 3.66, 5.58 : 6.46; 256 (16 of 2048) 3.12 : 3.58,
+// 5.62 : 6.38; one head of 4096 (32 tiles) 64 : 38, 70 : 43.
 inline bool few_row_tiles(const StepArgs& a, bool backward) {
     const int64_t tiles = (int64_t)((a.c + 127) / 128) * a.B, keys = tiles * a.n_kv * a.H_kv;
     return tiles * a.n_q * a.H < 256 || (backward && keys <= (uneven(a) ? 128 : 64));
@@ -151,7 +149,6 @@ hipError_t launch_rope(const void* x, void* y, const int32_t* pos, int64_t pos_s
 
 hipError_t launch_fwd_f32(const StepArgs& a, int dtype, hipStream_t st);
 hipError_t launch_bwd_f32(const StepArgs& a, int dtype, hipStream_t st);
-bool f32x3_wanted(const StepArgs& a, bool backward);
 hipError_t launch_f32x3(const StepArgs& a, bool backward, hipStream_t st);
 bool f32x3_split_wanted(const StepArgs& a, bool backward);
 hipError_t launch_f32x3_split(const StepArgs& a, bool backward, hipStream_t st);
