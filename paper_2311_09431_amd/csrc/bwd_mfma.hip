@@ -1127,6 +1127,7 @@ hipError_t launch_bwd_variant(const StepArgs& a, hipStream_t st) {
 hipError_t launch_bwd_mfma(const StepArgs& a, hipStream_t st) {
     const bool part = a.d % 8 != 0;
     if (a.d > 128) return launch_bwd_variant<256, false>(a, st);
+    if (a.d <= 32 && !part) return launch_bwd_variant<32, false>(a, st);
     if (a.d <= 64) return part ? launch_bwd_variant<64, true>(a, st) : launch_bwd_variant<64, false>(a, st);
     if (a.d <= 112) return part ? launch_bwd_variant<112, true>(a, st) : launch_bwd_variant<112, false>(a, st);
     return part ? launch_bwd_variant<128, true>(a, st) : launch_bwd_variant<128, false>(a, st);

@@ -599,6 +599,8 @@ hipError_t launch_fwd_mfma(const StepArgs& a, hipStream_t st) {
         else launch_fwd_rope<256>(a, st, grid, block, n_qtiles);
     } else if (a.d > 128) {
         launch_fwd_variant<256, false>(a, st, grid, block, n_qtiles);
+    } else if (a.d <= 32 && !part) {
+        launch_fwd_variant<32, false>(a, st, grid, block, n_qtiles);
     } else if (a.d <= 64) {
         if (part) launch_fwd_variant<64, true>(a, st, grid, block, n_qtiles);
         else launch_fwd_variant<64, false>(a, st, grid, block, n_qtiles);

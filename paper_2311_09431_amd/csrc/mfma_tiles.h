@@ -24,8 +24,8 @@ constexpr int TD = 128;          // tile columns: head dimensions up to 128 are 
                                  // 0..127 and 128..255 of the same rows ("halves")
 constexpr int TR = 64;           // tile rows streamed per iteration
 
-// DP, the number of columns a kernel instantiation computes: 64, 112, 128 or 256.  Tiles are
-// 128 columns wide (two of them, "halves", for 256), 64 for DP = 64; otherwise a smaller DP only leaves
+// DP, the number of columns a kernel instantiation computes: 32 (whole 16-byte chunks only), 64, 112, 128 or 256.  Tiles
+// are 128 columns wide (two of them, "halves", for 256), 64 for DP = 32 and 64; otherwise a smaller DP only leaves
 // out work: a contraction over the head dimension takes ksteps_of(DP) steps of 16 columns per half, a
 // product whose output has head-dimension columns blocks_of(DP) blocks of 32 per half.
 // 112 (head dimensions 65..112, e.g. the 100 of the paper's 3B model, Table 1) drops the last

@@ -386,6 +386,7 @@ __device__ inline bf16x8 negated(bf16x8 x) {
 template <int DP, bool PART, bool EXACT>
 __device__ inline void bwd_dq(const StepArgs& p, int n_tiles, int linear, char* lds, char* stats, uint32_t* masks) {
     constexpr int KS = ksteps_of(DP), MB = blocks_of(DP), WAVES = BWD_WAVES, LOADS = 2 * PIECES<DP>, TERMS = EXACT ? 3 : 1;
+    constexpr int LATE = KS > 2 ? KS - 2 : KS / 2, NEXT = MB > 1 ? 1 : 0;          // (32 columns: two k-steps, one block)
     const Lane<DP> ln;
     const int n = ln.n, h = ln.h;
     int rank, bh, dev_rank;
@@ -482,7 +483,7 @@ __device__ inline void bwd_dq(const StepArgs& p, int n_tiles, int linear, char* 
             }
             if (ks == KS / 2) wait_lds();           // the stage's last reads
             if (ks == KS / 2) loader.part(0, K, V, t2.key0, k);
-            if (ks == KS - 2) loader.part(1, K, V, t2.key0, k);
+            if (ks == LATE) loader.part(1, K, V, t2.key0, k);
         }
         asm volatile("" : "+v"(pr));            // there, beside the products
         __builtin_amdgcn_sched_barrier(0);
@@ -518,7 +519,7 @@ __device__ inline void bwd_dq(const StepArgs& p, int n_tiles, int linear, char* 
                         wait_all_but<LOADS>();
                         read_rows<DP>(kr, k_next, ln);
                     }
-                    if (g == 1 && mb == 1) read_rows<DP>(vr, k_next + SUB_BYTES<DP>, ln);
+                    if (g == 1 && mb == NEXT) read_rows<DP>(vr, k_next + SUB_BYTES<DP>, ln);
                 }
         __builtin_amdgcn_sched_barrier(0);
         t0 = t1;
@@ -546,6 +547,7 @@ __device__ inline void bwd_dq(const StepArgs& p, int n_tiles, int linear, char* 
 template <int DP, bool PART, bool EXACT>
 __device__ inline void bwd_dkdv(const StepArgs& p, int n_tiles, int linear, char* lds, char* stats, uint32_t* masks) {
     constexpr int KS = ksteps_of(DP), MB = blocks_of(DP), WAVES = BWD_WAVES, LOADS = 2 * PIECES<DP> + 2, TERMS = EXACT ? 3 : 1;
+    constexpr int LATE = KS > 2 ? KS - 2 : KS / 2, NEXT = MB > 1 ? 1 : 0;          // as in bwd_dq
     const Lane<DP> ln;
     const int n = ln.n, h = ln.h, wave = ln.wave;
     int tile, bh, dev_i;                                // low key tiles see most queries: first
@@ -694,7 +696,7 @@ __device__ inline void bwd_dkdv(const StepArgs& p, int n_tiles, int linear, char
             }
             if (ks == KS / 2) wait_lds();           // the stage's last reads
             if (ks == KS / 2) loader.part(0, Q, G, t2.a0, q);
-            if (ks == KS - 2) loader.part(1, Q, G, t2.a0, q);
+            if (ks == LATE) loader.part(1, Q, G, t2.a0, q);
         }
         asm volatile("" : "+v"(pr));            // there, beside the products
         __builtin_amdgcn_sched_barrier(0);
@@ -719,15 +721,16 @@ __device__ inline void bwd_dkdv(const StepArgs& p, int n_tiles, int linear, char
                     __builtin_amdgcn_sched_barrier(0);
                     if (t != TERMS - 1) continue;
                     // beside each of the first rounds something else
-                    if (i == 0 && mb == 1) {
-                        asm volatile("" : "+v"(dp));
+                    if (i == 0 && mb == NEXT) {
+                        if (MB > 1) asm volatile("" : "+v"(dp));
+                        else mfma_results_to_valu(dp);          // (one product behind its last)
 #pragma unroll
                         for (int r = 0; r < 8; ++r) ds[r] = pr[r] * dp[r];
                         as_operand<EXACT>(ds, 0, wd[0]);
                     }
                     if (i == 0 && mb == MB - 1) as_operand<EXACT>(pr, 1, wp[1]);
                     if (i == 1 && mb == 0) loader.part(2, Q, G, t2.a0, q);
-                    if (i == 1 && mb == 1) loader.part(3, Q, G, t2.a0, q);
+                    if (i == 1 && mb == NEXT) loader.part(3, Q, G, t2.a0, q);
                     if (i == 1 && mb == MB - 1) {
 #pragma unroll
                         for (int r = 8; r < 16; ++r) ds[r] = pr[r] * dp[r];
@@ -800,6 +803,7 @@ hipError_t run(const StepArgs& a, Pass pass, hipStream_t st) {
     return a.d % 8 ? run<DP, true>(a, pass, st) : run<DP, false>(a, pass, st);
 }
 hipError_t run(const StepArgs& a, Pass pass, hipStream_t st) {
+    if (a.d <= 32 && a.d % 8 == 0) return run<32, false>(a, pass, st);
     if (a.d <= 64) return run<64>(a, pass, st);
     if (a.d <= 112) return run<112>(a, pass, st);
     return run<128>(a, pass, st);
