@@ -828,14 +828,16 @@ bool rows_in_reach(const StepArgs& a) {
 // block of 128 rows is as well off in one 128-row tile up to 112 columns (d 64 7.9 / 8.3, d 128 10 / 8.5).  An odd number
 // of heads has every XCD stream all of them, full blocks of 65 to 128 tiles above 64 columns: d 128, 11 heads of
 // 1024 23.0 / 24.3, 13 of 1100 26.0 / 27.4, 15 of 1024 24.2 / 28.0, 9 of 1700 34.3 / 32.0, but 14 of 1152 25.2 / 23.6,
-// 15 on 3 of 1024 22.5 / 21.0.
+// 15 on 3 of 1024 22.5 / 21.0.  32 columns: 12 heads of 1000 rows, full, 13.8 / 9.8, 32 of 512 8.6 / 8.0; triangular 16
+// of 2048 23.7 / 17.5, 32 of 1024 14.4 / 14.3.
+bool narrow(const StepArgs& a) { return a.d <= 32 && a.d % 8 == 0; }          // 32 columns computed
 bool fwd_split_wanted(const StepArgs& a) {
     const int64_t tiles = (int64_t)((a.c + 127) / 128) * a.B * a.n_q * a.H, walk = (int64_t)a.c * a.n_kv;
     if (a.d > TD || (walk <= 128 && a.d <= 112)) return false;
     if (!rows_in_reach(a)) return false;
     if (tiles <= 64) return true;
-    if (tiles <= 128) return walk >= (a.layout == SA_STRIPED ? 512 : a.d > 64 && a.H == a.H_kv && a.B * a.H % 2 ? 1536 : 1024);
-    return tiles <= 256 && uneven(a) && walk >= (a.d <= 112 ? 4096 : 8192);
+    if (tiles <= 128) return walk >= (a.layout == SA_STRIPED || narrow(a) ? 512 : a.d > 64 && a.H == a.H_kv && a.B * a.H % 2 ? 1536 : 1024);
+    return tiles <= 256 && uneven(a) && walk >= (narrow(a) ? 2048 : a.d <= 112 ? 4096 : 8192);
 }
 hipError_t launch_fwd_split(const StepArgs& a, hipStream_t st) { return run(a, FWD, st); }
 // Backward step, by 128-row tiles of all keys ("tiles") and key/value heads: four times the workgroups walk a quarter
@@ -851,6 +853,8 @@ hipError_t launch_fwd_split(const StepArgs& a, hipStream_t st) { return run(a, F
 //  * 129 to 512 tiles up to 64 columns, triangular: up to 24 heads 1.15 to 1.5 (1.05), 56 1.1 (0.94), 100 1.0 (0.85),
 //    beyond 0.9 (0.7); 32 heads of 2048 rows (512 tiles) 99 / 99, d 32 80 / 82; full, 256: 46.4 / 45.8, 254 / 263
 //  * 256 tiles above 64 columns: 8 heads of 4096 137 / 160, 32 on 8 of 4096 500 / 574
+//  * 129 to 512 tiles, 32 columns computed, triangular: 32 heads of 1024 21.4 / 28.1, 16 of 2048 34.6 / 36.8, 8 of 4096 62 /
+//    57, 16 of 4096 108.6 / 109.3, 8 of 8192 205 / 192, 4 of 16384 400 / 364
 bool bwd_split_wanted(const StepArgs& a) {
     const int64_t t128 = (a.c + 127) / 128, t32 = (a.c + 31) / 32, heads = (int64_t)a.B * a.H_kv, group = a.H / a.H_kv;
     const int64_t keys = t128 * a.n_kv * heads, walk = (int64_t)a.c * a.n_q * group;
@@ -859,6 +863,7 @@ bool bwd_split_wanted(const StepArgs& a) {
     if (keys <= 64) return a.d <= 64 || uneven(a) || up_to(40);
     if (a.d > 64) return keys <= 128 && (uneven(a) ? walk >= 2048 && up_to(16) : group >= 4 && up_to(24));
     if (!uneven(a)) return keys <= 128 && walk >= (a.d <= 32 ? 6 : 4) * keys;
+    if (keys > 128 && narrow(a)) return keys <= 512 && walk >= 16 * keys;
     return up_to(56) && (keys <= 256 ? walk >= 4 * keys : keys <= 512 && walk > 4 * keys);
 }
 hipError_t launch_bwd_split(const StepArgs& a, hipStream_t st) { return run(a, BWD, st); }
