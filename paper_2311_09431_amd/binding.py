@@ -1,4 +1,4 @@
-"""ctypes binding of libstriped_attn.so: argument marshalling only.
+"""Binding of libstriped_attn.so: argument marshalling only, by ctypes, the hot entry points' by _marshal (csrc/marshal.cpp).
 
 Every function has the name of the C entry point it calls (include/striped_attn.h)
 and takes torch tensors living on the GPU; torch supplies device memory and the
@@ -6,7 +6,6 @@ current stream, nothing else.  There is no CPU fallback: if the library is not
 built, or a tensor is not on the GPU, the call raises.
 """
 import ctypes
-import math
 import os
 
 import torch
@@ -14,6 +13,11 @@ import torch
 CONTIGUOUS, STRIPED = 0, 1
 F32, BF16 = 0, 1
 MASK_EMPTY, MASK_TRI, MASK_FULL = 0, 1, 2
+
+try:
+    from . import _marshal
+except ImportError as e:            # (lib() says so)
+    _marshal, _why = None, e
 
 _LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libstriped_attn.so")
 _lib = None
@@ -41,6 +45,9 @@ def lib():
         if not os.path.exists(_LIB_PATH):
             raise RuntimeError("libstriped_attn.so is not built: run "
                                "`python -m paper_2311_09431_amd.build` (needs hipcc)")
+        if _marshal is None:
+            raise RuntimeError("_marshal is not built: run `python -m paper_2311_09431_amd.build` (%s)" % _why)
+        _marshal.set_shape_type(SaShape)
         L = ctypes.CDLL(_LIB_PATH)
         vp, i32, i64 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64
         shp = ctypes.POINTER(SaShape)
@@ -73,6 +80,16 @@ def lib():
         _lib = L
     return _lib
 
+
+class _Entries(dict):
+    """Entry point -> its address, for _marshal."""
+
+    def __missing__(self, name):
+        self[name] = ctypes.cast(getattr(lib(), name), ctypes.c_void_p).value
+        return self[name]
+
+
+_entry = _Entries()
 
 EXPORTS = ("sa_stripe_permute", "sa_unstripe_permute", "sa_rope", "sa_state_init", "sa_attn_step_fwd",
            "sa_attn_step_fwd_rope",
@@ -146,13 +163,10 @@ def sa_unstripe_permute(src, dst, N, seq_axis=2):
 
 
 def _permute(name, src, dst, N, seq_axis):
-    if not (src.is_contiguous() and dst.is_contiguous()) or src.shape != dst.shape \
-            or src.dtype != dst.dtype:
+    status = _marshal.permute(_entry[name], src, dst, N, seq_axis, _stream)
+    if status is None:
         raise ValueError("src and dst must be contiguous with equal shape and dtype")
-    outer = math.prod(src.shape[:seq_axis])
-    inner = math.prod(src.shape[seq_axis + 1:]) * src.element_size()
-    _check(getattr(lib(), name)(_ptr(src), _ptr(dst), outer, src.shape[seq_axis], inner, N, _stream()),
-           name)
+    _check(status, name)
 
 
 def sa_rope(x, y, pos, shape, base=10000.0, inverse=False):
@@ -160,17 +174,17 @@ def sa_rope(x, y, pos, shape, base=10000.0, inverse=False):
     if pos.dtype != torch.int32 or not pos.is_contiguous():
         raise TypeError("pos must be a contiguous int32 tensor")
     stride_b = pos.stride(0) if pos.dim() == 2 else 0
-    _check(lib().sa_rope(_ptr(x), _ptr(y), _ptr(pos), stride_b, ctypes.byref(shape), float(base),
-                         1 if inverse else 0, _stream()), "sa_rope")
+    _check(_marshal.rope(_entry["sa_rope"], x, y, pos, stride_b, shape, float(base), 1 if inverse else 0, _stream),
+           "sa_rope")
 
 
 def sa_state_init(o, lse, shape):
-    _check(lib().sa_state_init(_ptr(o), _ptr(lse), ctypes.byref(shape), _stream()), "sa_state_init")
+    _check(_marshal.two(_entry["sa_state_init"], o, lse, shape, _stream), "sa_state_init")
 
 
 def sa_attn_step_fwd(q, k, v, o, lse, q_dev, kv_dev, N, layout, shape):
-    _check(lib().sa_attn_step_fwd(_ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(lse), q_dev, kv_dev, N,
-                                  layout, ctypes.byref(shape), _stream()), "sa_attn_step_fwd")
+    _check(_marshal.step_fwd(_entry["sa_attn_step_fwd"], q, k, v, o, lse, q_dev, kv_dev, N, layout, shape, _stream),
+           "sa_attn_step_fwd")
 
 
 def sa_attn_step_fwd_rope(q, k, v, o, lse, q_pos, q_dev, kv_dev, N, layout, shape, base=10000.0):
@@ -185,34 +199,38 @@ def sa_attn_step_fwd_rope(q, k, v, o, lse, q_pos, q_dev, kv_dev, N, layout, shap
 
 
 def sa_finalize(o, out, shape):
-    _check(lib().sa_finalize(_ptr(o), _ptr(out), ctypes.byref(shape), _stream()), "sa_finalize")
+    _check(_marshal.two(_entry["sa_finalize"], o, out, shape, _stream), "sa_finalize")
 
 
 def sa_bwd_preprocess(o, dout, delta, shape):
-    _check(lib().sa_bwd_preprocess(_ptr(o), _ptr(dout), _ptr(delta), ctypes.byref(shape), _stream()),
-           "sa_bwd_preprocess")
+    _check(_marshal.three(_entry["sa_bwd_preprocess"], o, dout, delta, shape, _stream), "sa_bwd_preprocess")
 
 
 def sa_attn_step_bwd(q, k, v, dout, lse, delta, dq, dk, dv, q_dev, kv_dev, N, layout, shape):
-    _check(lib().sa_attn_step_bwd(_ptr(q), _ptr(k), _ptr(v), _ptr(dout), _ptr(lse), _ptr(delta),
-                                  _ptr(dq), _ptr(dk), _ptr(dv), q_dev, kv_dev, N, layout,
-                                  ctypes.byref(shape), _stream()), "sa_attn_step_bwd")
+    _check(_marshal.step_bwd(_entry["sa_attn_step_bwd"], q, k, v, dout, lse, delta, dq, dk, dv, q_dev, kv_dev, N,
+                             layout, shape, _stream), "sa_attn_step_bwd")
 
 
 def sa_ring_fwd(Q, K, V, O, LSE, N, layout, shape, q_dev_only=-1, timed=False):
     """Returns None, or (timed=True) an [N][N] list of step durations in ms."""
-    buf = (ctypes.c_float * (N * N))() if timed else None
+    if not timed:
+        return _check(_marshal.ring_fwd(_entry["sa_ring_fwd"], Q, K, V, O, LSE, N, layout, shape, q_dev_only, _stream),
+                      "sa_ring_fwd")
+    buf = (ctypes.c_float * (N * N))()
     _check(lib().sa_ring_fwd(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(LSE), N, layout,
                              ctypes.byref(shape), q_dev_only, buf, _stream()), "sa_ring_fwd")
-    return [[buf[i * N + j] for j in range(N)] for i in range(N)] if timed else None
+    return [[buf[i * N + j] for j in range(N)] for i in range(N)]
 
 
 def sa_ring_bwd(Q, K, V, dO, O, LSE, delta, dQ, dK, dV, N, layout, shape, q_dev_only=-1, timed=False):
-    buf = (ctypes.c_float * (N * N))() if timed else None
+    if not timed:
+        return _check(_marshal.ring_bwd(_entry["sa_ring_bwd"], Q, K, V, dO, O, LSE, delta, dQ, dK, dV, N, layout, shape,
+                                        q_dev_only, _stream), "sa_ring_bwd")
+    buf = (ctypes.c_float * (N * N))()
     _check(lib().sa_ring_bwd(_ptr(Q), _ptr(K), _ptr(V), _ptr(dO), _ptr(O), _ptr(LSE), _ptr(delta),
                              _ptr(dQ), _ptr(dK), _ptr(dV), N, layout, ctypes.byref(shape), q_dev_only,
                              buf, _stream()), "sa_ring_bwd")
-    return [[buf[i * N + j] for j in range(N)] for i in range(N)] if timed else None
+    return [[buf[i * N + j] for j in range(N)] for i in range(N)]
 
 
 def sa_attn_step_fwd_tiled(q, k, v, o, lse, q_dev, kv_dev, N, layout, shape, skip_bq, skip_bk):

@@ -2,7 +2,8 @@
 
     python -m paper_2311_09431_amd.build
 
-Objects go to _build/ at the repository root, the library next to this file.
+Objects go to _build/ at the repository root, the library and the binding's _marshal (host code on torch's headers, by
+g++) next to this file.
 """
 import glob
 import os
@@ -73,12 +74,31 @@ def _check_asm(src, obj):
         raise RuntimeError("%s: the compiled code breaks what its asm statements rest on:\n%s" % (src, "\n".join(findings)))
 
 
+def build_marshal():
+    """The binding's extension module, against the torch that is installed."""
+    import sysconfig
+    import torch
+    at = os.path.dirname(torch.__file__)
+    out = os.path.join(HERE, "_marshal" + sysconfig.get_config_var("EXT_SUFFIX"))
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-shared", "-fPIC",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, "-I" + os.path.join(at, "include"),
+           "-I" + os.path.join(at, "include", "torch", "csrc", "api", "include"),
+           "-I" + sysconfig.get_paths()["include"], os.path.join(CSRC, "marshal.cpp"), "-o", out,
+           "-L" + os.path.join(at, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-Wl,-rpath," + os.path.join(at, "lib")]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode:
+        raise RuntimeError("g++ failed on marshal.cpp:\n%s\n%s" % (r.stdout, r.stderr))
+    return out
+
+
 def build_library(extra_flags=(), jobs=8):
-    """Compile every source and link the shared library.  Always recompiles."""
+    """Compile every source and link the shared library; the binding's extension too.  Always recompiles."""
     os.makedirs(OBJ_DIR, exist_ok=True)
     with ThreadPoolExecutor(max_workers=jobs) as ex:
+        marshal = ex.submit(build_marshal)
         objs = list(ex.map(lambda s: _compile(s, list(extra_flags)), SOURCES))
     cmd = [_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-fno-gpu-rdc", *objs, "-o", LIB]
+    marshal.result()
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode:
         raise RuntimeError("link failed:\n%s\n%s" % (r.stdout, r.stderr))
