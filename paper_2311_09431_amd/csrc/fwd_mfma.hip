@@ -248,7 +248,7 @@ fwd_mfma_kernel(StepArgs p, int n_qtiles) {
     const int tid = threadIdx.x, lane = tid & 63, n = lane & 31, h = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);      // wave-uniform, kept scalar
     int rank, bh, dev = p.q_dev;
-    decode_block<true>((int)blockIdx.x, RING ? n_qtiles * p.n_q : n_qtiles, p.B * p.H, rank, bh);
+    decode_block<true>((int)blockIdx.x, RING ? n_qtiles * p.n_q : n_qtiles, p.B * p.H, uneven(p), rank, bh);
     if (RING) {
         int dev_rank;
         decode_rank(rank, n_qtiles, p.n_q, p.layout, rank, dev_rank);

@@ -271,6 +271,28 @@ __device__ __forceinline__ void mfma_vgpr_acc(f32x16& acc, bf16x8 a, bf16x8 b, b
     else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));
 }
 
+// Workgroup -> (tile rank, head), ranks heaviest first.  Consecutive workgroups go round-robin to the 8 XCDs; taken
+// in chunks of as many ranks as make a multiple of 8 workgroups, an XCD gets the same heads (and at most two others'
+// shares) of every chunk, and its L2 holds what they stream.  Head by head, an odd number of heads has every XCD
+// stream all of them: d 64, triangular, 25 heads of 2048 rows 125 -> 75 us, 15 of 4096 260 -> 145, 7 of 8192 360 ->
+// 242, 128 on 32 of 2048 343 -> 315.  Small launches of uneven work with few ranks, where a chunk is a large part of
+// the order, and ranks behind the last whole chunk stay head by head (9 heads of 500 rows, d 100, in chunks 15.3 ->
+// 16.1).  (Backward only: the forward gained as often as it lost, full blocks, d 128, 15 heads of 1024 28.0 -> 21.7, 3
+// of 5000 60.8 -> 63.7.)
+__device__ inline void decode_near(int linear, int n_ranks, int n_heads, bool uneven, int& rank, int& head) {
+    const int chunk = n_heads % 8 == 0 ? 1 : n_heads % 4 == 0 ? 2 : n_heads % 2 == 0 ? 4 : 8, size = chunk * n_heads;
+    const bool by_head = uneven && n_ranks < 4 * chunk && n_ranks * n_heads < 1024;
+    const int i = by_head ? n_ranks : linear / size;
+    if ((i + 1) * chunk > n_ranks) {
+        rank = linear / n_heads;
+        head = linear - rank * n_heads;
+        return;
+    }
+    const int j = linear - i * size, at = j % 8 * (size / 8) + j / 8;
+    head = at / chunk;
+    rank = i * chunk + at - head * chunk;
+}
+
 // Workgroup order of a 1-D grid over (tile rank, batch*head), rank 0 = heaviest tile.
 // Large grids: heads are taken in groups of 8; inside a group the index runs over
 // heads fastest and tile ranks slowest, so (i) every group runs heaviest-first and
@@ -281,11 +303,19 @@ __device__ __forceinline__ void mfma_vgpr_acc(f32x16& acc, bf16x8 a, bf16x8 b, b
 // heaviest-first over all heads; with SNAKE the second 256 workgroups run
 // lightest-first, so that the two workgroups sharing a CU (indices L and L + 256)
 // carry about the same total work.
+// Uneven launches in between: by ranks over all heads.  With groups the last heaviest workgroups start when half of
+// the launch is over, and it ends with them: 32 tiles of 32 heads, two workgroups to a compute unit, 1.46 times the
+// mean load, by ranks 1.0.  An XCD keeps its heads (decode_near), but all at a time.  Triangular step, us, forward /
+// backward, groups : ranks: d 128, 24 heads of 4096 122 / 426 : 109 / 381, 64 of 2048 97 / 342 : 86 / 306, 32 of 8192 (2048
+// workgroups) 515 / 1791 : 499 / 1740, but 32 of 16384 (4096) 1868 / 6724 : 1895 / 6838 and a ring of 8 x 4096, 16 heads
+// (4096), backward 12.97 : 13.43 ms; d 64, 40 of 2560 61 / 198 : 50 / 164, 16 of 12500 354 / 1136 : 320 / 1106.
 constexpr int HEAD_GROUP = 8;
 constexpr int N_CU = 256;
+constexpr int MOST_BY_RANK = 12 * N_CU;
 template <bool SNAKE>
-__device__ inline void decode_block(int linear, int n_tiles, int n_bh, int& rank, int& bh) {
+__device__ inline void decode_block(int linear, int n_tiles, int n_bh, bool uneven, int& rank, int& bh) {
     const int total = n_tiles * n_bh;
+    if (uneven && total > 2 * N_CU && total <= MOST_BY_RANK) return decode_near(linear, n_tiles, n_bh, true, rank, bh);
     if (total <= 2 * N_CU) {
         int s = linear;
         if (SNAKE && linear >= N_CU) s = total - 1 - (linear - N_CU);

@@ -208,26 +208,4 @@ __device__ inline void add_rows(float* row, float4 (&x)[share_of(DP, WAVES)], co
     }
 }
 
-// Workgroup -> (tile rank, head), ranks heaviest first.  Consecutive workgroups go round-robin to the 8 XCDs; taken
-// in chunks of as many ranks as make a multiple of 8 workgroups, an XCD gets the same heads (and at most two others'
-// shares) of every chunk, and its L2 holds what they stream.  Head by head, an odd number of heads has every XCD
-// stream all of them: d 64, triangular, 25 heads of 2048 rows 125 -> 75 us, 15 of 4096 260 -> 145, 7 of 8192 360 ->
-// 242, 128 on 32 of 2048 343 -> 315.  Small launches of uneven work with few ranks, where a chunk is a large part of
-// the order, and ranks behind the last whole chunk stay head by head (9 heads of 500 rows, d 100, in chunks 15.3 ->
-// 16.1).  (Backward only: the forward gained as often as it lost, full blocks, d 128, 15 heads of 1024 28.0 -> 21.7, 3
-// of 5000 60.8 -> 63.7.)
-__device__ inline void decode_near(int linear, int n_ranks, int n_heads, bool uneven, int& rank, int& head) {
-    const int chunk = n_heads % 8 == 0 ? 1 : n_heads % 4 == 0 ? 2 : n_heads % 2 == 0 ? 4 : 8, size = chunk * n_heads;
-    const bool by_head = uneven && n_ranks < 4 * chunk && n_ranks * n_heads < 1024;
-    const int i = by_head ? n_ranks : linear / size;
-    if ((i + 1) * chunk > n_ranks) {
-        rank = linear / n_heads;
-        head = linear - rank * n_heads;
-        return;
-    }
-    const int j = linear - i * size, at = j % 8 * (size / 8) + j / 8;
-    head = at / chunk;
-    rank = i * chunk + at - head * chunk;
-}
-
 }  // namespace sa
