@@ -3,7 +3,7 @@
 // fp32 storage above 128 columns (error budget 1e-5, so no reduced-precision products and the accurate
 // expf / logf) and the bf16 shapes the bf16 matrix-core kernels do not take (widened to fp32
 // on the way into LDS, so their probabilities are not rounded either).  fp32 up to 128 columns is
-// f32x3_step.hip's and f32x3_split.hip's, most short bf16 blocks to split_mfma.hip.
+// the work of f32x3_step.hip and f32x3_split.hip, most short bf16 blocks that of split_mfma.hip.
 //
 // Measured against kernels with one wavefront per row and serial dot products on the vector ALU: a full
 // forward block of 2048 rows, 8 key/value heads for 32, d 128, fp32, 14.6 ms, backward 63, where the split form
