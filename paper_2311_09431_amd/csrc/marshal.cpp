@@ -170,30 +170,44 @@ ENTRY(rope) {
         return run([&] { return f(x, y, pos, stride, s.at(), base, inverse, st); });
     });
 }
+// What a permutation along axis o moves, rows of `inner` bytes: as an index of t's shape, from the end if negative
+struct Extent { int64_t outer, rows, inner; };
+Extent extent(const at::Tensor& t, PyObject* o) {
+    const int64_t dims = t.dim(), axis = PyNumber_AsSsize_t(o, PyExc_IndexError);
+    if (axis == -1 && PyErr_Occurred()) throw ToStop();
+    if (axis < -dims || axis >= dims) {
+        PyErr_SetString(PyExc_IndexError, "tuple index out of range");
+        throw ToStop();
+    }
+    const int64_t at = axis < 0 ? axis + dims : axis;
+    Extent e = {1, t.size(at), t.element_size()};
+    for (int64_t i = 0; i < at; ++i) e.outer *= t.size(i);
+    for (int64_t i = at + 1; i < dims; ++i) e.inner *= t.size(i);
+    return e;
+}
+const at::Tensor& tensor(PyObject* o) {
+    if (!THPVariable_Check(o)) pointer(Py_None);
+    return THPVariable_Unpack(o);
+}
+// (tensor, axis): its extent
+ENTRY(extent_of) {
+    return guarded(n, 2, [&] {
+        const Extent e = extent(tensor(a[0]), a[1]);
+        return Py_BuildValue("LLL", (long long)e.outer, (long long)e.rows, (long long)e.inner);
+    });
+}
 // (function address, src, dst, N, seq_axis, stream): the tensors' sizes are looked at here.  None: not contiguous with equal
 // shape and type
 ENTRY(permute) {
     return guarded(n, 6, [&]() -> PyObject* {
         const auto f = reinterpret_cast<int (*)(P, P, int64_t, int64_t, int64_t, I, P)>(address(a[0]));
-        if (!THPVariable_Check(a[1]) || !THPVariable_Check(a[2])) pointer(Py_None);
-        const at::Tensor &src = THPVariable_Unpack(a[1]), &dst = THPVariable_Unpack(a[2]);
+        const at::Tensor &src = tensor(a[1]), &dst = tensor(a[2]);
         if (!src.is_contiguous() || !dst.is_contiguous() || src.sizes() != dst.sizes() || src.scalar_type() != dst.scalar_type())
             Py_RETURN_NONE;
         const I N = int32(a[3]);
-        int64_t axis = (int64_t)integer(a[4]);
-        const int64_t dims = src.dim();
-        if (axis < -dims || axis >= dims) {
-            PyErr_SetString(PyExc_IndexError, "tuple index out of range");
-            return nullptr;
-        }
-        // (as the slices shape[:axis] and shape[axis + 1:] read a negative axis)
-        int64_t outer = 1, inner = src.element_size();
-        const int64_t at = axis < 0 ? axis + dims : axis, behind = axis == -1 ? 0 : at + 1;
-        for (int64_t i = 0; i < at; ++i) outer *= src.size(i);
-        for (int64_t i = behind; i < dims; ++i) inner *= src.size(i);
+        const Extent e = extent(src, a[4]);
         P s = pointer(a[1]), d = pointer(a[2]), st = stream(a[5]);
-        const int64_t rows = src.size(at);
-        return run([&] { return f(s, d, outer, rows, inner, N, st); });
+        return run([&] { return f(s, d, e.outer, e.rows, e.inner, N, st); });
     });
 }
 PyObject* set_shape_type(PyObject*, PyObject* o) {
@@ -208,7 +222,7 @@ PyObject* set_shape_type(PyObject*, PyObject* o) {
 
 #define FAST(name) {#name, reinterpret_cast<PyCFunction>(reinterpret_cast<void*>(name)), METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {FAST(two), FAST(three), FAST(step_fwd), FAST(step_bwd), FAST(ring_fwd), FAST(ring_bwd), FAST(rope),
-                         FAST(permute), {"set_shape_type", set_shape_type, METH_O, nullptr}, {nullptr, nullptr, 0, nullptr}};
+                         FAST(permute), FAST(extent_of), {"set_shape_type", set_shape_type, METH_O, nullptr}, {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_marshal", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 
 }  // namespace

@@ -1,4 +1,4 @@
-"""Argument marshalling of the hot entry points (csrc/marshal.cpp): what it refuses, without a GPU."""
+"""Argument marshalling of the hot entry points (csrc/marshal.cpp): what it refuses, and the axes of a permutation."""
 import ctypes
 
 import pytest
@@ -46,9 +46,36 @@ def test_permute_looks_at_its_tensors_first():
             sa.sa_stripe_permute(x, other, 2, 1)
         with pytest.raises(ValueError):
             sa.sa_unstripe_permute(other, x, 2, 1)
-    for axis in (3, -4):
+    for axis in (3, -4, 1 << 64, -(1 << 64)):
         with pytest.raises(IndexError):
             sa.sa_stripe_permute(x, x.clone(), 2, axis)
+    with pytest.raises(TypeError):
+        sa.sa_stripe_permute(x, x.clone(), 2, 1.0)
+
+
+@pytest.mark.parametrize("shape", [(8,), (6, 4), (2, 8, 4), (3, 1, 5, 2)])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_a_permutation_stays_inside_its_tensor(shape, dtype):
+    # from whichever end the axis is counted: what is moved is the tensor, the rows along that axis
+    sa.lib()
+    x = torch.zeros(shape, dtype=dtype)
+    for axis in range(-len(shape), len(shape)):
+        outer, rows, inner = sa._marshal.extent_of(x, axis)
+        assert rows == shape[axis] and outer * rows * inner == x.numel() * x.element_size()
+        assert inner == x.stride(axis) * x.element_size()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32, torch.int32])
+def test_axes_counted_from_the_end(dtype):
+    x = torch.arange(2 * 6 * 12, device="cuda").view(2, 6, 12).to(dtype)
+    for axis in (-1, -2):
+        y, want, back = (torch.empty_like(x) for _ in range(3))
+        sa.sa_stripe_permute(x, y, 3, axis)
+        sa.sa_stripe_permute(x, want, 3, axis + 3)
+        sa.sa_unstripe_permute(y, back, 3, axis)
+        assert torch.equal(y, want) and torch.equal(back, x)
+        assert not torch.equal(y, x)
 
 
 def test_counts_and_addresses():
