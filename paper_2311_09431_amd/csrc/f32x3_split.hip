@@ -587,6 +587,13 @@ bool rows_in_reach(const StepArgs& a) {
     return ((int64_t)(a.c + 31) / 32 * 32 + OWN) * 4 * widest + 4 * a.d + 4096 < (int64_t(1) << 31);
 }
 
+// HIP takes fewer than 2^32 threads a launch.  (One beyond it, in parts, would be faster here than in 128-row workgroups;
+// nothing near such sizes has been measured.)
+bool fits_a_launch(const StepArgs& a, bool backward) {
+    const int64_t tiles = (a.c + OWN - 1) / OWN, owners = (int64_t)a.n_q * a.B * a.H + (backward ? (int64_t)a.n_kv * a.B * a.H_kv : 0);
+    return tiles * owners * 64 * (a.d <= 64 ? WAVES_OF<64> : WAVES_OF<128>) < (int64_t(1) << 32);
+}
+
 }  // namespace
 
 // Four times the workgroups of a quarter or an eighth of the walk, each with a start of its own, against 128-row (forward
@@ -613,7 +620,7 @@ double makespan(const Takes& k, double mean, double n1, double t1, double n2 = 0
 }  // namespace
 
 bool f32x3_split_wanted(const StepArgs& a, bool backward) {
-    if (a.d > TD || !rows_in_reach(a)) return false;
+    if (a.d > TD || !rows_in_reach(a) || !fits_a_launch(a, backward)) return false;
     const TakesAll& k = a.d <= 32 ? TAKES32 : a.d <= 64 ? TAKES64 : TAKES128;
     // contiguous layout: key shards behind the last played device are seen by nobody
     const int seen = a.layout == SA_STRIPED ? a.n_kv : a.q_dev + a.n_q - a.kv_dev;

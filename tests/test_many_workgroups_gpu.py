@@ -1,7 +1,7 @@
 """Rings of many short shards over as many (batch, head) pairs as the entry points take: more
 workgroups than one launch may hold (HIP: fewer than 2^32 threads), which the drivers play in parts.
 One row a shard and 257 devices; a few heads against fp64, the last of a part and the first of the next
-among them."""
+among them.  And fp32 steps of as many heads, whose kernels have up to 512 threads per 32 rows."""
 import numpy as np
 import pytest
 import torch
@@ -54,3 +54,27 @@ def test_ring_of_many_shards(B, H, Hkv):
                 dk, dv = dk + np.outer(ds, q[-1]), dv + np.outer(p, g[-1])
             assert np.abs(t["dk"][b, kvh].cpu().numpy() - dk).max() <= 2e-5
             assert np.abs(t["dv"][b, kvh].cpu().numpy() - dv).max() <= 2e-5
+
+
+def test_fp32_step_of_long_blocks():
+    # 65535 heads of 2080 rows: with 32 rows to a workgroup of 512 threads the backward would hold 1.016 * 2^32 threads
+    c = 2080
+    f32 = dict(dtype=torch.float32, device="cuda")
+    q, k, v, g = (inputs.gaussian((1, HEADS, c, D), 21 + i, device="cuda") for i in range(4))
+    o, dq, dk, dv = (torch.zeros(1, HEADS, c, D, **f32) for _ in range(4))
+    lse, delta = (torch.empty(1, HEADS, c, **f32) for _ in range(2))
+    shape = sa.shard_shape(q, c, lse)
+    sa.sa_state_init(o, lse, shape)
+    sa.sa_attn_step_fwd(q, k, v, o, lse, 0, 0, 1, sa.STRIPED, shape)
+    sa.sa_bwd_preprocess(o, g, delta, shape)
+    sa.sa_attn_step_bwd(q, k, v, g, lse, delta, dq, dk, dv, 0, 0, 1, sa.STRIPED, shape)
+    torch.cuda.synchronize()
+    for h in (0, 1, HEADS // 2, HEADS - 1):
+        Q, K, V, G = (inputs.to_f64(x[0, h]) for x in (q, k, v, g))
+        s = np.where(np.tri(c, dtype=bool), Q @ K.T / np.sqrt(D), -np.inf)
+        p = np.exp(s - s.max(axis=1, keepdims=True))
+        p /= p.sum(axis=1, keepdims=True)
+        ds = p * (G @ V.T - (p * (G @ V.T)).sum(axis=1, keepdims=True)) / np.sqrt(D)
+        assert np.abs(o[0, h].cpu().numpy() - p @ V).max() <= 1e-5
+        for got, want in ((dq, ds @ K), (dk, ds.T @ Q), (dv, p.T @ G)):
+            assert np.abs(got[0, h].cpu().numpy() - want).max() <= 2e-5 * max(1.0, np.abs(want).max())

@@ -65,3 +65,20 @@ def test_split_rules_at_their_edges():
     for H, c, d, route in ((512, 32, 32, "short"), (513, 32, 32, "fp32"), (384, 33, 32, "short"), (385, 33, 32, "fp32"), (1000, 33, 36, "short")):
         assert fwd(H, c, d) == route and bwd(H, c, d) == "short"
         assert routes.forward(routes.args(c, d, H, N=2)) == "short"
+
+
+@pytest.mark.parametrize("backward", [False, True])
+def test_a_split_fp32_launch_holds_fewer_threads_than_hip_takes(backward):
+    # workgroups of 32 rows, 512 threads up to 64 columns and 256 above; the rule takes the longest walks of the most heads
+    # up to 32 columns
+    taken = []
+    for d, threads in ((4, 512), (32, 512), (64, 512), (128, 256)):
+        for H, Hkv, N, layout in ((65535, 65535, 1, sa.STRIPED), (65535, 65535, 1, sa.CONTIGUOUS), (65535, 4369, 1, sa.STRIPED),
+                                  (8192, 8192, 8, sa.STRIPED), (32767, 1, 1, sa.STRIPED), (1024, 1, 16, sa.CONTIGUOUS)):
+            for c in (17, 40, 100, 129, 1000, 2048, 2080, 2112, 4096, 1 << 14, 1 << 17, 1 << 20):
+                a = routes.args(c, d, H, Hkv, layout=layout, N=N)
+                if routes._ask("f32x3_split_wanted", a, backward):
+                    workgroups = (c + 31) // 32 * N * (H + (Hkv if backward else 0))
+                    assert workgroups * threads < 1 << 32, (d, H, Hkv, N, c)
+                    taken.append(workgroups * threads)
+    assert max(taken) > 1 << 30         # (it is not that large launches are never taken)
