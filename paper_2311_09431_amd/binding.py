@@ -14,10 +14,21 @@ CONTIGUOUS, STRIPED = 0, 1
 F32, BF16 = 0, 1
 MASK_EMPTY, MASK_TRI, MASK_FULL = 0, 1, 2
 
+
+class _NotBuilt:
+    """In _marshal's place: every use says what to do."""
+
+    def __init__(self, why):
+        self._why = why
+
+    def __getattr__(self, name):
+        raise RuntimeError("_marshal is not built: run `python -m paper_2311_09431_amd.build` (%s)" % self._why)
+
+
 try:
     from . import _marshal
-except ImportError as e:            # (lib() says so)
-    _marshal, _why = None, e
+except ImportError as e:
+    _marshal = _NotBuilt(str(e))
 
 _LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libstriped_attn.so")
 _lib = None
@@ -45,8 +56,6 @@ def lib():
         if not os.path.exists(_LIB_PATH):
             raise RuntimeError("libstriped_attn.so is not built: run "
                                "`python -m paper_2311_09431_amd.build` (needs hipcc)")
-        if _marshal is None:
-            raise RuntimeError("_marshal is not built: run `python -m paper_2311_09431_amd.build` (%s)" % _why)
         _marshal.set_shape_type(SaShape)
         L = ctypes.CDLL(_LIB_PATH)
         vp, i32, i64 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64

@@ -84,3 +84,15 @@ def test_counts_and_addresses():
         sa._marshal.two(0, 1)
     # as the library's own address
     assert sa._entry["sa_finalize"] == ctypes.cast(sa.lib().sa_finalize, ctypes.c_void_p).value
+
+
+def test_a_binding_without_its_extension_says_how_to_build(monkeypatch):
+    # not there, or for another torch: each entry point, and the library's first use
+    s = shape()
+    monkeypatch.setattr(sa, "_marshal", sa._NotBuilt("no module"))
+    for call in calls(s):
+        with pytest.raises(RuntimeError, match="paper_2311_09431_amd.build.*no module"):
+            call()
+    monkeypatch.setattr(sa, "_lib", None)
+    with pytest.raises(RuntimeError, match="paper_2311_09431_amd.build.*no module"):
+        sa.lib()
