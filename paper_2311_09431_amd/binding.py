@@ -49,6 +49,17 @@ class StripedAttnError(RuntimeError):
         super().__init__("%s failed: %s (%d)" % (where, lib().sa_status_str(status).decode(), status))
 
 
+def _integer(x):
+    """What ctypes takes for a C integer, as an int."""
+    if isinstance(x, ctypes.c_int32):
+        return x.value
+    if hasattr(x, "__index__"):
+        return x.__index__()
+    if hasattr(x, "_as_parameter_"):
+        return _integer(x._as_parameter_)
+    raise ctypes.ArgumentError("int expected instead of %s instance" % type(x).__name__)
+
+
 def lib():
     """The loaded shared library (loads on first use; raises if it is not built)."""
     global _lib
@@ -56,7 +67,7 @@ def lib():
         if not os.path.exists(_LIB_PATH):
             raise RuntimeError("libstriped_attn.so is not built: run "
                                "`python -m paper_2311_09431_amd.build` (needs hipcc)")
-        _marshal.set_shape_type(SaShape)
+        _marshal.set_up(SaShape, _integer)
         L = ctypes.CDLL(_LIB_PATH)
         vp, i32, i64 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64
         shp = ctypes.POINTER(SaShape)

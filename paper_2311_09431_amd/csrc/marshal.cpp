@@ -12,6 +12,7 @@
 namespace {
 
 PyTypeObject* shape_type = nullptr;
+PyObject* other_integer = nullptr;          // for what is no Python integer
 
 struct ToStop {};          // a Python error is set
 
@@ -25,11 +26,13 @@ void* pointer(PyObject* o) {
 }
 // as ctypes converts to c_int32 and c_int64: no floats, whatever has __index__, bits beyond are dropped
 uint64_t integer(PyObject* o) {
-    if (PyFloat_Check(o)) {
-        PyErr_SetString(PyExc_TypeError, "int expected instead of float instance");
-        throw ToStop();
+    PyObject* other = nullptr;
+    if (!PyIndex_Check(o)) {
+        o = other = PyObject_CallOneArg(other_integer, o);
+        if (!o) throw ToStop();
     }
     const unsigned long long v = PyLong_AsUnsignedLongLongMask(o);
+    Py_XDECREF(other);
     if (v == (unsigned long long)-1 && PyErr_Occurred()) throw ToStop();
     return v;
 }
@@ -210,19 +213,24 @@ ENTRY(permute) {
         return run([&] { return f(s, d, e.outer, e.rows, e.inner, N, st); });
     });
 }
-PyObject* set_shape_type(PyObject*, PyObject* o) {
-    if (!PyType_Check(o)) {
-        PyErr_SetString(PyExc_TypeError, "expected a type");
-        return nullptr;
-    }
-    Py_INCREF(o);
-    shape_type = reinterpret_cast<PyTypeObject*>(o);
-    Py_RETURN_NONE;
+// (the type of a shape, a function that makes an integer of what is none)
+ENTRY(set_up) {
+    return guarded(n, 2, [&]() -> PyObject* {
+        if (!PyType_Check(a[0]) || !PyCallable_Check(a[1])) {
+            PyErr_SetString(PyExc_TypeError, "expected a type and a function");
+            return nullptr;
+        }
+        Py_INCREF(a[0]);
+        Py_INCREF(a[1]);
+        shape_type = reinterpret_cast<PyTypeObject*>(a[0]);
+        other_integer = a[1];
+        Py_RETURN_NONE;
+    });
 }
 
 #define FAST(name) {#name, reinterpret_cast<PyCFunction>(reinterpret_cast<void*>(name)), METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {FAST(two), FAST(three), FAST(step_fwd), FAST(step_bwd), FAST(ring_fwd), FAST(ring_bwd), FAST(rope),
-                         FAST(permute), FAST(extent_of), {"set_shape_type", set_shape_type, METH_O, nullptr}, {nullptr, nullptr, 0, nullptr}};
+                         FAST(permute), FAST(extent_of), FAST(set_up), {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_marshal", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 
 }  // namespace

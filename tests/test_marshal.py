@@ -96,3 +96,42 @@ def test_a_binding_without_its_extension_says_how_to_build(monkeypatch):
     monkeypatch.setattr(sa, "_lib", None)
     with pytest.raises(RuntimeError, match="paper_2311_09431_amd.build.*no module"):
         sa.lib()
+
+
+class AsParameter:
+    def __init__(self, x):
+        self._as_parameter_ = x
+
+
+class Index:
+    def __index__(self):
+        return 2
+
+
+TWO = [2, True + 1, Index(), ctypes.c_int32(2), AsParameter(Index()), AsParameter(ctypes.c_int32(2))]
+
+
+def test_integers_are_what_ctypes_takes_for_them():
+    x = torch.zeros(2, 8, 4)
+    f = ctypes.CFUNCTYPE(ctypes.c_int, ctypes.c_int32)(lambda n: n)
+    for n in TWO:
+        assert f(n) == 2
+        with pytest.raises(TypeError, match="GPU tensor"):      # the number has been taken
+            sa.sa_stripe_permute(x, x.clone(), n, 1)
+    for n in (2.0, "2", None, ctypes.c_int64(2), AsParameter(2.0)):
+        with pytest.raises(ctypes.ArgumentError):
+            f(n)
+        with pytest.raises(ctypes.ArgumentError):
+            sa.sa_stripe_permute(x, x.clone(), n, 1)
+
+
+@pytest.mark.gpu
+def test_a_step_with_such_integers():
+    q, k, v = (torch.randn(1, 1, 8, 4, device="cuda") for _ in range(3))
+    got = []
+    for two in TWO:
+        o, lse = torch.zeros_like(q), torch.full((1, 1, 8), -float("inf"), device="cuda")
+        s = sa.shard_shape(q, 8, lse)
+        sa.sa_attn_step_fwd(q, k, v, o, lse, two, 1, 3, ctypes.c_int32(sa.STRIPED), s)
+        got.append(torch.cat((o.flatten(), lse.flatten())))
+    assert all(torch.equal(g, got[0]) for g in got)
