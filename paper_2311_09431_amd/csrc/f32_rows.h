@@ -7,8 +7,9 @@
 // makes 0 * inf, inf - inf, or a sum of row weights that is no number.  All of these leave something
 // that is not finite in the row's accumulators or row sum, so a kernel looks there once, at its end,
 // and a row where it finds it is done over here: NaN and infinities then reach the rows that see them
-// and no others.  One wavefront and serial dot products: about the speed of a vector kernel, and only
-// for such rows.  The look costs 16 fmas per 32 x 32 accumulator and workgroup.
+// and no others.  Rows too small for three terms go the same way (FAINT).  One wavefront and serial dot products: about the
+// speed of a vector kernel, and only for such rows.  The looks cost 16 fmas and 16 maxima per 32 x 32 accumulator and
+// workgroup.
 #pragma once
 #include <hip/hip_bf16.h>
 
@@ -59,10 +60,31 @@ __device__ inline bool not_finite(const Acc& acc) {
         for (int r = 0; r < 16; ++r) z[r % 4] = fmaf(acc[mb][r], 0.f, z[r % 4]);
     return (z[0] + z[1]) + (z[2] + z[3]) != 0.f;
 }
+// The largest magnitude in the first NB accumulators (NaN passed over).  Three bf16 terms cover a number down to 2^-109;
+// below, the last one is subnormal and up to 2^-134 is lost of it.  So where operands are such terms, a row whose results
+// are all below FAINT, and not all zero, is done over here too; from FAINT on what is lost is below fp32's own
+// rounding, 2^-24 of the result, for weights and elements whose squares sum to less than 2^10 over the row.  dO, V, K or Q
+// scaled by 2^-100 to 2^-120, heads of 257 to 512 rows, the worst output's error against 64 bits: terms alone 4.6e-4, the
+// fp32 instruction 5.0e-7, done over 3.2e-7.  (Where every product has a factor below 2^-134, the result is
+// zero: it is below fp32's normal numbers but for factors beyond 2^8.)
+constexpr float FAINT = 0x1p-105f;
+template <int NB, typename Acc>
+__device__ inline float loudest(const Acc& acc) {
+    float z[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int mb = 0; mb < NB; ++mb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) z[r % 4] = fmaxf(z[r % 4], fabsf(acc[mb][r]));
+    return fmaxf(fmaxf(z[0], z[1]), fmaxf(z[2], z[3]));
+}
 // rows (bit n: lanes n and n + 32) for which a lane says so
 __device__ inline uint32_t row_mask(bool lane_says) {
     const uint64_t m = __builtin_amdgcn_ballot_w64(lane_says);
     return (uint32_t)m | (uint32_t)(m >> 32);
+}
+// the faint ones of the rows that lie in the shard
+__device__ inline uint32_t faint_rows(float top, bool in_shard) {
+    return row_mask(in_shard && top > 0.f) & ~row_mask(top >= FAINT);
 }
 
 // The rows set in a mask, taken in turn by the SPLIT wavefronts that own them: row(arguments, n).  The
@@ -91,16 +113,16 @@ constexpr int ROW_COLS = 256 / 64;
 
 template <typename T>
 __device__ inline float dot_rows(const T* x, const T* y, int d) {
-    float s = 0.f;
+    double s = 0.;          // (sums in fp64: a row done over is no further off than the kernels' own)
 #pragma unroll 1
     for (int t = 0; t < d; t += 4) {
         const float4 a = ld4<T>(x + t), b = ld4<T>(y + t);
-        s = fmaf(a.x, b.x, s);
-        s = fmaf(a.y, b.y, s);
-        s = fmaf(a.z, b.z, s);
-        s = fmaf(a.w, b.w, s);
+        s = fma((double)a.x, (double)b.x, s);
+        s = fma((double)a.y, (double)b.y, s);
+        s = fma((double)a.z, (double)b.z, s);
+        s = fma((double)a.w, (double)b.w, s);
     }
-    return s;
+    return (float)s;
 }
 __device__ inline float wave_max(float x) {
 #pragma unroll 1
@@ -116,15 +138,18 @@ __device__ inline float wave_sum(float x) {
 template <typename T>
 __device__ inline void add_weighted(float (&acc)[ROW_COLS], float weight, const T* rows, int64_t ss, int n, int col0,
                                     int d, int lane) {
+    double part[ROW_COLS] = {};
 #pragma unroll 1
     for (int i = 0; i < n; ++i) {
         const float w = __shfl(weight, i);
 #pragma unroll
         for (int k = 0; k < ROW_COLS; ++k) {
             const int col = col0 + lane + 64 * k;
-            if (col < d) acc[k] = fmaf(w, ld1(rows + i * ss + col), acc[k]);
+            if (col < d) part[k] = fma((double)w, (double)ld1(rows + i * ss + col), part[k]);
         }
     }
+#pragma unroll
+    for (int k = 0; k < ROW_COLS; ++k) acc[k] += (float)part[k];
 }
 
 // forward, query row a of the launch's device dev_i: its shards folded into (O, LSE)

@@ -6,8 +6,7 @@
 namespace sa {
 
 // x = hi + mid + lo (+ less than 2^-26 x; below 2^-109 in magnitude lo is a subnormal number, and x has
-// fewer than 24 bits left: with every element of dO scaled by 2^-108, 2^-112 and 2^-120 the error of dQ is
-// 3.1e-7, 2.0e-6 and 5.1e-4, that of fp32 sums 4.1e-7).  An infinite x, or one that rounds to an infinite hi, has NaN among its
+// fewer than 24 bits left: FAINT in f32_rows.h).  An infinite x, or one that rounds to an infinite hi, has NaN among its
 // terms, and every sum of products with it is NaN: the kernels do such rows over (f32_rows.h).
 __device__ inline void split(float x, __bf16& hi, __bf16& mid, __bf16& lo) {
     hi = (__bf16)x;

@@ -247,7 +247,7 @@ fwd_f32x3_split_kernel(StepArgs p, int n_tiles) {
     static_assert(PARTIAL_BYTES<DP, WAVES> <= STAGES_BYTES<DP>, "partial results");
     __shared__ __attribute__((aligned(1024))) char lds[STAGES_BYTES<DP> + OWN_BYTES<DP>];
     __shared__ float stats[WAVES * 64];                // [wave][m | l][32]
-    __shared__ uint32_t masks[WAVES];
+    __shared__ uint32_t masks[3 * WAVES];
 
     const RawLane<DP> ln;
     const int n = ln.n, h = ln.h;
@@ -334,7 +334,7 @@ fwd_f32x3_split_kernel(StepArgs p, int n_tiles) {
     }
     wait_all_but<0>();
     float* L = p.lse + b * p.stat_stride_b + hd * p.stat_stride_h + (int64_t)dev_i * p.c + a;
-    const uint32_t odd_rows = fold_forward<DP, WAVES, true>(p, acc, m, l, lds, stats, masks, ln, dev, a_own, a, L,
+    const uint32_t odd_rows = fold_forward<DP, WAVES, true, true>(p, acc, m, l, lds, stats, masks, ln, dev, a_own, a, L,
                                                             p.o + base + (int64_t)a * p.stride_s);
     each_row<WAVES>(odd_rows, ln.wave, [&](const StepArgs& again, int i) { fwd_row<float>(again, b, hd, dev_i, q0 + i, ln.lane); });
 }
@@ -422,8 +422,9 @@ __device__ inline void bwd_dq(const StepArgs& p, int n_tiles, int linear, char* 
     __syncthreads();
     put_partial<DP>(lds, acc, ln);
     put_odd(masks, a_own < p.c && not_finite<blocks_of(DP)>(acc), ln.wave, ln.lane);
+    put_faint<WAVES>(masks + WAVES, loudest<blocks_of(DP)>(acc), a_own < p.c, ln.wave, ln.lane);
     __syncthreads();
-    const uint32_t odd_rows = take_odd<WAVES>(masks);
+    const uint32_t odd_rows = take_odd<WAVES>(masks) | take_faint<WAVES>(masks + WAVES);
     if (a_own < p.c && !((odd_rows >> n) & 1)) add_rows<DP, WAVES>(DQ, old, lds, p.scale, d, ln);
     each_row<WAVES>(odd_rows, ln.wave, [&](const StepArgs& again, int i) { dq_row<float>(again, b, hd, dev_i, q0 + i, ln.lane); });
 }
@@ -548,8 +549,10 @@ __device__ inline void bwd_dkdv(const StepArgs& p, int n_tiles, int linear, char
     put_partial<DP>(lds, accv, ln);
     put_partial<DP>(lds + HALF, acck, ln);
     put_odd(masks, key_own < p.c && (not_finite<blocks_of(DP)>(accv) || not_finite<blocks_of(DP)>(acck)), ln.wave, ln.lane);
+    put_faint<WAVES>(masks + WAVES, loudest<blocks_of(DP)>(accv), key_own < p.c, ln.wave, ln.lane);
+    put_faint<WAVES>(masks + 3 * WAVES, loudest<blocks_of(DP)>(acck), key_own < p.c, ln.wave, ln.lane);
     __syncthreads();
-    const uint32_t odd_rows = take_odd<WAVES>(masks);
+    const uint32_t odd_rows = take_odd<WAVES>(masks) | take_faint<WAVES>(masks + WAVES) | take_faint<WAVES>(masks + 3 * WAVES);
     if (key_own < p.c && !((odd_rows >> n) & 1)) {
         add_rows<DP, WAVES>(p.dv + row, old_v, lds, 1.f, d, ln);
         add_rows<DP, WAVES>(p.dk + row, old_k, lds + HALF, p.scale, d, ln);
@@ -563,7 +566,7 @@ __global__ void __launch_bounds__(64 * WAVES_OF<DP>, WAVES_OF<DP> / 4)
 bwd_f32x3_split_kernel(StepArgs p, int n_tiles, BothKinds kinds) {
     __shared__ __attribute__((aligned(1024))) char lds[STAGES_BYTES<DP> + 2 * OWN_BYTES<DP>];
     __shared__ __attribute__((aligned(1024))) char stats[WAVES_OF<DP> * STAT_BYTES];
-    __shared__ uint32_t masks[WAVES_OF<DP>];
+    __shared__ uint32_t masks[5 * WAVES_OF<DP>];
     int linear = (int)blockIdx.x;
     if (owns_keys(kinds, linear)) bwd_dkdv<DP>(p, n_tiles, linear, lds, stats, masks);
     else bwd_dq<DP>(p, n_tiles, linear, lds, masks);

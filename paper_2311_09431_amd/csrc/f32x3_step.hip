@@ -282,7 +282,8 @@ fwd_f32x3_kernel(StepArgs p, int n_tiles) {
     const float top = fmaxf(old, part);
     // a row sum that is no positive number although the row sees a key: see f32_rows.h
     const uint32_t odd_rows =
-        row_mask(a_own < p.c && (not_finite<NB>(acc) || (!(l_tot > 0.f && l_tot < INFINITY) && sees_a_key(p, dev, a))));
+        row_mask(a_own < p.c && (not_finite<NB>(acc) || (!(l_tot > 0.f && l_tot < INFINITY) && sees_a_key(p, dev, a)))) |
+        faint_rows(loudest<NB>(acc), a_own < p.c);
     // no row here, or no key seen: state unchanged
     if (a_own < p.c && !((odd_rows >> n) & 1) && (part != -INFINITY || p.fresh)) {
         const float ref = top == -INFINITY ? 0.f : top;
@@ -354,12 +355,17 @@ struct Exchange {
     }
 };
 constexpr int EXCHANGED = 2 * GROUPS * 4096;
-// rows that either wavefront of a pair names
-__device__ inline uint32_t odd_of_pair(uint32_t* masks, bool odd, int wave, int lane) {
-    const uint32_t own = row_mask(odd);
-    if (lane == 0) masks[wave] = own;
+// rows that either wavefront of a pair names, and those that are faint in what both hold of them
+__device__ inline uint32_t odd_of_pair(uint32_t* masks, uint32_t odd, uint32_t some, uint32_t loud, int wave, int lane) {
+    if (lane == 0) {
+        masks[wave] = odd;
+        masks[2 * GROUPS + wave] = some;
+        masks[4 * GROUPS + wave] = loud;
+    }
     __syncthreads();
-    return __builtin_amdgcn_readfirstlane(masks[wave % GROUPS] | masks[wave % GROUPS + GROUPS]);
+    const uint32_t* const own = masks + wave % GROUPS;
+    auto either = [&](int i) { return own[2 * GROUPS * i] | own[2 * GROUPS * i + GROUPS]; };
+    return __builtin_amdgcn_readfirstlane(either(0) | (either(1) & ~either(2)));
 }
 
 // dQ.  The pair's wavefronts take half of its columns each.
@@ -459,7 +465,9 @@ __device__ inline void bwd_dq(const StepArgs& p, int n_tiles, int linear, char* 
         t_n = t_nn;
         parity ^= 1;
     }
-    const uint32_t odd_rows = odd_of_pair(masks, a_own < p.c && not_finite<NB>(acc), ln.wave, ln.lane);
+    const float top = loudest<NB>(acc);
+    const uint32_t odd_rows = odd_of_pair(masks, row_mask(a_own < p.c && not_finite<NB>(acc)), row_mask(a_own < p.c && top > 0.f),
+                                          row_mask(top >= FAINT), ln.wave, ln.lane);
     if (a_own < p.c && !((odd_rows >> n) & 1))
         add_rows<NB>(p.dq + base + (int64_t)a * p.stride_s, acc, p.scale, 32 * NB * role, d, h, p.fresh);
     each_row<2>(odd_rows, role, [&](const StepArgs& again, int i) { dq_row<float>(again, b, hd, dev_i, q0 + 32 * group + i, ln.lane); });
@@ -586,7 +594,9 @@ __device__ inline void bwd_dkdv(const StepArgs& p, int n_tiles, int linear, char
         t_n = t_nn;
         more = more_n;
     }
-    const uint32_t odd_rows = odd_of_pair(masks, key_own < p.c && not_finite<NB>(acc), ln.wave, ln.lane);
+    // (each has all columns of its result)
+    const uint32_t odd_rows = odd_of_pair(masks, row_mask(key_own < p.c && not_finite<NB>(acc)) |
+                                                     faint_rows(loudest<NB>(acc), key_own < p.c), 0, 0, ln.wave, ln.lane);
     if (key_own < p.c && !((odd_rows >> n) & 1))
         add_rows<NB>((role ? p.dk : p.dv) + row, acc, role ? p.scale : 1.f, 0, d, h, p.fresh);
     each_row<2>(odd_rows, role, [&](const StepArgs& again, int i) { dkdv_row<float>(again, b, kvh, dev_i, k0 + 32 * group + i, 0, d, ln.lane); });
@@ -600,7 +610,7 @@ bwd_f32x3_kernel(StepArgs p, int n_tiles, int n_first, bool keys_first) {
     __shared__ __attribute__((aligned(1024))) char lds[2 * BUFFER];
     __shared__ __attribute__((aligned(1024))) char tiles[EXCHANGED];
     __shared__ float stats[2 * 3 * TILE];          // [buffer][LSE hi | LSE lo | delta][row]
-    __shared__ uint32_t masks[2 * GROUPS];
+    __shared__ uint32_t masks[6 * GROUPS];
     const bool first = (int)blockIdx.x < n_first;
     const int linear = first ? (int)blockIdx.x : (int)blockIdx.x - n_first;
     if (first == keys_first) bwd_dkdv<DP>(p, n_tiles, linear, lds, tiles, stats, masks);

@@ -344,7 +344,7 @@ fwd_split_kernel(StepArgs p, int n_tiles) {
         }
     }
 
-    const uint32_t odd_rows = fold_forward<DP, WAVES, EXACT>(p, acc, m, l, lds, stats, masks, ln, dev, a_own, a, L,
+    const uint32_t odd_rows = fold_forward<DP, WAVES, EXACT, false>(p, acc, m, l, lds, stats, masks, ln, dev, a_own, a, L,
                                                              p.o + base + (int64_t)a * p.stride_s);
     if (EXACT) each_row<WAVES>(odd_rows, ln.wave, [&](const StepArgs& again, int i) { fwd_row<__hip_bfloat16>(again, b, hd, dev_i, q0 + i, ln.lane); });
 }

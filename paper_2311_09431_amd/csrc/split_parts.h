@@ -80,6 +80,19 @@ __device__ inline uint32_t take_odd(const uint32_t* masks) {
     for (int w = 0; w < WAVES; ++w) rows |= masks[w];
     return __builtin_amdgcn_readfirstlane(rows);
 }
+// rows that are faint (f32_rows.h) in all wavefronts' partial results; masks: two for each wavefront
+template <int WAVES>
+__device__ inline void put_faint(uint32_t* masks, float top, bool in_shard, int wave, int lane) {
+    const uint32_t some = row_mask(in_shard && top > 0.f), loud = row_mask(top >= FAINT);
+    if (lane == 0) {
+        masks[wave] = some;
+        masks[WAVES + wave] = loud;
+    }
+}
+template <int WAVES>
+__device__ inline uint32_t take_faint(const uint32_t* masks) {
+    return take_odd<WAVES>(masks) & ~take_odd<WAVES>(masks + WAVES);
+}
 // The sub-tiles of 32 keys that one wavefront of a query-owning workgroup takes: those of block kv whose
 // number v is `turn` modulo the number of wavefronts, turn being the wavefront's number less the sub-tiles of
 // the blocks before.
@@ -127,8 +140,8 @@ struct KeyCursor {
 
 // Forward, the end: the wavefronts' partial results (accumulators, base-2 reference m, half-wave row sum l) folded
 // into the running state of the lane's row (base: of the workgroup's rows' matrix, a: the row, clamped to the shard).
-// Returns the rows to do over (EXACT only).
-template <int DP, int WAVES, bool EXACT, typename Lane>
+// Returns the rows to do over (EXACT only; TERMS: V was three bf16 terms, masks are three for each wavefront).
+template <int DP, int WAVES, bool EXACT, bool TERMS, typename Lane>
 __device__ __forceinline__ uint32_t fold_forward(const StepArgs& p, f32x16 (&acc)[4], float m, float l, char* lds, float* stats,
                                                  uint32_t* masks, const Lane& ln, int dev, int a_own, int a, float* L, float* O) {
     constexpr int MB = blocks_of(DP), N = share_of(DP, WAVES);
@@ -161,6 +174,7 @@ __device__ __forceinline__ uint32_t fold_forward(const StepArgs& p, f32x16 (&acc
     if (EXACT)
         put_odd(masks, a_own < p.c && (not_finite<MB>(acc) ||
                                        (!(l_tot > 0.f && l_tot < INFINITY) && sees_a_key(p, dev, a))), ln.wave, ln.lane);
+    if (TERMS) put_faint<WAVES>(masks + WAVES, loudest<MB>(acc), a_own < p.c, ln.wave, ln.lane);
 
     const float part = l_tot == 0.f ? -INFINITY : fmaf(m_all, LN2_HI, fmaf(m_all, LN2_LO, logf(l_tot)));
     const float top = fmaxf(old, part);
@@ -169,7 +183,8 @@ __device__ __forceinline__ uint32_t fold_forward(const StepArgs& p, f32x16 (&acc
     const float inv = w_sum > 0.f ? 1.f / w_sum : 0.f;
     const float f_old = w_old * inv, f_part = l_tot > 0.f ? w_part * inv / l_tot : 0.f;
     __syncthreads();
-    const uint32_t odd_rows = EXACT ? take_odd<WAVES>(masks) : 0;
+    uint32_t odd_rows = EXACT ? take_odd<WAVES>(masks) : 0;
+    if (TERMS) odd_rows |= take_faint<WAVES>(masks + WAVES);
     // no row here, or no key seen: state unchanged
     if (a_own < p.c && !((odd_rows >> n) & 1) && (part != -INFINITY || p.fresh)) {
 #pragma unroll

@@ -2,11 +2,12 @@
 their sub-tiles of 32 rows by themselves, operands as three bf16 terms.  Against fp64 over the allowed pairs at the
 edges of the sub-tiles, of a round of the wavefronts (4 and 8 sub-tiles) and of the columns (32, 64, 128 computed, chunks
 of four), single steps on a running state, with grouped heads, infinities and NaN; the bounds are the fp32
-configuration's."""
+configuration's.  And magnitudes that three bf16 terms do not cover."""
 import pytest
 import torch
 
 from paper_2311_09431_amd import binding as sa
+from paper_2311_09431_amd import inputs
 from tests import routes
 from tests import test_nonfinite_gpu as nf
 
@@ -54,3 +55,39 @@ def test_rows_out_of_reach_are_others():
             taken = [p for p in pitches if routes._ask("f32x3_split_wanted", routes.args(c, d, 1, **{side: p}), False)]
             assert taken and all(behind * 4 * p + 4 * d + 4096 < 1 << 31 for p in taken)
             assert len(taken) < len(pitches)
+
+
+SMALL = [
+    # H, c, d, 32-row workgroups
+    (2, 257, 64, True),
+    (3, 160, 100, True),
+    (4, 289, 28, True),
+    (64, 512, 128, False),
+]
+
+
+@pytest.mark.parametrize("small", ["q", "k", "v", "g"])
+@pytest.mark.parametrize("H,c,d,split", SMALL)
+def test_small_magnitudes(H, c, d, split, small):
+    # three bf16 terms hold fewer than 24 bits of a number below 2^-109.  One operand scaled by a power of two: every output's
+    # error in the 2-norm as without (3.5e-7 here, the fp32 instruction's 5.0e-7), not more than 1e-6
+    for back in (False, True):
+        assert routes._ask("f32x3_split_wanted", routes.args(c, d, H, q_dev=0), back) == split
+    see = torch.ones(c, c, dtype=torch.bool, device="cuda").tril()
+    for exponent in (-100, -105, -109, -112, -116, -120):
+        x = {n: inputs.gaussian((1, H, c, d), 30 + i, device="cuda") for i, n in enumerate("qkvg")}
+        x[small] *= 2.0 ** exponent
+        o, lse, delta = torch.zeros_like(x["q"]), torch.empty(1, H, c, device="cuda"), torch.empty(1, H, c, device="cuda")
+        grads = [torch.zeros_like(o) for _ in range(3)]
+        shape = sa.shard_shape(x["q"], c, lse)
+        sa.sa_state_init(o, lse, shape)
+        sa.sa_attn_step_fwd(x["q"], x["k"], x["v"], o, lse, 0, 0, 1, sa.STRIPED, shape)
+        sa.sa_bwd_preprocess(o, x["g"], delta, shape)
+        sa.sa_attn_step_bwd(x["q"], x["k"], x["v"], x["g"], lse, delta, *grads, 0, 0, 1, sa.STRIPED, shape)
+        q, k, v, g = (x[n].double() for n in "qkvg")
+        t = lambda y: y.transpose(-1, -2).contiguous()      # noqa: E731
+        p = (q @ t(k) * d ** -0.5).masked_fill(~see, -float("inf")).softmax(-1)
+        ds = p * (g @ t(v) - (g * (p @ v)).sum(-1, keepdim=True)) * d ** -0.5
+        for name, got, want in (("O", o, p @ v), ("dQ", grads[0], ds @ k), ("dK", grads[1], t(ds) @ q), ("dV", grads[2], t(p) @ g)):
+            error = float((got.double() - want).norm() / want.norm())
+            assert error <= 1e-6, (name, exponent, error)
