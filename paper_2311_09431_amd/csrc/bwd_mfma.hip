@@ -131,8 +131,8 @@ __device__ __forceinline__ void dq_step(f32x16& s_cur, f32x16& dp_cur, f32x16& s
 // k_lds0 .. v_lds1: the tile buffers (two 128-column halves each when DP = 256), LDS objects of their
 // own: as parts of one array the compiler arranges the d = 256 kernels otherwise and a full step of
 // 8 heads, 8192 rows, takes 2.197 instead of 2.177 ms
-template <bool RAGGED, int WALK, int DP, bool PART>
-__device__ __forceinline__ void bwd_dq(const StepArgs& p, int n_tiles, int linear, bool by_rank, char* k_lds0, char* k_lds1,
+template <bool RAGGED, int WALK, int DP, bool PART, bool BY_RANK>
+__device__ __forceinline__ void bwd_dq(const StepArgs& p, int n_tiles, int linear, char* k_lds0, char* k_lds1,
                                        char* v_lds0, char* v_lds1) {
     constexpr int NH = halves_of(DP), KS = ksteps_of(DP), MB = halves_of(DP) * blocks_of(DP);      // k-steps per half, column blocks
 
@@ -140,7 +140,7 @@ __device__ __forceinline__ void bwd_dq(const StepArgs& p, int n_tiles, int linea
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);      // wave-uniform, kept scalar
     constexpr bool RING = WALK == WALK_RING;
     int rank, bh, dev = p.q_dev;
-    decode_block<true>(linear, RING ? n_tiles * p.n_q : n_tiles, p.B * p.H, by_rank, rank, bh);
+    decode_block<true, BY_RANK>(linear, RING ? n_tiles * p.n_q : n_tiles, p.B * p.H, rank, bh);
     if (RING) {
         int dev_rank;
         decode_rank(rank, n_tiles, p.n_q, p.layout, rank, dev_rank);
@@ -459,7 +459,7 @@ __device__ __forceinline__ void dkdv_step(f32x16& s_cur, f32x16& dp_cur, f32x16&
 // first to the last: the query heads that share this key/value head, each with the query shards of
 // the devices that see these keys.
 // q_lds0 .. g_lds1: the tile buffers, as in the dQ kernel; stat: KV_STAT_FLOATS floats
-template <int WALK, bool RAGGED, int DP, bool PART>
+template <int WALK, bool RAGGED, int DP, bool PART, bool BY_RANK>
 __device__ __forceinline__ void bwd_dkdv(const StepArgs& p, int n_tiles, int linear, char* q_lds0, char* q_lds1,
                                          char* g_lds0, char* g_lds1, float* stat) {
     constexpr int NH = halves_of(DP), KS = ksteps_of(DP), MB = blocks_of(DP);      // per half
@@ -469,7 +469,7 @@ __device__ __forceinline__ void bwd_dkdv(const StepArgs& p, int n_tiles, int lin
     constexpr bool RING = WALK == WALK_RING;
     int ktile, bhh, dev = p.kv_dev;               // triangular blocks: low key tiles see most queries: first
     // one workgroup per (key tile, device, batch, key/value head, 128-column half of dK / dV)
-    decode_block<false>(linear, RING ? n_tiles * p.n_kv : n_tiles, p.B * p.H_kv * NH, uneven(p), ktile, bhh);
+    decode_block<false, BY_RANK>(linear, RING ? n_tiles * p.n_kv : n_tiles, p.B * p.H_kv * NH, ktile, bhh);
     if (RING) {
         int dev_rank;
         decode_rank(ktile, n_tiles, p.n_kv, p.layout, ktile, dev_rank);
@@ -810,6 +810,7 @@ __device__ __forceinline__ void wide_step(f32x16& s_cur, f32x16& dp_cur, f32x16&
     }
 }
 
+template <bool BY_RANK>
 __global__ void __launch_bounds__(256, 1)
 bwd_dkdv_wide_kernel(StepArgs p, int n_tiles) {
     __shared__ __attribute__((aligned(1024))) char lds[3 * WIDE_STAGE];
@@ -818,7 +819,7 @@ bwd_dkdv_wide_kernel(StepArgs p, int n_tiles) {
     const int tid = threadIdx.x, lane = tid & 63, n = lane & 31, h = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     int ktile, bh, dev_rank;
-    decode_block<false>((int)blockIdx.x, n_tiles * p.n_kv, p.B * p.H_kv, uneven(p), ktile, bh);
+    decode_block<false, BY_RANK>((int)blockIdx.x, n_tiles * p.n_kv, p.B * p.H_kv, ktile, bh);
     decode_rank(ktile, n_tiles, p.n_kv, p.layout, ktile, dev_rank);
     const int dev = p.kv_dev + dev_rank;
     const int b = bh / p.H_kv, kvh = bh - b * p.H_kv;
@@ -986,20 +987,20 @@ bwd_dkdv_wide_kernel(StepArgs p, int n_tiles) {
         }
 }
 
-template <bool RAGGED, int WALK, int DP, bool PART>
+template <bool RAGGED, int WALK, int DP, bool PART, bool BY_RANK>
 __global__ void __launch_bounds__(256, DP > 128 ? 1 : 2)
 bwd_dq_mfma_kernel(StepArgs p, int n_tiles) {
     __shared__ __attribute__((aligned(1024))) char lds0[tile_bytes(DP) * halves_of(DP)];
     __shared__ __attribute__((aligned(1024))) char lds1[tile_bytes(DP) * halves_of(DP)];
     __shared__ __attribute__((aligned(1024))) char lds2[tile_bytes(DP) * halves_of(DP)];
     __shared__ __attribute__((aligned(1024))) char lds3[tile_bytes(DP) * halves_of(DP)];
-    bwd_dq<RAGGED, WALK, DP, PART>(p, n_tiles, (int)blockIdx.x, uneven(p), lds0, lds1, lds2, lds3);
+    bwd_dq<RAGGED, WALK, DP, PART, BY_RANK>(p, n_tiles, (int)blockIdx.x, lds0, lds1, lds2, lds3);
 }
 // WAVES: wavefronts per SIMD the register budget is cut for.  Up to 64 columns two fit (half the
 // operands and accumulators; the loops do not spill), and with half of the products per score it is
 // the vector work that needs hiding: 16 heads, d 64, backward step, 12500 tokens triangular
 // 1.46 -> 1.37 ms, full 2.87 -> 2.46; 32 heads of 32768, triangular, 17.3 -> 14.7 ms.
-template <int WALK, bool RAGGED, int DP, bool PART, int WAVES>
+template <int WALK, bool RAGGED, int DP, bool PART, int WAVES, bool BY_RANK>
 __global__ void __launch_bounds__(256, WAVES)
 bwd_dkdv_mfma_kernel(StepArgs p, int n_tiles) {
     __shared__ __attribute__((aligned(1024))) char lds0[tile_bytes(DP) * halves_of(DP)];
@@ -1007,7 +1008,7 @@ bwd_dkdv_mfma_kernel(StepArgs p, int n_tiles) {
     __shared__ __attribute__((aligned(1024))) char lds2[tile_bytes(DP) * halves_of(DP)];
     __shared__ __attribute__((aligned(1024))) char lds3[tile_bytes(DP) * halves_of(DP)];
     __shared__ __attribute__((aligned(16))) float stat[KV_STAT_FLOATS];
-    bwd_dkdv<WALK, RAGGED, DP, PART>(p, n_tiles, (int)blockIdx.x, lds0, lds1, lds2, lds3, stat);
+    bwd_dkdv<WALK, RAGGED, DP, PART, BY_RANK>(p, n_tiles, (int)blockIdx.x, lds0, lds1, lds2, lds3, stat);
 }
 // Both kinds of workgroups in one launch (each sequence heaviest first; above 512 of a kind by groups of
 // heads, see decode_block): where the key-owning ones do not fill the chip, or fill it once and last
@@ -1022,9 +1023,9 @@ bwd_both_mfma_kernel(StepArgs p, int n_tiles, BothKinds kinds) {
     __shared__ __attribute__((aligned(1024))) char lds3[tile_bytes(DP) * halves_of(DP)];
     __shared__ __attribute__((aligned(16))) float stat[KV_STAT_FLOATS];
     int linear = (int)blockIdx.x;
-    if (owns_keys(kinds, linear)) bwd_dkdv<WALK_RING, RAGGED, DP, PART>(p, n_tiles, linear, lds0, lds1, lds2, lds3, stat);
-    // (32 heads on 8 of 4096 rows, d 100, by ranks 464 -> 470 us)
-    else bwd_dq<RAGGED, WALK_RING, DP, PART>(p, n_tiles, linear, false, lds0, lds1, lds2, lds3);
+    if (owns_keys(kinds, linear)) bwd_dkdv<WALK_RING, RAGGED, DP, PART, false>(p, n_tiles, linear, lds0, lds1, lds2, lds3, stat);
+    // (by heads or groups of them, both: 32 heads on 8 of 4096 rows, d 100, by ranks 464 -> 470 us)
+    else bwd_dq<RAGGED, WALK_RING, DP, PART, false>(p, n_tiles, linear, lds0, lds1, lds2, lds3);
 }
 
 }  // namespace
@@ -1044,17 +1045,21 @@ bool bwd_mfma_supported(const StepArgs& a, int dtype) {
 }
 
 namespace {
-template <int WALK, int DP, bool PART>
+template <int WALK, int DP, bool PART, bool BY_RANK = false>
 void launch_dq(const StepArgs& a, hipStream_t st, int n_tiles) {
     const dim3 grid((unsigned)n_tiles * a.n_q * a.B * a.H), block(256);
-    if (a.c % BM) hipLaunchKernelGGL((bwd_dq_mfma_kernel<true, WALK, DP, PART>), grid, block, 0, st, a, n_tiles);
-    else hipLaunchKernelGGL((bwd_dq_mfma_kernel<false, WALK, DP, PART>), grid, block, 0, st, a, n_tiles);
+    if constexpr (WALK != WALK_FULL && !BY_RANK)
+        if (by_rank(uneven(a), grid.x, MOST_BY_RANK<DP, false>)) return launch_dq<WALK, DP, PART, true>(a, st, n_tiles);
+    if (a.c % BM) hipLaunchKernelGGL((bwd_dq_mfma_kernel<true, WALK, DP, PART, BY_RANK>), grid, block, 0, st, a, n_tiles);
+    else hipLaunchKernelGGL((bwd_dq_mfma_kernel<false, WALK, DP, PART, BY_RANK>), grid, block, 0, st, a, n_tiles);
 }
-template <int WALK, int DP, bool PART, int WAVES>
+template <int WALK, int DP, bool PART, int WAVES, bool BY_RANK = false>
 void launch_dkdv_waves(const StepArgs& a, hipStream_t st, int n_tiles) {
     const dim3 grid((unsigned)n_tiles * a.n_kv * a.B * a.H_kv * halves_of(DP)), block(256);
-    if (a.c % BM) hipLaunchKernelGGL((bwd_dkdv_mfma_kernel<WALK, true, DP, PART, WAVES>), grid, block, 0, st, a, n_tiles);
-    else hipLaunchKernelGGL((bwd_dkdv_mfma_kernel<WALK, false, DP, PART, WAVES>), grid, block, 0, st, a, n_tiles);
+    if constexpr (WALK != WALK_FULL && DP <= 128 && !BY_RANK)          // (above: bwd_dkdv_wide_kernel)
+        if (by_rank(uneven(a), grid.x, MOST_BY_RANK<DP, false>)) return launch_dkdv_waves<WALK, DP, PART, WAVES, true>(a, st, n_tiles);
+    if (a.c % BM) hipLaunchKernelGGL((bwd_dkdv_mfma_kernel<WALK, true, DP, PART, WAVES, BY_RANK>), grid, block, 0, st, a, n_tiles);
+    else hipLaunchKernelGGL((bwd_dkdv_mfma_kernel<WALK, false, DP, PART, WAVES, BY_RANK>), grid, block, 0, st, a, n_tiles);
 }
 template <int WALK, int DP, bool PART>
 void launch_dkdv(const StepArgs& a, hipStream_t st, int n_tiles) {
@@ -1113,7 +1118,10 @@ hipError_t launch_bwd_variant(const StepArgs& a, hipStream_t st) {
         // 320 tiles 285 : 239).
         const int64_t tiles = (int64_t)n_tiles * a.n_kv * a.B * a.H_kv;
         if (tiles > N_CU / 2) {
-            hipLaunchKernelGGL(bwd_dkdv_wide_kernel, dim3((unsigned)tiles), dim3(256), 0, st, a, n_tiles);
+            // (by ranks up to 1408 tiles; d 192 and 256, us, groups : ranks: 24 heads of 4096 529 : 465, 540 : 472, 44 of 4096
+            // 856 : 815, 897 : 878, 48 of 4096 849 : 891, 1030 : 1073, 64 of 4096 1134 : 1217, 1186 : 1357)
+            if (by_rank(uneven(a), tiles, 6 * N_CU - 1)) hipLaunchKernelGGL(bwd_dkdv_wide_kernel<true>, dim3((unsigned)tiles), dim3(256), 0, st, a, n_tiles);
+            else hipLaunchKernelGGL(bwd_dkdv_wide_kernel<false>, dim3((unsigned)tiles), dim3(256), 0, st, a, n_tiles);
             return hipGetLastError();
         }
     }

@@ -233,7 +233,7 @@ __device__ __forceinline__ void step(f32x16& s_cur, f32x16& s_next, bf16x8 (&p_c
 // last and the rows of all devices are in one grid.  Whole ring, 8 x 4096 tokens, 16 heads,
 // d 128, forward: 5.93 -> 4.03 ms; 4 x 1024 tokens, 2 heads, forward + backward: 1.42 -> 0.27 ms.
 // ROPE: the query rows are rotated by their position ids as they are loaded (d == DP).
-template <bool RAGGED, int WALK, int DP, bool PART, bool ROPE = false>
+template <bool RAGGED, int WALK, int DP, bool PART, bool BY_RANK, bool ROPE = false>
 __global__ void __launch_bounds__(64 * NW, DP > 128 ? 1 : 2)
 fwd_mfma_kernel(StepArgs p, int n_qtiles) {
     constexpr int NH = halves_of(DP), KS = ksteps_of(DP), MB = halves_of(DP) * blocks_of(DP);      // k-steps per half, column blocks
@@ -248,7 +248,7 @@ fwd_mfma_kernel(StepArgs p, int n_qtiles) {
     const int tid = threadIdx.x, lane = tid & 63, n = lane & 31, h = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);      // wave-uniform, kept scalar
     int rank, bh, dev = p.q_dev;
-    decode_block<true>((int)blockIdx.x, RING ? n_qtiles * p.n_q : n_qtiles, p.B * p.H, uneven(p), rank, bh);
+    decode_block<true, BY_RANK>((int)blockIdx.x, RING ? n_qtiles * p.n_q : n_qtiles, p.B * p.H, rank, bh);
     if (RING) {
         int dev_rank;
         decode_rank(rank, n_qtiles, p.n_q, p.layout, rank, dev_rank);
@@ -558,14 +558,16 @@ bool fwd_mfma_supported(const StepArgs& a, int dtype) {
 
 namespace {
 bool one_block(const StepArgs& a) { return a.n_q == 1 && a.n_kv == 1 && !a.fresh; }
-template <int WALK, int DP, bool PART>
+template <int WALK, int DP, bool PART, bool BY_RANK = false>
 void launch_fwd_walk(const StepArgs& a, hipStream_t st, dim3 grid, dim3 block, int n_qtiles) {
+    if constexpr (WALK != WALK_FULL && !BY_RANK)
+        if (by_rank(uneven(a), grid.x, MOST_BY_RANK<DP, true>)) return launch_fwd_walk<WALK, DP, PART, true>(a, st, grid, block, n_qtiles);
     // Up to 64 columns three workgroups fit a compute unit; uneven work that they would hold all (or
     // nearly all) at once is balanced better by two, so LDS is asked for that keeps the third out: 640
     // workgroups 96 -> 77 us, 768 96 -> 84, 1024 183 -> 173, but 1536 242 -> 260.
     const unsigned wgs = grid.x, keep_out = DP <= 64 && uneven(a) && wgs > 2 * N_CU && wgs <= 4 * N_CU ? 24576 : 0;
-    if (a.c % BM) hipLaunchKernelGGL((fwd_mfma_kernel<true, WALK, DP, PART>), grid, block, keep_out, st, a, n_qtiles);
-    else hipLaunchKernelGGL((fwd_mfma_kernel<false, WALK, DP, PART>), grid, block, keep_out, st, a, n_qtiles);
+    if (a.c % BM) hipLaunchKernelGGL((fwd_mfma_kernel<true, WALK, DP, PART, BY_RANK>), grid, block, keep_out, st, a, n_qtiles);
+    else hipLaunchKernelGGL((fwd_mfma_kernel<false, WALK, DP, PART, BY_RANK>), grid, block, keep_out, st, a, n_qtiles);
 }
 template <int DP, bool PART>
 void launch_fwd_variant(const StepArgs& a, hipStream_t st, dim3 grid, dim3 block, int n_qtiles) {
@@ -577,9 +579,11 @@ void launch_fwd_variant(const StepArgs& a, hipStream_t st, dim3 grid, dim3 block
 template <int DP>
 void launch_fwd_rope(const StepArgs& a, hipStream_t st, dim3 grid, dim3 block, int n_qtiles) {
     if (block_kind(a.q_dev, a.kv_dev, a.layout) == MASK_FULL)
-        hipLaunchKernelGGL((fwd_mfma_kernel<false, WALK_FULL, DP, false, true>), grid, block, 0, st, a, n_qtiles);
+        hipLaunchKernelGGL((fwd_mfma_kernel<false, WALK_FULL, DP, false, false, true>), grid, block, 0, st, a, n_qtiles);
+    else if (by_rank(uneven(a), grid.x, MOST_BY_RANK<DP, true>))
+        hipLaunchKernelGGL((fwd_mfma_kernel<false, WALK_TRI, DP, false, true, true>), grid, block, 0, st, a, n_qtiles);
     else
-        hipLaunchKernelGGL((fwd_mfma_kernel<false, WALK_TRI, DP, false, true>), grid, block, 0, st, a, n_qtiles);
+        hipLaunchKernelGGL((fwd_mfma_kernel<false, WALK_TRI, DP, false, false, true>), grid, block, 0, st, a, n_qtiles);
 }
 }  // namespace
 

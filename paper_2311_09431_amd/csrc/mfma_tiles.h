@@ -308,14 +308,20 @@ __device__ inline void decode_near(int linear, int n_ranks, int n_heads, bool un
 // mean load, by ranks 1.0.  An XCD keeps its heads (decode_near), but all at a time.  Triangular step, us, forward /
 // backward, groups : ranks: d 128, 24 heads of 4096 122 / 426 : 109 / 381, 64 of 2048 97 / 342 : 86 / 306, 32 of 8192 (2048
 // workgroups) 515 / 1791 : 499 / 1740, but 32 of 16384 (4096) 1868 / 6724 : 1895 / 6838 and a ring of 8 x 4096, 16 heads
-// (4096), backward 12.97 : 13.43 ms; d 64, 40 of 2560 61 / 198 : 50 / 164, 16 of 12500 354 / 1136 : 320 / 1106.
+// (4096), backward 12.97 : 13.43 ms; d 64, 40 of 2560 61 / 198 : 50 / 164, 16 of 12500 354 / 1136 : 320 / 1106.  The line
+// is where the gain ends, in workgroups: 3072 below 128 columns (48 heads of 8192, d 64, forward 452 : 419, d 100 740 : 723),
+// 2560 at 128 (40 of 8192 663 / 2280 : 641 / 2236, but 192 of 2048 forward 289 : 296, 24 of 16384 backward 5070 : 5153),
+// 2048 forward above (64 of 4096, d 256, 710 : 706, 40 of 8192 1498 : 1543, 96 of 4096 1054 : 1102).
+// A kernel has one of the two (BY_RANK): with both in its prologue small launches lost, us, one : both, 130 heads of 129
+// rows, d 128, forward 13.1 : 13.4, full block 15.5 : 15.9, 32 of 1024, d 256, full, 47.9 : 48.7, one of 512 25.4 : 25.9.
 constexpr int HEAD_GROUP = 8;
 constexpr int N_CU = 256;
-constexpr int MOST_BY_RANK = 12 * N_CU;
-template <bool SNAKE>
-__device__ inline void decode_block(int linear, int n_tiles, int n_bh, bool uneven, int& rank, int& bh) {
+template <int DP, bool FORWARD> constexpr int MOST_BY_RANK = (DP < 128 ? 12 : DP > 128 && FORWARD ? 8 : 10) * N_CU;
+inline bool by_rank(bool uneven, int64_t workgroups, int most) { return uneven && workgroups > 2 * N_CU && workgroups <= most; }
+template <bool SNAKE, bool BY_RANK>
+__device__ inline void decode_block(int linear, int n_tiles, int n_bh, int& rank, int& bh) {
+    if constexpr (BY_RANK) return decode_near(linear, n_tiles, n_bh, true, rank, bh);
     const int total = n_tiles * n_bh;
-    if (uneven && total > 2 * N_CU && total <= MOST_BY_RANK) return decode_near(linear, n_tiles, n_bh, true, rank, bh);
     if (total <= 2 * N_CU) {
         int s = linear;
         if (SNAKE && linear >= N_CU) s = total - 1 - (linear - N_CU);

@@ -14,7 +14,7 @@ from tests import routes
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("H,c,d", [(64, 1152, 64), (75, 900, 128), (58, 1280, 32), (38, 1792, 100)])
+@pytest.mark.parametrize("H,c,d", [(64, 1152, 64), (75, 900, 128), (58, 1280, 32), (38, 1792, 100), (75, 1024, 256)])
 def test_every_head_is_the_first(H, c, d):
     tiles = (c + 127) // 128
     assert 512 < tiles * H <= 3072
