@@ -20,7 +20,8 @@ LIB = os.path.join(HERE, "libstriped_attn.so")
 OBJ_DIR = os.path.join(ROOT, "_build")
 
 SOURCES = ["api.hip", "permute.hip", "elementwise.hip", "f32_step.hip", "fwd_mfma.hip",
-           "bwd_mfma.hip", "split_mfma.hip", "f32x3_step.hip", "f32x3_split.hip", "rows_step.hip"]
+           "bwd_mfma.hip", "split_mfma.hip", "f32x3_step.hip", "f32x3_split.hip", "f32_route.hip",
+           "rows_step.hip"]
 
 # Flags of single sources.  f32x3_step: score tiles are read by vector instructions right after
 # their products, so MFMA results stay out of the accumulation registers (forward 2.20 -> 2.10 ms,

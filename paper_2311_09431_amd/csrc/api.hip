@@ -111,7 +111,7 @@ size_t elt_size(int dtype) { return dtype == SA_F32 ? 4 : 2; }
 // hold one workgroup of 256 threads per 32 rows of each side (as many at d > 128, where a key-owning
 // workgroup has 64 rows and half of the columns; the bf16 forward workgroups of 512 threads, on blocks of fewer
 // than 128 rows or launches of a few workgroups, count as two; the fp32 ones of 512 threads per 32 rows are taken
-// only where their launch fits: f32x3_split_wanted).
+// only where their launch fits: f32x3_split_supported).
 constexpr int64_t kMostWorkgroups = (int64_t(1) << 24) - 1;
 int64_t workgroups_per_kv_head(const StepArgs& a) {
     return ((int64_t)a.c / 32 + 2) * ((int64_t)a.n_q * (a.H / a.H_kv) * (a.c < 128 ? 2 : 1) + a.n_kv);

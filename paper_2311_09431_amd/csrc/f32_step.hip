@@ -1,9 +1,9 @@
 // Ring-step kernels on the CDNA4 fp32 matrix cores (v_mfma_f32_32x32x2_f32: fp32 operands, fp32
 // accumulation): any head dimension up to 256, any block size, fp32 or bf16 inputs.  They serve
-// fp32 storage above 128 columns (error budget 1e-5, so no reduced-precision products and the accurate
+// fp32 storage above 128 columns and launches of few rows below (error budget 1e-5, so no reduced-precision products and the accurate
 // expf / logf) and the bf16 shapes the bf16 matrix-core kernels do not take (widened to fp32
-// on the way into LDS, so their probabilities are not rounded either).  fp32 up to 128 columns is
-// the work of f32x3_step.hip and f32x3_split.hip, most short bf16 blocks that of split_mfma.hip.
+// on the way into LDS, so their probabilities are not rounded either).  Most fp32 up to 128 columns is
+// the work of f32x3_step.hip and f32x3_split.hip (f32_route.hip), most short bf16 blocks that of split_mfma.hip.
 //
 // Measured against kernels with one wavefront per row and serial dot products on the vector ALU: a full
 // forward block of 2048 rows, 8 key/value heads for 32, d 128, fp32, 14.6 ms, backward 63, where the split form
@@ -528,20 +528,29 @@ hipError_t run(const StepArgs& a, int dtype, bool backward, hipStream_t st) {
     if (a.d <= 128) return run<__hip_bfloat16, 128>(a, backward, st);
     return run<__hip_bfloat16, 256>(a, backward, st);
 }
+// fp32 launches of few row tiles
+template <int DP>
+hipError_t run_few(const StepArgs& a, bool backward, hipStream_t st) {
+    return backward ? run_bwd<float, DP, 4>(a, st) : run_fwd<float, DP, 4>(a, st);
+}
+hipError_t launch_f32_storage(const StepArgs& a, bool backward, hipStream_t st) {
+    const F32Route route = f32_route(a, backward);
+    if (route == F32_SPLIT) return launch_f32x3_split(a, backward, st);
+    if (route != F32_INSTRUCTION) return launch_f32x3(a, backward, route == F32_TERMS_ALONE, st);
+    return a.d <= 32 ? run_few<32>(a, backward, st) : a.d <= 64 ? run_few<64>(a, backward, st) : run_few<128>(a, backward, st);
+}
 
 }  // namespace
 
 hipError_t launch_fwd_f32(const StepArgs& a, int dtype, hipStream_t st) {
     if (few_rows_wanted(a, dtype, false)) return launch_few_rows(a, dtype, false, st);
-    if (dtype == SA_F32 && a.d <= 128)
-        return f32x3_split_wanted(a, false) ? launch_f32x3_split(a, false, st) : launch_f32x3(a, false, st);
+    if (dtype == SA_F32 && a.d <= 128) return launch_f32_storage(a, false, st);
     if (short_exact_wanted(a, dtype, false)) return launch_short_exact(a, false, st);
     return run(a, dtype, false, st);
 }
 hipError_t launch_bwd_f32(const StepArgs& a, int dtype, hipStream_t st) {
     if (few_rows_wanted(a, dtype, true)) return launch_few_rows(a, dtype, true, st);
-    if (dtype == SA_F32 && a.d <= 128)
-        return f32x3_split_wanted(a, true) ? launch_f32x3_split(a, true, st) : launch_f32x3(a, true, st);
+    if (dtype == SA_F32 && a.d <= 128) return launch_f32_storage(a, true, st);
     if (short_exact_wanted(a, dtype, true)) return launch_short_exact(a, true, st);
     return run(a, dtype, true, st);
 }

@@ -584,59 +584,16 @@ hipError_t run(const StepArgs& a, bool backward, hipStream_t st) {
     return hipGetLastError();
 }
 
-// Both sides' rows come through descriptors with 32-bit byte offsets, up to 32 rows behind the block's last sub-tile.
-bool rows_in_reach(const StepArgs& a) {
+}  // namespace
+
+bool f32x3_split_supported(const StepArgs& a, bool backward) {
+    // both sides' rows come through descriptors with 32-bit byte offsets, up to 32 rows behind the block's last sub-tile
     const int64_t widest = a.stride_s > a.kv_stride_s ? a.stride_s : a.kv_stride_s;
-    return ((int64_t)(a.c + 31) / 32 * 32 + OWN) * 4 * widest + 4 * a.d + 4096 < (int64_t(1) << 31);
-}
-
-// HIP takes fewer than 2^32 threads a launch.  (One beyond it, in parts, would be faster here than in 128-row workgroups;
-// nothing near such sizes has been measured.)
-bool fits_a_launch(const StepArgs& a, bool backward) {
+    if (((int64_t)(a.c + 31) / 32 * 32 + OWN) * 4 * widest + 4 * a.d + 4096 >= (int64_t(1) << 31)) return false;
+    // HIP takes fewer than 2^32 threads a launch.  (One beyond it, in parts, would be faster here than in 128-row
+    // workgroups; nothing near such sizes has been measured.)
     const int64_t tiles = (a.c + OWN - 1) / OWN, owners = (int64_t)a.n_q * a.B * a.H + (backward ? (int64_t)a.n_kv * a.B * a.H_kv : 0);
-    return tiles * owners * 64 * (a.d <= 64 ? WAVES_OF<64> : WAVES_OF<128>) < (int64_t(1) << 32);
-}
-
-}  // namespace
-
-// Four times the workgroups of a quarter or an eighth of the walk, each with a start of its own, against 128-row (forward
-// launches of 512 such tiles and more: 256-row) workgroups that share the splitting of the streamed rows: neither the
-// number of tiles nor the walk decides alone.  So both sides' times are put together from what a workgroup takes,
-// us: `start` + `tile` per 32 streamed rows, fitted to steps of 128 to 2048 rows on an otherwise idle chip (to 10 %; one
-// head of 1024 rows, d 64, forward 65 / 18, backward 84 / 29; d 128, 109 / 37 and 163 / 72).  315 shapes of d 32, 64 and 128,
-// 1 to 256 heads of 40 to 4096 rows, groups of 4, rings of 2 to 16, measured both ways: what this picks takes 0.3 % more
-// than the better of the two (geometric mean; worst 1.23, whole ring of 4 x 256, 32 heads, d 32, backward 125 / 102).
-namespace {
-struct Takes { double start, tile; };
-struct TakesAll { Takes fwd128, fwd256, fwd_split, bwd128, bwd_split; double split_queries; };       // (of a key-owning one's)
-constexpr TakesAll TAKES32 = {{4.4, 1.86}, {5, 2.5}, {5.2, .235}, {6, 2.37}, {6.2, .43}, .85};
-constexpr TakesAll TAKES64 = {{5.8, 1.85}, {6, 2.85}, {6.6, .36}, {8.3, 2.36}, {8.5, .65}, .95};
-constexpr TakesAll TAKES128 = {{9.3, 3.1}, {13, 5}, {13.5, .735}, {13, 4.7}, {23.5, 1.5}, .8};
-
-// n1 workgroups with walks of up to t1 tiles, n2 of up to t2 (taking `less` of the others' time): the longest walk, or
-// rounds of as many as there are compute units; `mean`: the mean walk as a share of the longest.
-double makespan(const Takes& k, double mean, double n1, double t1, double n2 = 0., double t2 = 0., double less = 0.) {
-    const double all = n1 * (k.start + k.tile * mean * t1) + n2 * less * (k.start + k.tile * mean * t2);
-    const double longest = fmax(k.start + k.tile * t1, less * (k.start + k.tile * t2)), rounds = ceil((n1 + n2) / N_CU);
-    return fmax(longest, all / (n1 + n2) * rounds);
-}
-}  // namespace
-
-bool f32x3_split_wanted(const StepArgs& a, bool backward) {
-    if (a.d > TD || !rows_in_reach(a) || !fits_a_launch(a, backward)) return false;
-    const TakesAll& k = a.d <= 32 ? TAKES32 : a.d <= 64 ? TAKES64 : TAKES128;
-    // contiguous layout: key shards behind the last played device are seen by nobody
-    const int seen = a.layout == SA_STRIPED ? a.n_kv : a.q_dev + a.n_q - a.kv_dev;
-    const int n_kv = seen < a.n_kv ? seen : a.n_kv;
-    const double heads = (double)a.B * a.H * a.n_q, kv_heads = (double)a.B * a.H_kv * n_kv, mean = uneven(a) ? .5 : 1.;
-    const double keys = (double)a.c * n_kv / 32, queries = (double)a.c * a.n_q * (a.H / a.H_kv) / 32;        // tiles of a walk
-    auto tiles = [&](int rows) { return (double)((a.c + rows - 1) / rows); };
-    if (backward)
-        return makespan(k.bwd_split, mean, kv_heads * tiles(32), queries, heads * tiles(32), keys, k.split_queries) <
-               makespan(k.bwd128, mean, kv_heads * tiles(128), queries, heads * tiles(128), keys, 1.);
-    const bool wide = heads * tiles(128) >= 512;
-    return makespan(k.fwd_split, mean, heads * tiles(32), keys) <
-           makespan(wide ? k.fwd256 : k.fwd128, mean, heads * tiles(wide ? 256 : 128), keys);
+    return a.d <= TD && tiles * owners * 64 * (a.d <= 64 ? WAVES_OF<64> : WAVES_OF<128>) < (int64_t(1) << 32);
 }
 
 hipError_t launch_f32x3_split(const StepArgs& a, bool backward, hipStream_t st) {

@@ -1,5 +1,5 @@
 // Ring-step kernels for fp32 operands on the bf16 matrix cores, head dimension up to 128, launches
-// with enough 128-row workgroups to fill the chip (fewer: f32x3_split.hip, which has the rule).
+// with enough 128-row workgroups to fill the chip (fewer: f32x3_split.hip; the rule: f32_route.hip).
 //
 // The fp32 matrix cores run at a sixteenth of the bf16 rate.  A fp32 number is the sum of three
 // bf16 ones (each the rounding of what the ones before leave: 3 x 8 bits and two signs cover its 24
@@ -617,11 +617,177 @@ bwd_f32x3_kernel(StepArgs p, int n_tiles, int n_first, bool keys_first) {
     else bwd_dq<DP>(p, n_tiles, linear, lds, tiles, masks);
 }
 
+// The same with both operands and accumulators in one wavefront, above 64 columns: no exchange, and triangular blocks,
+// where a wavefront has work in some of the tiles only, cost less.  Faster for many heads of one or two tiles
+// (f32_route.hip: 128 heads of 128 rows, d 128, 58 : 46 us; 32 of 700 143 : 161).
+constexpr int ALONE = 4;
+template <int DP>
+__device__ inline void bwd_dq_alone(const StepArgs& p, int n_tiles, int linear, char* lds) {
+    constexpr int KS = ksteps_of(DP), NB = blocks_of(DP);
+    const Lane ln;
+    const int n = ln.n, h = ln.h;
+    int rank, bh, dev_rank;
+    decode(linear, p.B * p.H, rank, bh);
+    decode_rank(rank, n_tiles, p.n_q, p.layout, rank, dev_rank);
+    const int q0 = (n_tiles - 1 - rank) * 32 * ALONE, dev_i = p.n_q - 1 - dev_rank, dev = p.q_dev + dev_i;
+    const int b = bh / p.H, hd = bh - b * p.H, d = p.d;
+    const int64_t base = b * p.stride_b + hd * p.stride_h + dev_i * p.q_shard;
+    const int64_t kv_base = b * p.kv_stride_b + (hd / (p.H / p.H_kv)) * p.kv_stride_h;
+    const int64_t sbase = b * p.stat_stride_b + hd * p.stat_stride_h + (int64_t)dev_i * p.c;
+
+    const int a_own = q0 + 32 * ln.wave + n, a = min(a_own, p.c - 1);
+    bf16x8x3 qf[KS], gf[KS];
+    load_row<KS>(qf, (const float*)p.q + base + (int64_t)a * p.stride_s, h, d);
+    load_row<KS>(gf, (const float*)p.dout + base + (int64_t)a * p.stride_s, h, d);
+    const float delta = p.delta[sbase + a];
+    const Scale2 kappa(p.scale);
+    float lse, lse_lo;
+    to_base2(p.lse[sbase + a], lse, lse_lo);
+    f32x16 acc[NB];
+#pragma unroll
+    for (int mb = 0; mb < NB; ++mb) acc[mb] = zero16();
+
+    walk_keys<DP, ALONE>(p, dev, q0, kv_base, lds, [&](const char* k, const char* v, int key0, bool full, int off) {
+        const int wave_last = full ? p.c - 1 : min(q0 + 32 * ln.wave + 31, p.c - 1) - off;
+        if (key0 > wave_last) return;
+        const int lane_last = (full ? p.c - 1 : a - off) - key0;
+        f32x16 x = scores<KS>(k, qf, ln);
+        const f32x16 dp = scores<KS>(v, gf, ln);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const float pr = reg_row(r, h) <= lane_last ? kappa.exp2(x[r], lse, lse_lo) : 0.f;
+            x[r] = pr * (dp[r] - delta);
+        }
+        bf16x8x3 w[2];
+        terms_of(w, x);
+        accumulate<NB>(acc, k, w, ln.tr0, ln.tr1);
+    });
+    const uint32_t odd_rows = row_mask(a_own < p.c && not_finite<NB>(acc)) | faint_rows(loudest<NB>(acc), a_own < p.c);
+    if (a_own < p.c && !((odd_rows >> n) & 1))
+        add_rows<NB>(p.dq + base + (int64_t)a * p.stride_s, acc, p.scale, 0, d, h, p.fresh);
+    each_row<1>(odd_rows, 0, [&](const StepArgs& again, int i) { dq_row<float>(again, b, hd, dev_i, q0 + 32 * ln.wave + i, ln.lane); });
+}
+template <int DP>
+__device__ inline void bwd_dkdv_alone(const StepArgs& p, int n_tiles, int linear, char* lds, float* stats) {
+    constexpr int KS = ksteps_of(DP), NB = blocks_of(DP);
+    const Lane ln;
+    const int n = ln.n, h = ln.h, tid = threadIdx.x;
+    int tile, bh, dev_i;                                // low key tiles see most queries: first
+    decode(linear, p.B * p.H_kv, tile, bh);
+    decode_rank(tile, n_tiles, p.n_kv, p.layout, tile, dev_i);
+    const int k0 = tile * 32 * ALONE, dev = p.kv_dev + dev_i;
+    const int b = bh / p.H_kv, kvh = bh - b * p.H_kv, members = p.H / p.H_kv, d = p.d;
+    const int64_t kv_base = b * p.kv_stride_b + kvh * p.kv_stride_h + dev_i * p.kv_shard;
+
+    const int key_own = k0 + 32 * ln.wave + n, key = min(key_own, p.c - 1);
+    const int64_t row = kv_base + (int64_t)key * p.kv_stride_s;
+    const Scale2 kappa(p.scale);
+    bf16x8x3 kf[KS], vf[KS];
+    load_row<KS>(kf, (const float*)p.k + row, h, d);
+    load_row<KS>(vf, (const float*)p.v + row, h, d);
+    f32x16 acck[NB], accv[NB];
+#pragma unroll
+    for (int mb = 0; mb < NB; ++mb) acck[mb] = accv[mb] = zero16();
+
+    // (tiles and their statistics as in bwd_dkdv)
+    const int q_dev0 = p.layout == SA_STRIPED ? p.q_dev : max(p.q_dev, dev);
+    auto first_tile = [&](int q_dev) {
+        return block_kind(q_dev, dev, p.layout) == MASK_FULL ? 0 : (k0 + block_off(q_dev, dev, p.layout)) / TILE * TILE;
+    };
+    Staged<DP, ALONE> sq, sg;
+    float stat = 0.f;
+    int member_a = 0, dev_a = q_dev0, t_a = first_tile(q_dev0);
+    auto fetch = [&]() {
+        const int hd = kvh * members + member_a;
+        const int64_t base = b * p.stride_b + hd * p.stride_h + (dev_a - p.q_dev) * p.q_shard;
+        sq.fetch((const float*)p.q + base, p.stride_s, t_a, p.c, d);
+        sg.fetch((const float*)p.dout + base, p.stride_s, t_a, p.c, d);
+        if (tid < 2 * TILE) {
+            const int64_t at = b * p.stat_stride_b + hd * p.stat_stride_h + (int64_t)(dev_a - p.q_dev) * p.c +
+                               min(t_a + tid % TILE, p.c - 1);
+            stat = tid < TILE ? p.lse[at] : p.delta[at];
+        }
+        t_a += TILE;
+        if (t_a >= p.c) {
+            if (++dev_a == p.q_dev + p.n_q) {
+                dev_a = q_dev0;
+                ++member_a;
+            }
+            t_a = first_tile(dev_a);
+        }
+    };
+    auto put = [&](int parity) {
+        sq.put(lds + parity * BUFFER);
+        sg.put(lds + parity * BUFFER + OPERAND);
+        float* st = stats + parity * 3 * TILE;
+        if (tid < TILE) to_base2(stat, st[tid], st[TILE + tid]);
+        else if (tid < 2 * TILE) st[TILE + tid] = stat;
+    };
+    int q_dev = dev_a, t0 = t_a, parity = 0;
+    fetch();
+    put(0);
+    for (;;) {
+        const int dev_n = dev_a, t_n = t_a;
+        const bool more = member_a < members;
+        if (more) fetch();
+        __syncthreads();                // this tile is written, the other buffer read
+        const bool full = block_kind(q_dev, dev, p.layout) == MASK_FULL;
+        const int off = block_off(q_dev, dev, p.layout);
+        if (full || t0 + 31 >= k0 + 32 * ln.wave + off) {
+            const char* q = lds + parity * BUFFER;
+            const float* st = stats + parity * 3 * TILE;
+            const int lane_first = (full ? 0 : key_own + off) - t0, rows = p.c - t0;
+            const f32x16 x = scores<KS>(q, kf, ln);
+            f32x16 dp = scores<KS>(q + OPERAND, vf, ln), pr;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int i = reg_row(r, h);
+                pr[r] = i >= lane_first && i < rows ? kappa.exp2(x[r], st[i], st[TILE + i]) : 0.f;
+                dp[r] = pr[r] * (dp[r] - st[2 * TILE + i]);
+            }
+            bf16x8x3 w[2];
+            terms_of(w, pr);
+            accumulate<NB>(accv, q + OPERAND, w, ln.tr0, ln.tr1);
+            terms_of(w, dp);
+            accumulate<NB>(acck, q, w, ln.tr0, ln.tr1);
+        }
+        if (!more) break;
+        parity ^= 1;
+        put(parity);
+        q_dev = dev_n;
+        t0 = t_n;
+    }
+    const bool in_shard = key_own < p.c;
+    const uint32_t odd_rows = row_mask(in_shard && (not_finite<NB>(accv) || not_finite<NB>(acck))) |
+                              faint_rows(loudest<NB>(accv), in_shard) | faint_rows(loudest<NB>(acck), in_shard);
+    if (in_shard && !((odd_rows >> n) & 1)) {
+        add_rows<NB>(p.dv + row, accv, 1.f, 0, d, h, p.fresh);
+        add_rows<NB>(p.dk + row, acck, p.scale, 0, d, h, p.fresh);
+    }
+    each_row<1>(odd_rows, 0, [&](const StepArgs& again, int i) { dkdv_row<float>(again, b, kvh, dev_i, k0 + 32 * ln.wave + i, 0, d, ln.lane); });
+}
+template <int DP>
+__global__ void __launch_bounds__(64 * ALONE, 1)
+bwd_f32x3_alone_kernel(StepArgs p, int n_tiles, int n_dkdv) {
+    __shared__ __attribute__((aligned(1024))) char lds[2 * BUFFER];
+    __shared__ float stats[2 * 3 * TILE];          // [buffer][LSE hi | LSE lo | delta][row]
+    if ((int)blockIdx.x < n_dkdv) bwd_dkdv_alone<DP>(p, n_tiles, (int)blockIdx.x, lds, stats);
+    else bwd_dq_alone<DP>(p, n_tiles, (int)blockIdx.x - n_dkdv, lds);
+}
+
 template <int DP, int WAVES>
 hipError_t run_fwd(const StepArgs& a, hipStream_t st) {
     const int rows = 32 * WAVES, n_tiles = (a.c + rows - 1) / rows;
     hipLaunchKernelGGL((fwd_f32x3_kernel<DP, WAVES>), dim3((unsigned)n_tiles * a.n_q * a.B * a.H), dim3(64 * WAVES), 0, st,
                        a, n_tiles);
+    return hipGetLastError();
+}
+template <int DP>
+hipError_t run_alone(const StepArgs& a, hipStream_t st) {
+    const int rows = 32 * ALONE, n_tiles = (a.c + rows - 1) / rows;
+    const int n_dkdv = n_tiles * a.n_kv * a.B * a.H_kv, n_dq = n_tiles * a.n_q * a.B * a.H;
+    hipLaunchKernelGGL((bwd_f32x3_alone_kernel<DP>), dim3((unsigned)(n_dkdv + n_dq)), dim3(64 * ALONE), 0, st, a, n_tiles,
+                       n_dkdv);
     return hipGetLastError();
 }
 template <int DP>
@@ -639,7 +805,8 @@ hipError_t run(const StepArgs& a, bool backward, hipStream_t st) {
 
 }  // namespace
 
-hipError_t launch_f32x3(const StepArgs& a, bool backward, hipStream_t st) {
+hipError_t launch_f32x3(const StepArgs& a, bool backward, bool alone, hipStream_t st) {
+    if (alone) return run_alone<128>(a, st);
     return a.d <= 64 ? run<64>(a, backward, st) : run<128>(a, backward, st);
 }
 

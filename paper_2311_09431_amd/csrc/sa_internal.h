@@ -149,8 +149,12 @@ hipError_t launch_rope(const void* x, void* y, const int32_t* pos, int64_t pos_s
 
 hipError_t launch_fwd_f32(const StepArgs& a, int dtype, hipStream_t st);
 hipError_t launch_bwd_f32(const StepArgs& a, int dtype, hipStream_t st);
-hipError_t launch_f32x3(const StepArgs& a, bool backward, hipStream_t st);
-bool f32x3_split_wanted(const StepArgs& a, bool backward);
+// fp32 storage of up to 128 columns: the fp32 instruction, or three-term products in workgroups of 32 or of 128 rows (ALONE:
+// the backward's with one wavefront to 32 rows)
+enum F32Route : int { F32_INSTRUCTION = 0, F32_SPLIT = 1, F32_TERMS = 2, F32_TERMS_ALONE = 3 };
+F32Route f32_route(const StepArgs& a, bool backward);
+hipError_t launch_f32x3(const StepArgs& a, bool backward, bool alone, hipStream_t st);
+bool f32x3_split_supported(const StepArgs& a, bool backward);
 hipError_t launch_f32x3_split(const StepArgs& a, bool backward, hipStream_t st);
 bool fwd_mfma_supported(const StepArgs& a, int dtype);
 bool fwd_mfma_rope_supported(const StepArgs& a, int dtype);

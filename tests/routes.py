@@ -34,6 +34,13 @@ def _ask(name, a, *more):
     return fn(ctypes.byref(a), *more)
 
 
+def f32(a, backward):
+    """fp32 storage, up to 128 columns: the kind of kernel."""
+    fn = getattr(sa.lib(), "_ZN2sa9f32_routeERKNS_8StepArgsEb")
+    fn.restype, fn.argtypes = ctypes.c_int, [ctypes.c_void_p, ctypes.c_int]
+    return ("fp32 instruction", "split", "128 rows", "128 rows, one wavefront")[fn(ctypes.byref(a), backward)]
+
+
 def forward(a, dtype=sa.BF16):
     if not _ask("fwd_mfma_supported", a, dtype):
         return "short" if _ask("short_exact_wanted", a, dtype, False) else "fp32"

@@ -1,7 +1,7 @@
 """fp32 launches that fill the chip run on the bf16 matrix cores with every operand as three bf16
-terms.  Against the oracle at the edges of their 32-row tiles and 128- / 256-row workgroups, at the
-rule's own line (256 row tiles of 128; 512 for the forward's wide workgroups), with grouped heads
-and with scores that spread over many powers of two; the bounds are the fp32 configuration's."""
+terms, in workgroups of 128 rows (forward of 512 such tiles and more: 256).  Against the oracle at the edges of their
+32-row tiles and workgroups, at the forward's line, with grouped heads and with scores that spread over many powers of
+two; the bounds are the fp32 configuration's."""
 import numpy as np
 import pytest
 import torch
@@ -10,25 +10,34 @@ from oracle import striped_attention as orc
 from paper_2311_09431_amd import binding as sa
 from paper_2311_09431_amd import inputs
 from tests import helpers as hp
+from tests import routes
 
 pytestmark = pytest.mark.gpu
 
 CASES = [
-    # B, H, H_kv, c, d, N, spread of q and k
-    (4, 64, 64, 1, 4, 2, 1.0),          # one row
-    (4, 64, 64, 33, 36, 2, 1.0),        # half a chunk, a tile of one row
-    (4, 32, 8, 129, 64, 2, 1.0),        # last workgroup of one row, grouped heads
-    (2, 32, 32, 260, 100, 2, 1.0),
-    (1, 43, 43, 256, 128, 3, 1.0),      # 258 row tiles: four-wave workgroups
-    (1, 64, 64, 300, 128, 3, 2.0),      # 576: eight
-    (1, 32, 2, 260, 36, 3, 1.0),        # backward of 18 key tiles: streamed rows split (f32_step.hip)
-    (4, 16, 4, 300, 36, 3, 1.0),        # 144: this one's
+    # B, H, H_kv, c, d, N, spread of q and k; the directions these kernels take
+    (1, 96, 96, 17, 4, 1, 1.0, "fb"),           # half a tile
+    (2, 128, 128, 33, 36, 1, 1.0, "fb"),        # half a chunk, a tile of one row
+    (2, 64, 64, 129, 64, 1, 1.0, "fb"),         # last workgroup of one row
+    (4, 32, 8, 129, 64, 2, 1.0, "f"),           # grouped heads
+    (2, 32, 32, 260, 100, 2, 1.0, "fb"),
+    (1, 64, 64, 256, 128, 1, 1.0, "fb"),        # 128 row tiles: four-wave workgroups
+    (1, 64, 64, 300, 128, 3, 2.0, "fb"),        # 576: eight
+    (1, 200, 50, 300, 36, 1, 1.0, "fb"),
+    (4, 64, 64, 1, 4, 2, 1.0, ""),              # (few rows or tiles: other kernels)
+    (4, 64, 64, 33, 36, 2, 1.0, ""),
+    (1, 43, 43, 256, 128, 3, 1.0, "b"),
+    (1, 32, 2, 260, 36, 3, 1.0, ""),
+    (4, 16, 4, 300, 36, 3, 1.0, "f"),
 ]
 
 
 @pytest.mark.parametrize("layout", [sa.CONTIGUOUS, sa.STRIPED])
-@pytest.mark.parametrize("B,H,Hkv,c,d,N,std", CASES)
-def test_edges(layout, B, H, Hkv, c, d, N, std):
+@pytest.mark.parametrize("B,H,Hkv,c,d,N,std,these", CASES)
+def test_edges(layout, B, H, Hkv, c, d, N, std, these):
+    for back in (False, True):
+        if "fb"[back] in these:
+            assert routes.f32(routes.args(c, d, H, Hkv, B=B, layout=layout, N=N), back).startswith("128 rows")
     S, scale = N * c, 1.0 / np.sqrt(d)
     Q = inputs.gaussian((B, H, S, d), c + d, torch.float32, std)
     K = inputs.gaussian((B, Hkv, S, d), c + d + 1, torch.float32, std)

@@ -77,7 +77,7 @@ def test_a_split_fp32_launch_holds_fewer_threads_than_hip_takes(backward):
                                   (8192, 8192, 8, sa.STRIPED), (32767, 1, 1, sa.STRIPED), (1024, 1, 16, sa.CONTIGUOUS)):
             for c in (17, 40, 100, 129, 1000, 2048, 2080, 2112, 4096, 1 << 14, 1 << 17, 1 << 20):
                 a = routes.args(c, d, H, Hkv, layout=layout, N=N)
-                if routes._ask("f32x3_split_wanted", a, backward):
+                if routes.f32(a, backward) == "split":
                     workgroups = (c + 31) // 32 * N * (H + (Hkv if backward else 0))
                     assert workgroups * threads < 1 << 32, (d, H, Hkv, N, c)
                     taken.append(workgroups * threads)
