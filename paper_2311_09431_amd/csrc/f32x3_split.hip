@@ -247,7 +247,7 @@ fwd_f32x3_split_kernel(StepArgs p, int n_tiles) {
     static_assert(PARTIAL_BYTES<DP, WAVES> <= STAGES_BYTES<DP>, "partial results");
     __shared__ __attribute__((aligned(1024))) char lds[STAGES_BYTES<DP> + OWN_BYTES<DP>];
     __shared__ float stats[WAVES * 64];                // [wave][m | l][32]
-    __shared__ uint32_t masks[3 * WAVES];
+    __shared__ __attribute__((aligned(16))) uint32_t masks[4 * WAVES];          // (RowsToRedo)
 
     const RawLane<DP> ln;
     const int n = ln.n, h = ln.h;
@@ -419,12 +419,14 @@ __device__ inline void bwd_dq(const StepArgs& p, int n_tiles, int linear, char* 
     float* const DQ = p.dq + base + (int64_t)a * p.stride_s;
     float4 old[N];
     load_old<DP, WAVES>(old, DQ, d, !p.fresh && a_own < p.c, ln);
+    const RowsToRedo<WAVES> redo = {reinterpret_cast<uint4*>(masks), ln.lane, ln.wave, row_mask(a_own < p.c)};
+    const float top = loudest<blocks_of(DP)>(acc);          // (beside the loads)
+    const bool odd = a_own < p.c && not_finite<blocks_of(DP)>(acc);
     __syncthreads();
     put_partial<DP>(lds, acc, ln);
-    put_odd(masks, a_own < p.c && not_finite<blocks_of(DP)>(acc), ln.wave, ln.lane);
-    put_faint<WAVES>(masks + WAVES, loudest<blocks_of(DP)>(acc), a_own < p.c, ln.wave, ln.lane);
+    redo.put(odd, top, top);
     __syncthreads();
-    const uint32_t odd_rows = take_odd<WAVES>(masks) | take_faint<WAVES>(masks + WAVES);
+    const uint32_t odd_rows = redo.take(top, top);
     if (a_own < p.c && !((odd_rows >> n) & 1)) add_rows<DP, WAVES>(DQ, old, lds, p.scale, d, ln);
     each_row<WAVES>(odd_rows, ln.wave, [&](const StepArgs& again, int i) { dq_row<float>(again, b, hd, dev_i, q0 + i, ln.lane); });
 }
@@ -545,14 +547,15 @@ __device__ inline void bwd_dkdv(const StepArgs& p, int n_tiles, int linear, char
     float4 old_v[N], old_k[N];
     load_old<DP, WAVES>(old_v, p.dv + row, d, !p.fresh && key_own < p.c, ln);
     load_old<DP, WAVES>(old_k, p.dk + row, d, !p.fresh && key_own < p.c, ln);
+    const RowsToRedo<WAVES> redo = {reinterpret_cast<uint4*>(masks), ln.lane, ln.wave, row_mask(key_own < p.c)};
+    const float top_v = loudest<blocks_of(DP)>(accv), top_k = loudest<blocks_of(DP)>(acck);
+    const bool odd = key_own < p.c && (not_finite<blocks_of(DP)>(accv) || not_finite<blocks_of(DP)>(acck));
     __syncthreads();
     put_partial<DP>(lds, accv, ln);
     put_partial<DP>(lds + HALF, acck, ln);
-    put_odd(masks, key_own < p.c && (not_finite<blocks_of(DP)>(accv) || not_finite<blocks_of(DP)>(acck)), ln.wave, ln.lane);
-    put_faint<WAVES>(masks + WAVES, loudest<blocks_of(DP)>(accv), key_own < p.c, ln.wave, ln.lane);
-    put_faint<WAVES>(masks + 3 * WAVES, loudest<blocks_of(DP)>(acck), key_own < p.c, ln.wave, ln.lane);
+    redo.put(odd, top_v, top_k);
     __syncthreads();
-    const uint32_t odd_rows = take_odd<WAVES>(masks) | take_faint<WAVES>(masks + WAVES) | take_faint<WAVES>(masks + 3 * WAVES);
+    const uint32_t odd_rows = redo.take(top_v, top_k);
     if (key_own < p.c && !((odd_rows >> n) & 1)) {
         add_rows<DP, WAVES>(p.dv + row, old_v, lds, 1.f, d, ln);
         add_rows<DP, WAVES>(p.dk + row, old_k, lds + HALF, p.scale, d, ln);
@@ -566,7 +569,7 @@ __global__ void __launch_bounds__(64 * WAVES_OF<DP>, WAVES_OF<DP> / 4)
 bwd_f32x3_split_kernel(StepArgs p, int n_tiles, BothKinds kinds) {
     __shared__ __attribute__((aligned(1024))) char lds[STAGES_BYTES<DP> + 2 * OWN_BYTES<DP>];
     __shared__ __attribute__((aligned(1024))) char stats[WAVES_OF<DP> * STAT_BYTES];
-    __shared__ uint32_t masks[5 * WAVES_OF<DP>];
+    __shared__ __attribute__((aligned(16))) uint32_t masks[4 * WAVES_OF<DP>];          // (RowsToRedo)
     int linear = (int)blockIdx.x;
     if (owns_keys(kinds, linear)) bwd_dkdv<DP>(p, n_tiles, linear, lds, stats, masks);
     else bwd_dq<DP>(p, n_tiles, linear, lds, masks);

@@ -80,19 +80,44 @@ __device__ inline uint32_t take_odd(const uint32_t* masks) {
     for (int w = 0; w < WAVES; ++w) rows |= masks[w];
     return __builtin_amdgcn_readfirstlane(rows);
 }
-// rows that are faint (f32_rows.h) in all wavefronts' partial results; masks: two for each wavefront
+// Rows to do over where operands are three bf16 terms: those that some wavefront names, and those that are faint (f32_rows.h)
+// in all wavefronts' partial results of one sum or of the other.  Each wavefront puts what it says of its 32 rows beside its
+// partial results; behind the barrier a lane takes one wavefront's word and the lanes put them together.  Whether a row that no
+// wavefront finds loud is all zero is asked only then.  (Words that the wavefronts add their bits to: 0.1 us of a small
+// forward launch's 6, 0.3 of a backward one's 7.)
 template <int WAVES>
-__device__ inline void put_faint(uint32_t* masks, float top, bool in_shard, int wave, int lane) {
-    const uint32_t some = row_mask(in_shard && top > 0.f), loud = row_mask(top >= FAINT);
-    if (lane == 0) {
-        masks[wave] = some;
-        masks[WAVES + wave] = loud;
+struct RowsToRedo {
+    uint4* words;               // one for each wavefront
+    int lane, wave;
+    uint32_t in_shard;
+    __device__ inline void put(uint32_t x, uint32_t y, uint32_t z) const {
+        if (lane == 0) words[wave] = make_uint4(x, y, z, 0);
     }
-}
-template <int WAVES>
-__device__ inline uint32_t take_faint(const uint32_t* masks) {
-    return take_odd<WAVES>(masks) & ~take_odd<WAVES>(masks + WAVES);
-}
+    template <int TURN>
+    static __device__ inline uint32_t with_turned(uint32_t x) {         // of 16 lanes, TURN further on
+        return x | (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x120 + TURN, 0xf, 0xf, true);
+    }
+    static __device__ inline uint32_t over_wavefronts(uint32_t x) {
+        static_assert(WAVES == 4 || WAVES == 8, "");
+        x = with_turned<2>(with_turned<1>(x));
+        if (WAVES == 8) x = with_turned<4>(x);
+        return __builtin_amdgcn_readfirstlane(x);
+    }
+    // top0, top1: the largest magnitudes of this wavefront's partial sums
+    __device__ inline void put(bool odd, float top0, float top1) const {
+        put(row_mask(odd), row_mask(top0 >= FAINT), row_mask(top1 >= FAINT));
+    }
+    __device__ inline uint32_t take(float top0, float top1) const {
+        uint4 w = words[lane % WAVES];
+        const uint32_t named = over_wavefronts(w.x), quiet0 = in_shard & ~over_wavefronts(w.y), quiet1 = in_shard & ~over_wavefronts(w.z);
+        if ((quiet0 | quiet1) == 0) return named;           // (as all wavefronts find)
+        __syncthreads();
+        put(0, row_mask(top0 > 0.f), row_mask(top1 > 0.f));
+        __syncthreads();
+        w = words[lane % WAVES];
+        return named | (quiet0 & over_wavefronts(w.y)) | (quiet1 & over_wavefronts(w.z));
+    }
+};
 // The sub-tiles of 32 keys that one wavefront of a query-owning workgroup takes: those of block kv whose
 // number v is `turn` modulo the number of wavefronts, turn being the wavefront's number less the sub-tiles of
 // the blocks before.
@@ -140,7 +165,7 @@ struct KeyCursor {
 
 // Forward, the end: the wavefronts' partial results (accumulators, base-2 reference m, half-wave row sum l) folded
 // into the running state of the lane's row (base: of the workgroup's rows' matrix, a: the row, clamped to the shard).
-// Returns the rows to do over (EXACT only; TERMS: V was three bf16 terms, masks are three for each wavefront).
+// Returns the rows to do over (EXACT only; TERMS: V was three bf16 terms, masks are the words of RowsToRedo).
 template <int DP, int WAVES, bool EXACT, bool TERMS, typename Lane>
 __device__ __forceinline__ uint32_t fold_forward(const StepArgs& p, f32x16 (&acc)[4], float m, float l, char* lds, float* stats,
                                                  uint32_t* masks, const Lane& ln, int dev, int a_own, int a, float* L, float* O) {
@@ -149,6 +174,7 @@ __device__ __forceinline__ uint32_t fold_forward(const StepArgs& p, f32x16 (&acc
     const float old = p.fresh ? -INFINITY : *L;
     float4 o_old[N];
     load_old<DP, WAVES>(o_old, O, d, !p.fresh && a_own < p.c, ln);
+    const float top_acc = TERMS ? loudest<MB>(acc) : 0.f;           // (beside the loads)
     // the wavefronts' partial results against a common reference
     const float l_own = half_wave_sum(l);
     if (h == 0) {
@@ -171,10 +197,12 @@ __device__ __forceinline__ uint32_t fold_forward(const StepArgs& p, f32x16 (&acc
         for (int r = 0; r < 16; ++r) acc[mb][r] *= f;
     put_partial<DP>(lds, acc, ln);
     // a row sum that is no positive number although the row sees a key: see f32_rows.h
-    if (EXACT)
-        put_odd(masks, a_own < p.c && (not_finite<MB>(acc) ||
-                                       (!(l_tot > 0.f && l_tot < INFINITY) && sees_a_key(p, dev, a))), ln.wave, ln.lane);
-    if (TERMS) put_faint<WAVES>(masks + WAVES, loudest<MB>(acc), a_own < p.c, ln.wave, ln.lane);
+    const RowsToRedo<WAVES> redo = {reinterpret_cast<uint4*>(masks), ln.lane, ln.wave, row_mask(a_own < p.c)};
+    if (EXACT) {
+        const bool odd = a_own < p.c && (not_finite<MB>(acc) || (!(l_tot > 0.f && l_tot < INFINITY) && sees_a_key(p, dev, a)));
+        if (TERMS) redo.put(odd, top_acc * f, top_acc * f);
+        else put_odd(masks, odd, ln.wave, ln.lane);
+    }
 
     const float part = l_tot == 0.f ? -INFINITY : fmaf(m_all, LN2_HI, fmaf(m_all, LN2_LO, logf(l_tot)));
     const float top = fmaxf(old, part);
@@ -183,8 +211,7 @@ __device__ __forceinline__ uint32_t fold_forward(const StepArgs& p, f32x16 (&acc
     const float inv = w_sum > 0.f ? 1.f / w_sum : 0.f;
     const float f_old = w_old * inv, f_part = l_tot > 0.f ? w_part * inv / l_tot : 0.f;
     __syncthreads();
-    uint32_t odd_rows = EXACT ? take_odd<WAVES>(masks) : 0;
-    if (TERMS) odd_rows |= take_faint<WAVES>(masks + WAVES);
+    const uint32_t odd_rows = TERMS ? redo.take(top_acc * f, top_acc * f) : EXACT ? take_odd<WAVES>(masks) : 0;
     // no row here, or no key seen: state unchanged
     if (a_own < p.c && !((odd_rows >> n) & 1) && (part != -INFINITY || p.fresh)) {
 #pragma unroll
