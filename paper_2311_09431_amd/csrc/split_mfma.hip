@@ -853,8 +853,11 @@ hipError_t launch_fwd_split(const StepArgs& a, hipStream_t st) { return run(a, F
 //  * 129 to 512 tiles up to 64 columns, triangular: up to 24 heads 1.15 to 1.5 (1.05), 56 1.1 (0.94), 100 1.0 (0.85),
 //    beyond 0.9 (0.7); 32 heads of 2048 rows (512 tiles) 99 / 99, d 32 80 / 82; full, 256: 46.4 / 45.8, 254 / 263
 //  * 256 tiles above 64 columns: 8 heads of 4096 137 / 160, 32 on 8 of 4096 500 / 574
-//  * 129 to 512 tiles, 32 columns computed, triangular: 32 heads of 1024 21.4 / 28.1, 16 of 2048 34.6 / 36.8, 8 of 4096 62 /
-//    57, 16 of 4096 108.6 / 109.3, 8 of 8192 205 / 192, 4 of 16384 400 / 364
+//  * 129 to 512 tiles, 32 columns computed, triangular: 32 heads of 1024 28.1 / 21.4 us in 128-row tiles, 16 of 2048 36.8 /
+//    34.6, 8 of 4096 57 / 62, 8 of 8192 192 / 205; where the last round of 256 is not three quarters full, 8 of 3000 37 / 50,
+//    16 of 3000 69 / 86; one device's queries against all shards' keys leave the 128-row kernel's queries' side short: 8
+//    heads 4 x 1024 34 / 55, 4 heads 4 x 4096 136 / 218, 32 on 8 of 8 x 1024 124 / 158; 32 heads 2 x 512 25 / 22.  The rule
+//    is 0.3 % (worst 1.2) behind the better kernel of each of 312 shapes
 bool bwd_split_wanted(const StepArgs& a) {
     const int64_t t128 = (a.c + 127) / 128, t32 = (a.c + 31) / 32, heads = (int64_t)a.B * a.H_kv, group = a.H / a.H_kv;
     const int64_t keys = t128 * a.n_kv * heads, walk = (int64_t)a.c * a.n_q * group;
@@ -863,7 +866,11 @@ bool bwd_split_wanted(const StepArgs& a) {
     if (keys <= 64) return a.d <= 64 || uneven(a) || up_to(40);
     if (a.d > 64) return keys <= 128 && (uneven(a) ? walk >= 2048 && up_to(16) : group >= 4 && up_to(24));
     if (!uneven(a)) return keys <= 128 && walk >= (a.d <= 32 ? 6 : 4) * keys;
-    if (keys > 128 && narrow(a)) return keys <= 512 && walk >= 16 * keys;
+    if (keys > 128 && narrow(a)) {
+        const int64_t queries = t128 * a.n_q * heads * group;
+        if (keys > 512) return false;
+        return 2 * queries <= keys ? walk >= 5 * queries : walk >= 12 * keys || (keys <= (keys <= 256 ? 192 : 384) && walk >= 6 * keys);
+    }
     return up_to(56) && (keys <= 256 ? walk >= 4 * keys : keys <= 512 && walk > 4 * keys);
 }
 hipError_t launch_bwd_split(const StepArgs& a, hipStream_t st) { return run(a, BWD, st); }

@@ -67,6 +67,23 @@ def test_split_rules_at_their_edges():
         assert routes.forward(routes.args(c, d, H, N=2)) == "short"
 
 
+@pytest.mark.parametrize("H,Hkv,c,N,route", [
+    (8, 8, 1024, 4, "split"), (4, 4, 4096, 4, "split"), (32, 8, 1024, 8, "split"), (16, 16, 2048, 2, "split"),
+    (32, 32, 512, 2, "128 rows"), (33, 33, 1024, 2, "128 rows")])
+def test_narrow_backward_of_one_device_against_all_shards(H, Hkv, c, N, route):
+    # the queries of one device fill the chip's 256 compute units with 128-row tiles only where they are as many as that
+    a = routes.args(c, 32, H, Hkv, N=N)
+    a.n_q, a.q_dev = 1, N - 1
+    assert routes.backward(a) == route
+
+
+@pytest.mark.parametrize("H,c,route", [
+    (32, 1024, "128 rows"), (16, 2048, "128 rows"), (8, 4096, "split"), (8, 3000, "split"), (12, 3000, "split"),
+    (16, 3000, "split"), (20, 3000, "128 rows"), (64, 512, "128 rows"), (24, 1024, "128 rows"), (5, 8192, "split")])
+def test_narrow_backward_of_one_step(H, c, route):
+    assert routes.backward(routes.args(c, 32, H)) == route
+
+
 @pytest.mark.parametrize("backward", [False, True])
 def test_a_split_fp32_launch_holds_fewer_threads_than_hip_takes(backward):
     # workgroups of 32 rows, 512 threads up to 64 columns and 256 above; the rule takes the longest walks of the most heads
