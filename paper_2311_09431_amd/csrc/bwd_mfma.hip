@@ -1044,6 +1044,22 @@ bool bwd_mfma_supported(const StepArgs& a, int dtype) {
            rows * 2 * widest + 2 * a.d < (int64_t(1) << 31);
 }
 
+// Key-owning workgroups by ranks (decode_block).  Above 128 columns up to 1408 tiles; d 192 and 256, triangular step, us,
+// groups : ranks: 24 heads of 4096 529 : 465, 540 : 472, 44 of 4096 856 : 815, 897 : 878, 48 of 4096 849 : 891, 1030 : 1073,
+// 64 of 4096 1134 : 1217, 1186 : 1357.
+// A device's own queries against more shards of keys: every walk is that device's rows, and short ones leave little to
+// balance while an XCD's heads, all at a time, fall out of its L2.  Striped shares, whole backward, groups : ranks: d 128,
+// 32 heads 4 x 1024 195 : 211, 64 of 4 x 1024 346 : 390, d 100, 64 of 4 x 1000 319 : 342, d 256, 32 of 8 x 512 340 : 434, of
+// 2 x 2048 1 : 1.05; but 64 columns, 32 of 2 x 4096 1 : .94, 64 of 2 x 1024 124 : 118, up to three rounds 24 of 4 x 1000 1 :
+// .96, 24 of 2 x 2048 1 : .94, and with 32 columns computed, whose rows are few bytes, all: 64 of 2 x 1024 78 : 70, 32 of 8 x
+// 1024 155 : 150.
+bool dkdv_by_rank(const StepArgs& a) {
+    const int64_t tiles = (int64_t)((a.c + BM - 1) / BM) * a.n_kv * a.B * a.H_kv, walk = (int64_t)a.c * a.n_q * (a.H / a.H_kv);
+    if (!by_rank(uneven(a), tiles, a.d > 128 ? 6 * N_CU - 1 : a.d > 112 ? MOST_BY_RANK<128, false> : MOST_BY_RANK<64, false>)) return false;
+    if (a.n_kv <= a.n_q || a.d <= 32) return true;
+    return walk > (a.d > 128 ? 2048 : 2047) || (walk > 512 && tiles <= (a.d <= 112 && a.n_kv <= 2 * a.n_q ? 4 : 3) * N_CU);
+}
+
 namespace {
 template <int WALK, int DP, bool PART, bool BY_RANK = false>
 void launch_dq(const StepArgs& a, hipStream_t st, int n_tiles) {
@@ -1057,7 +1073,7 @@ template <int WALK, int DP, bool PART, int WAVES, bool BY_RANK = false>
 void launch_dkdv_waves(const StepArgs& a, hipStream_t st, int n_tiles) {
     const dim3 grid((unsigned)n_tiles * a.n_kv * a.B * a.H_kv * halves_of(DP)), block(256);
     if constexpr (WALK != WALK_FULL && DP <= 128 && !BY_RANK)          // (above: bwd_dkdv_wide_kernel)
-        if (by_rank(uneven(a), grid.x, MOST_BY_RANK<DP, false>)) return launch_dkdv_waves<WALK, DP, PART, WAVES, true>(a, st, n_tiles);
+        if (dkdv_by_rank(a)) return launch_dkdv_waves<WALK, DP, PART, WAVES, true>(a, st, n_tiles);
     if (a.c % BM) hipLaunchKernelGGL((bwd_dkdv_mfma_kernel<WALK, true, DP, PART, WAVES, BY_RANK>), grid, block, 0, st, a, n_tiles);
     else hipLaunchKernelGGL((bwd_dkdv_mfma_kernel<WALK, false, DP, PART, WAVES, BY_RANK>), grid, block, 0, st, a, n_tiles);
 }
@@ -1118,9 +1134,7 @@ hipError_t launch_bwd_variant(const StepArgs& a, hipStream_t st) {
         // 320 tiles 285 : 239).
         const int64_t tiles = (int64_t)n_tiles * a.n_kv * a.B * a.H_kv;
         if (tiles > N_CU / 2) {
-            // (by ranks up to 1408 tiles; d 192 and 256, us, groups : ranks: 24 heads of 4096 529 : 465, 540 : 472, 44 of 4096
-            // 856 : 815, 897 : 878, 48 of 4096 849 : 891, 1030 : 1073, 64 of 4096 1134 : 1217, 1186 : 1357)
-            if (by_rank(uneven(a), tiles, 6 * N_CU - 1)) hipLaunchKernelGGL(bwd_dkdv_wide_kernel<true>, dim3((unsigned)tiles), dim3(256), 0, st, a, n_tiles);
+            if (dkdv_by_rank(a)) hipLaunchKernelGGL(bwd_dkdv_wide_kernel<true>, dim3((unsigned)tiles), dim3(256), 0, st, a, n_tiles);
             else hipLaunchKernelGGL(bwd_dkdv_wide_kernel<false>, dim3((unsigned)tiles), dim3(256), 0, st, a, n_tiles);
             return hipGetLastError();
         }

@@ -162,6 +162,7 @@ hipError_t launch_fwd_mfma(const StepArgs& a, hipStream_t st);
 bool bwd_mfma_supported(const StepArgs& a, int dtype);
 hipError_t launch_bwd_mfma(const StepArgs& a, hipStream_t st);
 bool bwd_split_wanted(const StepArgs& a);
+bool dkdv_by_rank(const StepArgs& a);
 hipError_t launch_bwd_split(const StepArgs& a, hipStream_t st);
 bool fwd_split_wanted(const StepArgs& a);
 hipError_t launch_fwd_split(const StepArgs& a, hipStream_t st);

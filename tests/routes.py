@@ -51,3 +51,8 @@ def backward(a, dtype=sa.BF16):
     if not _ask("bwd_mfma_supported", a, dtype):
         return "short" if _ask("short_exact_wanted", a, dtype, True) else "fp32"
     return "split" if _ask("bwd_split_wanted", a) else "128 rows"
+
+
+def keys_by_rank(a):
+    """The key-owning workgroups of a bf16 backward in 128-row tiles, by ranks over all heads."""
+    return _ask("dkdv_by_rank", a)

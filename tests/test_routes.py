@@ -77,6 +77,19 @@ def test_narrow_backward_of_one_device_against_all_shards(H, Hkv, c, N, route):
     assert routes.backward(a) == route
 
 
+@pytest.mark.parametrize("H,Hkv,c,N,d,ranks", [
+    (32, 32, 1024, 4, 128, False), (64, 64, 1024, 4, 100, False), (32, 32, 512, 8, 256, False), (32, 32, 2048, 2, 256, False),
+    (24, 24, 512, 8, 256, False), (16, 16, 4096, 4, 128, True), (32, 32, 4096, 2, 64, True), (24, 24, 1000, 4, 100, True),
+    (64, 64, 1024, 2, 64, True), (64, 64, 1024, 2, 128, False), (32, 32, 1024, 8, 32, True), (32, 32, 1024, 8, 64, False),
+    (32, 8, 4096, 4, 128, True)])
+def test_keys_of_one_device_against_all_shards_by_ranks_only_where_walks_are_long(H, Hkv, c, N, d, ranks):
+    a = routes.args(c, d, H, Hkv, N=N)
+    whole = a.H_kv * N * ((c + 127) // 128)
+    assert routes.keys_by_rank(a) == (512 < whole <= (1535 if d > 128 else 2560))
+    a.n_q, a.q_dev = 1, N - 1
+    assert routes.keys_by_rank(a) == ranks
+
+
 @pytest.mark.parametrize("H,c,route", [
     (32, 1024, "128 rows"), (16, 2048, "128 rows"), (8, 4096, "split"), (8, 3000, "split"), (12, 3000, "split"),
     (16, 3000, "split"), (20, 3000, "128 rows"), (64, 512, "128 rows"), (24, 1024, "128 rows"), (5, 8192, "split")])
