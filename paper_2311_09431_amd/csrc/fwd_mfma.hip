@@ -556,12 +556,20 @@ bool fwd_mfma_supported(const StepArgs& a, int dtype) {
            rows * 2 * a.kv_stride_s + 2 * a.d < (int64_t(1) << 31);
 }
 
+// Query-owning workgroups by ranks (decode_block).  Above 128 columns walks over a striped ring's shards gain up to 1536:
+// 64 heads of 4 x 1024, d 256, us, groups : ranks: 686 : 717, of 4 x 1000 675 : 693.
+bool fwd_by_rank(const StepArgs& a) {
+    const int64_t tiles = (int64_t)((a.c + BM - 1) / BM) * a.n_q * a.B * a.H;
+    const bool ring = a.layout == SA_STRIPED && a.n_kv > 1;
+    return by_rank(uneven(a), tiles, a.d > 128 ? ring ? 6 * N_CU : MOST_BY_RANK<256, true> : a.d > 112 ? MOST_BY_RANK<128, true> : MOST_BY_RANK<64, true>);
+}
+
 namespace {
 bool one_block(const StepArgs& a) { return a.n_q == 1 && a.n_kv == 1 && !a.fresh; }
 template <int WALK, int DP, bool PART, bool BY_RANK = false>
 void launch_fwd_walk(const StepArgs& a, hipStream_t st, dim3 grid, dim3 block, int n_qtiles) {
     if constexpr (WALK != WALK_FULL && !BY_RANK)
-        if (by_rank(uneven(a), grid.x, MOST_BY_RANK<DP, true>)) return launch_fwd_walk<WALK, DP, PART, true>(a, st, grid, block, n_qtiles);
+        if (fwd_by_rank(a)) return launch_fwd_walk<WALK, DP, PART, true>(a, st, grid, block, n_qtiles);
     // Up to 64 columns three workgroups fit a compute unit; uneven work that they would hold all (or
     // nearly all) at once is balanced better by two, so LDS is asked for that keeps the third out: 640
     // workgroups 96 -> 77 us, 768 96 -> 84, 1024 183 -> 173, but 1536 242 -> 260.
@@ -580,7 +588,7 @@ template <int DP>
 void launch_fwd_rope(const StepArgs& a, hipStream_t st, dim3 grid, dim3 block, int n_qtiles) {
     if (block_kind(a.q_dev, a.kv_dev, a.layout) == MASK_FULL)
         hipLaunchKernelGGL((fwd_mfma_kernel<false, WALK_FULL, DP, false, false, true>), grid, block, 0, st, a, n_qtiles);
-    else if (by_rank(uneven(a), grid.x, MOST_BY_RANK<DP, true>))
+    else if (fwd_by_rank(a))
         hipLaunchKernelGGL((fwd_mfma_kernel<false, WALK_TRI, DP, false, true, true>), grid, block, 0, st, a, n_qtiles);
     else
         hipLaunchKernelGGL((fwd_mfma_kernel<false, WALK_TRI, DP, false, false, true>), grid, block, 0, st, a, n_qtiles);

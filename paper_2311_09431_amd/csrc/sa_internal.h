@@ -165,6 +165,7 @@ bool bwd_split_wanted(const StepArgs& a);
 bool dkdv_by_rank(const StepArgs& a);
 hipError_t launch_bwd_split(const StepArgs& a, hipStream_t st);
 bool fwd_split_wanted(const StepArgs& a);
+bool fwd_by_rank(const StepArgs& a);
 hipError_t launch_fwd_split(const StepArgs& a, hipStream_t st);
 bool few_rows_wanted(const StepArgs& a, int dtype, bool backward);
 hipError_t launch_few_rows(const StepArgs& a, int dtype, bool backward, hipStream_t st);

@@ -56,3 +56,8 @@ def backward(a, dtype=sa.BF16):
 def keys_by_rank(a):
     """The key-owning workgroups of a bf16 backward in 128-row tiles, by ranks over all heads."""
     return _ask("dkdv_by_rank", a)
+
+
+def queries_by_rank(a):
+    """The workgroups of a bf16 forward in 128-row tiles, by ranks over all heads."""
+    return _ask("fwd_by_rank", a)

@@ -90,6 +90,13 @@ def test_keys_of_one_device_against_all_shards_by_ranks_only_where_walks_are_lon
     assert routes.keys_by_rank(a) == ranks
 
 
+def test_wide_walks_over_a_striped_ring_go_by_ranks_up_to_six_rounds():
+    ranks = lambda c, d, H, **kw: routes.queries_by_rank(routes.args(c, d, H, **kw))     # noqa: E731
+    assert ranks(1024, 256, 48, N=4) and not ranks(1024, 256, 49, N=4) and not ranks(1000, 136, 64, N=4)
+    assert ranks(1024, 256, 64, N=4, layout=sa.CONTIGUOUS) and ranks(4096, 256, 64) and not ranks(4096, 256, 65)
+    assert ranks(1024, 128, 80, N=4) and not ranks(1024, 128, 81, N=4) and ranks(1024, 112, 96, N=4)
+
+
 @pytest.mark.parametrize("H,c,route", [
     (32, 1024, "128 rows"), (16, 2048, "128 rows"), (8, 4096, "split"), (8, 3000, "split"), (12, 3000, "split"),
     (16, 3000, "split"), (20, 3000, "128 rows"), (64, 512, "128 rows"), (24, 1024, "128 rows"), (5, 8192, "split")])
