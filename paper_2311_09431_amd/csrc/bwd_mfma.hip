@@ -1065,7 +1065,9 @@ template <int WALK, int DP, bool PART, bool BY_RANK = false>
 void launch_dq(const StepArgs& a, hipStream_t st, int n_tiles) {
     const dim3 grid((unsigned)n_tiles * a.n_q * a.B * a.H), block(256);
     if constexpr (WALK != WALK_FULL && !BY_RANK)
-        if (by_rank(uneven(a), grid.x, MOST_BY_RANK<DP, false>)) return launch_dq<WALK, DP, PART, true>(a, st, n_tiles);
+        // (between 64 and 128 columns computed many heads or few tiles lose, us, groups : ranks: d 100, whole backward, 336 heads of
+        // 384 153 : 162, 256 of 2 x 512 409 : 422, 512 of 768 627 : 648)
+        if (by_rank(uneven(a), grid.x, MOST_BY_RANK<DP, false>) && (DP != 112 || (a.B * a.H <= 192 && n_tiles * a.n_q >= 4))) return launch_dq<WALK, DP, PART, true>(a, st, n_tiles);
     if (a.c % BM) hipLaunchKernelGGL((bwd_dq_mfma_kernel<true, WALK, DP, PART, BY_RANK>), grid, block, 0, st, a, n_tiles);
     else hipLaunchKernelGGL((bwd_dq_mfma_kernel<false, WALK, DP, PART, BY_RANK>), grid, block, 0, st, a, n_tiles);
 }

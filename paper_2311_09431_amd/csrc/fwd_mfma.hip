@@ -556,12 +556,18 @@ bool fwd_mfma_supported(const StepArgs& a, int dtype) {
            rows * 2 * a.kv_stride_s + 2 * a.d < (int64_t(1) << 31);
 }
 
-// Query-owning workgroups by ranks (decode_block).  Above 128 columns walks over a striped ring's shards gain up to 1536:
-// 64 heads of 4 x 1024, d 256, us, groups : ranks: 686 : 717, of 4 x 1000 675 : 693.
+// Query-owning workgroups by ranks (decode_block), us, groups : ranks.  Above 128 columns walks over a striped ring's shards
+// gain up to 1536: 64 heads of 4 x 1024, d 256, 686 : 717, of 4 x 1000 675 : 693.  Many heads of few tiles have their groups'
+// tails short already and too much K and V in flight for the L2: triangular steps, d 64, 512 heads of 384 rows 33.1 : 36.6,
+// 512 of 640 61.6 : 69.7, 256 of 512 30.2 : 30.4, 256 of 768 45.3 : 44.0; d 128, 384 of 256 34.8 : 39.7, 256 of 1024 135 : 152,
+// 256 of 512 49.6 : 50.0, 160 of 1024 .97; d 100, 848 of 384 113 : 146, 320 of 1024 153 : 180, 192 of 1024 86.6 : 84.1; d 256,
+// 680 of 384 259 : 286, 256 of 384 81 : 88, 256 of 512 145 : 138.  32 columns computed: 1280 of 256 30.0 : 32.1, 512 of 256 .94.
 bool fwd_by_rank(const StepArgs& a) {
-    const int64_t tiles = (int64_t)((a.c + BM - 1) / BM) * a.n_q * a.B * a.H;
+    const int64_t ranks = (int64_t)((a.c + BM - 1) / BM) * a.n_q, heads = (int64_t)a.B * a.H;
     const bool ring = a.layout == SA_STRIPED && a.n_kv > 1;
-    return by_rank(uneven(a), tiles, a.d > 128 ? ring ? 6 * N_CU : MOST_BY_RANK<256, true> : a.d > 112 ? MOST_BY_RANK<128, true> : MOST_BY_RANK<64, true>);
+    if (!by_rank(uneven(a), ranks * heads, a.d > 128 ? ring ? 6 * N_CU : MOST_BY_RANK<256, true> : a.d > 112 ? MOST_BY_RANK<128, true> : MOST_BY_RANK<64, true>)) return false;
+    if (a.d <= 32 && a.d % 8 == 0) return heads <= 768;
+    return ranks >= 4 && heads <= (a.d <= 64 ? 256 : a.d <= 128 ? 192 : 512);
 }
 
 namespace {

@@ -97,6 +97,15 @@ def test_wide_walks_over_a_striped_ring_go_by_ranks_up_to_six_rounds():
     assert ranks(1024, 128, 80, N=4) and not ranks(1024, 128, 81, N=4) and ranks(1024, 112, 96, N=4)
 
 
+@pytest.mark.parametrize("d,few,most", [(64, 3, 256), (100, 3, 192), (128, 3, 192), (256, 3, 512), (32, 1, 768), (28, 3, 256)])
+def test_many_heads_of_few_tiles_stay_in_groups(d, few, most):
+    ranks = lambda tiles, H: routes.queries_by_rank(routes.args(128 * tiles, d, H))     # noqa: E731
+    assert ranks(few + 1, min(160, most) if few > 1 else 600)
+    assert few == 1 or not ranks(few, 192)
+    tiles = 4 if few > 1 else 2
+    assert ranks(tiles, most) and not ranks(tiles, most + 1)
+
+
 @pytest.mark.parametrize("H,c,route", [
     (32, 1024, "128 rows"), (16, 2048, "128 rows"), (8, 4096, "split"), (8, 3000, "split"), (12, 3000, "split"),
     (16, 3000, "split"), (20, 3000, "128 rows"), (64, 512, "128 rows"), (24, 1024, "128 rows"), (5, 8192, "split")])
