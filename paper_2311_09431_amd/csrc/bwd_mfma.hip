@@ -1046,7 +1046,8 @@ bool bwd_mfma_supported(const StepArgs& a, int dtype) {
 
 // Key-owning workgroups by ranks (decode_block).  Above 128 columns up to 1408 tiles; d 192 and 256, triangular step, us,
 // groups : ranks: 24 heads of 4096 529 : 465, 540 : 472, 44 of 4096 856 : 815, 897 : 878, 48 of 4096 849 : 891, 1030 : 1073,
-// 64 of 4096 1134 : 1217, 1186 : 1357.
+// 64 of 4096 1134 : 1217, 1186 : 1357; heads of few tiles a round or two more, whole backward, 384 of 512 624 : 592, 512 of 512
+// 872 : 851, 192 of 1024 .98.
 // A device's own queries against more shards of keys: every walk is that device's rows, and short ones leave little to
 // balance while an XCD's heads, all at a time, fall out of its L2.  Striped shares, whole backward, groups : ranks: d 128,
 // 32 heads 4 x 1024 195 : 211, 64 of 4 x 1024 346 : 390, d 100, 64 of 4 x 1000 319 : 342, d 256, 32 of 8 x 512 340 : 434, of
@@ -1054,8 +1055,8 @@ bool bwd_mfma_supported(const StepArgs& a, int dtype) {
 // .96, 24 of 2 x 2048 1 : .94, and with 32 columns computed, whose rows are few bytes, all: 64 of 2 x 1024 78 : 70, 32 of 8 x
 // 1024 155 : 150.
 bool dkdv_by_rank(const StepArgs& a) {
-    const int64_t tiles = (int64_t)((a.c + BM - 1) / BM) * a.n_kv * a.B * a.H_kv, walk = (int64_t)a.c * a.n_q * (a.H / a.H_kv);
-    if (!by_rank(uneven(a), tiles, a.d > 128 ? 6 * N_CU - 1 : a.d > 112 ? MOST_BY_RANK<128, false> : MOST_BY_RANK<64, false>)) return false;
+    const int64_t ranks = (int64_t)((a.c + BM - 1) / BM) * a.n_kv, tiles = ranks * a.B * a.H_kv, walk = (int64_t)a.c * a.n_q * (a.H / a.H_kv);
+    if (!by_rank(uneven(a), tiles, a.d > 128 ? (ranks <= 4 ? 8 * N_CU : ranks <= 8 ? 6 * N_CU : 6 * N_CU - 1) : a.d > 112 ? MOST_BY_RANK<128, false> : MOST_BY_RANK<64, false>)) return false;
     if (a.n_kv <= a.n_q || a.d <= 32) return true;
     return walk > (a.d > 128 ? 2048 : 2047) || (walk > 512 && tiles <= (a.d <= 112 && a.n_kv <= 2 * a.n_q ? 4 : 3) * N_CU);
 }

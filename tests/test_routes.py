@@ -106,6 +106,11 @@ def test_many_heads_of_few_tiles_stay_in_groups(d, few, most):
     assert ranks(tiles, most) and not ranks(tiles, most + 1)
 
 
+def test_wide_keys_go_by_ranks_further_where_heads_have_few_tiles():
+    ranks = lambda tiles, H: routes.keys_by_rank(routes.args(128 * tiles, 256, H))     # noqa: E731
+    assert ranks(4, 512) and not ranks(4, 513) and ranks(8, 192) and not ranks(8, 193) and ranks(9, 170) and not ranks(16, 96)
+
+
 @pytest.mark.parametrize("H,c,route", [
     (32, 1024, "128 rows"), (16, 2048, "128 rows"), (8, 4096, "split"), (8, 3000, "split"), (12, 3000, "split"),
     (16, 3000, "split"), (20, 3000, "128 rows"), (64, 512, "128 rows"), (24, 1024, "128 rows"), (5, 8192, "split")])
