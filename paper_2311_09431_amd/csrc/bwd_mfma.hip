@@ -1,5 +1,5 @@
 // Backward ring step on the CDNA4 matrix cores (bf16 operands, fp32 accumulate),
-// head dimension up to 256 (64, 112, 128 or 256 columns computed).  The paper describes no
+// head dimension up to 256 (32, 64, 112, 128 or 256 columns computed).  The paper describes no
 // backward pass; this is the analytic gradient of causal attention (Sec. 2.1) restricted to the pairs that
 // GetMask(j, k) allows, with P recomputed from the saved log-sum-exp:
 //   P = exp(scale q.k - LSE),  dV += P^T dO,  dP = dO V^T,
@@ -52,7 +52,7 @@ __device__ inline bf16x8 pack8(const f32x16& x, int first) {
 // visible, one releases the tile just finished for the next request.
 
 // DP: columns computed.  64 for head dimensions up to 64 (k-steps 4..7 of the S and dP
-// products and column blocks 2, 3 of the dQ product do not exist then), 112 for those up to 112
+// products and column blocks 2, 3 of the dQ product do not exist then), half of that up to 32 that are a multiple of 8, 112 for those up to 112
 // (no k-step 7), 128, or 256 for head dimensions above 128: the K and V tiles then come as two 128-column halves, tile_bytes(DP) apart in
 // LDS, and every slice holds one MFMA of each product per half.  PART: d % 8 == 4, the K and V
 // fragments that hold column d are cleared beyond it (part_ks = the k-step, or -1 for the lanes

@@ -1,5 +1,5 @@
 // Forward ring step on the CDNA4 matrix cores (bf16 operands, fp32 accumulate),
-// head dimension up to 256 (64, 112, 128 or 256 columns computed): AccumulateAttentionFragment
+// head dimension up to 256 (32, 64, 112, 128 or 256 columns computed): AccumulateAttentionFragment
 // of Algorithm 1 with the fused log-sum-exp merge, skipping every 32-key sub-tile
 // that GetMask(j, k) masks entirely for a 32-query wavefront (Sec. 2.2.1); a coarser
 // skipping granularity (Sec. 3.1) can be emulated on request.
@@ -107,7 +107,7 @@ __device__ inline bf16x8 lds_read_tr(const char* lds, uint32_t addr, uint32_t ad
 // MASK applies the element mask to s_cur: register r (key 8 (r/4) + 4h + r%4 of the
 // sub-tile) is allowed iff 8 (r/4) + r%4 <= mask_lim (mask_lim already holds -4h).
 // DP: columns computed.  64 for head dimensions up to 64 (k-steps 4..7 of the first product
-// and column blocks 2, 3 of the second do not exist then), 112 for those up to 112 (no k-step
+// and column blocks 2, 3 of the second do not exist then), half of that up to 32 that are a multiple of 8, 112 for those up to 112 (no k-step
 // 7), 128, or 256 for head dimensions above 128: the K and V tiles then come as two 128-column
 // halves, TILE_BYTES apart in LDS, and every slice holds one MFMA of each product per half.  PART: d % 8 == 4, the K fragment that holds
 // column d is cleared beyond it (part_ks = its k-step, or -1 for the lanes of the other

@@ -249,8 +249,8 @@ __device__ inline f32x16 mfma(bf16x8 a, bf16x8 b, f32x16 c) {
 // wait states (NOPs)": XDL (matrix core) write of a VGPR followed by a VALU read or write of
 // it needs passes + 3 wait states: 11 for this 8-pass instruction (19 for a 16-pass one).
 //  * In the loops the distance is structural: the last S / dP MFMA of a pipeline step is
-//    followed by that step's dV / dK products, 4 * MB >= 8 further MFMAs of 8 passes each
-//    (>= 256 cycles of the same in-order pipeline), before the next step's first VALU read.
+//    followed by that step's dV / dK products, 4 * MB >= 4 further MFMAs of 8 passes each
+//    (>= 128 cycles of the same in-order pipeline), before the next step's first VALU read.
 //  * In the prologue nothing lies between: mfma_results_to_valu() inserts 32 wait states and
 //    ties the two tiles to the asm statement, so no read of them can be scheduled before it.
 __device__ inline void mfma_results_to_valu(f32x16& a) { asm volatile("s_nop 15" : "+v"(a)); }
@@ -277,7 +277,7 @@ __device__ __forceinline__ void mfma_vgpr_acc(f32x16& acc, bf16x8 a, bf16x8 b, b
 // stream all of them: d 64, triangular, 25 heads of 2048 rows 125 -> 75 us, 15 of 4096 260 -> 145, 7 of 8192 360 ->
 // 242, 128 on 32 of 2048 343 -> 315.  Small launches of uneven work with few ranks, where a chunk is a large part of
 // the order, and ranks behind the last whole chunk stay head by head (9 heads of 500 rows, d 100, in chunks 15.3 ->
-// 16.1).  (Backward only: the forward gained as often as it lost, full blocks, d 128, 15 heads of 1024 28.0 -> 21.7, 3
+// 16.1).  (Of the 32-row workgroups the backward's only: the forward gained as often as it lost, full blocks, d 128, 15 heads of 1024 28.0 -> 21.7, 3
 // of 5000 60.8 -> 63.7.)
 __device__ inline void decode_near(int linear, int n_ranks, int n_heads, bool uneven, int& rank, int& head) {
     const int chunk = n_heads % 8 == 0 ? 1 : n_heads % 4 == 0 ? 2 : n_heads % 2 == 0 ? 4 : 8, size = chunk * n_heads;

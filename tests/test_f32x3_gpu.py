@@ -71,6 +71,7 @@ def test_a_score_of_minus_infinity_is_no_key():
     # an infinite key element makes scores of +-inf; where the row's query keeps them at -inf the key
     # drops out, as with the fp32 instruction
     B, H, c, d = 4, 64, 40, 32
+    assert routes.f32(routes.args(c, d, H, B=B), False) == "128 rows"
     Q, K, V = (inputs.gaussian((B, H, c, d), 5 + i).cuda() for i in range(3))
     Q[..., 0] = Q[..., 0].abs() + 0.1
     K[:, :, 7, 0] = -float("inf")

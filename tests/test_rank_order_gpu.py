@@ -19,7 +19,7 @@ def test_every_head_is_the_first(H, c, d):
     tiles = (c + 127) // 128
     assert 512 < tiles * H <= 3072
     a = routes.args(c, d, H)
-    assert routes.forward(a) == routes.backward(a) == "128 rows"
+    assert routes.forward(a) == routes.backward(a) == "128 rows" and routes.queries_by_rank(a) and routes.keys_by_rank(a)
     one = inputs.qkv(1, 1, c, d, c, torch.bfloat16, with_dout=True)
     q, k, v, g = (x.cuda().expand(1, H, c, d).contiguous() for x in one)
     o, lse = torch.empty(1, H, c, d, device="cuda"), torch.empty(1, H, c, device="cuda")
