@@ -61,11 +61,13 @@ __device__ inline bool not_finite(const Acc& acc) {
     return (z[0] + z[1]) + (z[2] + z[3]) != 0.f;
 }
 // The largest magnitude in the first NB accumulators (NaN passed over).  Three bf16 terms cover a number down to 2^-109;
-// below, the last one is subnormal and up to 2^-134 is lost of it.  So where operands are such terms, a row whose results
-// are all below FAINT, and not all zero, is done over here too; from FAINT on what is lost is below fp32's own
-// rounding, 2^-24 of the result, for weights and elements whose squares sum to less than 2^10 over the row.  dO, V, K or Q
-// scaled by 2^-100 to 2^-120, heads of 257 to 512 rows, the worst output's error against 64 bits: terms alone 4.6e-4, the
-// fp32 instruction 5.0e-7, done over 3.2e-7.  (Where every product has a factor below 2^-134, the result is
+// below, the last one is subnormal and up to 2^-134 is lost of it.  So where operands are such terms and the results of all 32
+// rows of a tile are below FAINT, those that are not all zero are done over here too; from FAINT on what is lost is below
+// fp32's own rounding, 2^-24 of the tile's largest row, for weights and elements whose squares sum to less than 2^10 over
+// the row.  (Faint rows beside a louder one are what peaked scores leave: keys whose every probability is that small, and
+// no operand.  Done over, each by itself, they cost 8 heads of 2048 rows, d 64, scores of standard deviation 300, 1.64 ms
+// backward instead of 0.12, of 50 0.49.)  dO, V, K or Q scaled by 2^-100 to 2^-120, heads of 257 to 512 rows, the worst
+// output's error against 64 bits: terms alone 4.6e-4, the fp32 instruction 5.0e-7, done over 3.2e-7.  (Where every product has a factor below 2^-134, the result is
 // zero: it is below fp32's normal numbers but for factors beyond 2^8.)
 constexpr float FAINT = 0x1p-105f;
 template <int NB, typename Acc>
@@ -82,9 +84,9 @@ __device__ inline uint32_t row_mask(bool lane_says) {
     const uint64_t m = __builtin_amdgcn_ballot_w64(lane_says);
     return (uint32_t)m | (uint32_t)(m >> 32);
 }
-// the faint ones of the rows that lie in the shard
+// the rows in the shard that are not all zero, if all are faint
 __device__ inline uint32_t faint_rows(float top, bool in_shard) {
-    return row_mask(in_shard && top > 0.f) & ~row_mask(top >= FAINT);
+    return row_mask(top >= FAINT) ? 0 : row_mask(in_shard && top > 0.f);
 }
 
 // The rows set in a mask, taken in turn by the SPLIT wavefronts that own them: row(arguments, n).  The

@@ -355,7 +355,7 @@ struct Exchange {
     }
 };
 constexpr int EXCHANGED = 2 * GROUPS * 4096;
-// rows that either wavefront of a pair names, and those that are faint in what both hold of them
+// rows that either wavefront of a pair names, and, if all are faint in what both hold of them, those with something
 __device__ inline uint32_t odd_of_pair(uint32_t* masks, uint32_t odd, uint32_t some, uint32_t loud, int wave, int lane) {
     if (lane == 0) {
         masks[wave] = odd;
@@ -365,7 +365,7 @@ __device__ inline uint32_t odd_of_pair(uint32_t* masks, uint32_t odd, uint32_t s
     __syncthreads();
     const uint32_t* const own = masks + wave % GROUPS;
     auto either = [&](int i) { return own[2 * GROUPS * i] | own[2 * GROUPS * i + GROUPS]; };
-    return __builtin_amdgcn_readfirstlane(either(0) | (either(1) & ~either(2)));
+    return __builtin_amdgcn_readfirstlane(either(0) | (either(2) ? 0 : either(1)));
 }
 
 // dQ.  The pair's wavefronts take half of its columns each.

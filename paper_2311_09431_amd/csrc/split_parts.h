@@ -80,11 +80,11 @@ __device__ inline uint32_t take_odd(const uint32_t* masks) {
     for (int w = 0; w < WAVES; ++w) rows |= masks[w];
     return __builtin_amdgcn_readfirstlane(rows);
 }
-// Rows to do over where operands are three bf16 terms: those that some wavefront names, and those that are faint (f32_rows.h)
-// in all wavefronts' partial results of one sum or of the other.  Each wavefront puts what it says of its 32 rows beside its
-// partial results; behind the barrier a lane takes one wavefront's word and the lanes put them together.  Whether a row that no
-// wavefront finds loud is all zero is asked only then.  (Words that the wavefronts add their bits to: 0.1 us of a small
-// forward launch's 6, 0.3 of a backward one's 7.)
+// Rows to do over where operands are three bf16 terms: those that some wavefront names, and all with something in them if
+// all are faint (f32_rows.h) in all wavefronts' partial results of one sum or of the other.  Each wavefront puts what it says
+// of its 32 rows beside its partial results; behind the barrier a lane takes one wavefront's word and the lanes put them
+// together.  Whether rows are all zero is asked only where no wavefront finds one loud.  (Words that the wavefronts add
+// their bits to: 0.1 us of a small forward launch's 6, 0.3 of a backward one's 7.)
 template <int WAVES>
 struct RowsToRedo {
     uint4* words;               // one for each wavefront
@@ -109,13 +109,13 @@ struct RowsToRedo {
     }
     __device__ inline uint32_t take(float top0, float top1) const {
         uint4 w = words[lane % WAVES];
-        const uint32_t named = over_wavefronts(w.x), quiet0 = in_shard & ~over_wavefronts(w.y), quiet1 = in_shard & ~over_wavefronts(w.z);
-        if ((quiet0 | quiet1) == 0) return named;           // (as all wavefronts find)
+        const uint32_t named = over_wavefronts(w.x), loud0 = over_wavefronts(w.y), loud1 = over_wavefronts(w.z);
+        if (loud0 && loud1) return named;            // (as all wavefronts find)
         __syncthreads();
         put(0, row_mask(top0 > 0.f), row_mask(top1 > 0.f));
         __syncthreads();
         w = words[lane % WAVES];
-        return named | (quiet0 & over_wavefronts(w.y)) | (quiet1 & over_wavefronts(w.z));
+        return named | (in_shard & ((loud0 ? 0 : over_wavefronts(w.y)) | (loud1 ? 0 : over_wavefronts(w.z))));
     }
 };
 // The sub-tiles of 32 keys that one wavefront of a query-owning workgroup takes: those of block kv whose

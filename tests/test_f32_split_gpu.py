@@ -92,3 +92,32 @@ def test_small_magnitudes(H, c, d, split, small):
         for name, got, want in (("O", o, p @ v), ("dQ", grads[0], ds @ k), ("dK", grads[1], t(ds) @ q), ("dV", grads[2], t(p) @ g)):
             error = float((got.double() - want).norm() / want.norm())
             assert error <= 1e-6, (name, exponent, error)
+
+
+@pytest.mark.parametrize("H,c,d,split", [(8, 2048, 64, True), (64, 2048, 128, False)])
+def test_peaked_scores_take_no_longer(H, c, d, split):
+    # scores of standard deviation 300 leave single keys whose every probability is below 2^-105 beside others: they are not
+    # rows too small for their terms (each done over by itself: 13 times the launch's time)
+    assert routes.f32(routes.args(c, d, H, q_dev=0), True) == ("split" if split else "128 rows")
+    times = []
+    for spread in (1, 300):
+        q, k, v, g = (inputs.gaussian((1, H, c, d), 30 + i, device="cuda") for i in range(4))
+        q *= spread
+        o, lse, delta = torch.empty_like(q), torch.empty(1, H, c, device="cuda"), torch.empty(1, H, c, device="cuda")
+        grads = [torch.empty_like(q) for _ in range(3)]
+        shape = sa.shard_shape(q, c, lse)
+        sa.sa_ring_fwd(q, k, v, o, lse, 1, sa.STRIPED, shape)
+        call = lambda: sa.sa_ring_bwd(q, k, v, g, o, lse, delta, *grads, 1, sa.STRIPED, shape)      # noqa: E731
+        call()
+        taken = []
+        for _ in range(5):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            for _ in range(4):
+                call()
+            end.record()
+            torch.cuda.synchronize()
+            taken.append(start.elapsed_time(end))
+        times.append(min(taken))
+        faint = [int(((x.abs().amax(-1) < 2.0 ** -105) & (x != 0).any(-1)).sum()) for x in grads[1:]]
+    assert all(faint) and times[1] <= 2 * times[0], (faint, times)
