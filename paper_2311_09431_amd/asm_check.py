@@ -14,14 +14,15 @@ import re
 from functools import cached_property
 
 RESULT_WAIT, OPERAND_WAIT, PASSES = 11, 2, 8
-_REG = re.compile(r"\b([va])(?:\[(\d+):(\d+)\]|(\d+))(?![\w.])")
+_NUMBER = r"(0x[0-9a-f]+|\d+)"         # (constants of asm statements above 64 are printed in hex)
+_REG = re.compile(r"\b([va])(?:\[%s:%s\]|\[%s\]|(\d+))(?![\w.])" % (_NUMBER, _NUMBER, _NUMBER))
 _OPERAND_END = re.compile(r",(?![^\[]*\])")
 
 
 def registers(text):
     out = set()
-    for kind, lo, hi, one in _REG.findall(text):
-        out.update((kind, i) for i in (range(int(lo), int(hi) + 1) if lo else (int(one),)))
+    for kind, lo, hi, boxed, one in _REG.findall(text):
+        out.update((kind, i) for i in (range(int(lo, 0), int(hi, 0) + 1) if lo else (int(boxed or one, 0),)))
     return out
 
 

@@ -20,7 +20,7 @@ LIB = os.path.join(HERE, "libstriped_attn.so")
 OBJ_DIR = os.path.join(ROOT, "_build")
 
 SOURCES = ["api.hip", "permute.hip", "elementwise.hip", "f32_step.hip", "fwd_mfma.hip",
-           "bwd_mfma.hip", "split_mfma.hip", "f32x3_step.hip", "f32x3_split.hip", "f32_route.hip",
+           "bwd_mfma.hip", "bwd_ring.hip", "split_mfma.hip", "f32x3_step.hip", "f32x3_split.hip", "f32_route.hip",
            "rows_step.hip"]
 
 # Flags of single sources.  f32x3_step: score tiles are read by vector instructions right after
@@ -31,7 +31,7 @@ SOURCE_FLAGS = {"f32x3_step.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
 
 # Sources with matrix instructions in asm statements, and their kernels whose accumulators are registers by
 # number: the assembly of these is looked over (asm_check.py).
-ASM_CHECKED = {"bwd_mfma.hip": ["bwd_dkdv_wide_kernel"], "split_mfma.hip": []}
+ASM_CHECKED = {"bwd_mfma.hip": ["bwd_dkdv_wide_kernel"], "bwd_ring.hip": ["bwd_dkdv_ring_kernel", "bwd_both_ring_kernel"], "split_mfma.hip": []}
 
 # packed fp32 VALU forms are switched off on purpose for the test machines
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-fno-gpu-rdc",

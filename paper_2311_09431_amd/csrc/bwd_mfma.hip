@@ -5,7 +5,7 @@
 //   P = exp(scale q.k - LSE),  dV += P^T dO,  dP = dO V^T,
 //   dS = P * (dP - delta),     dQ += scale dS K,  dK += scale dS^T Q.
 // Two deterministic kernels, no atomics: every output row is read-modify-written
-// by exactly one wavefront.
+// by exactly one wavefront.  (dK and dV at 65 to 128 columns, and dQ there where it shares their launch: bwd_ring.hip.)
 //
 //  * dq kernel: a workgroup owns 128 query rows (Q and dO stay in registers as
 //    B operands), key tiles stream through LDS.  S^T = K Q^T and dP^T = V dO^T
@@ -23,6 +23,7 @@
 
 #include <type_traits>
 
+#include "acc_file.h"
 #include "mfma_tiles.h"
 #include "sa_internal.h"
 
@@ -717,37 +718,6 @@ constexpr int WIDE_V_REGS = 1;                                     // of 16 k-st
 constexpr int WIDE_V_LDS = (16 - WIDE_V_REGS) * 1024;              // per wavefront
 constexpr int WIDE_NO_MASK = -(1 << 20);
 
-// The accumulators are the accumulation registers themselves, by number: dV^T block b is a[16 b : 16 b + 15],
-// dK^T block b 128 further on.  As variables of the compiler, tied to that file or not, they were carried
-// to vector registers and scratch memory and back around every loop (444 spilled registers).  Each
-// statement declares the whole file as overwritten, so that nothing of the compiler's lives there
-// across one; it has no reason to use the file at all while its own values fit the 256 vector
-// registers.  The build looks that outside of these statements no instruction names one, and for the wait states
-// of all products in asm statements (asm_check.py).
-#ifdef __HIP_DEVICE_COMPILE__
-#define ACC_TEN(b) "a" #b "0", "a" #b "1", "a" #b "2", "a" #b "3", "a" #b "4", "a" #b "5", "a" #b "6", "a" #b "7", "a" #b "8", "a" #b "9"
-#define ACC_FILE                                                                                                   \
-    "a0", "a1", "a2", "a3", "a4", "a5", "a6", "a7", "a8", "a9", ACC_TEN(1), ACC_TEN(2), ACC_TEN(3), ACC_TEN(4), ACC_TEN(5),    \
-        ACC_TEN(6), ACC_TEN(7), ACC_TEN(8), ACC_TEN(9), ACC_TEN(10), ACC_TEN(11), ACC_TEN(12), ACC_TEN(13), ACC_TEN(14), ACC_TEN(15), \
-        ACC_TEN(16), ACC_TEN(17), ACC_TEN(18), ACC_TEN(19), ACC_TEN(20), ACC_TEN(21), ACC_TEN(22), ACC_TEN(23), ACC_TEN(24),        \
-        "a250", "a251", "a252", "a253", "a254", "a255"
-#else
-#define ACC_FILE        // the host pass knows none of these names
-#endif
-__device__ __forceinline__ void acc_zero(int i) { asm volatile("v_accvgpr_write_b32 a[%0], 0" : : "n"(i) : ACC_FILE); }
-__device__ __forceinline__ float acc_read(int i) {
-    float x;
-    asm volatile("v_accvgpr_read_b32 %0, a[%1]" : "=v"(x) : "n"(i) : ACC_FILE);
-    return x;
-}
-// block += a b.  The two wait states stand in every one: b is packed by vector instructions, which the
-// compiler moves up to the very product that reads it, and its hazard recogniser does not see this one
-// (without them single columns of dK were wrong now and then).  They pass while the product before runs.
-__device__ __forceinline__ void acc_mfma(int block, bf16x8 a, bf16x8 b) {
-    asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 a[%2:%3], %0, %1, a[%2:%3]"
-                 : : "v"(a), "v"(b), "n"(16 * block), "n"(16 * block + 15) : ACC_FILE);
-}
-
 // products of one step, as dkdv_step.  arow: row reads in the next stage, tr0 / tr1: transposing reads
 // in the present one.
 template <bool NEXT>
@@ -963,7 +933,7 @@ bwd_dkdv_wide_kernel(StepArgs p, int n_tiles) {
     wide_step<false>(s_b, dp_b, s_a, dp_a, kf, vf, v_own, kappa, lds, arow, tr0, tr1,
                      stat + stage * 2 * WIDE_ROWS, stat, h, lim_cur + n - 4 * h);
 
-    asm volatile("s_nop 15\n\ts_nop 15" : : : ACC_FILE);      // the last products before they are read
+    acc_settle();
     if (key_own >= p.c) return;
     float* DK = p.dk + kv_base + (int64_t)key * ss;
     float* DV = p.dv + kv_base + (int64_t)key * ss;
@@ -1013,7 +983,7 @@ bwd_dkdv_mfma_kernel(StepArgs p, int n_tiles) {
 // Both kinds of workgroups in one launch (each sequence heaviest first; above 512 of a kind by groups of
 // heads, see decode_block): where the key-owning ones do not fill the chip, or fill it once and last
 // as long as the heaviest, the query-owning ones run beside and behind them instead of after.
-// One workgroup per compute unit (the key-owning side's registers).
+// One workgroup per compute unit (the key-owning side's registers).  Up to 64 columns and above 128.
 template <bool RAGGED, int DP, bool PART>
 __global__ void __launch_bounds__(256, 1)
 bwd_both_mfma_kernel(StepArgs p, int n_tiles, BothKinds kinds) {
@@ -1094,35 +1064,50 @@ void launch_dkdv(const StepArgs& a, hipStream_t st, int n_tiles) {
     launch_dkdv_waves<WALK, DP, PART, 1>(a, st, n_tiles);
 }
 template <int DP, bool PART>
-void launch_both(const StepArgs& a, hipStream_t st, int n_tiles) {
+hipError_t launch_both(const StepArgs& a, hipStream_t st, int n_tiles) {
     const int n_dkdv = n_tiles * a.n_kv * a.B * a.H_kv * halves_of(DP), n_dq = n_tiles * a.n_q * a.B * a.H;
     // (a group's long key walks all at once are no gain: 32 heads on 8 of 4096 rows 486 us, first 501)
     // (numbers that are no multiple of 8 one by one: 11 heads of 1600 rows, d 136, 92 us, in units of 8 97, 152 heads on 19 of
     // 1445, d 128, 419 / 448; those that are: see both_kinds)
     const int unit = n_dkdv % 8 || n_dq % 8 ? 1 : 8;
     const BothKinds kinds = both_kinds(a, n_dkdv, n_dq, a.H == a.H_kv ? 1.45 : 0., unit);
-    const dim3 grid((unsigned)(n_dkdv + n_dq)), block(256);
-    if (a.c % BM) hipLaunchKernelGGL((bwd_both_mfma_kernel<true, DP, PART>), grid, block, 0, st, a, n_tiles, kinds);
-    else hipLaunchKernelGGL((bwd_both_mfma_kernel<false, DP, PART>), grid, block, 0, st, a, n_tiles, kinds);
+    if constexpr (DP == 112 || DP == 128) {
+        return launch_bwd_ring(a, &kinds, n_dkdv + n_dq, st);
+    } else {
+        const dim3 grid((unsigned)(n_dkdv + n_dq)), block(256);
+        if (a.c % BM) hipLaunchKernelGGL((bwd_both_mfma_kernel<true, DP, PART>), grid, block, 0, st, a, n_tiles, kinds);
+        else hipLaunchKernelGGL((bwd_both_mfma_kernel<false, DP, PART>), grid, block, 0, st, a, n_tiles, kinds);
+        return hipGetLastError();
+    }
 }
-// Both kinds of workgroups in one launch.  Measured per backward step (d 128, one launch against
-// two, us): uneven work up to one key-owning workgroup per compute unit: 2048 x 2048 triangular,
-// 2 heads 60 / 102, 8 heads 66 / 106, 16 heads (256 workgroups) 92 / 115, 24 heads 137 / 131; 32
-// query heads on 8 key/value heads, 4096 x 4096, 515 / 642.  Even work (a full block) has no
-// tail to fill, only idle compute units: 128 + 128 workgroups 75 / 108, 256 + 256 144 / 133.
-// d 256 (two key-owning workgroups per tile): 256 of them 109 / 189, 512 207 / 225.
+// Both kinds of workgroups in one launch.  Measured per backward step (one launch against two, us; d 128, with this file's
+// kernels): uneven work up to one key-owning workgroup per compute unit: 2048 x 2048 triangular, 2 heads 60 / 102, 8 heads 66 /
+// 106, 16 heads (256 workgroups) 92 / 115, 24 heads 137 / 131; 32 query heads on 8 key/value heads, 4096 x 4096, 515 / 642.  Even
+// work (a full block) has no tail to fill, only idle compute units: 128 + 128 workgroups 75 / 108, 256 + 256 144 / 133.  d 256 (two
+// key-owning workgroups per tile): 256 of them 109 / 189, 512 207 / 225.
+// 65 to 128 columns (bwd_ring.hip, whose query-owning workgroups lose less where one is alone on its compute unit), d 128:
+//  * uneven work, key tiles: 320 (10 heads of 4096) 171 / 199, (20 of 2048) 103 / 113, (5 of 8192) 305 / 370, 294 (3 of 12500) 406 /
+//    534, 384 (12 of 4096) 197 / 209, (48 of 1024) 80 / 85, 403 (31 of 1600) 111 / 107, 512 (16 of 4096) 263 / 248; four query heads to
+//    a key/value head 320 588 / 633, 384 699 / 692;
+//  * a full block, workgroups of both kinds: 320 (10 heads of 2048) 99 / 104, (40 of 512) 40 / 45, 352 (44 of 512) 45.2 / 45.9, 384 (12 of
+//    2048) 110 / 107;
+//  * one device's queries against more shards of keys: its query-owning workgroups, one round at most, walk all of them, and the
+//    others fill the chip meanwhile.  Striped, device 7 of 8: 4 heads of 2048 307 / 375, 16 of 1024 202 / 265, 32 of 1024 (256 and
+//    2048 tiles) 348 / 404, 40 of 1024 449 / 470; 2 of 8192, N 4, 602 / 811; 32 heads on 8 of 1024, N 8, 301 / 326; but 64 of 1024, N 4
+//    (512 query tiles) 393 / 342, 32 of 896, N 16 (3584 key tiles) 860 / 658.  Contiguous, 8 of 2048, N 4, 252 / 281.
 template <int DP>
 bool want_both(const StepArgs& a, int n_tiles) {
     const int64_t keys = (int64_t)n_tiles * a.n_kv * a.B * a.H_kv * halves_of(DP), queries = (int64_t)n_tiles * a.n_q * a.B * a.H;
+    if constexpr (DP == 112 || DP == 128) {
+        if (a.n_kv > a.n_q && queries <= N_CU && keys <= 8 * N_CU) return true;
+        return uneven(a) ? keys <= (a.H < 4 * a.H_kv ? 6 : 5) * N_CU / 4 : keys + queries <= 11 * N_CU / 8;
+    }
     return uneven(a) ? keys <= N_CU * halves_of(DP) : keys + queries <= N_CU;
 }
 template <int DP, bool PART>
 hipError_t launch_bwd_variant(const StepArgs& a, hipStream_t st) {
     const int n_tiles = (a.c + BM - 1) / BM;
-    if (want_both<DP>(a, n_tiles)) {
-        launch_both<DP, PART>(a, st, n_tiles);
-        return hipGetLastError();
-    }
+    if (want_both<DP>(a, n_tiles)) return launch_both<DP, PART>(a, st, n_tiles);
     const bool one_block = a.n_q == 1 && a.n_kv == 1 && !a.fresh;
     const bool full = block_kind(a.q_dev, a.kv_dev, a.layout) == MASK_FULL;
     if (!one_block) launch_dq<WALK_RING, DP, PART>(a, st, n_tiles);
@@ -1142,8 +1127,9 @@ hipError_t launch_bwd_variant(const StepArgs& a, hipStream_t st) {
             return hipGetLastError();
         }
     }
+    if constexpr (DP == 112 || DP == 128) return launch_bwd_ring(a, nullptr, n_tiles * a.n_kv * a.B * a.H_kv, st);
     // query heads that share a key/value head are blocks of one walk
-    if (!one_block || a.H != a.H_kv) launch_dkdv<WALK_RING, DP, PART>(a, st, n_tiles);
+    else if (!one_block || a.H != a.H_kv) launch_dkdv<WALK_RING, DP, PART>(a, st, n_tiles);
     else if (full) launch_dkdv<WALK_FULL, DP, PART>(a, st, n_tiles);
     else if constexpr (DP <= 128) launch_dkdv<WALK_TRI, DP, PART>(a, st, n_tiles);      // above: launch_both or wide
     return hipGetLastError();

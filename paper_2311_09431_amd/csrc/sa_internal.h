@@ -161,6 +161,8 @@ bool fwd_mfma_rope_supported(const StepArgs& a, int dtype);
 hipError_t launch_fwd_mfma(const StepArgs& a, hipStream_t st);
 bool bwd_mfma_supported(const StepArgs& a, int dtype);
 hipError_t launch_bwd_mfma(const StepArgs& a, hipStream_t st);
+// 65 to 128 columns: dK and dV, or (kinds) both kinds of workgroups in one launch
+hipError_t launch_bwd_ring(const StepArgs& a, const BothKinds* kinds, int workgroups, hipStream_t st);
 bool bwd_split_wanted(const StepArgs& a);
 bool dkdv_by_rank(const StepArgs& a);
 hipError_t launch_bwd_split(const StepArgs& a, hipStream_t st);

@@ -48,6 +48,10 @@ def test_a_kernel_that_is_not_there():
     (["v_cvt_pk_bf16_f32 v3, v8, v9"] + OWN, False),
     (["v_cvt_pk_bf16_f32 v8, v3, v9"] + OTHER, False),
     (["v_permlane32_swap_b32_e32 v8, v3"] + OTHER, True),
+    # registers as asm statements print their constants
+    (by_hand("v_accvgpr_write_b32 a[0xa1], v8", MFMA % ("v[16:31]", "v[0:3]", "a[0xa0:0xa3]", "0")), True),
+    (by_hand("v_accvgpr_write_b32 a[63], v8", MFMA % ("v[16:31]", "v[0:3]", "a[60:63]", "0")), True),
+    (by_hand("v_accvgpr_write_b32 a[0xa4], v8", MFMA % ("v[16:31]", "v[0:3]", "a[0xa0:0xa3]", "0")), False),
     (["ds_read_b128 v[0:3], v9", "s_waitcnt lgkmcnt(0)"] + OTHER, False),
     # around a loop and over a branch
     ([".LBB0_1:", "s_nop 0"] + OTHER + ["s_cbranch_scc1 .LBB0_2", "v_mov_b32_e32 v4, v9", "s_branch .LBB0_1", ".LBB0_2:"], False),
