@@ -1067,13 +1067,14 @@ template <int DP, bool PART>
 hipError_t launch_both(const StepArgs& a, hipStream_t st, int n_tiles) {
     const int n_dkdv = n_tiles * a.n_kv * a.B * a.H_kv * halves_of(DP), n_dq = n_tiles * a.n_q * a.B * a.H;
     // (a group's long key walks all at once are no gain: 32 heads on 8 of 4096 rows 486 us, first 501)
-    // (numbers that are no multiple of 8 one by one: 11 heads of 1600 rows, d 136, 92 us, in units of 8 97, 152 heads on 19 of
-    // 1445, d 128, 419 / 448; those that are: see both_kinds)
-    const int unit = n_dkdv % 8 || n_dq % 8 ? 1 : 8;
-    const BothKinds kinds = both_kinds(a, n_dkdv, n_dq, a.H == a.H_kv ? 1.45 : 0., unit);
+    // (numbers that are no multiple of 8 one by one: 11 heads of 1600 rows, d 136, 92 us, in units of 8 97; those that are:
+    // see both_kinds)
+    const double ratio = a.H == a.H_kv ? 1.45 : 0.;
     if constexpr (DP == 112 || DP == 128) {
+        const PlacedKinds kinds = placed_kinds(a, n_dkdv, n_dq, ratio);
         return launch_bwd_ring(a, &kinds, n_dkdv + n_dq, st);
     } else {
+        const BothKinds kinds = both_kinds(a, n_dkdv, n_dq, ratio, n_dkdv % 8 || n_dq % 8 ? 1 : 8);
         const dim3 grid((unsigned)(n_dkdv + n_dq)), block(256);
         if (a.c % BM) hipLaunchKernelGGL((bwd_both_mfma_kernel<true, DP, PART>), grid, block, 0, st, a, n_tiles, kinds);
         else hipLaunchKernelGGL((bwd_both_mfma_kernel<false, DP, PART>), grid, block, 0, st, a, n_tiles, kinds);

@@ -685,16 +685,18 @@ bwd_dkdv_ring_kernel(StepArgs p, int n_tiles) {
 }
 template <int DP, bool PART>
 __global__ void __launch_bounds__(256, 1)
-bwd_both_ring_kernel(StepArgs p, int n_tiles, BothKinds kinds) {
+bwd_both_ring_kernel(StepArgs p, int n_tiles, PlacedKinds kinds) {
     __shared__ __attribute__((aligned(1024))) char lds[SLOTS * SLOT<DP>];
     __shared__ __attribute__((aligned(16))) float stat[STAT_FLOATS];
     int linear = (int)blockIdx.x;
-    if (owns_keys(kinds, linear)) dkdv_ring<DP, PART, false>(p, n_tiles, linear, lds, stat);
+    const int keys = __builtin_amdgcn_readfirstlane(owns_keys(kinds, linear));
+    linear = __builtin_amdgcn_readfirstlane(linear);        // (both kept scalar)
+    if (keys) dkdv_ring<DP, PART, false>(p, n_tiles, linear, lds, stat);
     else dq_ring<DP, PART>(p, n_tiles, linear, lds);
 }
 
 template <int DP, bool PART>
-hipError_t launch(const StepArgs& a, const BothKinds* kinds, int workgroups, hipStream_t st) {
+hipError_t launch(const StepArgs& a, const PlacedKinds* kinds, int workgroups, hipStream_t st) {
     const dim3 grid((unsigned)workgroups), block(256);
     const int n_tiles = (a.c + BM - 1) / BM;
     if (kinds) hipLaunchKernelGGL((bwd_both_ring_kernel<DP, PART>), grid, block, 0, st, a, n_tiles, *kinds);
@@ -704,7 +706,7 @@ hipError_t launch(const StepArgs& a, const BothKinds* kinds, int workgroups, hip
 }
 }  // namespace
 
-hipError_t launch_bwd_ring(const StepArgs& a, const BothKinds* kinds, int workgroups, hipStream_t st) {
+hipError_t launch_bwd_ring(const StepArgs& a, const PlacedKinds* kinds, int workgroups, hipStream_t st) {
     const bool part = a.d % 8 != 0;
     if (a.d <= 112) return part ? launch<112, true>(a, kinds, workgroups, st) : launch<112, false>(a, kinds, workgroups, st);
     return part ? launch<128, true>(a, kinds, workgroups, st) : launch<128, false>(a, kinds, workgroups, st);

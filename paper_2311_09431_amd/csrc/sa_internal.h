@@ -124,6 +124,62 @@ __device__ inline bool owns_keys(const BothKinds& b, int& linear) {
     return keys;
 }
 
+// The same for workgroups that have a compute unit to themselves (bwd_both_ring_kernel).  Consecutive workgroups go to the 8 XCDs
+// in turn and, within one, to its 4 shader engines in turn, whether there is room or not: 32 places.  One of a kind evenly
+// among the others comes back to the same places wherever their numbers are near a simple ratio (every fourth, with three
+// query heads to a key/value head: two XCDs, or in units of 8 one shader engine of each), and the launch waits for
+// those.  So the rarer kind's units go through the columns of rows of 32 places one after the other, as many in each row as
+// its share is.  Backward step, d 128 unless said, us, evenly : so: 72 heads on 24 of 1664 rows (312 key tiles) 350 : 228, 455 on
+// 65 of 512 569 : 212, 4050 on 270 of 128 1143 : 350, 160 on 32 of 1024 252 : 204; numbers that were no such ratio as before (32 on 8
+// of 4096 472 : 467, 16 of 2048 78.4 : 77.0, 10 of 4096 167 : 164).
+// One device's queries against more shards of keys: where their walks (of products, 3 a pair, each shard) outlast the keys' (4 a
+// pair, each head of the group), all of them go first and the short walks behind them fill up.  Last device, its share of a
+// ring, evenly and behind the first third or (contiguous) all of the keys : so: 16 heads of 8 x 1024 201 : 176, 25 of 14 x 505 434 :
+// 176, 8 on 2 of 12 x 3968, d 96, 1660 : 1156, 4 of 8 x 2048 303 : 297, contiguous 8 of 4 x 2048 253 : 215, 4 of 8 x 4096 979 : 826; but 2 of 4 x
+// 8192 607 : 616.
+// Units: 8 where both numbers are multiples (48 heads of 871 rows, d 116, 61.7, one by one 65.9, 16 of 2048 the same), else one by one.
+constexpr int PLACES = 32;
+struct PlacedKinds {
+    int queries_first, keys_first, shift;       // workgroups; log2 of a unit of the rest
+    int keys, total, rows, last;                // of the rest, units; rows of 32 places; key-owning workgroups of the end
+    uint32_t per_row, rarer;                    // units of the rarer kind: in 2^-24 a row, all
+};
+inline PlacedKinds placed_kinds(const StepArgs& a, int64_t n_keys, int64_t n_queries, double ratio) {
+    const bool ahead = a.n_kv > a.n_q && 3 * a.n_kv >= 4 * a.n_q * (a.H / a.H_kv);
+    PlacedKinds k;
+    k.queries_first = ahead ? (int)n_queries : 0;
+    if (ahead) n_queries = 0;
+    const BothKinds b = both_kinds(a, n_keys, n_queries, ratio, n_keys % 8 || n_queries % 8 ? 1 : 8);
+    k.keys_first = ahead ? (int)n_keys : b.first;
+    k.shift = b.unit == 8 ? 3 : 0;
+    k.keys = b.keys; k.total = b.total; k.last = b.last;
+    k.rarer = (uint32_t)(b.keys < b.total - b.keys ? b.keys : b.total - b.keys);
+    k.rows = b.total * b.unit >= PLACES ? b.total * b.unit / PLACES : 1;
+    k.per_row = (uint32_t)(((uint64_t)k.rarer << 24) / k.rows);
+    return k;
+}
+__host__ __device__ inline bool owns_keys(const PlacedKinds& k, int& linear) {
+    if (linear < k.queries_first) return false;
+    linear -= k.queries_first;
+    if (linear < k.keys_first) return true;
+    const int in_rest = linear - k.keys_first, u = in_rest >> k.shift, at = in_rest - (u << k.shift);
+    if (u >= k.total) {
+        const int end = in_rest - (k.total << k.shift);
+        const bool keys = end < k.last;
+        linear = keys ? k.keys_first + (k.keys << k.shift) + end : ((k.total - k.keys) << k.shift) + end - k.last;
+        return keys;
+    }
+    const int to_row = 5 - k.shift, cols = 1 << to_row, row = u >> to_row, col = u & (cols - 1);
+    auto before = [&](int r) -> int { return r >= k.rows ? (int)k.rarer : (int)(((uint64_t)r * k.per_row + (1u << 24) - 1) >> 24); };
+    // the rarer kind's units follow one another through the columns: those of this row are n from column `from` on, around the end
+    const int before_row = before(row), n = before(row + 1) - before_row, from = before_row & (cols - 1);
+    const bool is_rarer = ((col - from) & (cols - 1)) < n, keys = is_rarer == (2 * k.keys <= k.total);
+    const int behind = col - from < 0 ? 0 : col - from < n ? col - from : n, around = from + n - cols;
+    const int rarer = before_row + behind + (around < 0 ? 0 : around < col ? around : col);
+    linear = (keys ? k.keys_first : 0) + ((is_rarer ? rarer : u - rarer) << k.shift) + at;
+    return keys;
+}
+
 // The fp32 instruction's kernels: 128-row workgroups would leave compute units idle, and the streamed rows are split
 // over the wavefronts instead.  In the backward a key-owning workgroup walks the queries of its whole
 // group of heads, so with few key/value heads it is their number that counts.  One step, 32 query
@@ -162,7 +218,7 @@ hipError_t launch_fwd_mfma(const StepArgs& a, hipStream_t st);
 bool bwd_mfma_supported(const StepArgs& a, int dtype);
 hipError_t launch_bwd_mfma(const StepArgs& a, hipStream_t st);
 // 65 to 128 columns: dK and dV, or (kinds) both kinds of workgroups in one launch
-hipError_t launch_bwd_ring(const StepArgs& a, const BothKinds* kinds, int workgroups, hipStream_t st);
+hipError_t launch_bwd_ring(const StepArgs& a, const PlacedKinds* kinds, int workgroups, hipStream_t st);
 bool bwd_split_wanted(const StepArgs& a);
 bool dkdv_by_rank(const StepArgs& a);
 hipError_t launch_bwd_split(const StepArgs& a, hipStream_t st);
