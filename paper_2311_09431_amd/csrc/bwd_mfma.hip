@@ -994,7 +994,7 @@ bwd_both_mfma_kernel(StepArgs p, int n_tiles, BothKinds kinds) {
     __shared__ __attribute__((aligned(16))) float stat[KV_STAT_FLOATS];
     int linear = (int)blockIdx.x;
     if (owns_keys(kinds, linear)) bwd_dkdv<WALK_RING, RAGGED, DP, PART, false>(p, n_tiles, linear, lds0, lds1, lds2, lds3, stat);
-    // (by heads or groups of them, both: 32 heads on 8 of 4096 rows, d 100, by ranks 464 -> 470 us)
+    // (by heads or groups of them, both)
     else bwd_dq<RAGGED, WALK_RING, DP, PART, false>(p, n_tiles, linear, lds0, lds1, lds2, lds3);
 }
 
@@ -1029,6 +1029,37 @@ bool dkdv_by_rank(const StepArgs& a) {
     if (!by_rank(uneven(a), tiles, a.d > 128 ? (ranks <= 4 ? 8 * N_CU : ranks <= 8 ? 6 * N_CU : 6 * N_CU - 1) : a.d > 112 ? MOST_BY_RANK<128, false> : MOST_BY_RANK<64, false>)) return false;
     if (a.n_kv <= a.n_q || a.d <= 32) return true;
     return walk > (a.d > 128 ? 2048 : 2047) || (walk > 512 && tiles <= (a.d <= 112 && a.n_kv <= 2 * a.n_q ? 4 : 3) * N_CU);
+}
+
+// Both kinds of workgroups in one launch.  Measured per backward step, one launch / two, us.  Up to 64 columns and above 128 (this
+// file's kernels; measured at d 128, when they ran there too): uneven work up to one key-owning workgroup per compute unit: 2048 x
+// 2048 triangular, 2 heads 60 / 102, 8 heads 66 / 106, 16 heads (256 workgroups) 92 / 115, 24 heads 137 / 131.  Even work (a full
+// block) has no tail to fill, only idle compute units: 128 + 128 workgroups 75 / 108, 256 + 256 144 / 133.  d 256 (two
+// key-owning workgroups per tile): 256 of them 109 / 189, 512 207 / 225.
+// 65 to 128 columns (bwd_ring.hip, whose query-owning workgroups lose less where one is alone on its compute unit), d 128 and d 100:
+//  * uneven work, key tiles: 192 (16 heads of 1536) 51 / 83, 44 / 78, 256 (16 of 2048) 75 / 104, 67 / 98, (32 on 8 of 4096) 452 / 546,
+//    419 / 525, 294 (3 of 12500) 392 / 525, 364 / 510, 320 (10 of 4096) 170 / 199, 147 / 186, (20 of 2048) 101 / 111, 88 / 104, (5 of 8192) 292 /
+//    361, 270 / 348, 384 (12 of 4096) 191 / 203, 174 / 193, (24 of 2048) 113 / 119, 101 / 109; behind the line 512 (16 of 4096) 263 / 248;
+//    four query heads to a key/value head 320 (10 of 4096) 582 / 622, 539 / 591, behind the line 384 699 / 692;
+//  * of these, walks of many blocks of two or three tiles: two launches again from 257 key tiles on.  The kinds go out evenly (see
+//    launch_both) and the last key walks start late: 987 heads on 141 of 256 rows, d 96, 164 / 144, 1540 on 140 of 235, d 80, 224 /
+//    190, 240 on 80, 2 x 253 rows, d 128, 139 / 123; but one tile, 2264 on 283 of 128 rows, d 100, 167 / 196, four, 455 on 65 of 512 205 /
+//    210, twelve, 152 on 19 of 1445 351 / 410;
+//  * a full block, workgroups of both kinds: 256 (8 heads of 2048) 65 / 99, 59 / 96, 320 (10 of 2048) 93 / 102, 87 / 99, (40 of 512) 38 / 45, 34 / 41,
+//    352 (44 of 512) 43 / 45, 38 / 43; behind the line 384 (12 of 2048) 110 / 107;
+//  * one device's queries against more shards of keys: its query-owning workgroups, one round at most, walk all of them, and the
+//    others fill the chip meanwhile.  Striped, device 7 of 8: 4 heads of 2048 295 / 367, 293 / 361, 16 of 1024 173 / 258, 166 / 248, 32 of
+//    1024 (256 and 2048 tiles) 332 / 393, 297 / 353, 32 on 8 of 1024 285 / 323, 263 / 305; 2 of 8192, N 4, 609 / 805, 592 / 789;
+//    contiguous 8 of 2048, N 4, 208 / 276, 196 / 266, 4 of 4096, N 8, 797 / 1027, 743 / 991; behind the line, with the key walks in front,
+//    64 of 1024, N 4 (512 query tiles) 393 / 342, 32 of 896, N 16 (3584 key tiles) 860 / 658.
+bool bwd_one_launch(const StepArgs& a) {
+    const int n_tiles = (a.c + BM - 1) / BM, halves = a.d > D ? 2 : 1, group = a.H / a.H_kv;
+    const int64_t keys = (int64_t)n_tiles * a.n_kv * a.B * a.H_kv * halves, queries = (int64_t)n_tiles * a.n_q * a.B * a.H;
+    if (a.d <= 64 || a.d > D) return uneven(a) ? keys <= N_CU * halves : keys + queries <= N_CU;
+    if (a.n_kv > a.n_q && queries <= N_CU && keys <= 8 * N_CU) return true;
+    if (!uneven(a)) return keys + queries <= 11 * N_CU / 8;
+    if (keys > N_CU && (n_tiles == 2 || n_tiles == 3) && (int64_t)group * a.n_q > 5) return false;
+    return keys <= (group < 4 ? 6 : 5) * N_CU / 4;
 }
 
 namespace {
@@ -1066,7 +1097,8 @@ void launch_dkdv(const StepArgs& a, hipStream_t st, int n_tiles) {
 template <int DP, bool PART>
 hipError_t launch_both(const StepArgs& a, hipStream_t st, int n_tiles) {
     const int n_dkdv = n_tiles * a.n_kv * a.B * a.H_kv * halves_of(DP), n_dq = n_tiles * a.n_q * a.B * a.H;
-    // (a group's long key walks all at once are no gain: 32 heads on 8 of 4096 rows 486 us, first 501)
+    // (a group's long key walks all at once were no gain with this file's kernels at d 128: 32 heads on 8 of 4096 rows 486 us,
+    // first 501)
     // (numbers that are no multiple of 8 one by one: 11 heads of 1600 rows, d 136, 92 us, in units of 8 97; those that are:
     // see both_kinds)
     const double ratio = a.H == a.H_kv ? 1.45 : 0.;
@@ -1081,34 +1113,10 @@ hipError_t launch_both(const StepArgs& a, hipStream_t st, int n_tiles) {
         return hipGetLastError();
     }
 }
-// Both kinds of workgroups in one launch.  Measured per backward step (one launch against two, us; d 128, with this file's
-// kernels): uneven work up to one key-owning workgroup per compute unit: 2048 x 2048 triangular, 2 heads 60 / 102, 8 heads 66 /
-// 106, 16 heads (256 workgroups) 92 / 115, 24 heads 137 / 131; 32 query heads on 8 key/value heads, 4096 x 4096, 515 / 642.  Even
-// work (a full block) has no tail to fill, only idle compute units: 128 + 128 workgroups 75 / 108, 256 + 256 144 / 133.  d 256 (two
-// key-owning workgroups per tile): 256 of them 109 / 189, 512 207 / 225.
-// 65 to 128 columns (bwd_ring.hip, whose query-owning workgroups lose less where one is alone on its compute unit), d 128:
-//  * uneven work, key tiles: 320 (10 heads of 4096) 171 / 199, (20 of 2048) 103 / 113, (5 of 8192) 305 / 370, 294 (3 of 12500) 406 /
-//    534, 384 (12 of 4096) 197 / 209, (48 of 1024) 80 / 85, 403 (31 of 1600) 111 / 107, 512 (16 of 4096) 263 / 248; four query heads to
-//    a key/value head 320 588 / 633, 384 699 / 692;
-//  * a full block, workgroups of both kinds: 320 (10 heads of 2048) 99 / 104, (40 of 512) 40 / 45, 352 (44 of 512) 45.2 / 45.9, 384 (12 of
-//    2048) 110 / 107;
-//  * one device's queries against more shards of keys: its query-owning workgroups, one round at most, walk all of them, and the
-//    others fill the chip meanwhile.  Striped, device 7 of 8: 4 heads of 2048 307 / 375, 16 of 1024 202 / 265, 32 of 1024 (256 and
-//    2048 tiles) 348 / 404, 40 of 1024 449 / 470; 2 of 8192, N 4, 602 / 811; 32 heads on 8 of 1024, N 8, 301 / 326; but 64 of 1024, N 4
-//    (512 query tiles) 393 / 342, 32 of 896, N 16 (3584 key tiles) 860 / 658.  Contiguous, 8 of 2048, N 4, 252 / 281.
-template <int DP>
-bool want_both(const StepArgs& a, int n_tiles) {
-    const int64_t keys = (int64_t)n_tiles * a.n_kv * a.B * a.H_kv * halves_of(DP), queries = (int64_t)n_tiles * a.n_q * a.B * a.H;
-    if constexpr (DP == 112 || DP == 128) {
-        if (a.n_kv > a.n_q && queries <= N_CU && keys <= 8 * N_CU) return true;
-        return uneven(a) ? keys <= (a.H < 4 * a.H_kv ? 6 : 5) * N_CU / 4 : keys + queries <= 11 * N_CU / 8;
-    }
-    return uneven(a) ? keys <= N_CU * halves_of(DP) : keys + queries <= N_CU;
-}
 template <int DP, bool PART>
 hipError_t launch_bwd_variant(const StepArgs& a, hipStream_t st) {
     const int n_tiles = (a.c + BM - 1) / BM;
-    if (want_both<DP>(a, n_tiles)) return launch_both<DP, PART>(a, st, n_tiles);
+    if (bwd_one_launch(a)) return launch_both<DP, PART>(a, st, n_tiles);
     const bool one_block = a.n_q == 1 && a.n_kv == 1 && !a.fresh;
     const bool full = block_kind(a.q_dev, a.kv_dev, a.layout) == MASK_FULL;
     if (!one_block) launch_dq<WALK_RING, DP, PART>(a, st, n_tiles);

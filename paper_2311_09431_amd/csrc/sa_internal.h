@@ -217,6 +217,8 @@ bool fwd_mfma_rope_supported(const StepArgs& a, int dtype);
 hipError_t launch_fwd_mfma(const StepArgs& a, hipStream_t st);
 bool bwd_mfma_supported(const StepArgs& a, int dtype);
 hipError_t launch_bwd_mfma(const StepArgs& a, hipStream_t st);
+// whether the 128-row kernels' two kinds of workgroups share a launch
+bool bwd_one_launch(const StepArgs& a);
 // 65 to 128 columns: dK and dV, or (kinds) both kinds of workgroups in one launch
 hipError_t launch_bwd_ring(const StepArgs& a, const PlacedKinds* kinds, int workgroups, hipStream_t st);
 bool bwd_split_wanted(const StepArgs& a);

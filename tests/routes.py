@@ -53,6 +53,11 @@ def backward(a, dtype=sa.BF16):
     return "split" if _ask("bwd_split_wanted", a) else "128 rows"
 
 
+def one_launch(a):
+    """Whether both kinds of workgroups of a bf16 backward in 128-row tiles share a launch."""
+    return _ask("bwd_one_launch", a)
+
+
 def keys_by_rank(a):
     """The key-owning workgroups of a bf16 backward in 128-row tiles, by ranks over all heads."""
     return _ask("dkdv_by_rank", a)

@@ -133,3 +133,32 @@ def test_a_split_fp32_launch_holds_fewer_threads_than_hip_takes(backward):
                     assert workgroups * threads < 1 << 32, (d, H, Hkv, N, c)
                     taken.append(workgroups * threads)
     assert max(taken) > 1 << 30         # (it is not that large launches are never taken)
+
+
+def test_backward_in_one_launch_at_its_edges():
+    one = lambda H, c, d=128, Hkv=None, **kw: routes.one_launch(routes.args(c, d, H, Hkv, **kw))     # noqa: E731
+    full = dict(layout=sa.CONTIGUOUS)
+    # key tiles of uneven work; up to 64 columns and above 128 (two workgroups a tile) as many as compute units
+    assert one(12, 4096) and one(32, 1500) and not one(35, 1400) and one(384, 128) and not one(385, 128, 68)
+    assert one(160, 1024, 100, 40) and not one(164, 1024, 100, 41) and one(120, 1000, 112, 40)
+    assert one(256, 128, 64) and not one(257, 128, 64) and one(256, 128, 256) and not one(257, 128, 136)
+    # walks of more than five blocks, each of two or three tiles: up to a key tile per compute unit
+    for c, short in ((128, False), (129, True), (256, True), (384, True), (385, False)):
+        tiles = (c + 127) // 128
+        kv = 257 // tiles + 1
+        assert one(5 * kv, c, 96, kv) and one(6 * kv, c, 96, kv) != short and one(8 * (256 // tiles), c, 96, 256 // tiles)
+        assert one(3 * (kv // 2 + 1), c, 96, kv // 2 + 1, N=2) != short
+    # workgroups of both kinds of a full block
+    assert one(11, 2048, **full) and not one(12, 2048, **full) and one(176, 128, **full) and not one(177, 128, **full)
+    assert one(128, 128, 64, **full) and not one(129, 128, 64, **full)
+
+
+@pytest.mark.parametrize("layout", [sa.STRIPED, sa.CONTIGUOUS])
+def test_backward_of_one_device_in_one_launch_at_its_edges(layout):
+    def one(H, c, N, d=128):
+        a = routes.args(c, d, H, N=N, layout=layout)
+        a.n_q, a.q_dev = 1, N - 1
+        return routes.one_launch(a)
+    # one round of query tiles, eight of key tiles
+    assert one(32, 1024, 8) and not one(33, 1024, 8) and one(128, 256, 8, 100) and not one(128, 256, 9, 100)
+    assert not one(64, 1024, 4) and one(256, 128, 2, 68) and not one(257, 128, 2, 68)
