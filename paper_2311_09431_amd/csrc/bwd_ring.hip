@@ -301,8 +301,9 @@ __device__ __forceinline__ void dkdv_ring(const StepArgs& p, int n_tiles, int li
     };
     auto requested = [&]() {
         slot_byte = (slot_byte + SLOT<DP>) & (SLOTS * SLOT<DP> - 1);
-        at_byte += tile_pitch;
-        if (!next_of(req)) {
+        const bool in_block = next_of(req);
+        at_byte = next_tile_byte(at_byte, tile_pitch, in_block);
+        if (!in_block) {
             if (req.q_head < group) enter_req();
             else Qr[2] = Gr[2] = Sr[2] = 0;         // behind the walk's end: nothing is fetched, zeros go where nobody reads
         }
@@ -590,8 +591,9 @@ __device__ __forceinline__ void dq_ring(const StepArgs& p, int n_tiles, int line
     };
     auto requested = [&]() {
         slot_byte = (slot_byte + SLOT<DP>) & (SLOTS * SLOT<DP> - 1);
-        at_byte += tile_pitch;
-        if (!next_of(req)) {
+        const bool in_block = next_of(req);
+        at_byte = next_tile_byte(at_byte, tile_pitch, in_block);
+        if (!in_block) {
             if (req.kv < kv_end) enter_req();
             else Kr[2] = Vr[2] = 0;
         }

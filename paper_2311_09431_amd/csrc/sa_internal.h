@@ -180,6 +180,12 @@ __host__ __device__ inline bool owns_keys(const PlacedKinds& k, int& linear) {
     return keys;
 }
 
+// Where the next tile to request begins, in bytes: behind the one before, or at 0, where a walk is over and requests fetch
+// nothing.  Counted on they would pass 2^31 at the widest row strides: a negative scalar offset, which the range check
+// of a descriptor is not known to stop (offsets from 0 to 2^31 that lie behind the range, which may be empty, read as zeros:
+// measured, 4 and 16 bytes a lane).
+__host__ __device__ inline int next_tile_byte(int at, int tile_pitch, bool in_block) { return in_block ? at + tile_pitch : 0; }
+
 // The fp32 instruction's kernels: 128-row workgroups would leave compute units idle, and the streamed rows are split
 // over the wavefronts instead.  In the backward a key-owning workgroup walks the queries of its whole
 // group of heads, so with few key/value heads it is their number that counts.  One step, 32 query

@@ -1,14 +1,12 @@
 """Order of a backward launch that holds both kinds of workgroups, one to a compute unit (csrc/sa_internal.h, placed_kinds and
 owns_keys, compiled for the host): every workgroup once, each kind heaviest first, the rarer kind on all 32 places alike."""
 import ctypes
-import os
-import subprocess
 
 import numpy as np
 import pytest
 
 from paper_2311_09431_amd import binding as sa
-from paper_2311_09431_amd import build
+from tests import host_code
 from tests import routes
 
 SOURCE = """
@@ -23,12 +21,7 @@ extern "C" void order(const sa::StepArgs* a, int keys, int queries, double ratio
 
 @pytest.fixture(scope="module")
 def order(tmp_path_factory):
-    at = tmp_path_factory.mktemp("order")
-    (at / "order.hip").write_text(SOURCE)
-    lib = str(at / "order.so")
-    subprocess.run([build._hipcc(), "--cuda-host-only", "-O1", "-std=c++17", "-shared", "-fPIC", "-I" + build.CSRC,
-                    "-I" + os.path.join(build.ROOT, "include"), str(at / "order.hip"), "-o", lib], check=True, capture_output=True)
-    fn = ctypes.CDLL(lib).order
+    fn = host_code.library(tmp_path_factory.mktemp("order"), SOURCE).order
     fn.argtypes = [ctypes.c_void_p, ctypes.c_int, ctypes.c_int, ctypes.c_double] + [ctypes.c_void_p] * 3
     fn.restype = None
 
