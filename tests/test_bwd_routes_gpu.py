@@ -39,7 +39,7 @@ def test_step_against_the_oracle(B, H, Hkv, c, d, q_dev, kv_dev, layout):
     q, g = (inputs.gaussian((B, H, c, d), 60 + c + i, dt) for i in (0, 1))
     k, v = (inputs.gaussian((B, Hkv, c, d), 70 + c + i, dt) for i in (0, 1))
     a, b = np.arange(c)[:, None], np.arange(c)[None, :]
-    allowed = (b <= a - (kv_dev > q_dev)) if layout == sa.STRIPED else np.ones((c, c), bool)
+    allowed = (b <= a - (kv_dev > q_dev)) if layout == sa.STRIPED or q_dev == kv_dev else np.ones((c, c), bool)
     gq, gg, gk, gv = (x.cuda() for x in (q, g, k, v))
     f32 = dict(dtype=torch.float32, device="cuda")
     o, lse, delta = torch.empty(B, H, c, d, **f32), torch.empty(B, H, c, **f32), torch.empty(B, H, c, **f32)
