@@ -32,12 +32,14 @@ from paper_2311_09431_amd import inputs           # noqa: E402
 
 PEAK_BF16_TFLOPS = 2500.0      # MI355X dense bf16 MFMA
 PEAK_HBM_GBS = 8000.0
-# kernels of each family, as rocprofv3 names them
-FAMILIES = {
-    "fwd": ("fwd ring step (fwd_mfma_kernel)", ("fwd_mfma_kernel",)),
-    "bwd": ("bwd ring step (bwd_dq_mfma_kernel + bwd_dkdv_mfma_kernel)",
-            ("bwd_dq_mfma_kernel", "bwd_dkdv_mfma_kernel")),
-}
+def families(w):
+    """Kernels of each family in a workload's steps, as rocprofv3 names them (bf16, 128-row workgroups; those of few row
+    tiles run on others).  dK and dV: by the head dimension."""
+    dkdv = "bwd_dkdv_mfma_kernel" if w["d"] <= 64 else "bwd_dkdv_ring_kernel" if w["d"] <= 128 else "bwd_dkdv_wide_kernel"
+    return {"fwd": ("fwd ring step (fwd_mfma_kernel)", ("fwd_mfma_kernel",)),
+            "bwd": ("bwd ring step (bwd_dq_mfma_kernel + %s)" % dkdv, ("bwd_dq_mfma_kernel", dkdv))}
+
+
 F32_FAMILIES = {"fwd": "fwd ring step (fwd_f32_kernel)", "bwd": "bwd ring step (bwd_f32_kernel)"}
 
 
@@ -46,7 +48,8 @@ def measured_traffic(workload):
     this workload (profiles/ring_step_kernels_<workload>.txt): lines of the form
         TRAFFIC <kernel> read_GB=<x> written_GB=<y>
     written there from the FETCH_SIZE / WRITE_SIZE counter runs.  Returns {kernel: (read, written)};
-    empty when there is no summary for the workload, so a stale figure is never reported."""
+    empty when there is no summary for the workload.  A family is charged only where the summary has all of its present
+    kernels (families), so that no figure of a kernel that no longer runs is reported."""
     path = os.path.join(ROOT, "profiles", "ring_step_kernels_%s.txt" % workload)
     out = {}
     try:
@@ -359,7 +362,7 @@ def main():
     peak, bound = (157.3, "mfma") if f32 else (PEAK_BF16_TFLOPS, "mfma")
 
     def roof(rows, family, alg_bytes):
-        name, kernels = FAMILIES[family]
+        name, kernels = families(w)[family]
         if f32:
             name = F32_FAMILIES[family]
         live = [r for r in rows if r["ms"] > 0]

@@ -4,7 +4,7 @@
 
 Each DIR is the `-d` folder of one rocprofv3 run of `python bench.py ...` made with
 `--output-format csv -o P`:
-  --kt     `--kernel-trace --stats`              (P_kernel_stats.csv)
+  --kt     `--kernel-trace --stats`              (P_kernel_stats.csv, P_kernel_trace.csv)
   --fetch  `--pmc FETCH_SIZE`                     (P_counter_collection.csv)
   --write  `--pmc WRITE_SIZE`
   --sq     `--pmc SQ_... GRBM_GUI_ACTIVE`         (any counters; listed per kernel)
@@ -14,7 +14,7 @@ busy share, instructions per MFMA and (with --sq2) the wait shares of a wavefron
 Prints the per-kernel tables and, when both byte counters are there, one line per library
 kernel that bench.py parses:
     TRAFFIC <kernel> read_GB=<x> written_GB=<y>
-for the triangular-step instantiation of each matrix-core kernel.  FETCH_SIZE / WRITE_SIZE
+for the triangular steps of each matrix-core kernel, or a line that there are none.  FETCH_SIZE / WRITE_SIZE
 are KiB per dispatch; they are scaled by what the same counters read for permute_kernel, a
 plain copy that reads and writes its tensor once (bytes read = bytes written, and WRITE_SIZE
 matches the tensor size on this hardware), so the fetch factor is WRITE(copy) / FETCH(copy).
@@ -50,14 +50,38 @@ def kernel_stats(d, prefix):
     return out
 
 
+# Kernels whose name does not say what they walk; the last forward launch of the pass says it for them (its second template
+# argument: a triangular block, a full one, the blocks of several shards).  A contiguous pass ends with full blocks.
+_EITHER = re.compile(r"\bbwd_(dkdv_ring|both_ring|dkdv_wide)_kernel<")
+_FORWARD = re.compile(r"\bfwd_mfma_kernel<(?:true|false), (\d)\b")
+_OTHERS = {"1": " (contiguous)", "2": " (several blocks)"}
+
+
+def _labelled(rows):
+    """(kernel's short name, row) in the order of the dispatches, without torch's kernels."""
+    walk = "0"
+    for r in sorted(rows, key=lambda r: int(r["Dispatch_Id"])):
+        name = r["Kernel_Name"]
+        if "at::" in name:
+            continue
+        forward = _FORWARD.search(name)
+        walk = forward.group(1) if forward else walk
+        yield _short(name) + (_OTHERS.get(walk, "") if _EITHER.search(name) else ""), r
+
+
 def counters(d, prefix):
     """{kernel: {counter: [values per dispatch]}} without torch's kernels."""
     agg = collections.defaultdict(lambda: collections.defaultdict(list))
-    for r in csv.DictReader(open(_find(d, prefix, "_counter_collection.csv"))):
-        if "at::" in r["Kernel_Name"]:
-            continue
-        agg[_short(r["Kernel_Name"])][r["Counter_Name"]].append(float(r["Counter_Value"]))
+    for k, r in _labelled(csv.DictReader(open(_find(d, prefix, "_counter_collection.csv")))):
+        agg[k][r["Counter_Name"]].append(float(r["Counter_Value"]))
     return agg
+
+
+def average_ns(d, prefix):
+    times = collections.defaultdict(list)
+    for k, r in _labelled(csv.DictReader(open(_find(d, prefix, "_kernel_trace.csv")))):
+        times[k].append(int(r["End_Timestamp"]) - int(r["Start_Timestamp"]))
+    return {k: sum(v) / len(v) for k, v in times.items()}
 
 
 def counter_table(tag, agg):
@@ -69,8 +93,10 @@ def counter_table(tag, agg):
     return out
 
 
-# triangular-step instantiations: fwd / dq <RAGGED=false, WALK=0, ...>, dkdv <WALK=0, RAGGED=false, ...>
-_TRI = {"fwd_mfma_kernel": "<false, 0", "bwd_dq_mfma_kernel": "<false, 0", "bwd_dkdv_mfma_kernel": "<0, false"}
+# triangular-step instantiations: fwd / dq <RAGGED=false, WALK=0, ...>, dkdv <WALK=0, RAGGED=false, ...>; the backward has one of
+# the kernels for dK and dV, by the head dimension
+_TRI = {"fwd_mfma_kernel": "<false, 0", "bwd_dq_mfma_kernel": "<false, 0", "bwd_dkdv_mfma_kernel": "<0, false",
+        "bwd_dkdv_ring_kernel": "<", "bwd_dkdv_wide_kernel": "<"}
 
 
 def traffic_lines(fetch, write):
@@ -84,11 +110,13 @@ def traffic_lines(fetch, write):
                "reads equal its %.4g KiB of writes)" % (factor, w_copy)]
     for kern, inst in _TRI.items():
         for k in fetch:
-            if re.search(r"\b%s%s" % (kern, re.escape(inst)), k) and k in write:
+            if re.search(r"\b%s%s" % (kern, re.escape(inst)), k) and not k.endswith(tuple(_OTHERS.values())) and k in write:
                 rd = mean(fetch, k, "FETCH_SIZE") * factor * 1024 / 1e9
                 wr = mean(write, k, "WRITE_SIZE") * 1024 / 1e9
                 out.append("TRAFFIC %s read_GB=%.3f written_GB=%.3f" % (kern, rd, wr))
                 break
+        else:
+            out.append("(no triangular launches of %s)" % kern)
     return out
 
 
@@ -98,8 +126,7 @@ _XCDS, _SIMDS, _MFMA_FLOP = 8, 1024, 32768
 
 
 def derived_lines(kt_dir, prefix, sq, sq2):
-    avg_ns = {_short(r["Name"]): float(r["AverageNs"]) for r in
-              csv.DictReader(open(_find(kt_dir, prefix, "_kernel_stats.csv")))}
+    avg_ns = average_ns(kt_dir, prefix)
     mean = lambda v, c: sum(v[c]) / len(v[c]) if c in v else None
     out = ["", "derived per matrix-core kernel (kernel-trace average duration; clock = GRBM_GUI_ACTIVE / %d XCDs / "
                "duration; busy = SQ_VALU_MFMA_BUSY_CYCLES / (%d SIMDs x GRBM_GUI_ACTIVE / %d); executed = "
@@ -108,9 +135,9 @@ def derived_lines(kt_dir, prefix, sq, sq2):
         n_mfma, grbm = mean(v, "SQ_INSTS_MFMA"), mean(v, "GRBM_GUI_ACTIVE")
         if not n_mfma or not grbm or k not in avg_ns:
             continue
-        ns = avg_ns[k]
+        ns, of = avg_ns[k], next((x for x in _OTHERS.values() if k.endswith(x)), "")
         line = "DERIVED %-66s avg_ms=%7.3f executed_TFLOPs=%6.0f clock_GHz=%.2f" % (
-            (re.search(r"\w+<[^>]*>", k) or re.search(r".*", k)).group(0)[:66], ns / 1e6, n_mfma * _MFMA_FLOP / ns / 1e3, grbm / _XCDS / ns)
+            (re.search(r"\w+<[^>]*>", k) or re.search(r".*", k)).group(0)[:66 - len(of)] + of, ns / 1e6, n_mfma * _MFMA_FLOP / ns / 1e3, grbm / _XCDS / ns)
         busy, coex = mean(v, "SQ_VALU_MFMA_BUSY_CYCLES"), mean(v, "SQ_VALU_MFMA_COEXEC_CYCLES")
         if busy:
             line += " mfma_busy=%.0f%%" % (100 * busy / (_SIMDS * grbm / _XCDS))

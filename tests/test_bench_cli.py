@@ -41,9 +41,39 @@ def test_traffic_comes_from_the_committed_profile_or_not_at_all():
     sys.path.insert(0, ROOT)
     import bench
     t = bench.measured_traffic("cfg3")
-    # the summary of the default workload names all three matrix-core kernels
-    assert set(t) >= {"fwd_mfma_kernel", "bwd_dq_mfma_kernel", "bwd_dkdv_mfma_kernel"}
+    # the summary of the default workload names all its matrix-core kernels, no other
+    named = {k for _, kernels in bench.families(bench.WORKLOADS["cfg3"]).values() for k in kernels}
+    assert set(t) == named == {"fwd_mfma_kernel", "bwd_dq_mfma_kernel", "bwd_dkdv_ring_kernel"}
     assert all(0 < rd < 100 and 0 < wr < 100 for rd, wr in t.values())
     assert bench.measured_traffic("no-such-workload") == {}
-    for _, kernels in bench.FAMILIES.values():
-        assert all(k in t for k in kernels)
+
+
+def test_the_kernels_named_are_those_the_library_has():
+    # every head dimension's kernel for dK and dV is in the library, for that dimension
+    sys.path.insert(0, ROOT)
+    import bench
+    from paper_2311_09431_amd import build
+    with open(build.LIB, "rb") as f:
+        code = f.read()
+    for w in bench.WORKLOADS.values():
+        if w.get("dtype") == "f32":
+            continue
+        dkdv = bench.families(w)["bwd"][1][1]
+        columns = 64 if w["d"] <= 64 else 112 if w["d"] <= 112 else 128
+        instances = {"bwd_dkdv_ring_kernel": "ILi%d" % columns, "bwd_dkdv_mfma_kernel": "ILi0ELb0ELi%d" % columns, "bwd_dkdv_wide_kernel": "ILb"}
+        assert ("%d%s%s" % (len(dkdv), dkdv, instances[dkdv])).encode() in code, (w["d"], dkdv)
+
+
+def test_launches_are_told_apart_by_the_pass_they_belong_to():
+    from paper_2311_09431_amd import profsum
+    names = ["fwd_mfma_kernel<false, %d, 128, false>" % w for w in (2, 0, 1)]
+    ring, dq = "bwd_dkdv_ring_kernel<128, false, false>", "bwd_dq_mfma_kernel<false, 0, 128>"
+    played = [names[0], ring, names[1], "at::fill", dq, ring, names[1], names[2], ring]
+    rows = [{"Dispatch_Id": str(i), "Kernel_Name": n} for i, n in enumerate(played)]
+    assert [k for k, _ in profsum._labelled(reversed(rows))] == [
+        names[0], ring + " (several blocks)", names[1], dq, ring, names[1], names[2], ring + " (contiguous)"]
+    traffic = {k: {"FETCH_SIZE": [1e6], "WRITE_SIZE": [1e6]} for k, _ in profsum._labelled(rows)}
+    traffic["permute_kernel<int>"] = {"FETCH_SIZE": [1e6], "WRITE_SIZE": [1e6]}
+    lines = profsum.traffic_lines(traffic, traffic)
+    assert [x.split()[1] for x in lines if x.startswith("TRAFFIC")] == ["fwd_mfma_kernel", "bwd_dq_mfma_kernel", "bwd_dkdv_ring_kernel"]
+    assert sum("no triangular launches" in x for x in lines) == 2
