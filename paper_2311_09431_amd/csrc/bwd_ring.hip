@@ -238,7 +238,7 @@ __device__ __forceinline__ void dkdv_ring(const StepArgs& p, int n_tiles, int li
     const int64_t kv_base = b * p.kv_stride_b + kvh * p.kv_stride_h + (dev - p.kv_dev) * p.kv_shard;
     const int d = p.d;
     const int64_t ss = p.kv_stride_s;
-    const int pitch = 2 * (int)p.stride_s, tile_pitch = DT_ROWS * pitch;
+    const int pitch = 2 * (int)p.stride_s;
     const int k0 = ktile * BM, key_own = k0 + 32 * wave + n, key = min(key_own, p.c - 1);
 
     const Rows rows_kv((const __bf16*)p.k + kv_base + (int64_t)key * ss, (const __bf16*)p.v + kv_base + (int64_t)key * ss, h, d);
@@ -262,11 +262,11 @@ __device__ __forceinline__ void dkdv_ring(const StepArgs& p, int n_tiles, int li
     };
     enter_at();
     dt_rsrc Qr, Gr, Sr;
-    int at_byte;                            // of the tile to request, in Q and dO
+    TileByte byte{0, DT_ROWS * pitch};      // of the tile to request, in Q and dO
     auto enter_req = [&]() {
         const int hd = kvh * group + req.q_head;
         req.t = first_tile(req.q_dev);
-        at_byte = req.t * tile_pitch;
+        byte.block(req.t);
         const int64_t base = b * p.stride_b + hd * p.stride_h + (req.q_dev - p.q_dev) * p.q_shard;
         const int64_t sbase = b * p.stat_stride_b + hd * p.stat_stride_h + (int64_t)(req.q_dev - p.q_dev) * p.c;
         Qr = dt_make_rsrc((const __bf16*)p.q + base, p.c, pitch, d);
@@ -296,16 +296,19 @@ __device__ __forceinline__ void dkdv_ring(const StepArgs& p, int n_tiles, int li
     };
     auto request_piece = [&](int j) {
         char* const dst = lds + slot_byte + PIECES * wave * 1024;
-        if (j < PIECES) dt_load_piece(Qr, at_byte, gl[j], dst + j * 1024);
-        else dt_load_piece(Gr, at_byte, gl[j - PIECES], dst + tile_bytes(DP) + (j - PIECES) * 1024);
+        if (j < PIECES) dt_load_piece(Qr, byte.at, gl[j], dst + j * 1024);
+        else dt_load_piece(Gr, byte.at, gl[j - PIECES], dst + tile_bytes(DP) + (j - PIECES) * 1024);
     };
     auto requested = [&]() {
         slot_byte = (slot_byte + SLOT<DP>) & (SLOTS * SLOT<DP> - 1);
-        const bool in_block = next_of(req);
-        at_byte = next_tile_byte(at_byte, tile_pitch, in_block);
-        if (!in_block) {
-            if (req.q_head < group) enter_req();
-            else Qr[2] = Gr[2] = Sr[2] = 0;         // behind the walk's end: nothing is fetched, zeros go where nobody reads
+        byte.next();
+        if (!next_of(req)) {
+            if (req.q_head < group) {
+                enter_req();
+            } else {            // behind the walk's end: nothing is fetched, zeros go where nobody reads
+                Qr[2] = Gr[2] = Sr[2] = 0;
+                byte.stop();
+            }
         }
     };
     auto request = [&]() {
@@ -537,7 +540,7 @@ __device__ __forceinline__ void dq_ring(const StepArgs& p, int n_tiles, int line
     const int64_t sbase = b * p.stat_stride_b + hd * p.stat_stride_h + (int64_t)(dev - p.q_dev) * p.c;
     const int d = p.d;
     const int64_t ss = p.stride_s;
-    const int pitch = 2 * (int)p.kv_stride_s, tile_pitch = DT_ROWS * pitch;
+    const int pitch = 2 * (int)p.kv_stride_s;
     const int q0 = qt * BM, a_own = q0 + 32 * wave + n, a = min(a_own, p.c - 1);
 
     const Rows rows_qg((const __bf16*)p.q + base + (int64_t)a * ss, (const __bf16*)p.dout + base + (int64_t)a * ss, h, d);
@@ -564,11 +567,11 @@ __device__ __forceinline__ void dq_ring(const StepArgs& p, int n_tiles, int line
     };
     enter_at();
     dt_rsrc Kr, Vr;
-    int at_byte;
+    TileByte byte{0, DT_ROWS * pitch};
     auto enter_req = [&]() {
         req.t = 0;
         req.n = tiles_of(req.kv);
-        at_byte = 0;
+        byte.block(0);
         const int64_t from = kv_base + (req.kv - p.kv_dev) * p.kv_shard;
         Kr = dt_make_rsrc((const __bf16*)p.k + from, p.c, pitch, d);
         Vr = dt_make_rsrc((const __bf16*)p.v + from, p.c, pitch, d);
@@ -586,16 +589,19 @@ __device__ __forceinline__ void dq_ring(const StepArgs& p, int n_tiles, int line
     int slot_byte = 0;
     auto request_piece = [&](int j) {
         char* const dst = lds + slot_byte + PIECES * wave * 1024;
-        if (j < PIECES) dt_load_piece(Kr, at_byte, gl[j], dst + j * 1024);
-        else dt_load_piece(Vr, at_byte, gl[j - PIECES], dst + tile_bytes(DP) + (j - PIECES) * 1024);
+        if (j < PIECES) dt_load_piece(Kr, byte.at, gl[j], dst + j * 1024);
+        else dt_load_piece(Vr, byte.at, gl[j - PIECES], dst + tile_bytes(DP) + (j - PIECES) * 1024);
     };
     auto requested = [&]() {
         slot_byte = (slot_byte + SLOT<DP>) & (SLOTS * SLOT<DP> - 1);
-        const bool in_block = next_of(req);
-        at_byte = next_tile_byte(at_byte, tile_pitch, in_block);
-        if (!in_block) {
-            if (req.kv < kv_end) enter_req();
-            else Kr[2] = Vr[2] = 0;
+        byte.next();
+        if (!next_of(req)) {
+            if (req.kv < kv_end) {
+                enter_req();
+            } else {
+                Kr[2] = Vr[2] = 0;
+                byte.stop();
+            }
         }
     };
     auto request = [&]() {

@@ -180,11 +180,17 @@ __host__ __device__ inline bool owns_keys(const PlacedKinds& k, int& linear) {
     return keys;
 }
 
-// Where the next tile to request begins, in bytes: behind the one before, or at 0, where a walk is over and requests fetch
-// nothing.  Counted on they would pass 2^31 at the widest row strides: a negative scalar offset, which the range check
-// of a descriptor is not known to stop (offsets from 0 to 2^31 that lie behind the range, which may be empty, read as zeros:
-// measured, 4 and 16 bytes a lane).
-__host__ __device__ inline int next_tile_byte(int at, int tile_pitch, bool in_block) { return in_block ? at + tile_pitch : 0; }
+// Where the tile to request begins, in bytes.  Behind a walk's end, where requests fetch nothing, it stays: counted on it would
+// pass 2^31 at the widest row strides, a negative scalar offset, which the range check of a descriptor is not known to stop
+// (offsets from 0 to 2^31 behind the range, which may be empty, read as zeros: measured, 4 and 16 bytes a lane).
+// (Set to 0 there instead, the compiler gives every tile a jump or scalar registers it lacks: 32 heads of 32768 rows, d 128, 24460
+// -> 24640 us, 26 of d 100, 8 x 8192 rows, 18570 -> 18965.)
+struct TileByte {
+    int at, pitch;
+    __host__ __device__ void block(int first_tile) { at = first_tile * pitch; }
+    __host__ __device__ void next() { at += pitch; }
+    __host__ __device__ void stop() { pitch = 0; }
+};
 
 // The fp32 instruction's kernels: 128-row workgroups would leave compute units idle, and the streamed rows are split
 // over the wavefronts instead.  In the backward a key-owning workgroup walks the queries of its whole
