@@ -395,7 +395,7 @@ __device__ __forceinline__ void dkdv_step(f32x16& s_cur, f32x16& dp_cur, f32x16&
         lv[i] = *reinterpret_cast<const float2*>(stat_cur + 8 * (i / 2) + 4 * h + 2 * (i % 2));
     };
     // operands requested this many slices ahead of their use: row reads 2, transposed reads 3
-    // (3 / 4 and 4 / 5 measured the same to 1 % at 32768-token shards: LDS latency is covered)
+    // (3 / 4 and 4 / 5 measured the same to 1 % at d 128, when that ran here: LDS latency is covered)
     constexpr int AHEAD = 2, TAHEAD = 3;
 #pragma unroll
     for (int i = 0; i < AHEAD; ++i) {

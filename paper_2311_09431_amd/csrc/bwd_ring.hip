@@ -1,10 +1,11 @@
 // Backward ring step, 65 to 128 columns: kernels whose wavefronts are alone on their SIMD (dK and dV always, dQ where both kinds
 // of workgroups share a launch).
 //
-// A wavefront issues an instruction of any kind every four to five clocks (vector 5, exponential 9, LDS read 4 on the whole
-// compute unit, wait and s_nop 4, dependent scalar 8), a product of 32 x 32 x 16 takes the matrix core 33, and behind a product
-// there is room for about six others.  With all vector work beside the products of the scores and none beside the others, as in
-// bwd_mfma.hip, the first half of a sub-tile takes 760 clocks for 16 products and requests and walk 450 a tile on top.  So here:
+// A wavefront issues an instruction of any kind every four to five clocks (vector 5, exponential 9, wait and s_nop 4, dependent
+// scalar 8; LDS reads share the compute unit: a row read 4, a transposing one 2), a product of 32 x 32 x 16 takes the matrix core
+// 33, and behind a product there is room for about six others.  With all vector work beside the products of the scores and none
+// beside the others, as in bwd_mfma.hip, the first half of a sub-tile takes 760 clocks for 16 products and requests and walk 450
+// a tile on top.  So here:
 //  * behind every product an even share of everything else; half of a sub-tile's exponentials run beside the last products of the
 //    one before it, where its scores are complete;
 //  * Q and dO (K and V) tiles in a ring of four in LDS, one barrier a tile, in the middle of it: a tile is requested two
@@ -12,11 +13,14 @@
 //  * accumulators and the rows that stay (K and V, Q and dO) in accumulation registers by number, so that the vector ones hold
 //    everything else without spills.
 //
-// What bounds them: the matrix cores (16 or 8 + 16 products a sub-tile and its vector work beside them), at long blocks the clock
-// that their power leaves.  d 128, triangular unless said, with bwd_mfma.hip's kernels and with these, us.  dK and dV alone: 32 heads
-// of 640 rows 32.8 / 31.3, 16 of 1536 55.7 / 52.1, one of 16384 427 / 405, 128 of 1024 (full block) 195.7 / 192.7.  Backward step, one
-// launch: 9 heads of 1100 44.5 / 38.5, 6 of 3000 93.6 / 80.3; two: 16 of 1536 56.1 / 54.5, 32 of 4096 523 / 508, (full) 880 / 860,
-// 32 heads on 8 of 4096 499 / 472, 32 of 32768 25720 / 25330.
+// What bounds them: issue and the matrix cores (16 or 8 + 16 products a sub-tile and its vector work beside them), at long blocks the
+// clock that their power leaves.  Long dK/dV walks at d 128: 57 clocks a product, matrix cores 56 % busy at 1.9 GHz; of a wavefront's
+// cycles 15 % in waits and 30 % waiting to issue; LDS busy 36 %.  Backward step, d 128, triangular unless said, with bwd_mfma.hip's
+// kernels (keys up to 256 tiles in one launch) and with these and their launches, us, on one box.  One launch: 9 heads of 1100 44.6 /
+// 38.4, 6 of 3000 92.9 / 78.8, 16 of 1536 54.6 / 51.2, 32 heads on 8 of 4096 489 / 458, 10 of 4096 202 / 161, 3 of 12500 573 / 388; two: 32 of
+// 640 36.7 / 33.7, 32 of 4096 492 / 490, (full) 844 / 827, 128 of 1024 (full) 282 / 275, 32 of 32768 25720 / 24730.  Slower: a device's share
+// of a ring of 128-row shards with few heads, all of whose tiles are masked: 31 heads, 7 shards, d 120, 35.2 / 38.0, 32 on 16, 14, d 96,
+// 53.1 / 56.9.
 //
 // bwd_mfma.hip says what the products are; every sum has the order it has there, so the results have the same bits.
 #include <hip/hip_bf16.h>
