@@ -1097,8 +1097,9 @@ void launch_dkdv(const StepArgs& a, hipStream_t st, int n_tiles) {
 template <int DP, bool PART>
 hipError_t launch_both(const StepArgs& a, hipStream_t st, int n_tiles) {
     const int n_dkdv = n_tiles * a.n_kv * a.B * a.H_kv * halves_of(DP), n_dq = n_tiles * a.n_q * a.B * a.H;
-    // (a group's long key walks all at once were no gain with this file's kernels at d 128: 32 heads on 8 of 4096 rows 486 us,
-    // first 501)
+    // (The ratio, and none for groups: a group's long key walks in front are no gain.  25 calls of 65 to 384 key tiles with
+    // bwd_ring.hip's kernels, at d 128 and d 100, time against these: ratio 1.25 0.98 to 1.02, 1.7 0.97 to 1.03; for groups 0.35
+    // 0.99 to 1.05, 0.5 0.98 to 1.04: 455 heads on 65 of 512 rows 205 / 211 and 214 us, 32 on 8 of 4096 463 / 461 and 456.)
     // (numbers that are no multiple of 8 one by one: 11 heads of 1600 rows, d 136, 92 us, in units of 8 97; those that are:
     // see both_kinds)
     const double ratio = a.H == a.H_kv ? 1.45 : 0.;
