@@ -986,14 +986,16 @@ bwd_dkdv_mfma_kernel(StepArgs p, int n_tiles) {
 // One workgroup per compute unit (the key-owning side's registers).  Up to 64 columns and above 128.
 template <bool RAGGED, int DP, bool PART>
 __global__ void __launch_bounds__(256, 1)
-bwd_both_mfma_kernel(StepArgs p, int n_tiles, BothKinds kinds) {
+bwd_both_mfma_kernel(StepArgs p, int n_tiles, PlacedKinds kinds) {
     __shared__ __attribute__((aligned(1024))) char lds0[tile_bytes(DP) * halves_of(DP)];
     __shared__ __attribute__((aligned(1024))) char lds1[tile_bytes(DP) * halves_of(DP)];
     __shared__ __attribute__((aligned(1024))) char lds2[tile_bytes(DP) * halves_of(DP)];
     __shared__ __attribute__((aligned(1024))) char lds3[tile_bytes(DP) * halves_of(DP)];
     __shared__ __attribute__((aligned(16))) float stat[KV_STAT_FLOATS];
     int linear = (int)blockIdx.x;
-    if (owns_keys(kinds, linear)) bwd_dkdv<WALK_RING, RAGGED, DP, PART, false>(p, n_tiles, linear, lds0, lds1, lds2, lds3, stat);
+    const int keys = __builtin_amdgcn_readfirstlane(owns_keys(kinds, linear));
+    linear = __builtin_amdgcn_readfirstlane(linear);        // (both kept scalar)
+    if (keys) bwd_dkdv<WALK_RING, RAGGED, DP, PART, false>(p, n_tiles, linear, lds0, lds1, lds2, lds3, stat);
     // (by heads or groups of them, both)
     else bwd_dq<RAGGED, WALK_RING, DP, PART, false>(p, n_tiles, linear, lds0, lds1, lds2, lds3);
 }
@@ -1103,11 +1105,10 @@ hipError_t launch_both(const StepArgs& a, hipStream_t st, int n_tiles) {
     // (numbers that are no multiple of 8 one by one: 11 heads of 1600 rows, d 136, 92 us, in units of 8 97; those that are:
     // see both_kinds)
     const double ratio = a.H == a.H_kv ? 1.45 : 0.;
+    const PlacedKinds kinds = placed_kinds(a, n_dkdv, n_dq, ratio);
     if constexpr (DP == 112 || DP == 128) {
-        const PlacedKinds kinds = placed_kinds(a, n_dkdv, n_dq, ratio);
         return launch_bwd_ring(a, &kinds, n_dkdv + n_dq, st);
     } else {
-        const BothKinds kinds = both_kinds(a, n_dkdv, n_dq, ratio, n_dkdv % 8 || n_dq % 8 ? 1 : 8);
         const dim3 grid((unsigned)(n_dkdv + n_dq)), block(256);
         if (a.c % BM) hipLaunchKernelGGL((bwd_both_mfma_kernel<true, DP, PART>), grid, block, 0, st, a, n_tiles, kinds);
         else hipLaunchKernelGGL((bwd_both_mfma_kernel<false, DP, PART>), grid, block, 0, st, a, n_tiles, kinds);

@@ -124,7 +124,7 @@ __device__ inline bool owns_keys(const BothKinds& b, int& linear) {
     return keys;
 }
 
-// The same for workgroups that have a compute unit to themselves (bwd_both_ring_kernel).  Consecutive workgroups go to the 8 XCDs
+// The same for workgroups that have a compute unit to themselves (bwd_both_ring_kernel, bwd_both_mfma_kernel).  Consecutive ones go to the 8 XCDs
 // in turn and, within one, to its 4 shader engines in turn, whether there is room or not: 32 places.  One of a kind evenly
 // among the others comes back to the same places wherever their numbers are near a simple ratio (every fourth, with three
 // query heads to a key/value head: two XCDs, or in units of 8 one shader engine of each), and the launch waits for
@@ -138,14 +138,17 @@ __device__ inline bool owns_keys(const BothKinds& b, int& linear) {
 // 176, 8 on 2 of 12 x 3968, d 96, 1660 : 1156, 4 of 8 x 2048 303 : 297, contiguous 8 of 4 x 2048 253 : 215, 4 of 8 x 4096 979 : 826; but 2 of 4 x
 // 8192 607 : 616.
 // Units: 8 where both numbers are multiples (48 heads of 871 rows, d 116, 61.7, one by one 65.9, 16 of 2048 the same), else one by one.
-constexpr int PLACES = 32;
 struct PlacedKinds {
     int queries_first, keys_first, shift;       // workgroups; log2 of a unit of the rest
-    int keys, total, rows, last;                // of the rest, units; rows of 32 places; key-owning workgroups of the end
+    int keys, total, to_row, rows, last;        // of the rest, units; log2 of a row's, rows; key-owning workgroups of the end
     uint32_t per_row, rarer;                    // units of the rarer kind: in 2^-24 a row, all
 };
+// Up to 64 columns and above 128 (bwd_both_mfma_kernel) only where the rarer kind would be exactly in step, every second, fourth ...
+// workgroup or unit: 855 heads on 57 of 512 rows, d 48, 1406 : 256, 539 on 77 of 350, d 64, 338 : 119, 204 on 68 of 384 84 : 53, 30 on 15 of
+// 1280, d 136, 182 : 141.  Launches whose numbers are no such ratio, and shares, keep to the even order (rows of one place): some
+// gained and some lost by the other (378 heads on 126 of 128 rows, d 136, 72.5 : 78.7, 18 of 219 23.7 : 25.8).
 inline PlacedKinds placed_kinds(const StepArgs& a, int64_t n_keys, int64_t n_queries, double ratio) {
-    const bool ahead = a.n_kv > a.n_q && 3 * a.n_kv >= 4 * a.n_q * (a.H / a.H_kv);
+    const bool ring = a.d > 64 && a.d <= 128, ahead = ring && a.n_kv > a.n_q && 3 * a.n_kv >= 4 * a.n_q * (a.H / a.H_kv);
     PlacedKinds k;
     k.queries_first = ahead ? (int)n_queries : 0;
     if (ahead) n_queries = 0;
@@ -154,7 +157,9 @@ inline PlacedKinds placed_kinds(const StepArgs& a, int64_t n_keys, int64_t n_que
     k.shift = b.unit == 8 ? 3 : 0;
     k.keys = b.keys; k.total = b.total; k.last = b.last;
     k.rarer = (uint32_t)(b.keys < b.total - b.keys ? b.keys : b.total - b.keys);
-    k.rows = b.total * b.unit >= PLACES ? b.total * b.unit / PLACES : 1;
+    const bool in_step = k.rarer && b.total % (int)k.rarer == 0 && b.total / (int)k.rarer % 2 == 0;
+    k.to_row = ring || in_step ? 5 - k.shift : 0;           // 32 places
+    k.rows = b.total >> k.to_row ? b.total >> k.to_row : 1;
     k.per_row = (uint32_t)(((uint64_t)k.rarer << 24) / k.rows);
     return k;
 }
@@ -169,7 +174,7 @@ __host__ __device__ inline bool owns_keys(const PlacedKinds& k, int& linear) {
         linear = keys ? k.keys_first + (k.keys << k.shift) + end : ((k.total - k.keys) << k.shift) + end - k.last;
         return keys;
     }
-    const int to_row = 5 - k.shift, cols = 1 << to_row, row = u >> to_row, col = u & (cols - 1);
+    const int cols = 1 << k.to_row, row = u >> k.to_row, col = u & (cols - 1);
     auto before = [&](int r) -> int { return r >= k.rows ? (int)k.rarer : (int)(((uint64_t)r * k.per_row + (1u << 24) - 1) >> 24); };
     // the rarer kind's units follow one another through the columns: those of this row are n from column `from` on, around the end
     const int before_row = before(row), n = before(row + 1) - before_row, from = before_row & (cols - 1);

@@ -75,6 +75,14 @@ def test_walks_over_several_shards(H, Hkv, N, c, d, dev, one, layout):
         hp.check_grad("dV", dv[:, kvh:kvh + 1].numpy(), want_v.sum(1, keepdims=True), True)
 
 
+@pytest.mark.parametrize("H,Hkv,c,d", [(204, 68, 384, 64), (490, 70, 384, 48), (213, 71, 300, 24), (142, 71, 193, 136)])
+def test_groups_in_step_with_the_places_at_other_columns(H, Hkv, c, d):
+    # (bwd_mfma.hip's launch of both kinds: every fourth, eighth, fourth and, with two workgroups a key tile, second owns keys)
+    a = routes.args(c, d, H, Hkv)
+    assert routes.backward(a) == "128 rows" and routes.one_launch(a)
+    step_against_the_oracle(1, H, Hkv, c, d, 1, 0, sa.STRIPED)
+
+
 @pytest.mark.parametrize("side", ["stride_s", "kv_stride_s"])
 @pytest.mark.parametrize("c,d", [(128, 128), (250, 100)])
 def test_rows_at_the_end_of_reach(c, d, side):

@@ -1,5 +1,6 @@
 """Order of a backward launch that holds both kinds of workgroups, one to a compute unit (csrc/sa_internal.h, placed_kinds and
-owns_keys, compiled for the host): every workgroup once, each kind heaviest first, the rarer kind on all 32 places alike."""
+owns_keys, compiled for the host): every workgroup once, each kind heaviest first, the rarer kind on all 32 places alike, or (up to 64
+columns and above 128, where it is not in step with them) evenly among the others."""
 import ctypes
 
 import numpy as np
@@ -39,9 +40,10 @@ CASES = ([(t, kv * g, kv, 1, layout) for g in (1, 2, 3, 5, 7, 8, 15) for t, kv i
             for layout in (sa.STRIPED, sa.CONTIGUOUS)])
 
 
+@pytest.mark.parametrize("d", [128, 64])
 @pytest.mark.parametrize("tiles,H,Hkv,N,layout", CASES)
-def test_order(order, tiles, H, Hkv, N, layout):
-    a = routes.args(128 * tiles, 128, H, Hkv, N=N, layout=layout)
+def test_order(order, tiles, H, Hkv, N, layout, d):
+    a = routes.args(128 * tiles, d, H, Hkv, N=N, layout=layout)
     a.n_q, a.q_dev = 1, (N - 1 if N > 1 else a.q_dev)
     keys, queries = tiles * N * Hkv, tiles * H
     for ratio in (0., 1.45):
@@ -52,10 +54,24 @@ def test_order(order, tiles, H, Hkv, N, layout):
         unit = 8 if (keys - first[1]) % 8 == 0 and (queries - first[0]) % 8 == 0 else 1
         rest = owns[front:front + (len(owns) - front) // unit * unit]
         rarer = rest if 2 * rest.sum() <= len(rest) else ~rest
-        on = [int(rarer[place::32].sum()) for place in range(min(32, len(rarer)))]
-        assert not on or max(on) - min(on) <= 1, on
+        few, every = int(rarer.sum()) // unit, len(rarer) // unit
+        if d == 128 or (few and every % few == 0 and every // few % 2 == 0):
+            on = [int(rarer[place::32].sum()) for place in range(min(32, len(rarer)))]
+            assert not on or max(on) - min(on) <= 1, on
+        else:           # evenly
+            where = np.flatnonzero(rarer[::unit])
+            assert len(where) < 2 or np.ptp(np.diff(where)) <= 1
         # walks of queries that outlast all of keys lead (products: 3 to 4 a pair)
-        assert first[0] == (queries if N > 1 and 3 * N >= 4 * (H // Hkv) else 0)
+        assert first[0] == (queries if d == 128 and N > 1 and 3 * N >= 4 * (H // Hkv) else 0)
+
+
+@pytest.mark.parametrize("group", [20000, 30000])
+def test_a_large_group_evenly(order, group):
+    # fewer than 2^24 workgroups, of 384 and 500 key/value heads; d 64
+    heads = 384 if group == 30000 else 500
+    a = routes.args(128, 64, heads * group, heads)
+    owns, at, _ = order(a, heads, heads * group + 1, 0.)
+    assert np.array_equal(at[owns], np.arange(heads)) and np.array_equal(at[~owns], np.arange(heads * group + 1))
 
 
 def test_a_large_group(order):
